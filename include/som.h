@@ -235,7 +235,9 @@ typedef struct {
     double sum_dist;   /* sum over presented samples of the distance to the BMU (pre-update weights) */
     double sum_dist2;  /* same with squared distances */
     int64_t m;         /* samples presented */
-    int64_t n_recheck; /* samples whose best two float32 scores were too close and were re-decided exactly */
+    int64_t n_recheck; /* near ties: samples whose best two scores lie inside the rounding band that the
+                        search's arithmetic has for any input (re-decided exactly where the error
+                        bound of the sample at hand leaves the decision open) */
     int32_t n_empty;   /* nodes that were nobody's BMU */
     int32_t n_guarded; /* nodes left unchanged by the denominator threshold */
     float ms_bmu_acc;  /* device time of BMU + accumulation (all chunks), milliseconds */

@@ -122,8 +122,8 @@ int som_create(som_ctx** out, int device, void* hip_stream)
     bool ok = hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->qe, 2 * sizeof(double)) == hipSuccess;
     ok = ok && hipMalloc((void**)&c->small, 64) == hipSuccess;
-    ok = ok && hipMalloc((void**)&c->qe_part, kQeSlots * 2 * sizeof(double)) == hipSuccess;
-    ok = ok && hipMemset(c->qe_part, 0, kQeSlots * 2 * sizeof(double)) == hipSuccess;
+    ok = ok && hipMalloc((void**)&c->qe_part, kQeSlots * 3 * sizeof(double)) == hipSuccess;
+    ok = ok && hipMemset(c->qe_part, 0, kQeSlots * 3 * sizeof(double)) == hipSuccess;
     ok = ok && hipHostMalloc(&c->host_small, 256, hipHostMallocDefault) == hipSuccess;
     for (int i = 0; i < 2 && ok; ++i) {
         ok = ok && hipEventCreateWithFlags(&c->ev_copied[i], hipEventDisableTiming) == hipSuccess;

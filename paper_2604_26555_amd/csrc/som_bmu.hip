@@ -64,6 +64,8 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
+constexpr int kScalLo = 8;        // scal[8], scal[9]: bits of the largest |w - hi|^2 and |w - hi - lo|^2 (split search)
+
 // centre[f] = mean over nodes of W[k][f], f < D; zero up to the next multiple of 64.  Any vector would do (distances do not change when the same vector is
 // taken off samples and weights); the mean keeps |w_k - centre| as small as the spread of the map.
 __global__ void __launch_bounds__(1024) bmu_centre_kernel(const float* __restrict__ W, int K, int D, float* __restrict__ centre,
@@ -73,7 +75,7 @@ __global__ void __launch_bounds__(1024) bmu_centre_kernel(const float* __restric
     const int fl = threadIdx.x & 63, grp = threadIdx.x >> 6;
     const int f = blockIdx.x * 64 + fl;
     // this kernel runs first in every preparation: it also clears the result words (maximum norm, list lengths)
-    if (blockIdx.x == 0 && threadIdx.x < 8) scal[threadIdx.x] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x < 16) scal[threadIdx.x] = 0u;
     double s = 0.0;
     if (f < D) {
         // sixteen loads in flight per thread: the kernel is a chain of memory round trips otherwise
@@ -185,20 +187,35 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
     // squared norm of the centred row exactly as the stage holds it (float32 differences), summed in float64: the
     // first kpad / 4 wavefronts of the grid take four nodes each (coalesced reads of their rows), and a workgroup
     // hands its largest norm to scal[0] with one atomic (one per node, all on the same word, took 10 us)
-    __shared__ float wg_up[4];
+    // (and, for the split search's error bound, the largest norms of what the bf16 cut leaves over: w - hi and w - hi - lo)
+    __shared__ float wg_up[4][3];
     const int wv = e >> 6, lane = e & 63;
-    float up_max = 0.0f;
+    float up_max = 0.0f, lo_max = 0.0f, rest_max = 0.0f;
     if (wv * 4 < kpad) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int k = wv * 4 + q;
             double nrm = 0.0;
+            float lo2 = 0.0f, rest2 = 0.0f;
             if (k < K)
                 for (int f = lane; f < D; f += 64) {
-                    const double v = (double)(W[(size_t)k * D + f] - centre[f]);
+                    const float vf = W[(size_t)k * D + f] - centre[f];
+                    const double v = (double)vf;
                     nrm += v * v;
+                    const float d1 = vf - (float)(__bf16)vf, d2 = d1 - (float)(__bf16)d1;
+                    lo2 = fmaf(d1, d1, lo2);
+                    rest2 = fmaf(d2, d2, rest2);
                 }
             nrm = wave_sum(nrm);
+            if (sp.stage16) {
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) {
+                    lo2 += __shfl_xor(lo2, o);
+                    rest2 += __shfl_xor(rest2, o);
+                }
+                lo_max = fmaxf(lo_max, lo2);
+                rest_max = fmaxf(rest_max, rest2);
+            }
             if (lane == 0 && k < kpad) {
                 const int st = k / kNodesPerStage, r = k % kNodesPerStage;
                 const float nh = (k < K) ? (float)(-0.5 * nrm) : -INFINITY;
@@ -230,11 +247,16 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
             }
         }
     }
-    if (lane == 0) wg_up[threadIdx.x >> 6] = up_max;
+    if (lane == 0) {
+        wg_up[threadIdx.x >> 6][0] = up_max;
+        wg_up[threadIdx.x >> 6][1] = lo_max;
+        wg_up[threadIdx.x >> 6][2] = rest_max;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const float m = fmaxf(fmaxf(wg_up[0], wg_up[1]), fmaxf(wg_up[2], wg_up[3]));
-        if (m > 0.0f) atomicMax(&scal[0], __float_as_uint(m));
+    if (threadIdx.x < 3) {
+        const int t = threadIdx.x;
+        const float m = fmaxf(fmaxf(wg_up[0][t], wg_up[1][t]), fmaxf(wg_up[2][t], wg_up[3][t]));
+        if (m > 0.0f) atomicMax(&scal[t == 0 ? 0 : kScalLo + t - 1], __float_as_uint(m));
     }
 }
 
@@ -251,23 +273,31 @@ __global__ void fill_zero_kernel(uint32_t* p, size_t words)
 // Sum of distances and squared distances of a workgroup's samples -> one of kQeSlots partial-sum slots.  Every
 // wavefront adding to the same two words would serialise tens of thousands of atomics on one address; one pair
 // per workgroup spread over 256 slots does not show in the kernel time.  Called by all threads of the workgroup.
-__device__ __forceinline__ void group_qe_add(double* __restrict__ part, double qs, double qs2)
+// near: the split searches also count this lane's near ties, into kQeSlots further slots (counts are whole numbers: exact).
+__device__ __forceinline__ void group_qe_add(double* __restrict__ part, double qs, double qs2, int near = 0)
 {
     __shared__ double wsum[16][2];
+    __shared__ int wnear[16];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) near += __shfl_xor(near, o);
     qs = wave_sum(qs);
     qs2 = wave_sum(qs2);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) {
         wsum[wave][0] = qs;
         wsum[wave][1] = qs2;
+        wnear[wave] = near;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         double t0 = 0.0, t1 = 0.0;
+        int t2 = 0;
         for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
             t0 += wsum[w][0];
             t1 += wsum[w][1];
+            t2 += wnear[w];
         }
+        if (t2 != 0) unsafeAtomicAdd(&part[2 * kQeSlots + (blockIdx.x & (kQeSlots - 1))], (double)t2);
         if (t0 != 0.0 || t1 != 0.0) {
             const int slot = blockIdx.x & (kQeSlots - 1);
             unsafeAtomicAdd(&part[2 * slot], t0);
@@ -789,6 +819,18 @@ __device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& 
     }
 }
 
+// the same, and what the first parts leave over is added to left2 (squares)
+__device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo, float& left2)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        hi[i] = (__bf16)v[i];
+        const float left = v[i] - (float)hi[i];
+        lo[i] = (__bf16)left;
+        left2 = fmaf(left, left, left2);
+    }
+}
+
 // first feature of slot group q (four consecutive features)
 __device__ __forceinline__ int split_window(int q, int D) { return 4 * q < D - 4 ? 4 * q : D - 4; }
 
@@ -889,6 +931,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     bool valid[MS];
     const float* xrow[MS];
     float xnorm2[MS];       // search: squared norm of the centred sample (both lane halves hold the whole row's)
+    float err_w[MS], err_0[MS];   // search: a score errs by at most err_w |w| + err_0 + kErrNorm |w|^2 / 2 (see below)
     float cut[MS];          // CAND
     CandSet noted[MS];      // CAND
 #pragma unroll
@@ -903,15 +946,22 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         }
         const int64_t row = a.idx ? (int64_t)a.idx[ii] : ii;
         xrow[mb] = a.X + row * a.ldx;
-        float xs = 0.0f;     // this lane's slots, in the order the end of the tile adds them up
+        // squares of this lane's slots: all of them, weighted by how many of the large MFMAs follow (xa), and of what the
+        // first bf16 parts leave over (left2)
+        float xs = 0.0f, xa = 0.0f, left2 = 0.0f;
         if constexpr (TAIL) {
             float vt[4];
             tail_values(xrow[mb], a.D, vt);
             xt[mb] = tail_pack(vt);
+            if constexpr (!CAND) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float xv = g == 0 ? vt[t] : 0.0f;      // the packed block's features once each
-                xs = fmaf(xv, xv, xs);
+                for (int t = 0; t < 4; ++t) {
+                    const float xv = g == 0 ? vt[t] : 0.0f;      // the packed block's features once each
+                    const float left = xv - (float)(__bf16)xv;
+                    xs = fmaf(xv, xv, xs);
+                    left2 = fmaf(left, left, left2);
+                }
+                xa = xs;
             }
         }
         if constexpr (KB > 0) {
@@ -919,12 +969,44 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             centred_slots(xrow[mb], a.D, v);
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
-                split8(v[kb], xh[mb][kb], xl[mb][kb]);
+                if constexpr (CAND) {
+                    split8(v[kb], xh[mb][kb], xl[mb][kb]);
+                } else {
+                    split8(v[kb], xh[mb][kb], xl[mb][kb], left2);
+                    float s8 = 0.0f;
 #pragma unroll
-                for (int t = 0; t < 8; ++t) xs = fmaf(v[kb][t], v[kb][t], xs);
+                    for (int t = 0; t < 8; ++t) s8 = fmaf(v[kb][t], v[kb][t], s8);
+                    constexpr float after = (float)(KB + (TAIL ? 1 : 0));
+                    xs += s8;
+                    xa = fmaf((after - (float)kb) * (after - (float)kb), s8, xa);
+                }
             }
         }
-        xnorm2[mb] = CAND ? 0.0f : xs + __shfl_xor(xs, 32);
+        if constexpr (!CAND) {
+            // The error of a score, in three parts.  (1) What the bf16 cut drops: with x = xh + xl + xr and w likewise,
+            // |xl| |wl| + |xr| |w| + |x| |wr|, where |xr| <= 2^-9 |x - xh| and the largest |w - wh| and |wr| over the nodes come
+            // from the weight preparation: norms that were formed, a fraction of the worst case 3 * 2^-18 |x| |w|.
+            // (2) The pipe's accumulation.  How an MFMA orders and rounds the additions of its sixteen exact products to its
+            // accumulator C is not documented, so each MFMA is charged what seventeen float32 terms can lose when added in
+            // ANY order with one rounding to nearest per addition: 16 * 2^-24 (|C| + sum |products|).  (The largest error seen on
+            // operands built against aligning, truncating and sequential adders stays well inside 16 units:
+            // tests/test_gpu_matrix_pipe.py fails on the first result outside them.)  The small products (lo hi, hi lo) go first,
+            // into accumulators that hold nothing else, so they are charged for their own size; the large ones (hi hi) of block kb
+            // are in the accumulator of the KB - kb (+ 1 with a tail) MFMAs from their own on, which the weighted norm xa adds up.
+            // Half squared norms: in the accumulator of all 3 KB MFMAs, or of the packed block's only.
+            // (3) Six units for the roundings of the two centrings and of -|w|^2 / 2.
+            xs += __shfl_xor(xs, 32);
+            xa += __shfl_xor(xa, 32);
+            left2 += __shfl_xor(left2, 32);
+            const float lo_w = sqrtf(__uint_as_float(a.scal[kScalLo])) * 1.001f, rest_w = sqrtf(__uint_as_float(a.scal[kScalLo + 1])) * 1.001f;
+            const float nx = sqrtf(xs) * 1.0001f, nl = sqrtf(left2) * 1.0001f;
+            constexpr float unit = 5.9604645e-08f;
+            err_w[mb] = nl * (1.0078125f / 512.0f + 32.64f * KB * unit) + sqrtf(xa) * (1.0001f * 16.256f * unit) + nx * (6.0f * unit);
+            err_0[mb] = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (32.64f * KB * unit));
+            xnorm2[mb] = xs;
+        } else {
+            xnorm2[mb] = err_w[mb] = err_0[mb] = 0.0f;
+        }
     }
 
     // running best / runner-up scores of this lane's half of the rows (position in the block in the low four bits
@@ -995,33 +1077,31 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                 c[4 * q + 3] = t.w;
             }
         };
+        // the small products of all blocks first (lo hi, hi lo), then the large ones: what an MFMA can lose goes with what its
+        // accumulator holds
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
+        for (int grp = 0; grp < 3 * KB; ++grp) {
+            const int kb = grp < 2 * KB ? grp >> 1 : grp - 2 * KB;
+            const int term = grp < 2 * KB ? 1 + (grp & 1) : 0;
+            const bf16x8 wa = (term == 2) ? wl[kb] : wh[kb];
 #pragma unroll
-            for (int term = 0; term < 3; ++term) {
-                const int grp = 3 * kb + term;
-                const bf16x8 wa = (term == 2) ? wl[kb] : wh[kb];
+            for (int mb = 0; mb < MS; ++mb) {
+                cur[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, (term == 1) ? xl[mb][kb] : xh[mb][kb],
+                                                                  grp == 0 ? (TAIL ? zero16 : c) : cur[mb], 0, 0, 0);
+                // this MFMA's share of the previous block's fold, fenced so that it stays behind it
+                const int m = grp * MS + mb;
+                const int s0 = m * STEPS_ALL / (GROUPS * MS), s1 = (m + 1) * STEPS_ALL / (GROUPS * MS);
 #pragma unroll
-                for (int mb = 0; mb < MS; ++mb) {
-                    cur[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, (term == 1) ? xl[mb][kb] : xh[mb][kb],
-                                                                      grp == 0 ? (TAIL ? zero16 : c) : cur[mb], 0, 0, 0);
-                    // this MFMA's share of the previous block's fold, fenced so that it stays behind it
-                    const int m = grp * MS + mb;
-                    const int s0 = m * STEPS_ALL / (GROUPS * MS), s1 = (m + 1) * STEPS_ALL / (GROUPS * MS);
-#pragma unroll
-                    for (int sidx = s0; sidx < s1; ++sidx) fold_step(prev, sidx, tile - 1);
-                    if (mb + 1 < MS) __builtin_amdgcn_sched_barrier(0);
-                }
-                // LDS reads of the next block, into the registers this group has just finished with
-                if (more) {
-                    if (grp == 0) next_norms();
-                    if (term == 2) {
-                        wh[kb] = *reinterpret_cast<const bf16x8*>(wnext + kb * 64);
-                        wl[kb] = *reinterpret_cast<const bf16x8*>(wnext + kb * 64 + 16);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
+                for (int sidx = s0; sidx < s1; ++sidx) fold_step(prev, sidx, tile - 1);
+                if (mb + 1 < MS) __builtin_amdgcn_sched_barrier(0);
             }
+            // LDS reads of the next block, into the registers this group has just finished with
+            if (more) {
+                if (grp == 0) next_norms();
+                if (term == 2) wl[kb] = *reinterpret_cast<const bf16x8*>(wnext + kb * 64 + 16);
+                if (term == 0) wh[kb] = *reinterpret_cast<const bf16x8*>(wnext + kb * 64);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (TAIL) {
             constexpr int grp = 3 * KB;
@@ -1191,16 +1271,8 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // ---- join the two half-wavefronts, then lane (j, g) finishes block mp + g
     const float wmax2 = __uint_as_float(a.scal[0]);
     const float wmax = sqrtf(wmax2) * 1.000001f;
-    // Difference of two scores.  Per score: the split leaves 3 * 2^-18 (1 + 2^-7) |x||w|.  Every MFMA adds sixteen
-    // exact products to its accumulator C; how the pipe orders and rounds those additions is not documented, so each
-    // MFMA is charged what seventeen float32 terms can lose when added in ANY order with one rounding to nearest per
-    // addition: 16 * 2^-24 (|C| + sum |products|).  |C| + sum |products| never exceeds |w|^2 / 2 + (|xh| + |xl|)
-    // (|wh| + |wl|) <= 1.016 times the magnitude bound, hence 49 units for each of the 3 KB MFMAs.  (The largest error
-    // seen on operands built against aligning, truncating and sequential adders stays well inside 16 units:
-    // tests/test_gpu_matrix_pipe.py fails on the first result outside them.)  The packed tail block is one MFMA
-    // more.  The position bits take 16 units of the last place; -|w|^2/2 and the two centrings as in the float32 kernel.
-    const float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(49 * KB + (TAIL ? 17 : 0) + 1) * 5.9604645e-08f + 1.9073486e-06f) +
-                      12.0f * 5.9604645e-08f;
+    // |w|^2 / 2 in the accumulators: see (2) at the start of the tile; and six units as for the products
+    constexpr float kErrNorm = ((TAIL ? 16.256f : 48.768f * KB) + 6.0f) * 5.9604645e-08f;
     // (the window offsets are worked out again rather than carried through the stage loop in registers)
     int d_again = a.D;
     asm volatile("" : "+s"(d_again));
@@ -1209,9 +1281,10 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // blob (-|w|^2 / 2 in float32 behind the rows of its stage).
     const bool distances = a.d2 != nullptr || a.qe != nullptr;
     double qs = 0.0, qs2 = 0.0;
+    int near = 0;
 #pragma unroll
     for (int mp = 0; mp < MS; mp += 2) {
-        float r_best = 0.f, r_second = 0.f, r_xn = 0.f, r_part = 0.f, r_wn = 0.f;
+        float r_best = 0.f, r_second = 0.f, r_xn = 0.f, r_part = 0.f, r_wn = 0.f, r_ew = 0.f, r_e0 = 0.f;
         int r_node = 0;
         bool r_valid = false;
 #pragma unroll
@@ -1228,15 +1301,12 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             const float bst = other ? ob : best[mb];
             node = other ? on : node;
             node = node < a.K ? node : a.K - 1;
-            // squared norm of the centred sample and squared distance to the winner by direct differences on the
-            // float32 values, this lane's slots (the row is read again: it is still in the cache; the winner's
-            // centred weights come from the float32 copy of the stage rows, in the same slot order)
-            float xn = 0.f, part = 0.f, wn = 0.f;
-            if (!distances) {
-                xn = xnorm2[mb];
-                const char* blob = reinterpret_cast<const char*>(a.stage16) + (size_t)(node / kNodesPerStage) * STAGE_F4 * 16;
-                wn = -2.0f * reinterpret_cast<const float*>(blob + (size_t)kNodesPerStage * RS)[node % kNodesPerStage];
-            }
+            // the winner's squared norm from the stage blob, and where distances are wanted the squared distance to it by direct
+            // differences on the float32 values, this lane's slots (the row is read again: it is still in the cache; the
+            // winner's centred weights come from the float32 copy of the stage rows, in the same slot order)
+            float part = 0.f;
+            const char* blob = reinterpret_cast<const char*>(a.stage16) + (size_t)(node / kNodesPerStage) * STAGE_F4 * 16;
+            const float wn = -2.0f * reinterpret_cast<const float*>(blob + (size_t)kNodesPerStage * RS)[node % kNodesPerStage];
             if constexpr (TAIL) if (distances) {
                 // the packed block's features once each: lane half 0 takes them (its first slots of wwin hold the weights)
                 float vt[4];
@@ -1247,9 +1317,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                 for (int t = 0; t < 4; ++t) {
                     const float xv = g == 0 ? vt[t] : 0.0f, wv = g == 0 ? w[t] : 0.0f;
                     const float df = xv - wv;
-                    xn = fmaf(xv, xv, xn);
                     part = fmaf(df, df, part);
-                    wn = fmaf(wv, wv, wn);
                 }
             }
             if constexpr (KB > 0) if (distances) {
@@ -1264,22 +1332,18 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
 #pragma unroll
                     for (int t = 0; t < 8; ++t) {
                         const float df = v[kb][t] - w[t];
-                        xn = fmaf(v[kb][t], v[kb][t], xn);
                         part = fmaf(df, df, part);
-                        wn = fmaf(w[t], w[t], wn);
                     }
                 }
             }
-            if (distances) {
-                xn += __shfl_xor(xn, 32);
-                part += __shfl_xor(part, 32);
-                wn += __shfl_xor(wn, 32);
-            }
+            if (distances) part += __shfl_xor(part, 32);
             if (q == g) {
                 r_best = bst;
                 r_second = sec;
                 r_node = node;
-                r_xn = xn;
+                r_xn = xnorm2[mb];
+                r_ew = err_w[mb];
+                r_e0 = err_0[mb];
                 r_part = part;
                 r_wn = wn;
                 r_valid = valid[mb];
@@ -1287,13 +1351,25 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         }
         const int64_t i = wave0 + (mp + g) * 32 + j;
         const float xl2 = sqrtf(r_xn);
-        // The winner's score errs by at most rel / 2 of its own magnitude bound, |x||w_b| + |w_b|^2 / 2 with the
-        // winner's own norm; any other node's by at most rel / 2 of the bound with the largest norm.
+        // The winner's score errs by its own norm's bound.  A node that is in truth as near as the winner lies within the
+        // winner's distance of the sample, so its norm is at most |x| + |x - w_b| (and at most the largest); no other node
+        // can spoil the decision.  The position bits change a score by at most 2^-19 of itself, and a rival's score is
+        // within the bound of the best one.
         const float wb = fminf(sqrtf(r_wn) * 1.00001f, wmax);
-        const float bound = 0.5f * rel * ((xl2 * wb + 0.5f * wb * wb) + (xl2 * wmax + 0.5f * wmax2));
+        const float err_b = r_ew * wb + r_e0 + 0.5f * kErrNorm * wb * wb;
+        const float bits = fabsf(r_best) * (1.01f * 3.8146973e-06f);
+        const float far2 = fmaxf(r_xn * 1.00001f - 2.0f * r_best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
+        const float wo = fminf((xl2 + sqrtf(far2)) * 1.0001f, wmax);
+        const float bound = err_b + r_ew * wo + r_e0 + 0.5f * kErrNorm * wo * wo + bits;
         // (a sample that close to its node is re-decided for the sake of its distance: the centring roundings)
         const float tiny = (xl2 + wmax) * (xl2 + wmax) * 3.8146973e-06f;
         const bool close = r_valid && a.K > 1 && (!((r_best - r_second) > bound) || (distances && r_part < tiny));
+        // The statistic n_recheck counts the near ties: best two scores inside the band that holds for any input, split at
+        // its worst and all MFMAs at the full magnitude.  Only those that this sample's own bound leaves open are listed.
+        constexpr float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(49 * KB + (TAIL ? 17 : 0) + 1) * 5.9604645e-08f + 1.9073486e-06f) +
+                              12.0f * 5.9604645e-08f;
+        const float band = 0.5f * rel * ((xl2 * wb + 0.5f * wb * wb) + (xl2 * wmax + 0.5f * wmax2));
+        near += (close || (r_valid && a.K > 1 && !((r_best - r_second) > band))) ? 1 : 0;
         if (r_valid) {
             a.bmu[i] = r_node;
             if (a.d2) a.d2[i] = r_part;
@@ -1304,7 +1380,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         }
         if (r_valid) a.cut_all[i] = close ? r_best - bound : kNotListed;
     }
-    if (a.qe) group_qe_add(a.qe_part, qs, qs2);
+    if (a.qe) group_qe_add(a.qe_part, qs, qs2, near);
 }
 
 // full tiles for the workgroups below a.full_tiles, half tiles for the last partial round (as bmu_kernel)
@@ -1971,7 +2047,9 @@ __global__ void __launch_bounds__(256) bmu_exact_kernel(const BmuArgs a)
     const unsigned int count = by_cand ? a.scal[a.slot2] : listed;
     const uint32_t* __restrict__ list = by_cand ? a.recheck2 : a.recheck;
     if (blockIdx.x == 0 && tid == 0) {
-        atomicAdd(&a.scal[3], listed);  // running total over the calls that share one weight preparation
+        // running total over the calls that share one weight preparation (the split search for D <= 64 counts its near
+        // ties itself)
+        if (!a.counts_near) atomicAdd(&a.scal[3], listed);
         a.scal[3 - a.slot] = 0u;        // the next call counts into the other slots (1 and 2, 4 and 5)
         a.scal[9 - a.slot2] = 0u;
     }
@@ -2087,29 +2165,35 @@ __global__ void __launch_bounds__(256) bmu_exact_kernel(const BmuArgs a)
     if (a.qe) group_qe_add(a.qe_part, tid < kExactGroup ? qs : 0.0, tid < kExactGroup ? qs2 : 0.0);
 }
 
-// qe[0..1] += the call's partial sums, which are left zero for the next call
-__global__ void __launch_bounds__(kQeSlots) qe_finish_kernel(double* __restrict__ part, double* __restrict__ qe)
+// qe[0..1] += the call's partial sums, scal[3] += its near ties; the slots are left zero for the next call
+__global__ void __launch_bounds__(kQeSlots) qe_finish_kernel(double* __restrict__ part, double* __restrict__ qe,
+                                                             unsigned int* __restrict__ scal)
 {
-    __shared__ double w[kQeSlots / 64][2];
+    __shared__ double w[kQeSlots / 64][3];
     const int tid = threadIdx.x;
-    double s0 = part[2 * tid], s1 = part[2 * tid + 1];
+    double s0 = part[2 * tid], s1 = part[2 * tid + 1], s2 = part[2 * kQeSlots + tid];
     part[2 * tid] = 0.0;
     part[2 * tid + 1] = 0.0;
+    part[2 * kQeSlots + tid] = 0.0;
     s0 = wave_sum(s0);
     s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
     if ((tid & 63) == 0) {
         w[tid >> 6][0] = s0;
         w[tid >> 6][1] = s1;
+        w[tid >> 6][2] = s2;
     }
     __syncthreads();
     if (tid == 0) {
-        double t0 = 0.0, t1 = 0.0;
+        double t0 = 0.0, t1 = 0.0, t2 = 0.0;
         for (int q = 0; q < kQeSlots / 64; ++q) {
             t0 += w[q][0];
             t1 += w[q][1];
+            t2 += w[q][2];
         }
         qe[0] += t0;
         qe[1] += t1;
+        scal[3] += (unsigned int)t2;
     }
 }
 
@@ -2581,6 +2665,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     const bool cand_possible = a.K > 1 && a.K <= 65536 && a.m > (int64_t)kCandMin;
     a.cand_min = cand_possible ? kCandMin : 0xffffffffu;
     a.qe_part = ctx->qe_part;
+    a.counts_near = prep.stage16 && prep.nch == 1;
     // the list length restarts for every call (chunk): calls alternate between two counters, and each call's
     // exact pass clears the counter of the next one
     a.slot = 1 + (prep.calls & 1);
@@ -2629,7 +2714,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
         if ((rc = check_hip(ctx, hipGetLastError(), "bmu exact-pass launch"))) return rc;
     }
     if (a.qe) {
-        hipLaunchKernelGGL(qe_finish_kernel, dim3(1), dim3(kQeSlots), 0, ctx->stream, a.qe_part, a.qe);
+        hipLaunchKernelGGL(qe_finish_kernel, dim3(1), dim3(kQeSlots), 0, ctx->stream, a.qe_part, a.qe, a.scal);
         rc = check_hip(ctx, hipGetLastError(), "quantisation-error reduction launch");
     }
     return rc;

@@ -24,7 +24,8 @@ struct BmuPrep {
     float* wt = nullptr;           // [D][Kpad] transposed weights (as given, not centred)
     float* centre = nullptr;       // [D] column means of W; stage rows and sample registers hold values minus this
     // [0] = bits of max_k |w_k - centre|^2, [1], [2] = recheck-list length (alternating calls), [3] = total,
-    // [4], [5] = length of the second list (samples whose candidate slots overflowed; alternating calls)
+    // [4], [5] = length of the second list (samples whose candidate slots overflowed; alternating calls),
+    // [8], [9] = bits of max_k |w - hi|^2 and |w - hi - lo|^2 (bf16 parts)
     unsigned int* scal = nullptr;
     int kpad = 0, steps = 0, stride = 0;
     int nch = 1;                   // feature chunks of 2 * steps features (1 unless D > 64)
@@ -62,7 +63,8 @@ struct BmuArgs {
     int32_t* bmu;            // [m], always written
     float* d2;               // may be null
     double* qe;              // [2], accumulated (caller zeroes); may be null
-    double* qe_part;         // [kQeSlots][2] partial sums of this call (zero on entry, zeroed again by qe_finish_kernel)
+    double* qe_part;         // [kQeSlots][2] partial sums, then [kQeSlots] near ties (zero on entry, zeroed again by qe_finish_kernel)
+    int32_t counts_near;     // the search counts the near ties itself (n_recheck); otherwise the list's length is counted
 };
 
 constexpr int kQeSlots = 256;
@@ -99,7 +101,7 @@ struct som_ctx {
     int safeguard = 0;             // SOM_SAFEGUARD_*
     int reproducible = 0;          // prefer the fixed-order accumulation kernel
     int search = 0;                // SOM_SEARCH_*
-    double* qe_part = nullptr;     // [kQeSlots][2], zero between calls
+    double* qe_part = nullptr;     // [kQeSlots][2], then [kQeSlots], zero between calls
     void* topo_blob = nullptr;     // node distances, adjacency matrix and lists of the topology rebuild
     size_t topo_bytes = 0;
     // epoch-internal accumulators
