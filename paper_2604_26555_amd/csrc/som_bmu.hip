@@ -39,10 +39,12 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int kWavesPerGroup = 4;
 constexpr int kThreads = kWavesPerGroup * 64;
 
-constexpr uint32_t kCandMin = 6144;             // shortest list the candidate pass serves (about 25 us; the all-nodes pass takes 4.6 ns a sample)
+constexpr uint32_t kCandMin = 8192;             // shortest list the candidate pass serves: its tiles take about 40 us however few they are, the all-nodes
+                                                // pass about 3.5 ns a sample (both at K D = 51200), and up to here that is one sweep of its grid
 constexpr uint32_t kCandHalfTiles = 65536;      // up to this length its tiles are halved (one per compute unit and more)
 constexpr size_t kCandCapMax = (size_t)1 << 24; // longest one (bounds the candidate buffer at 512 MB + 64 MB)
 constexpr int kCandGrid = 2048;
+constexpr int kPairNodes = 65535;               // largest map whose node ids fit the pair list's 16-bit places (0xffff: none)
 
 // floats of one 128-node stage (padded rows + half squared norms), rounded up to one float4 per thread
 constexpr int stage_floats_for(int stride)
@@ -333,12 +335,15 @@ __device__ __forceinline__ void list_push(unsigned int* __restrict__ counter, ui
 // or kNotListed, and this kernel compacts the listed ones: a workgroup takes 4096 samples at a time, counts with a
 // scan, and reserves its entries with one atomic.  The order of the list is immaterial (every entry is decided on its
 // own).
+// A sample whose few candidates the search already knows (kPairs; their ids are in a.pairs) goes on the pair list, which
+// grows down from the end of the same array.
 constexpr float kNotListed = __builtin_nanf("");
+constexpr float kPairs = __builtin_inff();
 constexpr int kListThreads = 1024, kListPerThread = 4;
 
 __global__ void __launch_bounds__(kListThreads) bmu_list_kernel(const BmuArgs a)
 {
-    __shared__ unsigned int wave_base[kListThreads / 64];
+    __shared__ unsigned int wave_base[2][kListThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int64_t per_block = (int64_t)kListThreads * kListPerThread;
     for (int64_t chunk = blockIdx.x; chunk * per_block < a.m; chunk += gridDim.x) {
@@ -355,20 +360,20 @@ __global__ void __launch_bounds__(kListThreads) bmu_list_kernel(const BmuArgs a)
             for (int q = 0; q < kListPerThread; ++q) c[q] = (i0 + q < a.m) ? a.cut_all[i0 + q] : kNotListed;
         }
         static_assert(kListPerThread == 4, "a thread's cuts travel as one float4");
-        unsigned int mine = 0u;
+        unsigned int mine = 0u;                            // entries of the list below, entries of the pair list above bit 16
 #pragma unroll
-        for (int q = 0; q < kListPerThread; ++q) mine += (c[q] == c[q]) ? 1u : 0u;
+        for (int q = 0; q < kListPerThread; ++q) mine += (c[q] == kPairs) ? 0x10000u : (c[q] == c[q]) ? 1u : 0u;
         unsigned int incl = mine;                         // inclusive scan over the wavefront
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             const unsigned int t = __shfl_up(incl, o);
             if (lane >= o) incl += t;
         }
-        if (lane == 63) wave_base[wave] = incl;
+        if (lane == 63) wave_base[0][wave] = incl;
         __syncthreads();
         if (wave == 0) {
             // exclusive scan of the wavefronts' totals; the last lane reserves the workgroup's entries
-            const unsigned int w = lane < kListThreads / 64 ? wave_base[lane] : 0u;
+            const unsigned int w = lane < kListThreads / 64 ? wave_base[0][lane] : 0u;
             unsigned int wi = w;
 #pragma unroll
             for (int o = 1; o < kListThreads / 64; o <<= 1) {
@@ -376,16 +381,26 @@ __global__ void __launch_bounds__(kListThreads) bmu_list_kernel(const BmuArgs a)
                 if (lane >= o) wi += t;
             }
             const unsigned int total = __shfl(wi, kListThreads / 64 - 1);
-            unsigned int base = 0u;
-            if (lane == 0 && total) base = atomicAdd(&a.scal[a.slot], total);
-            base = __shfl(base, 0);
-            if (lane < kListThreads / 64) wave_base[lane] = base + wi - w;
+            // both lists' lengths are neighbours: one atomic reserves the entries of both
+            unsigned long long base = 0ull;
+            if (lane == 0 && total)
+                base = atomicAdd(reinterpret_cast<unsigned long long*>(&a.scal[a.slot]),
+                                 (unsigned long long)(total & 0xffffu) | ((unsigned long long)(total >> 16) << 32));
+            const unsigned int base0 = __shfl((unsigned int)base, 0), base1 = __shfl((unsigned int)(base >> 32), 0);
+            if (lane < kListThreads / 64) {
+                wave_base[0][lane] = base0 + ((wi - w) & 0xffffu);
+                wave_base[1][lane] = base1 + ((wi - w) >> 16);
+            }
         }
         __syncthreads();
-        unsigned int pos = wave_base[wave] + incl - mine;
+        const unsigned int before = incl - mine;
+        unsigned int pos = wave_base[0][wave] + (before & 0xffffu), pos1 = wave_base[1][wave] + (before >> 16);
 #pragma unroll
         for (int q = 0; q < kListPerThread; ++q) {
-            if (c[q] == c[q]) {
+            if (c[q] == kPairs) {
+                a.recheck_end[-1 - (int64_t)pos1] = (uint32_t)(i0 + q);
+                ++pos1;
+            } else if (c[q] == c[q]) {
                 a.recheck[pos] = (uint32_t)(i0 + q);
                 a.cutv[pos] = c[q];
                 ++pos;
@@ -929,9 +944,10 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // ---- this wavefront's samples: centred, cut into bf16 parts, kept in registers
     bf16x8 xh[MS][KBA], xl[MS][KBA], xt[MS];
     bool valid[MS];
-    const float* xrow[MS];
-    float xnorm2[MS];       // search: squared norm of the centred sample (both lane halves hold the whole row's)
-    float err_w[MS], err_0[MS];   // search: a score errs by at most err_w |w| + err_0 + kErrNorm |w|^2 / 2 (see below)
+    // search: squared norm of the centred sample (both lane halves hold the whole row's), err_w and err_0: a score errs by at
+    // most err_w |w| + err_0 + kErrNorm |w|^2 / 2 (see below).  They wait in LDS, behind the stages, for the end of the tile:
+    // the stage loop has no registers to spare for them.
+    float* const stash = reinterpret_cast<float*>(lds4 + 2 * STAGE_F4) + threadIdx.x;
     float cut[MS];          // CAND
     CandSet noted[MS];      // CAND
 #pragma unroll
@@ -945,13 +961,13 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             ii = (int64_t)a.recheck[ii];
         }
         const int64_t row = a.idx ? (int64_t)a.idx[ii] : ii;
-        xrow[mb] = a.X + row * a.ldx;
+        const float* xr = a.X + row * a.ldx;
         // squares of this lane's slots: all of them, weighted by how many of the large MFMAs follow (xa), and of what the
         // first bf16 parts leave over (left2)
         float xs = 0.0f, xa = 0.0f, left2 = 0.0f;
         if constexpr (TAIL) {
             float vt[4];
-            tail_values(xrow[mb], a.D, vt);
+            tail_values(xr, a.D, vt);
             xt[mb] = tail_pack(vt);
             if constexpr (!CAND) {
 #pragma unroll
@@ -966,7 +982,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         }
         if constexpr (KB > 0) {
             float v[KBA][8];
-            centred_slots(xrow[mb], a.D, v);
+            centred_slots(xr, a.D, v);
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
                 if constexpr (CAND) {
@@ -998,47 +1014,63 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             xs += __shfl_xor(xs, 32);
             xa += __shfl_xor(xa, 32);
             left2 += __shfl_xor(left2, 32);
-            const float lo_w = sqrtf(__uint_as_float(a.scal[kScalLo])) * 1.001f, rest_w = sqrtf(__uint_as_float(a.scal[kScalLo + 1])) * 1.001f;
-            const float nx = sqrtf(xs) * 1.0001f, nl = sqrtf(left2) * 1.0001f;
+            const float lo_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.scal[kScalLo])) * 1.001f;
+            const float rest_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.scal[kScalLo + 1])) * 1.001f;
+            const float nx = __builtin_amdgcn_sqrtf(xs) * 1.0001f, nl = __builtin_amdgcn_sqrtf(left2) * 1.0001f;
             constexpr float unit = 5.9604645e-08f;
-            err_w[mb] = nl * (1.0078125f / 512.0f + 32.64f * KB * unit) + sqrtf(xa) * (1.0001f * 16.256f * unit) + nx * (6.0f * unit);
-            err_0[mb] = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (32.64f * KB * unit));
-            xnorm2[mb] = xs;
-        } else {
-            xnorm2[mb] = err_w[mb] = err_0[mb] = 0.0f;
+            stash[(3 * mb + 0) * kThreads] = xs;
+            stash[(3 * mb + 1) * kThreads] = nl * (1.0078125f / 512.0f + 32.64f * KB * unit) + __builtin_amdgcn_sqrtf(xa) * (1.0001f * 16.256f * unit) + nx * (6.0f * unit);
+            stash[(3 * mb + 2) * kThreads] = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (32.64f * KB * unit));
         }
     }
 
-    // running best / runner-up scores of this lane's half of the rows (position in the block in the low four bits
-    // of the score) and the block the best one came from
-    float best[MS], second[MS], before[MS];
-    int tsel[MS];
+    // Running best / runner-up scores (position in the block in the low bits of the score) and the block the best one came
+    // from, for each of four classes of nodes: even and odd rows of the block, even and odd blocks.  Nodes that lie next to
+    // each other on the map, whose scores are the ones that come close, mostly fall into different classes (with the two lane
+    // halves: eight), so that a near tie is mostly one between class winners, whose ids are known at the end of the tile.
+    // Four sets instead of one cost registers, but no more fold instructions than the block numbers' updates.
+    constexpr int CLS = CAND ? 1 : 4;
+    float best[MS][CLS], second[MS][CLS], before[MS][CLS];
+    int tsel[MS][CLS];
 #pragma unroll
     for (int mb = 0; mb < MS; ++mb) {
-        best[mb] = -INFINITY;
-        second[mb] = -INFINITY;
-        before[mb] = -INFINITY;
-        tsel[mb] = 0;
+#pragma unroll
+        for (int c = 0; c < CLS; ++c) {
+            best[mb][c] = -INFINITY;
+            second[mb][c] = -INFINITY;
+            before[mb][c] = -INFINITY;
+            tsel[mb][c] = 0;
+        }
     }
-    // one fold step: scores r0, r0 + 1 of sample block mb of the node block `tile`.  With v1, v2 the two scores (position
-    // in their low bits), the largest of {best, second, v1, v2} is max3(best, v1, v2) and, because second <= best, the
-    // second largest is max(second, med3(best, v1, v2)): five vector instructions per two scores, plus two per block
-    // for the block number
-    auto fold_step = [&](const floatx16 (&acc)[MS], int step, int tile) {
-        const int mb = step >> 3, r0 = 2 * (step & 7);
+    // one fold step: scores r, r + 2 of sample block mb of node block nb of stage st.  With v1, v2 the two scores (position
+    // r / 2 + 8 (nb / 2) of the class in the stage in their low four bits), the largest of {best, second, v1, v2} is
+    // max3(best, v1, v2) and, because second <= best, the second largest is max(second, med3(best, v1, v2)): five vector
+    // instructions per two scores, plus two per stage and class for the stage number.  (The vector port is as busy as the
+    // matrix pipe here: with the class's block number updated per block, two instructions more per block and class, the
+    // kernel took 7 % longer.)
+    auto fold_step = [&](const floatx16 (&acc)[MS], int step, int st, int nb) {
+        const int mb = step >> 3, p = step & 1, r0 = 4 * ((step & 7) >> 1) + p, r1 = r0 + 2;
         if constexpr (CAND) {
             // (the set that the very first block "folds" holds the padding value, which reaches no cut)
+            const int tile = st * (kNodesPerStage / 32) + nb;
             if (acc[mb][r0] >= cut[mb]) noted[mb].note(tile * 32 + 4 * g, 8 * (r0 >> 2) + (r0 & 3));
-            if (acc[mb][r0 + 1] >= cut[mb]) noted[mb].note(tile * 32 + 4 * g, 8 * ((r0 + 1) >> 2) + ((r0 + 1) & 3));
+            if (acc[mb][r1] >= cut[mb]) noted[mb].note(tile * 32 + 4 * g, 8 * (r1 >> 2) + (r1 & 3));
             return;
+        } else {
+            const int c = 2 * (nb & 1) + p, pos = 8 * (nb >> 1);
+            if (nb < 2 && r0 < 2) before[mb][c] = best[mb][c];
+            const float v1 = __uint_as_float((__float_as_uint(acc[mb][r0]) & 0xfffffff0u) | (unsigned)(pos + (r0 >> 1)));
+            const float v2 = __uint_as_float((__float_as_uint(acc[mb][r1]) & 0xfffffff0u) | (unsigned)(pos + (r1 >> 1)));
+            const float mid = __builtin_amdgcn_fmed3f(best[mb][c], v1, v2);
+            best[mb][c] = vmax3(best[mb][c], v1, v2);
+            second[mb][c] = vmax(second[mb][c], mid);
+            if (nb >= 2 && r1 >= 14) tsel[mb][c] = (best[mb][c] > before[mb][c]) ? st : tsel[mb][c];
         }
-        if (r0 == 0) before[mb] = best[mb];
-        const float v1 = __uint_as_float((__float_as_uint(acc[mb][r0]) & 0xfffffff0u) | (unsigned)r0);
-        const float v2 = __uint_as_float((__float_as_uint(acc[mb][r0 + 1]) & 0xfffffff0u) | (unsigned)(r0 + 1));
-        const float mid = __builtin_amdgcn_fmed3f(best[mb], v1, v2);
-        best[mb] = vmax3(best[mb], v1, v2);
-        second[mb] = vmax(second[mb], mid);
-        if (r0 == 14) tsel[mb] = (best[mb] > before[mb]) ? tile : tsel[mb];
+    };
+    // node of a class winner: its stage, its class and the position in its score's low bits
+    auto node_of = [&](float v, int st, int c) {
+        const int pos = (int)(__float_as_uint(v) & 15u), r = 2 * (pos & 7) + (c & 1);
+        return st * kNodesPerStage + 32 * (2 * (pos >> 3) + (c >> 1)) + 8 * (r >> 2) + 4 * g + (r & 3);
     };
 
     // ---- stream the nodes through LDS
@@ -1064,7 +1096,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     constexpr int STEPS_ALL = 8 * MS;          // fold steps (two scores each) per node block
     auto block = [&](floatx16 (&cur)[MS], const floatx16 (&prev)[MS], bf16x8 (&wh)[KBA], bf16x8 (&wl)[KBA], bf16x8& wtl,
-                     floatx16& c, const char* wnext, const float4* nhnext, bool more, int tile) {
+                     floatx16& c, const char* wnext, const float4* nhnext, bool more, int prev_st, int prev_nb) {
         // the norms of the next block replace c once the block's first group has read it
         auto next_norms = [&]() {
             if constexpr (TAIL) return;      // the norms travel inside the packed block
@@ -1092,7 +1124,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                 const int m = grp * MS + mb;
                 const int s0 = m * STEPS_ALL / (GROUPS * MS), s1 = (m + 1) * STEPS_ALL / (GROUPS * MS);
 #pragma unroll
-                for (int sidx = s0; sidx < s1; ++sidx) fold_step(prev, sidx, tile - 1);
+                for (int sidx = s0; sidx < s1; ++sidx) fold_step(prev, sidx, prev_st, prev_nb);
                 if (mb + 1 < MS) __builtin_amdgcn_sched_barrier(0);
             }
             // LDS reads of the next block, into the registers this group has just finished with
@@ -1111,7 +1143,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                 const int m = grp * MS + mb;
                 const int s0 = m * STEPS_ALL / (GROUPS * MS), s1 = (m + 1) * STEPS_ALL / (GROUPS * MS);
 #pragma unroll
-                for (int sidx = s0; sidx < s1; ++sidx) fold_step(prev, sidx, tile - 1);
+                for (int sidx = s0; sidx < s1; ++sidx) fold_step(prev, sidx, prev_st, prev_nb);
                 if (mb + 1 < MS) __builtin_amdgcn_sched_barrier(0);
             }
             if (more) {
@@ -1157,16 +1189,18 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     for (int st = 0; st < nstages; ++st) {
         const int buf = st & 1;
         // (the last iteration reloads its own stage into the idle buffer, which keeps the loop branch-free)
+        // Nine float4 per thread (D > 50) would not leave the registers for the rest: they travel in two batches.
         float4 pre0, pre1, pre2, pre3, pre4, pre5, pre6, pre7, pre8;
         static_assert(PRE <= 9, "stage copy holds at most nine float4 per thread");
-        {
-            const int nxt = (st + 1 < nstages) ? st + 1 : st;
-            const float4* s4 = src4 + (size_t)nxt * STAGE_F4 + tid;
-#define SOM_PRE_LOAD(i) if constexpr (PRE > i) pre##i = s4[i * kThreads];
-            SOM_PRE_LOAD(0) SOM_PRE_LOAD(1) SOM_PRE_LOAD(2) SOM_PRE_LOAD(3) SOM_PRE_LOAD(4)
-            SOM_PRE_LOAD(5) SOM_PRE_LOAD(6) SOM_PRE_LOAD(7) SOM_PRE_LOAD(8)
-#undef SOM_PRE_LOAD
-        }
+        constexpr int FIRST = PRE > 8 ? 5 : PRE;
+        const float4* s4 = src4 + (size_t)((st + 1 < nstages) ? st + 1 : st) * STAGE_F4 + tid;
+        float4* d4 = lds4 + (buf ^ 1) * STAGE_F4 + tid;
+#define SOM_PRE_LOAD(i) if constexpr (PRE > i && i < FIRST) pre##i = s4[i * kThreads];
+#define SOM_PRE_STORE(i) if constexpr (PRE > i && i < FIRST) d4[i * kThreads] = pre##i;
+#define SOM_PRE_LOAD2(i) if constexpr (PRE > i && i >= FIRST) pre##i = s4[i * kThreads];
+#define SOM_PRE_STORE2(i) if constexpr (PRE > i && i >= FIRST) d4[i * kThreads] = pre##i;
+#define SOM_PRE_ALL(op) op(0) op(1) op(2) op(3) op(4) op(5) op(6) op(7) op(8)
+        SOM_PRE_ALL(SOM_PRE_LOAD)
         __builtin_amdgcn_sched_barrier(0);
         const char* wbuf = ldsb + (size_t)buf * STAGE_F4 * 16;
         const char* obuf = ldsb + (size_t)(buf ^ 1) * STAGE_F4 * 16;
@@ -1174,24 +1208,31 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         auto norms_of = [&](const char* base, int nb) {
             return reinterpret_cast<const float4*>(base + kNodesPerStage * RS + nb * 32 * 4) + g;
         };
-        const int tile = st * NB;
-        block(accA, accB, wh, wl, wtl, c, rows_of(wbuf, 1), norms_of(wbuf, 1), true, tile);
-        block(accB, accA, wh, wl, wtl, c, rows_of(wbuf, 2), norms_of(wbuf, 2), true, tile + 1);
-        {
-            float4* d4 = lds4 + (buf ^ 1) * STAGE_F4 + tid;
-#define SOM_PRE_STORE(i) if constexpr (PRE > i) d4[i * kThreads] = pre##i;
-            SOM_PRE_STORE(0) SOM_PRE_STORE(1) SOM_PRE_STORE(2) SOM_PRE_STORE(3) SOM_PRE_STORE(4)
-            SOM_PRE_STORE(5) SOM_PRE_STORE(6) SOM_PRE_STORE(7) SOM_PRE_STORE(8)
-#undef SOM_PRE_STORE
+        block(accA, accB, wh, wl, wtl, c, rows_of(wbuf, 1), norms_of(wbuf, 1), true, st - 1, 3);
+        if constexpr (FIRST < PRE) {
+            SOM_PRE_ALL(SOM_PRE_STORE)
+            SOM_PRE_ALL(SOM_PRE_LOAD2)
+            __builtin_amdgcn_sched_barrier(0);
         }
+        block(accB, accA, wh, wl, wtl, c, rows_of(wbuf, 2), norms_of(wbuf, 2), true, st, 0);
+        if constexpr (FIRST < PRE) {
+            SOM_PRE_ALL(SOM_PRE_STORE2)
+        } else {
+            SOM_PRE_ALL(SOM_PRE_STORE)
+        }
+#undef SOM_PRE_LOAD
+#undef SOM_PRE_STORE
+#undef SOM_PRE_LOAD2
+#undef SOM_PRE_STORE2
+#undef SOM_PRE_ALL
         __builtin_amdgcn_sched_barrier(0);
-        block(accA, accB, wh, wl, wtl, c, rows_of(wbuf, 3), norms_of(wbuf, 3), true, tile + 2);
+        block(accA, accB, wh, wl, wtl, c, rows_of(wbuf, 3), norms_of(wbuf, 3), true, st, 1);
         __syncthreads();
-        block(accB, accA, wh, wl, wtl, c, rows_of(obuf, 0), norms_of(obuf, 0), true, tile + 3);
+        block(accB, accA, wh, wl, wtl, c, rows_of(obuf, 0), norms_of(obuf, 0), true, st, 2);
     }
     // the last block's scores
 #pragma unroll
-    for (int sidx = 0; sidx < STEPS_ALL; ++sidx) fold_step(accB, sidx, nstages * (kNodesPerStage / 32) - 1);
+    for (int sidx = 0; sidx < STEPS_ALL; ++sidx) fold_step(accB, sidx, nstages - 1, 3);
 
     if constexpr (CAND) {
         // Direct float32 differences over the nodes this lane noted for its sample (the true winner is among the two
@@ -1205,7 +1246,9 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             const int n = noted[mb].n;
             const bool over = n >= kCandSlots;
             const int mine = (valid[mb] && !over) ? n : 0;
-            const float* xr = xrow[mb];
+            const int64_t ie = wave0 + mb * 32 + j;
+            const int64_t is = (int64_t)a.recheck[ie < (int64_t)count ? ie : (int64_t)count - 1];
+            const float* xr = a.X + (a.idx ? (int64_t)a.idx[is] : is) * a.ldx;
             const int D = a.D, whole = D / 4, rest = D - 4 * whole;
             float4 xv[16];
 #pragma unroll
@@ -1282,103 +1325,155 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     const bool distances = a.d2 != nullptr || a.qe != nullptr;
     double qs = 0.0, qs2 = 0.0;
     int near = 0;
+    // (square roots here are the hardware's, good to a unit in the last place; the factors behind them cover it)
+    auto root = [](float v) { return __builtin_amdgcn_sqrtf(v); };
+    // Both lane halves join their classes and each other's winners; then half g finishes block mp + g.
 #pragma unroll
     for (int mp = 0; mp < MS; mp += 2) {
-        float r_best = 0.f, r_second = 0.f, r_xn = 0.f, r_part = 0.f, r_wn = 0.f, r_ew = 0.f, r_e0 = 0.f;
+        float r_best = 0.f, r_second = 0.f, r_most = 0.f, r_part = 0.f;
         int r_node = 0;
         bool r_valid = false;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int mb = mp + q;
             if (mb >= MS) break;
-            const int rsel = (int)(__float_as_uint(best[mb]) & 15u);
-            int node = tsel[mb] * 32 + 8 * (rsel >> 2) + 4 * g + (rsel & 3);
-            const float ob = __shfl_xor(best[mb], 32);
-            const float os = __shfl_xor(second[mb], 32);
+            // winner and runner-up over this half's classes (equal scores are a near tie, decided elsewhere: any of them)
+            const float(&b)[CLS] = best[mb];
+            const float m01 = fmaxf(b[0], b[1]), m23 = fmaxf(b[2], b[3]);
+            float bst = fmaxf(m01, m23);
+            float most = fmaxf(fmaxf(second[mb][0], second[mb][1]), fmaxf(second[mb][2], second[mb][3]));
+            float sec = fmaxf(fmaxf(most, fminf(m01, m23)), fmaxf(fminf(b[0], b[1]), fminf(b[2], b[3])));
+            int key = 4 * tsel[mb][0];                                    // stage and class of the winner
+            key = b[1] == bst ? 4 * tsel[mb][1] + 1 : key;
+            key = b[2] == bst ? 4 * tsel[mb][2] + 2 : key;
+            key = b[3] == bst ? 4 * tsel[mb][3] + 3 : key;
+            int node = node_of(bst, key >> 2, key & 3);
+            const float ob = __shfl_xor(bst, 32);
+            const float os = __shfl_xor(sec, 32);
+            const float om = __shfl_xor(most, 32);
             const int on = __shfl_xor(node, 32);
-            const float sec = fmaxf(fmaxf(second[mb], os), fminf(best[mb], ob));
-            const bool other = (ob > best[mb]) || (ob == best[mb] && on < node);
-            const float bst = other ? ob : best[mb];
+            sec = fmaxf(fmaxf(sec, os), fminf(bst, ob));
+            most = fmaxf(most, om);
+            const bool other = (ob > bst) || (ob == bst && on < node);
+            bst = other ? ob : bst;
             node = other ? on : node;
-            node = node < a.K ? node : a.K - 1;
-            // the winner's squared norm from the stage blob, and where distances are wanted the squared distance to it by direct
-            // differences on the float32 values, this lane's slots (the row is read again: it is still in the cache; the
-            // winner's centred weights come from the float32 copy of the stage rows, in the same slot order)
+            node = (node >= 0 && node < a.K) ? node : a.K - 1;            // (only padding or non-finite scores get here)
+            // where distances are wanted the squared distance to the winner by direct differences on the float32 values, this
+            // lane's slots (the row is read again: it is still in the cache; the winner's centred weights come from the
+            // float32 copy of the stage rows, in the same slot order)
             float part = 0.f;
-            const char* blob = reinterpret_cast<const char*>(a.stage16) + (size_t)(node / kNodesPerStage) * STAGE_F4 * 16;
-            const float wn = -2.0f * reinterpret_cast<const float*>(blob + (size_t)kNodesPerStage * RS)[node % kNodesPerStage];
-            if constexpr (TAIL) if (distances) {
-                // the packed block's features once each: lane half 0 takes them (its first slots of wwin hold the weights)
-                float vt[4];
-                tail_values(xrow[mb], d_again, vt);
-                const float4 w0 = *reinterpret_cast<const float4*>(a.wwin + (size_t)node * WROW + KB * 16);
-                const float w[4] = {w0.x, w0.y, w0.z, w0.w};
+            if (distances) {
+                int64_t ii = wave0 + mb * 32 + j;
+                ii = ii < a.m ? ii : a.m - 1;
+                const float* xr = a.X + (a.idx ? (int64_t)a.idx[ii] : ii) * a.ldx;
+                if constexpr (TAIL) {
+                    // the packed block's features once each: lane half 0 takes them (its first slots of wwin hold the weights)
+                    float vt[4];
+                    tail_values(xr, d_again, vt);
+                    const float4 w0 = *reinterpret_cast<const float4*>(a.wwin + (size_t)node * WROW + KB * 16);
+                    const float w[4] = {w0.x, w0.y, w0.z, w0.w};
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float xv = g == 0 ? vt[t] : 0.0f, wv = g == 0 ? w[t] : 0.0f;
-                    const float df = xv - wv;
-                    part = fmaf(df, df, part);
-                }
-            }
-            if constexpr (KB > 0) if (distances) {
-                float v[KBA][8];
-                centred_slots(xrow[mb], d_again, v);
-                const float* wr = a.wwin + (size_t)node * WROW + g * 8;
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb) {
-                    const float4 w0 = *reinterpret_cast<const float4*>(wr + kb * 16);
-                    const float4 w1 = *reinterpret_cast<const float4*>(wr + kb * 16 + 4);
-                    const float w[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) {
-                        const float df = v[kb][t] - w[t];
+                    for (int t = 0; t < 4; ++t) {
+                        const float df = g == 0 ? vt[t] - w[t] : 0.0f;
                         part = fmaf(df, df, part);
                     }
                 }
+                if constexpr (KB > 0) {
+                    float v[KBA][8];
+                    centred_slots(xr, d_again, v);
+                    const float* wr = a.wwin + (size_t)node * WROW + g * 8;
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb) {
+                        const float4 w0 = *reinterpret_cast<const float4*>(wr + kb * 16);
+                        const float4 w1 = *reinterpret_cast<const float4*>(wr + kb * 16 + 4);
+                        const float w[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) {
+                            const float df = v[kb][t] - w[t];
+                            part = fmaf(df, df, part);
+                        }
+                    }
+                }
+                part += __shfl_xor(part, 32);
             }
-            if (distances) part += __shfl_xor(part, 32);
             if (q == g) {
                 r_best = bst;
                 r_second = sec;
+                r_most = most;
                 r_node = node;
-                r_xn = xnorm2[mb];
-                r_ew = err_w[mb];
-                r_e0 = err_0[mb];
                 r_part = part;
-                r_wn = wn;
                 r_valid = valid[mb];
             }
         }
         const int64_t i = wave0 + (mp + g) * 32 + j;
-        const float xl2 = sqrtf(r_xn);
+        // the sample's figures from the start of the tile, and the winner's squared norm from the stage blob
+        const int own = MS > 1 ? mp + g : 0;
+        const float xnorm2 = stash[(3 * own + 0) * kThreads], err_w = stash[(3 * own + 1) * kThreads], err_0 = stash[(3 * own + 2) * kThreads];
+        const char* blob = reinterpret_cast<const char*>(a.stage16) + (size_t)(r_node / kNodesPerStage) * STAGE_F4 * 16;
+        const float wn = -2.0f * reinterpret_cast<const float*>(blob + (size_t)kNodesPerStage * RS)[r_node % kNodesPerStage];
+        const float xl2 = root(xnorm2);
         // The winner's score errs by its own norm's bound.  A node that is in truth as near as the winner lies within the
         // winner's distance of the sample, so its norm is at most |x| + |x - w_b| (and at most the largest); no other node
         // can spoil the decision.  The position bits change a score by at most 2^-19 of itself, and a rival's score is
         // within the bound of the best one.
-        const float wb = fminf(sqrtf(r_wn) * 1.00001f, wmax);
-        const float err_b = r_ew * wb + r_e0 + 0.5f * kErrNorm * wb * wb;
+        const float wb = fminf(root(wn) * 1.00001f, wmax);
+        const float err_b = err_w * wb + err_0 + 0.5f * kErrNorm * wb * wb;
         const float bits = fabsf(r_best) * (1.01f * 3.8146973e-06f);
-        const float far2 = fmaxf(r_xn * 1.00001f - 2.0f * r_best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
-        const float wo = fminf((xl2 + sqrtf(far2)) * 1.0001f, wmax);
-        const float bound = err_b + r_ew * wo + r_e0 + 0.5f * kErrNorm * wo * wo + bits;
+        const float far2 = fmaxf(xnorm2 * 1.00001f - 2.0f * r_best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
+        const float wo = fminf((xl2 + root(far2)) * 1.0001f, wmax);
+        const float bound = err_b + err_w * wo + err_0 + 0.5f * kErrNorm * wo * wo + bits;
         // (a sample that close to its node is re-decided for the sake of its distance: the centring roundings)
         const float tiny = (xl2 + wmax) * (xl2 + wmax) * 3.8146973e-06f;
         const bool close = r_valid && a.K > 1 && (!((r_best - r_second) > bound) || (distances && r_part < tiny));
-        // The statistic n_recheck counts the near ties: best two scores inside the band that holds for any input, split at
-        // its worst and all MFMAs at the full magnitude.  Only those that this sample's own bound leaves open are listed.
-        constexpr float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(49 * KB + (TAIL ? 17 : 0) + 1) * 5.9604645e-08f + 1.9073486e-06f) +
-                              12.0f * 5.9604645e-08f;
-        const float band = 0.5f * rel * ((xl2 * wb + 0.5f * wb * wb) + (xl2 * wmax + 0.5f * wmax2));
-        near += (close || (r_valid && a.K > 1 && !((r_best - r_second) > band))) ? 1 : 0;
+        // Candidates: the class winners that reach the cut, two ids of each half at most; complete when no class's runner-up
+        // reaches it.  Otherwise (or with 16-bit ids not enough) the sample goes on the list of the candidate pass.
+        const float cut_at = r_best - bound;
+        bool open = !(r_most < cut_at) || a.K > kPairNodes;
+        if (__ballot(close) != 0ull) {
+            const float cut_other = __shfl_xor(cut_at, 32);
+            const bool want = close && !open;
+            const bool want_other = __shfl_xor(want ? 1 : 0, 32) != 0;
+            bool many[2] = {false, false};
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int mb = mp + q;
+                if (mb >= MS) break;
+                const float cut_mb = q == g ? cut_at : cut_other;
+                unsigned int packed = 0xffffffffu;
+                int hits = 0;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const unsigned id = (unsigned)node_of(best[mb][c], tsel[mb][c], c);
+                    const bool hit = best[mb][c] >= cut_mb;
+                    packed = hit ? (packed << 16) | id : packed;
+                    hits += hit ? 1 : 0;
+                }
+                many[q] = hits > 2;
+                if (q == g ? want : want_other) a.pairs[2 * (wave0 + mb * 32 + j) + g] = packed;
+            }
+            // (too many in the other half: it says so to the half that finishes this block)
+            const bool mine_many = g == 0 ? many[0] : many[1], others_many = g == 0 ? many[1] : many[0];
+            const int told = __shfl_xor(others_many ? 1 : 0, 32);
+            open = open || mine_many || told != 0;
+        }
         if (r_valid) {
+            if (a.qe) {
+                // The statistic n_recheck counts the near ties: best two scores inside the band that holds for any input, split
+                // at its worst and all MFMAs at the full magnitude.  Only those that this sample's own bound leaves open are
+                // listed.
+                constexpr float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(49 * KB + (TAIL ? 17 : 0) + 1) * 5.9604645e-08f + 1.9073486e-06f) +
+                                      12.0f * 5.9604645e-08f;
+                const float band = 0.5f * rel * ((xl2 * wb + 0.5f * wb * wb) + (xl2 * wmax + 0.5f * wmax2));
+                near += (close || (a.K > 1 && !((r_best - r_second) > band))) ? 1 : 0;
+                if (!close) {
+                    qs += sqrt((double)r_part);
+                    qs2 += (double)r_part;
+                }
+            }
             a.bmu[i] = r_node;
             if (a.d2) a.d2[i] = r_part;
-            if (!close) {
-                qs += sqrt((double)r_part);
-                qs2 += (double)r_part;
-            }
+            a.cut_all[i] = !close ? kNotListed : open ? cut_at : kPairs;
         }
-        if (r_valid) a.cut_all[i] = close ? r_best - bound : kNotListed;
     }
     if (a.qe) group_qe_add(a.qe_part, qs, qs2, near);
 }
@@ -1937,7 +2032,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
 // measured with every sample listed).  Larger groups or prefetched weights were measured and change nothing.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kExactGroup = 8;
-constexpr int kExactNodesPerThread = 4;
+constexpr int kExactNodesPerThread = 2;
+constexpr int kExactThreads = 512;         // K = 1024 in one sweep; 256 threads of four nodes each took 25 us for any short list (a chain
+                                           // of thirteen batches of loads with little to hide them), these take 14
 
 // ---------------------------------------------------------------------------------------------------------
 // Direct differences over the nodes the candidate pass noted (the true winner is among them: its score lies
@@ -2032,11 +2129,169 @@ __global__ void __launch_bounds__(256) bmu_cand_exact_kernel(const BmuArgs a)
     if (a.qe) group_qe_add(a.qe_part, qs, qs2);
 }
 
-__global__ void __launch_bounds__(256) bmu_exact_kernel(const BmuArgs a)
+// ---------------------------------------------------------------------------------------------------------
+// The pair list: samples whose candidates (at most four, two of each lane half) the split search already knows (D <= 64).
+// A workgroup takes 64 entries at a time: sixteen lanes fetch a row in one coalesced load (the samples' rows and two
+// candidates' at once), the rows meet in LDS, and one lane per candidate adds its squared
+// differences up, features in order as the other re-decisions do; lowest distance, then lowest node index.
+// Bound by LDS and the gathered rows: about 0.03 ns an entry, against 0.3 ns (K D = 51200) in the candidate pass, which
+// searches all nodes again.
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kPairGroup = 64;
+constexpr int kPairStride = 17;               // float4 of a row in LDS: odd, so that the lanes' 16-byte reads fall into distinct banks
+
+__device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__ rows, double& qs, double& qs2)
 {
-    __shared__ float4 xs4[64][kExactGroup / 4];   // [feature within a 64-wide slab][sample]
-    __shared__ float red_d[4][kExactGroup];
-    __shared__ int red_k[4][kExactGroup];
+    constexpr int kRowsAtOnce = kExactThreads / 16, PER = kPairGroup / kRowsAtOnce;      // entries per sixteen lanes
+    __shared__ uint2 entry_ids[kPairGroup];
+    __shared__ uint32_t entry_at[kPairGroup];
+    const unsigned int count = a.scal[a.slot + 1];
+    const int tid = threadIdx.x, sub = tid & 15, grp = tid >> 4;
+    const int D = a.D, whole = D / 4, rest = D - 4 * whole;
+    const int start = 4 * sub < D - 4 ? 4 * sub : D - 4;           // window inside the row
+    const bool fetch = 4 * sub < D;
+    // place t of an entry's candidates, the used ones in front (an unused half-place is 0xffff); -1: none
+    auto id_of = [&](const uint2& both, int t) {
+        const int n0 = (both.x == 0xffffffffu) ? 0 : (both.x >> 16) == 0xffffu ? 1 : 2;
+        const int n1 = (both.y == 0xffffffffu) ? 0 : (both.y >> 16) == 0xffffu ? 1 : 2;
+        if (t >= n0 + n1) return -1;
+        const int u = t < n0 ? t : t - n0;
+        const int id = (int)(((t < n0 ? both.x : both.y) >> (16 * u)) & 0xffffu);
+        return id < a.K ? id : -1;
+    };
+    // The chain list entry -> ids and row number -> rows is three dependent trips to memory: the sample positions are read two
+    // rounds ahead and the ids and row numbers one, so that a round waits for its rows only.
+    uint32_t at[PER], at_next[PER], row[PER], row_next[PER];
+    uint2 ids[PER], ids_next[PER];
+    auto position = [&](unsigned int p, int u) {
+        const unsigned int q = p + kRowsAtOnce * u + grp;
+        return a.recheck_end[-1 - (int64_t)(q < count ? q : count - 1)];
+    };
+    const unsigned int step = gridDim.x * kPairGroup, first = blockIdx.x * kPairGroup;
+    if (first >= count) return;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        at[u] = position(first, u);
+        at_next[u] = position(first + step < count ? first + step : first, u);
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        ids[u] = *reinterpret_cast<const uint2*>(a.pairs + 2 * (int64_t)at[u]);
+        row[u] = a.idx ? a.idx[at[u]] : at[u];
+    }
+    for (unsigned int p0 = first; p0 < count; p0 += step) {
+        float4 x4[PER], w4[PER][2];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            if (fetch) x4[u] = load4(a.X + (int64_t)row[u] * a.ldx + start);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int id = id_of(ids[u], q);
+                if (fetch && id >= 0) w4[u][q] = load4(a.W + (size_t)id * D + start);
+            }
+        }
+        uint32_t at_after[PER];
+        const unsigned int p2 = count - p0 > 2 * step ? p0 + 2 * step : p0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            ids_next[u] = *reinterpret_cast<const uint2*>(a.pairs + 2 * (int64_t)at_next[u]);
+            row_next[u] = a.idx ? a.idx[at_next[u]] : at_next[u];
+            at_after[u] = position(p2, u);
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            float4* r = rows + (kRowsAtOnce * u + grp) * 3 * kPairStride + sub;
+            if (fetch) r[0] = x4[u];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (fetch && id_of(ids[u], q) >= 0) r[(1 + q) * kPairStride] = w4[u][q];
+            if (sub == 0) {
+                entry_ids[kRowsAtOnce * u + grp] = ids[u];
+                entry_at[kRowsAtOnce * u + grp] = at[u];
+            }
+        }
+        // (third and fourth candidates, for few entries, take a second round)
+        bool more = false;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) more = more || id_of(ids[u], 2) >= 0;
+        const bool second_round = __syncthreads_or(more ? 1 : 0) != 0;
+        // this lane's candidate: entry tid / 2, place tid % 2 (and + 2 in the second round)
+        const int e = tid >> 1, c = tid & 1;
+        const bool mine = tid < 2 * kPairGroup && p0 + e < count;
+        const uint2 my_ids = mine ? entry_ids[e] : make_uint2(0xffffffffu, 0xffffffffu);
+        const int64_t ie = mine ? (int64_t)entry_at[e] : 0;
+        float bd = INFINITY;
+        int bk = 0x7fffffff;
+        for (int t0 = 0; t0 < (second_round ? 4 : 2); t0 += 2) {
+            if (t0 > 0) {
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < PER; ++u)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const int id = id_of(ids[u], 2 + q);
+                        if (fetch && id >= 0) rows[((kRowsAtOnce * u + grp) * 3 + 1 + q) * kPairStride + sub] = load4(a.W + (size_t)id * D + start);
+                    }
+                __syncthreads();
+            }
+            const int id = id_of(my_ids, t0 + c);
+            if (mine && id >= 0) {
+                const float4* rx = rows + e * 3 * kPairStride;
+                const float4* rw = rx + (1 + c) * kPairStride;
+                float d = 0.0f;
+                for (int q = 0; q < whole; ++q) {
+                    const float4 x = rx[q], w = rw[q];
+                    const float d0 = x.x - w.x, d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
+                    d = fmaf(d0, d0, d);
+                    d = fmaf(d1, d1, d);
+                    d = fmaf(d2, d2, d);
+                    d = fmaf(d3, d3, d);
+                }
+                if (rest > 0) {          // the window [D - 4, D): its leading elements are already counted
+                    const float4 x = rx[whole], w = rw[whole];
+                    const float d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
+                    if (rest > 2) d = fmaf(d1, d1, d);
+                    if (rest > 1) d = fmaf(d2, d2, d);
+                    d = fmaf(d3, d3, d);
+                }
+                if (d < bd || (d == bd && id < bk)) {
+                    bd = d;
+                    bk = id;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            at[u] = at_next[u];
+            at_next[u] = at_after[u];
+            row[u] = row_next[u];
+            ids[u] = ids_next[u];
+        }
+        const float od = __shfl_xor(bd, 1);
+        const int ok = __shfl_xor(bk, 1);
+        if (od < bd || (od == bd && ok < bk)) {
+            bd = od;
+            bk = ok;
+        }
+        if (mine && c == 0 && bk < a.K) {
+            a.bmu[ie] = bk;
+            if (a.d2) a.d2[ie] = bd;
+            qs += sqrt((double)bd);
+            qs2 += (double)bd;
+        }
+        __syncthreads();                 // the rows are rewritten by the next entries
+    }
+}
+
+template <bool PAIRS>
+__global__ void __launch_bounds__(kExactThreads) bmu_exact_kernel(const BmuArgs a)
+{
+    // PAIRS: three rows of each entry of the pair list; otherwise only the slab of the listed samples' features
+    __shared__ float4 lds4[PAIRS ? kPairGroup * 3 * kPairStride : 64 * (kExactGroup / 4)];
+    float4 (*xs4)[kExactGroup / 4] = reinterpret_cast<float4 (*)[kExactGroup / 4]>(lds4);   // [feature within a 64-wide slab][sample]
+    constexpr int kWaves = kExactThreads / 64;
+    __shared__ float red_d[kWaves][kExactGroup];
+    __shared__ int red_k[kWaves][kExactGroup];
     float* xs = reinterpret_cast<float*>(xs4);
     const float* __restrict__ wt = a.wt;
     const int tid = threadIdx.x;
@@ -2050,10 +2305,12 @@ __global__ void __launch_bounds__(256) bmu_exact_kernel(const BmuArgs a)
         // running total over the calls that share one weight preparation (the split search for D <= 64 counts its near
         // ties itself)
         if (!a.counts_near) atomicAdd(&a.scal[3], listed);
-        a.scal[3 - a.slot] = 0u;        // the next call counts into the other slots (1 and 2, 4 and 5)
+        a.scal[26 - a.slot] = 0u;       // the next call counts into the other slots (12, 13 and 14, 15; 4 and 5)
+        a.scal[27 - a.slot] = 0u;
         a.scal[9 - a.slot2] = 0u;
     }
     double qs = 0.0, qs2 = 0.0;
+    if constexpr (PAIRS) pair_list(a, lds4, qs, qs2);
     for (unsigned int g0 = blockIdx.x * kExactGroup; g0 < count; g0 += gridDim.x * kExactGroup) {
         float bestd[kExactGroup];
         int bestk[kExactGroup];
@@ -2062,7 +2319,7 @@ __global__ void __launch_bounds__(256) bmu_exact_kernel(const BmuArgs a)
             bestd[s] = INFINITY;
             bestk[s] = 0x7fffffff;
         }
-        for (int kb = 0; kb < a.kpad; kb += 256 * kExactNodesPerThread) {
+        for (int kb = 0; kb < a.kpad; kb += kExactThreads * kExactNodesPerThread) {
             float dist[kExactGroup][kExactNodesPerThread];
 #pragma unroll
             for (int s = 0; s < kExactGroup; ++s)
@@ -2071,7 +2328,7 @@ __global__ void __launch_bounds__(256) bmu_exact_kernel(const BmuArgs a)
             for (int d0 = 0; d0 < a.D; d0 += 64) {
                 const int dn = (a.D - d0 < 64) ? a.D - d0 : 64;
                 __syncthreads();
-                for (int e = tid; e < kExactGroup * dn; e += 256) {
+                for (int e = tid; e < kExactGroup * dn; e += kExactThreads) {
                     const int s = e / dn, d = e % dn;
                     const unsigned int ge = (g0 + s < count) ? g0 + s : count - 1;
                     const int64_t i = (int64_t)list[ge];
@@ -2079,18 +2336,19 @@ __global__ void __launch_bounds__(256) bmu_exact_kernel(const BmuArgs a)
                     xs[d * kExactGroup + s] = a.X[r * a.ldx + d0 + d];
                 }
                 __syncthreads();
-                // four features at a time: their sixteen weight loads are in flight together
-                for (int d = 0; d < dn; d += 4) {
-                    float w[4][kExactNodesPerThread];
+                // eight features at a time: their sixteen weight loads are in flight together
+                constexpr int kAtOnce = 8;
+                for (int d = 0; d < dn; d += kAtOnce) {
+                    float w[kAtOnce][kExactNodesPerThread];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t)
+                    for (int t = 0; t < kAtOnce; ++t)
 #pragma unroll
                         for (int u = 0; u < kExactNodesPerThread; ++u) {
-                            const int k = kb + u * 256 + tid;
+                            const int k = kb + u * kExactThreads + tid;
                             w[t][u] = (k < a.kpad && d + t < dn) ? wt[(size_t)(d0 + d + t) * a.kpad + k] : 0.f;
                         }
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) {
+                    for (int t = 0; t < kAtOnce; ++t) {
                         if (d + t < dn) {
                             float xv[kExactGroup];
 #pragma unroll
@@ -2114,7 +2372,7 @@ __global__ void __launch_bounds__(256) bmu_exact_kernel(const BmuArgs a)
             }
 #pragma unroll
             for (int u = 0; u < kExactNodesPerThread; ++u) {
-                const int k = kb + u * 256 + tid;
+                const int k = kb + u * kExactThreads + tid;
 #pragma unroll
                 for (int s = 0; s < kExactGroup; ++s)
                     if (k < a.K && dist[s][u] < bestd[s]) {
@@ -2146,7 +2404,7 @@ __global__ void __launch_bounds__(256) bmu_exact_kernel(const BmuArgs a)
         if (tid < kExactGroup && g0 + tid < count) {
             float bd = red_d[0][tid];
             int bk = red_k[0][tid];
-            for (int w = 1; w < 4; ++w) {
+            for (int w = 1; w < kWaves; ++w) {
                 const float od = red_d[w][tid];
                 const int ok = red_k[w][tid];
                 if (od < bd || (od == bd && ok < bk)) {
@@ -2162,7 +2420,7 @@ __global__ void __launch_bounds__(256) bmu_exact_kernel(const BmuArgs a)
             qs2 += (double)bd;
         }
     }
-    if (a.qe) group_qe_add(a.qe_part, tid < kExactGroup ? qs : 0.0, tid < kExactGroup ? qs2 : 0.0);
+    if (a.qe) group_qe_add(a.qe_part, qs, qs2);
 }
 
 // qe[0..1] += the call's partial sums, scal[3] += its near ties; the slots are left zero for the next call
@@ -2478,7 +2736,8 @@ static int launch_bmu(som_ctx* ctx, const BmuArgs& a)
 template <int KB, bool TAIL, int MS>
 static int launch_bmu_split(som_ctx* ctx, const BmuArgs& a)
 {
-    constexpr size_t lds_bytes = 2 * (size_t)split_stage_f4(KB, TAIL) * 16;
+    constexpr size_t lds_bytes = 2 * (size_t)split_stage_f4(KB, TAIL) * 16 + 3 * MS * kThreads * sizeof(float);
+    static_assert(lds_bytes + 512 <= 80 * 1024, "two workgroups per compute unit");
     static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
     bool& attr_set = attr_set_dev[ctx->device];
     auto kern = bmu_split_kernel<KB, TAIL, MS>;
@@ -2634,10 +2893,10 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
             ctx->recheck = nullptr;
             ctx->recheck_cap = 0;
         }
-        // sample positions [cap], cuts [cap], per-sample cuts [cap], second list [cand_cap], candidate sets [cand_cap][2]; the capacity is a
+        // sample positions [cap], cuts [cap], per-sample cuts [cap], pair-list ids [cap][2], second list [cand_cap], candidate sets [cand_cap][2]; the capacity is a
         // multiple of four entries so that the 16-byte candidate sets stay aligned
         const size_t cap = ((size_t)a.m + 3) / 4 * 4, ccap = cand_cap_for(cap);
-        const size_t bytes = cap * 12 + ccap * (4 + 2 * sizeof(ulonglong2));
+        const size_t bytes = cap * 20 + ccap * (4 + 2 * sizeof(ulonglong2));
         if (hipMalloc((void**)&ctx->recheck, bytes) != hipSuccess) {
             (void)hipGetLastError();
             return fail(ctx, SOM_ENOMEM, "cannot allocate the %lld-entry recheck list", (long long)a.m);
@@ -2656,7 +2915,9 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     a.recheck = ctx->recheck;
     a.cutv = (float*)(ctx->recheck + ctx->recheck_cap);
     a.cut_all = (float*)(ctx->recheck + 2 * ctx->recheck_cap);
-    a.recheck2 = ctx->recheck + 3 * ctx->recheck_cap;
+    a.recheck_end = ctx->recheck + ctx->recheck_cap;
+    a.pairs = ctx->recheck + 3 * ctx->recheck_cap;
+    a.recheck2 = ctx->recheck + 5 * ctx->recheck_cap;
     a.cand = (ulonglong2*)(a.recheck2 + cand_cap_for(ctx->recheck_cap));
     a.cand_cap = (uint32_t)cand_cap_for(ctx->recheck_cap);
     // The candidate pass repeats the search for the listed samples at matrix speed (under a nanosecond per sample
@@ -2668,7 +2929,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     a.counts_near = prep.stage16 && prep.nch == 1;
     // the list length restarts for every call (chunk): calls alternate between two counters, and each call's
     // exact pass clears the counter of the next one
-    a.slot = 1 + (prep.calls & 1);
+    a.slot = 12 + 2 * (prep.calls & 1);
     a.slot2 = 4 + (prep.calls & 1);
     ++prep.calls;
     hipEvent_t stop = nullptr;
@@ -2710,7 +2971,10 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
         }
     }
     if (a.K > 1) {
-        hipLaunchKernelGGL(bmu_exact_kernel, dim3(1024), dim3(256), 0, ctx->stream, a);
+        if (prep.stage16 && prep.nch == 1)
+            hipLaunchKernelGGL(bmu_exact_kernel<true>, dim3(1024), dim3(kExactThreads), 0, ctx->stream, a);
+        else
+            hipLaunchKernelGGL(bmu_exact_kernel<false>, dim3(1024), dim3(kExactThreads), 0, ctx->stream, a);
         if ((rc = check_hip(ctx, hipGetLastError(), "bmu exact-pass launch"))) return rc;
     }
     if (a.qe) {

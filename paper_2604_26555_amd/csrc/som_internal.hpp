@@ -23,9 +23,9 @@ struct BmuPrep {
     int nch16 = 0;                 // chunks of a stage in stage16 (1 for D <= 64, 64-feature chunks above)
     float* wt = nullptr;           // [D][Kpad] transposed weights (as given, not centred)
     float* centre = nullptr;       // [D] column means of W; stage rows and sample registers hold values minus this
-    // [0] = bits of max_k |w_k - centre|^2, [1], [2] = recheck-list length (alternating calls), [3] = total,
+    // [0] = bits of max_k |w_k - centre|^2, [3] = total,
     // [4], [5] = length of the second list (samples whose candidate slots overflowed; alternating calls),
-    // [8], [9] = bits of max_k |w - hi|^2 and |w - hi - lo|^2 (bf16 parts)
+    // [12], [13] = length of the list and of the pair list, [14], [15] the next call's, [8], [9] = bits of max_k |w - hi|^2 and |w - hi - lo|^2 (bf16 parts)
     unsigned int* scal = nullptr;
     int kpad = 0, steps = 0, stride = 0;
     int nch = 1;                   // feature chunks of 2 * steps features (1 unless D > 64)
@@ -48,10 +48,12 @@ struct BmuArgs {
     const float* wt;         // BmuPrep::wt
     const float* centre;     // BmuPrep::centre
     unsigned int* scal;      // BmuPrep::scal
-    int32_t slot;            // which of scal[1], scal[2] this call counts into
+    int32_t slot;            // scal[slot], scal[slot + 1] count this call's list and pair list (12 or 14)
     int64_t full_tiles;      // bmu_kernel: workgroups below this number take full tiles, the others half tiles
     float* cut_all;          // [m] per presented sample: its cut when it is to be re-decided, a NaN otherwise
     uint32_t* recheck;       // [m] sample positions to re-decide (compacted from cut_all by bmu_list_kernel)
+    uint32_t* recheck_end;   // end of the recheck array, from which the pair list grows down
+    uint32_t* pairs;         // [m][2] per sample on the pair list: two 16-bit candidate ids of each lane half (0xffff: none)
     // Candidate pass (long lists only): the search is repeated for the listed samples, and every node whose score
     // reaches the sample's cut is noted; direct differences are then taken over those few nodes only.
     float* cutv;             // [m] per list entry: best score minus the rounding bound
