@@ -24,17 +24,13 @@
 // Where the caller asks for distances, the winner's squared distance of all other samples is recomputed by direct
 // differences as well, so the reported distances never carry the cancellation error of the score form.
 //
-// The default search (bmu_split_kernel and bmu_split_wide_kernel further down) is the same scheme with the
+// The default search (bmu_split_kernel further down for D <= 64, som_bmu_wide.hip above) is the same scheme with the
 // contraction on the bf16 matrix pipe, samples and weights cut into two bf16 parts each.
-#include "som_internal.hpp"
-
-#include <hip/amd_detail/amd_hip_unsafe_atomics.h>
+#include "som_bmu_common.hpp"
 
 #include <math.h>
 
 namespace som {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kWavesPerGroup = 4;
 constexpr int kThreads = kWavesPerGroup * 64;
@@ -59,15 +55,6 @@ constexpr int stage_floats_for(int stride)
 // chunk.  One thread per element of the padded matrix (coalesced reads of W); the first kpad / 4 wavefronts also
 // compute four nodes' norms each, in float64.
 // ---------------------------------------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
-constexpr int kScalLo = 8;        // scal[8], scal[9]: bits of the largest |w - hi|^2 and |w - hi - lo|^2 (split search)
-
 // centre[f] = mean over nodes of W[k][f], f < D; zero up to the next multiple of 64.  Any vector would do (distances do not change when the same vector is
 // taken off samples and weights); the mean keeps |w_k - centre| as small as the spread of the map.
 __global__ void __launch_bounds__(1024) bmu_centre_kernel(const float* __restrict__ W, int K, int D, float* __restrict__ centre,
@@ -102,14 +89,11 @@ __global__ void __launch_bounds__(1024) bmu_centre_kernel(const float* __restric
 
 struct SplitPrep {
     char* stage16;       // null: no split search for this shape
-    float* wwin;         // float32 copy of the slots (D <= 64 only), or null
-    int kb_count, tail_r, nch16, row_bytes, stage16_bytes;
+    float* wwin;         // float32 copy of the slots
+    int kb_count, tail_r, row_bytes, stage16_bytes;
 };
-constexpr float kSplitPadNorm = -3.0e38f;     // padding nodes of the split search: finite, so that position bits cannot make a NaN
-
-// One slot of the rows for the bf16 matrix pipe: thread e takes (node, slot), chunks of kb_count 16-feature blocks (one
-// chunk for D <= 64, chunks of 64 features above).
-// tail_r > 0 (D <= 64 only): the last tail_r <= 4 features do not get a 16-feature block of their own (three MFMAs
+// One slot of the rows for the bf16 matrix pipe (D <= 64): thread e takes (node, slot).
+// tail_r > 0: the last tail_r <= 4 features do not get a 16-feature block of their own (three MFMAs
 // for a block that is mostly padding) but one packed block whose sixteen slots hold the three products side by side,
 //     weights  [ hi(r) | hi(r) | lo(r) | norm parts (3) | 0 ... ]   against samples  [ hi(r) | lo(r) | hi(r) | 1 1 1 | 0 ... ],
 // one MFMA (the norm parts are written by the wavefront that sums the node's norm).  The float32 copy of the packed
@@ -117,15 +101,13 @@ constexpr float kSplitPadNorm = -3.0e38f;     // padding nodes of the split sear
 __device__ __forceinline__ void split_prep_slot(const float* __restrict__ W, int K, int D, int kpad,
                                                 const float* __restrict__ centre, const SplitPrep& sp, int e)
 {
-    const int per_chunk = sp.kb_count * 16 + (sp.tail_r ? 16 : 0), slots = sp.nch16 * per_chunk;
+    const int slots = sp.kb_count * 16 + (sp.tail_r ? 16 : 0);
     if (e >= kpad * slots) return;
-    const int k = e / slots, sl = e - k * slots;
-    const int chunk = sl / per_chunk, within = sl - chunk * per_chunk;
+    const int k = e / slots, within = e - k * slots;
     const int kb = within >> 4, g = (within >> 3) & 1, t = within & 7;
-    char* row = sp.stage16 + ((size_t)(k / kNodesPerStage) * sp.nch16 + chunk) * sp.stage16_bytes +
-                (size_t)(k % kNodesPerStage) * sp.row_bytes;
+    char* row = sp.stage16 + (size_t)(k / kNodesPerStage) * sp.stage16_bytes + (size_t)(k % kNodesPerStage) * sp.row_bytes;
     if (kb < sp.kb_count) {
-        const int f0 = 64 * chunk + 4 * (4 * kb + 2 * g + (t >> 2));      // the slot group's own first feature
+        const int f0 = 4 * (4 * kb + 2 * g + (t >> 2));                   // the slot group's own first feature
         const int f = (f0 < D - 4 ? f0 : D - 4) + (t & 3);               // its window, always inside the row
         const bool real = k < K && f >= f0;
         const float v = real ? W[(size_t)k * D + f] - centre[f] : 0.0f;
@@ -134,7 +116,7 @@ __device__ __forceinline__ void split_prep_slot(const float* __restrict__ W, int
         __bf16* cell = reinterpret_cast<__bf16*>(row + kb * 64 + g * 32) + t;
         cell[0] = hi;
         cell[8] = lo;
-        if (sp.wwin) sp.wwin[e] = v;   // the same slots in float32, [node][kb][g][8]: the winner's row for the distances
+        sp.wwin[e] = v;   // the same slots in float32, [node][kb][g][8]: the winner's row for the distances
     } else {
         // packed tail: slot s = 8 g + t holds copy s / r of feature D - r + s % r (copies 0, 1: hi, copy 2: lo); the
         // three slots behind them belong to the norm
@@ -144,7 +126,7 @@ __device__ __forceinline__ void split_prep_slot(const float* __restrict__ W, int
         const __bf16 lo = (__bf16)(v - (float)hi);
         const int ns = sidx - 3 * sp.tail_r;
         if (ns < 0 || ns >= 3) reinterpret_cast<__bf16*>(row + sp.kb_count * 64 + g * 16)[t] = (copy == 2) ? lo : hi;
-        if (sp.wwin) sp.wwin[e] = (copy == 0) ? v : 0.0f;
+        sp.wwin[e] = (copy == 0) ? v : 0.0f;
     }
 }
 
@@ -225,20 +207,18 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
                     stage[((size_t)st * nch + ch) * stage_floats + (size_t)kNodesPerStage * stride + r] = nh;
                 if (sp.stage16) {
                     const float nf = nh > kSplitPadNorm ? nh : kSplitPadNorm;
-                    for (int ch = 0; ch < sp.nch16; ++ch) {
-                        char* blob = sp.stage16 + ((size_t)st * sp.nch16 + ch) * sp.stage16_bytes;
-                        reinterpret_cast<float*>(blob + (size_t)kNodesPerStage * sp.row_bytes)[r] = nf;
-                        if (sp.tail_r) {
-                            // -|w|^2 / 2 cut into three bf16 parts (exactly: 3 x 8 bits) in the three slots behind the
-                            // packed block's features; they meet ones on the samples' side
-                            const __bf16 p0 = (__bf16)nf;
-                            const __bf16 p1 = (__bf16)(nf - (float)p0);
-                            const __bf16 p2 = (__bf16)((nf - (float)p0) - (float)p1);
-                            __bf16* cell = reinterpret_cast<__bf16*>(blob + (size_t)r * sp.row_bytes + sp.kb_count * 64);
-                            cell[3 * sp.tail_r] = p0;          // slots 8 g + t are contiguous: [g = 0: 8][g = 1: 8]
-                            cell[3 * sp.tail_r + 1] = p1;
-                            cell[3 * sp.tail_r + 2] = p2;
-                        }
+                    char* blob = sp.stage16 + (size_t)st * sp.stage16_bytes;
+                    reinterpret_cast<float*>(blob + (size_t)kNodesPerStage * sp.row_bytes)[r] = nf;
+                    if (sp.tail_r) {
+                        // -|w|^2 / 2 cut into three bf16 parts (exactly: 3 x 8 bits) in the three slots behind the
+                        // packed block's features; they meet ones on the samples' side
+                        const __bf16 p0 = (__bf16)nf;
+                        const __bf16 p1 = (__bf16)(nf - (float)p0);
+                        const __bf16 p2 = (__bf16)((nf - (float)p0) - (float)p1);
+                        __bf16* cell = reinterpret_cast<__bf16*>(blob + (size_t)r * sp.row_bytes + sp.kb_count * 64);
+                        cell[3 * sp.tail_r] = p0;          // slots 8 g + t are contiguous: [g = 0: 8][g = 1: 8]
+                        cell[3 * sp.tail_r + 1] = p1;
+                        cell[3 * sp.tail_r + 2] = p2;
                     }
                 }
                 if (k < K) {
@@ -272,62 +252,6 @@ __global__ void fill_zero_kernel(uint32_t* p, size_t words)
 // helpers
 // ---------------------------------------------------------------------------------------------------------
 
-// Sum of distances and squared distances of a workgroup's samples -> one of kQeSlots partial-sum slots.  Every
-// wavefront adding to the same two words would serialise tens of thousands of atomics on one address; one pair
-// per workgroup spread over 256 slots does not show in the kernel time.  Called by all threads of the workgroup.
-// near: the split searches also count this lane's near ties, into kQeSlots further slots (counts are whole numbers: exact).
-__device__ __forceinline__ void group_qe_add(double* __restrict__ part, double qs, double qs2, int near = 0)
-{
-    __shared__ double wsum[16][2];
-    __shared__ int wnear[16];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) near += __shfl_xor(near, o);
-    qs = wave_sum(qs);
-    qs2 = wave_sum(qs2);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) {
-        wsum[wave][0] = qs;
-        wsum[wave][1] = qs2;
-        wnear[wave] = near;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t0 = 0.0, t1 = 0.0;
-        int t2 = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
-            t0 += wsum[w][0];
-            t1 += wsum[w][1];
-            t2 += wnear[w];
-        }
-        if (t2 != 0) unsafeAtomicAdd(&part[2 * kQeSlots + (blockIdx.x & (kQeSlots - 1))], (double)t2);
-        if (t0 != 0.0 || t1 != 0.0) {
-            const int slot = blockIdx.x & (kQeSlots - 1);
-            unsafeAtomicAdd(&part[2 * slot], t0);
-            unsafeAtomicAdd(&part[2 * slot + 1], t1);
-        }
-    }
-}
-
-// Append sample i (and its score cut) to the re-decision list for every lane with `push` set: one atomic per wavefront (the list
-// length is a single word; one atomic per listed sample serialises on it when a tenth of all samples is listed).
-// Called in converged control flow by all lanes of the wavefront.
-__device__ __forceinline__ void list_push(unsigned int* __restrict__ counter, uint32_t* __restrict__ list,
-                                          float* __restrict__ cutv, bool push, int64_t i, float cut)
-{
-    const unsigned long long mask = __ballot(push);
-    if (mask == 0ull) return;
-    const int lane = threadIdx.x & 63;
-    const int leader = __ffsll((long long)mask) - 1;
-    unsigned int base = 0u;
-    if (lane == leader) base = atomicAdd(counter, (unsigned int)__popcll(mask));
-    base = __shfl(base, leader);
-    const unsigned int below = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
-    if (push) {
-        list[base + below] = (uint32_t)i;
-        if (cutv) cutv[base + below] = cut;     // scores at or above this value may belong to the true winner
-    }
-}
-
 // The re-decision list of a pass.  The search kernels do not append to it themselves: one atomic per wavefront on the
 // list's single length word serialises in the memory system (about 10 ns each; with a few per cent of the samples
 // listed nearly every wavefront has one, and the 15,625 wavefronts of 10^6 samples then spent up to 0.1 ms of a
@@ -335,10 +259,6 @@ __device__ __forceinline__ void list_push(unsigned int* __restrict__ counter, ui
 // or kNotListed, and this kernel compacts the listed ones: a workgroup takes 4096 samples at a time, counts with a
 // scan, and reserves its entries with one atomic.  The order of the list is immaterial (every entry is decided on its
 // own).
-// A sample whose few candidates the search already knows (kPairs; their ids are in a.pairs) goes on the pair list, which
-// grows down from the end of the same array.
-constexpr float kNotListed = __builtin_nanf("");
-constexpr float kPairs = __builtin_inff();
 constexpr int kListThreads = 1024, kListPerThread = 4;
 
 __global__ void __launch_bounds__(kListThreads) bmu_list_kernel(const BmuArgs a)
@@ -410,14 +330,6 @@ __global__ void __launch_bounds__(kListThreads) bmu_list_kernel(const BmuArgs a)
     }
 }
 
-// sixteen bytes from a 4-byte aligned address in one load (global memory needs no more than dword alignment)
-__device__ __forceinline__ float4 load4(const float* p)
-{
-    float4 v;
-    __builtin_memcpy(&v, p, sizeof(v));
-    return v;
-}
-
 // Up to seven 16-bit node ids and their count in 128 bits of registers.  A hit shifts the ids up by one place (the
 // oldest drops out at the top, the count keeps counting, so an overflow shows): no memory traffic while the scores
 // are being formed, one 16-byte store per lane at the end.
@@ -447,23 +359,6 @@ __device__ __forceinline__ int cand_count(const ulonglong2& v) { return (int)(v.
 __device__ __forceinline__ int cand_id(const ulonglong2& v, int t)
 {
     return (int)(((t < 4) ? (v.x >> (16 * t)) : (v.y >> (16 * (t - 4)))) & 0xffffull);
-}
-
-// plain v_max_f32: the scores are never signalling NaNs worth quieting, and every VALU instruction here is paid
-// for in matrix time (float32 MFMA and the vector ALU share the same lanes)
-__device__ __forceinline__ float vmax(float a, float b)
-{
-    float r;
-    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
-// plain v_max3_f32, for the same reason
-__device__ __forceinline__ float vmax3(float a, float b, float c)
-{
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -789,8 +684,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// The same search with the contraction on the bf16 matrix pipe (this kernel: 4 <= D <= 64, bmu_split_wide_kernel
-// below: D > 64; the default for every map of more than one node).
+// The same search with the contraction on the bf16 matrix pipe (this kernel: 4 <= D <= 64, som_bmu_wide.hip: D > 64; the default for every map of more than one node).
 //
 // A float32 value v is cut into two bf16 parts, hi = bf16(v) and lo = bf16(v - hi) (both rounded to nearest, the
 // difference is exact in float32), so that |v - hi - lo| <= 2^-18 |v|.  A score then takes three bf16 MFMAs per 16
@@ -812,8 +706,6 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
 // and a select; 16 units of the last place are part of the bound), so padding nodes carry a large finite negative
 // norm here instead of -inf.
 // ---------------------------------------------------------------------------------------------------------
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
 // bytes of a stage row: kb whole 16-feature blocks of 64 bytes, 32 bytes for a packed tail block, 16 bytes of padding
 constexpr int split_row_bytes(int kb, bool tail = false) { return kb * 64 + (tail ? 32 : 0) + 16; }
 constexpr int split_stage_f4(int kb, bool tail = false)
@@ -822,29 +714,7 @@ constexpr int split_stage_f4(int kb, bool tail = false)
 }
 constexpr int kSplitMinNodes = 1;              // SOM_SEARCH_AUTO: every map of more than this many nodes (measured faster than the
                                                // float32 search from 2 x 2 nodes and from D = 4 on)
-constexpr size_t kPartsBytes = (size_t)8 << 30;    // workspace of the samples' bf16 parts (D > 64), per pass
 constexpr int kSplitMS = 2;
-
-__device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo)
-{
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        hi[i] = (__bf16)v[i];
-        lo[i] = (__bf16)(v[i] - (float)hi[i]);
-    }
-}
-
-// the same, and what the first parts leave over is added to left2 (squares)
-__device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo, float& left2)
-{
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        hi[i] = (__bf16)v[i];
-        const float left = v[i] - (float)hi[i];
-        lo[i] = (__bf16)left;
-        left2 = fmaf(left, left, left2);
-    }
-}
 
 // first feature of slot group q (four consecutive features)
 __device__ __forceinline__ int split_window(int q, int D) { return 4 * q < D - 4 ? 4 * q : D - 4; }
@@ -1774,256 +1644,6 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// The split search for D > 64: chunks of 64 features (four 16-feature blocks) through the same stage rows, one block
-// of 32 samples per wavefront, the four node blocks' accumulators of a stage live across the chunks (as
-// bmu_wide_tile).  A wavefront meets every chunk of its samples once per stage, so the samples' bf16 parts are not
-// made in this kernel (tried: the conversion, 250 vector instructions per chunk and stage beside 48 MFMAs, made it
-// slower than the float32 kernel) but once per pass by bmu_split_convert_kernel, into a[parts]: per presented
-// sample and slot group of eight features 32 bytes, [hi x 8 | lo x 8], which a lane reads as they are.
-// Every chunk's partial product is summed on its own from zero and then added, so that the roundings inside a chunk
-// are relative to |x_chunk| |w_chunk| and add up to at most |x| |w| over the chunks (Cauchy-Schwarz).
-// Slot group q of chunk ch is the row's window [min(64 ch + 4 q, D - 4), + 4); the weights (bmu_prep_split_kernel)
-// and the samples (the conversion) are zero in front of a shifted window's own features.
-// ---------------------------------------------------------------------------------------------------------
-// one thread per (presented sample, group of eight slots): centred, cut into bf16 parts
-__global__ void __launch_bounds__(256) bmu_split_convert_kernel(const BmuArgs a, int nch16)
-{
-    const int groups = nch16 * 8;
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= a.m * groups) return;
-    const int64_t i = e / groups;
-    const int grp = (int)(e - i * groups);
-    const int chunk = grp >> 3, kb = (grp >> 1) & 3, g = grp & 1;
-    const int64_t row = a.idx ? (int64_t)a.idx[i] : i;
-    const float* xr = a.X + row * a.ldx;
-    float v[8];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int f0 = 64 * chunk + 4 * (4 * kb + 2 * g + h);
-        const int start = f0 < a.D - 4 ? f0 : a.D - 4;
-        const int shift = f0 - start;                                     // own slots: index >= shift
-        const float4 x4 = load4(xr + start), c4 = load4(a.centre + start);
-        v[4 * h + 0] = shift <= 0 ? x4.x - c4.x : 0.0f;
-        v[4 * h + 1] = shift <= 1 ? x4.y - c4.y : 0.0f;
-        v[4 * h + 2] = shift <= 2 ? x4.z - c4.z : 0.0f;
-        v[4 * h + 3] = shift <= 3 ? x4.w - c4.w : 0.0f;
-    }
-    bf16x8 hi, lo;
-    split8(v, hi, lo);
-    bf16x8* out = reinterpret_cast<bf16x8*>(a.parts) + e * 2;
-    out[0] = hi;
-    out[1] = lo;
-}
-
-template <bool CAND>
-__device__ __forceinline__ void bmu_split_wide_tile(const BmuArgs& a, int64_t tile_index, unsigned int count, float4* lds4)
-{
-    constexpr int KB = 4, NBS = kNodesPerStage / 32;
-    constexpr int RS = split_row_bytes(KB);
-    constexpr int STAGE_F4 = split_stage_f4(KB);
-    constexpr int PRE = STAGE_F4 / kThreads;
-    static_assert(PRE <= 9, "stage copy holds at most nine float4 per thread");
-    const char* ldsb = reinterpret_cast<const char*>(lds4);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int j = lane & 31, g = lane >> 5;
-    const int64_t i = (tile_index * kWavesPerGroup + wave) * 32 + j;      // sample position, or list entry (CAND)
-    const int64_t total = CAND ? (int64_t)count : a.m;
-    const bool valid = i < total;
-    int64_t ii = valid ? i : total - 1;
-    float cut = NAN;                                                        // CAND; no score compares >= NaN
-    CandSet noted;
-    if constexpr (CAND) {
-        if (valid) cut = a.cutv[ii];
-        ii = (int64_t)a.recheck[ii];
-    }
-    const int64_t row = a.idx ? (int64_t)a.idx[ii] : ii;
-    const float* xr = a.X + row * a.ldx;
-
-    float best = -INFINITY, second = -INFINITY;
-    int rsel = 0, tsel = 0;
-    const int nstages = a.kpad / kNodesPerStage;
-    const int nch = (a.D + 63) / 64;
-    const int nq = nstages * nch;
-    const float4* src4 = reinterpret_cast<const float4*>(a.stage16);
-#pragma unroll
-    for (int p = 0; p < PRE; ++p) lds4[tid + p * kThreads] = src4[tid + p * kThreads];
-    __syncthreads();
-
-    // this lane's parts of a chunk: four groups of eight slots, 32 bytes each
-    const bf16x8* prow = reinterpret_cast<const bf16x8*>(a.parts) + (size_t)ii * (nch * 8) * 2;
-    auto read_chunk = [&](int chunk, bf16x8 (&h8)[KB], bf16x8 (&l8)[KB]) {
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-            const bf16x8* p = prow + (size_t)((chunk * 4 + kb) * 2 + g) * 2;
-            h8[kb] = p[0];
-            l8[kb] = p[1];
-        }
-    };
-    bf16x8 xh[KB], xl[KB];
-    read_chunk(0, xh, xl);
-
-    floatx16 acc[NBS];
-    int st = 0, ch = 0;
-    for (int q = 0; q < nq; ++q) {
-        const int buf = q & 1;
-        float4 pre0, pre1, pre2, pre3, pre4, pre5, pre6, pre7, pre8;
-        {
-            const int nxt = (q + 1 < nq) ? q + 1 : q;
-            const float4* s4 = src4 + (size_t)nxt * STAGE_F4 + tid;
-#define SOM_PRE_LOAD(i) if constexpr (PRE > i) pre##i = s4[i * kThreads];
-            SOM_PRE_LOAD(0) SOM_PRE_LOAD(1) SOM_PRE_LOAD(2) SOM_PRE_LOAD(3) SOM_PRE_LOAD(4)
-            SOM_PRE_LOAD(5) SOM_PRE_LOAD(6) SOM_PRE_LOAD(7) SOM_PRE_LOAD(8)
-#undef SOM_PRE_LOAD
-        }
-        // the samples' next chunk travels to registers during this chunk's arithmetic
-        const int chn = (ch + 1 == nch) ? 0 : ch + 1;
-        bf16x8 xhn[KB], xln[KB];
-        read_chunk(chn, xhn, xln);
-        __builtin_amdgcn_sched_barrier(0);
-        const char* wbuf = ldsb + (size_t)buf * STAGE_F4 * 16;
-        const float* nbuf = reinterpret_cast<const float*>(wbuf + kNodesPerStage * RS);
-        bf16x8 wh[KB], wl[KB];
-        {
-            const char* wrow = wbuf + j * RS + g * 32;
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-                wh[kb] = *reinterpret_cast<const bf16x8*>(wrow + kb * 64);
-                wl[kb] = *reinterpret_cast<const bf16x8*>(wrow + kb * 64 + 16);
-            }
-        }
-#pragma unroll
-        for (int nb = 0; nb < NBS; ++nb) {
-            if (ch == 0) {
-                const float4* nh = reinterpret_cast<const float4*>(nbuf + nb * 32 + 4 * g);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float4 v = nh[2 * t];
-                    acc[nb][4 * t + 0] = v.x;
-                    acc[nb][4 * t + 1] = v.y;
-                    acc[nb][4 * t + 2] = v.z;
-                    acc[nb][4 * t + 3] = v.w;
-                }
-            }
-            const char* wnext = wbuf + ((nb + 1) * 32 + j) * RS + g * 32;
-            floatx16 part;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) part[r] = 0.0f;
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh[kb], xh[kb], part, 0, 0, 0);
-                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh[kb], xl[kb], part, 0, 0, 0);
-                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl[kb], xh[kb], part, 0, 0, 0);
-                // the next block's rows, into the registers this block has finished with
-                if (nb + 1 < NBS) {
-                    wh[kb] = *reinterpret_cast<const bf16x8*>(wnext + kb * 64);
-                    wl[kb] = *reinterpret_cast<const bf16x8*>(wnext + kb * 64 + 16);
-                    __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);     // three MFMAs
-                    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);     // two LDS reads
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[nb][r] += part[r];
-            if (CAND && ch == nch - 1) {
-                const int tile = st * NBS + nb;
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (acc[nb][r] >= cut) noted.note(tile * 32 + 4 * g, 8 * (r >> 2) + (r & 3));
-            }
-            if (!CAND && ch == nch - 1) {
-                const int tile = st * NBS + nb;
-                const float before = best;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float v = acc[nb][r];
-                    rsel = (v > best) ? r : rsel;
-                    second = __builtin_amdgcn_fmed3f(best, second, v);
-                    best = vmax(best, v);
-                }
-                tsel = (best > before) ? tile : tsel;
-            }
-        }
-        {
-            float4* d4 = lds4 + (buf ^ 1) * STAGE_F4 + tid;
-#define SOM_PRE_STORE(i) if constexpr (PRE > i) d4[i * kThreads] = pre##i;
-            SOM_PRE_STORE(0) SOM_PRE_STORE(1) SOM_PRE_STORE(2) SOM_PRE_STORE(3) SOM_PRE_STORE(4)
-            SOM_PRE_STORE(5) SOM_PRE_STORE(6) SOM_PRE_STORE(7) SOM_PRE_STORE(8)
-#undef SOM_PRE_STORE
-        }
-        __syncthreads();
-        if (++ch == nch) {
-            ch = 0;
-            ++st;
-        }
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-            xh[kb] = xhn[kb];
-            xl[kb] = xln[kb];
-        }
-    }
-
-    if constexpr (CAND) {
-        if (valid) a.cand[(size_t)i * 2 + g] = noted.packed();
-        return;
-    }
-    // ---- join the two half-wavefronts; squared norm and exact winner distance from memory, half the features each
-    int node = tsel * 32 + 8 * (rsel >> 2) + 4 * g + (rsel & 3);
-    const float ob = __shfl_xor(best, 32), os = __shfl_xor(second, 32);
-    const int on = __shfl_xor(node, 32);
-    const float sec = fmaxf(fmaxf(second, os), fminf(best, ob));
-    const bool other = (ob > best) || (ob == best && on < node);
-    const float bst = other ? ob : best;
-    node = other ? on : node;
-    node = node < a.K ? node : a.K - 1;
-    float xn = 0.f, part = 0.f;
-    const float* wr = a.W + (size_t)node * a.D;
-    for (int f = g; f < a.D; f += 2) {
-        const float xv = xr[f];
-        const float xc = xv - a.centre[f];
-        const float df = xv - wr[f];
-        xn = fmaf(xc, xc, xn);
-        part = fmaf(df, df, part);
-    }
-    xn += __shfl_xor(xn, 32);
-    part += __shfl_xor(part, 32);
-    double qs = 0.0, qs2 = 0.0;
-    const float wmax2 = __uint_as_float(a.scal[0]);
-    const float wmax = sqrtf(wmax2) * 1.000001f;
-    // per score: the split leaves 3 * 2^-18 (1 + 2^-7); inside a chunk 12 MFMAs charged 16 units of 2^-24 each,
-    // times 1.016 for the parts' own magnitudes (any order of round-to-nearest additions, as in bmu_split_tile; relative
-    // to the chunk's magnitude, see above), one addition per chunk, one rounding for -|w|^2/2; two scores, plus the
-    // centring roundings and slack as in bmu_kernel
-    const float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(196 + nch + 1) * 5.9604645e-08f) + 12.0f * 5.9604645e-08f;
-    const float bound = (sqrtf(xn) * wmax + 0.5f * wmax2) * rel;
-    const bool mine = valid && g == 0;
-    const bool close = mine && a.K > 1 && !((bst - sec) > bound);
-    if (mine) {
-        a.bmu[i] = node;
-        if (a.d2) a.d2[i] = part;
-        if (!close) {
-            qs = sqrt((double)part);
-            qs2 = (double)part;
-        }
-    }
-    if (mine) a.cut_all[i] = close ? bst - bound : kNotListed;
-    if (a.qe) group_qe_add(a.qe_part, qs, qs2);
-}
-
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) bmu_split_wide_kernel(const BmuArgs a)
-{
-    extern __shared__ float4 lds4[];
-    bmu_split_wide_tile<false>(a, blockIdx.x, 0u, lds4);
-}
-
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) bmu_split_wide_cand_kernel(const BmuArgs a)
-{
-    extern __shared__ float4 lds4[];
-    const unsigned int count = a.scal[a.slot];
-    if (!cand_pass_serves(a, count)) return;
-    constexpr int64_t per_tile = (int64_t)kWavesPerGroup * 32;
-    for (int64_t t = blockIdx.x; t * per_tile < (int64_t)count; t += gridDim.x) bmu_split_wide_tile<true>(a, t, count, lds4);
-}
-
-// ---------------------------------------------------------------------------------------------------------
 // exact re-decision of the listed samples by direct differences, sum_d (x_d - w_kd)^2 for every node.
 // A workgroup takes kExactGroup samples at a time; thread t owns nodes t, t + 256, ... so one coalesced read of
 // the transposed weights serves all samples of the group, and the samples' features are broadcast from LDS.
@@ -2298,7 +1918,7 @@ __global__ void __launch_bounds__(kExactThreads) bmu_exact_kernel(const BmuArgs 
     const int lane = tid & 63, wave = tid >> 6;
     // the whole list, or what the candidate pass left over
     const unsigned int listed = a.scal[a.slot];
-    const bool by_cand = cand_pass_serves(a, listed);
+    const bool by_cand = a.second_only || cand_pass_serves(a, listed);
     const unsigned int count = by_cand ? a.scal[a.slot2] : listed;
     const uint32_t* __restrict__ list = by_cand ? a.recheck2 : a.recheck;
     if (blockIdx.x == 0 && tid == 0) {
@@ -2498,8 +2118,9 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     }
     const int stride = 2 * steps + 1;
     const int kpad = ((K + kNodesPerStage - 1) / kNodesPerStage) * kNodesPerStage;
-    const size_t stage_bytes = (size_t)(kpad / kNodesPerStage) * nch * stage_floats_for(stride) * sizeof(float);
-    const size_t wt_bytes = (size_t)D * kpad * sizeof(float);
+    const bool wide_split = D > 2 * kMaxStepsResident && K > kSplitMinNodes && ctx->search != SOM_SEARCH_FLOAT32;
+    const size_t stage_bytes = wide_split ? 0 : (size_t)(kpad / kNodesPerStage) * nch * stage_floats_for(stride) * sizeof(float);
+    const size_t wt_bytes = (size_t)D * kpad * sizeof(float) + 255 & ~(size_t)255;
     // the centre vector is zero-padded to whole chunks (and to the 64 entries the resident kernel reads)
     const size_t centre_floats = (size_t)(nch > 1 ? nch * 2 * steps : 64);
     const size_t centre_bytes = ((centre_floats > (size_t)D ? centre_floats : (size_t)D) * sizeof(float) + 255) / 256 * 256;
@@ -2510,10 +2131,10 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     // D <= 64: whole 16-feature blocks, and a remainder of one to four features goes into one packed block (one MFMA
     // instead of three for a block that would be mostly padding); larger remainders get a block of their own
     const int tail_r = (split && nch == 1 && D % 16 >= 1 && D % 16 <= 4) ? D % 16 : 0;
-    const int kb = !split ? 0 : (nch == 1 ? (tail_r ? D / 16 : (D + 15) / 16) : 4);
-    const int nch16 = !split ? 0 : (nch == 1 ? 1 : (D + 63) / 64);
-    const size_t stage16_one = split ? (size_t)split_stage_f4(kb, tail_r > 0) * 16 : 0;
-    const size_t stage16_bytes = (size_t)(kpad / kNodesPerStage) * nch16 * stage16_one;
+    const int kb = !split || nch > 1 ? 0 : (tail_r ? D / 16 : (D + 15) / 16);
+    // (D > 64: rows in the order of som_bmu_wide.hip)
+    const size_t stage16_one = (split && nch == 1) ? (size_t)split_stage_f4(kb, tail_r > 0) * 16 : 0;
+    const size_t stage16_bytes = !split ? 0 : nch == 1 ? (size_t)(kpad / kNodesPerStage) * stage16_one : bmu_wide_blob_bytes(K, D);
     const size_t wwin_bytes = (split && nch == 1) ? (size_t)kpad * (kb * 16 + (tail_r ? 16 : 0)) * sizeof(float) : 0;
     const size_t need = stage_bytes + wt_bytes + centre_bytes + stage16_bytes + wwin_bytes + 256;
     if (need > ctx->prep_bytes) {
@@ -2537,7 +2158,6 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     out->stage16 = split ? (void*)(base + 256 + stage_bytes + wt_bytes + centre_bytes) : nullptr;
     out->tail_r = tail_r;
     out->wwin = wwin_bytes ? (float*)(base + 256 + stage_bytes + wt_bytes + centre_bytes + stage16_bytes) : nullptr;
-    out->nch16 = nch16;
     out->kb = kb;
     out->kpad = kpad;
     out->steps = steps;
@@ -2546,6 +2166,10 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     out->calls = 0;
     hipLaunchKernelGGL(bmu_centre_kernel, dim3((unsigned)(centre_bytes / 256)), dim3(1024), 0, ctx->stream, W, K, D,
                        out->centre, out->scal);
+    if (wide_split) {
+        if (int rc = check_hip(ctx, hipGetLastError(), "bmu_centre launch")) return rc;
+        return bmu_wide_prepare(ctx, W, K, D, *out, qe, small);
+    }
     // one thread per element of the padded stage matrix and of the transposed copy, one wavefront per four nodes
     long long elems = (long long)kpad * nch * stride;
     if (elems < (long long)kpad * 16) elems = (long long)kpad * 16;
@@ -2556,10 +2180,9 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
         sp.wwin = out->wwin;
         sp.kb_count = kb;
         sp.tail_r = tail_r;
-        sp.nch16 = nch16;
         sp.row_bytes = split_row_bytes(kb, tail_r > 0);
         sp.stage16_bytes = (int)stage16_one;
-        const long long slots = (long long)kpad * nch16 * (kb * 16 + (tail_r ? 16 : 0));
+        const long long slots = (long long)kpad * (kb * 16 + (tail_r ? 16 : 0));
         if (elems < slots) elems = slots;
     }
     hipLaunchKernelGGL(bmu_prep_kernel, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0, ctx->stream, W, K, D, kpad,
@@ -2588,29 +2211,6 @@ static int launch_bmu_wide(som_ctx* ctx, const BmuArgs& a)
     return check_hip(ctx, hipGetLastError(), "bmu (wide) kernel launch");
 }
 
-static int launch_bmu_split_wide(som_ctx* ctx, const BmuArgs& a, int nch16)
-{
-    constexpr size_t lds_bytes = 2 * (size_t)split_stage_f4(4) * 16;
-    static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
-    bool& attr_set = attr_set_dev[ctx->device];
-    if (!attr_set) {
-        if (int rc = check_hip(ctx,
-                               hipFuncSetAttribute(reinterpret_cast<const void*>(bmu_split_wide_kernel),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes),
-                               "raising the dynamic LDS limit"))
-            return rc;
-        attr_set = true;
-    }
-    // the pass's samples as bf16 parts first
-    const int64_t groups8 = a.m * nch16 * 8;
-    hipLaunchKernelGGL(bmu_split_convert_kernel, dim3((unsigned)((groups8 + 255) / 256)), dim3(256), 0, ctx->stream, a, nch16);
-    if (int rc = check_hip(ctx, hipGetLastError(), "bmu (split, wide) conversion launch")) return rc;
-    const int64_t per_group = (int64_t)kWavesPerGroup * 32;
-    const int64_t groups = (a.m + per_group - 1) / per_group;
-    hipLaunchKernelGGL(bmu_split_wide_kernel, dim3((unsigned)groups), dim3(kThreads), lds_bytes, ctx->stream, a);
-    return check_hip(ctx, hipGetLastError(), "bmu (split, wide) kernel launch");
-}
-
 // grid of the candidate kernels: the tiles of the longest list they may serve, at most kCandGrid workgroups
 static unsigned cand_grid(const BmuArgs& a, int64_t per_tile)
 {
@@ -2636,24 +2236,6 @@ static int launch_bmu_wide_cand(som_ctx* ctx, const BmuArgs& a)
     }
     hipLaunchKernelGGL(kern, dim3(cand_grid(a, (int64_t)kWavesPerGroup * 32)), dim3(kThreads), lds_bytes, ctx->stream, a);
     return check_hip(ctx, hipGetLastError(), "bmu (wide) candidate kernel launch");
-}
-
-static int launch_bmu_split_wide_cand(som_ctx* ctx, const BmuArgs& a)
-{
-    constexpr size_t lds_bytes = 2 * (size_t)split_stage_f4(4) * 16;
-    static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
-    bool& attr_set = attr_set_dev[ctx->device];
-    if (!attr_set) {
-        if (int rc = check_hip(ctx,
-                               hipFuncSetAttribute(reinterpret_cast<const void*>(bmu_split_wide_cand_kernel),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes),
-                               "raising the dynamic LDS limit"))
-            return rc;
-        attr_set = true;
-    }
-    hipLaunchKernelGGL(bmu_split_wide_cand_kernel, dim3(cand_grid(a, (int64_t)kWavesPerGroup * 32)), dim3(kThreads),
-                       lds_bytes, ctx->stream, a);
-    return check_hip(ctx, hipGetLastError(), "bmu (split, wide) candidate kernel launch");
 }
 
 template <int STEPS, int MS>
@@ -2845,29 +2427,8 @@ int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
 {
     int64_t kRowsPerPass = (int64_t)1 << 27;
     const int64_t m = a.m;
-    // the split search for D > 64 reads the pass's samples as bf16 parts from a workspace of its own: 256 bytes per
-    // sample and chunk of 64 features, at most kPartsBytes in all (shorter passes for wide rows)
-    if (prep.stage16 && prep.nch > 1) {
-        const size_t row_bytes = (size_t)prep.nch16 * 256;
-        int64_t rows = (int64_t)(kPartsBytes / row_bytes) / 128 * 128;
-        if (rows < 128) rows = 128;
-        if (rows < kRowsPerPass) kRowsPerPass = rows;
-        const size_t need = (size_t)(m < kRowsPerPass ? m : kRowsPerPass) * row_bytes;
-        if (need > ctx->parts_bytes) {
-            if (ctx->parts_blob) {
-                if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync before workspace growth")) return rc;
-                (void)hipFree(ctx->parts_blob);
-                ctx->parts_blob = nullptr;
-                ctx->parts_bytes = 0;
-            }
-            if (hipMalloc(&ctx->parts_blob, need) != hipSuccess) {
-                (void)hipGetLastError();
-                return fail(ctx, SOM_ENOMEM, "cannot allocate %zu bytes for the samples' bf16 parts", need);
-            }
-            ctx->parts_bytes = need;
-        }
-        a.parts = ctx->parts_blob;
-    }
+    const bool wide_split = prep.stage16 && prep.nch > 1;
+    if (wide_split) kRowsPerPass = (int64_t)1 << 24;      // (the wide search keeps some hundred bytes per sample of a pass)
     for (int64_t off = 0; off < m; off += kRowsPerPass) {
         BmuArgs b = a;
         b.m = m - off < kRowsPerPass ? m - off : kRowsPerPass;
@@ -2926,7 +2487,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     const bool cand_possible = a.K > 1 && a.K <= 65536 && a.m > (int64_t)kCandMin;
     a.cand_min = cand_possible ? kCandMin : 0xffffffffu;
     a.qe_part = ctx->qe_part;
-    a.counts_near = prep.stage16 && prep.nch == 1;
+    a.counts_near = prep.stage16 ? 1 : 0;
     // the list length restarts for every call (chunk): calls alternate between two counters, and each call's
     // exact pass clears the counter of the next one
     a.slot = 12 + 2 * (prep.calls & 1);
@@ -2944,8 +2505,48 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
         stop = ctx->prof_events[ctx->prof_used].second;
         ++ctx->prof_used;
     }
-    int rc = prep.nch > 1 ? (prep.stage16        ? launch_bmu_split_wide(ctx, a, prep.nch16)
-                             : prep.steps == 25 ? launch_bmu_wide<25>(ctx, a)
+    const bool wide_split = prep.stage16 && prep.nch > 1;
+    if (ctx->units == 0) {
+        int units = 0;
+        if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || units < 1)
+            units = 256;
+        ctx->units = units;
+    }
+    if (wide_split) {
+        const size_t need = bmu_wide_work_bytes(ctx, prep, a.K, a.D, a.m);
+        if (need > ctx->parts_bytes) {
+            if (ctx->parts_blob) {
+                if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync before workspace growth")) return rc;
+                (void)hipFree(ctx->parts_blob);
+                ctx->parts_blob = nullptr;
+                ctx->parts_bytes = 0;
+            }
+            if (hipMalloc(&ctx->parts_blob, need) != hipSuccess) {
+                (void)hipGetLastError();
+                return fail(ctx, SOM_ENOMEM, "cannot allocate %zu bytes for the wide search's workspace", need);
+            }
+            ctx->parts_bytes = need;
+        }
+        if (int rc = bmu_wide_run(ctx, prep, a, ctx->parts_blob)) return rc;
+        if (stop) (void)hipEventRecord(stop, ctx->stream);
+        if (a.K > 1) {
+            if (int rc = bmu_wide_recheck(ctx, prep, a, ctx->parts_blob)) return rc;
+            BmuArgs b = a;                       // what the records left over; the distances come afterwards, for all samples
+            b.d2 = nullptr;
+            b.qe = nullptr;
+            b.second_only = 1;
+            hipLaunchKernelGGL(bmu_exact_kernel<false>, dim3(1024), dim3(kExactThreads), 0, ctx->stream, b);
+            if (int rc = check_hip(ctx, hipGetLastError(), "bmu exact-pass launch")) return rc;
+        }
+        if (a.d2 || a.qe)
+            if (int rc = bmu_wide_distances(ctx, a)) return rc;
+        if (a.qe) {
+            hipLaunchKernelGGL(qe_finish_kernel, dim3(1), dim3(kQeSlots), 0, ctx->stream, a.qe_part, a.qe, a.scal);
+            return check_hip(ctx, hipGetLastError(), "quantisation-error reduction launch");
+        }
+        return SOM_OK;
+    }
+    int rc = prep.nch > 1 ? (prep.steps == 25   ? launch_bmu_wide<25>(ctx, a)
                              : prep.steps == 28 ? launch_bmu_wide<28>(ctx, a)
                                                 : launch_bmu_wide<32>(ctx, a))
                           : (prep.stage16 ? dispatch_bmu_split(ctx, prep.kb, prep.tail_r > 0, a) : dispatch_bmu(ctx, prep.steps, a));
@@ -2957,8 +2558,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     }
     if (stop) (void)hipEventRecord(stop, ctx->stream);
     if (cand_possible) {
-        rc = prep.nch > 1 ? (prep.stage16        ? launch_bmu_split_wide_cand(ctx, a)
-                             : prep.steps == 25 ? launch_bmu_wide_cand<25>(ctx, a)
+        rc = prep.nch > 1 ? (prep.steps == 25   ? launch_bmu_wide_cand<25>(ctx, a)
                              : prep.steps == 28 ? launch_bmu_wide_cand<28>(ctx, a)
                                                 : launch_bmu_wide_cand<32>(ctx, a))
                           : (prep.stage16 ? dispatch_bmu_split_cand(ctx, prep.kb, prep.tail_r > 0, a) : dispatch_bmu_cand(ctx, prep.steps, a));

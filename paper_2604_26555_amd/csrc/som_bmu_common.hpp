@@ -1,0 +1,132 @@
+// Device helpers shared by the best-matching-unit kernels (som_bmu.hip, som_bmu_wide.hip).
+#pragma once
+
+#include "som_internal.hpp"
+
+#include <hip/amd_detail/amd_hip_unsafe_atomics.h>
+
+namespace som {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ double wave_sum(double v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+
+constexpr int kScalLo = 8;        // scal[8], scal[9]: bits of the largest |w - hi|^2 and |w - hi - lo|^2 (split search)
+
+constexpr float kSplitPadNorm = -3.0e38f;     // padding nodes of the split search: finite, so that position bits cannot make a NaN
+
+// Sum of distances and squared distances of a workgroup's samples -> one of kQeSlots partial-sum slots.  Every
+// wavefront adding to the same two words would serialise tens of thousands of atomics on one address; one pair
+// per workgroup spread over 256 slots does not show in the kernel time.  Called by all threads of the workgroup.
+// near: the split searches also count this lane's near ties, into kQeSlots further slots (counts are whole numbers: exact).
+__device__ __forceinline__ void group_qe_add(double* __restrict__ part, double qs, double qs2, int near = 0)
+{
+    __shared__ double wsum[16][2];
+    __shared__ int wnear[16];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) near += __shfl_xor(near, o);
+    qs = wave_sum(qs);
+    qs2 = wave_sum(qs2);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0) {
+        wsum[wave][0] = qs;
+        wsum[wave][1] = qs2;
+        wnear[wave] = near;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t0 = 0.0, t1 = 0.0;
+        int t2 = 0;
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+            t0 += wsum[w][0];
+            t1 += wsum[w][1];
+            t2 += wnear[w];
+        }
+        if (t2 != 0) unsafeAtomicAdd(&part[2 * kQeSlots + (blockIdx.x & (kQeSlots - 1))], (double)t2);
+        if (t0 != 0.0 || t1 != 0.0) {
+            const int slot = blockIdx.x & (kQeSlots - 1);
+            unsafeAtomicAdd(&part[2 * slot], t0);
+            unsafeAtomicAdd(&part[2 * slot + 1], t1);
+        }
+    }
+}
+
+// Append sample i (and its score cut) to the re-decision list for every lane with `push` set: one atomic per wavefront (the list
+// length is a single word; one atomic per listed sample serialises on it when a tenth of all samples is listed).
+// Called in converged control flow by all lanes of the wavefront.
+__device__ __forceinline__ void list_push(unsigned int* __restrict__ counter, uint32_t* __restrict__ list,
+                                          float* __restrict__ cutv, bool push, int64_t i, float cut)
+{
+    const unsigned long long mask = __ballot(push);
+    if (mask == 0ull) return;
+    const int lane = threadIdx.x & 63;
+    const int leader = __ffsll((long long)mask) - 1;
+    unsigned int base = 0u;
+    if (lane == leader) base = atomicAdd(counter, (unsigned int)__popcll(mask));
+    base = __shfl(base, leader);
+    const unsigned int below = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
+    if (push) {
+        list[base + below] = (uint32_t)i;
+        if (cutv) cutv[base + below] = cut;     // scores at or above this value may belong to the true winner
+    }
+}
+
+// A sample whose few candidates the search already knows (kPairs; their ids are in a.pairs) goes on the pair list, which
+// grows down from the end of the same array.
+constexpr float kNotListed = __builtin_nanf("");
+constexpr float kPairs = __builtin_inff();
+
+// sixteen bytes from a 4-byte aligned address in one load (global memory needs no more than dword alignment)
+__device__ __forceinline__ float4 load4(const float* p)
+{
+    float4 v;
+    __builtin_memcpy(&v, p, sizeof(v));
+    return v;
+}
+
+// plain v_max_f32: the scores are never signalling NaNs worth quieting, and every VALU instruction here is paid
+// for in matrix time (float32 MFMA and the vector ALU share the same lanes)
+__device__ __forceinline__ float vmax(float a, float b)
+{
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// plain v_max3_f32, for the same reason
+__device__ __forceinline__ float vmax3(float a, float b, float c)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        hi[i] = (__bf16)v[i];
+        lo[i] = (__bf16)(v[i] - (float)hi[i]);
+    }
+}
+
+// the same, and what the first parts leave over is added to left2 (squares)
+__device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo, float& left2)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        hi[i] = (__bf16)v[i];
+        const float left = v[i] - (float)hi[i];
+        lo[i] = (__bf16)left;
+        left2 = fmaf(left, left, left2);
+    }
+}
+
+} // namespace som

@@ -1,0 +1,814 @@
+// Best-matching-unit search for rows wider than 64 features (the default there): the scores of bmu_split_kernel
+// (som_bmu.hip: samples and weights cut into two bf16 parts, three bf16 MFMA products per float32 product) as a tiled
+// matrix product with the running arg-max behind it; N x K is never stored.
+//
+// Tile.  A workgroup of eight wavefronts forms 256 samples x 256 nodes at a time, features in chunks of 32; a wavefront
+// owns 64 samples x 128 nodes (four node blocks of 32, taken alternately by the two wavefronts of the same samples).
+// Per chunk it reads 12 + 4 fragments from LDS per 24 MFMAs, which keeps LDS at about half its rate; tiles of one block
+// of 32 samples per wavefront, as in the kernel before this one, read their samples' parts from memory once per 128
+// nodes, 32 bytes a lane at a stride of a whole row, and ran at a quarter of the matrix rate.
+//
+// Data path.  The weights are cut once per preparation and stored in the order in which the MFMA's lanes take them, so a
+// chunk of a node tile is 32 KB that go straight from memory to LDS (global_load_lds_dwordx4).  The samples are read in
+// float32, 128 contiguous bytes of a row per four lanes, centred, cut and written to LDS by the workgroup itself, for
+// every node tile again: the vector instructions (64 per thread and chunk) run beside 48 MFMAs, while a conversion pass
+// of its own would move every row twice more through memory (it took 0.3 ms of 3.2 at 10^6 x 200).  Both operands are
+// double-buffered; one barrier per chunk.  Chunks run on without a break across node tiles: a tile's scores are folded
+// while the next tile's first chunk is on the matrix pipe.
+//
+// Accumulation.  A chunk's products are summed on their own from zero, the small ones (lo hi, hi lo) first, and then
+// added to the tile's accumulators: the roundings inside a chunk are relative to |x_chunk| |w_chunk|, which add up to at
+// most |x| |w| over the chunks (Cauchy-Schwarz), instead of growing with the number of features.
+//
+// After the tiles, bmu_wide_join_kernel takes every sample's winners over the node tiles, its error bound from the norms
+// formed on the way, and decides which samples are open: those whose candidates are all known get their ids written
+// down, the others go through the tile kernel again (CAND), which notes every node that reaches the sample's cut.
+// bmu_wide_exact_kernel decides both by direct float32 differences, and what it cannot serve is left to the all-nodes pass.
+#include "som_bmu_common.hpp"
+
+#include <math.h>
+
+namespace som {
+
+constexpr int kWThreads = 512;
+constexpr int kWTile = 256;                       // samples, and nodes, of a tile
+constexpr int kWChunk = 32;                       // features of a chunk
+constexpr int kWBuf = kWTile * kWChunk * 4;       // bytes of an operand's chunk in LDS (hi and lo parts)
+constexpr int kWState = 12;                       // words of running state per lane
+constexpr size_t kWLds = 4 * (size_t)kWBuf + (kWThreads * kWState + kWTile) * sizeof(float);
+constexpr int kWIds = 14;                         // candidate ids of a record: 4 bytes count, fourteen 16-bit ids
+constexpr int kWRecord = 8;                       // 32-bit words of a record
+
+struct WideArgs {
+    const char* blob;        // weights' parts, [node tile][chunk][node block 8][kb 2][hi | lo][64 lanes][8] bf16
+    const float* norms;      // [node tiles * 256] -|w|^2 / 2
+    int nch, tiles;          // chunks of a row, node tiles
+    int splits, per_split;   // workgroups that share a sample tile, node tiles of each
+    int64_t rows;            // m of the pass
+    float4* best;            // [splits][m] best, second best class winner, highest of all others; id of the best (bits)
+    uint32_t* id2;           // [splits][m] id of the second
+    float4* norm;            // [m] |x|^2, weighted |x|^2, |x - hi|^2
+    uint32_t* record;        // [m][kWRecord] candidates of the listed samples
+    uint32_t cand_min;       // lists up to this length go to the all-nodes pass at once
+};
+
+// 64 lanes x 16 bytes, from the lanes' own addresses to 1 KB of LDS at offset lds (below 64 KB); counted by vmcnt
+__device__ __forceinline__ void lds_load16(const void* from, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(from) : "memory");
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Weight preparation: one wavefront per node cuts its row into parts in fragment order and sums its norms; the rest of the
+// grid writes the transposed copy that the all-nodes pass reads.
+// ---------------------------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) bmu_wide_prep_kernel(const float* __restrict__ W, int K, int D, int kpad, int tiles, int nch,
+                                                            const float* __restrict__ centre, char* __restrict__ blob,
+                                                            float* __restrict__ norms, float* __restrict__ wt,
+                                                            unsigned int* __restrict__ scal, double* __restrict__ qe,
+                                                            int32_t* __restrict__ small)
+{
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e < 2 && qe) qe[e] = 0.0;
+    if (e < 4 && small) small[e] = 0;
+    const int node_groups = tiles * kWTile / 4;               // workgroups that take four nodes each
+    if ((int)blockIdx.x >= node_groups) {
+        const int64_t t = (int64_t)(blockIdx.x - node_groups) * 256 + threadIdx.x;
+        if (t < (int64_t)D * kpad) {
+            const int f = (int)(t / kpad), k = (int)(t - (int64_t)f * kpad);
+            wt[t] = k < K ? W[(size_t)k * D + f] : 0.0f;
+        }
+        return;
+    }
+    __shared__ float most[4][3];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int k = blockIdx.x * 4 + wave;
+    double nrm = 0.0;
+    float lo2 = 0.0f, rest2 = 0.0f;
+    for (int o = lane; o < nch * 4; o += 64) {
+        float v[8];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int f0 = 8 * o + 4 * h, start = f0 < D - 4 ? f0 : D - 4, shift = f0 - start;    // own elements: >= shift
+            float4 w4 = {0.f, 0.f, 0.f, 0.f}, c4 = w4;
+            if (k < K) {
+                w4 = load4(W + (size_t)k * D + start);
+                c4 = load4(centre + start);
+            }
+            v[4 * h + 0] = shift <= 0 ? w4.x - c4.x : 0.0f;
+            v[4 * h + 1] = shift <= 1 ? w4.y - c4.y : 0.0f;
+            v[4 * h + 2] = shift <= 2 ? w4.z - c4.z : 0.0f;
+            v[4 * h + 3] = shift <= 3 ? w4.w - c4.w : 0.0f;
+        }
+        bf16x8 hi, lo;
+        split8(v, hi, lo, lo2);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            nrm += (double)v[t] * (double)v[t];
+            const float left = (v[t] - (float)hi[t]) - (float)lo[t];
+            rest2 = fmaf(left, left, rest2);
+        }
+        const int chunk = o >> 2, kb = (o >> 1) & 1, g = o & 1;
+        char* frag = blob + ((size_t)(k / kWTile) * nch + chunk) * kWBuf + (size_t)((((k % kWTile) >> 5) * 2 + kb) * 2) * 1024 +
+                     (g * 32 + (k & 31)) * 16;
+        *reinterpret_cast<bf16x8*>(frag) = hi;
+        *reinterpret_cast<bf16x8*>(frag + 1024) = lo;
+    }
+    nrm = wave_sum(nrm);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lo2 += __shfl_xor(lo2, o);
+        rest2 += __shfl_xor(rest2, o);
+    }
+    if (lane == 0) {
+        const float nh = (float)(-0.5 * nrm);
+        norms[k] = (k < K && nh > kSplitPadNorm) ? nh : kSplitPadNorm;
+        float up = (float)nrm;
+        if ((double)up < nrm) up = nextafterf(up, INFINITY);
+        most[wave][0] = k < K ? up : 0.0f;
+        most[wave][1] = lo2;
+        most[wave][2] = rest2;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        const int t = threadIdx.x;
+        const float m = fmaxf(fmaxf(most[0][t], most[1][t]), fmaxf(most[2][t], most[3][t]));
+        if (m > 0.0f) atomicMax(&scal[t == 0 ? 0 : kScalLo + t - 1], __float_as_uint(m));
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// The tiles.  CAND: the samples are the entries of the re-decision list, and every node that reaches the entry's cut is
+// appended to the sample's record (rare: an atomic each); the scores are those of the first pass bit for bit.
+// ---------------------------------------------------------------------------------------------------------
+template <bool CAND>
+__device__ __forceinline__ void wide_tile(const BmuArgs& a, const WideArgs& p, int64_t tile, int split, int64_t total, char* lds)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave & 1, ws = wave >> 1;               // which node blocks (alternating), which 64 samples
+    const int j = lane & 31, g = lane >> 5;
+    const int t_lo = split * p.per_split;
+    const int t_hi = t_lo + p.per_split < p.tiles ? t_lo + p.per_split : p.tiles;
+    const int nch = p.nch, nq = (t_hi - t_lo) * nch;
+    if (nq <= 0) return;                                    // (whole workgroup)
+    char* const bufA = lds;
+    char* const bufB = lds + 2 * kWBuf;
+    float* const state = reinterpret_cast<float*>(lds + 4 * kWBuf) + wave * (kWState * 64) + lane;
+    float* const nbuf = reinterpret_cast<float*>(lds + 4 * kWBuf) + kWThreads * kWState;
+    const unsigned ldsA = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) char*)bufA);
+
+    // ---- the samples this thread brings in: two rows, eight features (an octet) of each per chunk
+    const int oct = tid & 3;
+    const float* xrow[2];
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        int64_t i = tile * kWTile + (tid >> 2) + 128 * it;
+        i = i < total ? i : total - 1;
+        if constexpr (CAND) i = (int64_t)a.recheck[i];
+        xrow[it] = a.X + (a.idx ? (int64_t)a.idx[i] : i) * a.ldx;
+    }
+    float xs[2] = {0.f, 0.f}, left2[2] = {0.f, 0.f};
+    float4 xr[2][2];
+    auto load_item = [&](int it, int ch) {
+        const int f0 = ch * kWChunk + oct * 8;
+        xr[it][0] = load4(xrow[it] + (f0 < a.D - 4 ? f0 : a.D - 4));
+        xr[it][1] = load4(xrow[it] + (f0 + 4 < a.D - 4 ? f0 + 4 : a.D - 4));
+    };
+    float4 cen[2];
+    auto load_centre = [&](int ch) {
+        const int f0 = ch * kWChunk + oct * 8;
+        cen[0] = load4(a.centre + (f0 < a.D - 4 ? f0 : a.D - 4));
+        cen[1] = load4(a.centre + (f0 + 4 < a.D - 4 ? f0 + 4 : a.D - 4));
+    };
+    // centred, cut, written to buffer `buf`: fragment [sample block][kb][hi | lo], lane slot 32 g + (sample ^ 2 octet) so that
+    // eight neighbouring lanes (two samples, four octets) hit different banks
+    auto convert_item = [&](int it, int ch, int buf, bool norms) {
+        float v[8] = {xr[it][0].x - cen[0].x, xr[it][0].y - cen[0].y, xr[it][0].z - cen[0].z, xr[it][0].w - cen[0].w,
+                      xr[it][1].x - cen[1].x, xr[it][1].y - cen[1].y, xr[it][1].z - cen[1].z, xr[it][1].w - cen[1].w};
+        const int f0 = ch * kWChunk + oct * 8;
+        if (ch == nch - 1) {                                // windows shifted back at the end of the row: own elements only
+            const int s0 = f0 - (a.D - 4), s1 = s0 + 4;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                v[t] = t >= s0 ? v[t] : 0.0f;
+                v[4 + t] = t >= s1 ? v[4 + t] : 0.0f;
+            }
+        }
+        bf16x8 hi, lo;
+        if (!CAND && norms) {
+            split8(v, hi, lo, left2[it]);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) xs[it] = fmaf(v[t], v[t], xs[it]);
+        } else {
+            split8(v, hi, lo);
+        }
+        const int s = (tid >> 2) + 128 * it;
+        char* frag = bufB + buf * kWBuf + ((s >> 5) * 4 + (oct >> 1) * 2) * 1024 + ((oct & 1) * 32 + ((s & 31) ^ (2 * oct))) * 16;
+        *reinterpret_cast<bf16x8*>(frag) = hi;
+        *reinterpret_cast<bf16x8*>(frag + 1024) = lo;
+    };
+    // chunk ch of node tile t into buffer `buf`: every wavefront 4 KB
+    auto load_weights = [&](int t, int ch, int buf) {
+        const char* from = p.blob + ((size_t)t * nch + ch) * kWBuf + wave * 4096 + lane * 16;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) lds_load16(from + q * 1024, ldsA + buf * kWBuf + wave * 4096 + q * 1024);
+    };
+
+    // ---- running state per lane, sample block and row parity (CAND: none): best, runner-up, where the best came from
+    float cut[2];
+    int64_t sample[2];
+    if constexpr (CAND) {
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb) {
+            const int64_t e = tile * kWTile + ws * 64 + sb * 32 + j;
+            cut[sb] = e < total ? a.cutv[e] : NAN;          // no score compares >= NaN
+            sample[sb] = (int64_t)a.recheck[e < total ? e : total - 1];
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            state[(3 * c + 0) * 64] = -INFINITY;
+            state[(3 * c + 1) * 64] = -INFINITY;
+            state[(3 * c + 2) * 64] = 0.0f;
+        }
+    }
+
+    floatx16 acc[4][2];
+    // the scores of node block nb of tile t: as bmu_split_tile's fold, two classes (row parity) per lane; together with the
+    // lane halves and the two wavefronts of a sample, neighbouring nodes fall into eight classes
+    auto fold = [&](int nb, int t) {
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb) {
+            if constexpr (CAND) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (acc[nb][sb][r] >= cut[sb]) {
+                        const unsigned id = (unsigned)(t * kWTile + (2 * nb + wn) * 32 + 8 * (r >> 2) + 4 * g + (r & 3));
+                        uint32_t* rec = p.record + sample[sb] * kWRecord;
+                        const unsigned at = atomicAdd(rec, 1u);
+                        if (at < (unsigned)kWIds) reinterpret_cast<uint16_t*>(rec + 1)[at] = (uint16_t)id;
+                    }
+            } else {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    float* st = state + (sb * 2 + c) * 3 * 64;
+                    float best = st[0], second = st[64];
+                    const float before = best;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int r0 = 4 * q + c, r1 = r0 + 2;
+                        const float v1 = __uint_as_float((__float_as_uint(acc[nb][sb][r0]) & 0xfffffff8u) | (unsigned)(r0 >> 1));
+                        const float v2 = __uint_as_float((__float_as_uint(acc[nb][sb][r1]) & 0xfffffff8u) | (unsigned)(r1 >> 1));
+                        const float mid = __builtin_amdgcn_fmed3f(best, v1, v2);
+                        best = vmax3(best, v1, v2);
+                        second = vmax(second, mid);
+                    }
+                    st[0] = best;
+                    st[64] = second;
+                    if (best > before) st[128] = __int_as_float(4 * t + nb);
+                }
+            }
+        }
+    };
+    // blocks of a tile that hold any node at all
+    auto blocks_of = [&](int t) {
+        const int left = (a.K - t * kWTile + 31) >> 5;
+        return left < 8 ? left : 8;
+    };
+
+    // ---- first chunk, and the second one's samples on their way
+    load_weights(t_lo, 0, 0);
+    load_centre(0);
+    load_item(0, 0);
+    load_item(1, 0);
+    if (tid < kWTile) nbuf[tid] = p.norms[t_lo * kWTile + tid];
+    convert_item(0, 0, 0, true);
+    convert_item(1, 0, 0, true);
+    load_item(0, nch > 1 ? 1 : 0);
+    load_item(1, nch > 1 ? 1 : 0);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+    int t = t_lo, ch = 0;                       // of chunk q
+    for (int q = 0; q < nq; ++q) {
+        const int buf = q & 1;
+        int ch1 = ch + 1, t1 = t;               // of chunk q + 1
+        if (ch1 == nch) {
+            ch1 = 0;
+            ++t1;
+        }
+        const int ch2 = ch1 + 1 == nch ? 0 : ch1 + 1;
+        const bool more = q + 1 < nq;
+        const bool new_tile = more && ch1 == 0;
+        float norm_next = 0.0f;
+        // (the last iteration requests its own chunk's successor nowhere: its buffers stay unused)
+        if (more) load_weights(t1, ch1, buf ^ 1);
+        if (new_tile && tid < kWTile) norm_next = p.norms[t1 * kWTile + tid];
+        load_centre(ch1);
+        const char* fa = bufA + buf * kWBuf + wn * 4096 + lane * 16;
+        const char* fb = bufB + buf * kWBuf + ws * 8192;
+        bf16x8 xh[2][2], xl[2][2];
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            const char* f = fb + kb * 2048 + (g * 32 + (j ^ (4 * kb + 2 * g))) * 16;
+#pragma unroll
+            for (int sb = 0; sb < 2; ++sb) {
+                xh[sb][kb] = *reinterpret_cast<const bf16x8*>(f + sb * 4096);
+                xl[sb][kb] = *reinterpret_cast<const bf16x8*>(f + sb * 4096 + 1024);
+            }
+        }
+        const int blocks = blocks_of(t);
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+            const bool live = 2 * nb + wn < blocks;         // (a block of padding nodes is left out)
+            if (live) {
+                const char* f = fa + nb * 8192;
+                bf16x8 wh[2], wl[2];
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
+                    wh[kb] = *reinterpret_cast<const bf16x8*>(f + kb * 2048);
+                    wl[kb] = *reinterpret_cast<const bf16x8*>(f + kb * 2048 + 1024);
+                }
+                floatx16 part[2];
+#pragma unroll
+                for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) part[sb][r] = 0.0f;
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+                    for (int sb = 0; sb < 2; ++sb) part[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh[kb], xl[sb][kb], part[sb], 0, 0, 0);
+#pragma unroll
+                    for (int sb = 0; sb < 2; ++sb) part[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl[kb], xh[sb][kb], part[sb], 0, 0, 0);
+                }
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int sb = 0; sb < 2; ++sb) part[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wh[kb], xh[sb][kb], part[sb], 0, 0, 0);
+                if (ch == 0) {
+                    // the previous tile's scores are folded beside these MFMAs, then the accumulators start at -|w|^2 / 2
+                    if (q > 0) fold(nb, t - 1);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const float4 n4 = *reinterpret_cast<const float4*>(nbuf + (2 * nb + wn) * 32 + 8 * u + 4 * g);
+#pragma unroll
+                        for (int sb = 0; sb < 2; ++sb) {
+                            acc[nb][sb][4 * u + 0] = n4.x;
+                            acc[nb][sb][4 * u + 1] = n4.y;
+                            acc[nb][sb][4 * u + 2] = n4.z;
+                            acc[nb][sb][4 * u + 3] = n4.w;
+                        }
+                    }
+                }
+#pragma unroll
+                for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[nb][sb][r] += part[sb][r];
+            } else if (ch == 0 && q > 0) {
+                fold(nb, t - 1);                            // (the last tile only: its predecessor's blocks were whole)
+            }
+            // the next chunk's samples, a quarter of the way on: theirs are the loads of the iteration before
+            if (nb == 1 || nb == 2) {
+                const int it = nb - 1;
+                if (more) convert_item(it, ch1, buf ^ 1, q + 1 < nch);
+                load_item(it, ch2);
+            }
+        }
+        if (ch == nch - 1 && new_tile) {
+            // every wavefront has read this tile's norms long ago (chunk 0, nch >= 3 chunks and as many barriers back)
+            if (tid < kWTile) nbuf[tid] = norm_next;
+        }
+        // the weights' chunk is complete (the four loads behind it are the samples' of the chunk after next), and so are
+        // the LDS writes
+        asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        t = t1;
+        ch = ch1;
+    }
+    {
+        const int blocks = blocks_of(t_hi - 1);
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+            if (2 * nb + wn < blocks) fold(nb, t_hi - 1);
+    }
+    if constexpr (CAND) return;
+
+    // ---- norms of the samples (the first split's workgroup has them as well as any)
+    if (split == 0) {
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            // four lanes hold a sample's octets; the first two octets of a chunk are in the accumulator of both large MFMAs
+            float s = xs[it], w = (oct < 2 ? 4.0f : 1.0f) * xs[it], l = left2[it];
+            s += __shfl_xor(s, 1);
+            w += __shfl_xor(w, 1);
+            l += __shfl_xor(l, 1);
+            s += __shfl_xor(s, 2);
+            w += __shfl_xor(w, 2);
+            l += __shfl_xor(l, 2);
+            const int64_t i = tile * kWTile + (tid >> 2) + 128 * it;
+            if (oct == 0 && i < total) p.norm[i] = make_float4(s, w, l, 0.0f);
+        }
+    }
+    // ---- a sample's eight class winners of this workgroup: the two best with their ids, and the highest of all others
+    __syncthreads();
+    if (tid < kWTile) {
+        const int64_t i = tile * kWTile + tid;
+        const float* base = reinterpret_cast<const float*>(lds + 4 * kWBuf);
+        float b1 = -INFINITY, b2 = -INFINITY, others = -INFINITY;
+        int id1 = 0, id2 = 0;
+#pragma unroll
+        for (int wn1 = 0; wn1 < 2; ++wn1)
+#pragma unroll
+            for (int g1 = 0; g1 < 2; ++g1)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const float* st = base + (2 * (tid >> 6) + wn1) * (kWState * 64) + ((((tid >> 5) & 1) * 2 + c) * 3) * 64 +
+                                      g1 * 32 + (tid & 31);
+                    const float v = st[0];
+                    const int where = __float_as_int(st[128]);
+                    const int r = 2 * (int)(__float_as_uint(v) & 7u) + c;
+                    const int id = (where >> 2) * kWTile + (2 * (where & 3) + wn1) * 32 + 8 * (r >> 2) + 4 * g1 + (r & 3);
+                    others = fmaxf(others, st[64]);
+                    if (v > b1) {
+                        others = fmaxf(others, b2);
+                        b2 = b1;
+                        id2 = id1;
+                        b1 = v;
+                        id1 = id;
+                    } else if (v > b2) {
+                        others = fmaxf(others, b2);
+                        b2 = v;
+                        id2 = id;
+                    } else {
+                        others = fmaxf(others, v);
+                    }
+                }
+        if (i < total) {
+            p.best[(size_t)split * p.rows + i] = make_float4(b1, b2, others, __int_as_float(id1));
+            p.id2[(size_t)split * p.rows + i] = (uint32_t)id2;
+        }
+    }
+}
+
+// The splits of a sample tile get workgroup numbers 8 apart: they run on the same XCD at about the same time, and its L2
+// serves the rows to all but the first.
+__global__ void __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) bmu_wide_split_kernel(const BmuArgs a, const WideArgs p)
+{
+    extern __shared__ float4 wide_lds[];
+    const int64_t blk = blockIdx.x / (8 * p.splits);
+    const int within = (int)(blockIdx.x % (8 * p.splits));
+    const int64_t tile = blk * 8 + within % 8;
+    if (tile * kWTile >= a.m) return;
+    wide_tile<false>(a, p, tile, within / 8, a.m, reinterpret_cast<char*>(wide_lds));
+}
+
+// a fixed grid walks the (tile of the list, node tile) units: a short list still spreads over the chip
+__global__ void __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) bmu_wide_split_cand_kernel(const BmuArgs a, const WideArgs p)
+{
+    extern __shared__ float4 wide_lds[];
+    const unsigned int count = a.scal[a.slot];
+    if (count <= p.cand_min) return;
+    WideArgs one = p;
+    one.per_split = 1;
+    const int64_t units = ((int64_t)count + kWTile - 1) / kWTile * p.tiles;
+    for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+        wide_tile<true>(a, one, u / p.tiles, (int)(u % p.tiles), (int64_t)count, reinterpret_cast<char*>(wide_lds));
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Join: the winner over the splits, the sample's error bound, and the lists.
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kJoinThreads = 256;
+
+__global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuArgs a, const WideArgs p)
+{
+    __shared__ unsigned int wave_base[2][kJoinThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t i = (int64_t)blockIdx.x * kJoinThreads + tid;
+    const bool live = i < a.m;
+    bool close = false, open = false, near = false;
+    float cut = 0.0f;
+    if (live) {
+        float best = -INFINITY, second = -INFINITY;
+        int node = 0;
+        for (int s = 0; s < p.splits; ++s) {
+            const float4 r = p.best[(size_t)s * p.rows + i];
+            const bool up = r.x > best;
+            second = fmaxf(fmaxf(second, up ? best : r.x), fmaxf(r.y, r.z));
+            node = up ? __float_as_int(r.w) : node;
+            best = up ? r.x : best;
+        }
+        node = (node >= 0 && node < a.K) ? node : a.K - 1;       // (only padding or non-finite scores get here)
+        const float4 n = p.norm[i];
+        // The error of a score (as bmu_split_tile): what the cut drops, from the norms of the parts; a chunk's small products
+        // in the accumulator of four MFMAs, its large ones in two and one (the weighted norm), each charged sixteen
+        // roundings of 2^-24 whatever the order of its additions; one rounding per chunk's addition to the tile's
+        // accumulators; six units for the centrings and -|w|^2 / 2.
+        constexpr float unit = 5.9604645e-08f;
+        auto root = [](float v) { return __builtin_amdgcn_sqrtf(v); };      // within a unit in the last place
+        const float wmax2 = __uint_as_float(a.scal[0]), wmax = root(wmax2) * 1.00001f;
+        const float lo_w = root(__uint_as_float(a.scal[kScalLo])) * 1.001f, rest_w = root(__uint_as_float(a.scal[kScalLo + 1])) * 1.001f;
+        // (float32 sums over up to 2^13 squares in this order are within 2^-14 of their own size)
+        const float nx = root(n.x) * 1.0002f, nl = root(n.z) * 1.0002f;
+        const float add = (float)(p.nch + 1) * 1.016f;
+        const float err_w = nl * (1.0078125f / 512.0f + 65.28f * unit) + root(n.y) * (1.0002f * 16.256f * unit) + nx * ((6.0f + add) * unit);
+        const float err_0 = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (65.28f * unit));
+        const float err_n = 0.5f * (6.0f + add) * unit;
+        const float wn = -2.0f * p.norms[node];
+        const float wb = fminf(root(wn) * 1.00001f, wmax);
+        const float err_b = err_w * wb + err_0 + err_n * wb * wb;
+        const float bits = fabsf(best) * (1.01f * 1.9073486e-06f);          // two scores' position bits
+        const float far2 = fmaxf(n.x * 1.0002f - 2.0f * best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
+        const float wo = fminf((nx + root(far2)) * 1.0001f, wmax);          // norm of any node as near as the winner
+        const float bound = err_b + err_w * wo + err_0 + err_n * wo * wo + bits;
+        close = a.K > 1 && !((best - second) > bound);
+        cut = best - bound;
+        a.bmu[i] = node;
+        if (a.qe) {
+            // the statistic n_recheck: best two scores inside the band that holds for any input
+            const float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(196 + (a.D + 63) / 64 + 1) * unit) + 12.0f * unit;
+            near = close || (a.K > 1 && !((best - second) > (root(n.x) * wmax + 0.5f * wmax2) * rel));
+        }
+        if (close) {
+            uint32_t* rec = p.record + i * kWRecord;
+            uint16_t* ids = reinterpret_cast<uint16_t*>(rec + 1);
+            int hits = 0;
+            open = a.K > 65536 || !(cut == cut);
+            for (int s = 0; s < p.splits && !open; ++s) {
+                const float4 r = p.best[(size_t)s * p.rows + i];
+                const uint32_t id2 = p.id2[(size_t)s * p.rows + i];
+                if (r.x >= cut && hits < kWIds) ids[hits++] = (uint16_t)__float_as_int(r.w);
+                if (r.y >= cut && hits < kWIds) ids[hits++] = (uint16_t)id2;
+                open = open || r.z >= cut || hits >= kWIds;
+            }
+            rec[0] = open ? 0u : (unsigned)hits;                 // an open sample's record is filled by the candidate pass
+        }
+    }
+    // both lists' entries of this workgroup with one atomic
+    const unsigned long long m_open = __ballot(close && open), m_known = __ballot(close && !open);
+    const auto below = [&](unsigned long long m) {
+        return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
+    };
+    if (lane == 0) {
+        wave_base[0][wave] = (unsigned)__popcll(m_open);
+        wave_base[1][wave] = (unsigned)__popcll(m_known);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        unsigned int n0 = 0, n1 = 0;
+        unsigned int at[2][kJoinThreads / 64];
+        for (int w = 0; w < kJoinThreads / 64; ++w) {
+            at[0][w] = n0;
+            at[1][w] = n1;
+            n0 += wave_base[0][w];
+            n1 += wave_base[1][w];
+        }
+        unsigned long long base = 0ull;
+        if (n0 | n1)
+            base = atomicAdd(reinterpret_cast<unsigned long long*>(&a.scal[a.slot]), (unsigned long long)n0 | ((unsigned long long)n1 << 32));
+        for (int w = 0; w < kJoinThreads / 64; ++w) {
+            wave_base[0][w] = (unsigned int)base + at[0][w];
+            wave_base[1][w] = (unsigned int)(base >> 32) + at[1][w];
+        }
+    }
+    __syncthreads();
+    if (close && open) {
+        const unsigned int at = wave_base[0][wave] + below(m_open);
+        a.recheck[at] = (uint32_t)i;
+        a.cutv[at] = cut;
+    } else if (close) {
+        a.recheck_end[-1 - (int64_t)(wave_base[1][wave] + below(m_known))] = (uint32_t)i;
+    }
+    if (a.qe) group_qe_add(a.qe_part, 0.0, 0.0, near ? 1 : 0);
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Direct differences over the recorded candidates of both lists: sixteen lanes per sample, each a sixteenth of the features;
+// lowest distance, then lowest node index.  Samples without a usable record (more than fourteen candidates, none, or a
+// list that the candidate pass did not serve) go to the second list, which the all-nodes pass takes.
+// ---------------------------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) bmu_wide_exact_kernel(const BmuArgs a, const WideArgs p)
+{
+    const unsigned int n_open = a.scal[a.slot], n_known = a.scal[a.slot + 1], count = n_open + n_known;
+    const int sub = threadIdx.x & 15;
+    constexpr unsigned int per_group = 256 / 16;
+    for (unsigned int p0 = blockIdx.x * per_group; p0 < count; p0 += gridDim.x * per_group) {
+        const unsigned int q = p0 + (threadIdx.x >> 4);
+        const bool live = q < count;
+        const unsigned int qc = live ? q : count - 1;
+        const int64_t i = qc < n_open ? (int64_t)a.recheck[qc] : (int64_t)a.recheck_end[-1 - (int64_t)(qc - n_open)];
+        const uint32_t* rec = p.record + i * kWRecord;
+        const uint32_t found = rec[0];
+        const int64_t row = a.idx ? (int64_t)a.idx[i] : i;
+        const float* xr = a.X + row * a.ldx;
+        bool served = found > 0u && found <= (uint32_t)kWIds;
+        const int c = served ? (int)found : 0;
+        const uint16_t* ids = reinterpret_cast<const uint16_t*>(rec + 1);
+        float bd = INFINITY;
+        int bk = 0x7fffffff;
+        constexpr int kBatch = 2;                  // most samples have two candidates
+        for (int t0 = 0; t0 < kWIds; t0 += kBatch) {
+            if (__ballot(c > t0) == 0ull) break;
+            int node[kBatch];
+            float d[kBatch];
+#pragma unroll
+            for (int tt = 0; tt < kBatch; ++tt) {
+                const int k = t0 + tt < c ? (int)ids[t0 + tt] : -1;
+                node[tt] = k < a.K ? k : -1;
+                d[tt] = 0.0f;
+            }
+            for (int f0 = 0; f0 < a.D; f0 += 64) {
+                float xv[4], wv[kBatch][4];
+                int fo[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int f = f0 + 16 * u + sub;
+                    fo[u] = f < a.D ? f : -1;
+                    xv[u] = xr[fo[u] >= 0 ? f : a.D - 1];
+                }
+#pragma unroll
+                for (int tt = 0; tt < kBatch; ++tt) {
+                    const float* wr = a.W + (size_t)(node[tt] >= 0 ? node[tt] : 0) * a.D;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) wv[tt][u] = wr[fo[u] >= 0 ? fo[u] : a.D - 1];
+                }
+#pragma unroll
+                for (int tt = 0; tt < kBatch; ++tt)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const float df = fo[u] >= 0 ? xv[u] - wv[tt][u] : 0.0f;
+                        d[tt] = fmaf(df, df, d[tt]);
+                    }
+            }
+#pragma unroll
+            for (int tt = 0; tt < kBatch; ++tt) {
+                float v = d[tt];
+                v += __shfl_xor(v, 8);
+                v += __shfl_xor(v, 4);
+                v += __shfl_xor(v, 2);
+                v += __shfl_xor(v, 1);
+                const int k = node[tt];
+                if (k >= 0 && (v < bd || (v == bd && k < bk))) {
+                    bd = v;
+                    bk = k;
+                }
+            }
+        }
+        served = served && bk < a.K;
+        const bool mine = live && sub == 0;
+        if (mine && served) a.bmu[i] = bk;
+        list_push(&a.scal[a.slot2], a.recheck2, nullptr, mine && !served, i, 0.0f);
+    }
+}
+
+// distances to the winners, where they are asked for: direct differences on the values as given, sixteen lanes per sample
+__global__ void __launch_bounds__(256) bmu_wide_distance_kernel(const BmuArgs a)
+{
+    const int sub = threadIdx.x & 15;
+    constexpr int per_group = 256 / 16;
+    double qs = 0.0, qs2 = 0.0;
+    for (int64_t p0 = (int64_t)blockIdx.x * per_group; p0 < a.m; p0 += (int64_t)gridDim.x * per_group) {
+        const int64_t i = p0 + (threadIdx.x >> 4);
+        const bool live = i < a.m;
+        const int64_t ic = live ? i : a.m - 1;
+        const float* xr = a.X + (a.idx ? (int64_t)a.idx[ic] : ic) * a.ldx;
+        const int k = a.bmu[ic];
+        const float* wr = a.W + (size_t)(k >= 0 && k < a.K ? k : 0) * a.D;
+        float d = 0.0f;
+        const int whole = a.D / 64 * 64;
+        for (int f = 4 * sub; f < whole; f += 64) {
+            const float4 x = load4(xr + f), w = load4(wr + f);
+            const float d0 = x.x - w.x, d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
+            d = fmaf(d0, d0, d);
+            d = fmaf(d1, d1, d);
+            d = fmaf(d2, d2, d);
+            d = fmaf(d3, d3, d);
+        }
+        for (int f = whole + sub; f < a.D; f += 16) {
+            const float df = xr[f] - wr[f];
+            d = fmaf(df, df, d);
+        }
+        d += __shfl_xor(d, 8);
+        d += __shfl_xor(d, 4);
+        d += __shfl_xor(d, 2);
+        d += __shfl_xor(d, 1);
+        if (live && sub == 0) {
+            if (a.d2) a.d2[i] = d;
+            qs += sqrt((double)d);
+            qs2 += (double)d;
+        }
+    }
+    if (a.qe) group_qe_add(a.qe_part, qs, qs2);
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------------------------------------
+size_t bmu_wide_blob_bytes(int32_t K, int32_t D)
+{
+    const size_t tiles = ((size_t)K + kWTile - 1) / kWTile, nch = ((size_t)D + kWChunk - 1) / kWChunk;
+    return tiles * nch * kWBuf + tiles * kWTile * sizeof(float);
+}
+
+int bmu_wide_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, const BmuPrep& prep, double* qe, int32_t* small)
+{
+    const int tiles = (K + kWTile - 1) / kWTile, nch = (D + kWChunk - 1) / kWChunk;
+    char* blob = (char*)prep.stage16;
+    float* norms = (float*)(blob + (size_t)tiles * nch * kWBuf);
+    const int64_t groups = (int64_t)tiles * kWTile / 4 + ((int64_t)D * prep.kpad + 255) / 256;
+    hipLaunchKernelGGL(bmu_wide_prep_kernel, dim3((unsigned)groups), dim3(256), 0, ctx->stream, W, K, D, prep.kpad, tiles, nch,
+                       prep.centre, blob, norms, prep.wt, prep.scal, qe, small);
+    return check_hip(ctx, hipGetLastError(), "bmu (wide) preparation launch");
+}
+
+// Workgroups per sample tile: enough that the compute units are busy to the end.  A unit takes one workgroup at a time
+// (LDS), so the time goes with rounds x node tiles per workgroup, plus about half a node tile's chunks for filling the
+// pipeline and writing the results.
+static int wide_splits(int64_t tiles_m, int tiles, int nch, int units)
+{
+    int best = 1;
+    double best_cost = 0.0;
+    for (int s = 1; s <= tiles && s <= 16; ++s) {
+        const int per = (tiles + s - 1) / s;
+        if ((tiles + per - 1) / per != s) continue;
+        const double rounds = (double)((tiles_m * s + units - 1) / units);
+        const double cost = rounds * ((double)per * nch + 3.0);
+        if (s == 1 || cost < best_cost * 0.98) {
+            best = s;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+static WideArgs wide_args(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t D, int64_t m)
+{
+    WideArgs p{};
+    p.tiles = (K + kWTile - 1) / kWTile;
+    p.nch = (D + kWChunk - 1) / kWChunk;
+    p.blob = (const char*)prep.stage16;
+    p.norms = (const float*)(p.blob + (size_t)p.tiles * p.nch * kWBuf);
+    p.splits = wide_splits((m + kWTile - 1) / kWTile, p.tiles, p.nch, ctx->units > 0 ? ctx->units : 256);
+    p.per_split = (p.tiles + p.splits - 1) / p.splits;
+    p.rows = m;
+    return p;
+}
+
+// bytes of the pass's workspace: per-split winners, norms, candidate records
+size_t bmu_wide_work_bytes(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t D, int64_t m)
+{
+    const WideArgs p = wide_args(ctx, prep, K, D, m);
+    return (size_t)m * ((size_t)p.splits * 20 + 16 + kWRecord * 4) + 64;
+}
+
+int bmu_wide_run(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work)
+{
+    WideArgs p = wide_args(ctx, prep, a.K, a.D, a.m);
+    char* w = (char*)work;
+    p.best = (float4*)w;
+    p.norm = (float4*)(w + (size_t)a.m * p.splits * 16);
+    p.record = (uint32_t*)(w + (size_t)a.m * (p.splits * 16 + 16));
+    p.id2 = (uint32_t*)(w + (size_t)a.m * (p.splits * 16 + 16 + kWRecord * 4));
+    // a candidate tile takes one pass over its chunks however few entries it has; the all-nodes pass K D differences an entry
+    p.cand_min = a.K <= 65536 ? 256u : 0xffffffffu;
+    static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
+    bool& attr_set = attr_set_dev[ctx->device];
+    if (!attr_set) {
+        for (const void* k : {reinterpret_cast<const void*>(bmu_wide_split_kernel), reinterpret_cast<const void*>(bmu_wide_split_cand_kernel)})
+            if (int rc = check_hip(ctx, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWLds),
+                                   "raising the dynamic LDS limit"))
+                return rc;
+        attr_set = true;
+    }
+    const int64_t tiles_m = (a.m + kWTile - 1) / kWTile;
+    const int64_t blocks = (tiles_m + 7) / 8 * 8 * p.splits;
+    hipLaunchKernelGGL(bmu_wide_split_kernel, dim3((unsigned)blocks), dim3(kWThreads), kWLds, ctx->stream, a, p);
+    if (int rc = check_hip(ctx, hipGetLastError(), "bmu (wide, split) kernel launch")) return rc;
+    hipLaunchKernelGGL(bmu_wide_join_kernel, dim3((unsigned)((a.m + kJoinThreads - 1) / kJoinThreads)), dim3(kJoinThreads), 0, ctx->stream, a, p);
+    return check_hip(ctx, hipGetLastError(), "bmu (wide, split) join launch");
+}
+
+// the re-decision (K > 1): candidate pass and direct differences; what is left over is on the second list
+int bmu_wide_recheck(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work)
+{
+    WideArgs p = wide_args(ctx, prep, a.K, a.D, a.m);
+    char* w = (char*)work;
+    p.record = (uint32_t*)(w + (size_t)a.m * (p.splits * 16 + 16));
+    p.cand_min = a.K <= 65536 ? 256u : 0xffffffffu;
+    const int64_t most = (a.m + kWTile - 1) / kWTile * p.tiles;
+    hipLaunchKernelGGL(bmu_wide_split_cand_kernel, dim3((unsigned)(most < 256 ? most : 256)), dim3(kWThreads), kWLds, ctx->stream, a, p);
+    if (int rc = check_hip(ctx, hipGetLastError(), "bmu (wide, split) candidate launch")) return rc;
+    const int64_t groups = (a.m + 15) / 16;
+    hipLaunchKernelGGL(bmu_wide_exact_kernel, dim3((unsigned)(groups < 2048 ? groups : 2048)), dim3(256), 0, ctx->stream, a, p);
+    return check_hip(ctx, hipGetLastError(), "bmu (wide, split) candidate-distance launch");
+}
+
+int bmu_wide_distances(som_ctx* ctx, const BmuArgs& a)
+{
+    const int64_t groups = (a.m + 15) / 16;
+    hipLaunchKernelGGL(bmu_wide_distance_kernel, dim3((unsigned)(groups < 2048 ? groups : 2048)), dim3(256), 0, ctx->stream, a);
+    return check_hip(ctx, hipGetLastError(), "bmu (wide, split) distance launch");
+}
+
+} // namespace som

@@ -16,11 +16,10 @@ constexpr int kMaxStepsResident = 32; // BMU kernel keeps a sample's features in
 
 struct BmuPrep {
     float* stage = nullptr;        // [Kpad / 128][nch] blobs: 128 padded weight rows of a chunk, then -|w|^2 / 2
-    void* stage16 = nullptr;       // bf16 hi/lo stage rows of the split search (4 <= D <= 64), else null
+    void* stage16 = nullptr;       // bf16 hi/lo parts of the weights for the split search (D <= 64: stage rows; D > 64: som_bmu_wide.hip), else null
     float* wwin = nullptr;         // [Kpad][kb][2][8] the same slots as stage16 in float32 (centred, zeros off-window)
     int kb = 0;                    // whole 16-feature blocks of a stage16 row
     int tail_r = 0;                // features of the packed tail block behind them (0: none; D <= 64 only)
-    int nch16 = 0;                 // chunks of a stage in stage16 (1 for D <= 64, 64-feature chunks above)
     float* wt = nullptr;           // [D][Kpad] transposed weights (as given, not centred)
     float* centre = nullptr;       // [D] column means of W; stage rows and sample registers hold values minus this
     // [0] = bits of max_k |w_k - centre|^2, [3] = total,
@@ -44,7 +43,7 @@ struct BmuArgs {
     const void* stage16;     // BmuPrep::stage16 (null: float32 search)
     const float* wwin;       // BmuPrep::wwin
     int32_t tail_r;          // BmuPrep::tail_r
-    void* parts;             // split search, D > 64: the pass's samples as bf16 parts, [m][chunks * 8][hi x 8 | lo x 8]
+    int32_t second_only;     // bmu_exact_kernel: serve the second list whatever the first one's length
     const float* wt;         // BmuPrep::wt
     const float* centre;     // BmuPrep::centre
     unsigned int* scal;      // BmuPrep::scal
@@ -94,7 +93,7 @@ struct som_ctx {
     int32_t* bmu_ws = nullptr;     // BMU indices of the epoch drivers (one chunk's worth)
     size_t bmu_elems = 0;
     void* acc_blob = nullptr;      // per-workgroup float64 slices + counts of the accumulation pass
-    void* parts_blob = nullptr;    // the presented samples of a pass as bf16 parts (split search, D > 64)
+    void* parts_blob = nullptr;    // workspace of a pass of the wide split search (D > 64)
     size_t parts_bytes = 0;
     size_t acc_bytes = 0;
     void* upd_blob = nullptr;      // influence matrix + split-k partials of the update
@@ -138,6 +137,13 @@ int launch_fill_zero(som_ctx* ctx, void* p, size_t bytes);
 // qe (double[2]) and small (int32[4]) are zeroed by the preparation kernel when given
 int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out, double* qe, int32_t* small);
 int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs args);
+// split search for D > 64 (som_bmu_wide.hip)
+size_t bmu_wide_blob_bytes(int32_t K, int32_t D);
+int bmu_wide_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, const BmuPrep& prep, double* qe, int32_t* small);
+size_t bmu_wide_work_bytes(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t D, int64_t m);
+int bmu_wide_run(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work);
+int bmu_wide_recheck(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work);
+int bmu_wide_distances(som_ctx* ctx, const BmuArgs& a);
 int accumulate_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m,
                    const int32_t* bmu, int32_t K, double* S, unsigned long long* n, bool zero_first);
 // 1 = shape not served by the MFMA path (caller falls back), otherwise SOM_OK or an error code
