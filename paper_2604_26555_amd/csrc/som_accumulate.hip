@@ -186,6 +186,11 @@ int accumulate_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const u
         const int rc = accumulate_mfma_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first);
         if (rc != 1) return rc;
     }
+    // rows wider than one window of the LDS kernel: sorted by node first, every row read once
+    if (!ctx->reproducible && D > 63) {
+        const int rc = accumulate_sort_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first);
+        if (rc != 1) return rc;
+    }
     // float64 LDS atomics over node slabs when the K x 64 partial fits a few slabs
     {
         const int rc = accumulate_f64_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first);
