@@ -163,6 +163,7 @@ void som_destroy(som_ctx* c)
     if (c->acc_blob) (void)hipFree(c->acc_blob);
     if (c->parts_blob) (void)hipFree(c->parts_blob);
     if (c->upd_blob) (void)hipFree(c->upd_blob);
+    if (c->small_sums) (void)hipFree(c->small_sums);
     if (c->topo_blob) (void)hipFree(c->topo_blob);
     if (c->S) (void)hipFree(c->S);
     if (c->n) (void)hipFree(c->n);
@@ -249,6 +250,7 @@ int som_bmu(som_ctx* ctx, const float* X, int64_t N, int32_t D, int64_t ldx, con
         return fail(ctx, SOM_EINVAL, "X, W and bmu must be device-accessible memory");
     if (int rc = check_hip(ctx, hipSetDevice(ctx->device), "hipSetDevice")) return rc;
     if (m == 0) return qe ? launch_fill_zero(ctx, qe, 2 * sizeof(double)) : SOM_OK;
+    if (const int rc = small_bmu_run(ctx, X, D, ldx, idx, m, W, K, bmu, d2, qe); rc != 1) return rc;
     BmuPrep prep;
     if (int rc = bmu_prepare(ctx, W, K, D, &prep, qe, nullptr)) return rc;
     BmuArgs a{};
@@ -374,6 +376,8 @@ int som_epoch(som_ctx* ctx, const float* X, int64_t N, int32_t D, int64_t ldx, c
         }
         return SOM_OK;
     }
+    if (!stats)
+        if (const int rc = small_epoch_run(ctx, X, D, ldx, idx, m, W, K, G, sigma, eps_h); rc != 1) return rc;
     if (int rc = begin_epoch(ctx, K, D, m)) return rc;
     BmuPrep prep;
     if (stats) (void)hipEventRecord(ctx->ev_t[0], ctx->stream);

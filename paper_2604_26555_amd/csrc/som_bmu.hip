@@ -2447,22 +2447,27 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
 {
     if (a.m <= 0) return SOM_OK;
     auto cand_cap_for = [](size_t cap) { return cap < kCandCapMax ? cap : kCandCapMax; };
-    if ((size_t)a.m > ctx->recheck_cap) {
+    // (the candidate sets are the float32 searches' only: the split searches decide at the end of their candidate tiles, or
+    // keep records of their own)
+    const bool sets = prep.stage16 == nullptr;
+    if ((size_t)a.m > ctx->recheck_cap || (sets && !ctx->recheck_sets)) {
         if (ctx->recheck) {
             if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync before workspace growth")) return rc;
             (void)hipFree(ctx->recheck);
             ctx->recheck = nullptr;
             ctx->recheck_cap = 0;
+            ctx->recheck_sets = false;
         }
-        // sample positions [cap], cuts [cap], per-sample cuts [cap], pair-list ids [cap][2], second list [cand_cap], candidate sets [cand_cap][2]; the capacity is a
+        // sample positions [cap], cuts [cap], per-sample cuts [cap], pair-list ids [cap][2], candidate sets [cand_cap][2]; the capacity is a
         // multiple of four entries so that the 16-byte candidate sets stay aligned
         const size_t cap = ((size_t)a.m + 3) / 4 * 4, ccap = cand_cap_for(cap);
-        const size_t bytes = cap * 20 + ccap * (4 + 2 * sizeof(ulonglong2));
+        const size_t bytes = cap * 20 + (sets ? ccap * 2 * sizeof(ulonglong2) : 0);
         if (hipMalloc((void**)&ctx->recheck, bytes) != hipSuccess) {
             (void)hipGetLastError();
             return fail(ctx, SOM_ENOMEM, "cannot allocate the %lld-entry recheck list", (long long)a.m);
         }
         ctx->recheck_cap = cap;
+        ctx->recheck_sets = sets;
     }
     a.kpad = prep.kpad;
     a.stage = prep.stage;
@@ -2478,8 +2483,9 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     a.cut_all = (float*)(ctx->recheck + 2 * ctx->recheck_cap);
     a.recheck_end = ctx->recheck + ctx->recheck_cap;
     a.pairs = ctx->recheck + 3 * ctx->recheck_cap;
-    a.recheck2 = ctx->recheck + 5 * ctx->recheck_cap;
-    a.cand = (ulonglong2*)(a.recheck2 + cand_cap_for(ctx->recheck_cap));
+    // (the per-sample cuts are dead once the lists are made: the second list takes their place)
+    a.recheck2 = ctx->recheck + 2 * ctx->recheck_cap;
+    a.cand = (ulonglong2*)(ctx->recheck + 5 * ctx->recheck_cap);
     a.cand_cap = (uint32_t)cand_cap_for(ctx->recheck_cap);
     // The candidate pass repeats the search for the listed samples at matrix speed (under a nanosecond per sample
     // at K D = 51200, against 3.8 ns for direct differences over all nodes) but has the latency of a whole tile, so

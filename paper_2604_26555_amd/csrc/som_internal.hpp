@@ -90,6 +90,7 @@ struct som_ctx {
     size_t prep_bytes = 0;
     uint32_t* recheck = nullptr;   // one allocation: sample positions [cap], cuts [cap], second list, candidate slots
     size_t recheck_cap = 0;
+    bool recheck_sets = false;     // the allocation holds the candidate sets
     int32_t* bmu_ws = nullptr;     // BMU indices of the epoch drivers (one chunk's worth)
     size_t bmu_elems = 0;
     void* acc_blob = nullptr;      // per-workgroup float64 slices + counts of the accumulation pass
@@ -103,6 +104,9 @@ struct som_ctx {
     int reproducible = 0;          // prefer the fixed-order accumulation kernel
     int search = 0;                // SOM_SEARCH_*
     double* qe_part = nullptr;     // [kQeSlots][2], then [kQeSlots], zero between calls
+    double* small_sums = nullptr;  // small epochs: two sets of per-node sums and counts, of small_cells each
+    size_t small_cells = 0, small_clean = 0;   // small_clean: leading cells of set small_turn that are zero
+    int small_turn = 0;
     void* topo_blob = nullptr;     // node distances, adjacency matrix and lists of the topology rebuild
     size_t topo_bytes = 0;
     // epoch-internal accumulators
@@ -144,6 +148,11 @@ size_t bmu_wide_work_bytes(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t
 int bmu_wide_run(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work);
 int bmu_wide_recheck(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work);
 int bmu_wide_distances(som_ctx* ctx, const BmuArgs& a);
+// small calls (som_small.hip): 1 = not a small one, otherwise SOM_OK or an error code
+int small_bmu_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m, const float* W, int32_t K,
+                  int32_t* bmu, float* d2, double* qe);
+int small_epoch_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m, float* W, int32_t K,
+                    const float* G, double sigma, double eps_h);
 int accumulate_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m,
                    const int32_t* bmu, int32_t K, double* S, unsigned long long* n, bool zero_first);
 // 1 = shape not served by the MFMA path (caller falls back), otherwise SOM_OK or an error code

@@ -1,0 +1,485 @@
+// Small calls: maps and tables for which the search, the accumulation and the update are each a few microseconds of
+// arithmetic, so that what counts is how many kernels there are.  The general path takes ten (centre, preparation,
+// search, list, candidates, differences, sums, reduction, contraction, finish) of 2 to 25 us each; here a look-up is
+// one kernel and an epoch two.
+//
+// Distances are the float32 direct differences sum_d (x_d - w_kd)^2, features in order, that the general path's
+// re-decisions use (lowest distance, then lowest node index); so no bound, no list and no second decision.  The sums
+// are float64, like the general path's.
+//
+//   small_kernel      a few lanes per sample (each takes every SUB-th node, W in LDS), rows of at most 32 features;
+//                     with ACC the workgroup also adds its samples up in LDS and its sums onto the map's
+//   lookup_kernel     a thread per node and 4 or 8 samples per workgroup (rows of at most 64 features, any map): W comes
+//                     through LDS in pieces, the samples' values in scalar registers
+//   small_update_kernel   one wavefront per node: influences, the contraction over the nodes and the rule
+#include "som_bmu_common.hpp"
+
+#include <math.h>
+
+namespace som {
+
+constexpr int kSThreads = 512;
+constexpr size_t kSLds = 128 * 1024;          // W and the sums of small_kernel, a piece of W in lookup_kernel
+constexpr int kSFeatures = 32;                // small_kernel: features of a row at most
+constexpr int kSNodes = 512;                  // small epochs: nodes at most
+constexpr double kSWork = 3.0e8;              // m K D of a small epoch at most: about 20 us of vector arithmetic, what the
+                                              // general path spends on its launches
+constexpr double kLWork = 4.0e8;              // ... of a small look-up
+
+struct SmallArgs {
+    const float* X;
+    int64_t ldx;
+    const uint32_t* idx;
+    int64_t m;
+    int D, K, sub;                            // sub: lanes per sample (a power of two)
+    const float* W;
+    int32_t* bmu;                             // may be null (epochs)
+    float* d2;
+    double* qe_part;                          // may be null
+    double* S;                                // ACC: [K][D + 1], the last column counts
+};
+
+// DQ: float4 of a row
+template <int DQ, bool ACC>
+__global__ void __launch_bounds__(kSThreads) small_kernel(const SmallArgs a)
+{
+    extern __shared__ float4 small_lds[];
+    float4* const w4 = small_lds;                                             // [K][DQ], zeros behind the row
+    double* const sums = reinterpret_cast<double*>(small_lds + (size_t)a.K * DQ);   // ACC: [K][D + 1]
+    const int tid = threadIdx.x, D = a.D, K = a.K, DS = D + 1;
+    float* const wf = reinterpret_cast<float*>(w4);
+    for (int e = tid; e < K * DQ * 4; e += kSThreads) {
+        const int k = e / (DQ * 4), f = e - k * (DQ * 4);
+        wf[e] = f < D ? a.W[(size_t)k * D + f] : 0.0f;
+    }
+    if constexpr (ACC)
+        for (int e = tid; e < K * DS; e += kSThreads) sums[e] = 0.0;
+    __syncthreads();
+    const int sub = tid & (a.sub - 1), per = kSThreads / a.sub;
+    double qs = 0.0, qs2 = 0.0;
+    for (int64_t p0 = (int64_t)blockIdx.x * per; p0 < a.m; p0 += (int64_t)gridDim.x * per) {
+        const int64_t i = p0 + tid / a.sub;
+        const bool live = i < a.m;
+        const int64_t ic = live ? i : a.m - 1;
+        const float* xr = a.X + (a.idx ? (int64_t)a.idx[ic] : ic) * a.ldx;
+        float x[4 * DQ];
+#pragma unroll
+        for (int q = 0; q < DQ; ++q) {
+            if (4 * q + 4 <= D) {
+                const float4 v = load4(xr + 4 * q);
+                x[4 * q] = v.x;
+                x[4 * q + 1] = v.y;
+                x[4 * q + 2] = v.z;
+                x[4 * q + 3] = v.w;
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) x[4 * q + t] = 4 * q + t < D ? xr[4 * q + t] : 0.0f;
+            }
+        }
+        float bd = INFINITY;
+        int bk = 0x7fffffff;
+        // two nodes at a time: two chains of additions
+        for (int k = sub; k < K; k += 2 * a.sub) {
+            const int k1 = k + a.sub < K ? k + a.sub : k;
+            float d0 = 0.0f, d1 = 0.0f;
+#pragma unroll
+            for (int q = 0; q < DQ; ++q) {
+                const float4 u = w4[k * DQ + q], v = w4[k1 * DQ + q];
+                const float wu[4] = {u.x, u.y, u.z, u.w}, wv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float e0 = x[4 * q + t] - wu[t], e1 = x[4 * q + t] - wv[t];
+                    d0 = fmaf(e0, e0, d0);
+                    d1 = fmaf(e1, e1, d1);
+                }
+            }
+            if (d0 < bd) {
+                bd = d0;
+                bk = k;
+            }
+            if (d1 < bd) {
+                bd = d1;
+                bk = k1;
+            }
+        }
+        for (int o = 1; o < a.sub; o <<= 1) {
+            const float od = __shfl_xor(bd, o);
+            const int ok = __shfl_xor(bk, o);
+            if (od < bd || (od == bd && ok < bk)) {
+                bd = od;
+                bk = ok;
+            }
+        }
+        if (bk >= K) bk = 0;                                   // only reachable with non-finite input
+        if (live && sub == 0) {
+            if (a.bmu) a.bmu[i] = bk;
+            if (a.d2) a.d2[i] = bd;
+            qs += sqrt((double)bd);
+            qs2 += (double)bd;
+        }
+        if constexpr (ACC) {
+            // a sample's lanes share its features; the last place counts
+            if (live) {
+                double* s = sums + bk * DS;
+#pragma unroll
+                for (int f = 0; f < 4 * DQ; ++f)
+                    if (f < D && (f & (a.sub - 1)) == sub) unsafeAtomicAdd(&s[f], (double)x[f]);
+                if (sub == 0) unsafeAtomicAdd(&s[D], 1.0);
+            }
+        }
+    }
+    if constexpr (ACC) {
+        __syncthreads();
+        for (int e = tid; e < K * DS; e += kSThreads) {
+            const double v = sums[e];
+            if (v != 0.0) unsafeAtomicAdd(&a.S[e], v);
+        }
+    }
+    if (a.qe_part) group_qe_add(a.qe_part, qs, qs2);
+}
+
+// S samples per workgroup; nodes in pieces of `piece` (their rows in LDS, `stride` floats apart, odd or harmless to the banks)
+template <int S>
+__global__ void __launch_bounds__(kSThreads) lookup_kernel(const float* __restrict__ X, const float* __restrict__ W, const SmallArgs a,
+                                                           int piece, int stride)
+{
+    extern __shared__ float4 small_lds[];
+    __shared__ float red_d[kSThreads / 64][S];
+    __shared__ int red_k[kSThreads / 64][S];
+    float* const wl = reinterpret_cast<float*>(small_lds);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, D = a.D, K = a.K;
+    const int64_t i0 = (int64_t)blockIdx.x * S;
+    // the samples' rows: the same for the whole workgroup, so that their values are scalar loads
+    const float* xrow[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int64_t i = i0 + s < a.m ? i0 + s : a.m - 1;
+        xrow[s] = X + (a.idx ? (int64_t)a.idx[i] : i) * a.ldx;
+    }
+    float bd[S];
+    int bk[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        bd[s] = INFINITY;
+        bk[s] = 0x7fffffff;
+    }
+    for (int k0 = 0; k0 < K; k0 += piece) {
+        const int kn = K - k0 < piece ? K - k0 : piece;
+        __syncthreads();
+        // the piece's rows are contiguous in W
+        const float* from = W + (size_t)k0 * D;
+        if (stride == D) {
+            const int words = kn * D, whole = words / 4;
+            float4* to = reinterpret_cast<float4*>(wl);
+            for (int e = tid; e < whole; e += kSThreads) to[e] = load4(from + 4 * e);
+            for (int e = 4 * whole + tid; e < words; e += kSThreads) wl[e] = from[e];
+        } else {
+            const int dq = D / 4;                           // (a multiple of four: padded rows)
+            for (int e = tid; e < kn * dq; e += kSThreads) {
+                const int r = e / dq, q = e - r * dq;
+                const float4 v = load4(from + 4 * e);
+                float* to = wl + r * stride + 4 * q;
+                to[0] = v.x;
+                to[1] = v.y;
+                to[2] = v.z;
+                to[3] = v.w;
+            }
+        }
+        __syncthreads();
+        for (int n = tid; n < kn; n += kSThreads) {
+            const float* w = wl + n * stride;
+            float d[S];
+#pragma unroll
+            for (int s = 0; s < S; ++s) d[s] = 0.0f;
+            int f = 0;
+            for (; f + 8 <= D; f += 8) {
+                float wv[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) wv[t] = w[f + t];
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+#pragma unroll
+                    for (int s = 0; s < S; ++s) {
+                        const float e = xrow[s][f + t] - wv[t];
+                        d[s] = fmaf(e, e, d[s]);
+                    }
+            }
+            for (; f < D; ++f) {
+                const float wv = w[f];
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const float e = xrow[s][f] - wv;
+                    d[s] = fmaf(e, e, d[s]);
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+                if (d[s] < bd[s]) {
+                    bd[s] = d[s];
+                    bk[s] = k0 + n;
+                }
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        float d = bd[s];
+        int k = bk[s];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const float od = __shfl_xor(d, o);
+            const int ok = __shfl_xor(k, o);
+            if (od < d || (od == d && ok < k)) {
+                d = od;
+                k = ok;
+            }
+        }
+        if (lane == 0) {
+            red_d[wave][s] = d;
+            red_k[wave][s] = k;
+        }
+    }
+    __syncthreads();
+    double qs = 0.0, qs2 = 0.0;
+    if (tid < S && i0 + tid < a.m) {
+        float d = red_d[0][tid];
+        int k = red_k[0][tid];
+        for (int w = 1; w < kSThreads / 64; ++w) {
+            const float od = red_d[w][tid];
+            const int ok = red_k[w][tid];
+            if (od < d || (od == d && ok < k)) {
+                d = od;
+                k = ok;
+            }
+        }
+        if (k >= K) k = 0;                                     // only reachable with non-finite input
+        a.bmu[i0 + tid] = k;
+        if (a.d2) a.d2[i0 + tid] = d;
+        qs = sqrt((double)d);
+        qs2 = (double)d;
+    }
+    if (a.qe_part) group_qe_add(a.qe_part, qs, qs2);
+}
+
+// qe[0..1] = the call's partial sums, which are left zero for the next call
+__global__ void __launch_bounds__(kQeSlots) small_qe_kernel(double* __restrict__ part, double* __restrict__ qe)
+{
+    __shared__ double w[kQeSlots / 64][2];
+    const int tid = threadIdx.x;
+    double s0 = part[2 * tid], s1 = part[2 * tid + 1];
+    part[2 * tid] = 0.0;
+    part[2 * tid + 1] = 0.0;
+    s0 = wave_sum(s0);
+    s1 = wave_sum(s1);
+    if ((tid & 63) == 0) {
+        w[tid >> 6][0] = s0;
+        w[tid >> 6][1] = s1;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double t0 = 0.0, t1 = 0.0;
+        for (int q = 0; q < kQeSlots / 64; ++q) {
+            t0 += w[q][0];
+            t1 += w[q][1];
+        }
+        qe[0] = t0;
+        qe[1] = t1;
+    }
+}
+
+// The update of a small map (definitions in som_update.hip): a wavefront per node j.  S [K][D + 1] float64 with the counts in
+// the last column.  `clear`: the other call's sums, zero when the next call adds to them.
+constexpr int kUThreads = 256;
+
+__global__ void __launch_bounds__(kUThreads) small_update_kernel(const float* __restrict__ G, const double* __restrict__ S, int K, int D,
+                                                                 double inv2s2, bool shifted, double eps_h, bool plain, double eta,
+                                                                 double mu, float* __restrict__ V, float* __restrict__ W,
+                                                                 double* __restrict__ clear)
+{
+    __shared__ double h_lds[kUThreads / 64][kSNodes];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, DS = D + 1;
+    for (int e = blockIdx.x * kUThreads + tid; e < K * DS; e += gridDim.x * kUThreads) clear[e] = 0.0;
+    const int j = blockIdx.x * (kUThreads / 64) + wave;
+    if (j >= K) return;                                        // (no barrier below: a wavefront works on its own)
+    double* h = h_lds[wave];
+    double shift = 0.0;
+    if (shifted) {
+        shift = INFINITY;
+        for (int k = lane; k < K; k += 64) {
+            const double g = (double)G[(size_t)k * K + j];
+            if (S[(size_t)k * DS + D] != 0.0 && g * g < shift) shift = g * g;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) shift = fmin(shift, __shfl_xor(shift, o));
+    }
+    for (int k = lane; k < K; k += 64) {
+        const double g = (double)G[(size_t)k * K + j];
+        const double e = -(g * g - shift) * inv2s2;
+        const bool out = isinf(g) || isinf(shift) || (shifted && S[(size_t)k * DS + D] == 0.0);
+        h[k] = out ? 0.0 : exp(e);
+    }
+    __builtin_amdgcn_wave_barrier();
+    // lanes: a column each, in 64 / width parts over the nodes
+    int width = 1;
+    while (width < DS) width <<= 1;
+    const int c = lane & (width - 1), part = lane / width, parts = 64 / width;
+    double num = 0.0;
+    if (c < DS) {
+#pragma unroll 8
+        for (int k = part; k < K; k += parts) num += h[k] * S[(size_t)k * DS + c];
+    }
+    for (int o = width; o < 64; o <<= 1) num += __shfl_xor(num, o);
+    const double den = __shfl(num, D);
+    if (lane >= D) return;
+    const size_t e = (size_t)j * D + lane;
+    const bool ok = den >= eps_h;
+    if (plain) {
+        if (ok) W[e] = (float)(num / den);
+    } else {
+        const double w = (double)W[e];
+        const double delta = (ok ? eta * (num / den - w) : 0.0) + (V ? mu * (double)V[e] : 0.0);
+        W[e] = (float)(w + delta);
+        if (V) V[e] = (float)delta;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------------------------------------
+static size_t small_lds_bytes(int K, int D, bool acc)
+{
+    return (size_t)K * ((D + 3) / 4) * 16 + (acc ? (size_t)K * (D + 1) * 8 : 0);
+}
+
+template <bool ACC>
+static int launch_small(som_ctx* ctx, SmallArgs a, int blocks_most)
+{
+    // lanes per sample: enough threads for two wavefronts per SIMD, as long as every lane has nodes to look at
+    a.sub = 1;
+    while (a.sub < 16 && a.m * a.sub < 256 * 512 && a.sub * 8 <= a.K) a.sub <<= 1;
+    const int64_t per = kSThreads / a.sub, need = (a.m + per - 1) / per;
+    const unsigned blocks = (unsigned)(need < blocks_most ? need : blocks_most);
+    const size_t lds = small_lds_bytes(a.K, a.D, ACC);
+    static bool attr_set_dev[kMaxDevices][9] = {};       // the attribute belongs to the device, not to the process
+    const int dq = (a.D + 3) / 4;
+    auto launch = [&](auto kern) -> int {
+        bool& attr_set = attr_set_dev[ctx->device][dq];
+        if (!attr_set) {
+            if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSLds),
+                                   "raising the dynamic LDS limit"))
+                return rc;
+            attr_set = true;
+        }
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(kSThreads), lds, ctx->stream, a);
+        return check_hip(ctx, hipGetLastError(), "small-map kernel launch");
+    };
+    switch (dq) {
+    case 1: return launch(small_kernel<1, ACC>);
+    case 2: return launch(small_kernel<2, ACC>);
+    case 3: return launch(small_kernel<3, ACC>);
+    case 4: return launch(small_kernel<4, ACC>);
+    case 5: return launch(small_kernel<5, ACC>);
+    case 6: return launch(small_kernel<6, ACC>);
+    case 7: return launch(small_kernel<7, ACC>);
+    case 8: return launch(small_kernel<8, ACC>);
+    }
+    return fail(ctx, SOM_EINVAL, "no small-map kernel for %d features", a.D);
+}
+
+// look-ups; qe (may be null) is overwritten.  Returns 1 when the call is not a small one.
+int small_bmu_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m, const float* W, int32_t K,
+                  int32_t* bmu, float* d2, double* qe)
+{
+    if (ctx->search != SOM_SEARCH_AUTO || ctx->profiling || D > 64 || (double)m * K * D > kLWork) return 1;
+    SmallArgs a{};
+    a.X = X;
+    a.ldx = ldx;
+    a.idx = idx;
+    a.m = m;
+    a.D = D;
+    a.K = K;
+    a.W = W;
+    a.bmu = bmu;
+    a.d2 = d2;
+    a.qe_part = qe ? ctx->qe_part : nullptr;
+    int rc;
+    if (D <= kSFeatures && small_lds_bytes(K, D, false) <= kSLds / 2) {
+        rc = launch_small<false>(ctx, a, 2048);
+    } else {
+        // rows in LDS: a stride that is no multiple of four spreads a wavefront's reads over the banks
+        const int stride = D % 4 == 0 ? D + 1 : D;
+        int piece = (int)(kSLds / sizeof(float)) / stride;
+        if (piece > kSThreads) piece = piece / kSThreads * kSThreads;
+        if (piece > K) piece = K;
+        const size_t lds = ((size_t)piece * stride * sizeof(float) + 15) / 16 * 16;
+        static bool attr_set_dev[kMaxDevices] = {};
+        bool& attr_set = attr_set_dev[ctx->device];
+        if (!attr_set) {
+            for (const void* k : {reinterpret_cast<const void*>(lookup_kernel<4>), reinterpret_cast<const void*>(lookup_kernel<8>)})
+                if (int e = check_hip(ctx, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSLds), "raising the dynamic LDS limit"))
+                    return e;
+            attr_set = true;
+        }
+        // (four samples a workgroup while that does not fill the chip: every workgroup reads all of W)
+        if (m <= 4 * 256)
+            hipLaunchKernelGGL(lookup_kernel<4>, dim3((unsigned)((m + 3) / 4)), dim3(kSThreads), lds, ctx->stream, X, W, a, piece, stride);
+        else
+            hipLaunchKernelGGL(lookup_kernel<8>, dim3((unsigned)((m + 7) / 8)), dim3(kSThreads), lds, ctx->stream, X, W, a, piece, stride);
+        rc = check_hip(ctx, hipGetLastError(), "look-up kernel launch");
+    }
+    if (rc || !qe) return rc;
+    hipLaunchKernelGGL(small_qe_kernel, dim3(1), dim3(kQeSlots), 0, ctx->stream, ctx->qe_part, qe);
+    return check_hip(ctx, hipGetLastError(), "quantisation-error launch");
+}
+
+// a whole epoch without statistics.  Returns 1 when it is not a small one.
+int small_epoch_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m, float* W, int32_t K,
+                    const float* G, double sigma, double eps_h)
+{
+    if (ctx->search != SOM_SEARCH_AUTO || ctx->profiling || ctx->reproducible || D > kSFeatures || K > kSNodes ||
+        (double)m * K * D > kSWork || small_lds_bytes(K, D, true) > kSLds)
+        return 1;
+    // two sets of sums take turns: this call's update clears the other one for the next call
+    const size_t cells = (size_t)K * (D + 1);
+    if (cells > ctx->small_cells) {
+        if (ctx->small_sums) {
+            if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync before workspace growth")) return rc;
+            (void)hipFree(ctx->small_sums);
+            ctx->small_sums = nullptr;
+            ctx->small_cells = 0;
+        }
+        if (hipMalloc((void**)&ctx->small_sums, 2 * cells * sizeof(double)) != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(ctx, SOM_ENOMEM, "cannot allocate %zu bytes for the sums of a small map", 2 * cells * sizeof(double));
+        }
+        ctx->small_cells = cells;
+        ctx->small_clean = 0;
+    }
+    double* sums[2] = {ctx->small_sums, ctx->small_sums + ctx->small_cells};
+    const int turn = ctx->small_turn;
+    // (cells that are known to be zero in this call's set; a larger map than the last one clears its set first)
+    if (ctx->small_clean < cells)
+        if (int rc = launch_fill_zero(ctx, sums[turn], cells * sizeof(double))) return rc;
+    SmallArgs a{};
+    a.X = X;
+    a.ldx = ldx;
+    a.idx = idx;
+    a.m = m;
+    a.D = D;
+    a.K = K;
+    a.W = W;
+    a.S = sums[turn];
+    ctx->small_clean = 0;                                       // until this call's kernels are enqueued
+    // (every workgroup adds its sums onto the map's: at most one per compute unit)
+    if (int rc = launch_small<true>(ctx, a, 256)) return rc;
+    const double inv2s2 = 1.0 / (2.0 * sigma * sigma);
+    const bool plain = ctx->eta == 1.0 && ctx->mu == 0.0;
+    hipLaunchKernelGGL(small_update_kernel, dim3((unsigned)((K + kUThreads / 64 - 1) / (kUThreads / 64))), dim3(kUThreads), 0, ctx->stream,
+                       G, sums[turn], K, D, inv2s2, ctx->safeguard == SOM_SAFEGUARD_SHIFT, eps_h, plain, ctx->eta, ctx->mu, ctx->velocity,
+                       W, sums[turn ^ 1]);
+    if (int rc = check_hip(ctx, hipGetLastError(), "small-map update launch")) return rc;
+    ctx->small_turn = turn ^ 1;
+    ctx->small_clean = cells;
+    return SOM_OK;
+}
+
+} // namespace som
