@@ -181,8 +181,10 @@ __global__ void __launch_bounds__(256) accumulate_direct_kernel(const float* __r
 int accumulate_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m,
                    const int32_t* bmu, int32_t K, double* S, unsigned long long* n, bool zero_first)
 {
-    // fixed-order sums in MFMA accumulators when asked for (and the shape fits one workgroup's registers)
+    // fixed-order sums when asked for: a stable sort by node, or (fewer than four features, very large maps) MFMA accumulators
     if (ctx->reproducible) {
+        const int rs = accumulate_stable_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first);
+        if (rs != 1) return rs;
         const int rc = accumulate_mfma_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first);
         if (rc != 1) return rc;
     }

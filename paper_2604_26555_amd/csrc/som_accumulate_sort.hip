@@ -10,6 +10,10 @@
 //   4. sums      lane groups take equal ranges of the sorted order.
 // Bound by HBM in step 4 (D * 4 contiguous bytes per row); steps 1 to 3 cost about 20 us at 10^6 samples.
 // The order of a node's samples within a block is not fixed, so a sum can differ in its last bits between runs (float64).
+//
+// Fixed order of summation (som_set_reproducible): the same with a stable sort (a block is one wavefront's, which ranks its 64
+// samples at a time by ballots) and with the sorted order cut into segments of one node's samples each, whose sums are
+// stored and added in order: every sum is float64 and the same from run to run.
 #include "som_internal.hpp"
 
 #include <hip/amd_detail/amd_hip_unsafe_atomics.h>
@@ -19,6 +23,9 @@ namespace som {
 constexpr int kSortThreads = 1024;
 constexpr int kSortNodes = 16384;         // per-node counters of a workgroup in LDS (64 KB)
 constexpr int kSortBlocks = 512;          // blocks of samples at most
+constexpr int kStableWaves = 4;           // wavefronts (blocks) of a workgroup of the stable sort
+constexpr int kStableBlocks = 1024;
+constexpr int kStableNodes = 8192;        // per-node counters of four wavefronts in LDS (128 KB)
 
 __global__ void __launch_bounds__(kSortThreads) sort_hist_kernel(const int32_t* __restrict__ bmu, int64_t m, int K, int64_t per_block,
                                                                  uint32_t* __restrict__ hist, double* __restrict__ S_clear,
@@ -119,6 +126,174 @@ __global__ void __launch_bounds__(kSortThreads) sort_scatter_kernel(const int32_
     }
 }
 
+// The stable sort's histogram and scatter: a block is a wavefront's.
+__global__ void __launch_bounds__(64 * kStableWaves) stable_hist_kernel(const int32_t* __restrict__ bmu, int64_t m, int K, int64_t per_block,
+                                                                        int blocks, uint32_t* __restrict__ hist)
+{
+    extern __shared__ uint32_t sort_lds[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int block = blockIdx.x * kStableWaves + wave;
+    uint32_t* count = sort_lds + wave * K;
+    for (int k = lane; k < K; k += 64) count[k] = 0u;
+    __builtin_amdgcn_wave_barrier();
+    if (block >= blocks) return;                              // (no barrier below)
+    const int64_t lo = (int64_t)block * per_block, hi = lo + per_block < m ? lo + per_block : m;
+    for (int64_t i = lo + lane; i < hi; i += 64) {
+        const int b = bmu[i];
+        if (b >= 0 && b < K) atomicAdd(&count[b], 1u);
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (int k = lane; k < K; k += 64) hist[(size_t)block * K + k] = count[k];
+}
+
+// exclusive scan over the nodes: start[k] of the totals and seg[k] of the segments of `rows` samples (K + 1 entries each)
+__global__ void __launch_bounds__(1024) stable_starts_kernel(const uint32_t* __restrict__ total, int K, uint32_t rows,
+                                                             uint32_t* __restrict__ start, uint32_t* __restrict__ seg)
+{
+    __shared__ uint2 wave_sum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int per = (K + 1023) / 1024, k0 = tid * per;
+    uint2 mine = make_uint2(0u, 0u);
+    for (int u = 0; u < per; ++u) {
+        const uint32_t t = k0 + u < K ? total[k0 + u] : 0u;
+        mine.x += t;
+        mine.y += (t + rows - 1) / rows;
+    }
+    uint2 incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = __shfl_up(incl.x, o), y = __shfl_up(incl.y, o);
+        if (lane >= o) {
+            incl.x += x;
+            incl.y += y;
+        }
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    uint2 at = make_uint2(incl.x - mine.x, incl.y - mine.y);
+    for (int w = 0; w < wave; ++w) {
+        at.x += wave_sum[w].x;
+        at.y += wave_sum[w].y;
+    }
+    for (int u = 0; u < per && k0 + u < K; ++u) {
+        const uint32_t t = total[k0 + u];
+        start[k0 + u] = at.x;
+        seg[k0 + u] = at.y;
+        at.x += t;
+        at.y += (t + rows - 1) / rows;
+        if (k0 + u == K - 1) {
+            start[K] = at.x;
+            seg[K] = at.y;
+        }
+    }
+}
+
+__global__ void __launch_bounds__(64 * kStableWaves) stable_scatter_kernel(const int32_t* __restrict__ bmu, const uint32_t* __restrict__ idx,
+                                                                           int64_t m, int K, int64_t per_block, int blocks,
+                                                                           const uint32_t* __restrict__ hist,
+                                                                           const uint32_t* __restrict__ start, uint32_t* __restrict__ perm)
+{
+    extern __shared__ uint32_t sort_lds[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int block = blockIdx.x * kStableWaves + wave;
+    if (block >= blocks) return;                              // (no barrier: a wavefront works on its own)
+    uint32_t* place = sort_lds + wave * K;
+    for (int k = lane; k < K; k += 64) place[k] = start[k] + hist[(size_t)block * K + k];
+    __builtin_amdgcn_wave_barrier();
+    const int64_t lo = (int64_t)block * per_block, hi = lo + per_block < m ? lo + per_block : m;
+    int b_next = lo + lane < hi ? bmu[lo + lane] : -1;
+    for (int64_t i0 = lo; i0 < hi; i0 += 64) {
+        const int64_t i = i0 + lane;
+        int b = b_next;
+        b_next = i + 64 < hi ? bmu[i + 64] : -1;
+        if (b >= K) b = -1;
+        const uint32_t base = b >= 0 ? place[b] : 0u;
+        // rank of every lane among the lanes of the same node, in lane order
+        unsigned long long todo = __ballot(b >= 0);
+        uint32_t rank = 0u, same = 0u;
+        while (todo) {
+            const int v = __builtin_amdgcn_readlane(b, __builtin_ctzll(todo));
+            const unsigned long long m_v = __ballot(b == v);
+            if (b == v) {
+                rank = __builtin_amdgcn_mbcnt_hi((unsigned)(m_v >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m_v, 0));
+                same = (uint32_t)__popcll(m_v);
+            }
+            todo &= ~m_v;
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (b >= 0) {
+            perm[base + rank] = idx ? idx[i] : (uint32_t)i;
+            if (rank == 0u) place[b] = base + same;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// LANES lanes per segment of one node's samples, four features a lane (slab: 4 LANES features); sums of node's first segment to
+// part[seg] like the others, added up by stable_finish_kernel
+template <int LANES>
+__global__ void __launch_bounds__(256) stable_sums_kernel(const float* __restrict__ X, int D, int64_t ldx, const uint32_t* __restrict__ start,
+                                                          const uint32_t* __restrict__ seg, int K, const uint32_t* __restrict__ perm,
+                                                          uint32_t rows, int slabs, double* __restrict__ part)
+{
+    constexpr int per_group = 256 / LANES;
+    const int sub = threadIdx.x % LANES, first_lane = (threadIdx.x & 63) - sub;
+    const int64_t units = (int64_t)gridDim.x * per_group;
+    const int64_t all = (int64_t)seg[K] * slabs;
+    for (int64_t unit = (int64_t)blockIdx.x * per_group + threadIdx.x / LANES; unit < all; unit += units) {
+        const int slab = (int)(unit % slabs);
+        const uint32_t sg = (uint32_t)(unit / slabs);
+        int k = 0, top = K;                                   // the last node with seg[k] <= sg
+        while (top - k > 1) {
+            const int mid = (k + top) >> 1;
+            if (seg[mid] <= sg) k = mid;
+            else top = mid;
+        }
+        const uint32_t lo = start[k] + (sg - seg[k]) * rows, end = start[k + 1];
+        const uint32_t hi = end - lo < rows ? end : lo + rows;
+        const int f_own = (slab * LANES + sub) * 4;
+        const bool on = f_own < D;
+        const int f = f_own < D - 4 ? f_own : D - 4, shift = f_own - f;
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        constexpr int G = 8;                                  // rows in flight
+        for (uint32_t p = lo; p < hi; p += G) {
+            const int left = hi - p < (uint32_t)G ? (int)(hi - p) : G;
+            const uint32_t row_mine = perm[p + (sub < left ? sub : left - 1)];
+            float4 v[G];
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const uint32_t row = __shfl(row_mine, first_lane + (u < left ? u : 0));
+                if (u < left && on) __builtin_memcpy(&v[u], X + (int64_t)row * ldx + f, sizeof(float4));
+                else v[u] = float4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                acc[0] += (double)v[u].x;
+                acc[1] += (double)v[u].y;
+                acc[2] += (double)v[u].z;
+                acc[3] += (double)v[u].w;
+            }
+        }
+        if (on) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (t >= shift) part[(size_t)sg * D + f + t] = acc[t];
+        }
+    }
+}
+
+__global__ void __launch_bounds__(256) stable_finish_kernel(const double* __restrict__ part, const uint32_t* __restrict__ seg, int K, int D,
+                                                            int zero_first, double* __restrict__ S)
+{
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= K * D) return;
+    const int k = e / D, f = e - k * D;
+    double s = 0.0;
+#pragma unroll 8
+    for (uint32_t q = seg[k]; q < seg[k + 1]; ++q) s += part[(size_t)q * D + f];
+    S[e] = (zero_first ? 0.0 : S[e]) + s;
+}
+
 // LANES lanes (32 or 64) per range of the sorted order, four features a lane, features [4 LANES slab, ...) of the row.
 template <int LANES>
 __global__ void __launch_bounds__(256) sort_sums_kernel(const float* __restrict__ X, int D, int64_t ldx, const uint32_t* __restrict__ start,
@@ -191,6 +366,73 @@ __global__ void __launch_bounds__(256) sort_sums_kernel(const float* __restrict_
         }
 }
 
+static int sort_workspace(som_ctx* ctx, size_t need)
+{
+    if (need <= ctx->acc_bytes) return SOM_OK;
+    if (ctx->acc_blob) {
+        if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync before workspace growth")) return rc;
+        (void)hipFree(ctx->acc_blob);
+        ctx->acc_blob = nullptr;
+        ctx->acc_bytes = 0;
+    }
+    if (hipMalloc(&ctx->acc_blob, need) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(ctx, SOM_ENOMEM, "cannot allocate %zu bytes for the accumulation workspace", need);
+    }
+    ctx->acc_bytes = need;
+    return SOM_OK;
+}
+
+// The fixed-order sums.  Returns 1 when the shape is not served by this path.
+int accumulate_stable_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m, const int32_t* bmu,
+                          int32_t K, double* S, unsigned long long* n, bool zero_first)
+{
+    if (m <= 0 || D < 4 || K > kStableNodes) return 1;
+    int64_t per_block = (m + kStableBlocks - 1) / kStableBlocks;
+    if (per_block < 256) per_block = 256;
+    const int blocks = (int)((m + per_block - 1) / per_block);
+    // segments: about four wavefronts per SIMD, 32 to 1024 rows
+    const int lanes = D <= 64 ? 16 : D <= 128 ? 32 : 64;
+    const int slabs = (D + 4 * lanes - 1) / (4 * lanes);
+    int64_t rows = m * lanes * slabs / (256 * 4 * 4 * 64);
+    rows = rows < 32 ? 32 : rows > 1024 ? 1024 : rows;
+    const size_t segs_most = (size_t)(m / rows) + K;
+    const size_t hist_words = (size_t)blocks * K, words = (hist_words + 3 * (size_t)K + 2 + (size_t)m + 1) / 2 * 2;
+    if (int rc = sort_workspace(ctx, words * sizeof(uint32_t) + segs_most * D * sizeof(double))) return rc;
+    uint32_t* hist = (uint32_t*)ctx->acc_blob;
+    uint32_t* total = hist + hist_words;
+    uint32_t* start = total + K;
+    uint32_t* seg = start + K + 1;
+    uint32_t* perm = seg + K + 1;
+    double* part = (double*)(hist + words);
+    const size_t lds = (size_t)K * kStableWaves * sizeof(uint32_t);
+    static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
+    bool& attr_set = attr_set_dev[ctx->device];
+    if (!attr_set) {
+        for (const void* k : {reinterpret_cast<const void*>(stable_hist_kernel), reinterpret_cast<const void*>(stable_scatter_kernel)})
+            if (int rc = check_hip(ctx, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kStableNodes * kStableWaves * 4),
+                                   "raising the dynamic LDS limit"))
+                return rc;
+        attr_set = true;
+    }
+    const dim3 grid((blocks + kStableWaves - 1) / kStableWaves), wg(64 * kStableWaves);
+    hipLaunchKernelGGL(stable_hist_kernel, grid, wg, lds, ctx->stream, bmu, m, K, per_block, blocks, hist);
+    if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (stable) histogram launch")) return rc;
+    hipLaunchKernelGGL(sort_columns_kernel, dim3((K + 63) / 64), dim3(1024), 0, ctx->stream, hist, K, blocks, total, n, zero_first ? 1 : 0);
+    if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (stable) offsets launch")) return rc;
+    hipLaunchKernelGGL(stable_starts_kernel, dim3(1), dim3(1024), 0, ctx->stream, total, K, (uint32_t)rows, start, seg);
+    if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (stable) starts launch")) return rc;
+    hipLaunchKernelGGL(stable_scatter_kernel, grid, wg, lds, ctx->stream, bmu, idx, m, K, per_block, blocks, hist, start, perm);
+    if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (stable) scatter launch")) return rc;
+    const int64_t groups_most = ((int64_t)segs_most * slabs * lanes + 255) / 256;
+    const unsigned groups = (unsigned)(groups_most < 8192 ? groups_most : 8192);
+    auto kern = lanes == 16 ? stable_sums_kernel<16> : lanes == 32 ? stable_sums_kernel<32> : stable_sums_kernel<64>;
+    hipLaunchKernelGGL(kern, dim3(groups), dim3(256), 0, ctx->stream, X, D, ldx, start, seg, K, perm, (uint32_t)rows, slabs, part);
+    if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (stable) sums launch")) return rc;
+    hipLaunchKernelGGL(stable_finish_kernel, dim3((K * D + 255) / 256), dim3(256), 0, ctx->stream, part, seg, K, D, zero_first ? 1 : 0, S);
+    return check_hip(ctx, hipGetLastError(), "accumulate (stable) finish launch");
+}
+
 // Returns 1 when the shape is not served by this path, SOM_OK on success, a negative code on failure.
 int accumulate_sort_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m, const int32_t* bmu,
                         int32_t K, double* S, unsigned long long* n, bool zero_first)
@@ -201,19 +443,7 @@ int accumulate_sort_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, co
     const int blocks = (int)((m + per_block - 1) / per_block);
     const size_t hist_words = (size_t)blocks * K, small_words = 2 * (size_t)K + 1;
     const size_t need = (hist_words + small_words + (size_t)m) * sizeof(uint32_t);
-    if (need > ctx->acc_bytes) {
-        if (ctx->acc_blob) {
-            if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync before workspace growth")) return rc;
-            (void)hipFree(ctx->acc_blob);
-            ctx->acc_blob = nullptr;
-            ctx->acc_bytes = 0;
-        }
-        if (hipMalloc(&ctx->acc_blob, need) != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(ctx, SOM_ENOMEM, "cannot allocate %zu bytes for the accumulation workspace", need);
-        }
-        ctx->acc_bytes = need;
-    }
+    if (int rc = sort_workspace(ctx, need)) return rc;
     uint32_t* hist = (uint32_t*)ctx->acc_blob;
     uint32_t* total = hist + hist_words;
     uint32_t* start = total + K;

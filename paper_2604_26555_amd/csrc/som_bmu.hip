@@ -30,6 +30,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace som {
 
 constexpr int kWavesPerGroup = 4;
@@ -1056,9 +1058,13 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // writes of stage s + 1 and the first reads of it.
     constexpr int NB = kNodesPerStage / 32;
     static_assert(NB == 4, "two blocks, the LDS writes, one block, the barrier, one block");
-    for (int st = 0; st < nstages; ++st) {
+    // A last stage that ends in whole blocks of padding nodes (K = 400: a fifth of all blocks) is left to the code behind the
+    // loop, which stops at its last block of real nodes.
+    const int live_last = (a.K - (nstages - 1) * kNodesPerStage + 31) / 32;
+    const int nwhole = live_last < NB ? nstages - 1 : nstages;
+    for (int st = 0; st < nwhole; ++st) {
         const int buf = st & 1;
-        // (the last iteration reloads its own stage into the idle buffer, which keeps the loop branch-free)
+        // (the last iteration reloads its own stage into the idle buffer, which keeps the loads branch-free)
         // Nine float4 per thread (D > 50) would not leave the registers for the rest: they travel in two batches.
         float4 pre0, pre1, pre2, pre3, pre4, pre5, pre6, pre7, pre8;
         static_assert(PRE <= 9, "stage copy holds at most nine float4 per thread");
@@ -1101,8 +1107,39 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         block(accB, accA, wh, wl, wtl, c, rows_of(obuf, 0), norms_of(obuf, 0), true, st, 2);
     }
     // the last block's scores
+    auto fold_last = [&](const floatx16 (&acc)[MS], auto nb) {
 #pragma unroll
-    for (int sidx = 0; sidx < STEPS_ALL; ++sidx) fold_step(accB, sidx, nstages - 1, 3);
+        for (int sidx = 0; sidx < STEPS_ALL; ++sidx) fold_step(acc, sidx, nstages - 1, decltype(nb)::value);
+        if constexpr (!CAND) {
+            // the stage number of the classes whose last block (2 of the even ones, 3 of the odd ones) did not come
+#pragma unroll
+            for (int mb = 0; mb < MS; ++mb)
+#pragma unroll
+                for (int c = 0; c < CLS; ++c)
+                    if ((decltype(nb)::value < 2 && (c >> 1) <= decltype(nb)::value) || (decltype(nb)::value == 2 && (c >> 1) == 1))
+                        tsel[mb][c] = (best[mb][c] > before[mb][c]) ? nstages - 1 : tsel[mb][c];
+        }
+    };
+    if (live_last == NB) {
+        fold_last(accB, std::integral_constant<int, 3>{});
+    } else {
+        const int st = nstages - 1;
+        const char* wbuf = ldsb + (size_t)(st & 1) * STAGE_F4 * 16;
+        auto rows_of = [&](int nb) { return wbuf + (nb * 32 + j) * RS + g * 32; };
+        auto norms_of = [&](int nb) { return reinterpret_cast<const float4*>(wbuf + kNodesPerStage * RS + nb * 32 * 4) + g; };
+        block(accA, accB, wh, wl, wtl, c, rows_of(1), norms_of(1), true, st - 1, 3);
+        if (live_last == 1) {
+            fold_last(accA, std::integral_constant<int, 0>{});
+        } else {
+            block(accB, accA, wh, wl, wtl, c, rows_of(2), norms_of(2), true, st, 0);
+            if (live_last == 2) {
+                fold_last(accB, std::integral_constant<int, 1>{});
+            } else {
+                block(accA, accB, wh, wl, wtl, c, nullptr, nullptr, false, st, 1);
+                fold_last(accA, std::integral_constant<int, 2>{});
+            }
+        }
+    }
 
     if constexpr (CAND) {
         // Direct float32 differences over the nodes this lane noted for its sample (the true winner is among the two

@@ -4,11 +4,11 @@
 //     w_j <- Num_j / Den_j  where Den_j >= eps_h, otherwise w_j stays.
 // The contraction Num = H^T S (with n as one more column of S) is a dense K x K . K x (D + 1) product in float64:
 // it runs on v_mfma_f64_16x16x4_f64.
-//   1. contract_kernel     one wavefront = 16 updated nodes x up to 64 columns x one sixteenth of the k range; for
+//   1. contract_kernel     one wavefront = 16 or 32 updated nodes x up to 64 columns x a quarter of a part of the k range; for
 //                          D + 1 <= 64 the influences h = exp(-G^2 / 2 sigma^2) are computed in the wavefront right
 //                          where the MFMA needs them (each one is needed exactly once), otherwise influence_kernel
 //                          writes them out first and the wavefronts of the column slabs read them;
-//   2. finish_kernel       adds the sixteen partials in a fixed order, applies the threshold, writes W, counts.
+//   2. finish_kernel       adds the parts' partials in a fixed order, applies the threshold, writes W, counts.
 #include "som_internal.hpp"
 
 #include <math.h>
@@ -19,20 +19,35 @@ namespace som {
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-constexpr int kSplitK = 16;  // wavefronts sharing one block of updated nodes (partials are stored, then summed in order)
+// Parts of the k range: the four wavefronts of a workgroup take a quarter each and add their results in LDS, and up to
+// kSplitK workgroups share a block of updated nodes where those alone leave the chip idle (their partials are stored, then
+// summed in order).  With sixteen stored partials whatever the shape, the partials were most of the traffic: 262 MB each way
+// at K = 1024, D = 2000 (207 + 53 us for contraction and finish there, 96 + 11 now; 228 + 28 -> 153 + 14 us at K = 4096, D = 50).
+constexpr int kSplitK = 4;
 
-// shift[j] = min over occupied nodes k of G[k][j]^2 (+inf when there is none): one thread per updated node j
-__global__ void __launch_bounds__(256) shift_kernel(const float* __restrict__ G, const unsigned long long* __restrict__ n,
-                                                    int K, double* __restrict__ shift)
+// shift[j] = min over occupied nodes k of G[k][j]^2 (+inf when there is none): 64 columns per workgroup, sixteen runs of rows
+__global__ void __launch_bounds__(1024) shift_kernel(const float* __restrict__ G, const unsigned long long* __restrict__ n,
+                                                     int K, double* __restrict__ shift)
 {
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= K) return;
+    __shared__ double low[16][64];
+    const int l = threadIdx.x & 63, seg = threadIdx.x >> 6;
+    const int j = blockIdx.x * 64 + l;
+    const int per = (K + 15) / 16, lo = seg * per, hi = lo + per < K ? lo + per : K;
     double m = INFINITY;
-    for (int k = 0; k < K; ++k) {
-        const double gd = (double)G[(size_t)k * K + j];
-        if (n[k] != 0ull && gd * gd < m) m = gd * gd;
+    if (j < K) {
+#pragma unroll 8
+        for (int k = lo; k < hi; ++k) {
+            const double gd = (double)G[(size_t)k * K + j];
+            if (n[k] != 0ull && gd * gd < m) m = gd * gd;
+        }
     }
-    shift[j] = m;
+    low[seg][l] = m;
+    __syncthreads();
+    if (seg == 0 && j < K) {
+#pragma unroll
+        for (int q = 1; q < 16; ++q) m = low[q][l] < m ? low[q][l] : m;
+        shift[j] = m;
+    }
 }
 
 // h = exp(-(g^2 - shift_j) / 2 sigma^2); with a shift only occupied nodes k contribute (their exponent is <= 0)
@@ -52,41 +67,51 @@ __global__ void __launch_bounds__(256) influence_kernel(const float* __restrict_
     H[e] = influence_of((double)G[e], inv2s2, shift ? shift[j] : 0.0, !shift || n[k] != 0ull);
 }
 
-// grid (ceil(K / 16), ceil((D + 1) / 64), kSplitK / 4), 4 wavefronts per workgroup, one k-split each.
+// grid (ceil(K / (16 JT)), ceil((D + 1) / 64), splits), 4 wavefronts per workgroup, a quarter of the workgroup's k range each.
 // MFMA operands (16 x 16 x 4, float64): lane l supplies A[i = l % 16][k = l / 16] = h[k][j0 + i] and
 // B[k = l / 16][c = l % 16] = S[k][c0 + c] (column D is n); its register r receives row l / 16 + 4 r, column l % 16.
-template <bool FUSED>
+// JT = 2: two blocks of sixteen updated nodes per wavefront, for maps with enough of them: S is read half as often.
+template <bool FUSED, int JT>
 __global__ void __launch_bounds__(256) contract_kernel(const float* __restrict__ G, const double* __restrict__ H,
                                                        double inv2s2, const double* __restrict__ shift,
                                                        const double* __restrict__ S,
                                                        const unsigned long long* __restrict__ n, int K, int D,
                                                        double* __restrict__ part)
 {
+    __shared__ double sums[4][4][4][64];               // [wavefront][column block][register][lane]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int z = blockIdx.z * 4 + wave;
-    const int j0 = blockIdx.x * 16, c0 = blockIdx.y * 64;
-    const int kper = ((K + kSplitK * 4 - 1) / (kSplitK * 4)) * 4;
+    const int j0 = blockIdx.x * 16 * JT, c0 = blockIdx.y * 64;
+    const int slices = gridDim.z * 4, z = blockIdx.z * 4 + wave;
+    const int kper = ((K + slices * 4 - 1) / (slices * 4)) * 4;
     const int k_lo = z * kper;
     const int k_hi = (k_lo + kper < K) ? k_lo + kper : K;
     const int li = lane & 15, lk = lane >> 4;
-    const int j = j0 + li;
-    doublex4 acc[4];
+    doublex4 acc[JT][4];
+    int jc[JT];
+    double shift_j[JT];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = doublex4{0.0, 0.0, 0.0, 0.0};
-    // Sixteen k-steps at a time: first every load of the batch (one wavefront per SIMD has nothing else to cover a
-    // round trip to L2 with), then the sixteen exponentials, then the MFMAs.
-    constexpr int kBatch = 16;
-    const int jc = j < K ? j : K - 1;
-    const double shift_j = (FUSED && shift) ? shift[jc] : 0.0;
+    for (int q = 0; q < JT; ++q) {
+        const int j = j0 + 16 * q + li;
+        jc[q] = j < K ? j : K - 1;
+        shift_j[q] = (FUSED && shift) ? shift[jc[q]] : 0.0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[q][t] = doublex4{0.0, 0.0, 0.0, 0.0};
+    }
+    // kBatch k-steps at a time: first every load of the batch (one wavefront per SIMD has nothing else to cover a
+    // round trip to L2 with), then the exponentials, then the MFMAs.
+    constexpr int kBatch = 16 / JT;
     for (int kb = k_lo; kb < k_hi; kb += 4 * kBatch) {
-        float gv[kBatch];
-        double nv[kBatch], sv[kBatch][4];
+        float gv[JT][kBatch];
+        double nv[JT][kBatch], sv[kBatch][4];
 #pragma unroll
         for (int s = 0; s < kBatch; ++s) {
             const int k = kb + 4 * s + lk;
             const int kc = k < K ? k : K - 1;                 // clamped row: the loads are unconditional
-            if (FUSED) gv[s] = G[(size_t)kc * K + jc];
-            else nv[s] = H[(size_t)kc * K + jc];              // holds h until it is replaced by n below
+#pragma unroll
+            for (int q = 0; q < JT; ++q) {
+                if (FUSED) gv[q][s] = G[(size_t)kc * K + jc[q]];
+                else nv[q][s] = H[(size_t)kc * K + jc[q]];
+            }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int c = c0 + 16 * t + li;
@@ -96,35 +121,42 @@ __global__ void __launch_bounds__(256) contract_kernel(const float* __restrict__
 #pragma unroll
         for (int s = 0; s < kBatch; ++s) {
             const int k = kb + 4 * s + lk;
-            const bool in = k < k_hi && j < K;
-            double h;
-            if (FUSED) {
-                const bool occupied = !shift || n[k < K ? k : K - 1] != 0ull;
-                h = in ? influence_of((double)gv[s], inv2s2, shift_j, occupied) : 0.0;
-            } else {
-                h = in ? nv[s] : 0.0;
-            }
+            const bool occupied = !(FUSED && shift) || n[k < K ? k : K - 1] != 0ull;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int c = c0 + 16 * t + li;
-                const double b = (k < k_hi && c <= D) ? sv[s][t] : 0.0;
-                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(h, b, acc[t], 0, 0, 0);
+            for (int q = 0; q < JT; ++q) {
+                const bool in = k < k_hi && j0 + 16 * q + li < K;
+                double h;
+                if (FUSED) h = in ? influence_of((double)gv[q][s], inv2s2, shift_j[q], occupied) : 0.0;
+                else h = in ? nv[q][s] : 0.0;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int c = c0 + 16 * t + li;
+                    const double b = (k < k_hi && c <= D) ? sv[s][t] : 0.0;
+                    acc[q][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(h, b, acc[q][t], 0, 0, 0);
+                }
             }
         }
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int c = c0 + 16 * t + li;
+    for (int q = 0; q < JT; ++q) {
+        if (q > 0) __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sums[wave][t][r][lane] = acc[q][t][r];
+        __syncthreads();
+        const int c = c0 + 16 * wave + li;                     // wavefront w adds up column block w
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int jr = j0 + lk + 4 * r;
-            if (jr < K && c <= D) part[((size_t)z * K + jr) * (D + 1) + c] = acc[t][r];
+            const int jr = j0 + 16 * q + lk + 4 * r;
+            const double v = ((sums[0][wave][r][lane] + sums[1][wave][r][lane]) + sums[2][wave][r][lane]) + sums[3][wave][r][lane];
+            if (jr < K && c <= D) part[((size_t)blockIdx.z * K + jr) * (D + 1) + c] = v;
         }
     }
 }
 
 // plain = true: w <- Num / Den (eta = 1, no momentum);  otherwise delta = eta (Num / Den - w) + mu v, w += delta
-__global__ void __launch_bounds__(256) finish_kernel(const double* __restrict__ part,
+__global__ void __launch_bounds__(256) finish_kernel(const double* __restrict__ part, int splits,
                                                      const unsigned long long* __restrict__ n, int K, int D,
                                                      double eps_h, bool plain, double eta, double mu,
                                                      float* __restrict__ V, float* __restrict__ W,
@@ -136,8 +168,7 @@ __global__ void __launch_bounds__(256) finish_kernel(const double* __restrict__ 
     const size_t stride = (size_t)K * (D + 1);
     const double* row = part + (size_t)j * (D + 1);
     double num = 0.0, den = 0.0;
-#pragma unroll
-    for (int z = 0; z < kSplitK; ++z) {
+    for (int z = 0; z < splits; ++z) {
         num += row[z * stride + d];
         den += row[z * stride + D];
     }
@@ -164,26 +195,31 @@ static int update_launch(som_ctx* ctx, double* H, double* part, double* shift_ws
 {
     const size_t h_elems = (size_t)K * K;
     const double inv2s2 = 1.0 / (2.0 * sigma * sigma);
-    const dim3 grid((K + 15) / 16, (D + 1 + 63) / 64, kSplitK / 4);
+    // a wavefront for every SIMD: 4 per block of sixteen nodes and 64 columns, more splits where those are too few
+    const int jt = K >= 2048 ? 2 : 1;
+    const int blocks = ((K + 16 * jt - 1) / (16 * jt)) * ((D + 1 + 63) / 64);
+    const int splits = blocks >= 256 ? 1 : blocks >= 128 ? 2 : kSplitK;
+    const dim3 grid((K + 16 * jt - 1) / (16 * jt), (D + 1 + 63) / 64, splits);
     double* shift = nullptr;
     if (ctx->safeguard == SOM_SAFEGUARD_SHIFT) {
         shift = shift_ws;
-        hipLaunchKernelGGL(shift_kernel, dim3((K + 255) / 256), dim3(256), 0, ctx->stream, G, n, K, shift);
+        hipLaunchKernelGGL(shift_kernel, dim3((K + 63) / 64), dim3(1024), 0, ctx->stream, G, n, K, shift);
         if (int rc = check_hip(ctx, hipGetLastError(), "exponent shift launch")) return rc;
     }
     if (grid.y == 1) {
-        hipLaunchKernelGGL(contract_kernel<true>, grid, dim3(256), 0, ctx->stream, G, (const double*)nullptr, inv2s2,
-                           (const double*)shift, S, n, K, D, part);
+        auto kern = jt == 2 ? contract_kernel<true, 2> : contract_kernel<true, 1>;
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, ctx->stream, G, (const double*)nullptr, inv2s2, (const double*)shift, S, n, K, D,
+                           part);
     } else {
         hipLaunchKernelGGL(influence_kernel, dim3((unsigned)((h_elems + 255) / 256)), dim3(256), 0, ctx->stream, G, K, inv2s2,
                            (const double*)shift, n, H);
         if (int rc = check_hip(ctx, hipGetLastError(), "influence kernel launch")) return rc;
-        hipLaunchKernelGGL(contract_kernel<false>, grid, dim3(256), 0, ctx->stream, G, (const double*)H, inv2s2,
-                           (const double*)nullptr, S, n, K, D, part);
+        auto kern = jt == 2 ? contract_kernel<false, 2> : contract_kernel<false, 1>;
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, ctx->stream, G, (const double*)H, inv2s2, (const double*)nullptr, S, n, K, D, part);
     }
     if (int rc = check_hip(ctx, hipGetLastError(), "contraction kernel launch")) return rc;
     const bool plain = ctx->eta == 1.0 && ctx->mu == 0.0;
-    hipLaunchKernelGGL(finish_kernel, dim3((K * D + 255) / 256), dim3(256), 0, ctx->stream, part, n, K, D, eps_h, plain,
+    hipLaunchKernelGGL(finish_kernel, dim3((K * D + 255) / 256), dim3(256), 0, ctx->stream, part, splits, n, K, D, eps_h, plain,
                        ctx->eta, ctx->mu, ctx->velocity, W, small);
     return check_hip(ctx, hipGetLastError(), "update finish launch");
 }
