@@ -282,15 +282,26 @@ __global__ void __launch_bounds__(256) stable_sums_kernel(const float* __restric
     }
 }
 
-__global__ void __launch_bounds__(256) stable_finish_kernel(const double* __restrict__ part, const uint32_t* __restrict__ seg, int K, int D,
-                                                            int zero_first, double* __restrict__ S)
+// a workgroup per node and 64 features: sixteen runs of the node's segments, added up in order
+__global__ void __launch_bounds__(1024) stable_finish_kernel(const double* __restrict__ part, const uint32_t* __restrict__ seg, int D,
+                                                             int zero_first, double* __restrict__ S)
 {
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= K * D) return;
-    const int k = e / D, f = e - k * D;
+    __shared__ double run[16][64];
+    const int l = threadIdx.x & 63, r = threadIdx.x >> 6;
+    const int k = blockIdx.x, f = blockIdx.y * 64 + l;
+    const uint32_t first = seg[k], all = seg[k + 1] - first, per = (all + 15) / 16;
+    const uint32_t lo = r * per, hi = lo + per < all ? lo + per : all;
     double s = 0.0;
-#pragma unroll 8
-    for (uint32_t q = seg[k]; q < seg[k + 1]; ++q) s += part[(size_t)q * D + f];
+    if (f < D) {
+#pragma unroll 4
+        for (uint32_t q = lo; q < hi; ++q) s += part[(size_t)(first + q) * D + f];
+    }
+    run[r][l] = s;
+    __syncthreads();
+    if (r != 0 || f >= D) return;
+#pragma unroll
+    for (int q = 1; q < 16; ++q) s += run[q][l];
+    const size_t e = (size_t)k * D + f;
     S[e] = (zero_first ? 0.0 : S[e]) + s;
 }
 
@@ -429,7 +440,7 @@ int accumulate_stable_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, 
     auto kern = lanes == 16 ? stable_sums_kernel<16> : lanes == 32 ? stable_sums_kernel<32> : stable_sums_kernel<64>;
     hipLaunchKernelGGL(kern, dim3(groups), dim3(256), 0, ctx->stream, X, D, ldx, start, seg, K, perm, (uint32_t)rows, slabs, part);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (stable) sums launch")) return rc;
-    hipLaunchKernelGGL(stable_finish_kernel, dim3((K * D + 255) / 256), dim3(256), 0, ctx->stream, part, seg, K, D, zero_first ? 1 : 0, S);
+    hipLaunchKernelGGL(stable_finish_kernel, dim3(K, (D + 63) / 64), dim3(1024), 0, ctx->stream, part, seg, D, zero_first ? 1 : 0, S);
     return check_hip(ctx, hipGetLastError(), "accumulate (stable) finish launch");
 }
 

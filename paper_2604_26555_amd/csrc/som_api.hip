@@ -330,6 +330,17 @@ struct HostSmall {
     unsigned int scal[4];
 };
 
+static __global__ void stats_kernel(const double* __restrict__ qe, const int32_t* __restrict__ small, const unsigned int* __restrict__ scal,
+                             HostSmall* __restrict__ out)
+{
+    const int t = threadIdx.x;
+    if (t < 2) out->qe[t] = qe[t];
+    if (t < 4) {
+        out->small[t] = small[t];
+        out->scal[t] = scal[t];
+    }
+}
+
 static int begin_epoch(som_ctx* ctx, int32_t K, int32_t D, int64_t chunk_rows)
 {
     if (int rc = grow(ctx, &ctx->bmu_ws, &ctx->bmu_elems, (size_t)chunk_rows, "the BMU indices")) return rc;
@@ -338,16 +349,19 @@ static int begin_epoch(som_ctx* ctx, int32_t K, int32_t D, int64_t chunk_rows)
     return SOM_OK;   // qe and the small counters are cleared by the weight-preparation kernel
 }
 
-static int finish_stats(som_ctx* ctx, int64_t m, int64_t n_recheck, som_stats* stats, bool timed, float ms_h2d)
+// scal: the preparation's result words
+static int finish_stats(som_ctx* ctx, const unsigned int* scal, int64_t m, som_stats* stats, bool timed, float ms_h2d)
 {
     HostSmall* h = (HostSmall*)ctx->host_small;
-    if (int rc = check_hip(ctx, hipMemcpyAsync(h->qe, ctx->qe, sizeof(h->qe), hipMemcpyDeviceToHost, ctx->stream), "reading statistics")) return rc;
-    if (int rc = check_hip(ctx, hipMemcpyAsync(h->small, ctx->small, sizeof(h->small), hipMemcpyDeviceToHost, ctx->stream), "reading statistics")) return rc;
+    // (one small kernel writes all of them to the pinned mirror: three copies of a few words each took 4 us of the stream
+    // apiece and as much of the host's time)
+    hipLaunchKernelGGL(stats_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->qe, ctx->small, scal, h);
+    if (int rc = check_hip(ctx, hipGetLastError(), "reading statistics")) return rc;
     if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "waiting for the epoch")) return rc;
     stats->sum_dist = h->qe[0];
     stats->sum_dist2 = h->qe[1];
     stats->m = m;
-    stats->n_recheck = n_recheck;
+    stats->n_recheck = h->scal[3];
     stats->n_guarded = h->small[0];
     stats->n_empty = h->small[1];
     stats->ms_bmu_acc = stats->ms_update = 0.f;
@@ -394,16 +408,11 @@ int som_epoch(som_ctx* ctx, const float* X, int64_t N, int32_t D, int64_t ldx, c
     a.bmu = ctx->bmu_ws;
     if (int rc = bmu_run(ctx, prep, a)) return rc;
     if (int rc = accumulate_run(ctx, X, D, ldx, idx, m, ctx->bmu_ws, K, ctx->S, ctx->n, true)) return rc;
-    HostSmall* h = (HostSmall*)ctx->host_small;
-    if (stats) {
-        (void)hipEventRecord(ctx->ev_t[1], ctx->stream);
-        if (int rc = check_hip(ctx, hipMemcpyAsync(h->scal, prep.scal, sizeof(h->scal), hipMemcpyDeviceToHost, ctx->stream), "reading statistics")) return rc;
-    }
+    if (stats) (void)hipEventRecord(ctx->ev_t[1], ctx->stream);
     if (int rc = update_run(ctx, ctx->S, ctx->n, G, K, D, sigma, eps_h, W, ctx->small)) return rc;
     if (stats) {
         (void)hipEventRecord(ctx->ev_t[2], ctx->stream);
-        if (int rc = finish_stats(ctx, m, 0, stats, true, 0.f)) return rc;
-        stats->n_recheck = h->scal[3];
+        if (int rc = finish_stats(ctx, prep.scal, m, stats, true, 0.f)) return rc;
     }
     return SOM_OK;
 }
@@ -523,7 +532,6 @@ static int stream_epoch(som_ctx* ctx, const ChunkSource& src, int64_t N, int32_t
         (void)hipGetLastError();
         return rc;
     };
-    HostSmall* h = (HostSmall*)ctx->host_small;
     for (int64_t c = 0; c < nchunks; ++c) {
         const int b = (int)(c & 1);
         const int64_t lo = c * chunk_rows;
@@ -566,8 +574,6 @@ static int stream_epoch(som_ctx* ctx, const ChunkSource& src, int64_t N, int32_t
         (void)hipEventRecord(ctx->ev_consumed[b], ctx->stream);
     }
     (void)hipEventRecord(ctx->ev_t[1], ctx->stream);
-    if (int rc = check_hip(ctx, hipMemcpyAsync(h->scal, prep.scal, sizeof(h->scal), hipMemcpyDeviceToHost, ctx->stream), "reading statistics"))
-        return bail(rc);
     if (int rc = update_run(ctx, ctx->S, ctx->n, G, K, D, sigma, eps_h, W, ctx->small)) return bail(rc);
     (void)hipEventRecord(ctx->ev_t[2], ctx->stream);
     int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "waiting for the epoch");
@@ -578,7 +584,7 @@ static int stream_epoch(som_ctx* ctx, const ChunkSource& src, int64_t N, int32_t
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, ctx->h2d_events[2 * c], ctx->h2d_events[2 * c + 1]) == hipSuccess) ms_h2d += ms;
     }
-    if (stats) return finish_stats(ctx, N, (int64_t)h->scal[3], stats, true, ms_h2d);
+    if (stats) return finish_stats(ctx, prep.scal, N, stats, true, ms_h2d);
     return SOM_OK;
 }
 

@@ -135,14 +135,47 @@ __device__ __forceinline__ void split_prep_slot(const float* __restrict__ W, int
 // The rows for the bf16 matrix pipe (stage16 != null; layout at bmu_split_tile) are written by the same launch: one thread per
 // (node, slot), and the wavefront that sums a node's norm also writes it where the split search reads it.
 
+// OWN (D <= 64): the workgroup works out the centre itself, as the mean of up to kCentreNodes nodes spread over the map (any
+// vector near the middle of the weights does, and it is the same one in every workgroup), instead of waiting for a kernel of
+// its own; workgroup 0 stores it for the search.
+constexpr int kCentreNodes = 64;
+
+template <bool OWN>
 __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__ W, int K, int D, int kpad, int stride,
-                                                       int nch, int stage_floats, const float* __restrict__ centre,
+                                                       int nch, int stage_floats, float* __restrict__ centre_mem,
                                                        float* __restrict__ stage, float* __restrict__ wt,
-                                                       unsigned int* __restrict__ scal, double* __restrict__ qe,
-                                                       int32_t* __restrict__ small, const SplitPrep sp)
+                                                       unsigned int* __restrict__ scal, unsigned int* __restrict__ scal_next,
+                                                       double* __restrict__ qe, int32_t* __restrict__ small, const SplitPrep sp)
 {
     const int e = blockIdx.x * 256 + threadIdx.x;
     const int cols = nch * stride;
+    __shared__ float centre_lds[64];
+    __shared__ float centre_part[4][64];
+    const float* centre = centre_mem;
+    if constexpr (OWN) {
+        // (the result words of this call were cleared by the call before; this one clears the next one's)
+        if (blockIdx.x == 0 && threadIdx.x < 16) scal_next[threadIdx.x] = 0u;
+        const int f = threadIdx.x & 63, q = threadIdx.x >> 6;
+        const int count = K < kCentreNodes ? K : kCentreNodes;
+        float v[kCentreNodes / 4];
+#pragma unroll
+        for (int u = 0; u < kCentreNodes / 4; ++u) {
+            const int t = 4 * u + q;
+            v[u] = (t < count && f < D) ? W[(size_t)((int64_t)t * K / count) * D + f] : 0.0f;
+        }
+        float s = 0.0f;
+#pragma unroll
+        for (int u = 0; u < kCentreNodes / 4; ++u) s += v[u];
+        centre_part[q][f] = s;
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            const float c = (((centre_part[0][f] + centre_part[1][f]) + centre_part[2][f]) + centre_part[3][f]) / (float)count;
+            centre_lds[f] = c;                       // (zero behind the row)
+            if (blockIdx.x == 0) centre_mem[f] = c;
+        }
+        __syncthreads();
+        centre = centre_lds;
+    }
     if (e < 2 && qe) qe[e] = 0.0;
     if (e < 4 && small) small[e] = 0;
     if (sp.stage16) split_prep_slot(W, K, D, kpad, centre, sp, e);
@@ -1941,7 +1974,7 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
 }
 
 template <bool PAIRS>
-__global__ void __launch_bounds__(kExactThreads) bmu_exact_kernel(const BmuArgs a)
+__global__ void __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) bmu_exact_kernel(const BmuArgs a)
 {
     // PAIRS: three rows of each entry of the pair list; otherwise only the slab of the listed samples' features
     __shared__ float4 lds4[PAIRS ? kPairGroup * 3 * kPairStride : 64 * (kExactGroup / 4)];
@@ -2186,7 +2219,10 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
             return fail(ctx, SOM_ENOMEM, "cannot allocate %zu bytes for the weight workspace", need);
         }
         ctx->prep_bytes = need;
+        ctx->prep_clean = false;
     }
+    // (a call that went through the centre kernel leaves no cleared words behind, nor does a new allocation)
+    const bool fresh = !ctx->prep_clean;
     char* base = (char*)ctx->prep_blob;
     out->scal = (unsigned int*)base;
     out->stage = (float*)(base + 256);
@@ -2201,8 +2237,20 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     out->stride = stride;
     out->nch = nch;
     out->calls = 0;
-    hipLaunchKernelGGL(bmu_centre_kernel, dim3((unsigned)(centre_bytes / 256)), dim3(1024), 0, ctx->stream, W, K, D,
-                       out->centre, out->scal);
+    const bool own_centre = nch == 1;
+    unsigned int* scal_next = nullptr;
+    if (own_centre) {
+        // two sets of result words take turns; both are clear after the allocation
+        out->scal = (unsigned int*)(base + 128 * ctx->prep_turn);
+        ctx->prep_turn ^= 1;
+        scal_next = (unsigned int*)(base + 128 * ctx->prep_turn);
+        if (fresh)
+            if (int rc = launch_fill_zero(ctx, out->scal, 64)) return rc;
+    } else {
+        hipLaunchKernelGGL(bmu_centre_kernel, dim3((unsigned)(centre_bytes / 256)), dim3(1024), 0, ctx->stream, W, K, D,
+                           out->centre, out->scal);
+    }
+    ctx->prep_clean = own_centre;
     if (wide_split) {
         if (int rc = check_hip(ctx, hipGetLastError(), "bmu_centre launch")) return rc;
         return bmu_wide_prepare(ctx, W, K, D, *out, qe, small);
@@ -2222,8 +2270,9 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
         const long long slots = (long long)kpad * (kb * 16 + (tail_r ? 16 : 0));
         if (elems < slots) elems = slots;
     }
-    hipLaunchKernelGGL(bmu_prep_kernel, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0, ctx->stream, W, K, D, kpad,
-                       stride, nch, stage_floats_for(stride), out->centre, out->stage, out->wt, out->scal, qe, small, sp);
+    auto kern = own_centre ? bmu_prep_kernel<true> : bmu_prep_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0, ctx->stream, W, K, D, kpad, stride, nch,
+                       stage_floats_for(stride), out->centre, out->stage, out->wt, out->scal, scal_next, qe, small, sp);
     return check_hip(ctx, hipGetLastError(), "bmu_prep launch");
 }
 

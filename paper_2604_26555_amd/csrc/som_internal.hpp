@@ -88,6 +88,8 @@ struct som_ctx {
     // BMU workspaces (grown on demand)
     void* prep_blob = nullptr;
     size_t prep_bytes = 0;
+    int prep_turn = 0;             // which of two sets of result words the next preparation uses
+    bool prep_clean = false;       // that set is clear
     uint32_t* recheck = nullptr;   // one allocation: sample positions [cap], cuts [cap], second list, candidate slots
     size_t recheck_cap = 0;
     bool recheck_sets = false;     // the allocation holds the candidate sets
