@@ -89,96 +89,17 @@ __global__ void __launch_bounds__(1024) bmu_centre_kernel(const float* __restric
     }
 }
 
-struct SplitPrep {
-    char* stage16;       // null: no split search for this shape
-    float* wwin;         // float32 copy of the slots
-    int kb_count, tail_r, row_bytes, stage16_bytes;
-};
-// One slot of the rows for the bf16 matrix pipe (D <= 64): thread e takes (node, slot).
-// tail_r > 0: the last tail_r <= 4 features do not get a 16-feature block of their own (three MFMAs
-// for a block that is mostly padding) but one packed block whose sixteen slots hold the three products side by side,
-//     weights  [ hi(r) | hi(r) | lo(r) | norm parts (3) | 0 ... ]   against samples  [ hi(r) | lo(r) | hi(r) | 1 1 1 | 0 ... ],
-// one MFMA (the norm parts are written by the wavefront that sums the node's norm).  The float32 copy of the packed
-// block (wwin) carries the r centred weights in its first slots.
-__device__ __forceinline__ void split_prep_slot(const float* __restrict__ W, int K, int D, int kpad,
-                                                const float* __restrict__ centre, const SplitPrep& sp, int e)
-{
-    const int slots = sp.kb_count * 16 + (sp.tail_r ? 16 : 0);
-    if (e >= kpad * slots) return;
-    const int k = e / slots, within = e - k * slots;
-    const int kb = within >> 4, g = (within >> 3) & 1, t = within & 7;
-    char* row = sp.stage16 + (size_t)(k / kNodesPerStage) * sp.stage16_bytes + (size_t)(k % kNodesPerStage) * sp.row_bytes;
-    if (kb < sp.kb_count) {
-        const int f0 = 4 * (4 * kb + 2 * g + (t >> 2));                   // the slot group's own first feature
-        const int f = (f0 < D - 4 ? f0 : D - 4) + (t & 3);               // its window, always inside the row
-        const bool real = k < K && f >= f0;
-        const float v = real ? W[(size_t)k * D + f] - centre[f] : 0.0f;
-        const __bf16 hi = (__bf16)v;
-        const __bf16 lo = (__bf16)(v - (float)hi);
-        __bf16* cell = reinterpret_cast<__bf16*>(row + kb * 64 + g * 32) + t;
-        cell[0] = hi;
-        cell[8] = lo;
-        sp.wwin[e] = v;   // the same slots in float32, [node][kb][g][8]: the winner's row for the distances
-    } else {
-        // packed tail: slot s = 8 g + t holds copy s / r of feature D - r + s % r (copies 0, 1: hi, copy 2: lo); the
-        // three slots behind them belong to the norm
-        const int sidx = 8 * g + t, copy = sidx / sp.tail_r, f = D - sp.tail_r + sidx % sp.tail_r;
-        const float v = (k < K && copy < 3) ? W[(size_t)k * D + f] - centre[f] : 0.0f;
-        const __bf16 hi = (__bf16)v;
-        const __bf16 lo = (__bf16)(v - (float)hi);
-        const int ns = sidx - 3 * sp.tail_r;
-        if (ns < 0 || ns >= 3) reinterpret_cast<__bf16*>(row + sp.kb_count * 64 + g * 16)[t] = (copy == 2) ? lo : hi;
-        sp.wwin[e] = (copy == 0) ? v : 0.0f;
-    }
-}
-
-// The rows for the bf16 matrix pipe (stage16 != null; layout at bmu_split_tile) are written by the same launch: one thread per
-// (node, slot), and the wavefront that sums a node's norm also writes it where the split search reads it.
-
-// OWN (D <= 64): the workgroup works out the centre itself, as the mean of up to kCentreNodes nodes spread over the map (any
-// vector near the middle of the weights does, and it is the same one in every workgroup), instead of waiting for a kernel of
-// its own; workgroup 0 stores it for the search.
-constexpr int kCentreNodes = 64;
-
-template <bool OWN>
+// The float32 search's stages (and any search's transposed copy, norms and maximum where the bf16 search does not apply).
 __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__ W, int K, int D, int kpad, int stride,
-                                                       int nch, int stage_floats, float* __restrict__ centre_mem,
+                                                       int nch, int stage_floats, const float* __restrict__ centre,
                                                        float* __restrict__ stage, float* __restrict__ wt,
-                                                       unsigned int* __restrict__ scal, unsigned int* __restrict__ scal_next,
-                                                       double* __restrict__ qe, int32_t* __restrict__ small, const SplitPrep sp)
+                                                       unsigned int* __restrict__ scal, double* __restrict__ qe,
+                                                       int32_t* __restrict__ small)
 {
     const int e = blockIdx.x * 256 + threadIdx.x;
     const int cols = nch * stride;
-    __shared__ float centre_lds[64];
-    __shared__ float centre_part[4][64];
-    const float* centre = centre_mem;
-    if constexpr (OWN) {
-        // (the result words of this call were cleared by the call before; this one clears the next one's)
-        if (blockIdx.x == 0 && threadIdx.x < 16) scal_next[threadIdx.x] = 0u;
-        const int f = threadIdx.x & 63, q = threadIdx.x >> 6;
-        const int count = K < kCentreNodes ? K : kCentreNodes;
-        float v[kCentreNodes / 4];
-#pragma unroll
-        for (int u = 0; u < kCentreNodes / 4; ++u) {
-            const int t = 4 * u + q;
-            v[u] = (t < count && f < D) ? W[(size_t)((int64_t)t * K / count) * D + f] : 0.0f;
-        }
-        float s = 0.0f;
-#pragma unroll
-        for (int u = 0; u < kCentreNodes / 4; ++u) s += v[u];
-        centre_part[q][f] = s;
-        __syncthreads();
-        if (threadIdx.x < 64) {
-            const float c = (((centre_part[0][f] + centre_part[1][f]) + centre_part[2][f]) + centre_part[3][f]) / (float)count;
-            centre_lds[f] = c;                       // (zero behind the row)
-            if (blockIdx.x == 0) centre_mem[f] = c;
-        }
-        __syncthreads();
-        centre = centre_lds;
-    }
     if (e < 2 && qe) qe[e] = 0.0;
     if (e < 4 && small) small[e] = 0;
-    if (sp.stage16) split_prep_slot(W, K, D, kpad, centre, sp, e);
     if (e < kpad * cols) {
         const int k = e / cols, c = e - k * cols;
         const int ch = c / stride, fl = c - ch * stride;
@@ -206,56 +127,25 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
     // squared norm of the centred row exactly as the stage holds it (float32 differences), summed in float64: the
     // first kpad / 4 wavefronts of the grid take four nodes each (coalesced reads of their rows), and a workgroup
     // hands its largest norm to scal[0] with one atomic (one per node, all on the same word, took 10 us)
-    // (and, for the split search's error bound, the largest norms of what the bf16 cut leaves over: w - hi and w - hi - lo)
-    __shared__ float wg_up[4][3];
+    __shared__ float wg_up[4];
     const int wv = e >> 6, lane = e & 63;
-    float up_max = 0.0f, lo_max = 0.0f, rest_max = 0.0f;
+    float up_max = 0.0f;
     if (wv * 4 < kpad) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int k = wv * 4 + q;
             double nrm = 0.0;
-            float lo2 = 0.0f, rest2 = 0.0f;
             if (k < K)
                 for (int f = lane; f < D; f += 64) {
-                    const float vf = W[(size_t)k * D + f] - centre[f];
-                    const double v = (double)vf;
+                    const double v = (double)(W[(size_t)k * D + f] - centre[f]);
                     nrm += v * v;
-                    const float d1 = vf - (float)(__bf16)vf, d2 = d1 - (float)(__bf16)d1;
-                    lo2 = fmaf(d1, d1, lo2);
-                    rest2 = fmaf(d2, d2, rest2);
                 }
             nrm = wave_sum(nrm);
-            if (sp.stage16) {
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) {
-                    lo2 += __shfl_xor(lo2, o);
-                    rest2 += __shfl_xor(rest2, o);
-                }
-                lo_max = fmaxf(lo_max, lo2);
-                rest_max = fmaxf(rest_max, rest2);
-            }
             if (lane == 0 && k < kpad) {
                 const int st = k / kNodesPerStage, r = k % kNodesPerStage;
                 const float nh = (k < K) ? (float)(-0.5 * nrm) : -INFINITY;
                 for (int ch = 0; ch < nch; ++ch)
                     stage[((size_t)st * nch + ch) * stage_floats + (size_t)kNodesPerStage * stride + r] = nh;
-                if (sp.stage16) {
-                    const float nf = nh > kSplitPadNorm ? nh : kSplitPadNorm;
-                    char* blob = sp.stage16 + (size_t)st * sp.stage16_bytes;
-                    reinterpret_cast<float*>(blob + (size_t)kNodesPerStage * sp.row_bytes)[r] = nf;
-                    if (sp.tail_r) {
-                        // -|w|^2 / 2 cut into three bf16 parts (exactly: 3 x 8 bits) in the three slots behind the
-                        // packed block's features; they meet ones on the samples' side
-                        const __bf16 p0 = (__bf16)nf;
-                        const __bf16 p1 = (__bf16)(nf - (float)p0);
-                        const __bf16 p2 = (__bf16)((nf - (float)p0) - (float)p1);
-                        __bf16* cell = reinterpret_cast<__bf16*>(blob + (size_t)r * sp.row_bytes + sp.kb_count * 64);
-                        cell[3 * sp.tail_r] = p0;          // slots 8 g + t are contiguous: [g = 0: 8][g = 1: 8]
-                        cell[3 * sp.tail_r + 1] = p1;
-                        cell[3 * sp.tail_r + 2] = p2;
-                    }
-                }
                 if (k < K) {
                     float up = (float)nrm;
                     if ((double)up < nrm) up = nextafterf(up, INFINITY);
@@ -264,16 +154,140 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
             }
         }
     }
+    if (lane == 0) wg_up[threadIdx.x >> 6] = up_max;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const float m = fmaxf(fmaxf(wg_up[0], wg_up[1]), fmaxf(wg_up[2], wg_up[3]));
+        if (m > 0.0f) atomicMax(&scal[0], __float_as_uint(m));
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Weight preparation of the bf16 search for D <= 64, one launch: a wavefront per node and lane per feature.
+//   * Centre: the mean of up to kCentreNodes nodes spread over the map, worked out by every workgroup for itself (any vector
+//     near the middle of the weights does; a kernel of its own for the mean over all nodes cost 5 us and a launch).
+//   * Stage rows (layout at bmu_split_tile) and their float32 copy (wwin: the same slots, for the distances) are put together
+//     in LDS and leave it as whole lines, as do the sixteen nodes' columns of the transposed copy.
+//   * Packed tail (tail_r > 0): the last tail_r <= 4 features do not get a 16-feature block of their own (three MFMAs for a
+//     block that is mostly padding) but one packed block whose sixteen slots hold the three products side by side,
+//         weights  [ hi(r) | hi(r) | lo(r) | norm parts (3) | 0 ... ]   against samples  [ hi(r) | lo(r) | hi(r) | 1 1 1 | 0 ... ],
+//     one MFMA.  wwin carries the r centred weights in the block's first slots.
+//   * Norms: -|w|^2 / 2 behind the stage's rows (and as three bf16 parts in the packed block), the largest norms of the nodes
+//     and of what the bf16 cut leaves over (w - hi, w - hi - lo) in scal.
+// The result words of this call were cleared by the call before; this one clears the next one's (scal_next).
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kCentreNodes = 64;
+constexpr int kPrepNodes = 16;           // nodes (wavefronts) of a workgroup: 64 bytes of a row of the transposed copy
+
+struct SplitPrep {
+    char* stage16;
+    float* wwin;
+    int kb_count, tail_r, row_bytes, stage16_bytes;
+};
+
+__global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const float* __restrict__ W, int K, int D, int kpad,
+                                                                         float* __restrict__ centre, float* __restrict__ wt,
+                                                                         unsigned int* __restrict__ scal, unsigned int* __restrict__ scal_next,
+                                                                         double* __restrict__ qe, int32_t* __restrict__ small, const SplitPrep sp)
+{
+    __shared__ float part[kPrepNodes][64];
+    __shared__ float given[kPrepNodes][65];
+    __shared__ uint4 rows16[kPrepNodes * 272 / 16];           // [node][row_bytes]
+    __shared__ float wide[kPrepNodes * 64];                   // [node][slots]
+    __shared__ float most[kPrepNodes][3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int k0 = blockIdx.x * kPrepNodes, k = k0 + wave;
+    if (blockIdx.x == 0) {
+        if (tid < 16) scal_next[tid] = 0u;
+        if (tid < 2 && qe) qe[tid] = 0.0;
+        if (tid < 4 && small) small[tid] = 0;
+    }
+    const bool real = k < K && lane < D;
+    const float w = real ? W[(size_t)k * D + lane] : 0.0f;
+    const int count = K < kCentreNodes ? K : kCentreNodes;
+    float v4[kCentreNodes / kPrepNodes];
+#pragma unroll
+    for (int u = 0; u < kCentreNodes / kPrepNodes; ++u) {
+        const int t = wave * (kCentreNodes / kPrepNodes) + u;
+        v4[u] = (t < count && lane < D) ? W[(size_t)((int64_t)t * K / count) * D + lane] : 0.0f;
+    }
+    float s = 0.0f;
+#pragma unroll
+    for (int u = 0; u < kCentreNodes / kPrepNodes; ++u) s += v4[u];
+    part[wave][lane] = s;
+    given[wave][lane] = w;
+    const int slots = sp.kb_count * 16 + (sp.tail_r ? 16 : 0);
+    for (int e = tid; e < kPrepNodes * sp.row_bytes / 16; e += 64 * kPrepNodes) rows16[e] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < kPrepNodes * slots) wide[tid] = 0.0f;
+    __syncthreads();
+    float c = 0.0f;
+#pragma unroll
+    for (int u = 0; u < kPrepNodes; ++u) c += part[u][lane];
+    c /= (float)count;                                        // zero behind the row
+    if (blockIdx.x == 0 && wave == 0) centre[lane] = c;
+    const float v = real ? w - c : 0.0f;
+    const __bf16 hi = (__bf16)v;
+    const float left = v - (float)hi;
+    const __bf16 lo = (__bf16)left;
+    const float rest = left - (float)lo;
+    const double nrm = wave_sum((double)v * (double)v);
+    float lo2 = left * left, rest2 = rest * rest;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lo2 += __shfl_xor(lo2, o);
+        rest2 += __shfl_xor(rest2, o);
+    }
+    char* const row = reinterpret_cast<char*>(rows16) + wave * sp.row_bytes;
+    if (real) {
+        const int tail0 = D - sp.tail_r;
+        if (lane < tail0) {
+            // slot group q = four features, its window [min(4 q, D - 4), + 4): own elements only, zeros in front of them
+            const int q = lane >> 2, start = 4 * q < D - 4 ? 4 * q : D - 4;
+            const int kb = q >> 2, g = (q >> 1) & 1, t = (q & 1) * 4 + lane - start;
+            __bf16* cell = reinterpret_cast<__bf16*>(row + kb * 64 + g * 32) + t;
+            cell[0] = hi;
+            cell[8] = lo;
+            wide[wave * slots + (kb * 2 + g) * 8 + t] = v;
+        } else {
+            __bf16* cell = reinterpret_cast<__bf16*>(row + sp.kb_count * 64) + (lane - tail0);
+            cell[0] = hi;
+            cell[sp.tail_r] = hi;
+            cell[2 * sp.tail_r] = lo;
+            wide[wave * slots + sp.kb_count * 16 + lane - tail0] = v;
+        }
+    }
     if (lane == 0) {
-        wg_up[threadIdx.x >> 6][0] = up_max;
-        wg_up[threadIdx.x >> 6][1] = lo_max;
-        wg_up[threadIdx.x >> 6][2] = rest_max;
+        const float nh = (float)(-0.5 * nrm);
+        const float nf = (k < K && nh > kSplitPadNorm) ? nh : kSplitPadNorm;
+        reinterpret_cast<float*>(sp.stage16 + (size_t)(k / kNodesPerStage) * sp.stage16_bytes +
+                                 (size_t)kNodesPerStage * sp.row_bytes)[k % kNodesPerStage] = nf;
+        if (sp.tail_r) {
+            // cut into three bf16 parts (exactly: 3 x 8 bits), which meet ones on the samples' side
+            const __bf16 p0 = (__bf16)nf;
+            const __bf16 p1 = (__bf16)(nf - (float)p0);
+            const __bf16 p2 = (__bf16)((nf - (float)p0) - (float)p1);
+            __bf16* cell = reinterpret_cast<__bf16*>(row + sp.kb_count * 64) + 3 * sp.tail_r;
+            cell[0] = p0;
+            cell[1] = p1;
+            cell[2] = p2;
+        }
+        float up = (float)nrm;
+        if ((double)up < nrm) up = nextafterf(up, INFINITY);
+        most[wave][0] = k < K ? up : 0.0f;
+        most[wave][1] = lo2;
+        most[wave][2] = rest2;
     }
     __syncthreads();
-    if (threadIdx.x < 3) {
-        const int t = threadIdx.x;
-        const float m = fmaxf(fmaxf(wg_up[0][t], wg_up[1][t]), fmaxf(wg_up[2][t], wg_up[3][t]));
-        if (m > 0.0f) atomicMax(&scal[t == 0 ? 0 : kScalLo + t - 1], __float_as_uint(m));
+    // sixteen rows of a stage are contiguous (kNodesPerStage is a multiple of sixteen)
+    uint4* to = reinterpret_cast<uint4*>(sp.stage16 + (size_t)(k0 / kNodesPerStage) * sp.stage16_bytes + (size_t)(k0 % kNodesPerStage) * sp.row_bytes);
+    for (int e = tid; e < kPrepNodes * sp.row_bytes / 16; e += 64 * kPrepNodes) to[e] = rows16[e];
+    if (tid < kPrepNodes * slots) sp.wwin[(size_t)k0 * slots + tid] = wide[tid];
+    const int f = tid >> 4, q = tid & 15;
+    if (f < D) wt[(size_t)f * kpad + k0 + q] = given[q][f];
+    if (tid < 3) {
+        float m = most[0][tid];
+        for (int u = 1; u < kPrepNodes; ++u) m = fmaxf(m, most[u][tid]);
+        if (m > 0.0f) atomicMax(&scal[tid == 0 ? 0 : kScalLo + tid - 1], __float_as_uint(m));
     }
 }
 
@@ -855,8 +869,10 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     float* const stash = reinterpret_cast<float*>(lds4 + 2 * STAGE_F4) + threadIdx.x;
     float cut[MS];          // CAND
     CandSet noted[MS];      // CAND
+    unsigned int found[MS]; // CAND: hits of the block in hand
 #pragma unroll
     for (int mb = 0; mb < MS; ++mb) {
+        found[mb] = 0u;
         const int64_t i = wave0 + mb * 32 + j;
         const int64_t total = CAND ? (int64_t)count : a.m;
         valid[mb] = i < total;
@@ -956,10 +972,23 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     auto fold_step = [&](const floatx16 (&acc)[MS], int step, int st, int nb) {
         const int mb = step >> 3, p = step & 1, r0 = 4 * ((step & 7) >> 1) + p, r1 = r0 + 2;
         if constexpr (CAND) {
+            // A bit per score that reaches the cut, two instructions each and no branch; what a block found is noted behind
+            // its last step.  (A compare and a branch per score kept the fold from running beside the MFMAs: 2.2 ns an entry at
+            // K = 4096, where a tile of the search takes 1.0 ns a sample.)
             // (the set that the very first block "folds" holds the padding value, which reaches no cut)
-            const int tile = st * (kNodesPerStage / 32) + nb;
-            if (acc[mb][r0] >= cut[mb]) noted[mb].note(tile * 32 + 4 * g, 8 * (r0 >> 2) + (r0 & 3));
-            if (acc[mb][r1] >= cut[mb]) noted[mb].note(tile * 32 + 4 * g, 8 * (r1 >> 2) + (r1 & 3));
+            found[mb] = 2u * found[mb] + (acc[mb][r0] >= cut[mb] ? 1u : 0u);
+            found[mb] = 2u * found[mb] + (acc[mb][r1] >= cut[mb] ? 1u : 0u);
+            if (r1 == 15) {
+                const int base = (st * (kNodesPerStage / 32) + nb) * 32 + 4 * g;
+                while (__ballot(found[mb] != 0u) != 0ull) {
+                    if (found[mb] != 0u) {
+                        const int bit = 31 - __builtin_clz(found[mb]);          // 15 - place in the order of the steps
+                        found[mb] ^= 1u << bit;
+                        const int place = 15 - bit, quad = place >> 2, r = 4 * quad + ((place >> 1) & 1) + 2 * (place & 1);
+                        noted[mb].note(base, 8 * (r >> 2) + (r & 3));
+                    }
+                }
+            }
             return;
         } else {
             const int c = 2 * (nb & 1) + p, pos = 8 * (nb >> 1);
@@ -1389,7 +1418,13 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                     hits += hit ? 1 : 0;
                 }
                 many[q] = hits > 2;
-                if (q == g ? want : want_other) a.pairs[2 * (wave0 + mb * 32 + j) + g] = packed;
+                // both halves' ids in one row of four places, the used ones in front; half g writes places 2 g and 2 g + 1
+                const unsigned int theirs = (unsigned int)__shfl_xor((int)packed, 32);
+                const unsigned int h0 = g == 0 ? packed : theirs, h1 = g == 0 ? theirs : packed;
+                const bool none0 = h0 == 0xffffffffu, one0 = !none0 && (h0 >> 16) == 0xffffu;
+                const unsigned int w0 = none0 ? h1 : one0 ? (h0 & 0xffffu) | (h1 << 16) : h0;
+                const unsigned int w1 = none0 ? 0xffffffffu : one0 ? (h1 >> 16) | 0xffff0000u : h1;
+                if (q == g ? want : want_other) a.pairs[2 * (wave0 + mb * 32 + j) + g] = g == 0 ? w0 : w1;
             }
             // (too many in the other half: it says so to the half that finishes this block)
             const bool mine_many = g == 0 ? many[0] : many[1], others_many = g == 0 ? many[1] : many[0];
@@ -1723,6 +1758,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kExactGroup = 8;
 constexpr int kExactNodesPerThread = 2;
+constexpr size_t kExactLds = 64 * (kExactGroup / 4) * 16;      // bytes: a slab of 64 features of the samples in hand
 constexpr int kExactThreads = 512;         // K = 1024 in one sweep; 256 threads of four nodes each took 25 us for any short list (a chain
                                            // of thirteen batches of loads with little to hide them), these take 14
 
@@ -1821,142 +1857,144 @@ __global__ void __launch_bounds__(256) bmu_cand_exact_kernel(const BmuArgs a)
 
 // ---------------------------------------------------------------------------------------------------------
 // The pair list: samples whose candidates (at most four, two of each lane half) the split search already knows (D <= 64).
-// A workgroup takes 64 entries at a time: sixteen lanes fetch a row in one coalesced load (the samples' rows and two
-// candidates' at once), the rows meet in LDS, and one lane per candidate adds its squared
-// differences up, features in order as the other re-decisions do; lowest distance, then lowest node index.
-// Bound by LDS and the gathered rows: about 0.03 ns an entry, against 0.3 ns (K D = 51200) in the candidate pass, which
-// searches all nodes again.
+// A wavefront takes sixteen entries at a time, on its own (no barrier): sixteen lanes fetch a row in one coalesced load, the
+// samples' rows and two candidates' each; the rows meet in the wavefront's part of LDS, the next entries' rows are requested,
+// and one lane per candidate adds its squared differences up, features in order as the other re-decisions do; lowest
+// distance, then lowest node index.  With a workgroup of eight wavefronts in step (barriers around fetch and sums) the
+// latency of every round was in the open: 0.17 ns an entry at D = 50, whatever the occupancy.
 // ---------------------------------------------------------------------------------------------------------
-constexpr int kPairGroup = 64;
-constexpr int kPairStride = 17;               // float4 of a row in LDS: odd, so that the lanes' 16-byte reads fall into distinct banks
+constexpr int kPairGroup = 16;                // entries of a wavefront's round
 
-__device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__ rows, double& qs, double& qs2)
+// float4 of LDS that a wavefront's entries take: three rows (an odd number each, so that the lanes' 16-byte reads fall into distinct banks) and their ids
+__host__ __device__ constexpr int pair_lds_f4(int D) { return kPairGroup * (3 * (((D + 3) / 4) | 1) + 1); }
+
+__device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__ lds, double& qs, double& qs2)
 {
-    constexpr int kRowsAtOnce = kExactThreads / 16, PER = kPairGroup / kRowsAtOnce;      // entries per sixteen lanes
-    __shared__ uint2 entry_ids[kPairGroup];
-    __shared__ uint32_t entry_at[kPairGroup];
+    constexpr int PER = kPairGroup / 4;                            // entries per sixteen lanes
     const unsigned int count = a.scal[a.slot + 1];
-    const int tid = threadIdx.x, sub = tid & 15, grp = tid >> 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int sub = lane & 15, grp = lane >> 4;
     const int D = a.D, whole = D / 4, rest = D - 4 * whole;
+    const int stride = ((D + 3) / 4) | 1;             // float4 of a row
+    float4* const rows = lds + wave * pair_lds_f4(D);
+    uint4* const info = reinterpret_cast<uint4*>(rows + kPairGroup * 3 * stride);      // [entry] ids, sample position
     const int start = 4 * sub < D - 4 ? 4 * sub : D - 4;           // window inside the row
-    const bool fetch = 4 * sub < D;
-    // place t of an entry's candidates, the used ones in front (an unused half-place is 0xffff); -1: none
-    auto id_of = [&](const uint2& both, int t) {
-        const int n0 = (both.x == 0xffffffffu) ? 0 : (both.x >> 16) == 0xffffu ? 1 : 2;
-        const int n1 = (both.y == 0xffffffffu) ? 0 : (both.y >> 16) == 0xffffu ? 1 : 2;
-        if (t >= n0 + n1) return -1;
-        const int u = t < n0 ? t : t - n0;
-        const int id = (int)(((t < n0 ? both.x : both.y) >> (16 * u)) & 0xffffu);
-        return id < a.K ? id : -1;
-    };
-    // The chain list entry -> ids and row number -> rows is three dependent trips to memory: the sample positions are read two
-    // rounds ahead and the ids and row numbers one, so that a round waits for its rows only.
-    uint32_t at[PER], at_next[PER], row[PER], row_next[PER];
-    uint2 ids[PER], ids_next[PER];
+    const bool own = 4 * sub < D;
+    const unsigned int step = gridDim.x * (kExactThreads / 64) * kPairGroup;
+    const unsigned int first = (blockIdx.x * (kExactThreads / 64) + wave) * kPairGroup;
+    if (first >= count) return;
+    // The chain list entry -> ids and row number -> rows is three dependent trips to memory: sample positions are read two
+    // rounds ahead, ids and row numbers one, rows while the round before is summed.
     auto position = [&](unsigned int p, int u) {
-        const unsigned int q = p + kRowsAtOnce * u + grp;
+        const unsigned int q = p + 4 * u + grp;
         return a.recheck_end[-1 - (int64_t)(q < count ? q : count - 1)];
     };
-    const unsigned int step = gridDim.x * kPairGroup, first = blockIdx.x * kPairGroup;
-    if (first >= count) return;
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        at[u] = position(first, u);
-        at_next[u] = position(first + step < count ? first + step : first, u);
-    }
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        ids[u] = *reinterpret_cast<const uint2*>(a.pairs + 2 * (int64_t)at[u]);
-        row[u] = a.idx ? a.idx[at[u]] : at[u];
-    }
-    for (unsigned int p0 = first; p0 < count; p0 += step) {
-        float4 x4[PER], w4[PER][2];
+    auto after = [&](unsigned int p) { return count - p > step ? p + step : p; };     // (the last round's again at the end)
+    const unsigned int k_most = (unsigned int)a.K - 1u;
+    auto row_of = [&](unsigned int id) { return load4(a.W + (size_t)(id < k_most ? id : k_most) * D + start); };
+    uint32_t at[PER], at_next[PER];
+    uint2 ids[PER];
+    float4 x4[PER], w4[PER][2];
+    auto request = [&](const uint2 (&c)[PER], const uint32_t (&row)[PER]) {
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-            if (fetch) x4[u] = load4(a.X + (int64_t)row[u] * a.ldx + start);
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int id = id_of(ids[u], q);
-                if (fetch && id >= 0) w4[u][q] = load4(a.W + (size_t)id * D + start);
-            }
+            x4[u] = load4(a.X + (int64_t)row[u] * a.ldx + start);
+            // (a single candidate's row twice)
+            const unsigned int i0 = c[u].x & 0xffffu, i1 = c[u].x >> 16;
+            w4[u][0] = row_of(i0);
+            w4[u][1] = row_of(i1 == 0xffffu ? i0 : i1);
         }
-        uint32_t at_after[PER];
-        const unsigned int p2 = count - p0 > 2 * step ? p0 + 2 * step : p0;
+    };
+    {
+        uint32_t row[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            at[u] = position(first, u);
+            at_next[u] = position(after(first), u);
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            ids[u] = *reinterpret_cast<const uint2*>(a.pairs + 2 * (int64_t)at[u]);
+            row[u] = a.idx ? a.idx[at[u]] : at[u];
+        }
+        request(ids, row);
+    }
+    for (unsigned int p0 = first;; p0 += step) {
+        uint2 ids_next[PER];
+        uint32_t row_next[PER], at_after[PER];
+        const unsigned int p2 = after(after(p0));
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             ids_next[u] = *reinterpret_cast<const uint2*>(a.pairs + 2 * (int64_t)at_next[u]);
             row_next[u] = a.idx ? a.idx[at_next[u]] : at_next[u];
             at_after[u] = position(p2, u);
         }
+        // this round's rows to LDS, the next one's on their way
+        if (own) {
 #pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            float4* r = rows + (kRowsAtOnce * u + grp) * 3 * kPairStride + sub;
-            if (fetch) r[0] = x4[u];
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-                if (fetch && id_of(ids[u], q) >= 0) r[(1 + q) * kPairStride] = w4[u][q];
-            if (sub == 0) {
-                entry_ids[kRowsAtOnce * u + grp] = ids[u];
-                entry_at[kRowsAtOnce * u + grp] = at[u];
+            for (int u = 0; u < PER; ++u) {
+                float4* r = rows + (4 * u + grp) * 3 * stride + sub;
+                r[0] = x4[u];
+                r[stride] = w4[u][0];
+                r[2 * stride] = w4[u][1];
             }
         }
-        // (third and fourth candidates, for few entries, take a second round)
-        bool more = false;
+        unsigned int third = 0xffffffffu;
 #pragma unroll
-        for (int u = 0; u < PER; ++u) more = more || id_of(ids[u], 2) >= 0;
-        const bool second_round = __syncthreads_or(more ? 1 : 0) != 0;
-        // this lane's candidate: entry tid / 2, place tid % 2 (and + 2 in the second round)
-        const int e = tid >> 1, c = tid & 1;
-        const bool mine = tid < 2 * kPairGroup && p0 + e < count;
-        const uint2 my_ids = mine ? entry_ids[e] : make_uint2(0xffffffffu, 0xffffffffu);
-        const int64_t ie = mine ? (int64_t)entry_at[e] : 0;
+        for (int u = 0; u < PER; ++u) {
+            if (sub == 0) info[4 * u + grp] = make_uint4(ids[u].x, ids[u].y, at[u], 0u);
+            third &= ids[u].y;
+        }
+        __builtin_amdgcn_wave_barrier();
+        const bool last = count - p0 <= step;
+        const bool second_round = __ballot(third != 0xffffffffu) != 0ull;
+        if (!last) request(ids_next, row_next);
+        // this lane's candidate: entry lane / 2, place lane % 2 (and + 2 in the rare second round)
+        const int e = (lane >> 1) & (kPairGroup - 1), c = lane & 1;
+        const uint4 my = info[e];
+        const bool mine = lane < 2 * kPairGroup && p0 + e < count;
         float bd = INFINITY;
         int bk = 0x7fffffff;
-        for (int t0 = 0; t0 < (second_round ? 4 : 2); t0 += 2) {
-            if (t0 > 0) {
-                __syncthreads();
-#pragma unroll
-                for (int u = 0; u < PER; ++u)
-#pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        const int id = id_of(ids[u], 2 + q);
-                        if (fetch && id >= 0) rows[((kRowsAtOnce * u + grp) * 3 + 1 + q) * kPairStride + sub] = load4(a.W + (size_t)id * D + start);
-                    }
-                __syncthreads();
+        auto sum = [&](unsigned int both) {
+            const unsigned int id = c == 0 ? both & 0xffffu : both >> 16;
+            const float4* rx = rows + e * 3 * stride;
+            const float4* rw = rx + (1 + c) * stride;
+            float d = 0.0f;
+#pragma unroll 4
+            for (int q = 0; q < whole; ++q) {
+                const float4 x = rx[q], w = rw[q];
+                const float d0 = x.x - w.x, d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
+                d = fmaf(d0, d0, d);
+                d = fmaf(d1, d1, d);
+                d = fmaf(d2, d2, d);
+                d = fmaf(d3, d3, d);
             }
-            const int id = id_of(my_ids, t0 + c);
-            if (mine && id >= 0) {
-                const float4* rx = rows + e * 3 * kPairStride;
-                const float4* rw = rx + (1 + c) * kPairStride;
-                float d = 0.0f;
-                for (int q = 0; q < whole; ++q) {
-                    const float4 x = rx[q], w = rw[q];
-                    const float d0 = x.x - w.x, d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
-                    d = fmaf(d0, d0, d);
-                    d = fmaf(d1, d1, d);
-                    d = fmaf(d2, d2, d);
-                    d = fmaf(d3, d3, d);
-                }
-                if (rest > 0) {          // the window [D - 4, D): its leading elements are already counted
-                    const float4 x = rx[whole], w = rw[whole];
-                    const float d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
-                    if (rest > 2) d = fmaf(d1, d1, d);
-                    if (rest > 1) d = fmaf(d2, d2, d);
-                    d = fmaf(d3, d3, d);
-                }
-                if (d < bd || (d == bd && id < bk)) {
-                    bd = d;
-                    bk = id;
-                }
+            if (rest > 0) {          // the window [D - 4, D): its leading elements are already counted
+                const float4 x = rx[whole], w = rw[whole];
+                const float d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
+                if (rest > 2) d = fmaf(d1, d1, d);
+                if (rest > 1) d = fmaf(d2, d2, d);
+                d = fmaf(d3, d3, d);
             }
-        }
+            if (id != 0xffffu && (d < bd || (d == bd && (int)id < bk))) {
+                bd = d;
+                bk = (int)id;
+            }
+        };
+        sum(my.x);
+        if (second_round) {
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            at[u] = at_next[u];
-            at_next[u] = at_after[u];
-            row[u] = row_next[u];
-            ids[u] = ids_next[u];
+            for (int u = 0; u < PER; ++u)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const unsigned int id = q == 0 ? ids[u].y & 0xffffu : ids[u].y >> 16;
+                    if (own && id != 0xffffu) rows[((4 * u + grp) * 3 + 1 + q) * stride + sub] = row_of(id);
+                }
+            __builtin_amdgcn_wave_barrier();
+            sum(my.y);
         }
+        __builtin_amdgcn_wave_barrier();
         const float od = __shfl_xor(bd, 1);
         const int ok = __shfl_xor(bk, 1);
         if (od < bd || (od == bd && ok < bk)) {
@@ -1964,20 +2002,28 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
             bk = ok;
         }
         if (mine && c == 0 && bk < a.K) {
-            a.bmu[ie] = bk;
-            if (a.d2) a.d2[ie] = bd;
-            qs += sqrt((double)bd);
-            qs2 += (double)bd;
+            a.bmu[my.z] = bk;
+            if (a.d2) a.d2[my.z] = bd;
+            if (a.qe) {
+                qs += sqrt((double)bd);
+                qs2 += (double)bd;
+            }
         }
-        __syncthreads();                 // the rows are rewritten by the next entries
+        if (last) break;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            at[u] = at_next[u];
+            at_next[u] = at_after[u];
+            ids[u] = ids_next[u];
+        }
     }
 }
 
 template <bool PAIRS>
-__global__ void __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) bmu_exact_kernel(const BmuArgs a)
+__global__ void __launch_bounds__(kExactThreads) bmu_exact_kernel(const BmuArgs a)
 {
-    // PAIRS: three rows of each entry of the pair list; otherwise only the slab of the listed samples' features
-    __shared__ float4 lds4[PAIRS ? kPairGroup * 3 * kPairStride : 64 * (kExactGroup / 4)];
+    // PAIRS: three rows of each entry of the pair list in hand; otherwise only the slab of the listed samples' features
+    extern __shared__ float4 lds4[];
     float4 (*xs4)[kExactGroup / 4] = reinterpret_cast<float4 (*)[kExactGroup / 4]>(lds4);   // [feature within a 64-wide slab][sample]
     constexpr int kWaves = kExactThreads / 64;
     __shared__ float red_d[kWaves][kExactGroup];
@@ -2026,38 +2072,48 @@ __global__ void __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per
                     xs[d * kExactGroup + s] = a.X[r * a.ldx + d0 + d];
                 }
                 __syncthreads();
-                // eight features at a time: their sixteen weight loads are in flight together
+                // Eight features at a time: their sixteen weight loads are in flight together (no condition on any: with one
+                // branch per load the compiler kept them apart, and the pass took twice as long on a 4096-node map).
                 constexpr int kAtOnce = 8;
-                for (int d = 0; d < dn; d += kAtOnce) {
+                const float* wcol[kExactNodesPerThread];
+#pragma unroll
+                for (int u = 0; u < kExactNodesPerThread; ++u) {
+                    const int k = kb + u * kExactThreads + tid;
+                    wcol[u] = wt + (size_t)d0 * a.kpad + (k < a.kpad ? k : a.kpad - 1);
+                }
+                auto add = [&](int d, const float (&w)[kExactNodesPerThread]) {
+                    float xv[kExactGroup];
+#pragma unroll
+                    for (int q = 0; q < kExactGroup / 4; ++q) {
+                        const float4 v4 = xs4[d][q];
+                        xv[4 * q + 0] = v4.x;
+                        xv[4 * q + 1] = v4.y;
+                        xv[4 * q + 2] = v4.z;
+                        xv[4 * q + 3] = v4.w;
+                    }
+#pragma unroll
+                    for (int s = 0; s < kExactGroup; ++s)
+#pragma unroll
+                        for (int u = 0; u < kExactNodesPerThread; ++u) {
+                            const float df = xv[s] - w[u];
+                            dist[s][u] = fmaf(df, df, dist[s][u]);
+                        }
+                };
+                int d = 0;
+                for (; d + kAtOnce <= dn; d += kAtOnce) {
                     float w[kAtOnce][kExactNodesPerThread];
 #pragma unroll
                     for (int t = 0; t < kAtOnce; ++t)
 #pragma unroll
-                        for (int u = 0; u < kExactNodesPerThread; ++u) {
-                            const int k = kb + u * kExactThreads + tid;
-                            w[t][u] = (k < a.kpad && d + t < dn) ? wt[(size_t)(d0 + d + t) * a.kpad + k] : 0.f;
-                        }
+                        for (int u = 0; u < kExactNodesPerThread; ++u) w[t][u] = wcol[u][(size_t)(d + t) * a.kpad];
 #pragma unroll
-                    for (int t = 0; t < kAtOnce; ++t) {
-                        if (d + t < dn) {
-                            float xv[kExactGroup];
+                    for (int t = 0; t < kAtOnce; ++t) add(d + t, w[t]);
+                }
+                for (; d < dn; ++d) {
+                    float w[kExactNodesPerThread];
 #pragma unroll
-                            for (int q = 0; q < kExactGroup / 4; ++q) {
-                                const float4 v4 = xs4[d + t][q];
-                                xv[4 * q + 0] = v4.x;
-                                xv[4 * q + 1] = v4.y;
-                                xv[4 * q + 2] = v4.z;
-                                xv[4 * q + 3] = v4.w;
-                            }
-#pragma unroll
-                            for (int s = 0; s < kExactGroup; ++s)
-#pragma unroll
-                                for (int u = 0; u < kExactNodesPerThread; ++u) {
-                                    const float df = xv[s] - w[t][u];
-                                    dist[s][u] = fmaf(df, df, dist[s][u]);
-                                }
-                        }
-                    }
+                    for (int u = 0; u < kExactNodesPerThread; ++u) w[u] = wcol[u][(size_t)d * a.kpad];
+                    add(d, w);
                 }
             }
 #pragma unroll
@@ -2189,7 +2245,8 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     const int stride = 2 * steps + 1;
     const int kpad = ((K + kNodesPerStage - 1) / kNodesPerStage) * kNodesPerStage;
     const bool wide_split = D > 2 * kMaxStepsResident && K > kSplitMinNodes && ctx->search != SOM_SEARCH_FLOAT32;
-    const size_t stage_bytes = wide_split ? 0 : (size_t)(kpad / kNodesPerStage) * nch * stage_floats_for(stride) * sizeof(float);
+    const bool no_stage = wide_split || (D >= 4 && K > kSplitMinNodes && ctx->search != SOM_SEARCH_FLOAT32);
+    const size_t stage_bytes = no_stage ? 0 : (size_t)(kpad / kNodesPerStage) * nch * stage_floats_for(stride) * sizeof(float);
     const size_t wt_bytes = (size_t)D * kpad * sizeof(float) + 255 & ~(size_t)255;
     // the centre vector is zero-padded to whole chunks (and to the 64 entries the resident kernel reads)
     const size_t centre_floats = (size_t)(nch > 1 ? nch * 2 * steps : 64);
@@ -2237,20 +2294,27 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     out->stride = stride;
     out->nch = nch;
     out->calls = 0;
-    const bool own_centre = nch == 1;
-    unsigned int* scal_next = nullptr;
-    if (own_centre) {
-        // two sets of result words take turns; both are clear after the allocation
+    ctx->prep_clean = false;
+    if (split && nch == 1) {
+        // two sets of result words take turns; this launch clears the next one's
         out->scal = (unsigned int*)(base + 128 * ctx->prep_turn);
         ctx->prep_turn ^= 1;
-        scal_next = (unsigned int*)(base + 128 * ctx->prep_turn);
         if (fresh)
             if (int rc = launch_fill_zero(ctx, out->scal, 64)) return rc;
-    } else {
-        hipLaunchKernelGGL(bmu_centre_kernel, dim3((unsigned)(centre_bytes / 256)), dim3(1024), 0, ctx->stream, W, K, D,
-                           out->centre, out->scal);
+        SplitPrep sp{};
+        sp.stage16 = (char*)out->stage16;
+        sp.wwin = out->wwin;
+        sp.kb_count = kb;
+        sp.tail_r = tail_r;
+        sp.row_bytes = split_row_bytes(kb, tail_r > 0);
+        sp.stage16_bytes = (int)stage16_one;
+        hipLaunchKernelGGL(bmu_split_prep_kernel, dim3((unsigned)(kpad / kPrepNodes)), dim3(64 * kPrepNodes), 0, ctx->stream, W, K, D, kpad,
+                           out->centre, out->wt, out->scal, (unsigned int*)(base + 128 * ctx->prep_turn), qe, small, sp);
+        ctx->prep_clean = true;
+        return check_hip(ctx, hipGetLastError(), "bmu (split) preparation launch");
     }
-    ctx->prep_clean = own_centre;
+    hipLaunchKernelGGL(bmu_centre_kernel, dim3((unsigned)(centre_bytes / 256)), dim3(1024), 0, ctx->stream, W, K, D,
+                       out->centre, out->scal);
     if (wide_split) {
         if (int rc = check_hip(ctx, hipGetLastError(), "bmu_centre launch")) return rc;
         return bmu_wide_prepare(ctx, W, K, D, *out, qe, small);
@@ -2259,20 +2323,8 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     long long elems = (long long)kpad * nch * stride;
     if (elems < (long long)kpad * 16) elems = (long long)kpad * 16;
     if (elems < (long long)kpad * D) elems = (long long)kpad * D;
-    SplitPrep sp{};
-    if (split) {
-        sp.stage16 = (char*)out->stage16;
-        sp.wwin = out->wwin;
-        sp.kb_count = kb;
-        sp.tail_r = tail_r;
-        sp.row_bytes = split_row_bytes(kb, tail_r > 0);
-        sp.stage16_bytes = (int)stage16_one;
-        const long long slots = (long long)kpad * (kb * 16 + (tail_r ? 16 : 0));
-        if (elems < slots) elems = slots;
-    }
-    auto kern = own_centre ? bmu_prep_kernel<true> : bmu_prep_kernel<false>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0, ctx->stream, W, K, D, kpad, stride, nch,
-                       stage_floats_for(stride), out->centre, out->stage, out->wt, out->scal, scal_next, qe, small, sp);
+    hipLaunchKernelGGL(bmu_prep_kernel, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0, ctx->stream, W, K, D, kpad, stride, nch,
+                       stage_floats_for(stride), out->centre, out->stage, out->wt, out->scal, qe, small);
     return check_hip(ctx, hipGetLastError(), "bmu_prep launch");
 }
 
@@ -2627,7 +2679,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
             b.d2 = nullptr;
             b.qe = nullptr;
             b.second_only = 1;
-            hipLaunchKernelGGL(bmu_exact_kernel<false>, dim3(1024), dim3(kExactThreads), 0, ctx->stream, b);
+            hipLaunchKernelGGL(bmu_exact_kernel<false>, dim3(1024), dim3(kExactThreads), kExactLds, ctx->stream, b);
             if (int rc = check_hip(ctx, hipGetLastError(), "bmu exact-pass launch")) return rc;
         }
         if (a.d2 || a.qe)
@@ -2664,9 +2716,24 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     }
     if (a.K > 1) {
         if (prep.stage16 && prep.nch == 1)
-            hipLaunchKernelGGL(bmu_exact_kernel<true>, dim3(1024), dim3(kExactThreads), 0, ctx->stream, a);
+            {
+            constexpr size_t lds_bytes = (size_t)(kExactThreads / 64) * pair_lds_f4(64) * 16;
+            static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
+            bool& attr_set = attr_set_dev[ctx->device];
+            if (!attr_set) {
+                if ((rc = check_hip(ctx,
+                                    hipFuncSetAttribute(reinterpret_cast<const void*>(bmu_exact_kernel<true>),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes),
+                                    "raising the dynamic LDS limit")))
+                    return rc;
+                attr_set = true;
+            }
+            // (rows of D features; two workgroups fit a compute unit up to D = 52)
+            const size_t rows = (size_t)(kExactThreads / 64) * pair_lds_f4(a.D) * 16, lds = rows > kExactLds ? rows : kExactLds;
+            hipLaunchKernelGGL(bmu_exact_kernel<true>, dim3(1024), dim3(kExactThreads), lds, ctx->stream, a);
+        }
         else
-            hipLaunchKernelGGL(bmu_exact_kernel<false>, dim3(1024), dim3(kExactThreads), 0, ctx->stream, a);
+            hipLaunchKernelGGL(bmu_exact_kernel<false>, dim3(1024), dim3(kExactThreads), kExactLds, ctx->stream, a);
         if ((rc = check_hip(ctx, hipGetLastError(), "bmu exact-pass launch"))) return rc;
     }
     if (a.qe) {

@@ -52,7 +52,7 @@ struct BmuArgs {
     float* cut_all;          // [m] per presented sample: its cut when it is to be re-decided, a NaN otherwise
     uint32_t* recheck;       // [m] sample positions to re-decide (compacted from cut_all by bmu_list_kernel)
     uint32_t* recheck_end;   // end of the recheck array, from which the pair list grows down
-    uint32_t* pairs;         // [m][2] per sample on the pair list: two 16-bit candidate ids of each lane half (0xffff: none)
+    uint32_t* pairs;         // [m][2] per sample on the pair list: up to four 16-bit candidate ids, the used ones in front (0xffff: none)
     // Candidate pass (long lists only): the search is repeated for the listed samples, and every node whose score
     // reaches the sample's cut is noted; direct differences are then taken over those few nodes only.
     float* cutv;             // [m] per list entry: best score minus the rounding bound
