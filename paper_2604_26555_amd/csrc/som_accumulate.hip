@@ -183,14 +183,16 @@ int accumulate_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const u
 {
     // fixed-order sums when asked for: a stable sort by node, or (fewer than four features, very large maps) MFMA accumulators
     if (ctx->reproducible) {
-        const int rs = accumulate_stable_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first);
+        const int rs = accumulate_sort_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first, true);
         if (rs != 1) return rs;
         const int rc = accumulate_mfma_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first);
         if (rc != 1) return rc;
     }
-    // rows wider than one window of the LDS kernel: sorted by node first, every row read once
-    if (!ctx->reproducible && D > 63) {
-        const int rc = accumulate_sort_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first);
+    // Rows wider than one window of the LDS kernel, and maps whose sums take eight slabs of its LDS or more (every slab scans all
+    // BMU indices: 152 us at 10^6 x 50 on 4096 nodes against 107; 57 against 90 on 1024 nodes): sorted by node first, every row
+    // read once.
+    if (!ctx->reproducible && (D > 63 || (size_t)K * (D + 1) * sizeof(double) > 7 * (size_t)150 * 1024)) {
+        const int rc = accumulate_sort_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first, false);
         if (rc != 1) return rc;
     }
     // float64 LDS atomics over node slabs when the K x 64 partial fits a few slabs

@@ -2,21 +2,20 @@
 //
 // For rows wider than one feature window of the LDS kernels (som_accumulate_f64.hip: 63 features, one pass over all BMU
 // indices and one strided pass over the rows per window, 32 launches at D = 2000).  Here the sample positions are sorted by
-// node first, and then every row is read once, whole, by the wavefront that holds its node's running sum in registers:
-// no atomics but one per feature where a range of the sorted order begins or ends inside a node's samples.
-//   1. hist      a workgroup per block of samples counts its samples per node in LDS (and clears S where asked);
+// node first, and then every row is read once, whole, by lanes that hold its node's running sum in registers (no atomics).
+//   1. hist      a workgroup per block of samples counts its samples per node in LDS;
 //   2. columns   per node, the counts of the blocks become running offsets, the total goes to n;
-//   3. scatter   every workgroup adds up the nodes' totals to start positions and writes its samples' row numbers there;
-//   4. sums      lane groups take equal ranges of the sorted order.
-// Bound by HBM in step 4 (D * 4 contiguous bytes per row); steps 1 to 3 cost about 20 us at 10^6 samples.
+//   3. starts    the nodes' totals become start positions, and their samples are cut into segments;
+//   4. scatter   every workgroup writes its samples' row numbers to their places;
+//   5. sums      a group of lanes adds up a segment (four features a lane, float64) and stores it;
+//   6. finish    a node's segments are added up in order.
+// Bound by HBM in step 5 (D * 4 contiguous bytes per row); steps 1 to 4 cost about 25 us at 10^6 samples.  (With equal ranges of
+// the sorted order and an atomic per feature at every node boundary instead of segments, step 5 took 217 us at 10^5 x 2000.)
 // The order of a node's samples within a block is not fixed, so a sum can differ in its last bits between runs (float64).
 //
-// Fixed order of summation (som_set_reproducible): the same with a stable sort (a block is one wavefront's, which ranks its 64
-// samples at a time by ballots) and with the sorted order cut into segments of one node's samples each, whose sums are
-// stored and added in order: every sum is float64 and the same from run to run.
+// Fixed order of summation (som_set_reproducible): the same with a stable sort: a block is one wavefront's, which ranks its 64
+// samples at a time by ballots.
 #include "som_internal.hpp"
-
-#include <hip/amd_detail/amd_hip_unsafe_atomics.h>
 
 namespace som {
 
@@ -28,14 +27,11 @@ constexpr int kStableBlocks = 1024;
 constexpr int kStableNodes = 8192;        // per-node counters of four wavefronts in LDS (128 KB)
 
 __global__ void __launch_bounds__(kSortThreads) sort_hist_kernel(const int32_t* __restrict__ bmu, int64_t m, int K, int64_t per_block,
-                                                                 uint32_t* __restrict__ hist, double* __restrict__ S_clear,
-                                                                 size_t cells)
+                                                                 uint32_t* __restrict__ hist)
 {
     extern __shared__ uint32_t sort_lds[];
     const int tid = threadIdx.x;
     for (int k = tid; k < K; k += kSortThreads) sort_lds[k] = 0u;
-    if (S_clear)
-        for (size_t c = (size_t)blockIdx.x * kSortThreads + tid; c < cells; c += (size_t)gridDim.x * kSortThreads) S_clear[c] = 0.0;
     __syncthreads();
     const int64_t lo = (int64_t)blockIdx.x * per_block, hi = lo + per_block < m ? lo + per_block : m;
     for (int64_t i = lo + tid; i < hi; i += kSortThreads) {
@@ -85,39 +81,15 @@ __global__ void __launch_bounds__(1024) sort_columns_kernel(uint32_t* __restrict
     }
 }
 
-// start[k] = samples of the nodes before k (k = 0 .. K); row numbers to their places.  Workgroup 0 also writes start.
+// row numbers to their places: start[k] + what the blocks before hold of node k + a place inside the block
 __global__ void __launch_bounds__(kSortThreads) sort_scatter_kernel(const int32_t* __restrict__ bmu, const uint32_t* __restrict__ idx,
                                                                     int64_t m, int K, int64_t per_block,
-                                                                    const uint32_t* __restrict__ hist, const uint32_t* __restrict__ total,
-                                                                    uint32_t* __restrict__ start, uint32_t* __restrict__ perm)
+                                                                    const uint32_t* __restrict__ hist, const uint32_t* __restrict__ start,
+                                                                    uint32_t* __restrict__ perm)
 {
     extern __shared__ uint32_t sort_lds[];
-    __shared__ uint32_t wave_sum[kSortThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // exclusive scan of the totals: thread t takes K / 1024 consecutive nodes
-    const int per = (K + kSortThreads - 1) / kSortThreads, k0 = tid * per;
-    uint32_t mine = 0u;
-    for (int u = 0; u < per; ++u) mine += k0 + u < K ? total[k0 + u] : 0u;
-    uint32_t incl = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
-    }
-    if (lane == 63) wave_sum[wave] = incl;
-    __syncthreads();
-    uint32_t at = incl - mine;
-    for (int w = 0; w < wave; ++w) at += wave_sum[w];
-    for (int u = 0; u < per; ++u) {
-        const int k = k0 + u;
-        if (k >= K) break;
-        if (blockIdx.x == 0) {
-            start[k] = at;
-            if (k == K - 1) start[K] = at + total[k];
-        }
-        sort_lds[k] = at + hist[(size_t)blockIdx.x * K + k];
-        at += total[k];
-    }
+    const int tid = threadIdx.x;
+    for (int k = tid; k < K; k += kSortThreads) sort_lds[k] = start[k] + hist[(size_t)blockIdx.x * K + k];
     __syncthreads();
     const int64_t lo = (int64_t)blockIdx.x * per_block, hi = lo + per_block < m ? lo + per_block : m;
     for (int64_t i = lo + tid; i < hi; i += kSortThreads) {
@@ -147,7 +119,7 @@ __global__ void __launch_bounds__(64 * kStableWaves) stable_hist_kernel(const in
 }
 
 // exclusive scan over the nodes: start[k] of the totals and seg[k] of the segments of `rows` samples (K + 1 entries each)
-__global__ void __launch_bounds__(1024) stable_starts_kernel(const uint32_t* __restrict__ total, int K, uint32_t rows,
+__global__ void __launch_bounds__(1024) sort_starts_kernel(const uint32_t* __restrict__ total, int K, uint32_t rows,
                                                              uint32_t* __restrict__ start, uint32_t* __restrict__ seg)
 {
     __shared__ uint2 wave_sum[16];
@@ -229,12 +201,13 @@ __global__ void __launch_bounds__(64 * kStableWaves) stable_scatter_kernel(const
     }
 }
 
-// LANES lanes per segment of one node's samples, four features a lane (slab: 4 LANES features); sums of node's first segment to
-// part[seg] like the others, added up by stable_finish_kernel
+// LANES lanes per segment of one node's samples, four features a lane (slab: 4 LANES features); the sums go to
+// part[seg], added up by sort_finish_kernel, or to S where the node has no other segment
 template <int LANES>
-__global__ void __launch_bounds__(256) stable_sums_kernel(const float* __restrict__ X, int D, int64_t ldx, const uint32_t* __restrict__ start,
+__global__ void __launch_bounds__(256) sort_sums_kernel(const float* __restrict__ X, int D, int64_t ldx, const uint32_t* __restrict__ start,
                                                           const uint32_t* __restrict__ seg, int K, const uint32_t* __restrict__ perm,
-                                                          uint32_t rows, int slabs, double* __restrict__ part)
+                                                          uint32_t rows, int slabs, double* __restrict__ part, int zero_first,
+                                                          double* __restrict__ S)
 {
     constexpr int per_group = 256 / LANES;
     const int sub = threadIdx.x % LANES, first_lane = (threadIdx.x & 63) - sub;
@@ -277,19 +250,24 @@ __global__ void __launch_bounds__(256) stable_sums_kernel(const float* __restric
         if (on) {
 #pragma unroll
             for (int t = 0; t < 4; ++t)
-                if (t >= shift) part[(size_t)sg * D + f + t] = acc[t];
+                if (t >= shift) {
+                    if (seg[k + 1] - seg[k] == 1) S[(size_t)k * D + f + t] = (zero_first ? 0.0 : S[(size_t)k * D + f + t]) + acc[t];
+                    else part[(size_t)sg * D + f + t] = acc[t];
+                }
         }
     }
 }
 
-// a workgroup per node and 64 features: sixteen runs of the node's segments, added up in order
-__global__ void __launch_bounds__(1024) stable_finish_kernel(const double* __restrict__ part, const uint32_t* __restrict__ seg, int D,
+// a workgroup per node and 64 features: sixteen runs of the node's segments, added up in order (a single segment's sums are in S
+// already)
+__global__ void __launch_bounds__(1024) sort_finish_kernel(const double* __restrict__ part, const uint32_t* __restrict__ seg, int D,
                                                              int zero_first, double* __restrict__ S)
 {
     __shared__ double run[16][64];
     const int l = threadIdx.x & 63, r = threadIdx.x >> 6;
     const int k = blockIdx.x, f = blockIdx.y * 64 + l;
     const uint32_t first = seg[k], all = seg[k + 1] - first, per = (all + 15) / 16;
+    if (all == 1) return;
     const uint32_t lo = r * per, hi = lo + per < all ? lo + per : all;
     double s = 0.0;
     if (f < D) {
@@ -303,78 +281,6 @@ __global__ void __launch_bounds__(1024) stable_finish_kernel(const double* __res
     for (int q = 1; q < 16; ++q) s += run[q][l];
     const size_t e = (size_t)k * D + f;
     S[e] = (zero_first ? 0.0 : S[e]) + s;
-}
-
-// LANES lanes (32 or 64) per range of the sorted order, four features a lane, features [4 LANES slab, ...) of the row.
-template <int LANES>
-__global__ void __launch_bounds__(256) sort_sums_kernel(const float* __restrict__ X, int D, int64_t ldx, const uint32_t* __restrict__ start,
-                                                        int K, const uint32_t* __restrict__ perm, int per_range, int slabs,
-                                                        double* __restrict__ S)
-{
-    constexpr int per_group = 256 / LANES;
-    const int sub = threadIdx.x % LANES, first_lane = (threadIdx.x & 63) - sub;
-    const int64_t unit = (int64_t)blockIdx.x * per_group + threadIdx.x / LANES;
-    const int slab = (int)(unit % slabs);
-    const int64_t range = unit / slabs;
-    const uint32_t all = start[K];
-    const int64_t lo = range * per_range;
-    const bool work = lo < (int64_t)all;
-    const int64_t hi = lo + per_range < (int64_t)all ? lo + per_range : (int64_t)all;
-    // node of position lo: the last k with start[k] <= lo
-    int k = 0;
-    if (work) {
-        int top = K;
-        while (top - k > 1) {
-            const int mid = (k + top) >> 1;
-            if ((int64_t)start[mid] <= lo) k = mid;
-            else top = mid;
-        }
-    }
-    // this lane's four features: a window [f, f + 4) inside the row, its leading elements another lane's where it is shifted back
-    const int f_own = (slab * LANES + sub) * 4;
-    const bool on = f_own < D;
-    const int f = f_own < D - 4 ? f_own : D - 4, shift = f_own - f;
-    int64_t next = work ? (int64_t)start[k + 1] : 0;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    auto flush = [&]() {
-        if (on) {
-            double* s = S + (size_t)k * D + f;
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                if (t >= shift) unsafeAtomicAdd(&s[t], acc[t]);
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[t] = 0.0;
-    };
-    constexpr int G = 8;                            // rows in flight
-    if (work)
-        for (int64_t p = lo; p < hi;) {
-            while (p >= next) {                    // (empty nodes in between)
-                if (p > lo) flush();
-                ++k;
-                next = (int64_t)start[k + 1];
-            }
-            const int64_t stop = next < hi ? next : hi;
-            // row numbers of up to G rows at a time, one per lane, handed round
-            const int left = stop - p < G ? (int)(stop - p) : G;
-            const uint32_t row_mine = perm[p + (sub < left ? sub : left - 1)];
-            float4 v[G];
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                const uint32_t row = __shfl(row_mine, first_lane + (u < left ? u : 0));
-                if (u < left && on) __builtin_memcpy(&v[u], X + (int64_t)row * ldx + f, sizeof(float4));
-                else v[u] = float4{0.f, 0.f, 0.f, 0.f};
-            }
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                acc[0] += (double)v[u].x;
-                acc[1] += (double)v[u].y;
-                acc[2] += (double)v[u].z;
-                acc[3] += (double)v[u].w;
-            }
-            p += left;
-            if (p >= hi) flush();
-        }
 }
 
 static int sort_workspace(som_ctx* ctx, size_t need)
@@ -394,15 +300,16 @@ static int sort_workspace(som_ctx* ctx, size_t need)
     return SOM_OK;
 }
 
-// The fixed-order sums.  Returns 1 when the shape is not served by this path.
-int accumulate_stable_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m, const int32_t* bmu,
-                          int32_t K, double* S, unsigned long long* n, bool zero_first)
+// Returns 1 when the shape is not served by this path, SOM_OK on success, a negative code on failure.
+int accumulate_sort_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m, const int32_t* bmu,
+                        int32_t K, double* S, unsigned long long* n, bool zero_first, bool stable)
 {
-    if (m <= 0 || D < 4 || K > kStableNodes) return 1;
-    int64_t per_block = (m + kStableBlocks - 1) / kStableBlocks;
-    if (per_block < 256) per_block = 256;
+    if (m <= 0 || D < 4 || K > (stable ? kStableNodes : kSortNodes)) return 1;
+    const int most = stable ? kStableBlocks : kSortBlocks;
+    int64_t per_block = (m + most - 1) / most;
+    if (per_block < (stable ? 256 : 2048)) per_block = stable ? 256 : 2048;
     const int blocks = (int)((m + per_block - 1) / per_block);
-    // segments: about four wavefronts per SIMD, 32 to 1024 rows
+    // segments: about four wavefronts per SIMD, 32 to 1024 rows (half as long: 213 -> 276 us at 10^6 x 200)
     const int lanes = D <= 64 ? 16 : D <= 128 ? 32 : 64;
     const int slabs = (D + 4 * lanes - 1) / (4 * lanes);
     int64_t rows = m * lanes * slabs / (256 * 4 * 4 * 64);
@@ -416,75 +323,36 @@ int accumulate_stable_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, 
     uint32_t* seg = start + K + 1;
     uint32_t* perm = seg + K + 1;
     double* part = (double*)(hist + words);
-    const size_t lds = (size_t)K * kStableWaves * sizeof(uint32_t);
+    const size_t lds = (size_t)K * sizeof(uint32_t) * (stable ? kStableWaves : 1);
     static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
     bool& attr_set = attr_set_dev[ctx->device];
     if (!attr_set) {
-        for (const void* k : {reinterpret_cast<const void*>(stable_hist_kernel), reinterpret_cast<const void*>(stable_scatter_kernel)})
+        for (const void* k : {reinterpret_cast<const void*>(stable_hist_kernel), reinterpret_cast<const void*>(stable_scatter_kernel),
+                              reinterpret_cast<const void*>(sort_hist_kernel), reinterpret_cast<const void*>(sort_scatter_kernel)})
             if (int rc = check_hip(ctx, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kStableNodes * kStableWaves * 4),
                                    "raising the dynamic LDS limit"))
                 return rc;
         attr_set = true;
     }
-    const dim3 grid((blocks + kStableWaves - 1) / kStableWaves), wg(64 * kStableWaves);
-    hipLaunchKernelGGL(stable_hist_kernel, grid, wg, lds, ctx->stream, bmu, m, K, per_block, blocks, hist);
-    if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (stable) histogram launch")) return rc;
-    hipLaunchKernelGGL(sort_columns_kernel, dim3((K + 63) / 64), dim3(1024), 0, ctx->stream, hist, K, blocks, total, n, zero_first ? 1 : 0);
-    if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (stable) offsets launch")) return rc;
-    hipLaunchKernelGGL(stable_starts_kernel, dim3(1), dim3(1024), 0, ctx->stream, total, K, (uint32_t)rows, start, seg);
-    if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (stable) starts launch")) return rc;
-    hipLaunchKernelGGL(stable_scatter_kernel, grid, wg, lds, ctx->stream, bmu, idx, m, K, per_block, blocks, hist, start, perm);
-    if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (stable) scatter launch")) return rc;
-    const int64_t groups_most = ((int64_t)segs_most * slabs * lanes + 255) / 256;
-    const unsigned groups = (unsigned)(groups_most < 8192 ? groups_most : 8192);
-    auto kern = lanes == 16 ? stable_sums_kernel<16> : lanes == 32 ? stable_sums_kernel<32> : stable_sums_kernel<64>;
-    hipLaunchKernelGGL(kern, dim3(groups), dim3(256), 0, ctx->stream, X, D, ldx, start, seg, K, perm, (uint32_t)rows, slabs, part);
-    if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (stable) sums launch")) return rc;
-    hipLaunchKernelGGL(stable_finish_kernel, dim3(K, (D + 63) / 64), dim3(1024), 0, ctx->stream, part, seg, D, zero_first ? 1 : 0, S);
-    return check_hip(ctx, hipGetLastError(), "accumulate (stable) finish launch");
-}
-
-// Returns 1 when the shape is not served by this path, SOM_OK on success, a negative code on failure.
-int accumulate_sort_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m, const int32_t* bmu,
-                        int32_t K, double* S, unsigned long long* n, bool zero_first)
-{
-    if (m <= 0 || D < 4 || K > kSortNodes) return 1;
-    int64_t per_block = (m + kSortBlocks - 1) / kSortBlocks;
-    if (per_block < 2048) per_block = 2048;
-    const int blocks = (int)((m + per_block - 1) / per_block);
-    const size_t hist_words = (size_t)blocks * K, small_words = 2 * (size_t)K + 1;
-    const size_t need = (hist_words + small_words + (size_t)m) * sizeof(uint32_t);
-    if (int rc = sort_workspace(ctx, need)) return rc;
-    uint32_t* hist = (uint32_t*)ctx->acc_blob;
-    uint32_t* total = hist + hist_words;
-    uint32_t* start = total + K;
-    uint32_t* perm = start + K + 1;
-    const size_t lds = (size_t)K * sizeof(uint32_t);
-    hipLaunchKernelGGL(sort_hist_kernel, dim3(blocks), dim3(kSortThreads), lds, ctx->stream, bmu, m, K, per_block, hist,
-                       zero_first ? S : (double*)nullptr, (size_t)K * D);
+    const dim3 grid(stable ? (blocks + kStableWaves - 1) / kStableWaves : blocks), wg(stable ? 64 * kStableWaves : kSortThreads);
+    if (stable) hipLaunchKernelGGL(stable_hist_kernel, grid, wg, lds, ctx->stream, bmu, m, K, per_block, blocks, hist);
+    else hipLaunchKernelGGL(sort_hist_kernel, grid, wg, lds, ctx->stream, bmu, m, K, per_block, hist);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) histogram launch")) return rc;
     hipLaunchKernelGGL(sort_columns_kernel, dim3((K + 63) / 64), dim3(1024), 0, ctx->stream, hist, K, blocks, total, n, zero_first ? 1 : 0);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) offsets launch")) return rc;
-    hipLaunchKernelGGL(sort_scatter_kernel, dim3(blocks), dim3(kSortThreads), lds, ctx->stream, bmu, idx, m, K, per_block, hist, total,
-                       start, perm);
+    hipLaunchKernelGGL(sort_starts_kernel, dim3(1), dim3(1024), 0, ctx->stream, total, K, (uint32_t)rows, start, seg);
+    if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) starts launch")) return rc;
+    if (stable) hipLaunchKernelGGL(stable_scatter_kernel, grid, wg, lds, ctx->stream, bmu, idx, m, K, per_block, blocks, hist, start, perm);
+    else hipLaunchKernelGGL(sort_scatter_kernel, grid, wg, lds, ctx->stream, bmu, idx, m, K, per_block, hist, start, perm);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) scatter launch")) return rc;
-    // Ranges: about eight wavefronts per SIMD over the slabs, but no shorter than 32 rows (the additions at a range's two
-    // ends are atomics on S).
-    const int lanes = D <= 128 ? 32 : 64;
-    const int slabs = (D + 4 * lanes - 1) / (4 * lanes);
-    int64_t ranges = (int64_t)256 * 4 * 8 * (64 / lanes) / slabs;
-    if (ranges < 1) ranges = 1;
-    int64_t per_range = (m + ranges - 1) / ranges;
-    if (per_range < 32) per_range = 32;
-    ranges = (m + per_range - 1) / per_range;
-    const int64_t groups = (ranges * slabs * lanes + 255) / 256;
-    if (lanes == 32)
-        hipLaunchKernelGGL(sort_sums_kernel<32>, dim3((unsigned)groups), dim3(256), 0, ctx->stream, X, D, ldx, start, K, perm,
-                           (int)per_range, slabs, S);
-    else
-        hipLaunchKernelGGL(sort_sums_kernel<64>, dim3((unsigned)groups), dim3(256), 0, ctx->stream, X, D, ldx, start, K, perm,
-                           (int)per_range, slabs, S);
-    return check_hip(ctx, hipGetLastError(), "accumulate (sort) sums launch");
+    const int64_t groups_most = ((int64_t)segs_most * slabs * lanes + 255) / 256;
+    const unsigned groups = (unsigned)(groups_most < 8192 ? groups_most : 8192);
+    auto kern = lanes == 16 ? sort_sums_kernel<16> : lanes == 32 ? sort_sums_kernel<32> : sort_sums_kernel<64>;
+    hipLaunchKernelGGL(kern, dim3(groups), dim3(256), 0, ctx->stream, X, D, ldx, start, seg, K, perm, (uint32_t)rows, slabs, part,
+                       zero_first ? 1 : 0, S);
+    if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) sums launch")) return rc;
+    hipLaunchKernelGGL(sort_finish_kernel, dim3(K, (D + 63) / 64), dim3(1024), 0, ctx->stream, part, seg, D, zero_first ? 1 : 0, S);
+    return check_hip(ctx, hipGetLastError(), "accumulate (sort) finish launch");
 }
 
 } // namespace som

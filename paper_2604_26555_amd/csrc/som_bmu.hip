@@ -1466,23 +1466,23 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
     }
 }
 
-// candidate pass of the split search: a fixed grid walks the tiles of the list (as bmu_cand_kernel)
+// candidate pass of the split search: a fixed grid walks the tiles of the list.  Whole rounds of two tiles per compute unit,
+// and what is left (a short list: everything) in tiles of half the size: a list of 1032 tiles took three rounds for two.
 template <int KB, bool TAIL, int MS>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) bmu_split_cand_kernel(const BmuArgs a)
 {
     extern __shared__ float4 lds4[];
     const unsigned int count = a.scal[a.slot];
     if (!cand_pass_serves(a, count)) return;
-    constexpr int64_t per_tile = (int64_t)kWavesPerGroup * MS * 32;
-    if constexpr (MS > 1) {
-        if (count <= kCandHalfTiles) {
-            for (int64_t t = blockIdx.x; t * (per_tile / 2) < (int64_t)count; t += gridDim.x)
-                bmu_split_tile<KB, TAIL, MS / 2, true>(a, 0, t, count, lds4);
-            return;
-        }
+    constexpr unsigned int per_tile = (unsigned int)kWavesPerGroup * MS * 32;
+    static_assert(MS == 2, "half tiles");
+    constexpr unsigned int round = 512;
+    const unsigned int full = count <= kCandHalfTiles ? 0u : count / per_tile / round * round;
+    const unsigned int halves = (count - full * per_tile + per_tile / 2 - 1) / (per_tile / 2);
+    for (unsigned int t = blockIdx.x; t < full + halves; t += gridDim.x) {
+        if (t < full) bmu_split_tile<KB, TAIL, MS, true>(a, 0, t, count, lds4);
+        else bmu_split_tile<KB, TAIL, MS / 2, true>(a, (int64_t)full * per_tile, t - full, count, lds4);
     }
-    for (int64_t t = blockIdx.x; t * per_tile < (int64_t)count; t += gridDim.x)
-        bmu_split_tile<KB, TAIL, MS, true>(a, 0, t, count, lds4);
 }
 
 // ---------------------------------------------------------------------------------------------------------
