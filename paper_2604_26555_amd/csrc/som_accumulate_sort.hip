@@ -202,12 +202,11 @@ __global__ void __launch_bounds__(64 * kStableWaves) stable_scatter_kernel(const
 }
 
 // LANES lanes per segment of one node's samples, four features a lane (slab: 4 LANES features); the sums go to
-// part[seg], added up by sort_finish_kernel, or to S where the node has no other segment
+// part[seg], added up by sort_finish_kernel, or to S (null: S is added to) where the node has no other segment
 template <int LANES>
 __global__ void __launch_bounds__(256) sort_sums_kernel(const float* __restrict__ X, int D, int64_t ldx, const uint32_t* __restrict__ start,
                                                           const uint32_t* __restrict__ seg, int K, const uint32_t* __restrict__ perm,
-                                                          uint32_t rows, int slabs, double* __restrict__ part, int zero_first,
-                                                          double* __restrict__ S)
+                                                          uint32_t rows, int slabs, double* part, double* S)
 {
     constexpr int per_group = 256 / LANES;
     const int sub = threadIdx.x % LANES, first_lane = (threadIdx.x & 63) - sub;
@@ -227,6 +226,7 @@ __global__ void __launch_bounds__(256) sort_sums_kernel(const float* __restrict_
         const int f_own = (slab * LANES + sub) * 4;
         const bool on = f_own < D;
         const int f = f_own < D - 4 ? f_own : D - 4, shift = f_own - f;
+        double* const to = (S && seg[k + 1] - seg[k] == 1) ? S + (size_t)k * D : part + (size_t)sg * D;
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
         constexpr int G = 8;                                  // rows in flight
         for (uint32_t p = lo; p < hi; p += G) {
@@ -250,37 +250,39 @@ __global__ void __launch_bounds__(256) sort_sums_kernel(const float* __restrict_
         if (on) {
 #pragma unroll
             for (int t = 0; t < 4; ++t)
-                if (t >= shift) {
-                    if (seg[k + 1] - seg[k] == 1) S[(size_t)k * D + f + t] = (zero_first ? 0.0 : S[(size_t)k * D + f + t]) + acc[t];
-                    else part[(size_t)sg * D + f + t] = acc[t];
-                }
+                if (t >= shift) to[f + t] = acc[t];
         }
     }
 }
 
-// a workgroup per node and 64 features: sixteen runs of the node's segments, added up in order (a single segment's sums are in S
-// already)
+// a workgroup per node, 64 features at a time: sixteen runs of the node's segments, added up in order (a single segment's sums
+// are in S already; with a workgroup per 64 features their mere launch took 60 us at D = 2000)
 __global__ void __launch_bounds__(1024) sort_finish_kernel(const double* __restrict__ part, const uint32_t* __restrict__ seg, int D,
                                                              int zero_first, double* __restrict__ S)
 {
     __shared__ double run[16][64];
     const int l = threadIdx.x & 63, r = threadIdx.x >> 6;
-    const int k = blockIdx.x, f = blockIdx.y * 64 + l;
+    const int k = blockIdx.x;
     const uint32_t first = seg[k], all = seg[k + 1] - first, per = (all + 15) / 16;
-    if (all == 1) return;
+    if (all == 1 && zero_first) return;
     const uint32_t lo = r * per, hi = lo + per < all ? lo + per : all;
-    double s = 0.0;
-    if (f < D) {
+    for (int f0 = 64 * blockIdx.y; f0 < D; f0 += 64 * gridDim.y) {
+        const int f = f0 + l;
+        double s = 0.0;
+        if (f < D) {
 #pragma unroll 4
-        for (uint32_t q = lo; q < hi; ++q) s += part[(size_t)(first + q) * D + f];
-    }
-    run[r][l] = s;
-    __syncthreads();
-    if (r != 0 || f >= D) return;
+            for (uint32_t q = lo; q < hi; ++q) s += part[(size_t)(first + q) * D + f];
+        }
+        run[r][l] = s;
+        __syncthreads();
+        if (r == 0 && f < D) {
 #pragma unroll
-    for (int q = 1; q < 16; ++q) s += run[q][l];
-    const size_t e = (size_t)k * D + f;
-    S[e] = (zero_first ? 0.0 : S[e]) + s;
+            for (int q = 1; q < 16; ++q) s += run[q][l];
+            const size_t e = (size_t)k * D + f;
+            S[e] = (zero_first ? 0.0 : S[e]) + s;
+        }
+        __syncthreads();
+    }
 }
 
 static int sort_workspace(som_ctx* ctx, size_t need)
@@ -313,6 +315,7 @@ int accumulate_sort_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, co
     const int lanes = D <= 64 ? 16 : D <= 128 ? 32 : 64;
     const int slabs = (D + 4 * lanes - 1) / (4 * lanes);
     int64_t rows = m * lanes * slabs / (256 * 4 * 4 * 64);
+    if (slabs > 1) rows /= 2;                 // (10^5 x 2000: 2.33, 2.13, 2.07 ms an epoch with 390, 195, 97 rows)
     rows = rows < 32 ? 32 : rows > 1024 ? 1024 : rows;
     const size_t segs_most = (size_t)(m / rows) + K;
     const size_t hist_words = (size_t)blocks * K, words = (hist_words + 3 * (size_t)K + 2 + (size_t)m + 1) / 2 * 2;
@@ -349,9 +352,9 @@ int accumulate_sort_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, co
     const unsigned groups = (unsigned)(groups_most < 8192 ? groups_most : 8192);
     auto kern = lanes == 16 ? sort_sums_kernel<16> : lanes == 32 ? sort_sums_kernel<32> : sort_sums_kernel<64>;
     hipLaunchKernelGGL(kern, dim3(groups), dim3(256), 0, ctx->stream, X, D, ldx, start, seg, K, perm, (uint32_t)rows, slabs, part,
-                       zero_first ? 1 : 0, S);
+                       zero_first ? S : (double*)nullptr);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) sums launch")) return rc;
-    hipLaunchKernelGGL(sort_finish_kernel, dim3(K, (D + 63) / 64), dim3(1024), 0, ctx->stream, part, seg, D, zero_first ? 1 : 0, S);
+    hipLaunchKernelGGL(sort_finish_kernel, dim3(K, D > 256 ? 4 : 1), dim3(1024), 0, ctx->stream, part, seg, D, zero_first ? 1 : 0, S);
     return check_hip(ctx, hipGetLastError(), "accumulate (sort) finish launch");
 }
 
