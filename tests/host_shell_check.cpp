@@ -163,10 +163,10 @@ int main(int argc, char** argv)
     if (argc > 1 && strcmp(argv[1], "--device") == 0) {
         if (with_a_device() != 0) ++failures;
     }
-    if (failures) {
+    if (failures)
         fprintf(stderr, "host_shell_check: %d failure(s)\n", failures);
-        return 1;
-    }
-    printf("host_shell_check: ok\n");
-    return 0;
+    else
+        printf("host_shell_check: ok\n");
+    fflush(nullptr);               // (said before anything on the way out can end the process)
+    return failures ? 1 : 0;
 }
