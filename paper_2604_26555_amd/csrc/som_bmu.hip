@@ -187,7 +187,7 @@ struct SplitPrep {
 
 __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const float* __restrict__ W, int K, int D, int kpad,
                                                                          float* __restrict__ centre, float* __restrict__ wt,
-                                                                         unsigned int* __restrict__ scal, unsigned int* __restrict__ scal_next,
+                                                                         unsigned int* __restrict__ scal, unsigned int* __restrict__ tops,
                                                                          double* __restrict__ qe, int32_t* __restrict__ small, const SplitPrep sp)
 {
     __shared__ float part[kPrepNodes][64];
@@ -198,7 +198,7 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int k0 = blockIdx.x * kPrepNodes, k = k0 + wave;
     if (blockIdx.x == 0) {
-        if (tid < 16) scal_next[tid] = 0u;
+        if (tid < 16) scal[tid] = 0u;
         if (tid < 2 && qe) qe[tid] = 0.0;
         if (tid < 4 && small) small[tid] = 0;
     }
@@ -287,7 +287,7 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
     if (tid < 3) {
         float m = most[0][tid];
         for (int u = 1; u < kPrepNodes; ++u) m = fmaxf(m, most[u][tid]);
-        if (m > 0.0f) atomicMax(&scal[tid == 0 ? 0 : kScalLo + tid - 1], __float_as_uint(m));
+        if (m > 0.0f) atomicMax(&tops[tid], __float_as_uint(m));
     }
 }
 
@@ -314,6 +314,10 @@ __global__ void __launch_bounds__(kListThreads) bmu_list_kernel(const BmuArgs a)
 {
     __shared__ unsigned int wave_base[2][kListThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (a.tops && blockIdx.x == 0 && tid < 3) {            // the search has read them: zero again for the next preparation
+        a.tops[4 + tid] = a.tops[tid];
+        a.tops[tid] = 0u;
+    }
     constexpr int64_t per_block = (int64_t)kListThreads * kListPerThread;
     for (int64_t chunk = blockIdx.x; chunk * per_block < a.m; chunk += gridDim.x) {
         const int64_t i0 = chunk * per_block + (int64_t)tid * kListPerThread;
@@ -935,8 +939,8 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             xs += __shfl_xor(xs, 32);
             xa += __shfl_xor(xa, 32);
             left2 += __shfl_xor(left2, 32);
-            const float lo_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.scal[kScalLo])) * 1.001f;
-            const float rest_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.scal[kScalLo + 1])) * 1.001f;
+            const float lo_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.norms[1])) * 1.001f;
+            const float rest_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.norms[2])) * 1.001f;
             const float nx = __builtin_amdgcn_sqrtf(xs) * 1.0001f, nl = __builtin_amdgcn_sqrtf(left2) * 1.0001f;
             constexpr float unit = 5.9604645e-08f;
             stash[(3 * mb + 0) * kThreads] = xs;
@@ -1281,7 +1285,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         return;
     }
     // ---- join the two half-wavefronts, then lane (j, g) finishes block mp + g
-    const float wmax2 = __uint_as_float(a.scal[0]);
+    const float wmax2 = __uint_as_float(a.norms[0]);
     const float wmax = sqrtf(wmax2) * 1.000001f;
     // |w|^2 / 2 in the accumulators: see (2) at the start of the tile; and six units as for the products
     constexpr float kErrNorm = ((TAIL ? 16.256f : 48.768f * KB) + 6.0f) * 5.9604645e-08f;
@@ -2278,10 +2282,9 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
         ctx->prep_bytes = need;
         ctx->prep_clean = false;
     }
-    // (a call that went through the centre kernel leaves no cleared words behind, nor does a new allocation)
-    const bool fresh = !ctx->prep_clean;
     char* base = (char*)ctx->prep_blob;
     out->scal = (unsigned int*)base;
+    out->tops = (unsigned int*)(base + 128);
     out->stage = (float*)(base + 256);
     out->wt = (float*)(base + 256 + stage_bytes);
     out->centre = (float*)(base + 256 + stage_bytes + wt_bytes);
@@ -2294,13 +2297,11 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     out->stride = stride;
     out->nch = nch;
     out->calls = 0;
-    ctx->prep_clean = false;
     if (split && nch == 1) {
-        // two sets of result words take turns; this launch clears the next one's
-        out->scal = (unsigned int*)(base + 128 * ctx->prep_turn);
-        ctx->prep_turn ^= 1;
-        if (fresh)
-            if (int rc = launch_fill_zero(ctx, out->scal, 64)) return rc;
+        // (after a new allocation, or a call that failed between here and its list kernel)
+        if (!ctx->prep_clean)
+            if (int rc = launch_fill_zero(ctx, out->tops, 64)) return rc;
+        ctx->prep_clean = false;
         SplitPrep sp{};
         sp.stage16 = (char*)out->stage16;
         sp.wwin = out->wwin;
@@ -2309,8 +2310,7 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
         sp.row_bytes = split_row_bytes(kb, tail_r > 0);
         sp.stage16_bytes = (int)stage16_one;
         hipLaunchKernelGGL(bmu_split_prep_kernel, dim3((unsigned)(kpad / kPrepNodes)), dim3(64 * kPrepNodes), 0, ctx->stream, W, K, D, kpad,
-                           out->centre, out->wt, out->scal, (unsigned int*)(base + 128 * ctx->prep_turn), qe, small, sp);
-        ctx->prep_clean = true;
+                           out->centre, out->wt, out->scal, out->tops, qe, small, sp);
         return check_hip(ctx, hipGetLastError(), "bmu (split) preparation launch");
     }
     hipLaunchKernelGGL(bmu_centre_kernel, dim3((unsigned)(centre_bytes / 256)), dim3(1024), 0, ctx->stream, W, K, D,
@@ -2616,6 +2616,8 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     a.wt = prep.wt;
     a.centre = prep.centre;
     a.scal = prep.scal;
+    a.norms = prep.calls == 0 ? prep.tops : prep.tops + 4;
+    a.tops = prep.stage16 && prep.nch == 1 && prep.calls == 0 ? prep.tops : nullptr;
     a.recheck = ctx->recheck;
     a.cutv = (float*)(ctx->recheck + ctx->recheck_cap);
     a.cut_all = (float*)(ctx->recheck + 2 * ctx->recheck_cap);
@@ -2699,6 +2701,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
         const int64_t chunks = (a.m + kListThreads * kListPerThread - 1) / (kListThreads * kListPerThread);
         hipLaunchKernelGGL(bmu_list_kernel, dim3((unsigned)(chunks < 1024 ? chunks : 1024)), dim3(kListThreads), 0, ctx->stream, a);
         if ((rc = check_hip(ctx, hipGetLastError(), "bmu list launch"))) return rc;
+        if (a.tops) ctx->prep_clean = true;
     }
     if (stop) (void)hipEventRecord(stop, ctx->stream);
     if (cand_possible) {

@@ -22,10 +22,14 @@ struct BmuPrep {
     int tail_r = 0;                // features of the packed tail block behind them (0: none; D <= 64 only)
     float* wt = nullptr;           // [D][Kpad] transposed weights (as given, not centred)
     float* centre = nullptr;       // [D] column means of W; stage rows and sample registers hold values minus this
-    // [0] = bits of max_k |w_k - centre|^2, [3] = total,
+    // Result words, cleared by every preparation: [0] = bits of max_k |w_k - centre|^2, [3] = total,
     // [4], [5] = length of the second list (samples whose candidate slots overflowed; alternating calls),
     // [12], [13] = length of the list and of the pair list, [14], [15] the next call's, [8], [9] = bits of max_k |w - hi|^2 and |w - hi - lo|^2 (bf16 parts)
     unsigned int* scal = nullptr;
+    // Split search for D <= 64: the three maxima above are found by atomics in [0..2], which are zero whenever no call is in
+    // progress; the first pass's list kernel moves them to [4..6], where later passes read them.  (What a call leaves behind
+    // does not depend on which call it is, so a captured call can be replayed.)
+    unsigned int* tops = nullptr;
     int kpad = 0, steps = 0, stride = 0;
     int nch = 1;                   // feature chunks of 2 * steps features (1 unless D > 64)
     int calls = 0;                 // bmu_run calls served by this preparation (selects the list counter)
@@ -47,6 +51,8 @@ struct BmuArgs {
     const float* wt;         // BmuPrep::wt
     const float* centre;     // BmuPrep::centre
     unsigned int* scal;      // BmuPrep::scal
+    const unsigned int* norms;   // split search, D <= 64: the three maxima (BmuPrep::tops, or + 4 after the first pass)
+    unsigned int* tops;      // first pass of the same: BmuPrep::tops, to be moved; else null
     int32_t slot;            // scal[slot], scal[slot + 1] count this call's list and pair list (12 or 14)
     int64_t full_tiles;      // bmu_kernel: workgroups below this number take full tiles, the others half tiles
     float* cut_all;          // [m] per presented sample: its cut when it is to be re-decided, a NaN otherwise
@@ -88,8 +94,7 @@ struct som_ctx {
     // BMU workspaces (grown on demand)
     void* prep_blob = nullptr;
     size_t prep_bytes = 0;
-    int prep_turn = 0;             // which of two sets of result words the next preparation uses
-    bool prep_clean = false;       // that set is clear
+    bool prep_clean = false;       // its maxima (BmuPrep::tops) are zero
     uint32_t* recheck = nullptr;   // one allocation: sample positions [cap], cuts [cap], second list, candidate slots
     size_t recheck_cap = 0;
     bool recheck_sets = false;     // the allocation holds the candidate sets
