@@ -111,8 +111,8 @@ struct som_ctx {
     int reproducible = 0;          // prefer the fixed-order accumulation kernel
     int search = 0;                // SOM_SEARCH_*
     double* qe_part = nullptr;     // [kQeSlots][2], then [kQeSlots], zero between calls
-    double* small_sums = nullptr;  // small epochs: two sets of per-node sums and counts, of small_cells each
-    size_t small_cells = 0, small_clean = 0;   // small_clean: leading cells of set small_turn that are zero
+    double* small_sums = nullptr;  // small epochs: three sets of per-node sums and counts (som_small.hip)
+    size_t small_clean = 0;        // leading cells of set small_turn (0 or 1) that are zero
     int small_turn = 0;
     void* topo_blob = nullptr;     // node distances, adjacency matrix and lists of the topology rebuild
     size_t topo_bytes = 0;

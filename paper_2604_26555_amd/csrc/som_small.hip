@@ -20,6 +20,7 @@ namespace som {
 
 constexpr int kSThreads = 512;
 constexpr size_t kSLds = 128 * 1024;          // W and the sums of small_kernel, a piece of W in lookup_kernel
+constexpr size_t kSCells = kSLds / sizeof(double);   // cells of a set of sums: they are in LDS beside W, so never as many
 constexpr int kSFeatures = 32;                // small_kernel: features of a row at most
 constexpr int kSNodes = 512;                  // small epochs: nodes at most
 constexpr double kSWork = 3.0e8;              // m K D of a small epoch at most: about 20 us of vector arithmetic, what the
@@ -287,7 +288,7 @@ __global__ void __launch_bounds__(kQeSlots) small_qe_kernel(double* __restrict__
 }
 
 // The update of a small map (definitions in som_update.hip): a wavefront per node j.  S [K][D + 1] float64 with the counts in
-// the last column.  `clear`: the other call's sums, zero when the next call adds to them.
+// the last column.  `clear`: the other call's sums, zero when the next call adds to them (null under capture).
 constexpr int kUThreads = 256;
 
 __global__ void __launch_bounds__(kUThreads) small_update_kernel(const float* __restrict__ G, const double* __restrict__ S, int K, int D,
@@ -297,7 +298,8 @@ __global__ void __launch_bounds__(kUThreads) small_update_kernel(const float* __
 {
     __shared__ double h_lds[kUThreads / 64][kSNodes];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, DS = D + 1;
-    for (int e = blockIdx.x * kUThreads + tid; e < K * DS; e += gridDim.x * kUThreads) clear[e] = 0.0;
+    if (clear)
+        for (int e = blockIdx.x * kUThreads + tid; e < K * DS; e += gridDim.x * kUThreads) clear[e] = 0.0;
     const int j = blockIdx.x * (kUThreads / 64) + wave;
     if (j >= K) return;                                        // (no barrier below: a wavefront works on its own)
     double* h = h_lds[wave];
@@ -438,27 +440,27 @@ int small_epoch_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const 
     if (ctx->search != SOM_SEARCH_AUTO || ctx->profiling || ctx->reproducible || D > kSFeatures || K > kSNodes ||
         (double)m * K * D > kSWork || small_lds_bytes(K, D, true) > kSLds)
         return 1;
-    // two sets of sums take turns: this call's update clears the other one for the next call
+    // Two sets of sums take turns: this call's update clears the other one for the next call.  Under capture that would bake
+    // one turn into the graph, and its replays would add to sums that nothing has cleared: a captured call clears the third
+    // set with a launch of its own and leaves the turns alone.
     const size_t cells = (size_t)K * (D + 1);
-    if (cells > ctx->small_cells) {
-        if (ctx->small_sums) {
-            if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync before workspace growth")) return rc;
-            (void)hipFree(ctx->small_sums);
-            ctx->small_sums = nullptr;
-            ctx->small_cells = 0;
-        }
-        if (hipMalloc((void**)&ctx->small_sums, 2 * cells * sizeof(double)) != hipSuccess) {
+    if (!ctx->small_sums) {
+        if (hipMalloc((void**)&ctx->small_sums, 3 * kSCells * sizeof(double)) != hipSuccess) {
             (void)hipGetLastError();
-            return fail(ctx, SOM_ENOMEM, "cannot allocate %zu bytes for the sums of a small map", 2 * cells * sizeof(double));
+            return fail(ctx, SOM_ENOMEM, "cannot allocate %zu bytes for the sums of a small map", 3 * kSCells * sizeof(double));
         }
-        ctx->small_cells = cells;
         ctx->small_clean = 0;
     }
-    double* sums[2] = {ctx->small_sums, ctx->small_sums + ctx->small_cells};
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (ctx->stream)                                            // (the null stream cannot be captured)
+        if (int rc = check_hip(ctx, hipStreamIsCapturing(ctx->stream, &status), "capture status")) return rc;
+    const bool captured = status != hipStreamCaptureStatusNone;
     const int turn = ctx->small_turn;
+    double* const sums = ctx->small_sums + (captured ? 2 : turn) * kSCells;
+    double* const next = captured ? nullptr : ctx->small_sums + (turn ^ 1) * kSCells;
     // (cells that are known to be zero in this call's set; a larger map than the last one clears its set first)
-    if (ctx->small_clean < cells)
-        if (int rc = launch_fill_zero(ctx, sums[turn], cells * sizeof(double))) return rc;
+    if (captured || ctx->small_clean < cells)
+        if (int rc = launch_fill_zero(ctx, sums, cells * sizeof(double))) return rc;
     SmallArgs a{};
     a.X = X;
     a.ldx = ldx;
@@ -467,18 +469,20 @@ int small_epoch_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const 
     a.D = D;
     a.K = K;
     a.W = W;
-    a.S = sums[turn];
-    ctx->small_clean = 0;                                       // until this call's kernels are enqueued
+    a.S = sums;
+    if (!captured) ctx->small_clean = 0;                        // until this call's kernels are enqueued
     // (every workgroup adds its sums onto the map's: at most one per compute unit)
     if (int rc = launch_small<true>(ctx, a, 256)) return rc;
     const double inv2s2 = 1.0 / (2.0 * sigma * sigma);
     const bool plain = ctx->eta == 1.0 && ctx->mu == 0.0;
     hipLaunchKernelGGL(small_update_kernel, dim3((unsigned)((K + kUThreads / 64 - 1) / (kUThreads / 64))), dim3(kUThreads), 0, ctx->stream,
-                       G, sums[turn], K, D, inv2s2, ctx->safeguard == SOM_SAFEGUARD_SHIFT, eps_h, plain, ctx->eta, ctx->mu, ctx->velocity,
-                       W, sums[turn ^ 1]);
+                       G, sums, K, D, inv2s2, ctx->safeguard == SOM_SAFEGUARD_SHIFT, eps_h, plain, ctx->eta, ctx->mu, ctx->velocity, W,
+                       next);
     if (int rc = check_hip(ctx, hipGetLastError(), "small-map update launch")) return rc;
-    ctx->small_turn = turn ^ 1;
-    ctx->small_clean = cells;
+    if (!captured) {
+        ctx->small_turn = turn ^ 1;
+        ctx->small_clean = cells;
+    }
     return SOM_OK;
 }
 

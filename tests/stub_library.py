@@ -26,7 +26,7 @@ def link(directory) -> str:
 class StubContext:
     """One context of the stubbed library.  Every call returns (return code, [kernel names in launch order])."""
 
-    def __init__(self, path: str):
+    def __init__(self, path: str, stream=None):
         self.lib = C.CDLL(path)
         for name in ("stub_allocated", "stub_freed"):
             getattr(self.lib, name).restype = C.c_size_t
@@ -37,13 +37,16 @@ class StubContext:
         self._buf = C.create_string_buffer(4096)          # stands for every array: no kernel runs, nothing is read
         self._p = C.c_void_p(C.addressof(self._buf))
         self.ctx = C.c_void_p()
-        assert self.lib.som_create(C.byref(self.ctx), C.c_int(0), None) == 0
+        assert self.lib.som_create(C.byref(self.ctx), C.c_int(0), C.c_void_p(stream)) == 0
 
     def close(self):
         self.lib.som_destroy(self.ctx)
 
     def switch(self, name, value):
         assert getattr(self.lib, name)(self.ctx, C.c_int(value)) == 0
+
+    def capturing(self, on):
+        self.lib.stub_capturing(C.c_int(int(on)))
 
     def limit(self, nbytes=None):
         """Allocations above nbytes fail from here on (None: none does)."""

@@ -88,11 +88,14 @@ def test_replayed_searches(cap, search, m, distinct, copies, D):
     assert np.array_equal(bmu.cpu().numpy(), want[0])
 
 
-@pytest.mark.parametrize("m,rows,D,epochs", [(20_000, 20, 50, 1), (20_000, 20, 50, 2), (3_000, 12, 80, 1)])
+# the last two are small epochs (two kernels each)
+@pytest.mark.parametrize("m,rows,D,epochs", [(20_000, 20, 50, 1), (20_000, 20, 50, 2), (3_000, 12, 80, 1),
+                                             (5_000, 10, 8, 1), (5_000, 10, 8, 2)])
 def test_replayed_epochs(cap, m, rows, D, epochs):
     X = GaussianMixture(9 + D, D, 5).rows(0, m)
     W0 = X[draw_initial_rows(4, m, rows * rows)].copy()
     G = dev(oracle.rect_lattice_distances(rows, rows).astype(np.float32))
+    # (eager epochs between the replays are a map of their own; with D = 8 a small epoch too)
     G2 = dev(oracle.rect_lattice_distances(7, 7).astype(np.float32))
     Xd, W0d, Wd, W2d = dev(X), dev(W0), dev(W0), dev(W0[:49])
 
