@@ -25,7 +25,8 @@ constexpr int kSFeatures = 32;                // small_kernel: features of a row
 constexpr int kSNodes = 512;                  // small epochs: nodes at most
 constexpr double kSWork = 3.0e8;              // m K D of a small epoch at most: about 20 us of vector arithmetic, what the
                                               // general path spends on its launches
-constexpr double kLWork = 4.0e8;              // ... of a small look-up
+constexpr double kLWork = 4.0e8;              // ... of a small look-up,
+constexpr double kLSteps = 6.0e8;             // and the same with rows and features rounded up (look_up_rows)
 
 struct SmallArgs {
     const float* X;
@@ -40,18 +41,24 @@ struct SmallArgs {
     double* S;                                // ACC: [K][D + 1], the last column counts
 };
 
+// Where node k's row (dq float4) starts in LDS, in float4.  The lanes of a sample read neighbouring nodes' rows at once: rows
+// of four or eight float4 are moved on by one float4 after every 256 bytes, or all of them start in the same few banks
+// (32 features, 400 nodes, 1000 samples: 28.9 us without, 14 with; the general path takes 23).  Rows of two or six meet in
+// pairs at most and stay as they are.
+__host__ __device__ constexpr int small_row(int k, int dq) { return k * dq + (dq == 4 ? k >> 2 : dq == 8 ? k >> 1 : 0); }
+
 // DQ: float4 of a row
 template <int DQ, bool ACC>
 __global__ void __launch_bounds__(kSThreads) small_kernel(const SmallArgs a)
 {
     extern __shared__ float4 small_lds[];
-    float4* const w4 = small_lds;                                             // [K][DQ], zeros behind the row
-    double* const sums = reinterpret_cast<double*>(small_lds + (size_t)a.K * DQ);   // ACC: [K][D + 1]
+    float4* const w4 = small_lds;                                             // K rows of DQ, zeros behind the row
+    double* const sums = reinterpret_cast<double*>(small_lds + small_row(a.K, DQ) + 1);   // ACC: [K][D + 1]
     const int tid = threadIdx.x, D = a.D, K = a.K, DS = D + 1;
     float* const wf = reinterpret_cast<float*>(w4);
     for (int e = tid; e < K * DQ * 4; e += kSThreads) {
         const int k = e / (DQ * 4), f = e - k * (DQ * 4);
-        wf[e] = f < D ? a.W[(size_t)k * D + f] : 0.0f;
+        wf[small_row(k, DQ) * 4 + f] = f < D ? a.W[(size_t)k * D + f] : 0.0f;
     }
     if constexpr (ACC)
         for (int e = tid; e < K * DS; e += kSThreads) sums[e] = 0.0;
@@ -82,10 +89,11 @@ __global__ void __launch_bounds__(kSThreads) small_kernel(const SmallArgs a)
         // two nodes at a time: two chains of additions
         for (int k = sub; k < K; k += 2 * a.sub) {
             const int k1 = k + a.sub < K ? k + a.sub : k;
+            const float4 *r0 = w4 + small_row(k, DQ), *r1 = w4 + small_row(k1, DQ);
             float d0 = 0.0f, d1 = 0.0f;
 #pragma unroll
             for (int q = 0; q < DQ; ++q) {
-                const float4 u = w4[k * DQ + q], v = w4[k1 * DQ + q];
+                const float4 u = r0[q], v = r1[q];
                 const float wu[4] = {u.x, u.y, u.z, u.w}, wv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
@@ -347,6 +355,7 @@ __global__ void __launch_bounds__(kUThreads) small_update_kernel(const float* __
 // ---------------------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------------------
+// rows and sums of small_kernel; what the rows' places take beyond them (at most a sixteenth) is not counted here
 static size_t small_lds_bytes(int K, int D, bool acc)
 {
     return (size_t)K * ((D + 3) / 4) * 16 + (acc ? (size_t)K * (D + 1) * 8 : 0);
@@ -360,13 +369,13 @@ static int launch_small(som_ctx* ctx, SmallArgs a, int blocks_most)
     while (a.sub < 16 && a.m * a.sub < 256 * 512 && a.sub * 8 <= a.K) a.sub <<= 1;
     const int64_t per = kSThreads / a.sub, need = (a.m + per - 1) / per;
     const unsigned blocks = (unsigned)(need < blocks_most ? need : blocks_most);
-    const size_t lds = small_lds_bytes(a.K, a.D, ACC);
+    const size_t lds = (size_t)(small_row(a.K, (a.D + 3) / 4) + 1) * 16 + (ACC ? (size_t)a.K * (a.D + 1) * 8 : 0);
     static bool attr_set_dev[kMaxDevices][9] = {};       // the attribute belongs to the device, not to the process
     const int dq = (a.D + 3) / 4;
     auto launch = [&](auto kern) -> int {
         bool& attr_set = attr_set_dev[ctx->device][dq];
         if (!attr_set) {
-            if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSLds),
+            if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kSLds + kSLds / 16)),
                                    "raising the dynamic LDS limit"))
                 return rc;
             attr_set = true;
@@ -387,11 +396,59 @@ static int launch_small(som_ctx* ctx, SmallArgs a, int blocks_most)
     return fail(ctx, SOM_EINVAL, "no small-map kernel for %d features", a.D);
 }
 
+// LDS layout of lookup_kernel: rows of `stride` floats (one that is no multiple of four spreads a wavefront's reads over the
+// banks), `piece` nodes at a time
+struct LookupLds {
+    int stride, piece;
+    size_t bytes;
+};
+static LookupLds lookup_lds(int K, int D)
+{
+    LookupLds l;
+    l.stride = D % 4 == 0 ? D + 1 : D;
+    l.piece = (int)(kSLds / sizeof(float)) / l.stride;
+    if (l.piece > kSThreads) l.piece = l.piece / kSThreads * kSThreads;
+    if (l.piece > K) l.piece = K;
+    l.bytes = ((size_t)l.piece * l.stride * sizeof(float) + 15) / 16 * 16;
+    return l;
+}
+
+static bool lookup_in_lds(int K, int D) { return D <= kSFeatures && small_lds_bytes(K, D, false) <= kSLds / 2; }
+
+// The most rows of a look-up that go through one kernel here; the others take the general path.  Both sides were timed over
+// D = 3 ... 64, K = 16 ... 20000 and rows from 300 across the line, with and without distances, on rows that the caches hold
+// and on rows that they do not.
+//   lookup_kernel: a workgroup stages all of W and walks all of it for its eight samples, with as many threads as it has
+//   whatever K is, so its time goes with the rounds of workgroups (256 units, up to three on a unit as LDS allows) and jumps
+//   at each.  Share of the general path's time (cached rows / others): D = 50, K = 64, three to a unit: 0.62 / 0.62 for the
+//   6144 rows of one round, 0.75 to 0.9 / 0.99 in the second, 0.9 to 1.0 / 1.35 in the third; K = 512, one to a unit: 0.50 /
+//   0.56 for 2048 rows, 0.88 / 0.95 in the second round, 1.2 / 1.2 and more in the third.  Wide rows whose W comes in several
+//   pieces lose the second round (K = 2048, D = 50: 1.1 / 1.1); narrow ones (to 40 features: 0.95 to 1.05 / 1.0 at K =
+//   1500, 0.8 / 0.75 at D = 16, K = 2048) win it, and where a round is shorter still beside the general path's launches the
+//   third as well (D = 8, K = 4096: 0.82 / 0.72; the fourth 1.03 / 0.89).
+//   small_kernel: the lanes per sample halve when the samples double (launch_small), so the time goes up in steps at powers
+//   of two of the rows, and it works on whole groups of four features.  Rows and features rounded up so, times the nodes:
+//   up to 5.5e8 it takes 0.7 to 0.99 of the general path's time on 256 to 4096 nodes, at 6.3e8 0.98 to 1.02, at 7.3e8 1.1 and
+//   more (m K D alone put 5 features on 1024 nodes at 1.35).  Up to 128 nodes the general path's tiles are mostly
+//   prologue and it stays behind on all of m K D <= kLWork (16 features: 0.81).
+// (D < 4: the general path is the float32 search, slower than either up to m K D.)
+static double look_up_rows(int K, int D)
+{
+    const double by_work = kLWork / ((double)K * D);
+    if (D < 4) return by_work;
+    if (lookup_in_lds(K, D)) return K <= 128 ? by_work : exp2(floor(log2(kLSteps / ((double)K * ((D + 3) / 4 * 4))))) - 1.0;
+    const LookupLds l = lookup_lds(K, D);
+    const int fit = (int)((size_t)160 * 1024 / (l.bytes + 1024)), pieces = (K + l.piece - 1) / l.piece;
+    const int rounds = D <= 8 ? 3 : D <= 40 || pieces == 1 ? 2 : 1;
+    const double by_rounds = 8.0 * 256 * rounds * (fit < 3 ? fit : 3);
+    return by_work < by_rounds ? by_work : by_rounds;
+}
+
 // look-ups; qe (may be null) is overwritten.  Returns 1 when the call is not a small one.
 int small_bmu_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m, const float* W, int32_t K,
                   int32_t* bmu, float* d2, double* qe)
 {
-    if (ctx->search != SOM_SEARCH_AUTO || ctx->profiling || D > 64 || (double)m * K * D > kLWork) return 1;
+    if (ctx->search != SOM_SEARCH_AUTO || ctx->profiling || D > 64 || (double)m > look_up_rows(K, D)) return 1;
     SmallArgs a{};
     a.X = X;
     a.ldx = ldx;
@@ -404,15 +461,10 @@ int small_bmu_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const ui
     a.d2 = d2;
     a.qe_part = qe ? ctx->qe_part : nullptr;
     int rc;
-    if (D <= kSFeatures && small_lds_bytes(K, D, false) <= kSLds / 2) {
+    if (lookup_in_lds(K, D)) {
         rc = launch_small<false>(ctx, a, 2048);
     } else {
-        // rows in LDS: a stride that is no multiple of four spreads a wavefront's reads over the banks
-        const int stride = D % 4 == 0 ? D + 1 : D;
-        int piece = (int)(kSLds / sizeof(float)) / stride;
-        if (piece > kSThreads) piece = piece / kSThreads * kSThreads;
-        if (piece > K) piece = K;
-        const size_t lds = ((size_t)piece * stride * sizeof(float) + 15) / 16 * 16;
+        const LookupLds l = lookup_lds(K, D);
         static bool attr_set_dev[kMaxDevices] = {};
         bool& attr_set = attr_set_dev[ctx->device];
         if (!attr_set) {
@@ -423,9 +475,9 @@ int small_bmu_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const ui
         }
         // (four samples a workgroup while that does not fill the chip: every workgroup reads all of W)
         if (m <= 4 * 256)
-            hipLaunchKernelGGL(lookup_kernel<4>, dim3((unsigned)((m + 3) / 4)), dim3(kSThreads), lds, ctx->stream, X, W, a, piece, stride);
+            hipLaunchKernelGGL(lookup_kernel<4>, dim3((unsigned)((m + 3) / 4)), dim3(kSThreads), l.bytes, ctx->stream, X, W, a, l.piece, l.stride);
         else
-            hipLaunchKernelGGL(lookup_kernel<8>, dim3((unsigned)((m + 7) / 8)), dim3(kSThreads), lds, ctx->stream, X, W, a, piece, stride);
+            hipLaunchKernelGGL(lookup_kernel<8>, dim3((unsigned)((m + 7) / 8)), dim3(kSThreads), l.bytes, ctx->stream, X, W, a, l.piece, l.stride);
         rc = check_hip(ctx, hipGetLastError(), "look-up kernel launch");
     }
     if (rc || !qe) return rc;

@@ -35,3 +35,38 @@ def test_captured_small_epochs_clear_their_own_sums(library):
         assert ctx.epoch(5000, 100, 8) == (0, small)
     finally:
         ctx.close()
+
+
+# (K, D, most rows of a look-up in one kernel, that kernel).  lookup_kernel: full rounds of 8 rows x 256 units x workgroups on
+# a unit; small_kernel: a power of two of the rows, or (few nodes, or fewer than four features) m K D <= 4e8.
+@pytest.mark.parametrize("K,D,rows,kernel", [
+    (64, 50, 2 * 3 * 2048, "lookup_kernel<8>"), (128, 33, 2 * 3 * 2048, "lookup_kernel<8>"), (400, 50, 2 * 2 * 2048, "lookup_kernel<8>"),
+    (512, 50, 2 * 2048, "lookup_kernel<8>"), (1024, 50, 2048, "lookup_kernel<8>"), (1024, 64, 2048, "lookup_kernel<8>"),
+    (4096, 64, 1525, "lookup_kernel<8>"), (20000, 64, 312, "lookup_kernel<4>"), (1500, 40, 2 * 2048, "lookup_kernel<8>"),
+    (2048, 16, 2 * 2048, "lookup_kernel<8>"), (4096, 8, 3 * 2048, "lookup_kernel<8>"), (9000, 3, 14814, "lookup_kernel<8>"),
+    (100, 8, 500_000, "small_kernel<2,false>"), (128, 16, 195_312, "small_kernel<4,false>"), (16, 4, 6_250_000, "small_kernel<1,false>"),
+    (129, 16, 262_143, "small_kernel<4,false>"), (400, 32, 32_767, "small_kernel<8,false>"), (1024, 5, 65_535, "small_kernel<2,false>"),
+    (4096, 4, 32_767, "small_kernel<1,false>"), (1024, 2, 195_312, "small_kernel<1,false>"),
+])
+def test_look_ups_on_both_sides_of_their_line(ctx, K, D, rows, kernel):
+    assert ctx.bmu(rows, K, D) == (0, [kernel])
+    assert ctx.launches[0][5] < 160 * 1024 - 1024            # LDS of a unit, beside the kernel's own few hundred bytes
+    assert ctx.bmu(rows, K, D, qe=True) == (0, [kernel, "small_qe_kernel"])
+    rc, names = ctx.bmu(rows + 1, K, D)
+    assert rc == 0 and not any(n.startswith(("lookup", "small")) for n in names) and len(names) >= 4
+    # a profile, and the float32 search, are of the general path
+    for switch, on, off in (("som_profile", 1, 0), ("som_set_search", 1, 0)):
+        ctx.switch(switch, on)
+        rc, names = ctx.bmu(1000, K, D)
+        assert rc == 0 and not any(n.startswith(("lookup", "small")) for n in names)
+        ctx.switch(switch, off)
+    rc, names = ctx.bmu(1000, K, 65)
+    assert rc == 0 and "bmu_wide_split_kernel" in names      # rows of more than 64 features
+
+
+def test_look_ups_take_no_more_threads_than_nodes_are_worth(ctx):
+    """A workgroup's time goes with ceil(K / 512) and not with K: tens of thousands of rows on a map of few nodes are not a
+    small look-up (12,500 workgroups at 100,000 rows of 50 features on 80 nodes)."""
+    for K in (16, 64, 80, 128, 256, 400):
+        rc, names = ctx.bmu(20_000, K, 50)
+        assert rc == 0 and any(n.startswith("bmu_split_kernel") for n in names), (K, names)
