@@ -178,6 +178,24 @@ __global__ void __launch_bounds__(256) accumulate_direct_kernel(const float* __r
     }
 }
 
+// The sort by node (six launches, float64, reads every row once) against the LDS kernel over slabs of nodes and windows of 63
+// features (two launches a window, every slab scans all BMU indices), both timed for D = 4 ... 5000, K = 16 ... 16384, m = 10
+// ... 5 * 10^6 and even, uneven and clustered shares of the nodes:
+//   * wide rows (two windows or more): the sort takes 0.02 to 1.0 of the time, except where it has fewer rows than nodes to
+//     spread its launches over: 1.1 to 1.5 up to 126 features (two windows).
+//   * one window: the sort wins only where the slabs are many and leave compute units idle, and the rows cover its launches:
+//     K = 4096, D = 50 (11 slabs) 10^5 rows 49 us against 29, 5 * 10^5 70 against 65, 10^6 106 against 109 to 130, 5 * 10^6
+//     376 against 465 to 710; K = 3136, D = 50 (9 slabs) 10^6 rows 102 against 90; above 6400 nodes its counters per block
+//     cost more than the slabs (K = 16384, D = 16: 172 against 92).
+//   * maps beyond the LDS kernel's slabs: always (what is left for them holds float32 partial sums).
+static bool sort_pays(int64_t m, int32_t K, int32_t D)
+{
+    const int slabs = accumulate_f64_slabs(K, D);
+    if (slabs > kFMaxSlabs || D > 126) return true;
+    if (D > 63) return m >= 256 && m >= K;
+    return slabs > 9 && K <= 6400 && m >= 750000;
+}
+
 int accumulate_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m,
                    const int32_t* bmu, int32_t K, double* S, unsigned long long* n, bool zero_first)
 {
@@ -187,11 +205,7 @@ int accumulate_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const u
         if (rs != 1) return rs;
         const int rc = accumulate_mfma_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first);
         if (rc != 1) return rc;
-    }
-    // Rows wider than one window of the LDS kernel, and maps whose sums take eight slabs of its LDS or more (every slab scans all
-    // BMU indices: 152 us at 10^6 x 50 on 4096 nodes against 107; 57 against 90 on 1024 nodes): sorted by node first, every row
-    // read once.
-    if (!ctx->reproducible && (D > 63 || (size_t)K * (D + 1) * sizeof(double) > 7 * (size_t)150 * 1024)) {
+    } else if (sort_pays(m, K, D)) {
         const int rc = accumulate_sort_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first, false);
         if (rc != 1) return rc;
     }

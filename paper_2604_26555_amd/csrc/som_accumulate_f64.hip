@@ -30,7 +30,6 @@ namespace som {
 
 constexpr int kFThreads = 1024;
 constexpr size_t kFLdsBytes = 150 * 1024;     // slab
-constexpr int kFMaxSlabs = 16;
 
 // GATHER: rows are taken through the index list (a scalar load per row; kept out of the plain variant because its
 // wait would also wait for the LDS atomics in flight)
@@ -197,6 +196,13 @@ __global__ void __launch_bounds__(256) accumulate_f64_reduce_kernel(const double
     }
 }
 
+// slabs of LDS that the sums of a map take, one window of features at a time
+int accumulate_f64_slabs(int32_t K, int32_t D)
+{
+    const int ks_max = (int)(kFLdsBytes / ((size_t)((D < 63 ? D : 63) + 1) * sizeof(double)));
+    return (K + ks_max - 1) / ks_max;
+}
+
 // Returns 1 when the shape is not served by this path (the caller then tries the others), SOM_OK on success, a
 // negative code on failure.  Rows wider than 63 features go through in windows of 63 (one kernel + reduce per
 // window through the same slices).  Served: a K x 64 float64 partial that fits kFMaxSlabs slabs of LDS.
@@ -205,9 +211,7 @@ int accumulate_f64_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, con
 {
     if (m <= 0 || ldx >= (1 << 22)) return 1;               // row offsets inside a round of passes are 32-bit
     const int window = D < 63 ? D : 63;                      // features per pass; lane 0 carries the count
-    const size_t row_bytes = (size_t)(window + 1) * sizeof(double);
-    const int ks_max = (int)(kFLdsBytes / row_bytes);
-    const int nslabs = (K + ks_max - 1) / ks_max;
+    const int nslabs = accumulate_f64_slabs(K, D);
     if (nslabs > kFMaxSlabs) return 1;
     const int ks = (K + nslabs - 1) / nslabs;                  // balanced slabs
     // One workgroup per compute unit and never more workgroups than compute units (with one resident workgroup

@@ -1,7 +1,8 @@
 // Per-BMU sample sums and counts by counting sort:  S_k += x_i,  n_k += 1  for k = b_i  (the inner sums of Eq. 3).
 //
 // For rows wider than one feature window of the LDS kernels (som_accumulate_f64.hip: 63 features, one pass over all BMU
-// indices and one strided pass over the rows per window, 32 launches at D = 2000).  Here the sample positions are sorted by
+// indices and one strided pass over the rows per window, 64 launches at D = 2000), and for maps of many slabs
+// (som_accumulate.hip, sort_pays).  Here the sample positions are sorted by
 // node first, and then every row is read once, whole, by lanes that hold its node's running sum in registers (no atomics).
 //   1. hist      a workgroup per block of samples counts its samples per node in LDS;
 //   2. columns   per node, the counts of the blocks become running offsets, the total goes to n;

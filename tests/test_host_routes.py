@@ -70,3 +70,27 @@ def test_look_ups_take_no_more_threads_than_nodes_are_worth(ctx):
     for K in (16, 64, 80, 128, 256, 400):
         rc, names = ctx.bmu(20_000, K, 50)
         assert rc == 0 and any(n.startswith("bmu_split_kernel") for n in names), (K, names)
+
+
+SORT = ["sort_hist_kernel", "sort_columns_kernel", "sort_starts_kernel", "sort_scatter_kernel", "sort_sums_kernel", "sort_finish_kernel"]
+STABLE = ["stable_hist_kernel", "sort_columns_kernel", "sort_starts_kernel", "stable_scatter_kernel", "sort_sums_kernel", "sort_finish_kernel"]
+SLABS = ["accumulate_f64_kernel", "accumulate_f64_reduce_kernel"]
+MFMA = ["accumulate_mfma_kernel", "accumulate_mfma_reduce_kernel"]
+FLOAT32 = ["accumulate_kernel", "accumulate_reduce_kernel"]
+
+
+def plain(result):
+    rc, names = result
+    return rc, [n.split("<")[0] for n in names]
+
+
+@pytest.mark.parametrize("m,K,D,kernels", [
+    (1_000_000, 1024, 50, SLABS), (749_999, 4096, 50, SLABS), (750_000, 4096, 50, SORT), (1_000_000, 3136, 50, SLABS),
+    (1_000_000, 6401, 40, SLABS), (1_000_000, 6400, 40, SORT), (5_000_000, 16384, 16, SLABS), (100, 16384, 50, SORT),
+    (255, 16, 64, 2 * SLABS), (256, 16, 64, SORT), (1023, 1024, 126, 2 * SLABS), (1024, 1024, 126, SORT), (10, 1024, 127, SORT),
+    (10, 16, 2000, SORT), (1000, 16385, 200, FLOAT32), (1000, 16385, 16, SLABS), (1000, 16385, 63, FLOAT32),
+])
+def test_accumulation_routes(ctx, m, K, D, kernels):
+    for zero_first in (True, False):
+        assert plain(ctx.accumulate(m, K, D, zero_first)) == (0, kernels)
+
