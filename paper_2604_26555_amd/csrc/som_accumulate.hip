@@ -199,15 +199,17 @@ static bool sort_pays(int64_t m, int32_t K, int32_t D)
 int accumulate_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m,
                    const int32_t* bmu, int32_t K, double* S, unsigned long long* n, bool zero_first)
 {
+    // (the sort needs four bytes a sample and more: where it finds no memory the others, which need less, are asked)
     // fixed-order sums when asked for: a stable sort by node, or (fewer than four features, very large maps) MFMA accumulators
     if (ctx->reproducible) {
         const int rs = accumulate_sort_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first, true);
-        if (rs != 1) return rs;
+        if (rs != 1 && rs != SOM_ENOMEM) return rs;
         const int rc = accumulate_mfma_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first);
         if (rc != 1) return rc;
+        if (rs == SOM_ENOMEM) return rs;                 // a shape whose order is promised: not summed in any other
     } else if (sort_pays(m, K, D)) {
         const int rc = accumulate_sort_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first, false);
-        if (rc != 1) return rc;
+        if (rc != 1 && rc != SOM_ENOMEM) return rc;
     }
     // float64 LDS atomics over node slabs when the K x 64 partial fits a few slabs
     {

@@ -94,3 +94,23 @@ def test_accumulation_routes(ctx, m, K, D, kernels):
     for zero_first in (True, False):
         assert plain(ctx.accumulate(m, K, D, zero_first)) == (0, kernels)
 
+
+def test_accumulation_without_memory_for_the_sort(ctx):
+    """The sort's workspace goes with the samples; the kernels that served such calls before it need less, and do again."""
+    m, K, D = 20_000_000, 100, 200
+    ctx.limit(64 << 20)                                          # the sort asks for 80 MB and more here
+    assert plain(ctx.accumulate(m, K, D)) == (0, 4 * SLABS)
+    # a fixed order stays a fixed order: the MFMA accumulators where they apply, an error elsewhere
+    ctx.switch("som_set_reproducible", 1)
+    assert plain(ctx.accumulate(m, K, D)) == (0, 4 * MFMA)
+    assert plain(ctx.accumulate(m, 4096, D)) == (-2, []) and "accumulation workspace" in ctx.error()
+    ctx.limit()
+    assert plain(ctx.accumulate(m, K, D)) == (0, STABLE)
+    assert plain(ctx.accumulate(m, 4096, D)) == (0, STABLE)
+    ctx.switch("som_set_reproducible", 0)
+    assert plain(ctx.accumulate(m, K, D)) == (0, SORT)
+    # nothing at all: an error, and the context works afterwards
+    ctx.limit(1 << 10)
+    assert plain(ctx.accumulate(2 * m, K, D))[0] == -2
+    ctx.limit()
+    assert plain(ctx.accumulate(2 * m, K, D)) == (0, SORT)
