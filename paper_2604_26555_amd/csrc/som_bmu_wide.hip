@@ -55,7 +55,7 @@ struct WideArgs {
 // 64 lanes x 16 bytes, from the lanes' own addresses to 1 KB of LDS at offset lds (below 64 KB); counted by vmcnt
 __device__ __forceinline__ void lds_load16(const void* from, unsigned lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(from) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(from) : "memory", "m0");
 }
 
 // ---------------------------------------------------------------------------------------------------------

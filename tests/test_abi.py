@@ -80,3 +80,16 @@ def test_nothing_committed_points_at_the_working_folder():
         record = re.fullmatch(r"[A-Z]+_r\d+\.json", f)        # nor are the records of benchmark and test runs (BENCH_r01.json ...)
         if f.endswith((".py", ".hip", ".hpp", ".h", ".cpp", ".md", ".json")) and f not in reviews and not record:
             assert needle not in open(os.path.join(ROOT, f), errors="ignore").read(), f
+
+
+def test_assembly_names_the_registers_it_writes():
+    """An inline-assembly statement that writes m0 must say so, or the compiler may keep a value of its own there."""
+    found = 0
+    csrc = os.path.join(ROOT, "paper_2604_26555_amd", "csrc")
+    for f in sorted(os.listdir(csrc)):
+        for asm in re.findall(r"\basm\s+(?:volatile\s*)?\((.*?)\);", open(os.path.join(csrc, f)).read(), flags=re.S):
+            template = asm.split('" :')[0]
+            if re.search(r"\bm0\b", template):
+                found += 1
+                assert re.search(r'"m0"', asm), f"{f}: {asm.strip()[:120]}"
+    assert found >= 1
