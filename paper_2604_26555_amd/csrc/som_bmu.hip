@@ -689,7 +689,7 @@ __device__ __forceinline__ void bmu_tile(const BmuArgs& a, int64_t first, int64_
                 qs2 += (double)r_part;
             }
         }
-        if (r_valid) a.cut_all[i] = close ? r_best - bound : kNotListed;
+        if (r_valid) a.cut_all[i] = close ? list_cut(r_best - bound) : kNotListed;
     }
     if (a.qe) group_qe_add(a.qe_part, qs, qs2);
 }
@@ -1451,7 +1451,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             }
             a.bmu[i] = r_node;
             if (a.d2) a.d2[i] = r_part;
-            a.cut_all[i] = !close ? kNotListed : open ? cut_at : kPairs;
+            a.cut_all[i] = !close ? kNotListed : open ? list_cut(cut_at) : kPairs;
         }
     }
     if (a.qe) group_qe_add(a.qe_part, qs, qs2, near);
@@ -1731,7 +1731,7 @@ __device__ __forceinline__ void bmu_wide_tile(const BmuArgs& a, int64_t tile_ind
             qs2 = (double)part;
         }
     }
-    if (mine) a.cut_all[i] = close ? bst - bound : kNotListed;
+    if (mine) a.cut_all[i] = close ? list_cut(bst - bound) : kNotListed;
     if (a.qe) group_qe_add(a.qe_part, qs, qs2);
 }
 

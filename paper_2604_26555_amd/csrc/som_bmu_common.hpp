@@ -81,6 +81,10 @@ __device__ __forceinline__ void list_push(unsigned int* __restrict__ counter, ui
 constexpr float kNotListed = __builtin_nanf("");
 constexpr float kPairs = __builtin_inff();
 
+// The cut of a listed sample.  A row that holds no number, or whose scores overflow, has none and reads like one of the two
+// marks above: any node may be its winner.
+__device__ __forceinline__ float list_cut(float cut) { return fabsf(cut) < INFINITY ? cut : -INFINITY; }
+
 // sixteen bytes from a 4-byte aligned address in one load (global memory needs no more than dword alignment)
 __device__ __forceinline__ float4 load4(const float* p)
 {

@@ -36,6 +36,17 @@ def search(request, som):
     som.som_set_search("auto")
 
 
+@pytest.fixture(params=["auto", "tiles", "float32"])
+def path(request, som):
+    """The same, and with it the default search proper at sizes that go through one kernel of som_small.hip by default: a
+    context that keeps a profile keeps its calls off that path."""
+    som.som_set_search("float32" if request.param == "float32" else "auto")
+    som.som_profile(request.param == "tiles")
+    yield request.param
+    som.som_profile(False)
+    som.som_set_search("auto")
+
+
 def dev(a, dtype=None):
     t = torch.from_numpy(np.ascontiguousarray(a))
     if dtype is not None:
@@ -82,7 +93,7 @@ def check_bmu(b_gpu, d2_gpu, X, W, idx=None):
     (1500, 400, 4), (1500, 450, 17), (1200, 500, 33), (1100, 640, 49), (1000, 385, 64),   # more node stages
     (1200, 400, 65), (900, 500, 67), (700, 390, 127), (800, 450, 129), (600, 1024, 257), (500, 400, 1000),  # chunks of 64
 ])
-def test_bmu_matches_oracle(som, search, m, K, D):
+def test_bmu_matches_oracle(som, path, m, K, D):
     X, W = problem(100 + m + K + D, m, K, D)
     d2 = torch.empty(m, dtype=torch.float32, device="cuda")
     qe = torch.full((2,), -1.0, dtype=torch.float64, device="cuda")
@@ -96,14 +107,14 @@ def test_bmu_matches_oracle(som, search, m, K, D):
     check_bmu(som.som_bmu(dev(X), dev(W))[0].cpu().numpy(), None, X, W)
 
 
-def test_bmu_exact_ties_and_duplicates(som, search):
+def test_bmu_exact_ties_and_duplicates(som, path):
     W = np.array([[1.0, 0.0], [-1.0, 0.0], [0.0, 1.0], [0.0, -1.0], [0.0, 1.0]], dtype=np.float32)
     X = np.array([[0.0, 0.0], [0.0, 0.5], [0.25, 0.25], [-3.0, 0.0]], dtype=np.float32)
     b_gpu, _, _ = som.som_bmu(dev(X), dev(W))
     assert b_gpu.cpu().tolist() == oracle.bmu(X, W)[0].tolist() == [0, 2, 0, 1]
 
 
-def test_bmu_index_list_and_leading_dimension(som, search):
+def test_bmu_index_list_and_leading_dimension(som, path):
     X, W = problem(7, 5000, 64, 10)
     pad = np.full((5000, 13), 1e9, dtype=np.float32)       # garbage beyond D must never be read as features
     pad[:, :10] = X
@@ -116,7 +127,7 @@ def test_bmu_index_list_and_leading_dimension(som, search):
     check_bmu(b_plain.cpu().numpy(), None, X, W, idx)
 
 
-def test_bmu_large_norm_small_gap(som, search):
+def test_bmu_large_norm_small_gap(som, path):
     # clusters far from the origin: |x|^2 ~ 1e5 while neighbouring nodes differ by ~1e-2 in squared distance,
     # so the float32 score form alone could not decide; the direct re-decision has to
     rng = np.random.default_rng(3)
@@ -142,7 +153,7 @@ def test_bmu_wide_rows_that_are_not_16_byte_aligned(som):
 
 
 @pytest.mark.parametrize("D", [20, 200])
-def test_bmu_far_from_the_origin(som, search, D):
+def test_bmu_far_from_the_origin(som, path, D):
     """Data and weights sit at 1000 +- 0.01 per coordinate: |x|^2 is 10^6 D while neighbouring nodes differ by about
     1e-4 in squared distance.  Only the centred score form (and the exact re-decision behind it) can tell them apart."""
     rng = np.random.default_rng(D)
@@ -152,7 +163,7 @@ def test_bmu_far_from_the_origin(som, search, D):
     check_bmu(b_gpu.cpu().numpy(), None, X, W)
 
 
-def test_bmu_sample_on_a_node(som, search):
+def test_bmu_sample_on_a_node(som, path):
     """Samples that coincide with a node (distance exactly zero) or sit next to one far from the origin."""
     rng = np.random.default_rng(9)
     W = (50.0 + rng.normal(size=(64, 30))).astype(np.float32)
@@ -164,7 +175,7 @@ def test_bmu_sample_on_a_node(som, search):
 
 
 @pytest.mark.parametrize("scale", [1e-12, 1e-3, 1e6, 1e12])
-def test_bmu_at_extreme_scales(som, search, scale):
+def test_bmu_at_extreme_scales(som, path, scale):
     """The same problem multiplied by a power of ten: scores scale with its square, the decisions must not change."""
     X, W = problem(4242, 5000, 300, 50)
     X, W = (X * np.float32(scale)).astype(np.float32), (W * np.float32(scale)).astype(np.float32)
@@ -335,7 +346,7 @@ def test_bmu_long_recheck_list_with_near_copies(som, search):
     assert (b2.cpu().numpy() == b1).all()
 
 
-def test_bmu_and_accumulate_on_seeded_random_shapes(som, search):
+def test_bmu_and_accumulate_on_seeded_random_shapes(som, path):
     """Thirty shapes drawn with a fixed seed from awkward values (D around the kernels' chunk widths, K around the
     stage and block sizes, ragged m, duplicated nodes for long re-decision lists, row lists, padded row strides):
     BMUs, distances, quantisation-error sums, counts and sums against the oracle."""
@@ -371,6 +382,33 @@ def test_bmu_and_accumulate_on_seeded_random_shapes(som, search):
         S_or, n_or = oracle.accumulate(X, idx, b_np, K)
         assert np.array_equal(n.cpu().numpy(), n_or)
         np.testing.assert_allclose(S.cpu().numpy(), S_or, rtol=1e-9, atol=1e-6 * max(1.0, float(np.abs(X).max())))
+
+
+@pytest.mark.parametrize("m,K,D", [(300, 100, 8), (300, 100, 30), (400, 100, 50), (400, 1024, 40), (20_000, 300, 20), (30_000, 300, 50),
+                                   (30_000, 1024, 64), (500, 300, 100), (900, 700, 200)])
+def test_rows_with_nan_and_infinities(som, path, m, K, D):
+    """Rows that hold a NaN or an infinity get unit 0 (no distance of theirs is below infinity) and a distance that is not
+    finite; every other row gets what it gets without them."""
+    X, W = GaussianMixture(30 + D, D, 6).rows(0, m), GaussianMixture(31 + D, D, 6).rows(0, K)
+    clean = X.copy()
+    bad = np.array([0, 1, 2, 63, 64, m // 2, m - 2, m - 1])
+    X[bad[0]] = np.nan
+    X[bad[1], D // 2] = np.nan
+    X[bad[2], D - 1] = np.inf
+    X[bad[3], 0] = -np.inf
+    X[bad[4]] = np.inf
+    X[bad[5], :2] = [np.inf, -np.inf]
+    X[bad[6], D - 1] = np.nan
+    X[bad[7]] = -np.inf
+    good = np.setdiff1d(np.arange(m), bad)
+    d2, d2c = torch.empty(m, device="cuda"), torch.empty(m, device="cuda")
+    b = som.som_bmu(dev(X), dev(W), d2=d2)[0].cpu().numpy()
+    bc = som.som_bmu(dev(clean), dev(W), d2=d2c)[0].cpu().numpy()
+    plain = som.som_bmu(dev(X), dev(W))[0].cpu().numpy()
+    assert np.array_equal(b[good], bc[good]) and np.array_equal(d2.cpu().numpy()[good], d2c.cpu().numpy()[good])
+    assert (b[bad] == 0).all() and not np.isfinite(d2.cpu().numpy()[bad]).any()
+    assert np.array_equal(plain, b)
+    check_bmu(bc, None, clean, W)
 
 
 # ------------------------------------------------------------------------------------------- stage 2
