@@ -51,8 +51,9 @@ __global__ void __launch_bounds__(kAccThreads) accumulate_kernel(const float* __
 
     // the (sample, feature) pairs of a flush block are numbered e = s * wcur + f and dealt to the threads in order,
     // so every LDS atomic instruction carries 64 useful lanes; e / wcur is a multiply-high by ceil(2^32 / wcur),
-    // exact while e * wcur < 2^32 (e < kFlushRows * wcur, wcur <= 256)
-    const unsigned int magic = (unsigned int)((0x100000000ull + (unsigned)wcur - 1) / (unsigned)wcur);
+    // exact while e * wcur < 2^32 (e < kFlushRows * wcur, wcur <= 256); ceil(2^32 / 1) does not fit 32 bits, so a slab of one
+    // feature takes e itself
+    const unsigned int magic = wcur == 1 ? 0u : (unsigned int)((0x100000000ull + (unsigned)wcur - 1) / (unsigned)wcur);
 
     bool first = true;
     for (int64_t base = lo; base < hi || first; base += kFlushRows) {
@@ -67,7 +68,7 @@ __global__ void __launch_bounds__(kAccThreads) accumulate_kernel(const float* __
             for (int u = 0; u < kAccUnroll; ++u) {
                 const int e = e0 + u * kAccThreads + tid;
                 const unsigned int ec = (unsigned int)(e < elems ? e : elems - 1);
-                const unsigned int sidx = __umulhi(ec, magic);
+                const unsigned int sidx = magic ? __umulhi(ec, magic) : ec;
                 f[u] = (int)(ec - sidx * (unsigned)wcur);
                 rows[u] = base + sidx;
             }

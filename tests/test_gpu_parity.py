@@ -437,6 +437,27 @@ def test_accumulate_matches_oracle(som, m, K, D):
             som.som_set_reproducible(False)
 
 
+def test_accumulate_slabs_of_one_feature(som):
+    """Maps beyond the sort's counters and the float64 kernel's slabs: the float32 kernel's feature slabs, the last one (and,
+    above 12288 nodes, every one) a single feature wide."""
+    for reproducible, m, K, D in ((True, 9000, 8193, 70), (False, 3000, 16385, 20), (False, 5000, 18000, 18), (True, 20_000, 12289, 25)):
+        X, _ = problem(77 + K + D, m, 64, D)
+        rng = np.random.default_rng(K)
+        b = rng.integers(0, K, size=m).astype(np.int32)
+        b[rng.random(m) < 0.4] = K - 1
+        S_or, n_or = oracle.accumulate(X, None, b, K)
+        scale = np.abs(X).max() * np.maximum(n_or, 1)[:, None]
+        som.som_set_reproducible(reproducible)
+        try:
+            S = torch.full((K, D), 7.0, dtype=torch.float64, device="cuda")
+            n = torch.full((K,), 7, dtype=torch.int64, device="cuda")
+            som.som_accumulate(dev(X), dev(b), K, S, n, zero_first=True)
+        finally:
+            som.som_set_reproducible(False)
+        assert (n.cpu().numpy() == n_or).all()
+        assert (np.abs(S.cpu().numpy() - S_or) <= 1e-6 * scale).all()
+
+
 @pytest.mark.parametrize("m,K,D,crowd", [(70_000, 4096, 50, None), (33_333, 2304, 50, None), (150_001, 1600, 50, 7),
                                          (20_000, 2500, 100, None), (9000, 4096, 50, 4000), (64, 4096, 50, None)])
 def test_accumulate_on_large_maps(som, m, K, D, crowd):
