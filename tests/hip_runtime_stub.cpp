@@ -30,6 +30,8 @@ std::map<void*, size_t> device_memory;
 std::string launched;                       // one line per launch: name grid.x grid.y grid.z block lds
 size_t limit = ~(size_t)0, allocated = 0, freed = 0;
 bool capturing = false;
+std::string failing;                        // launches of kernels with this name fail
+hipError_t last_error = hipSuccess;
 int event_word, stream_word;
 
 } // namespace
@@ -42,7 +44,9 @@ void stub_reset()
     limit = ~(size_t)0;
     allocated = freed = 0;
     capturing = false;
+    failing.clear();
 }
+void stub_fail(const char* kernel) { failing = kernel; }
 const char* stub_launches() { return launched.c_str(); }
 void stub_limit(size_t bytes) { limit = bytes; }
 void stub_capturing(int on) { capturing = on != 0; }
@@ -88,6 +92,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void**, size_t lds, hipStream_t)
 {
     const auto it = kernels().find(f);
+    if (!failing.empty() && it != kernels().end() && it->second.rfind(failing, 0) == 0) return last_error = hipErrorLaunchFailure;
     char sizes[128];
     snprintf(sizes, sizeof(sizes), " %u %u %u %u %zu\n", grid.x, grid.y, grid.z, block.x, lds);
     launched += (it == kernels().end() ? std::string("?") : it->second) + sizes;
@@ -160,7 +165,12 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int)
 }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError()
+{
+    const hipError_t e = last_error;
+    last_error = hipSuccess;
+    return e;
+}
 const char* hipGetErrorString(hipError_t) { return "an error of the stub"; }
 
 hipError_t hipEventCreate(hipEvent_t* e)

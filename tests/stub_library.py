@@ -48,6 +48,10 @@ class StubContext:
     def capturing(self, on):
         self.lib.stub_capturing(C.c_int(int(on)))
 
+    def fail(self, kernel=""):
+        """Launches of kernels whose name starts with this fail from here on (empty: none does)."""
+        self.lib.stub_fail(C.c_char_p(kernel.encode()))
+
     def limit(self, nbytes=None):
         """Allocations above nbytes fail from here on (None: none does)."""
         self.lib.stub_limit(C.c_size_t(nbytes if nbytes is not None else 2 ** 64 - 1))

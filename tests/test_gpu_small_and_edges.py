@@ -1,0 +1,290 @@
+"""The kernels of small calls on both sides of their limits, and the wide search, the sort and the default search at the
+sizes where they can go wrong, against the oracle.
+
+Bars as in tests/test_gpu_parity.py: units outside the 1e-5 near-tie mask identical (inside it the oracle's update follows the
+GPU's unit), distances and weights within 1e-4 relative, counts exact, float64 sums within 1e-9 of max|x| n_k."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from synth import GaussianMixture, draw_initial_rows, draw_subset
+
+pytestmark = pytest.mark.gpu
+
+REL = 1e-4
+
+
+@pytest.fixture(scope="module")
+def som():
+    from paper_2604_26555_amd import Som
+    s = Som(0)
+    yield s
+    s.close()
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def rows(seed, m, D, n_comp=6):
+    return GaussianMixture(seed, D, n_comp).rows(0, m)
+
+
+def check_units(b_gpu, X, W):
+    b, best, second = oracle.bmu_gram(X, W)
+    mask = oracle.near_tie_mask(best, second)
+    assert ((b_gpu == b) | mask).all(), f"{int(((b_gpu != b) & ~mask).sum())} wrong units outside the near-tie mask"
+    return b, best, mask
+
+
+def check_weights(W_gpu, W_or, den=None):
+    keep = np.ones(len(W_or), dtype=bool)
+    if den is not None:
+        keep = ~((den > oracle.DEFAULT_EPS_H / 4) & (den < 4 * oracle.DEFAULT_EPS_H))
+    err = np.abs(W_gpu.astype(np.float64) - W_or) / np.maximum(np.abs(W_or).max(axis=1, keepdims=True), 1e-30)
+    assert (err[keep] <= REL).all(), f"max relative weight error {err[keep].max():.3e}"
+
+
+# ---------------------------------------------------------------------------------------------------- small epochs
+def epoch_against_oracle(som, X, W, G, sigma, idx=None):
+    """One epoch without statistics from W; the oracle follows the GPU's units inside the near-tie mask."""
+    Xd, Wd = dev(X), dev(W)
+    idx_d = dev(idx.astype(np.int32)) if idx is not None else None
+    Xp = X if idx is None else X[idx.astype(np.int64)]
+    b_gpu = som.som_bmu(Xd, Wd, idx=idx_d)[0].cpu().numpy()
+    b, _, mask = check_units(b_gpu, Xp, W)
+    ref = oracle.epoch_grouped(Xp, None, W, G.astype(np.float64), sigma, b=np.where(mask, b_gpu, b))
+    som.som_epoch(Xd, Wd, dev(G), sigma, idx=idx_d, want_stats=False)
+    som.som_sync()
+    check_weights(Wd.cpu().numpy(), ref["W"], ref["den"])
+    return Wd.cpu().numpy()
+
+
+def square(side):
+    return oracle.rect_lattice_distances(side, side).astype(np.float32)
+
+
+def line(K):
+    i = np.arange(K)
+    return np.abs(i[:, None] - i[None, :]).astype(np.float32)
+
+
+def test_small_epochs_on_maps_that_grow_and_shrink(som):
+    """The two sets of sums take turns, each cleared by the call before as far as that call's map went; a refused call
+    between them changes nothing, and neither does a large epoch."""
+    from paper_2604_26555_amd import SomError
+    for it, (side, D, m) in enumerate([(10, 8, 3000), (7, 8, 2000), (15, 8, 3000), (15, 8, 1000), (4, 3, 50), (10, 24, 4000),
+                                       (22, 8, 5000), (22, 12, 4000), (1, 5, 300), (10, 8, 1), (10, 8, 3000)]):
+        X = rows(40 + it, m, D)
+        W = rows(80 + it, side * side, D)
+        print(f"small epoch {it}: {side} x {side} nodes, {m} x {D}", flush=True)
+        epoch_against_oracle(som, X, W, square(side), 1.5)
+        if it == 3:
+            with pytest.raises(SomError):
+                som.som_epoch(dev(X), dev(W), dev(square(side)), -1.0, want_stats=False)
+            X2, W2 = rows(7, 9000, 50), rows(8, 400, 50)
+            epoch_against_oracle(som, X2, W2, square(20), 2.0)
+
+
+@pytest.mark.parametrize("m,K,D", [
+    (375_000, 100, 8), (375_001, 100, 8),              # m K D = 3e8 and one row more
+    (4000, 200, 32), (4000, 200, 33),                  # features of small_kernel
+    (3000, 512, 8), (3000, 513, 8),                    # nodes of a small epoch
+    (3000, 334, 32), (3000, 335, 32),                  # W and the sums in LDS
+    (700, 512, 16), (700, 500, 13), (900, 300, 29),    # rows moved on in LDS (four and eight float4)
+    (5000, 3, 1), (5000, 17, 2), (5000, 33, 31), (63, 64, 20), (1, 100, 8),
+])
+def test_small_epochs_on_both_sides_of_their_limits(som, m, K, D):
+    X = rows(500 + K + D, m, D)
+    W = X[draw_initial_rows(3, m, K)].copy() if K <= m else rows(501 + K, K, D)
+    epoch_against_oracle(som, X, W, line(K), 1.0 + 0.02 * K)
+
+
+def test_small_epochs_with_a_row_list_and_padded_rows(som):
+    X = rows(61, 6000, 10)
+    idx = draw_subset(61, 0, 6000, 2500)
+    W = X[draw_initial_rows(5, 6000, 81)].copy()
+    epoch_against_oracle(som, X, W, square(9), 1.0, idx=idx)
+    buf = np.full((6000, 13), 1e9, dtype=np.float32)
+    buf[:, :10] = X
+    Wa, Wb = dev(W), dev(W)
+    som.som_epoch(dev(X), Wa, dev(square(9)), 1.0, want_stats=False)
+    som.som_epoch(dev(buf)[:, :10], Wb, dev(square(9)), 1.0, want_stats=False)
+    np.testing.assert_allclose(Wb.cpu().numpy(), Wa.cpu().numpy(), rtol=1e-6, atol=1e-7)
+
+
+@pytest.mark.parametrize("eta,mu", [(0.5, 0.0), (1.0, 0.3), (0.25, 0.9)])
+@pytest.mark.parametrize("safeguard", ["threshold", "shift"])
+def test_small_epochs_with_momentum_and_shifted_exponents(som, eta, mu, safeguard):
+    """The rule inside small_update_kernel, two epochs (the second one uses the velocity the first one wrote); sigma is small
+    and two thirds of the nodes are far from every row, so denominators underflow: guarded nodes coast on their velocity, with
+    shifted exponents they follow the nearest occupied nodes; one node is cut off from all others."""
+    K, D, m, sigma = 100, 8, 2000, 0.08
+    X = rows(71, m, D)
+    W = X[draw_initial_rows(2, m, K)].copy()
+    W[::3] += 500.0
+    W[1::3] -= 700.0
+    G = square(10).copy()
+    G[37, :] = G[:, 37] = np.inf
+    G[37, 37] = 0.0
+    W[37] = 1e4                                                  # nobody's unit, reached by no occupied node
+    V = (np.random.default_rng(1).normal(size=(K, D)) * 0.1).astype(np.float32)
+    Xd, Gd, Wd, Vd = dev(X), dev(G), dev(W), dev(V)
+    try:
+        som.som_set_safeguard(safeguard)
+        som.som_set_update_rule(eta, mu, Vd)
+        for _ in range(2):
+            W32, V32 = Wd.cpu().numpy().copy(), Vd.cpu().numpy().copy()
+            b_gpu = som.som_bmu(Xd, Wd)[0].cpu().numpy()
+            b, _, mask = check_units(b_gpu, X, W32)
+            S, n = oracle.accumulate(X, None, np.where(mask, b_gpu, b), K)
+            assert (n == 0).sum() > 10 and n[37] == 0                # (fewer in the second epoch: the shift fetches nodes)
+            if safeguard == "threshold":
+                W_or, V_or, guarded = oracle.neighborhood_update_momentum(S, n, G.astype(np.float64), sigma, W32, V32, eta, mu)
+                assert guarded.any() and not guarded.all()
+            else:
+                target, unchanged = oracle.neighborhood_update_shifted(S, n, G.astype(np.float64), sigma, W32)
+                assert unchanged.sum() == 1 and unchanged[37]
+                V_or = np.where(unchanged[:, None], 0.0, eta * (target - W32)) + mu * V32
+                W_or = W32 + V_or
+            som.som_epoch(Xd, Wd, Gd, sigma, want_stats=False)
+            som.som_sync()
+            check_weights(Wd.cpu().numpy(), W_or)
+            np.testing.assert_allclose(Vd.cpu().numpy(), V_or, rtol=1e-4, atol=1e-4)
+    finally:
+        som.som_set_update_rule(1.0, 0.0, None)
+        som.som_set_safeguard("threshold")
+
+
+# ---------------------------------------------------------------------------------------------------- look-ups
+@pytest.mark.parametrize("m,K,D", [
+    (12_288, 64, 50), (12_289, 64, 50), (4096, 512, 50), (4097, 512, 50), (2048, 1024, 64), (2049, 1024, 64),
+    (1024, 700, 57), (1025, 700, 57),                  # four and eight rows a workgroup
+    (3, 1, 40), (9, 511, 33), (17, 513, 44), (800, 1300, 61), (5, 2100, 64),    # W in one, two and more pieces
+    (4096, 2048, 16), (4097, 2048, 16), (6144, 4096, 8), (6145, 4096, 8), (3000, 4400, 3),
+    (32_767, 400, 32), (32_768, 400, 32), (65_535, 1024, 5), (65_536, 1024, 5), (1000, 512, 32), (1000, 1024, 16),
+])
+def test_look_ups_on_both_sides_of_their_line(som, m, K, D):
+    X, W = rows(900 + K + D, m, D), rows(901 + K + D, K, D)
+    X[: min(m, K, 5)] = W[: min(m, K, 5)]                       # rows that lie on a node
+    if K > 20:
+        W[K - 3:] = W[2:5]                                      # and nodes that exist twice: the lower index
+    d2 = torch.full((m,), -1.0, device="cuda")
+    qe = torch.full((2,), -1.0, dtype=torch.float64, device="cuda")
+    b_gpu = som.som_bmu(dev(X), dev(W), d2=d2, qe=qe)[0].cpu().numpy()
+    b, best, _ = check_units(b_gpu, X, W)
+    if K > 20:
+        assert (b_gpu < K - 3).all()
+    same = b_gpu == b
+    np.testing.assert_allclose(d2.cpu().numpy()[same], best[same], rtol=REL, atol=1e-12)
+    q = qe.cpu().numpy()
+    assert abs(q[0] - np.sqrt(best).sum()) <= REL * np.sqrt(best).sum() and abs(q[1] - best.sum()) <= REL * best.sum()
+    assert np.array_equal(som.som_bmu(dev(X), dev(W))[0].cpu().numpy(), b_gpu)
+    idx = draw_subset(7, 0, m, max(1, m // 3))
+    part = som.som_bmu(dev(X), dev(W), idx=dev(idx.astype(np.int32)))[0].cpu().numpy()
+    assert np.array_equal(part, b_gpu[idx.astype(np.int64)])
+
+
+# ---------------------------------------------------------------------------------------------------- one context, all searches
+def test_searches_that_follow_each_other_on_one_context(som):
+    """Narrow, wide and float32 searches, look-ups and epochs share the context's preparation and its result words: long and
+    short re-decision lists after each other, in both orders, each against the oracle."""
+    shapes = [(30_000, 96, 3, 50), (2000, 100, 1, 100), (300, 64, 1, 8), (20_000, 300, 1, 50), (6000, 50, 4, 130), (30_000, 96, 2, 20),
+              (500, 200, 2, 64)]
+    order = shapes + shapes[::-1] + [shapes[0], shapes[0], shapes[4], shapes[0]]
+    data = {}
+    for m, distinct, copies, D in shapes:
+        X = rows(3 + D + distinct, m, D)
+        W = np.concatenate([X[draw_initial_rows(5, m, distinct)]] * copies)
+        data[(m, distinct, copies, D)] = (dev(X), dev(W), X, W, oracle.bmu_gram(X, W))
+    for it, key in enumerate(order):
+        Xd, Wd, X, W, (b, best, second) = data[key]
+        som.som_set_search("float32" if it % 5 == 3 else "auto")
+        som.som_profile(it % 3 == 1)                             # keeps a call off the small path
+        qe = torch.empty(2, dtype=torch.float64, device="cuda")
+        b_gpu = som.som_bmu(Xd, Wd, qe=qe)[0].cpu().numpy()
+        som.som_profile(False)
+        som.som_set_search("auto")
+        assert ((b_gpu == b) | oracle.near_tie_mask(best, second)).all(), f"call {it}: {key}"
+        assert (b_gpu < key[1]).all()
+        assert abs(qe.cpu().numpy()[1] - best.sum()) <= REL * best.sum(), f"call {it}: {key}"
+
+
+# ---------------------------------------------------------------------------------------------------- wide search
+@pytest.mark.parametrize("K", [65536, 65537])
+@pytest.mark.parametrize("m", [256, 257])
+def test_wide_search_at_the_limits_of_its_records(som, m, K):
+    """Four copies of every node inside each block of 4096, so that every sample is a tie that the joined winners leave open:
+    256 of them are few enough for the all-nodes pass, 257 go through the candidate pass; above 65536 nodes the 16-bit ids
+    do not reach and the all-nodes pass takes every list.  The nodes are far apart, so the answer is the lowest copy."""
+    D = 66
+    rng = np.random.default_rng(12)
+    base = rng.normal(size=(16384, D)).astype(np.float32) * 3.0
+    W = np.concatenate([np.concatenate([base[1024 * b:1024 * (b + 1)]] * 4) for b in range(16)])
+    lowest = np.concatenate([4096 * b + np.arange(1024) for b in range(16)])
+    if K > len(W):
+        W = np.concatenate([W, np.full((1, D), 1e3, dtype=np.float32)])
+    pick = rng.integers(0, 16384, size=m)
+    X = (base[pick] + 0.01 * rng.normal(size=(m, D))).astype(np.float32)
+    d2 = torch.empty(m, device="cuda")
+    b = som.som_bmu(dev(X), dev(W), d2=d2)[0].cpu().numpy()
+    assert np.array_equal(b, lowest[pick])
+    want = ((X.astype(np.float64) - base[pick].astype(np.float64)) ** 2).sum(1)
+    np.testing.assert_allclose(d2.cpu().numpy(), want, rtol=REL)
+
+
+@pytest.mark.parametrize("m,K,D", [(500, 1700, 70), (257, 1281, 65), (255, 2560, 97), (513, 769, 128), (300, 4353, 66), (1, 700, 80),
+                                   (2049, 257, 96), (100, 255, 127)])
+def test_wide_search_with_ragged_splits(som, m, K, D):
+    """Node tiles that do not divide among the workgroups of a sample tile, last tiles of a few nodes, sample tiles of one row."""
+    X, W = rows(200 + K, m, D), rows(201 + K, K, D)
+    W[K - 1] = W[0]                                              # the last node of the last tile against the first
+    X[0] = W[0]
+    d2 = torch.empty(m, device="cuda")
+    qe = torch.empty(2, dtype=torch.float64, device="cuda")
+    b_gpu = som.som_bmu(dev(X), dev(W), d2=d2, qe=qe)[0].cpu().numpy()
+    b, best, _ = check_units(b_gpu, X, W)
+    assert b_gpu[0] == 0
+    np.testing.assert_allclose(d2.cpu().numpy()[b_gpu == b], best[b_gpu == b], rtol=REL, atol=1e-12)
+    assert abs(qe.cpu().numpy()[1] - best.sum()) <= REL * best.sum()
+
+
+# ---------------------------------------------------------------------------------------------------- accumulation by sort
+@pytest.mark.parametrize("reproducible", [False, True])
+@pytest.mark.parametrize("m,K,D", [(9000, 8192, 70), (9000, 8193, 70), (5000, 16384, 66), (5000, 16385, 66), (257, 1, 200), (4097, 300, 64),
+                                   (20_001, 100, 126), (2048, 77, 129), (3000, 16385, 20), (64, 8192, 50), (30_000, 40, 2001)])
+def test_accumulation_by_sort_at_its_limits(som, reproducible, m, K, D):
+    """Per-node counters at the ends of their LDS, one node, one segment, many segments, sums that a call adds to."""
+    X = rows(600 + K + D, m, D)
+    rng = np.random.default_rng(K + D)
+    b = rng.integers(0, K, size=m).astype(np.int32)
+    b[rng.random(m) < 0.4] = K - 1                               # a crowded last node: many segments
+    b[::97] = -1                                                 # entries outside the map are skipped
+    b[5::97] = K
+    inside = (b >= 0) & (b < K)
+    S_or, n_or = oracle.accumulate(X[inside], None, b[inside], K)
+    # (fewer than four features or more nodes than the sort's counters in a fixed order, and more slabs than the LDS kernel
+    # serves: float32 partial sums, otherwise float64)
+    bar = (1e-6 if K > 8192 else 1e-9) * np.abs(X).max() * np.maximum(n_or, 1)[:, None]
+    som.som_set_reproducible(reproducible)
+    try:
+        out = []
+        for _ in range(2):
+            S = torch.full((K, D), 7.0, dtype=torch.float64, device="cuda")
+            n = torch.full((K,), 7, dtype=torch.int64, device="cuda")
+            som.som_accumulate(dev(X), dev(b), K, S, n, zero_first=True)
+            assert np.array_equal(n.cpu().numpy(), n_or)
+            assert (np.abs(S.cpu().numpy() - S_or) <= bar).all()
+            out.append(S.cpu().numpy().copy())
+        if reproducible and K <= 8192:
+            assert np.array_equal(out[0], out[1])
+        som.som_accumulate(dev(X), dev(b), K, S, n, zero_first=False)
+        assert np.array_equal(n.cpu().numpy(), 2 * n_or)
+        assert (np.abs(S.cpu().numpy() - 2 * S_or) <= 2 * bar).all()
+        idx = draw_subset(9, 0, m, max(1, m // 2))
+        S2, n2 = oracle.accumulate(X[idx.astype(np.int64)][inside[: len(idx)]], None, b[: len(idx)][inside[: len(idx)]], K)
+        som.som_accumulate(dev(X), dev(b[: len(idx)]), K, S, n, idx=dev(idx.astype(np.int32)), zero_first=True)
+        assert np.array_equal(n.cpu().numpy(), n2) and (np.abs(S.cpu().numpy() - S2) <= bar + 1e-6 * (K > 8192)).all()
+    finally:
+        som.som_set_reproducible(False)

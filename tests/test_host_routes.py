@@ -114,3 +114,51 @@ def test_accumulation_without_memory_for_the_sort(ctx):
     assert plain(ctx.accumulate(2 * m, K, D))[0] == -2
     ctx.limit()
     assert plain(ctx.accumulate(2 * m, K, D)) == (0, SORT)
+
+
+@pytest.mark.parametrize("kernel", ["small_kernel", "small_update_kernel"])
+def test_a_small_epoch_that_failed_leaves_nothing_behind(ctx, kernel):
+    """Neither launch of a failed epoch is counted on: the next one clears its sums itself."""
+    small = ["small_kernel<2,true>", "small_update_kernel"]
+    assert ctx.epoch(5000, 100, 8) == (0, ["fill_zero_kernel"] + small)
+    ctx.fail(kernel)
+    rc, names = ctx.epoch(5000, 100, 8)
+    assert rc == -3 and "small-map" in ctx.error()
+    ctx.fail()
+    assert ctx.epoch(5000, 100, 8) == (0, ["fill_zero_kernel"] + small)
+    assert ctx.epoch(5000, 100, 8) == (0, small)
+
+
+@pytest.mark.parametrize("kernel", ["bmu_split_prep_kernel", "bmu_split_kernel", "bmu_list_kernel"])
+def test_a_search_that_failed_before_its_list_leaves_no_maxima_behind(ctx, kernel):
+    """The maxima that the preparation finds are zero again once the list kernel has run; a call that did not get there makes
+    the next one clear them.  Another search in between does not touch them."""
+    rc, usual = ctx.bmu(100_000, 300, 50)
+    assert rc == 0 and usual[0] == "fill_zero_kernel" and usual[1] == "bmu_split_prep_kernel"
+    rc, again = ctx.bmu(100_000, 300, 50)
+    assert rc == 0 and again == usual[1:]
+    ctx.fail(kernel)
+    assert ctx.bmu(100_000, 300, 50)[0] == -3
+    ctx.fail()
+    assert ctx.bmu(100_000, 300, 50) == (0, usual)
+    assert ctx.bmu(100, 50, 3)[0] == 0                                    # (a small look-up, and the float32 search)
+    ctx.switch("som_set_search", 1)
+    assert ctx.bmu(5000, 200, 50)[0] == 0
+    ctx.switch("som_set_search", 0)
+    assert ctx.bmu(100_000, 300, 50) == (0, again)
+    assert ctx.bmu(100_000, 3000, 50)[1][:2] == ["fill_zero_kernel", "bmu_split_prep_kernel"]     # a new allocation
+
+
+# small epochs: without statistics, in the default mode, up to 32 features, 512 nodes, m K D = 3e8, W and the sums in LDS
+@pytest.mark.parametrize("m,K,D,small", [
+    (375_000, 100, 8, True), (375_001, 100, 8, False), (4000, 200, 32, True), (4000, 200, 33, False), (3000, 512, 8, True),
+    (3000, 513, 8, False), (3000, 334, 32, True), (3000, 335, 32, False), (10, 1, 1, True)])
+def test_small_epochs_on_both_sides_of_their_limits(ctx, m, K, D, small):
+    rc, names = ctx.epoch(m, K, D)
+    assert rc == 0 and (names[-1] == "small_update_kernel") == small, names
+    assert all(lds <= 160 * 1024 - 1024 for *_, lds in ctx.launches)
+    for switch in ("som_profile", "som_set_search", "som_set_reproducible"):
+        ctx.switch(switch, 1)
+        rc, names = ctx.epoch(m, K, D)
+        ctx.switch(switch, 0)
+        assert rc == 0 and "small_update_kernel" not in names
