@@ -2418,7 +2418,8 @@ static int launch_bmu(som_ctx* ctx, const BmuArgs& a)
     constexpr size_t lds_bytes = 2 * (size_t)stage_floats_for(STRIDE) * sizeof(float);
     // maps that end in whole blocks of padding nodes take the variant that skips them
     const bool pad = a.kpad - a.K >= 32;
-    static bool attr_set[2] = {false, false};
+    static bool attr_set_dev[kMaxDevices][2] = {};    // the attribute belongs to the device, not to the process
+    bool* attr_set = attr_set_dev[ctx->device];
     auto kern = pad ? bmu_kernel<STEPS, MS, true> : bmu_kernel<STEPS, MS, false>;
     if (!attr_set[pad]) {
         if (int rc = check_hip(ctx,

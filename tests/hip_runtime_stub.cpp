@@ -27,6 +27,8 @@ std::map<const void*, std::string>& kernels()
     return m;
 }
 std::map<void*, size_t> device_memory;
+std::map<std::pair<int, const void*>, size_t> lds_limit;     // per device: what a kernel's dynamic LDS was raised to
+int device = 0;
 std::string launched;                       // one line per launch: name grid.x grid.y grid.z block lds
 size_t limit = ~(size_t)0, allocated = 0, freed = 0;
 bool capturing = false;
@@ -93,6 +95,8 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void**, size_t 
 {
     const auto it = kernels().find(f);
     if (!failing.empty() && it != kernels().end() && it->second.rfind(failing, 0) == 0) return last_error = hipErrorLaunchFailure;
+    const auto raised = lds_limit.find({device, f});
+    if (lds > (raised == lds_limit.end() ? 64 * 1024 : raised->second)) return last_error = hipErrorInvalidValue;
     char sizes[128];
     snprintf(sizes, sizeof(sizes), " %u %u %u %u %zu\n", grid.x, grid.y, grid.z, block.x, lds);
     launched += (it == kernels().end() ? std::string("?") : it->second) + sizes;
@@ -148,10 +152,14 @@ hipError_t hipGetSymbolAddress(void** p, const void*)
 
 hipError_t hipGetDeviceCount(int* n)
 {
-    *n = 1;
+    *n = 2;
     return hipSuccess;
 }
-hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipSetDevice(int d)
+{
+    device = d;
+    return hipSuccess;
+}
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* prop, int)
 {
     memset(prop, 0, sizeof(*prop));
@@ -164,7 +172,11 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int)
     return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
-hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void* f, hipFuncAttribute, int bytes)
+{
+    lds_limit[{device, f}] = (size_t)bytes;
+    return hipSuccess;
+}
 hipError_t hipGetLastError()
 {
     const hipError_t e = last_error;

@@ -26,7 +26,7 @@ def link(directory) -> str:
 class StubContext:
     """One context of the stubbed library.  Every call returns (return code, [kernel names in launch order])."""
 
-    def __init__(self, path: str, stream=None):
+    def __init__(self, path: str, stream=None, device=0):
         self.lib = C.CDLL(path)
         for name in ("stub_allocated", "stub_freed"):
             getattr(self.lib, name).restype = C.c_size_t
@@ -37,7 +37,7 @@ class StubContext:
         self._buf = C.create_string_buffer(4096)          # stands for every array: no kernel runs, nothing is read
         self._p = C.c_void_p(C.addressof(self._buf))
         self.ctx = C.c_void_p()
-        assert self.lib.som_create(C.byref(self.ctx), C.c_int(0), C.c_void_p(stream)) == 0
+        assert self.lib.som_create(C.byref(self.ctx), C.c_int(device), C.c_void_p(stream)) == 0
 
     def close(self):
         self.lib.som_destroy(self.ctx)

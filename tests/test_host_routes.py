@@ -162,3 +162,24 @@ def test_small_epochs_on_both_sides_of_their_limits(ctx, m, K, D, small):
         rc, names = ctx.epoch(m, K, D)
         ctx.switch(switch, 0)
         assert rc == 0 and "small_update_kernel" not in names
+
+
+def test_dynamic_lds_is_raised_on_every_device(library):
+    """The limit on a kernel's dynamic LDS belongs to the device: a second one needs it raised as the first did."""
+    contexts = [stub_library.StubContext(library, device=d) for d in (0, 1)]
+    try:
+        for ctx in contexts:
+            for search in (0, 1):
+                ctx.switch("som_set_search", search)
+                for D in (8, 16, 17, 24, 32, 33, 40, 50, 55, 64, 100, 130, 200):
+                    for K in (64, 400, 1024):
+                        assert ctx.bmu(200_000, K, D)[0] == 0 and ctx.bmu(500, K, D)[0] == 0, (search, K, D, ctx.error())
+                        assert ctx.epoch(3000, K, D)[0] == 0, (search, K, D, ctx.error())
+            for fixed in (0, 1):
+                ctx.switch("som_set_reproducible", fixed)
+                for K, D in ((300, 3), (1024, 3), (2000, 31), (8000, 100), (12_000, 70), (18_000, 40), (6000, 63)):
+                    for m in (100_000, 10_000_000):
+                        assert ctx.accumulate(m, K, D)[0] == 0, (fixed, m, K, D, ctx.error())
+    finally:
+        for ctx in contexts:
+            ctx.close()
