@@ -28,6 +28,14 @@
  * waiting, unless a [host] output is requested (som_epoch's stats, som_epoch_host, som_epoch_file).  The caller owns every
  * buffer it passes and keeps it alive until som_sync (or a synchronising call) returns; the library owns only
  * its internal workspaces.  A context is bound to one device and is not thread-safe.
+ *
+ * Calls that only enqueue (som_bmu, som_accumulate, som_neighborhood_update, som_topology, som_epoch without stats) may be
+ * recorded into a HIP graph once the context has served the same call outside of one, and the graph replayed in stream
+ * order with other calls on the context: workspaces are allocated on demand, which capture forbids, and a later call that
+ * needs a larger one frees what the graph still uses.
+ *
+ * Rows that hold a NaN or an infinity: their distances are not below infinity to any node, their unit is 0 and their
+ * distance is not finite.
  */
 #ifndef SOM_H
 #define SOM_H
@@ -70,13 +78,14 @@ int som_sync(som_ctx* ctx);
 
 /*
  * Measurement support (not an operation of the paper).  While profiling is enabled the library brackets every
- * launch of its BMU search kernel (in the default search together with the small kernel that compacts the
- * search's per-sample marks into the re-decision list) with a pair of HIP events on the context's stream; som_profile_read waits for the
+ * launch of its BMU search kernel (in the default search together with the kernel that decides which samples are listed
+ * for re-decision) with a pair of HIP events on the context's stream; som_profile_read waits for the
  * stream, writes up to `capacity` kernel durations in milliseconds (launch order) to ms [host], stores the number
  * of launches recorded since the last read in *count [host], and starts a new record.  A call over more rows than one
- * pass holds (2^27; fewer for D > 64 in the default search, whose pass must fit the samples' bf16 parts into 8 GB)
- * launches the kernel once per pass; for D > 64 in the default search a launch's bracket includes the conversion of
- * the pass's samples.
+ * pass holds (2^27; 2^24 for D > 64 in the default search) launches the kernel once per pass.
+ * PROFILING CHANGES WHAT RUNS FOR SMALL CALLS: look-ups and epochs that go through one or two kernels of their own otherwise
+ * (see SOM_SEARCH_AUTO) take the general path while it is enabled, so their profile is of kernels that an unprofiled call
+ * does not launch.  The results are the same.
  */
 int som_profile(som_ctx* ctx, int enable);
 int som_profile_read(som_ctx* ctx, float* ms, int32_t capacity, int32_t* count);
@@ -114,13 +123,13 @@ int som_read_probe(som_ctx* ctx, const void* p, int64_t bytes);
  *   X [device] N x D, ldx;  idx [device] m row numbers or NULL;  W [device] K x D
  *   bmu [device] int32[m], required: bmu[i] = b(x_{idx[i]})
  *   d2  [device] float[m] or NULL: squared distance to the BMU by float32 direct differences: on the values as
- *       given for re-decided samples, on values centred by the column means of W for the others (relative
- *       error up to 6e-5 from the two centring roundings; samples that close to their node are re-decided)
+ *       given for re-decided samples, for D > 64 and for small calls, on values centred near the middle of W for the
+ *       others (relative error up to 6e-5 from the two centring roundings; samples that close to their node are re-decided)
  *   qe  [device] double[2] or NULL, OVERWRITTEN with { sum_i sqrt(d2_i), sum_i d2_i }  (the quantisation
  *       error of Section 4.1.2 is qe[0] / m)
  * The N x K distance matrix is never formed in memory.  m == 0 is allowed (qe becomes {0, 0}).
- * With d2 and qe both NULL no distance is formed for samples that are not re-decided: for 4 <= D <= 64 the default
- * search then reads every row once instead of twice.
+ * With d2 and qe both NULL no distance is formed for samples that are not re-decided: the default search for D >= 4 then
+ * reads every row once instead of twice.
  */
 int som_bmu(som_ctx* ctx, const float* X, int64_t N, int32_t D, int64_t ldx,
             const uint32_t* idx, int64_t m, const float* W, int32_t K,
@@ -207,11 +216,13 @@ enum { SOM_SAFEGUARD_THRESHOLD = 0, SOM_SAFEGUARD_SHIFT = 1 };
 int som_set_safeguard(som_ctx* ctx, int mode);
 
 /*
- * Accumulation order (not an operation of the paper).  By default the per-BMU sums are taken with float64 LDS
- * atomics: counts are exact, a sum can differ between two runs by a few units in its 16th digit because the order
- * of the additions is not fixed.  With on != 0 every later som_accumulate / som_epoch / som_epoch_host on this
- * context uses the slower kernel that adds in a fixed order wherever it applies (K <= 1024, or K <= 2048 with
- * D <= 31): S, and with it W, is then bit-identical from run to run.
+ * Accumulation order (not an operation of the paper).  By default the per-BMU sums are taken in float64 in an order that is
+ * not fixed (LDS atomics, or a sort by node): counts are exact, a sum can differ between two runs by a few units in its
+ * 16th digit.  With on != 0 every later som_accumulate / som_epoch / som_epoch_host on this context adds in a fixed order
+ * wherever a fixed-order kernel applies: a stable sort by node and float64 sums for D >= 4 and K <= 8192, matrix-pipe
+ * accumulators (float32 over at most 16384 rows, then float64) for D < 4 and K <= 2048.  S, and with it W, is then
+ * bit-identical from run to run.  Where the sort finds no memory (4 bytes a sample and more) the accumulators take over for
+ * K <= 1024, or K <= 2048 with D <= 31; other shapes return SOM_ENOMEM then.
  */
 int som_set_reproducible(som_ctx* ctx, int on);
 
@@ -221,9 +232,11 @@ int som_set_reproducible(som_ctx* ctx, int on);
  * rounding bound of the arithmetic in use is re-decided by direct float32 differences.
  *   SOM_SEARCH_AUTO (default)  for D >= 4 and K > 1 the samples and weights are cut into two bf16 parts each
  *                              and a score is the sum of three bf16 MFMA products (worst-case error of a
- *                              difference of two scores: below 2^-14 of |x||w| + |w|^2/2); for D > 64 the samples' parts
- *                              are written once per call into a library-owned workspace of up to 8 GB (rows go
- *                              through in passes that fit it); other shapes use the float32 MFMA search;
+ *                              difference of two scores: below 2^-14 of |x||w| + |w|^2/2); for D > 64 the call keeps 68 to
+ *                              368 bytes per sample of a pass of 2^24 rows; other shapes use the float32 MFMA search.
+ *                              Small calls form no scores: a look-up (som_bmu with D <= 64, up to about m K D = 4e8) takes
+ *                              direct differences over all nodes in one kernel, and a small epoch (no statistics,
+ *                              D <= 32, K <= 512, m K D <= 3e8, the default order of summation) is two kernels;
  *   SOM_SEARCH_FLOAT32         float32 MFMA for every shape.
  * Applies to every later som_bmu / som_epoch / som_epoch_host on this context.
  */

@@ -1,6 +1,7 @@
 // Per-BMU sample sums and counts (the inner sums of Eq. 3 grouped by best-matching unit):
 //     S_k += x_i,  n_k += 1   for k = b_i.
-// The pass is bound by reading X once.  Global floating-point atomics serialise in the memory system, so every
+// Which kernel a call takes (accumulate_run: the sort, the float64 LDS kernel, the MFMA accumulators), and the fallback for
+// maps that none of them holds, described here.  The pass is bound by reading X once.  Global floating-point atomics serialise in the memory system, so every
 // workgroup owns a contiguous range of samples and a slab of `ws` features, adds its samples into a float32
 // partial P[K][ws] held in LDS (LDS atomics; consecutive lanes take consecutive features of a sample, so a
 // sample's lanes never collide), and moves the partial into its own slice of a global workspace every kFlushRows

@@ -20,7 +20,8 @@
 // closer than that worst-case bound is put on a list and re-decided by direct differences sum_d (x_d - w_kd)^2 on
 // the values as given (lowest index wins ties): over every node (bmu_exact_kernel), or, for long lists, over the
 // few nodes whose score lies inside the bound, which a second pass of the search collects (bmu_cand_kernel +
-// bmu_cand_exact_kernel; the bf16 search for D <= 64 takes the differences at the end of its candidate tile).
+// bmu_cand_exact_kernel; the bf16 search for D <= 64 takes the differences at the end of its candidate tile, and knows the
+// candidates of most of its near ties without that pass: pair_list).
 // Where the caller asks for distances, the winner's squared distance of all other samples is recomputed by direct
 // differences as well, so the reported distances never carry the cancellation error of the score form.
 //
@@ -164,8 +165,10 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
 
 // ---------------------------------------------------------------------------------------------------------
 // Weight preparation of the bf16 search for D <= 64, one launch: a wavefront per node and lane per feature.
-//   * Centre: the mean of up to kCentreNodes nodes spread over the map, worked out by every workgroup for itself (any vector
-//     near the middle of the weights does; a kernel of its own for the mean over all nodes cost 5 us and a launch).
+//   * Centre: the mean of up to kCentreNodes nodes, every (K / kCentreNodes)-th, worked out by every workgroup for itself (any
+//     vector will do, the nearer to the middle of the weights the tighter the bounds; a kernel of its own for the mean over
+//     all nodes cost 5 us and a launch).  On a lattice whose number of columns divides that stride the nodes are all in one
+//     column (64 x 64; 32 x 32: two columns), so the centre is off the middle there and more samples are listed than need be.
 //   * Stage rows (layout at bmu_split_tile) and their float32 copy (wwin: the same slots, for the distances) are put together
 //     in LDS and leave it as whole lines, as do the sixteen nodes' columns of the transposed copy.
 //   * Packed tail (tail_r > 0): the last tail_r <= 4 features do not get a 16-feature block of their own (three MFMAs for a
@@ -775,7 +778,7 @@ __device__ __forceinline__ int split_window(int q, int D) { return 4 * q < D - 4
 // CAND = true: the candidate pass over the first `count` entries of the re-decision list (as in bmu_tile): the same
 // scores are formed again, bit for bit, and every node whose score reaches the entry's cut is noted.
 // KB whole 16-feature blocks (three MFMAs each) and, with TAIL, one packed block for the last a.tail_r <= 4 features
-// (one MFMA; layout in bmu_prep_split_kernel).
+// (one MFMA; layout at bmu_split_prep_kernel).
 template <int KB, bool TAIL, int MS, bool CAND>
 __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, int64_t tile_index, unsigned int count,
                                                float4* lds4)
@@ -2256,8 +2259,6 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     const size_t centre_floats = (size_t)(nch > 1 ? nch * 2 * steps : 64);
     const size_t centre_bytes = ((centre_floats > (size_t)D ? centre_floats : (size_t)D) * sizeof(float) + 255) / 256 * 256;
     // rows for the bf16 matrix pipe where the split search applies
-    // (small maps stay with the float32 search: a tile is mostly prologue and epilogue there, and the split search's
-    // are the longer ones; measured at 10^7 x 50: 256 nodes 3.5 ms against 4.5, 576 nodes 5.7 against 5.1)
     const bool split = D >= 4 && K > kSplitMinNodes && ctx->search != SOM_SEARCH_FLOAT32;
     // D <= 64: whole 16-feature blocks, and a remainder of one to four features goes into one packed block (one MFMA
     // instead of three for a block that would be mostly padding); larger remainders get a block of their own
@@ -2559,7 +2560,8 @@ static int dispatch_bmu(som_ctx* ctx, int steps, const BmuArgs& a)
 
 static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a);
 
-// The rows go through in passes of at most 2^27: the re-decision workspace then stays near 2.2 GB whatever m is,
+// The rows go through in passes of at most 2^27: the re-decision workspace then stays at 2.7 GB (20 bytes a row; the float32
+// searches' candidate sets 0.5 GB more) whatever m is,
 // and a pass's list stays within what the candidate pass can hold (2^24 entries, an eighth of a pass) — one call over
 // 10^9 rows listed more than that and fell back to direct differences over all nodes for every listed sample.
 int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs a)

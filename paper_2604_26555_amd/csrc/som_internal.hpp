@@ -95,7 +95,7 @@ struct som_ctx {
     void* prep_blob = nullptr;
     size_t prep_bytes = 0;
     bool prep_clean = false;       // its maxima (BmuPrep::tops) are zero
-    uint32_t* recheck = nullptr;   // one allocation: sample positions [cap], cuts [cap], second list, candidate slots
+    uint32_t* recheck = nullptr;   // one allocation: lists [cap], cuts [cap], per-sample marks or second list [cap], pair ids [cap][2], candidate sets
     size_t recheck_cap = 0;
     bool recheck_sets = false;     // the allocation holds the candidate sets
     int32_t* bmu_ws = nullptr;     // BMU indices of the epoch drivers (one chunk's worth)

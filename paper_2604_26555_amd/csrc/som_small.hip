@@ -23,8 +23,8 @@ constexpr size_t kSLds = 128 * 1024;          // W and the sums of small_kernel,
 constexpr size_t kSCells = kSLds / sizeof(double);   // cells of a set of sums: they are in LDS beside W, so never as many
 constexpr int kSFeatures = 32;                // small_kernel: features of a row at most
 constexpr int kSNodes = 512;                  // small epochs: nodes at most
-constexpr double kSWork = 3.0e8;              // m K D of a small epoch at most: about 20 us of vector arithmetic, what the
-                                              // general path spends on its launches
+constexpr double kSWork = 3.0e8;              // m K D of a small epoch at most: 0.4 to 0.8 of the general path's time there (D = 2 ... 32,
+                                              // K = 16 ... 512), at 6e8 0.5 to 1.3
 constexpr double kLWork = 4.0e8;              // ... of a small look-up,
 constexpr double kLSteps = 6.0e8;             // and the same with rows and features rounded up (look_up_rows)
 

@@ -258,8 +258,8 @@ int update_run(som_ctx* ctx, const double* S, const unsigned long long* n, const
 // The same update for callers that cannot allocate (som_neighborhood_update_static): the split-k partials and the
 // exponent shifts live in a fixed device array instead of a grown workspace.  One array per GPU, shared by every
 // call on that GPU and holding the last call's contents; every cell a call reads it has written first (the
-// contraction writes all kSplitK partials of every node and column, the shift kernel every node), so nothing needs
-// clearing.  Host code never uses the array's name as an address: the device address is looked up once per device.
+// contraction writes every node and column of the partials that its launch has, the finish kernel reads those, the shift
+// kernel writes every node), so nothing needs clearing.  Host code never uses the array's name as an address: the device address is looked up once per device.
 // ---------------------------------------------------------------------------------------------------------
 static __device__ __align__(256) double scratch[(size_t)kSplitK * kUpdateStaticCells + kUpdateStaticNodes];
 

@@ -113,3 +113,43 @@ def test_replayed_epochs(cap, m, rows, D, epochs):
         np.testing.assert_allclose(Wd.cpu().numpy(), want, rtol=2e-7, atol=1e-6 * np.abs(want).max(), err_msg=f"replay {r}")
     cap.eager(call)
     np.testing.assert_allclose(Wd.cpu().numpy(), want, rtol=2e-7, atol=1e-6 * np.abs(want).max())
+
+
+@pytest.mark.parametrize("m,side,D,kind,reproducible,shift", [(20_000, 12, 50, "mst", False, False), (5_000, 9, 100, "rng", False, True),
+                                                              (30_000, 66, 40, "rng", False, False), (8_000, 20, 64, "mst", True, True)])
+def test_replayed_stages(cap, m, side, D, kind, reproducible, shift):
+    """The graph rebuild, the accumulation and the update one by one, on units that are given."""
+    K = side * side
+    X = GaussianMixture(19 + D, D, 5).rows(0, m)
+    W0 = GaussianMixture(20 + D, D, 5).rows(0, K)
+    b = np.random.default_rng(D).integers(0, K, size=m).astype(np.int32)
+    Xd, W0d, Wd, bd = dev(X), dev(W0), dev(W0), dev(b)
+    G = torch.empty((K, K), device="cuda")
+    S = torch.empty((K, D), dtype=torch.float64, device="cuda")
+    n = torch.empty(K, dtype=torch.int64, device="cuda")
+    guarded = torch.empty(1, dtype=torch.int32, device="cuda")
+    S2, n2, b2 = torch.empty_like(S[:49]), torch.empty_like(n[:49]), dev(b[:1000] % 49)
+    cap.som.som_set_reproducible(reproducible)
+    cap.som.som_set_safeguard("shift" if shift else "threshold")
+
+    def call():
+        Wd.copy_(W0d)
+        cap.som.som_topology(Wd, kind, G=G)
+        cap.som.som_accumulate(Xd, bd, K, S, n, zero_first=True)
+        cap.som.som_neighborhood_update(S, n, G, 1.5, Wd, n_guarded=guarded)
+
+    print(f"replayed stages: m={m} K={K} D={D} {kind}", flush=True)
+    cap.eager(call)
+    S_or, n_or = oracle.accumulate(X, None, b, K)
+    assert np.array_equal(n.cpu().numpy(), n_or)
+    np.testing.assert_allclose(S.cpu().numpy(), S_or, rtol=1e-9, atol=1e-9 * np.abs(X).max() * m)
+    want = [t.cpu().numpy().copy() for t in (G, S, n, Wd, guarded)]
+    cap.record(call)
+    for r in cap.replays(lambda: cap.som.som_accumulate(Xd[:1000], b2, 49, S2, n2, zero_first=True)):
+        assert np.array_equal(G.cpu().numpy(), want[0]) and np.array_equal(n.cpu().numpy(), want[2]), f"replay {r}"
+        np.testing.assert_allclose(S.cpu().numpy(), want[1], rtol=1e-9, atol=1e-9 * np.abs(X).max() * m, err_msg=f"replay {r}")
+        np.testing.assert_allclose(Wd.cpu().numpy(), want[3], rtol=1e-6, atol=1e-6, err_msg=f"replay {r}")
+        assert int(guarded.item()) == int(want[4][0])
+        for t in (G, S, n, guarded):
+            t.fill_(3)
+        torch.cuda.synchronize()
