@@ -183,8 +183,12 @@ __global__ void __launch_bounds__(256) accumulate_direct_kernel(const float* __r
 // The sort by node (six launches, float64, reads every row once) against the LDS kernel over slabs of nodes and windows of 63
 // features (two launches a window, every slab scans all BMU indices), both timed for D = 4 ... 5000, K = 16 ... 16384, m = 10
 // ... 5 * 10^6 and even, uneven and clustered shares of the nodes:
-//   * wide rows (two windows or more): the sort takes 0.02 to 1.0 of the time, except where it has fewer rows than nodes to
-//     spread its launches over: 1.1 to 1.5 up to 126 features (two windows).
+//   * three windows or more: the sort takes 0.03 to 1.07 of the time.
+//   * two windows (64 to 126 features): 0.75 to 1.0, except with fewer rows than nodes to spread its launches over (1.1 to 1.5);
+//     with more than 8 slabs below half a million rows (100,000 to 300,000 rows of 64 to 112 features on 2304 to 4096 nodes: 1.1
+//     to 1.3; from 10^6 rows 0.5 to 0.95); and with 65 to 96 features, whose lanes beyond D idle, from 800,000 rows on up to 8
+//     slabs (K = 1024, D = 72: 100,000 rows 40 us against 42, 10^6 124 against 115, 3 * 10^6 341 against 309; D = 100: 140
+//     against 152, 375 against 372; K = 100, D = 72: 10^7 rows 942 against 811).
 //   * one window: the sort wins only where the slabs are many and leave compute units idle, and the rows cover its launches:
 //     K = 4096, D = 50 (11 slabs) 10^5 rows 49 us against 29, 5 * 10^5 70 against 65, 10^6 106 against 109 to 130, 5 * 10^6
 //     376 against 465 to 710; K = 3136, D = 50 (9 slabs) 10^6 rows 102 against 90; above 6400 nodes its counters per block
@@ -194,7 +198,10 @@ static bool sort_pays(int64_t m, int32_t K, int32_t D)
 {
     const int slabs = accumulate_f64_slabs(K, D);
     if (slabs > kFMaxSlabs || D > 126) return true;
-    if (D > 63) return m >= 256 && m >= K;
+    if (D > 63) {
+        if (slabs > 8) return m >= 500000;
+        return m >= 256 && m >= K && !(D > 64 && D <= 96 && m >= 800000);
+    }
     return slabs > 9 && K <= 6400 && m >= 750000;
 }
 

@@ -317,7 +317,11 @@ int accumulate_sort_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, co
     const int slabs = (D + 4 * lanes - 1) / (4 * lanes);
     int64_t rows = m * lanes * slabs / (256 * 4 * 4 * 64);
     if (slabs > 1) rows /= 2;                 // (10^5 x 2000: 2.33, 2.13, 2.07 ms an epoch with 390, 195, 97 rows)
-    rows = rows < 32 ? 32 : rows > 1024 ? 1024 : rows;
+    // Every wavefront reads its own stretch of X.  Where X is large and the nodes' shares are uneven, long segments lose a third
+    // or more at some lengths (K = 1024, 150 features: 5 * 10^6 rows 1365 us with 1024 rows, 922 with 256; 10^7 rows of 72
+    // features 1472, 994; K = 4096: 1520, 1131), and even ones of 256 rows 5 % at most (K = 100, 10^7 rows of 150: 1692, 1761).
+    const int64_t longest = (double)m * D * 4.0 > 2.5e9 ? 256 : 1024;
+    rows = rows < 32 ? 32 : rows > longest ? longest : rows;
     const size_t segs_most = (size_t)(m / rows) + K;
     const size_t hist_words = (size_t)blocks * K, words = (hist_words + 3 * (size_t)K + 2 + (size_t)m + 1) / 2 * 2;
     if (int rc = sort_workspace(ctx, words * sizeof(uint32_t) + segs_most * D * sizeof(double))) return rc;

@@ -88,6 +88,8 @@ def plain(result):
     (1_000_000, 1024, 50, SLABS), (749_999, 4096, 50, SLABS), (750_000, 4096, 50, SORT), (1_000_000, 3136, 50, SLABS),
     (1_000_000, 6401, 40, SLABS), (1_000_000, 6400, 40, SORT), (5_000_000, 16384, 16, SLABS), (100, 16384, 50, SORT),
     (255, 16, 64, 2 * SLABS), (256, 16, 64, SORT), (1023, 1024, 126, 2 * SLABS), (1024, 1024, 126, SORT), (10, 1024, 127, SORT),
+    (799_999, 1024, 96, SORT), (800_000, 1024, 65, 2 * SLABS), (800_000, 1024, 96, 2 * SLABS), (800_000, 1024, 64, SORT),
+    (800_000, 1024, 97, SORT), (499_999, 4096, 64, 2 * SLABS), (500_000, 4096, 64, SORT), (800_000, 4096, 72, SORT),
     (10, 16, 2000, SORT), (1000, 16385, 200, FLOAT32), (1000, 16385, 16, SLABS), (1000, 16385, 63, FLOAT32),
 ])
 def test_accumulation_routes(ctx, m, K, D, kernels):
