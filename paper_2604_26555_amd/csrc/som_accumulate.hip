@@ -193,11 +193,11 @@ __global__ void __launch_bounds__(256) accumulate_direct_kernel(const float* __r
 //     K = 4096, D = 50 (11 slabs) 10^5 rows 49 us against 29, 5 * 10^5 70 against 65, 10^6 106 against 109 to 130, 5 * 10^6
 //     376 against 465 to 710; K = 3136, D = 50 (9 slabs) 10^6 rows 102 against 90; above 6400 nodes its counters per block
 //     cost more than the slabs (K = 16384, D = 16: 172 against 92).
-//   * maps beyond the LDS kernel's slabs: always (what is left for them holds float32 partial sums).
-static bool sort_pays(int64_t m, int32_t K, int32_t D)
+//   * maps beyond the LDS kernel's slabs, and strides beyond its offsets: always (what is left for them holds float32 partial sums).
+static bool sort_pays(int64_t m, int32_t K, int32_t D, int64_t ldx)
 {
     const int slabs = accumulate_f64_slabs(K, D);
-    if (slabs > kFMaxSlabs || D > 126) return true;
+    if (slabs > kFMaxSlabs || ldx >= kFStride || D > 126) return true;
     if (D > 63) {
         if (slabs > 8) return m >= 500000;
         return m >= 256 && m >= K && !(D > 64 && D <= 96 && m >= 800000);
@@ -216,7 +216,7 @@ int accumulate_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const u
         const int rc = accumulate_mfma_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first);
         if (rc != 1) return rc;
         if (rs == SOM_ENOMEM) return rs;                 // a shape whose order is promised: not summed in any other
-    } else if (sort_pays(m, K, D)) {
+    } else if (sort_pays(m, K, D, ldx)) {
         const int rc = accumulate_sort_run(ctx, X, D, ldx, idx, m, bmu, K, S, n, zero_first, false);
         if (rc != 1 && rc != SOM_ENOMEM) return rc;
     }

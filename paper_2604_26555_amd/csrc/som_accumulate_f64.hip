@@ -209,7 +209,7 @@ int accumulate_f64_slabs(int32_t K, int32_t D)
 int accumulate_f64_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m,
                        const int32_t* bmu, int32_t K, double* S, unsigned long long* n, bool zero_first)
 {
-    if (m <= 0 || ldx >= (1 << 22)) return 1;               // row offsets inside a round of passes are 32-bit
+    if (m <= 0 || ldx >= kFStride) return 1;                // row offsets inside a round of passes are 32-bit
     const int window = D < 63 ? D : 63;                      // features per pass; lane 0 carries the count
     const int nslabs = accumulate_f64_slabs(K, D);
     if (nslabs > kFMaxSlabs) return 1;

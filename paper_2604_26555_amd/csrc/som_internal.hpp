@@ -168,7 +168,8 @@ int accumulate_mfma_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, co
 // 1 = shape not served; stable: fixed order of summation
 int accumulate_sort_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m,
                         const int32_t* bmu, int32_t K, double* S, unsigned long long* n, bool zero_first, bool stable);
-constexpr int kFMaxSlabs = 16;                  // most slabs of LDS that accumulate_f64_run serves
+constexpr int kFMaxSlabs = 16;                  // most slabs of LDS that accumulate_f64_run serves,
+constexpr int64_t kFStride = 1 << 22;           // and rows nearer to each other than this many floats
 int accumulate_f64_slabs(int32_t K, int32_t D);
 int accumulate_f64_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m,
                         const int32_t* bmu, int32_t K, double* S, unsigned long long* n, bool zero_first);

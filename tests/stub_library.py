@@ -70,9 +70,9 @@ class StubContext:
         i64, i32, p = C.c_int64, C.c_int32, self._p
         return self._run(self.lib.som_bmu, p, i64(m), i32(D), i64(D), None, i64(m), p, i32(K), p, p if d2 else None, p if qe else None)
 
-    def accumulate(self, m, K, D, zero_first=True):
+    def accumulate(self, m, K, D, zero_first=True, ldx=None):
         i64, i32, p = C.c_int64, C.c_int32, self._p
-        return self._run(self.lib.som_accumulate, p, i64(m), i32(D), i64(D), None, i64(m), p, i32(K), p, p, C.c_int(int(zero_first)))
+        return self._run(self.lib.som_accumulate, p, i64(m), i32(D), i64(ldx or D), None, i64(m), p, i32(K), p, p, C.c_int(int(zero_first)))
 
     def epoch(self, m, K, D):
         i64, i32, f64, p = C.c_int64, C.c_int32, C.c_double, self._p

@@ -288,3 +288,23 @@ def test_accumulation_by_sort_at_its_limits(som, reproducible, m, K, D):
         assert np.array_equal(n.cpu().numpy(), n2) and (np.abs(S.cpu().numpy() - S2) <= bar + 1e-6 * (K > 8192)).all()
     finally:
         som.som_set_reproducible(False)
+
+
+@pytest.mark.parametrize("m,K,D,ldx", [(40, 16, 8, 1 << 22), (33, 300, 70, (1 << 22) + 3), (650_000, 200, 1000, 1000), (700_001, 3, 900, 900)])
+def test_accumulation_by_sort_of_rows_far_apart_and_of_large_matrices(som, m, K, D, ldx):
+    """Strides beyond the slab kernel's offsets; matrices beyond 2.5 GB, whose segments are shorter: float64 sums in both."""
+    gen = torch.Generator(device="cuda").manual_seed(m + D)
+    X = torch.empty((m - 1) * ldx + D, device="cuda").as_strided((m, D), (ldx, 1))
+    X.copy_(torch.rand(m, D, generator=gen, device="cuda") - 0.5)
+    b = (torch.rand(m, generator=gen, device="cuda") ** 2 * K).to(torch.int32).clamp_(max=K - 1)
+    S = torch.full((K, D), 7.0, dtype=torch.float64, device="cuda")
+    n = torch.full((K,), 7, dtype=torch.int64, device="cuda")
+    som.som_accumulate(X, b, K, S, n, zero_first=True)
+    want = torch.zeros(K, D, dtype=torch.float64, device="cuda")
+    for i in range(0, m, 50_000):
+        want.index_add_(0, b[i:i + 50_000].long(), X[i:i + 50_000].double())
+    n_want = torch.bincount(b.long(), minlength=K)
+    assert torch.equal(n, n_want)
+    # both sides add up to n_k doubles: n_k units of the last place of sums below n_k / 2
+    bar = n_want.double()[:, None] ** 2 * 2.0 ** -53
+    assert ((S - want).abs() <= bar).all()

@@ -97,6 +97,13 @@ def test_accumulation_routes(ctx, m, K, D, kernels):
         assert plain(ctx.accumulate(m, K, D, zero_first)) == (0, kernels)
 
 
+def test_accumulation_of_rows_far_apart_keeps_float64_sums(ctx):
+    """The slab kernel's row offsets hold strides below 2^22 floats; beyond them the sort serves every call that it can."""
+    for m, K, D in ((100, 1024, 100), (1_000_000, 1024, 72), (1000, 4096, 50), (1000, 16, 8)):
+        assert plain(ctx.accumulate(m, K, D, ldx=(1 << 22) - 1))[1][0] == SLABS[0]
+        assert plain(ctx.accumulate(m, K, D, ldx=1 << 22)) == (0, SORT)
+
+
 def test_accumulation_without_memory_for_the_sort(ctx):
     """The sort's workspace goes with the samples; the kernels that served such calls before it need less, and do again."""
     m, K, D = 20_000_000, 100, 200
