@@ -165,10 +165,11 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
 
 // ---------------------------------------------------------------------------------------------------------
 // Weight preparation of the bf16 search for D <= 64, one launch: a wavefront per node and lane per feature.
-//   * Centre: the mean of up to kCentreNodes nodes, every (K / kCentreNodes)-th, worked out by every workgroup for itself (any
-//     vector will do, the nearer to the middle of the weights the tighter the bounds; a kernel of its own for the mean over
-//     all nodes cost 5 us and a launch).  On a lattice whose number of columns divides that stride the nodes are all in one
-//     column (64 x 64; 32 x 32: two columns), so the centre is off the middle there and more samples are listed than need be.
+//   * Centre: the mean of up to kCentreNodes nodes, one from each stretch of K / kCentreNodes at a place that a hash of its number
+//     picks, worked out by every workgroup for itself (any vector will do, the nearer to the middle of the weights the tighter
+//     the bounds; a kernel of its own for the mean over all nodes cost 5 us and a launch).  Every (K / kCentreNodes)-th node
+//     instead would be one or two columns of a lattice whose side divides that stride, off the middle: 10^6 x 50 on 64 x 64
+//     nodes took 2.29 ms an epoch with those and takes 2.05 with these (shorter lists of near ties), on 32 x 32 0.452 and 0.448.
 //   * Stage rows (layout at bmu_split_tile) and their float32 copy (wwin: the same slots, for the distances) are put together
 //     in LDS and leave it as whole lines, as do the sixteen nodes' columns of the transposed copy.
 //   * Packed tail (tail_r > 0): the last tail_r <= 4 features do not get a 16-feature block of their own (three MFMAs for a
@@ -187,6 +188,17 @@ struct SplitPrep {
     float* wwin;
     int kb_count, tail_r, row_bytes, stage16_bytes;
 };
+
+// the t-th of `count` nodes whose mean is the centre (count = K: all of them)
+__device__ __forceinline__ int centre_node(int t, int count, int K)
+{
+    if (count == K) return t;
+    uint32_t h = (uint32_t)t * 0x9e3779b1u;
+    h ^= h >> 15;
+    h *= 0x85ebca77u;
+    h ^= h >> 13;
+    return (int)((int64_t)t * K / count) + (int)__umulhi(h, (uint32_t)(K / count));
+}
 
 __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const float* __restrict__ W, int K, int D, int kpad,
                                                                          float* __restrict__ centre, float* __restrict__ wt,
@@ -212,7 +224,7 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
 #pragma unroll
     for (int u = 0; u < kCentreNodes / kPrepNodes; ++u) {
         const int t = wave * (kCentreNodes / kPrepNodes) + u;
-        v4[u] = (t < count && lane < D) ? W[(size_t)((int64_t)t * K / count) * D + lane] : 0.0f;
+        v4[u] = (t < count && lane < D) ? W[(size_t)centre_node(t, count, K) * D + lane] : 0.0f;
     }
     float s = 0.0f;
 #pragma unroll
