@@ -902,9 +902,9 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         }
         const int64_t row = a.idx ? (int64_t)a.idx[ii] : ii;
         const float* xr = a.X + row * a.ldx;
-        // squares of this lane's slots: all of them, weighted by how many of the large MFMAs follow (xa), and of what the
-        // first bf16 parts leave over (left2)
-        float xs = 0.0f, xa = 0.0f, left2 = 0.0f;
+        // squares of this lane's slots: all of them, weighted by how many of the large MFMAs follow (xa), of what the first bf16
+        // parts leave over (left2) and of what both do (rest2)
+        float xs = 0.0f, xa = 0.0f, left2 = 0.0f, rest2 = 0.0f;
         if constexpr (TAIL) {
             float vt[4];
             tail_values(xr, a.D, vt);
@@ -914,8 +914,10 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                 for (int t = 0; t < 4; ++t) {
                     const float xv = g == 0 ? vt[t] : 0.0f;      // the packed block's features once each
                     const float left = xv - (float)(__bf16)xv;
+                    const float rest = left - (float)(__bf16)left;
                     xs = fmaf(xv, xv, xs);
                     left2 = fmaf(left, left, left2);
+                    rest2 = fmaf(rest, rest, rest2);
                 }
                 xa = xs;
             }
@@ -928,7 +930,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                 if constexpr (CAND) {
                     split8(v[kb], xh[mb][kb], xl[mb][kb]);
                 } else {
-                    split8(v[kb], xh[mb][kb], xl[mb][kb], left2);
+                    split8(v[kb], xh[mb][kb], xl[mb][kb], left2, rest2);
                     float s8 = 0.0f;
 #pragma unroll
                     for (int t = 0; t < 8; ++t) s8 = fmaf(v[kb][t], v[kb][t], s8);
@@ -940,8 +942,8 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         }
         if constexpr (!CAND) {
             // The error of a score, in three parts.  (1) What the bf16 cut drops: with x = xh + xl + xr and w likewise,
-            // |xl| |wl| + |xr| |w| + |x| |wr|, where |xr| <= 2^-9 |x - xh| and the largest |w - wh| and |wr| over the nodes come
-            // from the weight preparation: norms that were formed, a fraction of the worst case 3 * 2^-18 |x| |w|.
+            // |xl| |wl| + |xr| |w| + |x| |wr|, where the largest |w - wh| and |wr| over the nodes come from the weight preparation:
+            // norms that were formed (a part has eight significant bits, so the worst case is 3 * 2^-16 |x| |w|, several times more).
             // (2) The pipe's accumulation.  How an MFMA orders and rounds the additions of its sixteen exact products to its
             // accumulator C is not documented, so each MFMA is charged what seventeen float32 terms can lose when added in
             // ANY order with one rounding to nearest per addition: 16 * 2^-24 (|C| + sum |products|).  (The largest error seen on
@@ -954,12 +956,14 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             xs += __shfl_xor(xs, 32);
             xa += __shfl_xor(xa, 32);
             left2 += __shfl_xor(left2, 32);
+            rest2 += __shfl_xor(rest2, 32);
             const float lo_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.norms[1])) * 1.001f;
             const float rest_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.norms[2])) * 1.001f;
             const float nx = __builtin_amdgcn_sqrtf(xs) * 1.0001f, nl = __builtin_amdgcn_sqrtf(left2) * 1.0001f;
+            const float nr = __builtin_amdgcn_sqrtf(rest2 + kRestFloor) * 1.0001f;
             constexpr float unit = 5.9604645e-08f;
             stash[(3 * mb + 0) * kThreads] = xs;
-            stash[(3 * mb + 1) * kThreads] = nl * (1.0078125f / 512.0f + 32.64f * KB * unit) + __builtin_amdgcn_sqrtf(xa) * (1.0001f * 16.256f * unit) + nx * (6.0f * unit);
+            stash[(3 * mb + 1) * kThreads] = nr * 1.0078125f + nl * (32.64f * KB * unit) + __builtin_amdgcn_sqrtf(xa) * (1.0001f * 16.256f * unit) + nx * (6.0f * unit);
             stash[(3 * mb + 2) * kThreads] = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (32.64f * KB * unit));
         }
     }
@@ -1452,9 +1456,8 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         }
         if (r_valid) {
             if (a.qe) {
-                // The statistic n_recheck counts the near ties: best two scores inside the band that holds for any input, split
-                // at its worst and all MFMAs at the full magnitude.  Only those that this sample's own bound leaves open are
-                // listed.
+                // The statistic n_recheck counts the near ties: best two scores inside a band of fixed relative width, 3 * 2^-18 for
+                // the cut and all MFMAs at the full magnitude.  Only those that this sample's own bound leaves open are listed.
                 constexpr float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(49 * KB + (TAIL ? 17 : 0) + 1) * 5.9604645e-08f + 1.9073486e-06f) +
                                       12.0f * 5.9604645e-08f;
                 const float band = 0.5f * rel * ((xl2 * wb + 0.5f * wb * wb) + (xl2 * wmax + 0.5f * wmax2));

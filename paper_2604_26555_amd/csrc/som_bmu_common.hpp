@@ -18,6 +18,8 @@ __device__ __forceinline__ double wave_sum(double v)
 
 constexpr int kScalLo = 8;        // scal[8], scal[9]: bits of the largest |w - hi|^2 and |w - hi - lo|^2 (split search)
 
+constexpr float kRestFloor = 1e-37f;          // added to rest2 (split8): covers squares that underflow
+
 constexpr float kSplitPadNorm = -3.0e38f;     // padding nodes of the split search: finite, so that position bits cannot make a NaN
 
 // Sum of distances and squared distances of a workgroup's samples -> one of kQeSlots partial-sum slots.  Every
@@ -130,6 +132,20 @@ __device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& 
         const float left = v[i] - (float)hi[i];
         lo[i] = (__bf16)left;
         left2 = fmaf(left, left, left2);
+    }
+}
+
+// the same, and what both parts leave over is added to rest2 (both differences are exact)
+__device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo, float& left2, float& rest2)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        hi[i] = (__bf16)v[i];
+        const float left = v[i] - (float)hi[i];
+        lo[i] = (__bf16)left;
+        left2 = fmaf(left, left, left2);
+        const float rest = left - (float)lo[i];
+        rest2 = fmaf(rest, rest, rest2);
     }
 }
 

@@ -501,7 +501,9 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
         }
         node = (node >= 0 && node < a.K) ? node : a.K - 1;       // (only padding or non-finite scores get here)
         const float4 n = p.norm[i];
-        // The error of a score (as bmu_split_tile): what the cut drops, from the norms of the parts; a chunk's small products
+        // The error of a score (as bmu_split_tile): what the cut drops, from the norms of the parts (a second part leaves at most
+        // 2^-8 of what the first one left: eight significant bits; summing those squares as well takes registers that the tile
+        // does not have, 1.88 -> 2.00 ms at 10^6 x 200); a chunk's small products
         // in the accumulator of four MFMAs, its large ones in two and one (the weighted norm), each charged sixteen
         // roundings of 2^-24 whatever the order of its additions; one rounding per chunk's addition to the tile's
         // accumulators; six units for the centrings and -|w|^2 / 2.
@@ -512,7 +514,7 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
         // (float32 sums over up to 2^13 squares in this order are within 2^-14 of their own size)
         const float nx = root(n.x) * 1.0002f, nl = root(n.z) * 1.0002f;
         const float add = (float)(p.nch + 1) * 1.016f;
-        const float err_w = nl * (1.0078125f / 512.0f + 65.28f * unit) + root(n.y) * (1.0002f * 16.256f * unit) + nx * ((6.0f + add) * unit);
+        const float err_w = nl * (1.0078125f / 256.0f + 65.28f * unit) + root(n.y) * (1.0002f * 16.256f * unit) + nx * ((6.0f + add) * unit);
         const float err_0 = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (65.28f * unit));
         const float err_n = 0.5f * (6.0f + add) * unit;
         const float wn = -2.0f * p.norms[node];
@@ -526,7 +528,7 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
         cut = best - bound;
         a.bmu[i] = node;
         if (a.qe) {
-            // the statistic n_recheck: best two scores inside the band that holds for any input
+            // the statistic n_recheck: best two scores inside a band of fixed relative width, 3 * 2^-18 for the cut
             const float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(196 + (a.D + 63) / 64 + 1) * unit) + 12.0f * unit;
             near = close || (a.K > 1 && !((best - second) > (root(n.x) * wmax + 0.5f * wmax2) * rel));
         }
