@@ -122,9 +122,9 @@ int som_read_probe(som_ctx* ctx, const void* p, int64_t bytes);
  * Best-matching-unit search (Section 3.3.1, definition of b(x)).
  *   X [device] N x D, ldx;  idx [device] m row numbers or NULL;  W [device] K x D
  *   bmu [device] int32[m], required: bmu[i] = b(x_{idx[i]})
- *   d2  [device] float[m] or NULL: squared distance to the BMU by float32 direct differences: on the values as
- *       given for re-decided samples, for D > 64 and for small calls, on values centred near the middle of W for the
- *       others (relative error up to 6e-5 from the two centring roundings; samples that close to their node are re-decided)
+ *   d2  [device] float[m] or NULL: squared distance to the BMU by float32 direct differences on the values as given (the
+ *       float32 search: on values centred near the middle of W for samples that are not re-decided, relative error up to
+ *       6e-5 from the two centring roundings; samples that close to their node are re-decided)
  *   qe  [device] double[2] or NULL, OVERWRITTEN with { sum_i sqrt(d2_i), sum_i d2_i }  (the quantisation
  *       error of Section 4.1.2 is qe[0] / m)
  * The N x K distance matrix is never formed in memory.  m == 0 is allowed (qe becomes {0, 0}).

@@ -22,8 +22,9 @@
 // few nodes whose score lies inside the bound, which a second pass of the search collects (bmu_cand_kernel +
 // bmu_cand_exact_kernel; the bf16 search for D <= 64 takes the differences at the end of its candidate tile, and knows the
 // candidates of most of its near ties without that pass: pair_list).
-// Where the caller asks for distances, the winner's squared distance of all other samples is recomputed by direct
-// differences as well, so the reported distances never carry the cancellation error of the score form.
+// Where the caller asks for distances, the squared distance to the winner is formed by direct differences as well (in a
+// stream over the rows of its own behind the bf16 searches), so the reported distances never carry the cancellation error of
+// the score form.
 //
 // The default search (bmu_split_kernel further down for D <= 64, som_bmu_wide.hip above) is the same scheme with the
 // contraction on the bf16 matrix pipe, samples and weights cut into two bf16 parts each.
@@ -170,12 +171,12 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
 //     the bounds; a kernel of its own for the mean over all nodes cost 5 us and a launch).  Every (K / kCentreNodes)-th node
 //     instead would be one or two columns of a lattice whose side divides that stride, off the middle: 10^6 x 50 on 64 x 64
 //     nodes took 2.29 ms an epoch with those and takes 2.05 with these (shorter lists of near ties), on 32 x 32 0.452 and 0.448.
-//   * Stage rows (layout at bmu_split_tile) and their float32 copy (wwin: the same slots, for the distances) are put together
-//     in LDS and leave it as whole lines, as do the sixteen nodes' columns of the transposed copy.
+//   * Stage rows (layout at bmu_split_tile) are put together in LDS and leave it as whole lines, as do the sixteen nodes'
+//     columns of the transposed copy.
 //   * Packed tail (tail_r > 0): the last tail_r <= 4 features do not get a 16-feature block of their own (three MFMAs for a
 //     block that is mostly padding) but one packed block whose sixteen slots hold the three products side by side,
 //         weights  [ hi(r) | hi(r) | lo(r) | norm parts (3) | 0 ... ]   against samples  [ hi(r) | lo(r) | hi(r) | 1 1 1 | 0 ... ],
-//     one MFMA.  wwin carries the r centred weights in the block's first slots.
+//     one MFMA.
 //   * Norms: -|w|^2 / 2 behind the stage's rows (and as three bf16 parts in the packed block), the largest norms of the nodes
 //     and of what the bf16 cut leaves over (w - hi, w - hi - lo) in scal.
 // The result words of this call were cleared by the call before; this one clears the next one's (scal_next).
@@ -185,7 +186,6 @@ constexpr int kPrepNodes = 16;           // nodes (wavefronts) of a workgroup: 6
 
 struct SplitPrep {
     char* stage16;
-    float* wwin;
     int kb_count, tail_r, row_bytes, stage16_bytes;
 };
 
@@ -208,7 +208,6 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
     __shared__ float part[kPrepNodes][64];
     __shared__ float given[kPrepNodes][65];
     __shared__ uint4 rows16[kPrepNodes * 272 / 16];           // [node][row_bytes]
-    __shared__ float wide[kPrepNodes * 64];                   // [node][slots]
     __shared__ float most[kPrepNodes][3];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int k0 = blockIdx.x * kPrepNodes, k = k0 + wave;
@@ -231,9 +230,7 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
     for (int u = 0; u < kCentreNodes / kPrepNodes; ++u) s += v4[u];
     part[wave][lane] = s;
     given[wave][lane] = w;
-    const int slots = sp.kb_count * 16 + (sp.tail_r ? 16 : 0);
     for (int e = tid; e < kPrepNodes * sp.row_bytes / 16; e += 64 * kPrepNodes) rows16[e] = make_uint4(0u, 0u, 0u, 0u);
-    if (tid < kPrepNodes * slots) wide[tid] = 0.0f;
     __syncthreads();
     float c = 0.0f;
 #pragma unroll
@@ -262,13 +259,11 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
             __bf16* cell = reinterpret_cast<__bf16*>(row + kb * 64 + g * 32) + t;
             cell[0] = hi;
             cell[8] = lo;
-            wide[wave * slots + (kb * 2 + g) * 8 + t] = v;
         } else {
             __bf16* cell = reinterpret_cast<__bf16*>(row + sp.kb_count * 64) + (lane - tail0);
             cell[0] = hi;
             cell[sp.tail_r] = hi;
             cell[2 * sp.tail_r] = lo;
-            wide[wave * slots + sp.kb_count * 16 + lane - tail0] = v;
         }
     }
     if (lane == 0) {
@@ -296,7 +291,6 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
     // sixteen rows of a stage are contiguous (kNodesPerStage is a multiple of sixteen)
     uint4* to = reinterpret_cast<uint4*>(sp.stage16 + (size_t)(k0 / kNodesPerStage) * sp.stage16_bytes + (size_t)(k0 % kNodesPerStage) * sp.row_bytes);
     for (int e = tid; e < kPrepNodes * sp.row_bytes / 16; e += 64 * kPrepNodes) to[e] = rows16[e];
-    if (tid < kPrepNodes * slots) sp.wwin[(size_t)k0 * slots + tid] = wide[tid];
     const int f = tid >> 4, q = tid & 15;
     if (f < D) wt[(size_t)f * kpad + k0 + q] = given[q][f];
     if (tid < 3) {
@@ -329,10 +323,6 @@ __global__ void __launch_bounds__(kListThreads) bmu_list_kernel(const BmuArgs a)
 {
     __shared__ unsigned int wave_base[2][kListThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (a.tops && blockIdx.x == 0 && tid < 3) {            // the search has read them: zero again for the next preparation
-        a.tops[4 + tid] = a.tops[tid];
-        a.tops[tid] = 0u;
-    }
     constexpr int64_t per_block = (int64_t)kListThreads * kListPerThread;
     for (int64_t chunk = blockIdx.x; chunk * per_block < a.m; chunk += gridDim.x) {
         const int64_t i0 = chunk * per_block + (int64_t)tid * kListPerThread;
@@ -791,6 +781,49 @@ __device__ __forceinline__ int split_window(int q, int D) { return 4 * q < D - 4
 // scores are formed again, bit for bit, and every node whose score reaches the entry's cut is noted.
 // KB whole 16-feature blocks (three MFMAs each) and, with TAIL, one packed block for the last a.tail_r <= 4 features
 // (one MFMA; layout at bmu_split_prep_kernel).
+// first feature of lane half g's h-th window of k-block kb: only the last block of a row without a packed tail can be shifted
+template <int KB, bool TAIL>
+__device__ __forceinline__ int split_start(int kb, int g, int h, int D)
+{
+    return TAIL || kb < KB - 1 ? 16 * kb + 8 * g + 4 * h : split_window(4 * kb + 2 * g + h, D);
+}
+
+// A lane's part of the rows of MS sample blocks, as given.
+template <int KB, bool TAIL, int MS, bool CAND>
+struct SplitRows {
+    float4 x[MS][KB > 0 ? KB : 1][2], t[MS];
+
+    __device__ __forceinline__ void load(const BmuArgs& a, int64_t wave0, int64_t total, int j, int g)
+    {
+#pragma unroll
+        for (int mb = 0; mb < MS; ++mb) {
+            int64_t ii = wave0 + mb * 32 + j;
+            ii = ii < total ? ii : total - 1;
+            if constexpr (CAND) ii = (int64_t)a.recheck[ii];
+            const float* xr = a.X + (a.idx ? (int64_t)a.idx[ii] : ii) * a.ldx;
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) x[mb][kb][h] = load4(xr + split_start<KB, TAIL>(kb, g, h, a.D));
+            if constexpr (TAIL) t[mb] = load4(xr + a.D - 4);         // (inside the row: D >= 4)
+        }
+    }
+};
+
+// the two halves of a wavefront trade: a keeps its lower half's values and takes b's in its upper half, b the others
+__device__ __forceinline__ void swap_halves(float& a, float& b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_halves(int& a, int& b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)a, (unsigned)b, false, false);
+    a = (int)r[0];
+    b = (int)r[1];
+}
+
 template <int KB, bool TAIL, int MS, bool CAND>
 __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, int64_t tile_index, unsigned int count,
                                                float4* lds4)
@@ -798,90 +831,19 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     constexpr int RS = split_row_bytes(KB, TAIL);
     constexpr int STAGE_F4 = split_stage_f4(KB, TAIL);
     constexpr int KBA = KB > 0 ? KB : 1;               // array lengths (no zero-length arrays when D <= 4)
-    constexpr int WROW = KB * 16 + (TAIL ? 16 : 0);    // floats of a node's row in wwin
     constexpr int PRE = STAGE_F4 / kThreads;
     const char* ldsb = reinterpret_cast<const char*>(lds4);
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63;
+    int lane = tid & 63;
+    if constexpr (CAND) asm volatile("" : "+v"(lane));
     const int wave = tid >> 6;
     const int j = lane & 31;
     const int g = lane >> 5;
     const int64_t wave0 = first + (tile_index * kWavesPerGroup + wave) * (MS * 32);
 
-    // This lane's 8 KB slots of a sample row, centred; slots in front of a shifted window's own features read zero
-    // (they meet zero weights in the stage rows, and stay out of the norms and distances).
-    auto centred_slots = [&](const float* xr, int D, float (&v)[KBA][8]) {
-        float4 raw[KBA][2], cen[KBA][2];
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int start = split_window(4 * kb + 2 * g + h, D);
-                raw[kb][h] = load4(xr + start);
-                cen[kb][h] = load4(a.centre + start);
-            }
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int q = 4 * kb + 2 * g + h;
-                const int shift = 4 * q - split_window(q, D);            // own slots: i >= shift
-                v[kb][4 * h + 0] = shift <= 0 ? raw[kb][h].x - cen[kb][h].x : 0.0f;
-                v[kb][4 * h + 1] = shift <= 1 ? raw[kb][h].y - cen[kb][h].y : 0.0f;
-                v[kb][4 * h + 2] = shift <= 2 ? raw[kb][h].z - cen[kb][h].z : 0.0f;
-                v[kb][4 * h + 3] = shift <= 3 ? raw[kb][h].w - cen[kb][h].w : 0.0f;
-            }
-    };
-
-    // the last tail_r features of a row, centred: vt[t] = feature D - tail_r + t (zero for t >= tail_r); one 16-byte
-    // load of the window [D - 4, D), which lies inside the row because D >= 4
-    const int tail_r = TAIL ? a.tail_r : 0;
-    auto tail_values = [&](const float* xr, int D, float (&vt)[4]) {
-        const float4 raw = load4(xr + D - 4), cen = load4(a.centre + D - 4);
-        const float c4[4] = {raw.x - cen.x, raw.y - cen.y, raw.z - cen.z, raw.w - cen.w};
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int src = 4 - tail_r + t;              // 0 .. 3 for t < tail_r
-            float v = c4[3];
-            v = src == 2 ? c4[2] : v;
-            v = src == 1 ? c4[1] : v;
-            v = src == 0 ? c4[0] : v;
-            vt[t] = t < tail_r ? v : 0.0f;
-        }
-    };
-    // this lane's eight slots of the packed block: slot s = 8 g + i holds copy s / tail_r of tail feature s % tail_r,
-    // the samples' copies being hi, lo, hi (against the weights' hi, hi, lo)
-    auto tail_pack = [&](const float (&vt)[4]) {
-        bf16x8 out;
-        __bf16 hi[4], lo[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            hi[t] = (__bf16)vt[t];
-            lo[t] = (__bf16)(vt[t] - (float)hi[t]);
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int sidx = 8 * g + i;
-            const int copy = (sidx >= tail_r) + (sidx >= 2 * tail_r) + (sidx >= 3 * tail_r);
-            const int t = sidx - copy * tail_r;
-            __bf16 h = hi[3], l = lo[3];
-            h = t == 2 ? hi[2] : h;
-            l = t == 2 ? lo[2] : l;
-            h = t == 1 ? hi[1] : h;
-            l = t == 1 ? lo[1] : l;
-            h = t == 0 ? hi[0] : h;
-            l = t == 0 ? lo[0] : l;
-            const __bf16 zero = (__bf16)0.0f, one = (__bf16)1.0f;
-            const int ns = sidx - 3 * tail_r;                 // 0, 1, 2: opposite the three parts of -|w|^2 / 2
-            out[i] = copy > 2 ? ((ns >= 0 && ns < 3) ? one : zero) : (copy == 1 ? l : h);
-        }
-        return out;
-    };
-
     // ---- this wavefront's samples: centred, cut into bf16 parts, kept in registers
     bf16x8 xh[MS][KBA], xl[MS][KBA], xt[MS];
-    bool valid[MS];
     // search: squared norm of the centred sample (both lane halves hold the whole row's), err_w and err_0: a score errs by at
     // most err_w |w| + err_0 + kErrNorm |w|^2 / 2 (see below).  They wait in LDS, behind the stages, for the end of the tile:
     // the stage loop has no registers to spare for them.
@@ -889,55 +851,110 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     float cut[MS];          // CAND
     CandSet noted[MS];      // CAND
     unsigned int found[MS]; // CAND: hits of the block in hand
+    const int64_t total = CAND ? (int64_t)count : a.m;
+    SplitRows<KB, TAIL, MS, CAND> raw;
+    raw.load(a, wave0, total, j, g);
+    if constexpr (CAND) {
+#pragma unroll
+        for (int mb = 0; mb < MS; ++mb) {
+            const int64_t i = wave0 + mb * 32 + j;
+            cut[mb] = i < total ? a.cutv[i] : NAN;       // no score compares >= NaN
+            found[mb] = 0u;
+        }
+    }
+    const int tail_r = TAIL ? a.tail_r : 0;
+    // The packed block (layout at bmu_split_prep_kernel): slot s of the sixteen holds copy s / tail_r of tail feature s % tail_r,
+    // the samples' copies being hi, lo, hi (against the weights' hi, hi, lo), then three ones.  A lane's four words (slots 8 g to
+    // 8 g + 7) are put together from the window [D - 4, D) by byte permutations: which bytes of the four hi and of the four
+    // lo parts, and the ones.
+    unsigned int tail_sel[4][3];
+    if constexpr (TAIL) {
+        auto choose = [&](auto r_) {
+            constexpr int r = decltype(r_)::value;
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+#pragma unroll
+                for (int part = 0; part < 3; ++part) {
+                    constexpr auto sel = [](int gg, int w_, int part_) {
+                        unsigned int out = 0u;
+                        for (int h = 0; h < 2; ++h) {
+                            const int slot = 8 * gg + 2 * w_ + h, copy = slot / r;
+                            const unsigned at = 2u * (unsigned)(4 - r + slot % r);
+                            const bool hit = part_ == 2 ? (slot >= 3 * r && slot < 3 * r + 3) : (copy < 3 && (copy == 1) == (part_ == 1));
+                            const unsigned v = part_ == 2 ? (hit ? 0x3f80u : 0u) : hit ? (at | ((at + 1u) << 8)) : 0x0c0cu;
+                            out |= v << (16 * h);
+                        }
+                        return out;
+                    };
+                    tail_sel[w][part] = g == 0 ? sel(0, w, part) : sel(1, w, part);
+                }
+        };
+        if (tail_r == 1) choose(std::integral_constant<int, 1>{});
+        else if (tail_r == 2) choose(std::integral_constant<int, 2>{});
+        else if (tail_r == 3) choose(std::integral_constant<int, 3>{});
+        else choose(std::integral_constant<int, 4>{});
+    }
 #pragma unroll
     for (int mb = 0; mb < MS; ++mb) {
-        found[mb] = 0u;
-        const int64_t i = wave0 + mb * 32 + j;
-        const int64_t total = CAND ? (int64_t)count : a.m;
-        valid[mb] = i < total;
-        int64_t ii = valid[mb] ? i : total - 1;
-        if constexpr (CAND) {
-            cut[mb] = valid[mb] ? a.cutv[ii] : NAN;     // no score compares >= NaN
-            ii = (int64_t)a.recheck[ii];
-        }
-        const int64_t row = a.idx ? (int64_t)a.idx[ii] : ii;
-        const float* xr = a.X + row * a.ldx;
-        // squares of this lane's slots: all of them, weighted by how many of the large MFMAs follow (xa), of what the first bf16
-        // parts leave over (left2) and of what both do (rest2)
-        float xs = 0.0f, xa = 0.0f, left2 = 0.0f, rest2 = 0.0f;
+        // squares: of the first parts, the same weighted by how many of the large MFMAs follow (xa), of the second parts (lo2) and
+        // of what both leave over (rest2)
+        float hi2 = 0.0f, xa = 0.0f, lo2 = 0.0f, rest2 = 0.0f;
         if constexpr (TAIL) {
-            float vt[4];
-            tail_values(xr, a.D, vt);
-            xt[mb] = tail_pack(vt);
-            if constexpr (!CAND) {
+            const float4 cen = load4(a.centre + a.D - 4);
+            const float4 v4 = raw.t[mb];
+            // (elements in front of the tail belong to the whole blocks)
+            const float v[4] = {tail_r > 3 ? v4.x - cen.x : 0.0f, tail_r > 2 ? v4.y - cen.y : 0.0f, tail_r > 1 ? v4.z - cen.z : 0.0f, v4.w - cen.w};
+            unsigned int h[2], l[2];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float xv = g == 0 ? vt[t] : 0.0f;      // the packed block's features once each
-                    const float left = xv - (float)(__bf16)xv;
-                    const float rest = left - (float)(__bf16)left;
-                    xs = fmaf(xv, xv, xs);
-                    left2 = fmaf(left, left, left2);
-                    rest2 = fmaf(rest, rest, rest2);
+            for (int q = 0; q < 2; ++q) {
+                const SplitPair p(v[2 * q], v[2 * q + 1]);
+                if constexpr (!CAND) {
+                    hi2 = square2(p.hi, hi2);
+                    lo2 = square2(p.lo, lo2);
+                    rest2 = p.rest2(rest2);
                 }
-                xa = xs;
+                h[q] = p.hi;
+                l[q] = p.lo;
             }
+            // (both lane halves hold the tail's features: they count once)
+            hi2 = g == 0 ? hi2 : 0.0f;
+            lo2 = g == 0 ? lo2 : 0.0f;
+            rest2 = g == 0 ? rest2 : 0.0f;
+            xa = hi2;
+            uint4 out;
+            out.x = __builtin_amdgcn_perm(h[1], h[0], tail_sel[0][0]) | __builtin_amdgcn_perm(l[1], l[0], tail_sel[0][1]) | tail_sel[0][2];
+            out.y = __builtin_amdgcn_perm(h[1], h[0], tail_sel[1][0]) | __builtin_amdgcn_perm(l[1], l[0], tail_sel[1][1]) | tail_sel[1][2];
+            out.z = __builtin_amdgcn_perm(h[1], h[0], tail_sel[2][0]) | __builtin_amdgcn_perm(l[1], l[0], tail_sel[2][1]) | tail_sel[2][2];
+            out.w = __builtin_amdgcn_perm(h[1], h[0], tail_sel[3][0]) | __builtin_amdgcn_perm(l[1], l[0], tail_sel[3][1]) | tail_sel[3][2];
+            xt[mb] = __builtin_bit_cast(bf16x8, out);
         }
-        if constexpr (KB > 0) {
-            float v[KBA][8];
-            centred_slots(xr, a.D, v);
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-                if constexpr (CAND) {
-                    split8(v[kb], xh[mb][kb], xl[mb][kb]);
-                } else {
-                    split8(v[kb], xh[mb][kb], xl[mb][kb], left2, rest2);
-                    float s8 = 0.0f;
+        for (int kb = 0; kb < KB; ++kb) {
+            float v[8];
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) s8 = fmaf(v[kb][t], v[kb][t], s8);
-                    constexpr float after = (float)(KB + (TAIL ? 1 : 0));
-                    xs += s8;
-                    xa = fmaf((after - (float)kb) * (after - (float)kb), s8, xa);
+            for (int h = 0; h < 2; ++h) {
+                const int q = 4 * kb + 2 * g + h, start = split_start<KB, TAIL>(kb, g, h, a.D);
+                const float4 cen = load4(a.centre + start), x4 = raw.x[mb][kb][h];
+                v[4 * h + 0] = x4.x - cen.x;
+                v[4 * h + 1] = x4.y - cen.y;
+                v[4 * h + 2] = x4.z - cen.z;
+                v[4 * h + 3] = x4.w - cen.w;
+                if (!TAIL && kb == KB - 1) {
+                    // (slots in front of a shifted window's own features read zero: they meet zero weights in the stage rows, and
+                    // stay out of the norms)
+                    const int shift = 4 * q - start;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) v[4 * h + t] = shift <= t ? v[4 * h + t] : 0.0f;
                 }
+            }
+            if constexpr (CAND) {
+                split8(v, xh[mb][kb], xl[mb][kb]);
+            } else {
+                float s8 = 0.0f;
+                split8(v, xh[mb][kb], xl[mb][kb], s8, lo2, rest2);
+                constexpr float after = (float)(KB + (TAIL ? 1 : 0));
+                hi2 += s8;
+                xa = fmaf((after - (float)kb) * (after - (float)kb), s8, xa);
             }
         }
         if constexpr (!CAND) {
@@ -953,16 +970,18 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             // are in the accumulator of the KB - kb (+ 1 with a tail) MFMAs from their own on, which the weighted norm xa adds up.
             // Half squared norms: in the accumulator of all 3 KB MFMAs, or of the packed block's only.
             // (3) Six units for the roundings of the two centrings and of -|w|^2 / 2.
-            xs += __shfl_xor(xs, 32);
+            hi2 += __shfl_xor(hi2, 32);
             xa += __shfl_xor(xa, 32);
-            left2 += __shfl_xor(left2, 32);
+            lo2 += __shfl_xor(lo2, 32);
             rest2 += __shfl_xor(rest2, 32);
             const float lo_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.norms[1])) * 1.001f;
             const float rest_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.norms[2])) * 1.001f;
-            const float nx = __builtin_amdgcn_sqrtf(xs) * 1.0001f, nl = __builtin_amdgcn_sqrtf(left2) * 1.0001f;
+            // |xl| (before its own cut) and |x| are at most what their parts add up to
             const float nr = __builtin_amdgcn_sqrtf(rest2 + kRestFloor) * 1.0001f;
+            const float nl = __builtin_amdgcn_sqrtf(lo2) * 1.0001f + nr, nh = __builtin_amdgcn_sqrtf(hi2) * 1.0001f;
+            const float nx = nh + nl;
             constexpr float unit = 5.9604645e-08f;
-            stash[(3 * mb + 0) * kThreads] = xs;
+            stash[(3 * mb + 0) * kThreads] = nx;
             stash[(3 * mb + 1) * kThreads] = nr * 1.0078125f + nl * (32.64f * KB * unit) + __builtin_amdgcn_sqrtf(xa) * (1.0001f * 16.256f * unit) + nx * (6.0f * unit);
             stash[(3 * mb + 2) * kThreads] = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (32.64f * KB * unit));
         }
@@ -1024,12 +1043,6 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             if (nb >= 2 && r1 >= 14) tsel[mb][c] = (best[mb][c] > before[mb][c]) ? st : tsel[mb][c];
         }
     };
-    // node of a class winner: its stage, its class and the position in its score's low bits
-    auto node_of = [&](float v, int st, int c) {
-        const int pos = (int)(__float_as_uint(v) & 15u), r = 2 * (pos & 7) + (c & 1);
-        return st * kNodesPerStage + 32 * (2 * (pos >> 3) + (c >> 1)) + 8 * (r >> 2) + 4 * g + (r & 3);
-    };
-
     // ---- stream the nodes through LDS
     const int nstages = a.kpad / kNodesPerStage;
     const float4* src4 = reinterpret_cast<const float4*>(a.stage16);
@@ -1232,13 +1245,13 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         // lowest distance, then lowest node index; the halves are joined at the end.  An entry whose set overflowed
         // in either half (more than seven candidates) or that noted nothing goes to the second list, which the
         // all-nodes kernel serves.  The row stays in registers across the candidates: D <= 64.
-        double qs = 0.0, qs2 = 0.0;
 #pragma unroll
         for (int mb = 0; mb < MS; ++mb) {
             const int n = noted[mb].n;
             const bool over = n >= kCandSlots;
-            const int mine = (valid[mb] && !over) ? n : 0;
             const int64_t ie = wave0 + mb * 32 + j;
+            const bool valid = ie < total;
+            const int mine = (valid && !over) ? n : 0;
             const int64_t is = (int64_t)a.recheck[ie < (int64_t)count ? ie : (int64_t)count - 1];
             const float* xr = a.X + (a.idx ? (int64_t)a.idx[is] : is) * a.ldx;
             const int D = a.D, whole = D / 4, rest = D - 4 * whole;
@@ -1290,189 +1303,113 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                 bk = ok;
             }
             const bool served = !over && !oover && bk < a.K;
-            const bool writer = valid[mb] && g == 0;
+            const bool writer = valid && g == 0;
             const int64_t i = writer ? (int64_t)a.recheck[wave0 + mb * 32 + j] : 0;
-            if (writer && served) {
-                a.bmu[i] = bk;
-                if (a.d2) a.d2[i] = bd;
-                qs += sqrt((double)bd);
-                qs2 += (double)bd;
-            }
+            if (writer && served) a.bmu[i] = bk;
             list_push(&a.scal[a.slot2], a.recheck2, nullptr, writer && !served, i, 0.0f);
         }
-        if (a.qe) group_qe_add(a.qe_part, qs, qs2);
         return;
     }
-    // ---- join the two half-wavefronts, then lane (j, g) finishes block mp + g
+    // ---- winners and bounds
     const float wmax2 = __uint_as_float(a.norms[0]);
     const float wmax = sqrtf(wmax2) * 1.000001f;
     // |w|^2 / 2 in the accumulators: see (2) at the start of the tile; and six units as for the products
     constexpr float kErrNorm = ((TAIL ? 16.256f : 48.768f * KB) + 6.0f) * 5.9604645e-08f;
-    // (the window offsets are worked out again rather than carried through the stage loop in registers)
-    int d_again = a.D;
-    asm volatile("" : "+s"(d_again));
-    // Squared distances (d2, the quantisation-error sums) only where the caller wants them: without them the rows are
-    // not read a second time, the sample's norm comes from the start of the tile and the winner's from the stage
-    // blob (-|w|^2 / 2 in float32 behind the rows of its stage).
-    const bool distances = a.d2 != nullptr || a.qe != nullptr;
-    double qs = 0.0, qs2 = 0.0;
-    int near = 0;
     // (square roots here are the hardware's, good to a unit in the last place; the factors behind them cover it)
     auto root = [](float v) { return __builtin_amdgcn_sqrtf(v); };
-    // Both lane halves join their classes and each other's winners; then half g finishes block mp + g.
+    // Lane (j, g) finishes sample j of block g (MS = 1: half 0 does): the halves trade what they hold of each other's block, and
+    // all eight class winners of a sample meet in one lane: places 0 to 3 from half 0's rows, 4 to 7 from half 1's.
+    static_assert(MS <= 2, "a block per lane half");
+    float won[8], most;
+    int from[8];
 #pragma unroll
-    for (int mp = 0; mp < MS; mp += 2) {
-        float r_best = 0.f, r_second = 0.f, r_most = 0.f, r_part = 0.f;
-        int r_node = 0;
-        bool r_valid = false;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int mb = mp + q;
-            if (mb >= MS) break;
-            // winner and runner-up over this half's classes (equal scores are a near tie, decided elsewhere: any of them)
-            const float(&b)[CLS] = best[mb];
-            const float m01 = fmaxf(b[0], b[1]), m23 = fmaxf(b[2], b[3]);
-            float bst = fmaxf(m01, m23);
-            float most = fmaxf(fmaxf(second[mb][0], second[mb][1]), fmaxf(second[mb][2], second[mb][3]));
-            float sec = fmaxf(fmaxf(most, fminf(m01, m23)), fmaxf(fminf(b[0], b[1]), fminf(b[2], b[3])));
-            int key = 4 * tsel[mb][0];                                    // stage and class of the winner
-            key = b[1] == bst ? 4 * tsel[mb][1] + 1 : key;
-            key = b[2] == bst ? 4 * tsel[mb][2] + 2 : key;
-            key = b[3] == bst ? 4 * tsel[mb][3] + 3 : key;
-            int node = node_of(bst, key >> 2, key & 3);
-            const float ob = __shfl_xor(bst, 32);
-            const float os = __shfl_xor(sec, 32);
-            const float om = __shfl_xor(most, 32);
-            const int on = __shfl_xor(node, 32);
-            sec = fmaxf(fmaxf(sec, os), fminf(bst, ob));
-            most = fmaxf(most, om);
-            const bool other = (ob > bst) || (ob == bst && on < node);
-            bst = other ? ob : bst;
-            node = other ? on : node;
-            node = (node >= 0 && node < a.K) ? node : a.K - 1;            // (only padding or non-finite scores get here)
-            // where distances are wanted the squared distance to the winner by direct differences on the float32 values, this
-            // lane's slots (the row is read again: it is still in the cache; the winner's centred weights come from the
-            // float32 copy of the stage rows, in the same slot order)
-            float part = 0.f;
-            if (distances) {
-                int64_t ii = wave0 + mb * 32 + j;
-                ii = ii < a.m ? ii : a.m - 1;
-                const float* xr = a.X + (a.idx ? (int64_t)a.idx[ii] : ii) * a.ldx;
-                if constexpr (TAIL) {
-                    // the packed block's features once each: lane half 0 takes them (its first slots of wwin hold the weights)
-                    float vt[4];
-                    tail_values(xr, d_again, vt);
-                    const float4 w0 = *reinterpret_cast<const float4*>(a.wwin + (size_t)node * WROW + KB * 16);
-                    const float w[4] = {w0.x, w0.y, w0.z, w0.w};
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const float df = g == 0 ? vt[t] - w[t] : 0.0f;
-                        part = fmaf(df, df, part);
-                    }
-                }
-                if constexpr (KB > 0) {
-                    float v[KBA][8];
-                    centred_slots(xr, d_again, v);
-                    const float* wr = a.wwin + (size_t)node * WROW + g * 8;
-#pragma unroll
-                    for (int kb = 0; kb < KB; ++kb) {
-                        const float4 w0 = *reinterpret_cast<const float4*>(wr + kb * 16);
-                        const float4 w1 = *reinterpret_cast<const float4*>(wr + kb * 16 + 4);
-                        const float w[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) {
-                            const float df = v[kb][t] - w[t];
-                            part = fmaf(df, df, part);
-                        }
-                    }
-                }
-                part += __shfl_xor(part, 32);
-            }
-            if (q == g) {
-                r_best = bst;
-                r_second = sec;
-                r_most = most;
-                r_node = node;
-                r_part = part;
-                r_valid = valid[mb];
-            }
-        }
-        const int64_t i = wave0 + (mp + g) * 32 + j;
-        // the sample's figures from the start of the tile, and the winner's squared norm from the stage blob
-        const int own = MS > 1 ? mp + g : 0;
-        const float xnorm2 = stash[(3 * own + 0) * kThreads], err_w = stash[(3 * own + 1) * kThreads], err_0 = stash[(3 * own + 2) * kThreads];
-        const char* blob = reinterpret_cast<const char*>(a.stage16) + (size_t)(r_node / kNodesPerStage) * STAGE_F4 * 16;
-        const float wn = -2.0f * reinterpret_cast<const float*>(blob + (size_t)kNodesPerStage * RS)[r_node % kNodesPerStage];
-        const float xl2 = root(xnorm2);
-        // The winner's score errs by its own norm's bound.  A node that is in truth as near as the winner lies within the
-        // winner's distance of the sample, so its norm is at most |x| + |x - w_b| (and at most the largest); no other node
-        // can spoil the decision.  The position bits change a score by at most 2^-19 of itself, and a rival's score is
-        // within the bound of the best one.
-        const float wb = fminf(root(wn) * 1.00001f, wmax);
-        const float err_b = err_w * wb + err_0 + 0.5f * kErrNorm * wb * wb;
-        const float bits = fabsf(r_best) * (1.01f * 3.8146973e-06f);
-        const float far2 = fmaxf(xnorm2 * 1.00001f - 2.0f * r_best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
-        const float wo = fminf((xl2 + root(far2)) * 1.0001f, wmax);
-        const float bound = err_b + err_w * wo + err_0 + 0.5f * kErrNorm * wo * wo + bits;
-        // (a sample that close to its node is re-decided for the sake of its distance: the centring roundings)
-        const float tiny = (xl2 + wmax) * (xl2 + wmax) * 3.8146973e-06f;
-        const bool close = r_valid && a.K > 1 && (!((r_best - r_second) > bound) || (distances && r_part < tiny));
-        // Candidates: the class winners that reach the cut, two ids of each half at most; complete when no class's runner-up
-        // reaches it.  Otherwise (or with 16-bit ids not enough) the sample goes on the list of the candidate pass.
-        const float cut_at = r_best - bound;
-        bool open = !(r_most < cut_at) || a.K > kPairNodes;
-        if (__ballot(close) != 0ull) {
-            const float cut_other = __shfl_xor(cut_at, 32);
-            const bool want = close && !open;
-            const bool want_other = __shfl_xor(want ? 1 : 0, 32) != 0;
-            bool many[2] = {false, false};
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int mb = mp + q;
-                if (mb >= MS) break;
-                const float cut_mb = q == g ? cut_at : cut_other;
-                unsigned int packed = 0xffffffffu;
-                int hits = 0;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const unsigned id = (unsigned)node_of(best[mb][c], tsel[mb][c], c);
-                    const bool hit = best[mb][c] >= cut_mb;
-                    packed = hit ? (packed << 16) | id : packed;
-                    hits += hit ? 1 : 0;
-                }
-                many[q] = hits > 2;
-                // both halves' ids in one row of four places, the used ones in front; half g writes places 2 g and 2 g + 1
-                const unsigned int theirs = (unsigned int)__shfl_xor((int)packed, 32);
-                const unsigned int h0 = g == 0 ? packed : theirs, h1 = g == 0 ? theirs : packed;
-                const bool none0 = h0 == 0xffffffffu, one0 = !none0 && (h0 >> 16) == 0xffffu;
-                const unsigned int w0 = none0 ? h1 : one0 ? (h0 & 0xffffu) | (h1 << 16) : h0;
-                const unsigned int w1 = none0 ? 0xffffffffu : one0 ? (h1 >> 16) | 0xffff0000u : h1;
-                if (q == g ? want : want_other) a.pairs[2 * (wave0 + mb * 32 + j) + g] = g == 0 ? w0 : w1;
-            }
-            // (too many in the other half: it says so to the half that finishes this block)
-            const bool mine_many = g == 0 ? many[0] : many[1], others_many = g == 0 ? many[1] : many[0];
-            const int told = __shfl_xor(others_many ? 1 : 0, 32);
-            open = open || mine_many || told != 0;
-        }
-        if (r_valid) {
-            if (a.qe) {
-                // The statistic n_recheck counts the near ties: best two scores inside a band of fixed relative width, 3 * 2^-18 for
-                // the cut and all MFMAs at the full magnitude.  Only those that this sample's own bound leaves open are listed.
-                constexpr float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(49 * KB + (TAIL ? 17 : 0) + 1) * 5.9604645e-08f + 1.9073486e-06f) +
-                                      12.0f * 5.9604645e-08f;
-                const float band = 0.5f * rel * ((xl2 * wb + 0.5f * wb * wb) + (xl2 * wmax + 0.5f * wmax2));
-                near += (close || (a.K > 1 && !((r_best - r_second) > band))) ? 1 : 0;
-                if (!close) {
-                    qs += sqrt((double)r_part);
-                    qs2 += (double)r_part;
-                }
-            }
-            a.bmu[i] = r_node;
-            if (a.d2) a.d2[i] = r_part;
-            a.cut_all[i] = !close ? kNotListed : open ? list_cut(cut_at) : kPairs;
-        }
+    for (int c = 0; c < 4; ++c) {
+        won[c] = best[0][c];
+        won[4 + c] = best[MS - 1][c];
+        swap_halves(won[c], won[4 + c]);
+        from[c] = tsel[0][c];
+        from[4 + c] = tsel[MS - 1][c];
+        swap_halves(from[c], from[4 + c]);
     }
-    if (a.qe) group_qe_add(a.qe_part, qs, qs2, near);
+    {
+        float m0 = fmaxf(fmaxf(second[0][0], second[0][1]), fmaxf(second[0][2], second[0][3]));
+        float m1 = fmaxf(fmaxf(second[MS - 1][0], second[MS - 1][1]), fmaxf(second[MS - 1][2], second[MS - 1][3]));
+        swap_halves(m0, m1);
+        most = fmaxf(m0, m1);
+    }
+    // winner and runner-up (equal scores are a near tie, decided elsewhere: any of them)
+    float r_best = won[0], r_second = -INFINITY;
+#pragma unroll
+    for (int q = 1; q < 7; q += 2) {
+        const float mid = __builtin_amdgcn_fmed3f(r_best, won[q], won[q + 1]);
+        r_best = fmaxf(fmaxf(r_best, won[q]), won[q + 1]);
+        r_second = fmaxf(r_second, mid);
+    }
+    r_second = fmaxf(fmaxf(r_second, fminf(r_best, won[7])), most);
+    r_best = fmaxf(r_best, won[7]);
+    // node of a score that won place q in stage st
+    auto node_of = [](float v, int st, int q) {
+        const unsigned pos = __float_as_uint(v) & 15u;
+        return st * kNodesPerStage + (int)(((pos & 8u) << 3) + ((pos & 6u) << 2) + ((pos & 1u) << 1)) + 32 * ((q >> 1) & 1) + (q & 1) + 4 * (q >> 2);
+    };
+    int r_stage = from[0], r_place = 0;
+#pragma unroll
+    for (int q = 1; q < 8; ++q) {
+        r_stage = won[q] == r_best ? from[q] : r_stage;
+        r_place = won[q] == r_best ? 32 * ((q >> 1) & 1) + (q & 1) + 4 * (q >> 2) : r_place;
+    }
+    int r_node = node_of(r_best, r_stage, 0) + r_place;
+    r_node = (r_node >= 0 && r_node < a.K) ? r_node : a.K - 1;            // (only padding or non-finite scores get here)
+    const int64_t i = wave0 + (MS > 1 ? lane : j);
+    const bool r_valid = i < a.m && (MS > 1 || g == 0);
+    // the sample's figures from the start of the tile, and the winner's squared norm from the stage blob
+    const int own = MS > 1 ? g : 0;
+    const float xl2 = stash[(3 * own + 0) * kThreads], err_w = stash[(3 * own + 1) * kThreads], err_0 = stash[(3 * own + 2) * kThreads];
+    const char* blob = reinterpret_cast<const char*>(a.stage16) + (size_t)(r_node / kNodesPerStage) * STAGE_F4 * 16;
+    const float wn = -2.0f * reinterpret_cast<const float*>(blob + (size_t)kNodesPerStage * RS)[r_node % kNodesPerStage];
+    // The winner's score errs by its own norm's bound.  A node that is in truth as near as the winner lies within the
+    // winner's distance of the sample, so its norm is at most |x| + |x - w_b| (and at most the largest); no other node
+    // can spoil the decision.  The position bits change a score by at most 2^-19 of itself, and a rival's score is
+    // within the bound of the best one.
+    const float wb = fminf(root(wn) * 1.00001f, wmax);
+    const float err_b = err_w * wb + err_0 + 0.5f * kErrNorm * wb * wb;
+    const float bits = fabsf(r_best) * (1.01f * 3.8146973e-06f);
+    const float far2 = fmaxf(xl2 * xl2 * 1.00001f - 2.0f * r_best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
+    const float wo = fminf((xl2 + root(far2)) * 1.0001f, wmax);
+    const float bound = err_b + err_w * wo + err_0 + 0.5f * kErrNorm * wo * wo + bits;
+    const bool close = r_valid && a.K > 1 && !((r_best - r_second) > bound);
+    // Candidates: the class winners that reach the cut, four at most; complete when no class's runner-up reaches it.  Otherwise
+    // (or with 16-bit ids not enough) the sample goes on the list of the candidate pass.
+    const float cut_at = r_best - bound;
+    bool open = !(most < cut_at) || a.K > kPairNodes;
+    if (__ballot(close) != 0ull) {
+        unsigned int p0 = 0xffffffffu, p1 = 0xffffffffu;         // four places, the used ones in front
+        int hits = 0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const bool hit = won[q] >= cut_at;
+            const unsigned id = (unsigned)node_of(won[q], from[q], q);
+            p1 = hit ? (p1 << 16) | (p0 >> 16) : p1;
+            p0 = hit ? (p0 << 16) | id : p0;
+            hits += hit ? 1 : 0;
+        }
+        open = open || hits > 4;
+        if (close && !open) *reinterpret_cast<uint2*>(a.pairs + 2 * i) = make_uint2(p0, p1);
+    }
+    int near = 0;
+    if (r_valid) {
+        if (a.qe) {
+            // The statistic n_recheck counts the near ties: best two scores inside a band of fixed relative width, 3 * 2^-18 for
+            // the cut and all MFMAs at the full magnitude.  Only those that this sample's own bound leaves open are listed.
+            constexpr float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(49 * KB + (TAIL ? 17 : 0) + 1) * 5.9604645e-08f + 1.9073486e-06f) +
+                                  12.0f * 5.9604645e-08f;
+            const float band = 0.5f * rel * ((xl2 * wb + 0.5f * wb * wb) + (xl2 * wmax + 0.5f * wmax2));
+            near = (close || (a.K > 1 && !((r_best - r_second) > band))) ? 1 : 0;
+        }
+        a.bmu[i] = r_node;
+        a.cut_all[i] = !close ? kNotListed : open ? list_cut(cut_at) : kPairs;
+    }
+    if (a.qe) group_qe_add(a.qe_part, 0.0, 0.0, near);
 }
 
 // full tiles for the workgroups below a.full_tiles, half tiles for the last partial round (as bmu_kernel)
@@ -1502,8 +1439,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
     const unsigned int full = count <= kCandHalfTiles ? 0u : count / per_tile / round * round;
     const unsigned int halves = (count - full * per_tile + per_tile / 2 - 1) / (per_tile / 2);
     for (unsigned int t = blockIdx.x; t < full + halves; t += gridDim.x) {
-        if (t < full) bmu_split_tile<KB, TAIL, MS, true>(a, 0, t, count, lds4);
-        else bmu_split_tile<KB, TAIL, MS / 2, true>(a, (int64_t)full * per_tile, t - full, count, lds4);
+        BmuArgs b = a;                     // (nothing derived from these is carried from tile to tile: registers)
+        asm volatile("" : "+s"(b.centre), "+s"(b.D), "+s"(b.tail_r), "+s"(b.K));
+        if (t < full) bmu_split_tile<KB, TAIL, MS, true>(b, 0, t, count, lds4);
+        else bmu_split_tile<KB, TAIL, MS / 2, true>(b, (int64_t)full * per_tile, t - full, count, lds4);
     }
 }
 
@@ -1890,7 +1829,7 @@ constexpr int kPairGroup = 16;                // entries of a wavefront's round
 // float4 of LDS that a wavefront's entries take: three rows (an odd number each, so that the lanes' 16-byte reads fall into distinct banks) and their ids
 __host__ __device__ constexpr int pair_lds_f4(int D) { return kPairGroup * (3 * (((D + 3) / 4) | 1) + 1); }
 
-__device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__ lds, double& qs, double& qs2)
+__device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__ lds)
 {
     constexpr int PER = kPairGroup / 4;                            // entries per sixteen lanes
     const unsigned int count = a.scal[a.slot + 1];
@@ -2023,14 +1962,7 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
             bd = od;
             bk = ok;
         }
-        if (mine && c == 0 && bk < a.K) {
-            a.bmu[my.z] = bk;
-            if (a.d2) a.d2[my.z] = bd;
-            if (a.qe) {
-                qs += sqrt((double)bd);
-                qs2 += (double)bd;
-            }
-        }
+        if (mine && c == 0 && bk < a.K) a.bmu[my.z] = bk;
         if (last) break;
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
@@ -2067,8 +1999,12 @@ __global__ void __launch_bounds__(kExactThreads) bmu_exact_kernel(const BmuArgs 
         a.scal[27 - a.slot] = 0u;
         a.scal[9 - a.slot2] = 0u;
     }
+    if (PAIRS && a.tops && blockIdx.x == 0 && tid < 3) {   // the search has read its maxima: kept for later passes, zero again for the next preparation
+        a.tops[4 + tid] = a.tops[tid];
+        a.tops[tid] = 0u;
+    }
     double qs = 0.0, qs2 = 0.0;
-    if constexpr (PAIRS) pair_list(a, lds4, qs, qs2);
+    if constexpr (PAIRS) pair_list(a, lds4);
     for (unsigned int g0 = blockIdx.x * kExactGroup; g0 < count; g0 += gridDim.x * kExactGroup) {
         float bestd[kExactGroup];
         int bestk[kExactGroup];
@@ -2191,6 +2127,79 @@ __global__ void __launch_bounds__(kExactThreads) bmu_exact_kernel(const BmuArgs 
     if (a.qe) group_qe_add(a.qe_part, qs, qs2);
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// Distances to the winners, where they are asked for, for rows of up to 4 LPR <= 64 features: direct differences on the values
+// as given.  Bound by memory: a wavefront takes 64 consecutive samples, LPR lanes a row (16 bytes each, and the winner's row
+// from L2), up to eight rows of each group in flight; lane `sub` of a group keeps the sum of its sub-th sample, so units, row
+// numbers, distances and the square roots are one coalesced access, or one instruction, per 64 samples.
+// 900,000 listed rows of 25 features 30 us, 250,000 x 37 12 us.  (At the end of the search's tiles, where the rows were read again
+// before, it took 28 and 6 us of the search, and for samples near their node values that the centrings had rounded.)
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kDistThreads = 256;
+
+template <int LPR>
+__global__ void __launch_bounds__(kDistThreads) bmu_distance_kernel(const BmuArgs a)
+{
+    constexpr int U = LPR < 8 ? LPR : 8;
+    const int lane = threadIdx.x & 63, sub = lane & (LPR - 1), group = lane & ~(LPR - 1);
+    const int start = 4 * sub < a.D - 4 ? 4 * sub : a.D - 4, shift = 4 * sub - start;      // own elements of the window: >= shift
+    const int64_t units = (a.m + 63) / 64, step = (int64_t)gridDim.x * (kDistThreads / 64);
+    double qs = 0.0, qs2 = 0.0;
+    auto sample = [&](int64_t unit) {
+        const int64_t i = unit * 64 + lane;
+        return i < a.m ? i : a.m - 1;
+    };
+    int64_t unit = (int64_t)blockIdx.x * (kDistThreads / 64) + (threadIdx.x >> 6);
+    int node = 0;
+    uint32_t row = 0;
+    if (unit < units) {
+        const int64_t i = sample(unit);
+        node = a.bmu[i];
+        row = a.idx ? a.idx[i] : (uint32_t)i;
+    }
+    for (; unit < units; unit += step) {
+        const int64_t next = sample(unit + step < units ? unit + step : unit);
+        const int node_next = a.bmu[next];
+        const uint32_t row_next = a.idx ? a.idx[next] : (uint32_t)next;
+        node = (node >= 0 && node < a.K) ? node : 0;
+        float mine = 0.0f;
+#pragma unroll
+        for (int b = 0; b < LPR; b += U) {
+            float4 x[U], w[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t r = __shfl(row, group + b + u);
+                const int k = __shfl(node, group + b + u);
+                x[u] = load4(a.X + (int64_t)r * a.ldx + start);
+                w[u] = load4(a.W + (size_t)k * a.D + start);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float d0 = shift <= 0 ? x[u].x - w[u].x : 0.0f, d1 = shift <= 1 ? x[u].y - w[u].y : 0.0f;
+                const float d2 = shift <= 2 ? x[u].z - w[u].z : 0.0f, d3 = shift <= 3 ? x[u].w - w[u].w : 0.0f;
+                float d = d0 * d0;
+                d = fmaf(d1, d1, d);
+                d = fmaf(d2, d2, d);
+                d = fmaf(d3, d3, d);
+#pragma unroll
+                for (int o = LPR / 2; o > 0; o >>= 1) d += __shfl_xor(d, o);
+                mine = sub == b + u ? d : mine;
+            }
+        }
+        const int64_t i = unit * 64 + lane;
+        if (i < a.m) {
+            if (a.d2) a.d2[i] = mine;
+            if (a.qe) {
+                qs += sqrt((double)mine);
+                qs2 += (double)mine;
+            }
+        }
+        node = node_next;
+        row = row_next;
+    }
+    if (a.qe) group_qe_add(a.qe_part, qs, qs2);
+}
+
 // qe[0..1] += the call's partial sums, scal[3] += its near ties; the slots are left zero for the next call
 __global__ void __launch_bounds__(kQeSlots) qe_finish_kernel(double* __restrict__ part, double* __restrict__ qe,
                                                              unsigned int* __restrict__ scal)
@@ -2282,8 +2291,7 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     // (D > 64: rows in the order of som_bmu_wide.hip)
     const size_t stage16_one = (split && nch == 1) ? (size_t)split_stage_f4(kb, tail_r > 0) * 16 : 0;
     const size_t stage16_bytes = !split ? 0 : nch == 1 ? (size_t)(kpad / kNodesPerStage) * stage16_one : bmu_wide_blob_bytes(K, D);
-    const size_t wwin_bytes = (split && nch == 1) ? (size_t)kpad * (kb * 16 + (tail_r ? 16 : 0)) * sizeof(float) : 0;
-    const size_t need = stage_bytes + wt_bytes + centre_bytes + stage16_bytes + wwin_bytes + 256;
+    const size_t need = stage_bytes + wt_bytes + centre_bytes + stage16_bytes + 256;
     if (need > ctx->prep_bytes) {
         if (ctx->prep_blob) {
             if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync before workspace growth")) return rc;
@@ -2306,7 +2314,6 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     out->centre = (float*)(base + 256 + stage_bytes + wt_bytes);
     out->stage16 = split ? (void*)(base + 256 + stage_bytes + wt_bytes + centre_bytes) : nullptr;
     out->tail_r = tail_r;
-    out->wwin = wwin_bytes ? (float*)(base + 256 + stage_bytes + wt_bytes + centre_bytes + stage16_bytes) : nullptr;
     out->kb = kb;
     out->kpad = kpad;
     out->steps = steps;
@@ -2314,13 +2321,12 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     out->nch = nch;
     out->calls = 0;
     if (split && nch == 1) {
-        // (after a new allocation, or a call that failed between here and its list kernel)
+        // (after a new allocation, or a call that failed between here and its last kernel)
         if (!ctx->prep_clean)
             if (int rc = launch_fill_zero(ctx, out->tops, 64)) return rc;
         ctx->prep_clean = false;
         SplitPrep sp{};
         sp.stage16 = (char*)out->stage16;
-        sp.wwin = out->wwin;
         sp.kb_count = kb;
         sp.tail_r = tail_r;
         sp.row_bytes = split_row_bytes(kb, tail_r > 0);
@@ -2573,6 +2579,19 @@ static int dispatch_bmu(som_ctx* ctx, int steps, const BmuArgs& a)
     return fail(ctx, SOM_EINVAL, "no BMU kernel for %d steps", steps);
 }
 
+static int launch_bmu_distances(som_ctx* ctx, const BmuArgs& a)
+{
+    const int64_t groups = (a.m + kDistThreads - 1) / kDistThreads;
+    const dim3 grid((unsigned)(groups < 2048 ? groups : 2048)), block(kDistThreads);
+    if (a.D <= 16)
+        hipLaunchKernelGGL(bmu_distance_kernel<4>, grid, block, 0, ctx->stream, a);
+    else if (a.D <= 32)
+        hipLaunchKernelGGL(bmu_distance_kernel<8>, grid, block, 0, ctx->stream, a);
+    else
+        hipLaunchKernelGGL(bmu_distance_kernel<16>, grid, block, 0, ctx->stream, a);
+    return check_hip(ctx, hipGetLastError(), "bmu distance launch");
+}
+
 static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a);
 
 // The rows go through in passes of at most 2^27: the re-decision workspace then stays at 2.7 GB (20 bytes a row; the float32
@@ -2629,7 +2648,6 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     a.stage = prep.stage;
     a.stride = prep.stride;
     a.stage16 = prep.stage16;
-    a.wwin = prep.wwin;
     a.tail_r = prep.tail_r;
     a.wt = prep.wt;
     a.centre = prep.centre;
@@ -2719,7 +2737,6 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
         const int64_t chunks = (a.m + kListThreads * kListPerThread - 1) / (kListThreads * kListPerThread);
         hipLaunchKernelGGL(bmu_list_kernel, dim3((unsigned)(chunks < 1024 ? chunks : 1024)), dim3(kListThreads), 0, ctx->stream, a);
         if ((rc = check_hip(ctx, hipGetLastError(), "bmu list launch"))) return rc;
-        if (a.tops) ctx->prep_clean = true;
     }
     if (stop) (void)hipEventRecord(stop, ctx->stream);
     if (cand_possible) {
@@ -2751,12 +2768,18 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
             }
             // (rows of D features; two workgroups fit a compute unit up to D = 52)
             const size_t rows = (size_t)(kExactThreads / 64) * pair_lds_f4(a.D) * 16, lds = rows > kExactLds ? rows : kExactLds;
-            hipLaunchKernelGGL(bmu_exact_kernel<true>, dim3(1024), dim3(kExactThreads), lds, ctx->stream, a);
+            BmuArgs b = a;                       // the distances come afterwards, for all samples
+            b.d2 = nullptr;
+            b.qe = nullptr;
+            hipLaunchKernelGGL(bmu_exact_kernel<true>, dim3(1024), dim3(kExactThreads), lds, ctx->stream, b);
         }
         else
             hipLaunchKernelGGL(bmu_exact_kernel<false>, dim3(1024), dim3(kExactThreads), kExactLds, ctx->stream, a);
         if ((rc = check_hip(ctx, hipGetLastError(), "bmu exact-pass launch"))) return rc;
+        if (a.tops) ctx->prep_clean = true;
     }
+    if (prep.stage16 && (a.d2 || a.qe))
+        if ((rc = launch_bmu_distances(ctx, a))) return rc;
     if (a.qe) {
         hipLaunchKernelGGL(qe_finish_kernel, dim3(1), dim3(kQeSlots), 0, ctx->stream, a.qe_part, a.qe, a.scal);
         rc = check_hip(ctx, hipGetLastError(), "quantisation-error reduction launch");

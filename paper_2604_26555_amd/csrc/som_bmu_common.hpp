@@ -113,40 +113,93 @@ __device__ __forceinline__ float vmax3(float a, float b, float c)
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+
+// Two floats and their two bf16 parts: one conversion per pair and part (element by element the compiler takes three), a shift or a
+// mask back to float, exact differences.
+struct SplitPair {
+    uint32_t hi, lo;
+    float left0, left1;
+
+    __device__ __forceinline__ SplitPair(float v0, float v1)
+    {
+        hi = pack(v0, v1);
+        left0 = v0 - first(hi);
+        left1 = v1 - second(hi);
+        lo = pack(left0, left1);
+    }
+    static __device__ __forceinline__ uint32_t pack(float v0, float v1)
+    {
+        const floatx2 v = {v0, v1};
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+    }
+    static __device__ __forceinline__ float first(uint32_t p) { return __uint_as_float(p << 16); }
+    static __device__ __forceinline__ float second(uint32_t p) { return __uint_as_float(p & 0xffff0000u); }
+    // sum + the squares of what both parts leave over
+    __device__ __forceinline__ float rest2(float sum) const
+    {
+        const float r0 = left0 - first(lo), r1 = left1 - second(lo);
+        return fmaf(r1, r1, fmaf(r0, r0, sum));
+    }
+};
+
+// sum + the squares of a pair of parts (v_dot2c_f32_bf16: for norms that enter bounds with a factor to spare)
+__device__ __forceinline__ float square2(uint32_t p, float sum)
+{
+    const bf16x2 v = __builtin_bit_cast(bf16x2, p);
+    return __builtin_amdgcn_fdot2_f32_bf16(v, v, sum, false);
+}
 
 __device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo)
 {
+    uint4 h, l;
+    uint32_t* hp = &h.x;
+    uint32_t* lp = &l.x;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        hi[i] = (__bf16)v[i];
-        lo[i] = (__bf16)(v[i] - (float)hi[i]);
+    for (int i = 0; i < 4; ++i) {
+        const SplitPair p(v[2 * i], v[2 * i + 1]);
+        hp[i] = p.hi;
+        lp[i] = p.lo;
     }
+    hi = __builtin_bit_cast(bf16x8, h);
+    lo = __builtin_bit_cast(bf16x8, l);
 }
 
 // the same, and what the first parts leave over is added to left2 (squares)
 __device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo, float& left2)
 {
+    uint4 h, l;
+    uint32_t* hp = &h.x;
+    uint32_t* lp = &l.x;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        hi[i] = (__bf16)v[i];
-        const float left = v[i] - (float)hi[i];
-        lo[i] = (__bf16)left;
-        left2 = fmaf(left, left, left2);
+    for (int i = 0; i < 4; ++i) {
+        const SplitPair p(v[2 * i], v[2 * i + 1]);
+        hp[i] = p.hi;
+        lp[i] = p.lo;
+        left2 = fmaf(p.left1, p.left1, fmaf(p.left0, p.left0, left2));
     }
+    hi = __builtin_bit_cast(bf16x8, h);
+    lo = __builtin_bit_cast(bf16x8, l);
 }
 
-// the same, and what both parts leave over is added to rest2 (both differences are exact)
-__device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo, float& left2, float& rest2)
+// the same with the squares of the first parts, of the second parts and of what both leave over
+__device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo, float& hi2, float& lo2, float& rest2)
 {
+    uint4 h, l;
+    uint32_t* hp = &h.x;
+    uint32_t* lp = &l.x;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        hi[i] = (__bf16)v[i];
-        const float left = v[i] - (float)hi[i];
-        lo[i] = (__bf16)left;
-        left2 = fmaf(left, left, left2);
-        const float rest = left - (float)lo[i];
-        rest2 = fmaf(rest, rest, rest2);
+    for (int i = 0; i < 4; ++i) {
+        const SplitPair p(v[2 * i], v[2 * i + 1]);
+        hp[i] = p.hi;
+        lp[i] = p.lo;
+        hi2 = square2(p.hi, hi2);
+        lo2 = square2(p.lo, lo2);
+        rest2 = p.rest2(rest2);
     }
+    hi = __builtin_bit_cast(bf16x8, h);
+    lo = __builtin_bit_cast(bf16x8, l);
 }
 
 } // namespace som

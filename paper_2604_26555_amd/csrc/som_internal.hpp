@@ -17,7 +17,6 @@ constexpr int kMaxStepsResident = 32; // BMU kernel keeps a sample's features in
 struct BmuPrep {
     float* stage = nullptr;        // [Kpad / 128][nch] blobs: 128 padded weight rows of a chunk, then -|w|^2 / 2
     void* stage16 = nullptr;       // bf16 hi/lo parts of the weights for the split search (D <= 64: stage rows; D > 64: som_bmu_wide.hip), else null
-    float* wwin = nullptr;         // [Kpad][kb][2][8] the same slots as stage16 in float32 (centred, zeros off-window)
     int kb = 0;                    // whole 16-feature blocks of a stage16 row
     int tail_r = 0;                // features of the packed tail block behind them (0: none; D <= 64 only)
     float* wt = nullptr;           // [D][Kpad] transposed weights (as given, not centred)
@@ -27,7 +26,7 @@ struct BmuPrep {
     // [12], [13] = length of the list and of the pair list, [14], [15] the next call's, [8], [9] = bits of max_k |w - hi|^2 and |w - hi - lo|^2 (bf16 parts)
     unsigned int* scal = nullptr;
     // Split search for D <= 64: the three maxima above are found by atomics in [0..2], which are zero whenever no call is in
-    // progress; the first pass's list kernel moves them to [4..6], where later passes read them.  (What a call leaves behind
+    // progress; the first pass moves them to [4..6], where later passes read them.  (What a call leaves behind
     // does not depend on which call it is, so a captured call can be replayed.)
     unsigned int* tops = nullptr;
     int kpad = 0, steps = 0, stride = 0;
@@ -45,7 +44,6 @@ struct BmuArgs {
     const float* stage;      // BmuPrep::stage
     int32_t stride;          // BmuPrep::stride (floats per row of the float32 stage)
     const void* stage16;     // BmuPrep::stage16 (null: float32 search)
-    const float* wwin;       // BmuPrep::wwin
     int32_t tail_r;          // BmuPrep::tail_r
     int32_t second_only;     // bmu_exact_kernel: serve the second list whatever the first one's length
     const float* wt;         // BmuPrep::wt
