@@ -39,8 +39,10 @@ namespace som {
 constexpr int kWavesPerGroup = 4;
 constexpr int kThreads = kWavesPerGroup * 64;
 
-constexpr uint32_t kCandMin = 8192;             // shortest list the candidate pass serves: its tiles take about 40 us however few they are, the all-nodes
-                                                // pass about 3.5 ns a sample (both at K D = 51200), and up to here that is one sweep of its grid
+constexpr uint32_t kCandMin = 4096;             // shortest list the candidate pass serves: its tiles take 15 to 30 us however few they are, the all-nodes
+                                                // pass about 3.5 ns a sample (at K D = 51200); 6,000 entries on 400 nodes x 64: 18 + 13 us with it,
+                                                // 5 + 55 without
+constexpr uint32_t kCandMinFloat = 8192;        // the same of the float32 searches, whose tiles take about 40 us
 constexpr uint32_t kCandHalfTiles = 65536;      // up to this length its tiles are halved (one per compute unit and more)
 constexpr size_t kCandCapMax = (size_t)1 << 24; // longest one (bounds the candidate buffer at 512 MB + 64 MB)
 constexpr int kCandGrid = 2048;
@@ -172,7 +174,7 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
 //     instead would be one or two columns of a lattice whose side divides that stride, off the middle: 10^6 x 50 on 64 x 64
 //     nodes took 2.29 ms an epoch with those and takes 2.05 with these (shorter lists of near ties), on 32 x 32 0.452 and 0.448.
 //   * Stage rows (layout at bmu_split_tile) are put together in LDS and leave it as whole lines, as do the sixteen nodes'
-//     columns of the transposed copy.
+//     columns of the transposed copy; a plain copy of the rows in the stages' order serves the pair list.
 //   * Packed tail (tail_r > 0): the last tail_r <= 4 features do not get a 16-feature block of their own (three MFMAs for a
 //     block that is mostly padding) but one packed block whose sixteen slots hold the three products side by side,
 //         weights  [ hi(r) | hi(r) | lo(r) | norm parts (3) | 0 ... ]   against samples  [ hi(r) | lo(r) | hi(r) | 1 1 1 | 0 ... ],
@@ -181,11 +183,37 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
 //     and of what the bf16 cut leaves over (w - hi, w - hi - lo) in scal.
 // The result words of this call were cleared by the call before; this one clears the next one's (scal_next).
 // ---------------------------------------------------------------------------------------------------------
+// Which node a row of the stages holds.  The search keeps its winners by class of rows (bits 0, 2 and 5 of the row: bmu_split_tile), and
+// a near tie within one class costs a pass of its own, so nodes that come close should fall into different classes: the rows of a
+// whole stage of 128 are ordered such that those three bits are a remainder of the node's number: its bits as a polynomial over
+// two elements, modulo x^3 + x^2 + 1 (bit i adds kClassOf[i % 7]).  Two nodes next to each other on a lattice, whatever its width
+// from 8 to 64, then share a class in 5 % of the cases on average and 11 % at worst (in a diagonal 14 and 24, two columns or rows
+// on 5 and 10); with nodes in their own order 6 and 50 (11 and 75, 38 and 77).  Samples left to the candidate pass, 10^6 x 50 on
+// 64 x 64 nodes: 254,000 then, 79,000 now; on 32 x 32 36,000 and 23,000; on 20 x 20 (500,000 x 64) 1,500 and 6,000.
+constexpr unsigned class_mask(int bit)                    // the bits of a node's number, from bit 3 on, that flip this bit of its class
+{
+    constexpr unsigned kClassOf[7] = {1, 2, 4, 5, 7, 3, 6};
+    unsigned m = 0u;
+    for (int i = 3; i < 32; ++i) m |= ((kClassOf[i % 7] >> bit) & 1u) << i;
+    return m;
+}
+__host__ __device__ __forceinline__ int node_of_row(int row, int K)
+{
+    if ((row | (kNodesPerStage - 1)) >= K) return row;                       // (a stage with padding rows keeps its order)
+    static_assert(kNodesPerStage == 128, "seven bits");
+    constexpr unsigned m0 = class_mask(0), m1 = class_mask(1), m2 = class_mask(2);
+    const unsigned s = (unsigned)row;
+    const unsigned high = (s & ~127u) | (s & 64u) | ((s & 24u) << 1) | ((s & 2u) << 2);      // bits 3 and up of the node
+    const unsigned f = (__builtin_popcount(high & m0) & 1) | (__builtin_popcount(high & m1) & 1) << 1 | (__builtin_popcount(high & m2) & 1) << 2;
+    return (int)(high | (((s & 1u) | ((s & 4u) >> 1) | ((s & 32u) >> 3)) ^ f));
+}
+
 constexpr int kCentreNodes = 64;
 constexpr int kPrepNodes = 16;           // nodes (wavefronts) of a workgroup: 64 bytes of a row of the transposed copy
 
 struct SplitPrep {
     char* stage16;
+    float* wrow;
     int kb_count, tail_r, row_bytes, stage16_bytes;
 };
 
@@ -210,14 +238,14 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
     __shared__ uint4 rows16[kPrepNodes * 272 / 16];           // [node][row_bytes]
     __shared__ float most[kPrepNodes][3];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int k0 = blockIdx.x * kPrepNodes, k = k0 + wave;
+    const int k0 = blockIdx.x * kPrepNodes, k = k0 + wave;           // rows of the stages (and of the transposed copy)
     if (blockIdx.x == 0) {
         if (tid < 16) scal[tid] = 0u;
         if (tid < 2 && qe) qe[tid] = 0.0;
         if (tid < 4 && small) small[tid] = 0;
     }
     const bool real = k < K && lane < D;
-    const float w = real ? W[(size_t)k * D + lane] : 0.0f;
+    const float w = real ? W[(size_t)node_of_row(k, K) * D + lane] : 0.0f;
     const int count = K < kCentreNodes ? K : kCentreNodes;
     float v4[kCentreNodes / kPrepNodes];
 #pragma unroll
@@ -293,6 +321,7 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
     for (int e = tid; e < kPrepNodes * sp.row_bytes / 16; e += 64 * kPrepNodes) to[e] = rows16[e];
     const int f = tid >> 4, q = tid & 15;
     if (f < D) wt[(size_t)f * kpad + k0 + q] = given[q][f];
+    if (real) sp.wrow[(size_t)k * D + lane] = w;
     if (tid < 3) {
         float m = most[0][tid];
         for (int u = 1; u < kPrepNodes; ++u) m = fmaxf(m, most[u][tid]);
@@ -774,6 +803,28 @@ constexpr int kSplitMinNodes = 1;              // SOM_SEARCH_AUTO: every map of 
                                                // float32 search from 2 x 2 nodes and from D = 4 on)
 constexpr int kSplitMS = 2;
 
+// The candidate pass: what a wavefront keeps in LDS behind the stages.  A lane whose scores of a block reach its sample's cut adds one
+// entry (which of its sixteen rows, the sample, the block) to the wavefront's queue; the direct differences are taken from the queue,
+// a lane an entry, so that lanes share the work whosever samples' it is, and the nearest candidate of each sample is kept as the
+// least (distance, node) in one 64-bit word.  (With up to seven ids in each lane's registers, every lane walked the longest
+// set of its wavefront, and samples with more went to the all-nodes pass.)  10^6 x 50 on
+// 64 x 64 nodes: pass and all-nodes pass 430 + 284 us then, 352 + 23 with the queue.
+struct CandQueue {
+    static constexpr size_t kFixed = 64 * (sizeof(unsigned long long) + sizeof(uint32_t));
+    unsigned long long* nearest;     // [64] per sample of the tile
+    uint32_t* row;                   // [64] its row of X
+    uint2* entry;                    // [kQueue]
+};
+constexpr int cand_queue(int kb, bool tail)            // entries; two workgroups fit a compute unit
+{
+    const size_t left = (80 * 1024 - 2 * (size_t)split_stage_f4(kb, tail) * 16) / kWavesPerGroup - CandQueue::kFixed;
+    return left / sizeof(uint2) < 512 ? (int)(left / sizeof(uint2)) / 16 * 16 : 512;
+}
+constexpr size_t cand_lds(int kb, bool tail)
+{
+    return 2 * (size_t)split_stage_f4(kb, tail) * 16 + kWavesPerGroup * (CandQueue::kFixed + (size_t)cand_queue(kb, tail) * sizeof(uint2));
+}
+
 // first feature of slot group q (four consecutive features)
 __device__ __forceinline__ int split_window(int q, int D) { return 4 * q < D - 4 ? 4 * q : D - 4; }
 
@@ -849,17 +900,31 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // the stage loop has no registers to spare for them.
     float* const stash = reinterpret_cast<float*>(lds4 + 2 * STAGE_F4) + threadIdx.x;
     float cut[MS];          // CAND
-    CandSet noted[MS];      // CAND
     unsigned int found[MS]; // CAND: hits of the block in hand
     const int64_t total = CAND ? (int64_t)count : a.m;
     SplitRows<KB, TAIL, MS, CAND> raw;
     raw.load(a, wave0, total, j, g);
+    // CAND: the wavefront's queue, its length (which may pass the end: those entries are lost, and lost remembers whose), and each
+    // sample's row
+    constexpr int QUEUE = cand_queue(KB, TAIL);
+    CandQueue cq{};
+    unsigned int queued = 0u, lost = 0u;
     if constexpr (CAND) {
+        char* at = reinterpret_cast<char*>(lds4 + 2 * STAGE_F4) + wave * (CandQueue::kFixed + QUEUE * sizeof(uint2));
+        cq.nearest = reinterpret_cast<unsigned long long*>(at);
+        cq.entry = reinterpret_cast<uint2*>(at + 64 * sizeof(unsigned long long));
+        cq.row = reinterpret_cast<uint32_t*>(at + 64 * sizeof(unsigned long long) + QUEUE * sizeof(uint2));
 #pragma unroll
         for (int mb = 0; mb < MS; ++mb) {
             const int64_t i = wave0 + mb * 32 + j;
             cut[mb] = i < total ? a.cutv[i] : NAN;       // no score compares >= NaN
+            cut[mb] = cut[mb] > -INFINITY ? cut[mb] : NAN;      // (a row without a cut: to the all-nodes pass)
             found[mb] = 0u;
+            const uint32_t is = a.recheck[i < total ? i : total - 1];
+            if (g == 0) {
+                cq.row[mb * 32 + j] = a.idx ? a.idx[is] : is;
+                cq.nearest[mb * 32 + j] = ~0ull;
+            }
         }
     }
     const int tail_r = TAIL ? a.tail_r : 0;
@@ -1021,14 +1086,15 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             found[mb] = 2u * found[mb] + (acc[mb][r0] >= cut[mb] ? 1u : 0u);
             found[mb] = 2u * found[mb] + (acc[mb][r1] >= cut[mb] ? 1u : 0u);
             if (r1 == 15) {
-                const int base = (st * (kNodesPerStage / 32) + nb) * 32 + 4 * g;
-                while (__ballot(found[mb] != 0u) != 0ull) {
+                const unsigned long long hit = __ballot(found[mb] != 0u);
+                if (hit != 0ull) {
+                    const unsigned int at = queued + __builtin_amdgcn_mbcnt_hi((unsigned)(hit >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hit, 0));
                     if (found[mb] != 0u) {
-                        const int bit = 31 - __builtin_clz(found[mb]);          // 15 - place in the order of the steps
-                        found[mb] ^= 1u << bit;
-                        const int place = 15 - bit, quad = place >> 2, r = 4 * quad + ((place >> 1) & 1) + 2 * (place & 1);
-                        noted[mb].note(base, 8 * (r >> 2) + (r & 3));
+                        if (at < (unsigned)QUEUE) cq.entry[at] = make_uint2(found[mb] | ((unsigned)(mb * 64 + lane) << 16), (unsigned)(st * (kNodesPerStage / 32) + nb));
+                        else lost |= 1u << mb;
                     }
+                    queued += (unsigned)__popcll(hit);
+                    found[mb] = 0u;
                 }
             }
             return;
@@ -1124,6 +1190,52 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         }
     };
 
+    // CAND: direct float32 differences on the values as given over the queue's candidates, features in order
+    auto serve = [&]() {
+        const unsigned int n = queued < (unsigned)QUEUE ? queued : (unsigned)QUEUE;
+        const int D = a.D, whole = D / 4, rest = D - 4 * whole;
+        __builtin_amdgcn_wave_barrier();
+        for (unsigned int e0 = 0; e0 < n; e0 += 64) {
+            const uint2 e = cq.entry[e0 + lane < n ? e0 + lane : n - 1];
+            unsigned int bits = e0 + lane < n ? e.x & 0xffffu : 0u;
+            const unsigned int whose = e.x >> 16, smp = (whose >> 6) * 32 + (whose & 31u);
+            const float* xr = a.X + (int64_t)cq.row[smp] * a.ldx;
+            const unsigned int base = e.y * 32 + 4 * ((whose >> 5) & 1u);
+            while (__ballot(bits != 0u) != 0ull) {
+                if (bits != 0u) {
+                    const int bit = 31 - __builtin_clz(bits);          // 15 - place in the order of the steps
+                    bits ^= 1u << bit;
+                    const int place = 15 - bit, r = 4 * (place >> 2) + ((place >> 1) & 1) + 2 * (place & 1);
+                    const unsigned int id = (unsigned)node_of_row((int)(base + 8 * (r >> 2) + (r & 3)), a.K);
+                    if (id < (unsigned)a.K) {
+                        const float* wr = a.W + (size_t)id * D;
+                        float d = 0.0f;
+#pragma unroll 4
+                        for (int q = 0; q < whole; ++q) {
+                            const float4 x4 = load4(xr + 4 * q), w4 = load4(wr + 4 * q);
+                            const float d0 = x4.x - w4.x, d1 = x4.y - w4.y, d2 = x4.z - w4.z, d3 = x4.w - w4.w;
+                            d = fmaf(d0, d0, d);
+                            d = fmaf(d1, d1, d);
+                            d = fmaf(d2, d2, d);
+                            d = fmaf(d3, d3, d);
+                        }
+                        if (rest > 0) {          // the window [D - 4, D): its leading elements are already counted
+                            const float4 x4 = load4(xr + D - 4), w4 = load4(wr + D - 4);
+                            const float d1 = x4.y - w4.y, d2 = x4.z - w4.z, d3 = x4.w - w4.w;
+                            if (rest > 2) d = fmaf(d1, d1, d);
+                            if (rest > 1) d = fmaf(d2, d2, d);
+                            d = fmaf(d3, d3, d);
+                        }
+                        // (no distance is negative, so their bits are in order)
+                        if (d < INFINITY) atomicMin(&cq.nearest[smp], (unsigned long long)__float_as_uint(d) << 32 | id);
+                    }
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        queued = 0u;
+    };
+
     // The first node block's operands; every later block's are read while the block before it is on the matrix pipe.
     bf16x8 wh[KBA], wl[KBA], wtl;
     floatx16 c;
@@ -1203,6 +1315,9 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         block(accA, accB, wh, wl, wtl, c, rows_of(wbuf, 3), norms_of(wbuf, 3), true, st, 1);
         __syncthreads();
         block(accB, accA, wh, wl, wtl, c, rows_of(obuf, 0), norms_of(obuf, 0), true, st, 2);
+        if constexpr (CAND) {
+            if (queued > (unsigned)QUEUE / 2) serve();
+        }
     }
     // the last block's scores
     auto fold_last = [&](const floatx16 (&acc)[MS], auto nb) {
@@ -1240,74 +1355,18 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     }
 
     if constexpr (CAND) {
-        // Direct float32 differences over the nodes this lane noted for its sample (the true winner is among the two
-        // lane halves' candidates: its score lies within the rounding bound of the best one found), features in order,
-        // lowest distance, then lowest node index; the halves are joined at the end.  An entry whose set overflowed
-        // in either half (more than seven candidates) or that noted nothing goes to the second list, which the
-        // all-nodes kernel serves.  The row stays in registers across the candidates: D <= 64.
-#pragma unroll
-        for (int mb = 0; mb < MS; ++mb) {
-            const int n = noted[mb].n;
-            const bool over = n >= kCandSlots;
-            const int64_t ie = wave0 + mb * 32 + j;
-            const bool valid = ie < total;
-            const int mine = (valid && !over) ? n : 0;
-            const int64_t is = (int64_t)a.recheck[ie < (int64_t)count ? ie : (int64_t)count - 1];
-            const float* xr = a.X + (a.idx ? (int64_t)a.idx[is] : is) * a.ldx;
-            const int D = a.D, whole = D / 4, rest = D - 4 * whole;
-            float4 xv[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) xv[q] = (mine > 0 && q < whole) ? load4(xr + 4 * q) : float4{0.f, 0.f, 0.f, 0.f};
-            // the last one to three features: the window [D - 4, D), its leading elements already counted
-            const float4 xt4 = (mine > 0 && rest > 0) ? load4(xr + D - 4) : float4{0.f, 0.f, 0.f, 0.f};
-            float bd = INFINITY;
-            int bk = 0x7fffffff;
-            for (int t = 0; t < kCandSlots - 1; ++t) {
-                if (__ballot(t < mine) == 0ull) break;
-                if (t < mine) {
-                    const unsigned long long word = t < 4 ? noted[mb].lo >> (16 * t) : noted[mb].hi >> (16 * (t - 4));
-                    const int id = (int)(word & 0xffffull);
-                    if (id < a.K) {
-                        const float* wr = a.W + (size_t)id * D;
-                        float d = 0.0f;
-#pragma unroll
-                        for (int q = 0; q < 16; ++q) {
-                            if (q < whole) {
-                                const float4 w4 = load4(wr + 4 * q);
-                                const float d0 = xv[q].x - w4.x, d1 = xv[q].y - w4.y, d2 = xv[q].z - w4.z, d3 = xv[q].w - w4.w;
-                                d = fmaf(d0, d0, d);
-                                d = fmaf(d1, d1, d);
-                                d = fmaf(d2, d2, d);
-                                d = fmaf(d3, d3, d);
-                            }
-                        }
-                        if (rest > 0) {
-                            const float4 w4 = load4(wr + D - 4);
-                            const float d1 = xt4.y - w4.y, d2 = xt4.z - w4.z, d3 = xt4.w - w4.w;
-                            if (rest > 2) d = fmaf(d1, d1, d);
-                            if (rest > 1) d = fmaf(d2, d2, d);
-                            d = fmaf(d3, d3, d);
-                        }
-                        if (d < bd || (d == bd && id < bk)) {
-                            bd = d;
-                            bk = id;
-                        }
-                    }
-                }
-            }
-            const float od = __shfl_xor(bd, 32);
-            const int ok = __shfl_xor(bk, 32);
-            const bool oover = __shfl_xor(over ? 1 : 0, 32) != 0;
-            if (od < bd || (od == bd && ok < bk)) {
-                bd = od;
-                bk = ok;
-            }
-            const bool served = !over && !oover && bk < a.K;
-            const bool writer = valid && g == 0;
-            const int64_t i = writer ? (int64_t)a.recheck[wave0 + mb * 32 + j] : 0;
-            if (writer && served) a.bmu[i] = bk;
-            list_push(&a.scal[a.slot2], a.recheck2, nullptr, writer && !served, i, 0.0f);
-        }
+        // The true winner is among a sample's candidates: its score lies within the rounding bound of the best one found.  Entries
+        // that lost some (the queue overflowed within a stage) or have none (no number, no cut) go to the second list, which the
+        // all-nodes kernel serves.
+        serve();
+        lost |= (unsigned)__shfl_xor((int)lost, 32);
+        const int64_t ie = wave0 + (MS > 1 ? lane : j);
+        const bool writer = ie < total && (MS > 1 || g == 0);
+        const unsigned long long best_key = cq.nearest[MS > 1 ? lane : j];
+        const bool served = best_key != ~0ull && ((lost >> (MS > 1 ? g : 0)) & 1u) == 0u;
+        const int64_t i = writer ? (int64_t)a.recheck[ie] : 0;
+        if (writer && served) a.bmu[i] = (int32_t)(unsigned)best_key;
+        list_push(&a.scal[a.slot2], a.recheck2, nullptr, writer && !served, i, 0.0f);
         return;
     }
     // ---- winners and bounds
@@ -1347,8 +1406,8 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     }
     r_second = fmaxf(fmaxf(r_second, fminf(r_best, won[7])), most);
     r_best = fmaxf(r_best, won[7]);
-    // node of a score that won place q in stage st
-    auto node_of = [](float v, int st, int q) {
+    // row of a score that won place q in stage st
+    auto row_of = [](float v, int st, int q) {
         const unsigned pos = __float_as_uint(v) & 15u;
         return st * kNodesPerStage + (int)(((pos & 8u) << 3) + ((pos & 6u) << 2) + ((pos & 1u) << 1)) + 32 * ((q >> 1) & 1) + (q & 1) + 4 * (q >> 2);
     };
@@ -1358,15 +1417,15 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         r_stage = won[q] == r_best ? from[q] : r_stage;
         r_place = won[q] == r_best ? 32 * ((q >> 1) & 1) + (q & 1) + 4 * (q >> 2) : r_place;
     }
-    int r_node = node_of(r_best, r_stage, 0) + r_place;
-    r_node = (r_node >= 0 && r_node < a.K) ? r_node : a.K - 1;            // (only padding or non-finite scores get here)
+    int r_row = row_of(r_best, r_stage, 0) + r_place;
+    r_row = (r_row >= 0 && r_row < a.K) ? r_row : a.K - 1;               // (only padding or non-finite scores get here)
     const int64_t i = wave0 + (MS > 1 ? lane : j);
     const bool r_valid = i < a.m && (MS > 1 || g == 0);
     // the sample's figures from the start of the tile, and the winner's squared norm from the stage blob
     const int own = MS > 1 ? g : 0;
     const float xl2 = stash[(3 * own + 0) * kThreads], err_w = stash[(3 * own + 1) * kThreads], err_0 = stash[(3 * own + 2) * kThreads];
-    const char* blob = reinterpret_cast<const char*>(a.stage16) + (size_t)(r_node / kNodesPerStage) * STAGE_F4 * 16;
-    const float wn = -2.0f * reinterpret_cast<const float*>(blob + (size_t)kNodesPerStage * RS)[r_node % kNodesPerStage];
+    const char* blob = reinterpret_cast<const char*>(a.stage16) + (size_t)(r_row / kNodesPerStage) * STAGE_F4 * 16;
+    const float wn = -2.0f * reinterpret_cast<const float*>(blob + (size_t)kNodesPerStage * RS)[r_row % kNodesPerStage];
     // The winner's score errs by its own norm's bound.  A node that is in truth as near as the winner lies within the
     // winner's distance of the sample, so its norm is at most |x| + |x - w_b| (and at most the largest); no other node
     // can spoil the decision.  The position bits change a score by at most 2^-19 of itself, and a rival's score is
@@ -1388,7 +1447,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const bool hit = won[q] >= cut_at;
-            const unsigned id = (unsigned)node_of(won[q], from[q], q);
+            const unsigned id = (unsigned)row_of(won[q], from[q], q);
             p1 = hit ? (p1 << 16) | (p0 >> 16) : p1;
             p0 = hit ? (p0 << 16) | id : p0;
             hits += hit ? 1 : 0;
@@ -1406,7 +1465,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             const float band = 0.5f * rel * ((xl2 * wb + 0.5f * wb * wb) + (xl2 * wmax + 0.5f * wmax2));
             near = (close || (a.K > 1 && !((r_best - r_second) > band))) ? 1 : 0;
         }
-        a.bmu[i] = r_node;
+        a.bmu[i] = node_of_row(r_row, a.K);
         a.cut_all[i] = !close ? kNotListed : open ? list_cut(cut_at) : kPairs;
     }
     if (a.qe) group_qe_add(a.qe_part, 0.0, 0.0, near);
@@ -1817,17 +1876,21 @@ __global__ void __launch_bounds__(256) bmu_cand_exact_kernel(const BmuArgs a)
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// The pair list: samples whose candidates (at most four, two of each lane half) the split search already knows (D <= 64).
+// The pair list: samples whose candidates (at most four) the split search already knows (D <= 64).
 // A wavefront takes sixteen entries at a time, on its own (no barrier): sixteen lanes fetch a row in one coalesced load, the
 // samples' rows and two candidates' each; the rows meet in the wavefront's part of LDS, the next entries' rows are requested,
 // and one lane per candidate adds its squared differences up, features in order as the other re-decisions do; lowest
 // distance, then lowest node index.  With a workgroup of eight wavefronts in step (barriers around fetch and sums) the
 // latency of every round was in the open: 0.17 ns an entry at D = 50, whatever the occupancy.
+// The few entries with a third or fourth candidate wait in LDS until there are sixteen of them, and then take a round of their own.
+// (Served in the round where they came, nearly every round waited for their rows: 4.0 million entries of 10^7 x 50 took 0.62 ms and
+// take 0.48; the same with more rows in flight cost registers, and with them wavefronts, for 0.55.)
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kPairGroup = 16;                // entries of a wavefront's round
 
-// float4 of LDS that a wavefront's entries take: three rows (an odd number each, so that the lanes' 16-byte reads fall into distinct banks) and their ids
-__host__ __device__ constexpr int pair_lds_f4(int D) { return kPairGroup * (3 * (((D + 3) / 4) | 1) + 1); }
+// float4 of LDS that a wavefront's entries take: three rows (an odd number each, so that the lanes' 16-byte reads fall into distinct
+// banks), their ids, and twice as many entries that wait
+__host__ __device__ constexpr int pair_lds_f4(int D) { return kPairGroup * (3 * (((D + 3) / 4) | 1) + 1 + 2); }
 
 __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__ lds)
 {
@@ -1839,11 +1902,88 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
     const int stride = ((D + 3) / 4) | 1;             // float4 of a row
     float4* const rows = lds + wave * pair_lds_f4(D);
     uint4* const info = reinterpret_cast<uint4*>(rows + kPairGroup * 3 * stride);      // [entry] ids, sample position
+    uint4* const later = info + kPairGroup;           // [2 kPairGroup] third and fourth id, sample position, nearest so far (distance, row of the stages)
+    unsigned int waiting = 0u;
     const int start = 4 * sub < D - 4 ? 4 * sub : D - 4;           // window inside the row
     const bool own = 4 * sub < D;
     const unsigned int step = gridDim.x * (kExactThreads / 64) * kPairGroup;
     const unsigned int first = (blockIdx.x * (kExactThreads / 64) + wave) * kPairGroup;
     if (first >= count) return;
+    const unsigned int k_most = (unsigned int)a.K - 1u;
+    auto row_of = [&](unsigned int id) { return load4(a.wrow + (size_t)(id < k_most ? id : k_most) * D + start); };
+    // the rows of entry e for this lane's window: the sample's and two candidates' (a single candidate's row twice)
+    auto fetch = [&](unsigned int both, uint32_t row, float4& x, float4& w0, float4& w1) {
+        const unsigned int i0 = both & 0xffffu, i1 = both >> 16;
+        x = load4(a.X + (int64_t)row * a.ldx + start);
+        w0 = row_of(i0);
+        w1 = row_of(i1 == 0xffffu ? i0 : i1);
+    };
+    auto lay = [&](int u, const float4& x, const float4& w0, const float4& w1) {
+        float4* r = rows + (4 * u + grp) * 3 * stride + sub;
+        if (own) {
+            r[0] = x;
+            r[stride] = w0;
+            r[2 * stride] = w1;
+        }
+    };
+    // this lane's candidate: entry lane / 2, place lane % 2
+    const int e = (lane >> 1) & (kPairGroup - 1), c = lane & 1;
+    float bd;
+    int bk;                                           // row of the stages
+    // (which node a row holds matters only where two are exactly as near)
+    auto nearer = [&](float d, int k) {
+        bool take = d < bd;
+        const bool tie = d == bd && d < INFINITY;
+        if (__ballot(tie) != 0ull) take = take || (tie && node_of_row(k, a.K) < node_of_row(bk, a.K));
+        bd = take ? d : bd;
+        bk = take ? k : bk;
+    };
+    auto sum = [&](unsigned int both) {
+        const unsigned int id = c == 0 ? both & 0xffffu : both >> 16;
+        const float4* rx = rows + e * 3 * stride;
+        const float4* rw = rx + (1 + c) * stride;
+        float d = 0.0f;
+#pragma unroll 4
+        for (int q = 0; q < whole; ++q) {
+            const float4 x = rx[q], w = rw[q];
+            const float d0 = x.x - w.x, d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
+            d = fmaf(d0, d0, d);
+            d = fmaf(d1, d1, d);
+            d = fmaf(d2, d2, d);
+            d = fmaf(d3, d3, d);
+        }
+        if (rest > 0) {          // the window [D - 4, D): its leading elements are already counted
+            const float4 x = rx[whole], w = rw[whole];
+            const float d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
+            if (rest > 2) d = fmaf(d1, d1, d);
+            if (rest > 1) d = fmaf(d2, d2, d);
+            d = fmaf(d3, d3, d);
+        }
+        nearer(id != 0xffffu ? d : INFINITY, (int)id);
+        nearer(__shfl_xor(bd, 1), __shfl_xor(bk, 1));
+    };
+    // up to sixteen of the entries that wait, the last ones
+    auto serve_later = [&]() {
+        const unsigned int n = waiting < (unsigned)kPairGroup ? waiting : (unsigned)kPairGroup, base = waiting - n;
+        __builtin_amdgcn_wave_barrier();
+        float4 x[PER], w[PER][2];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const unsigned int q = 4 * u + grp;
+            const uint4 l = later[base + (q < n ? q : 0u)];
+            fetch(l.x, a.idx ? a.idx[l.y] : l.y, x[u], w[u][0], w[u][1]);
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) lay(u, x[u], w[u][0], w[u][1]);
+        __builtin_amdgcn_wave_barrier();
+        const uint4 l = later[base + ((unsigned)e < n ? (unsigned)e : 0u)];
+        bd = __uint_as_float(l.z);
+        bk = (int)l.w;
+        sum(l.x);
+        if (lane < 2 * (int)n && c == 0 && bk < a.K) a.bmu[l.y] = node_of_row(bk, a.K);
+        waiting = base;
+        __builtin_amdgcn_wave_barrier();
+    };
     // The chain list entry -> ids and row number -> rows is three dependent trips to memory: sample positions are read two
     // rounds ahead, ids and row numbers one, rows while the round before is summed.
     auto position = [&](unsigned int p, int u) {
@@ -1851,21 +1991,9 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
         return a.recheck_end[-1 - (int64_t)(q < count ? q : count - 1)];
     };
     auto after = [&](unsigned int p) { return count - p > step ? p + step : p; };     // (the last round's again at the end)
-    const unsigned int k_most = (unsigned int)a.K - 1u;
-    auto row_of = [&](unsigned int id) { return load4(a.W + (size_t)(id < k_most ? id : k_most) * D + start); };
     uint32_t at[PER], at_next[PER];
     uint2 ids[PER];
     float4 x4[PER], w4[PER][2];
-    auto request = [&](const uint2 (&c)[PER], const uint32_t (&row)[PER]) {
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            x4[u] = load4(a.X + (int64_t)row[u] * a.ldx + start);
-            // (a single candidate's row twice)
-            const unsigned int i0 = c[u].x & 0xffffu, i1 = c[u].x >> 16;
-            w4[u][0] = row_of(i0);
-            w4[u][1] = row_of(i1 == 0xffffu ? i0 : i1);
-        }
-    };
     {
         uint32_t row[PER];
 #pragma unroll
@@ -1878,7 +2006,8 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
             ids[u] = *reinterpret_cast<const uint2*>(a.pairs + 2 * (int64_t)at[u]);
             row[u] = a.idx ? a.idx[at[u]] : at[u];
         }
-        request(ids, row);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) fetch(ids[u].x, row[u], x4[u], w4[u][0], w4[u][1]);
     }
     for (unsigned int p0 = first;; p0 += step) {
         uint2 ids_next[PER];
@@ -1891,78 +2020,31 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
             at_after[u] = position(p2, u);
         }
         // this round's rows to LDS, the next one's on their way
-        if (own) {
-#pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                float4* r = rows + (4 * u + grp) * 3 * stride + sub;
-                r[0] = x4[u];
-                r[stride] = w4[u][0];
-                r[2 * stride] = w4[u][1];
-            }
-        }
-        unsigned int third = 0xffffffffu;
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
+            lay(u, x4[u], w4[u][0], w4[u][1]);
             if (sub == 0) info[4 * u + grp] = make_uint4(ids[u].x, ids[u].y, at[u], 0u);
-            third &= ids[u].y;
         }
         __builtin_amdgcn_wave_barrier();
         const bool last = count - p0 <= step;
-        const bool second_round = __ballot(third != 0xffffffffu) != 0ull;
-        if (!last) request(ids_next, row_next);
-        // this lane's candidate: entry lane / 2, place lane % 2 (and + 2 in the rare second round)
-        const int e = (lane >> 1) & (kPairGroup - 1), c = lane & 1;
+        if (!last)
+#pragma unroll
+            for (int u = 0; u < PER; ++u) fetch(ids_next[u].x, row_next[u], x4[u], w4[u][0], w4[u][1]);
         const uint4 my = info[e];
-        const bool mine = lane < 2 * kPairGroup && p0 + e < count;
-        float bd = INFINITY;
-        int bk = 0x7fffffff;
-        auto sum = [&](unsigned int both) {
-            const unsigned int id = c == 0 ? both & 0xffffu : both >> 16;
-            const float4* rx = rows + e * 3 * stride;
-            const float4* rw = rx + (1 + c) * stride;
-            float d = 0.0f;
-#pragma unroll 4
-            for (int q = 0; q < whole; ++q) {
-                const float4 x = rx[q], w = rw[q];
-                const float d0 = x.x - w.x, d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
-                d = fmaf(d0, d0, d);
-                d = fmaf(d1, d1, d);
-                d = fmaf(d2, d2, d);
-                d = fmaf(d3, d3, d);
-            }
-            if (rest > 0) {          // the window [D - 4, D): its leading elements are already counted
-                const float4 x = rx[whole], w = rw[whole];
-                const float d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
-                if (rest > 2) d = fmaf(d1, d1, d);
-                if (rest > 1) d = fmaf(d2, d2, d);
-                d = fmaf(d3, d3, d);
-            }
-            if (id != 0xffffu && (d < bd || (d == bd && (int)id < bk))) {
-                bd = d;
-                bk = (int)id;
-            }
-        };
+        const bool mine = lane < 2 * kPairGroup && p0 + e < count && c == 0;
+        bd = INFINITY;
+        bk = 0x7fffffff;
         sum(my.x);
-        if (second_round) {
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int u = 0; u < PER; ++u)
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const unsigned int id = q == 0 ? ids[u].y & 0xffffu : ids[u].y >> 16;
-                    if (own && id != 0xffffu) rows[((4 * u + grp) * 3 + 1 + q) * stride + sub] = row_of(id);
-                }
-            __builtin_amdgcn_wave_barrier();
-            sum(my.y);
+        const bool more = mine && my.y != 0xffffffffu;
+        if (mine && !more && bk < a.K) a.bmu[my.z] = node_of_row(bk, a.K);
+        const unsigned long long wait = __ballot(more);
+        if (wait != 0ull) {
+            const unsigned int to = waiting + __builtin_amdgcn_mbcnt_hi((unsigned)(wait >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)wait, 0));
+            if (more) later[to] = make_uint4(my.y, my.z, __float_as_uint(bd), (unsigned)bk);
+            waiting += (unsigned)__popcll(wait);
+            if (waiting >= (unsigned)kPairGroup) serve_later();
         }
         __builtin_amdgcn_wave_barrier();
-        const float od = __shfl_xor(bd, 1);
-        const int ok = __shfl_xor(bk, 1);
-        if (od < bd || (od == bd && ok < bk)) {
-            bd = od;
-            bk = ok;
-        }
-        if (mine && c == 0 && bk < a.K) a.bmu[my.z] = bk;
         if (last) break;
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
@@ -1971,6 +2053,7 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
             ids[u] = ids_next[u];
         }
     }
+    if (waiting != 0u) serve_later();
 }
 
 template <bool PAIRS>
@@ -2076,10 +2159,11 @@ __global__ void __launch_bounds__(kExactThreads) bmu_exact_kernel(const BmuArgs 
             }
 #pragma unroll
             for (int u = 0; u < kExactNodesPerThread; ++u) {
-                const int k = kb + u * kExactThreads + tid;
+                // (PAIRS: the transposed copy is in the stages' order; a thread's columns are of rising stages, so of rising nodes)
+                const int col = kb + u * kExactThreads + tid, k = PAIRS ? node_of_row(col, a.K) : col;
 #pragma unroll
                 for (int s = 0; s < kExactGroup; ++s)
-                    if (k < a.K && dist[s][u] < bestd[s]) {
+                    if (col < a.K && dist[s][u] < bestd[s]) {
                         bestd[s] = dist[s][u];
                         bestk[s] = k;
                     }
@@ -2291,7 +2375,8 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     // (D > 64: rows in the order of som_bmu_wide.hip)
     const size_t stage16_one = (split && nch == 1) ? (size_t)split_stage_f4(kb, tail_r > 0) * 16 : 0;
     const size_t stage16_bytes = !split ? 0 : nch == 1 ? (size_t)(kpad / kNodesPerStage) * stage16_one : bmu_wide_blob_bytes(K, D);
-    const size_t need = stage_bytes + wt_bytes + centre_bytes + stage16_bytes + 256;
+    const size_t wrow_bytes = (split && nch == 1) ? (size_t)K * D * sizeof(float) : 0;
+    const size_t need = stage_bytes + wt_bytes + centre_bytes + stage16_bytes + wrow_bytes + 256;
     if (need > ctx->prep_bytes) {
         if (ctx->prep_blob) {
             if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync before workspace growth")) return rc;
@@ -2314,6 +2399,7 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     out->centre = (float*)(base + 256 + stage_bytes + wt_bytes);
     out->stage16 = split ? (void*)(base + 256 + stage_bytes + wt_bytes + centre_bytes) : nullptr;
     out->tail_r = tail_r;
+    out->wrow = wrow_bytes ? (float*)(base + 256 + stage_bytes + wt_bytes + centre_bytes + stage16_bytes) : nullptr;
     out->kb = kb;
     out->kpad = kpad;
     out->steps = steps;
@@ -2327,6 +2413,7 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
         ctx->prep_clean = false;
         SplitPrep sp{};
         sp.stage16 = (char*)out->stage16;
+        sp.wrow = out->wrow;
         sp.kb_count = kb;
         sp.tail_r = tail_r;
         sp.row_bytes = split_row_bytes(kb, tail_r > 0);
@@ -2517,7 +2604,8 @@ static int launch_bmu_split(som_ctx* ctx, const BmuArgs& a)
 template <int KB, bool TAIL, int MS>
 static int launch_bmu_split_cand(som_ctx* ctx, const BmuArgs& a)
 {
-    constexpr size_t lds_bytes = 2 * (size_t)split_stage_f4(KB, TAIL) * 16;
+    constexpr size_t lds_bytes = cand_lds(KB, TAIL);
+    static_assert(lds_bytes <= 80 * 1024, "two workgroups per compute unit");
     static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
     bool& attr_set = attr_set_dev[ctx->device];
     auto kern = bmu_split_cand_kernel<KB, TAIL, MS>;
@@ -2650,6 +2738,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     a.stage16 = prep.stage16;
     a.tail_r = prep.tail_r;
     a.wt = prep.wt;
+    a.wrow = prep.wrow;
     a.centre = prep.centre;
     a.scal = prep.scal;
     a.norms = prep.calls == 0 ? prep.tops : prep.tops + 4;
@@ -2667,7 +2756,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     // at K D = 51200, against 3.8 ns for direct differences over all nodes) but has the latency of a whole tile, so
     // it only serves lists above a minimum length; node ids are 16-bit there.
     const bool cand_possible = a.K > 1 && a.K <= 65536 && a.m > (int64_t)kCandMin;
-    a.cand_min = cand_possible ? kCandMin : 0xffffffffu;
+    a.cand_min = !cand_possible ? 0xffffffffu : prep.stage16 ? kCandMin : kCandMinFloat;
     a.qe_part = ctx->qe_part;
     a.counts_near = prep.stage16 ? 1 : 0;
     // the list length restarts for every call (chunk): calls alternate between two counters, and each call's
@@ -2753,8 +2842,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
         }
     }
     if (a.K > 1) {
-        if (prep.stage16 && prep.nch == 1)
-            {
+        if (prep.stage16 && prep.nch == 1) {
             constexpr size_t lds_bytes = (size_t)(kExactThreads / 64) * pair_lds_f4(64) * 16;
             static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
             bool& attr_set = attr_set_dev[ctx->device];

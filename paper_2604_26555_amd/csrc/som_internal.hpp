@@ -17,9 +17,10 @@ constexpr int kMaxStepsResident = 32; // BMU kernel keeps a sample's features in
 struct BmuPrep {
     float* stage = nullptr;        // [Kpad / 128][nch] blobs: 128 padded weight rows of a chunk, then -|w|^2 / 2
     void* stage16 = nullptr;       // bf16 hi/lo parts of the weights for the split search (D <= 64: stage rows; D > 64: som_bmu_wide.hip), else null
+    float* wrow = nullptr;         // [K][D] the weights as given in the stages' order (split search for D <= 64)
     int kb = 0;                    // whole 16-feature blocks of a stage16 row
     int tail_r = 0;                // features of the packed tail block behind them (0: none; D <= 64 only)
-    float* wt = nullptr;           // [D][Kpad] transposed weights (as given, not centred)
+    float* wt = nullptr;           // [D][Kpad] transposed weights (as given, not centred); split search for D <= 64: nodes in the stages' order
     float* centre = nullptr;       // [D] column means of W; stage rows and sample registers hold values minus this
     // Result words, cleared by every preparation: [0] = bits of max_k |w_k - centre|^2, [3] = total,
     // [4], [5] = length of the second list (samples whose candidate slots overflowed; alternating calls),
@@ -47,6 +48,7 @@ struct BmuArgs {
     int32_t tail_r;          // BmuPrep::tail_r
     int32_t second_only;     // bmu_exact_kernel: serve the second list whatever the first one's length
     const float* wt;         // BmuPrep::wt
+    const float* wrow;       // BmuPrep::wrow
     const float* centre;     // BmuPrep::centre
     unsigned int* scal;      // BmuPrep::scal
     const unsigned int* norms;   // split search, D <= 64: the three maxima (BmuPrep::tops, or + 4 after the first pass)
@@ -56,7 +58,7 @@ struct BmuArgs {
     float* cut_all;          // [m] per presented sample: its cut when it is to be re-decided, a NaN otherwise
     uint32_t* recheck;       // [m] sample positions to re-decide (compacted from cut_all by bmu_list_kernel)
     uint32_t* recheck_end;   // end of the recheck array, from which the pair list grows down
-    uint32_t* pairs;         // [m][2] per sample on the pair list: up to four 16-bit candidate ids, the used ones in front (0xffff: none)
+    uint32_t* pairs;         // [m][2] per sample on the pair list: up to four 16-bit rows of the stages, the used ones in front (0xffff: none)
     // Candidate pass (long lists only): the search is repeated for the listed samples, and every node whose score
     // reaches the sample's cut is noted; direct differences are then taken over those few nodes only.
     float* cutv;             // [m] per list entry: best score minus the rounding bound

@@ -308,3 +308,22 @@ def test_accumulation_by_sort_of_rows_far_apart_and_of_large_matrices(som, m, K,
     # both sides add up to n_k doubles: n_k units of the last place of sums below n_k / 2
     bar = n_want.double()[:, None] ** 2 * 2.0 ** -53
     assert ((S - want).abs() <= bar).all()
+
+
+@pytest.mark.parametrize("m,K,bases,D", [
+    (20_000, 1024, 512, 50), (20_000, 1000, 333, 25), (20_000, 1024, 256, 37),      # two, three and four nodes exactly as near: the pair list
+    (3000, 1024, 256, 50), (20_000, 1024, 60, 64), (20_000, 4096, 500, 20),         # more: the candidate pass (short lists: all nodes)
+    (20_000, 1024, 4, 50), (20_000, 640, 3, 64), (20_001, 130, 2, 8),               # so many that its queues overflow
+])
+def test_bmu_exact_ties_over_many_nodes(som, m, K, bases, D):
+    """Every node is one of `bases` rows far apart, so each sample has K / bases winners that are exactly as near: the lowest index,
+    whichever of the re-decisions finds it and wherever the rows lie in the stages."""
+    rng = np.random.default_rng(m + K + bases + D)
+    base = rng.uniform(-10, 10, (bases, D)).astype(np.float32)
+    W = base[rng.permutation(np.arange(K) % bases)]
+    X = (base[rng.integers(bases, size=m)] + rng.normal(size=(m, D)) * 0.05).astype(np.float32)
+    first = np.array([np.flatnonzero((W == b).all(1))[0] for b in base])
+    near = np.concatenate([((x[:, None, :].astype(np.float64) - base[None].astype(np.float64)) ** 2).sum(2).argmin(1)
+                           for x in np.array_split(X, max(1, m * bases * D // 10_000_000))])
+    b, _, _ = som.som_bmu(dev(X), dev(W))
+    assert np.array_equal(b.cpu().numpy(), first[near])
