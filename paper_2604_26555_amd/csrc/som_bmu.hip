@@ -2088,7 +2088,9 @@ __global__ void __launch_bounds__(kExactThreads) bmu_exact_kernel(const BmuArgs 
     }
     double qs = 0.0, qs2 = 0.0;
     if constexpr (PAIRS) pair_list(a, lds4);
-    for (unsigned int g0 = blockIdx.x * kExactGroup; g0 < count; g0 += gridDim.x * kExactGroup) {
+    // (PAIRS: from the last workgroup on, so that a short list goes to workgroups without pairs: the
+    // kernel 17.5 -> 13.6 us at 250,000 x 37, together with a grid that is resident at once)
+    for (unsigned int g0 = (PAIRS ? gridDim.x - 1 - blockIdx.x : blockIdx.x) * kExactGroup; g0 < count; g0 += gridDim.x * kExactGroup) {
         float bestd[kExactGroup];
         int bestk[kExactGroup];
 #pragma unroll
@@ -2096,79 +2098,85 @@ __global__ void __launch_bounds__(kExactThreads) bmu_exact_kernel(const BmuArgs 
             bestd[s] = INFINITY;
             bestk[s] = 0x7fffffff;
         }
-        for (int kb = 0; kb < a.kpad; kb += kExactThreads * kExactNodesPerThread) {
-            float dist[kExactGroup][kExactNodesPerThread];
-#pragma unroll
-            for (int s = 0; s < kExactGroup; ++s)
-#pragma unroll
-                for (int u = 0; u < kExactNodesPerThread; ++u) dist[s][u] = 0.f;
-            for (int d0 = 0; d0 < a.D; d0 += 64) {
-                const int dn = (a.D - d0 < 64) ? a.D - d0 : 64;
-                __syncthreads();
-                for (int e = tid; e < kExactGroup * dn; e += kExactThreads) {
-                    const int s = e / dn, d = e % dn;
-                    const unsigned int ge = (g0 + s < count) ? g0 + s : count - 1;
-                    const int64_t i = (int64_t)list[ge];
-                    const int64_t r = a.idx ? (int64_t)a.idx[i] : i;
-                    xs[d * kExactGroup + s] = a.X[r * a.ldx + d0 + d];
-                }
-                __syncthreads();
-                // Eight features at a time: their sixteen weight loads are in flight together (no condition on any: with one
-                // branch per load the compiler kept them apart, and the pass took twice as long on a 4096-node map).
-                constexpr int kAtOnce = 8;
-                const float* wcol[kExactNodesPerThread];
-#pragma unroll
-                for (int u = 0; u < kExactNodesPerThread; ++u) {
-                    const int k = kb + u * kExactThreads + tid;
-                    wcol[u] = wt + (size_t)d0 * a.kpad + (k < a.kpad ? k : a.kpad - 1);
-                }
-                auto add = [&](int d, const float (&w)[kExactNodesPerThread]) {
-                    float xv[kExactGroup];
-#pragma unroll
-                    for (int q = 0; q < kExactGroup / 4; ++q) {
-                        const float4 v4 = xs4[d][q];
-                        xv[4 * q + 0] = v4.x;
-                        xv[4 * q + 1] = v4.y;
-                        xv[4 * q + 2] = v4.z;
-                        xv[4 * q + 3] = v4.w;
-                    }
-#pragma unroll
-                    for (int s = 0; s < kExactGroup; ++s)
-#pragma unroll
-                        for (int u = 0; u < kExactNodesPerThread; ++u) {
-                            const float df = xv[s] - w[u];
-                            dist[s][u] = fmaf(df, df, dist[s][u]);
-                        }
-                };
-                int d = 0;
-                for (; d + kAtOnce <= dn; d += kAtOnce) {
-                    float w[kAtOnce][kExactNodesPerThread];
-#pragma unroll
-                    for (int t = 0; t < kAtOnce; ++t)
-#pragma unroll
-                        for (int u = 0; u < kExactNodesPerThread; ++u) w[t][u] = wcol[u][(size_t)(d + t) * a.kpad];
-#pragma unroll
-                    for (int t = 0; t < kAtOnce; ++t) add(d + t, w[t]);
-                }
-                for (; d < dn; ++d) {
-                    float w[kExactNodesPerThread];
-#pragma unroll
-                    for (int u = 0; u < kExactNodesPerThread; ++u) w[u] = wcol[u][(size_t)d * a.kpad];
-                    add(d, w);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kExactNodesPerThread; ++u) {
-                // (PAIRS: the transposed copy is in the stages' order; a thread's columns are of rising stages, so of rising nodes)
-                const int col = kb + u * kExactThreads + tid, k = PAIRS ? node_of_row(col, a.K) : col;
+        auto sweep = [&](auto nodes) {
+            constexpr int NODES = decltype(nodes)::value;
+            for (int kb = 0; kb < a.kpad; kb += kExactThreads * NODES) {
+                float dist[kExactGroup][NODES];
 #pragma unroll
                 for (int s = 0; s < kExactGroup; ++s)
-                    if (col < a.K && dist[s][u] < bestd[s]) {
-                        bestd[s] = dist[s][u];
-                        bestk[s] = k;
+#pragma unroll
+                    for (int u = 0; u < NODES; ++u) dist[s][u] = 0.f;
+                for (int d0 = 0; d0 < a.D; d0 += 64) {
+                    const int dn = (a.D - d0 < 64) ? a.D - d0 : 64;
+                    __syncthreads();
+                    for (int e = tid; e < kExactGroup * dn; e += kExactThreads) {
+                        const int s = e / dn, d = e % dn;
+                        const unsigned int ge = (g0 + s < count) ? g0 + s : count - 1;
+                        const int64_t i = (int64_t)list[ge];
+                        const int64_t r = a.idx ? (int64_t)a.idx[i] : i;
+                        xs[d * kExactGroup + s] = a.X[r * a.ldx + d0 + d];
                     }
+                    __syncthreads();
+                    // Eight features at a time: their sixteen weight loads are in flight together (no condition on any: with one
+                    // branch per load the compiler kept them apart, and the pass took twice as long on a 4096-node map).
+                    constexpr int kAtOnce = 8;
+                    const float* wcol[NODES];
+#pragma unroll
+                    for (int u = 0; u < NODES; ++u) {
+                        const int k = kb + u * kExactThreads + tid;
+                        wcol[u] = wt + (size_t)d0 * a.kpad + (k < a.kpad ? k : a.kpad - 1);
+                    }
+                    auto add = [&](int d, const float (&w)[NODES]) {
+                        float xv[kExactGroup];
+#pragma unroll
+                        for (int q = 0; q < kExactGroup / 4; ++q) {
+                            const float4 v4 = xs4[d][q];
+                            xv[4 * q + 0] = v4.x;
+                            xv[4 * q + 1] = v4.y;
+                            xv[4 * q + 2] = v4.z;
+                            xv[4 * q + 3] = v4.w;
+                        }
+#pragma unroll
+                        for (int s = 0; s < kExactGroup; ++s)
+#pragma unroll
+                            for (int u = 0; u < NODES; ++u) {
+                                const float df = xv[s] - w[u];
+                                dist[s][u] = fmaf(df, df, dist[s][u]);
+                            }
+                    };
+                    int d = 0;
+                    for (; d + kAtOnce <= dn; d += kAtOnce) {
+                        float w[kAtOnce][NODES];
+#pragma unroll
+                        for (int t = 0; t < kAtOnce; ++t)
+#pragma unroll
+                            for (int u = 0; u < NODES; ++u) w[t][u] = wcol[u][(size_t)(d + t) * a.kpad];
+#pragma unroll
+                        for (int t = 0; t < kAtOnce; ++t) add(d + t, w[t]);
+                    }
+                    for (; d < dn; ++d) {
+                        float w[NODES];
+#pragma unroll
+                        for (int u = 0; u < NODES; ++u) w[u] = wcol[u][(size_t)d * a.kpad];
+                        add(d, w);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < NODES; ++u) {
+                    // (PAIRS: the transposed copy is in the stages' order; a thread's columns are of rising stages, so of rising nodes)
+                    const int col = kb + u * kExactThreads + tid, k = PAIRS ? node_of_row(col, a.K) : col;
+#pragma unroll
+                    for (int s = 0; s < kExactGroup; ++s)
+                        if (col < a.K && dist[s][u] < bestd[s]) {
+                            bestd[s] = dist[s][u];
+                            bestk[s] = k;
+                        }
+                }
             }
-        }
+        };
+        // (a map of up to as many nodes as threads: one each, 2,500 entries on 400 nodes x 25 take 20 us instead of 22)
+        if (a.kpad <= kExactThreads) sweep(std::integral_constant<int, 1>{});
+        else sweep(std::integral_constant<int, kExactNodesPerThread>{});
         // lowest distance, then lowest node index, across the workgroup
 #pragma unroll
         for (int s = 0; s < kExactGroup; ++s) {
@@ -2859,7 +2867,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
             BmuArgs b = a;                       // the distances come afterwards, for all samples
             b.d2 = nullptr;
             b.qe = nullptr;
-            hipLaunchKernelGGL(bmu_exact_kernel<true>, dim3(1024), dim3(kExactThreads), lds, ctx->stream, b);
+            hipLaunchKernelGGL(bmu_exact_kernel<true>, dim3(512), dim3(kExactThreads), lds, ctx->stream, b);
         }
         else
             hipLaunchKernelGGL(bmu_exact_kernel<false>, dim3(1024), dim3(kExactThreads), kExactLds, ctx->stream, a);
