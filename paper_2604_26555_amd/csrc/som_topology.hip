@@ -12,6 +12,7 @@
 //                      d2[p][q]: every pair against 64 nodes near p first, the few pairs left against all nodes
 //   csr_*              degree count, exclusive scan, ascending neighbour lists
 //   bfs_kernel         one wavefront per source, frontier queue and distance row in LDS
+//   tree_hops_kernel   the same for spanning trees: lanes walk along the branches
 #include "som_internal.hpp"
 
 #include <math.h>
@@ -412,13 +413,11 @@ __global__ void __launch_bounds__(256) csr_fill_kernel(const unsigned char* __re
 // a compare-and-swap on its distance, and the claimed ones of a step are appended through a ballot (the queue
 // position is a wave-uniform register, not a counter in memory).  LDS operations of one wavefront execute in
 // order, so a later step sees the earlier steps' claims and queue entries.
-__global__ void __launch_bounds__(64) bfs_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K,
-                                                 float* __restrict__ G)
+__device__ __forceinline__ void bfs_source(const int* __restrict__ off, const int* __restrict__ nbr, int K, int src, int* dist,
+                                           float* __restrict__ G)
 {
-    extern __shared__ int bfs_lds[];
-    int* dist = bfs_lds;                                                       // [K]
-    unsigned short* queue = reinterpret_cast<unsigned short*>(bfs_lds + K);    // [K]
-    const int lane = threadIdx.x, src = blockIdx.x;
+    unsigned short* queue = reinterpret_cast<unsigned short*>(dist + K);       // [K], behind dist [K]
+    const int lane = threadIdx.x & 63;
     for (int v = lane; v < K; v += 64) dist[v] = (v == src) ? 0 : -1;
     if (lane == 0) queue[0] = (unsigned short)src;
     int head = 0, tail = 1;
@@ -452,6 +451,106 @@ __global__ void __launch_bounds__(64) bfs_kernel(const int* __restrict__ off, co
         const int d = dist[v];
         G[(size_t)src * K + v] = d < 0 ? INFINITY : (float)d;
     }
+}
+
+__global__ void __launch_bounds__(64) bfs_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K,
+                                                 float* __restrict__ G)
+{
+    extern __shared__ int bfs_lds[];
+    bfs_source(off, nbr, K, blockIdx.x, bfs_lds, G);
+}
+
+// The same for a spanning tree: between two nodes there is one way, so nothing has to be claimed.  A lane walks on from its node to a
+// neighbour that is not where it came from, notes the distance and puts what else branches off on a stack in LDS, from which idle
+// lanes take; the sources of a workgroup share the lists, as 16-bit numbers in LDS.  A step is one LDS read: a node's
+// record holds its first two neighbours, and only a node with more (or a source with two) looks at the list.
+// Bound by latency: a tree of K nodes is up to K levels deep, and at each the breadth-first search goes queue -> list -> neighbour ->
+// claim, once per neighbour: 0.36 ms at K = 1024 (a map along a path, 10^7 x 50), with its lists in LDS as well; this
+// walk takes 0.18 ms.
+// (Weights that are no numbers can give edges that are no tree: more visits than nodes, or fewer, and the source is searched
+// breadth first instead.)
+constexpr int kTreeSources = 4;
+constexpr size_t kTreeLds = 160 * 1024;
+
+// bytes of LDS: records ([K] offset, degree, two neighbours) and list ([2 (K - 1)] neighbours), and per source stack and distances
+__host__ __device__ constexpr size_t tree_list_bytes(int K) { return (size_t)K * 12; }
+__host__ __device__ constexpr size_t tree_source_bytes(int K) { return ((size_t)K * 6 + 3) / 4 * 4; }
+
+__global__ void __launch_bounds__(64 * kTreeSources) tree_hops_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K,
+                                                                      float* __restrict__ G)
+{
+    extern __shared__ unsigned int tree_lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int src = blockIdx.x * (int)(blockDim.x >> 6) + wave;
+    uint2* node = reinterpret_cast<uint2*>(tree_lds);                                  // [K] offset and degree; first and second neighbour
+    unsigned short* list = reinterpret_cast<unsigned short*>(tree_lds + 2 * K);        // [2 K]
+    unsigned int* stack = tree_lds + 3 * K + wave * (tree_source_bytes(K) / 4);        // [K] node, where from above bit 16
+    unsigned short* dist = reinterpret_cast<unsigned short*>(stack + K);               // [K]
+    constexpr unsigned kNowhere = 0xffffu;                 // (K <= 12000)
+    const int nnz = off[K];                                                            // 2 (K - 1)
+    for (int v = threadIdx.x; v < K; v += blockDim.x) {
+        const int o = off[v], deg = off[v + 1] - o;
+        const unsigned n0 = deg > 0 ? (unsigned)nbr[o] : kNowhere, n1 = deg > 1 ? (unsigned)nbr[o + 1] : kNowhere;
+        node[v] = make_uint2((unsigned)o | (unsigned)deg << 16, n0 | n1 << 16);
+    }
+    for (int e = threadIdx.x; e < nnz && e < 2 * K; e += blockDim.x) list[e] = (unsigned short)nbr[e];
+    __syncthreads();
+    if (src >= K) return;
+    unsigned v = lane == 0 ? (unsigned)src : kNowhere, from = kNowhere, d = 0;
+    unsigned pending = 0;
+    int visits = 0;
+    while (nnz == 2 * (K - 1) && visits <= K) {
+        const bool active = v != kNowhere;
+        const uint2 r = node[active ? v : 0u];
+        visits += (int)__popcll(__ballot(active));
+        if (active) dist[v] = (unsigned short)d;
+        const unsigned n0 = r.y & 0xffffu, n1 = r.y >> 16, deg = r.x >> 16;
+        const unsigned next = !active ? kNowhere : n0 != from ? n0 : n1;
+        unsigned left = active && (deg > 2 || (n0 != from && n1 != from && deg == 2)) ? deg : 0u;
+        if (__any(left > 0)) {
+            unsigned e = r.x & 0xffffu;
+            do {
+                bool put = false;
+                unsigned u = 0;
+                if (left > 0) {
+                    u = list[e];
+                    ++e;
+                    --left;
+                    put = u != from && u != next;
+                }
+                const unsigned long long mask = __ballot(put);
+                if (put) {
+                    const unsigned at = pending + __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
+                    if (at < (unsigned)K) stack[at] = u | v << 16;
+                }
+                pending = pending + (unsigned)__popcll(mask) < (unsigned)K ? pending + (unsigned)__popcll(mask) : (unsigned)K;
+            } while (__any(left > 0));
+        }
+        from = v;
+        v = next;
+        ++d;
+        const unsigned long long idle = __ballot(v == kNowhere);
+        if (pending > 0) {
+            __builtin_amdgcn_wave_barrier();
+            const unsigned place = __builtin_amdgcn_mbcnt_hi((unsigned)(idle >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)idle, 0));
+            if (v == kNowhere && place < pending) {
+                const unsigned s = stack[pending - 1 - place];
+                v = s & 0xffffu;
+                from = s >> 16;
+                d = (unsigned)dist[from] + 1;
+            }
+            const unsigned taken = (unsigned)__popcll(idle);
+            pending = pending > taken ? pending - taken : 0;
+        } else if (idle == ~0ull) {
+            break;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (visits != K) {
+        bfs_source(off, nbr, K, src, reinterpret_cast<int*>(stack), G);
+        return;
+    }
+    for (int u = lane; u < K; u += 64) G[(size_t)src * K + u] = (float)dist[u];
 }
 
 } // namespace som
@@ -523,6 +622,24 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
     hipLaunchKernelGGL(csr_scan_kernel, dim3(1), dim3(1024), 0, ctx->stream, deg, K, off);
     hipLaunchKernelGGL(csr_fill_kernel, dim3((K + 3) / 4), dim3(256), 0, ctx->stream, A, K, off, nbr);
     if (int rc = check_hip(ctx, hipGetLastError(), "adjacency launch")) return rc;
+    if (kind == SOM_TOPOLOGY_MST && tree_list_bytes(K) + tree_source_bytes(K) <= kTreeLds) {
+        // as many sources to a workgroup as give a compute unit most wavefronts
+        int sources = 1;
+        size_t most = 0;
+        for (int n = 1; n <= kTreeSources; ++n) {
+            const size_t bytes = tree_list_bytes(K) + n * tree_source_bytes(K), waves = bytes <= kTreeLds ? n * (kTreeLds / bytes) : 0;
+            if (waves >= most && waves > 0) {
+                most = waves;
+                sources = n;
+            }
+        }
+        const size_t lds = tree_list_bytes(K) + sources * tree_source_bytes(K);
+        if (lds > 48 * 1024) {
+            if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(tree_hops_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTreeLds), "raising the dynamic LDS limit")) return rc;
+        }
+        hipLaunchKernelGGL(tree_hops_kernel, dim3((K + sources - 1) / sources), dim3(64 * sources), lds, ctx->stream, off, nbr, K, G);
+        return check_hip(ctx, hipGetLastError(), "hop-count launch");
+    }
     // dist[K] int32 + queue[K] uint16 per wavefront (72 KB at the 12000-node limit)
     const size_t bfs_lds_bytes = ((size_t)K * 6 + 3) / 4 * 4;
     if (bfs_lds_bytes > 48 * 1024) {

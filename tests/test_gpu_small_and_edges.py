@@ -327,3 +327,24 @@ def test_bmu_exact_ties_over_many_nodes(som, m, K, bases, D):
                            for x in np.array_split(X, max(1, m * bases * D // 10_000_000))])
     b, _, _ = som.som_bmu(dev(X), dev(W))
     assert np.array_equal(b.cpu().numpy(), first[near])
+
+
+@pytest.mark.parametrize("shape,K", [("chain", 2), ("chain", 3), ("chain", 65), ("chain", 1500), ("star", 4), ("star", 70), ("star", 300),
+                                     ("comb", 66), ("comb", 513), ("random", 1), ("random", 1025), ("random", 2500)])
+def test_spanning_tree_hops_of_every_shape(som, shape, K):
+    """The walk over a spanning tree: long branches, nodes with very many branches, both mixed, and sizes around a wavefront."""
+    rng = np.random.default_rng(K)
+    if shape == "chain":                                    # along a line, in a mixed order
+        W = (np.sort(rng.uniform(0, 10 * K, K))[rng.permutation(K)])[:, None]
+    elif shape == "star":                                   # leaves 10 to 11 from the hub, at least 14 from each other
+        W = np.zeros((K, K))
+        W[np.arange(1, K), np.arange(1, K)] = 10 + np.arange(1, K) / K
+        W = W[rng.permutation(K)]
+    elif shape == "comb":                                   # a spine with teeth of four nodes
+        i = np.arange(K)
+        W = np.stack([(i // 5) * 3.0 + 0.001 * (i // 5) ** 1.1, (i % 5) * (1.0 + 0.0005 * i)], 1)
+    else:
+        W = rng.normal(size=(K, 6))
+    W = W.astype(np.float32)
+    T = som.som_topology(dev(W), "mst").cpu().numpy()
+    assert np.array_equal(T, oracle.graph_distances("mst", W).astype(np.float32))
