@@ -25,6 +25,7 @@ constexpr int kSFeatures = 32;                // small_kernel: features of a row
 constexpr int kSNodes = 512;                  // small epochs: nodes at most
 constexpr double kSWork = 3.0e8;              // m K D of a small epoch at most: 0.4 to 0.8 of the general path's time there (D = 2 ... 32,
                                               // K = 16 ... 512), at 6e8 0.5 to 1.3
+constexpr int kSFlight = 8;                   // lookup_kernel: loads of W under way in a thread
 constexpr double kLWork = 4.0e8;              // ... of a small look-up,
 constexpr double kLSteps = 6.0e8;             // and the same with rows and features rounded up (look_up_rows)
 
@@ -147,14 +148,51 @@ __global__ void __launch_bounds__(kSThreads) small_kernel(const SmallArgs a)
     if (a.qe_part) group_qe_add(a.qe_part, qs, qs2);
 }
 
-// S samples per workgroup; nodes in pieces of `piece` (their rows in LDS, `stride` floats apart, odd or harmless to the banks)
+// v of the lane that a DPP control names, ~0 where there is none
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ unsigned dpp(unsigned v)
+{
+    return (unsigned)__builtin_amdgcn_update_dpp(-1, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ unsigned less(unsigned a, unsigned b) { return a < b ? a : b; }
+// the least of a full wavefront, for every lane
+__device__ __forceinline__ unsigned wave_min(unsigned v)
+{
+    v = less(v, dpp<0x111>(v));              // one to the right in a row of sixteen,
+    v = less(v, dpp<0x112>(v));              // two,
+    v = less(v, dpp<0x114>(v));              // four,
+    v = less(v, dpp<0x118>(v));              // eight: the row's last lane has its least
+    v = less(v, dpp<0x142, 0xa>(v));         // which the next row takes over,
+    v = less(v, dpp<0x143, 0xc>(v));         // and the upper half
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+// the least of each eight lanes, for each of them
+__device__ __forceinline__ unsigned min_of_eight(unsigned v)
+{
+    v = less(v, dpp<0xb1>(v));               // (neighbours, pairs, and the halves mirrored)
+    v = less(v, dpp<0x4e>(v));
+    return less(v, dpp<0x141>(v));
+}
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// S samples per workgroup; nodes in pieces of `piece` (their rows in LDS, `stride` floats apart, odd or harmless to the banks).
+// A look-up is one round of workgroups, so what counts is the chain of waits in one of them.  Of the 27,500 cycles that a
+// workgroup took for 4 samples of 50 features on 1024 nodes, 8000 brought W in (a load at a time in each thread: now kSFlight
+// of them), 8100 were differences (6400 is what the vector units need) and 9600 the join of the threads' winners, where every
+// step waited for a shuffle through LDS; DPP moves and one barrier do it in about 1500.  Look-ups with distances and
+// quantisation error, in us: 1000 rows 15.4 -> 12.5, 12,288 rows of 50 features on 64 nodes 40.3 -> 32.1, 2000 of 37 on 400
+// 15.5 -> 11.2, 4095 of 40 on 1500 43.3 -> 36.7, 300 of 64 on 20,000 248 -> 191.  The samples' rows in LDS in place of scalar
+// loads: 13.1 against 12.4 (the broadcast reads cost more than the loads' latency).  Parts of the nodes on workgroups of their
+// own, joined by the last to arrive: 15.7 against 15.4 at 1000 rows (faster only for a few rows on many nodes).
 template <int S>
 __global__ void __launch_bounds__(kSThreads) lookup_kernel(const float* __restrict__ X, const float* __restrict__ W, const SmallArgs a,
                                                            int piece, int stride)
 {
     extern __shared__ float4 small_lds[];
-    __shared__ float red_d[kSThreads / 64][S];
-    __shared__ int red_k[kSThreads / 64][S];
+    __shared__ uint2 red[S][kSThreads / 64];
     float* const wl = reinterpret_cast<float*>(small_lds);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, D = a.D, K = a.K;
     const int64_t i0 = (int64_t)blockIdx.x * S;
@@ -180,18 +218,34 @@ __global__ void __launch_bounds__(kSThreads) lookup_kernel(const float* __restri
         if (stride == D) {
             const int words = kn * D, whole = words / 4;
             float4* to = reinterpret_cast<float4*>(wl);
-            for (int e = tid; e < whole; e += kSThreads) to[e] = load4(from + 4 * e);
+#pragma nounroll
+            for (int e = tid; e < whole; e += kSFlight * kSThreads) {
+                float4 v[kSFlight];
+#pragma unroll
+                for (int t = 0; t < kSFlight; ++t) v[t] = load4(from + 4 * (e + t * kSThreads < whole ? e + t * kSThreads : e));
+#pragma unroll
+                for (int t = 0; t < kSFlight; ++t)
+                    if (e + t * kSThreads < whole) to[e + t * kSThreads] = v[t];
+            }
             for (int e = 4 * whole + tid; e < words; e += kSThreads) wl[e] = from[e];
         } else {
             const int dq = D / 4;                           // (a multiple of four: padded rows)
-            for (int e = tid; e < kn * dq; e += kSThreads) {
-                const int r = e / dq, q = e - r * dq;
-                const float4 v = load4(from + 4 * e);
-                float* to = wl + r * stride + 4 * q;
-                to[0] = v.x;
-                to[1] = v.y;
-                to[2] = v.z;
-                to[3] = v.w;
+            const int whole = kn * dq;
+#pragma nounroll
+            for (int e = tid; e < whole; e += kSFlight * kSThreads) {
+                float4 v[kSFlight];
+#pragma unroll
+                for (int t = 0; t < kSFlight; ++t) v[t] = load4(from + 4 * (e + t * kSThreads < whole ? e + t * kSThreads : e));
+#pragma unroll
+                for (int t = 0; t < kSFlight; ++t)
+                    if (e + t * kSThreads < whole) {
+                        const int r = (e + t * kSThreads) / dq, q = e + t * kSThreads - r * dq;
+                        float* to = wl + r * stride + 4 * q;
+                        to[0] = v[t].x;
+                        to[1] = v[t].y;
+                        to[2] = v[t].z;
+                        to[3] = v[t].w;
+                    }
             }
         }
         __syncthreads();
@@ -231,42 +285,40 @@ __global__ void __launch_bounds__(kSThreads) lookup_kernel(const float* __restri
     }
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-        float d = bd[s];
-        int k = bk[s];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const float od = __shfl_xor(d, o);
-            const int ok = __shfl_xor(k, o);
-            if (od < d || (od == d && ok < k)) {
-                d = od;
-                k = ok;
-            }
-        }
-        if (lane == 0) {
-            red_d[wave][s] = d;
-            red_k[wave][s] = k;
-        }
+        const unsigned d = wave_min(__float_as_uint(bd[s]));                  // (no distance is negative or NaN)
+        const unsigned k = wave_min(__float_as_uint(bd[s]) == d ? (unsigned)bk[s] : 0x7fffffffu);
+        if (lane == 0) red[s][wave] = make_uint2(d, k);
     }
     __syncthreads();
+    if (wave != 0) return;
+    // eight lanes to a sample
+    static_assert(kSThreads == 8 * 64 && S <= 8, "a wavefront joins all samples' eight winners");
+    const int s = lane >> 3;
+    const uint2 mine = red[s < S ? s : 0][lane & 7];
+    const unsigned bits = min_of_eight(mine.x);
+    int k = (int)min_of_eight(mine.x == bits ? mine.y : 0x7fffffffu);
+    const float d = __uint_as_float(bits);
     double qs = 0.0, qs2 = 0.0;
-    if (tid < S && i0 + tid < a.m) {
-        float d = red_d[0][tid];
-        int k = red_k[0][tid];
-        for (int w = 1; w < kSThreads / 64; ++w) {
-            const float od = red_d[w][tid];
-            const int ok = red_k[w][tid];
-            if (od < d || (od == d && ok < k)) {
-                d = od;
-                k = ok;
-            }
-        }
+    if ((lane & 7) == 0 && s < S && i0 + s < a.m) {
         if (k >= K) k = 0;                                     // only reachable with non-finite input
-        a.bmu[i0 + tid] = k;
-        if (a.d2) a.d2[i0 + tid] = d;
+        a.bmu[i0 + s] = k;
+        if (a.d2) a.d2[i0 + s] = d;
         qs = sqrt((double)d);
         qs2 = (double)d;
     }
-    if (a.qe_part) group_qe_add(a.qe_part, qs, qs2);
+    if (a.qe_part) {
+        double t0 = 0.0, t1 = 0.0;
+#pragma unroll
+        for (int t = 0; t < S; ++t) {
+            t0 += lane_value(qs, 8 * t);
+            t1 += lane_value(qs2, 8 * t);
+        }
+        if (lane == 0 && (t0 != 0.0 || t1 != 0.0)) {
+            const int slot = blockIdx.x & (kQeSlots - 1);
+            unsafeAtomicAdd(&a.qe_part[2 * slot], t0);
+            unsafeAtomicAdd(&a.qe_part[2 * slot + 1], t1);
+        }
+    }
 }
 
 // qe[0..1] = the call's partial sums, which are left zero for the next call
@@ -418,6 +470,8 @@ static bool lookup_in_lds(int K, int D) { return D <= kSFeatures && small_lds_by
 // The most rows of a look-up that go through one kernel here; the others take the general path.  Both sides were timed over
 // D = 3 ... 64, K = 16 ... 20000 and rows from 300 across the line, with and without distances, on rows that the caches hold
 // and on rows that they do not.
+// (Timed before the threads' winners were joined by DPP moves: a look-up takes 0.75 to 0.95 of those times now, so the lines
+// are on the safe side.)
 //   lookup_kernel: a workgroup stages all of W and walks all of it for its eight samples, with as many threads as it has
 //   whatever K is, so its time goes with the rounds of workgroups (256 units, up to three on a unit as LDS allows) and jumps
 //   at each.  Share of the general path's time (cached rows / others): D = 50, K = 64, three to a unit: 0.62 / 0.62 for the

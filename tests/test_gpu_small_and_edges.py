@@ -186,6 +186,27 @@ def test_look_ups_on_both_sides_of_their_line(som, m, K, D):
     assert np.array_equal(part, b_gpu[idx.astype(np.int64)])
 
 
+@pytest.mark.parametrize("m,K,bases,D", [
+    (1, 64, 1, 50), (5, 63, 2, 33), (1001, 512, 3, 50), (1023, 1024, 40, 64), (1025, 1500, 7, 37), (2047, 700, 100, 52), (1000, 2100, 2, 61),
+    (1001, 512, 3, 8), (4999, 100, 4, 32),
+])
+def test_look_ups_take_the_lowest_of_equal_nodes(som, m, K, bases, D):
+    """Nodes exactly as near in the same thread, in neighbouring lanes, rows of lanes, wavefronts and pieces of W."""
+    rng = np.random.default_rng(m + K + bases + D)
+    base = rng.uniform(-10, 10, (bases, D)).astype(np.float32)
+    W = base[rng.permutation(np.arange(K) % bases)]
+    pick = rng.integers(bases, size=m)
+    X = base[pick].copy()                                       # on the nodes: distance zero, whichever of them
+    first = np.array([np.flatnonzero((W == b).all(1))[0] for b in base])
+    X[m // 2, D // 2] = np.nan                                  # no distance is less than another: the first node
+    want = first[pick]
+    want[m // 2] = 0
+    d2 = torch.full((m,), -1.0, device="cuda")
+    b = som.som_bmu(dev(X), dev(W), d2=d2)[0].cpu().numpy()
+    assert np.array_equal(b, want)
+    assert (np.delete(d2.cpu().numpy(), m // 2) == 0).all()
+
+
 # ---------------------------------------------------------------------------------------------------- one context, all searches
 def test_searches_that_follow_each_other_on_one_context(som):
     """Narrow, wide and float32 searches, look-ups and epochs share the context's preparation and its result words: long and
