@@ -101,6 +101,16 @@ def test_small_epochs_on_both_sides_of_their_limits(som, m, K, D):
     epoch_against_oracle(som, X, W, line(K), 1.0 + 0.02 * K)
 
 
+@pytest.mark.parametrize("m,K,D", [
+    (9000, 256, 7), (9000, 293, 6), (20_000, 227, 8), (20_000, 228, 8), (4097, 512, 3), (8200, 65, 31), (8200, 64, 31),   # K (D + 1) around 2048
+    (40_000, 101, 8), (16_385, 16, 8), (33, 100, 8), (700, 1, 4), (700, 2, 32), (5000, 511, 15),                          # nodes left over
+])
+def test_small_epochs_with_one_and_eight_copies_of_the_sums(som, m, K, D):
+    X = rows(600 + K + D, m, D)
+    W = X[draw_initial_rows(4, m, K)].copy() if K <= m else rows(601 + K, K, D)
+    epoch_against_oracle(som, X, W, line(K), 1.0 + 0.02 * K)
+
+
 def test_small_epochs_with_a_row_list_and_padded_rows(som):
     X = rows(61, 6000, 10)
     idx = draw_subset(61, 0, 6000, 2500)
