@@ -43,37 +43,51 @@ __global__ void __launch_bounds__(kSortThreads) sort_hist_kernel(const int32_t* 
     for (int k = tid; k < K; k += kSortThreads) hist[(size_t)blockIdx.x * K + k] = sort_lds[k];
 }
 
-// hist[block][k] -> number of node k's samples in the blocks before; total[k]; n[k] (+)= total[k].  64 nodes and sixteen
-// runs of blocks per workgroup.
+// hist[block][k] -> number of node k's samples in the blocks before; total[k]; n[k] (+)= total[k].  16 nodes and 64 runs of
+// blocks per workgroup: a thread's loads follow each other, so that short runs count (64 nodes and sixteen runs: 12.6 us for
+// 1023 blocks of 400 nodes, 6.0 now).
 __global__ void __launch_bounds__(1024) sort_columns_kernel(uint32_t* __restrict__ hist, int K, int blocks, uint32_t* __restrict__ total,
                                                             unsigned long long* __restrict__ n, int zero_first)
 {
-    __shared__ uint32_t run[16][64];
-    const int l = threadIdx.x & 63, seg = threadIdx.x >> 6;
-    const int k = blockIdx.x * 64 + l;
-    const int per = (blocks + 15) / 16, lo = seg * per, hi = lo + per < blocks ? lo + per : blocks;
+    __shared__ uint32_t run[16][16];
+    const int l = threadIdx.x & 15, seg = threadIdx.x >> 4, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int k = blockIdx.x * 16 + l, kc = k < K ? k : K - 1;
+    const int per = (blocks + 63) / 64, lo = seg * per, hi = lo + per < blocks ? lo + per : blocks;
     uint32_t s = 0u;
-    if (k < K) {
-#pragma unroll 8
-        for (int b = lo; b < hi; ++b) s += hist[(size_t)b * K + k];
-    }
-    run[seg][l] = s;
-    __syncthreads();
-    if (k >= K) return;
-    uint32_t at = 0u, all = 0u;
-    for (int q = 0; q < 16; ++q) {
-        const uint32_t v = run[q][l];
-        at += q < seg ? v : 0u;
-        all += v;
-    }
     for (int b0 = lo; b0 < hi; b0 += 8) {
         uint32_t v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = b0 + u < hi ? hist[(size_t)(b0 + u) * K + k] : 0u;
+        for (int u = 0; u < 8; ++u) v[u] = hist[(size_t)(b0 + u < hi ? b0 + u : lo) * K + kc];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += b0 + u < hi ? v[u] : 0u;
+    }
+    uint32_t at = s;                                           // up to and with this run, in the wavefront's four
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) {
+        const uint32_t before = __shfl_up(at, o);
+        if (lane >= o) at += before;
+    }
+    if (lane >= 48) run[wave][l] = at;
+    at -= s;
+    __syncthreads();
+    uint32_t all = 0u;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const uint32_t v = run[q][l];
+        at += q < wave ? v : 0u;
+        all += v;
+    }
+    if (k >= K) return;
+    for (int b0 = lo; b0 < hi; b0 += 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = hist[(size_t)(b0 + u < hi ? b0 + u : lo) * K + k];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            if (b0 + u < hi) hist[(size_t)(b0 + u) * K + k] = at;
-            at += v[u];
+            if (b0 + u < hi) {
+                hist[(size_t)(b0 + u) * K + k] = at;
+                at += v[u];
+            }
         }
     }
     if (seg == 0) {
@@ -346,7 +360,7 @@ int accumulate_sort_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, co
     if (stable) hipLaunchKernelGGL(stable_hist_kernel, grid, wg, lds, ctx->stream, bmu, m, K, per_block, blocks, hist);
     else hipLaunchKernelGGL(sort_hist_kernel, grid, wg, lds, ctx->stream, bmu, m, K, per_block, hist);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) histogram launch")) return rc;
-    hipLaunchKernelGGL(sort_columns_kernel, dim3((K + 63) / 64), dim3(1024), 0, ctx->stream, hist, K, blocks, total, n, zero_first ? 1 : 0);
+    hipLaunchKernelGGL(sort_columns_kernel, dim3((K + 15) / 16), dim3(1024), 0, ctx->stream, hist, K, blocks, total, n, zero_first ? 1 : 0);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) offsets launch")) return rc;
     hipLaunchKernelGGL(sort_starts_kernel, dim3(1), dim3(1024), 0, ctx->stream, total, K, (uint32_t)rows, start, seg);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) starts launch")) return rc;

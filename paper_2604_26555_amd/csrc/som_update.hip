@@ -25,23 +25,37 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // at K = 1024, D = 2000 (207 + 53 us for contraction and finish there, 96 + 11 now; 228 + 28 -> 153 + 14 us at K = 4096, D = 50).
 constexpr int kSplitK = 4;
 
-// shift[j] = min over occupied nodes k of G[k][j]^2 (+inf when there is none): 64 columns per workgroup, sixteen runs of rows
+// shift[j] = min over occupied nodes k of G[k][j]^2 (+inf when there is none): 16 columns per workgroup, every 64th row a thread,
+// eight loads under way.  A chain of loads is all there is: with 64 columns and runs of K / 16 rows, whose branches on n[k] kept
+// the loads apart, 12.8 us at K = 400, 4.6 now.
 __global__ void __launch_bounds__(1024) shift_kernel(const float* __restrict__ G, const unsigned long long* __restrict__ n,
                                                      int K, double* __restrict__ shift)
 {
-    __shared__ double low[16][64];
-    const int l = threadIdx.x & 63, seg = threadIdx.x >> 6;
-    const int j = blockIdx.x * 64 + l;
-    const int per = (K + 15) / 16, lo = seg * per, hi = lo + per < K ? lo + per : K;
+    __shared__ double low[16][16];
+    const int l = threadIdx.x & 15, seg = threadIdx.x >> 4, wave = threadIdx.x >> 6;
+    const int j = blockIdx.x * 16 + l, jc = j < K ? j : K - 1;
     double m = INFINITY;
-    if (j < K) {
-#pragma unroll 8
-        for (int k = lo; k < hi; ++k) {
-            const double gd = (double)G[(size_t)k * K + j];
-            if (n[k] != 0ull && gd * gd < m) m = gd * gd;
+    for (int k0 = seg; k0 < K; k0 += 8 * 64) {
+        float g[8];
+        unsigned long long on[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int k = k0 + 64 * t < K ? k0 + 64 * t : k0;
+            g[t] = G[(size_t)k * K + jc];
+            on[t] = n[k];
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const double g2 = (double)g[t] * (double)g[t];
+            m = on[t] != 0ull && g2 < m ? g2 : m;
         }
     }
-    low[seg][l] = m;
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) {
+        const double other = __shfl_xor(m, o);
+        m = other < m ? other : m;
+    }
+    if ((threadIdx.x & 48) == 0) low[wave][l] = m;
     __syncthreads();
     if (seg == 0 && j < K) {
 #pragma unroll
@@ -105,6 +119,7 @@ __global__ void __launch_bounds__(256) contract_kernel(const float* __restrict__
         double nv[JT][kBatch], sv[kBatch][4];
 #pragma unroll
         for (int s = 0; s < kBatch; ++s) {
+            if (kb + 4 * s >= k_hi) continue;                 // (small maps end early: 7 of 16 steps at K = 437, 13.1 -> 8.8 us)
             const int k = kb + 4 * s + lk;
             const int kc = k < K ? k : K - 1;                 // clamped row: the loads are unconditional
 #pragma unroll
@@ -120,6 +135,7 @@ __global__ void __launch_bounds__(256) contract_kernel(const float* __restrict__
         }
 #pragma unroll
         for (int s = 0; s < kBatch; ++s) {
+            if (kb + 4 * s >= k_hi) continue;
             const int k = kb + 4 * s + lk;
             const bool occupied = !(FUSED && shift) || n[k < K ? k : K - 1] != 0ull;
 #pragma unroll
@@ -211,7 +227,7 @@ static int update_launch(som_ctx* ctx, double* H, double* part, double* shift_ws
     double* shift = nullptr;
     if (ctx->safeguard == SOM_SAFEGUARD_SHIFT) {
         shift = shift_ws;
-        hipLaunchKernelGGL(shift_kernel, dim3((K + 63) / 64), dim3(1024), 0, ctx->stream, G, n, K, shift);
+        hipLaunchKernelGGL(shift_kernel, dim3((K + 15) / 16), dim3(1024), 0, ctx->stream, G, n, K, shift);
         if (int rc = check_hip(ctx, hipGetLastError(), "exponent shift launch")) return rc;
     }
     if (grid.y == 1) {
