@@ -12,6 +12,7 @@
 #include "som_internal.hpp"
 
 #include <math.h>
+#include <type_traits>
 
 #include <mutex>
 
@@ -114,12 +115,12 @@ __global__ void __launch_bounds__(256) contract_kernel(const float* __restrict__
     // kBatch k-steps at a time: first every load of the batch (one wavefront per SIMD has nothing else to cover a
     // round trip to L2 with), then the exponentials, then the MFMAs.
     constexpr int kBatch = 16 / JT;
-    for (int kb = k_lo; kb < k_hi; kb += 4 * kBatch) {
+    auto batch = [&](int kb, auto whole) {
         float gv[JT][kBatch];
         double nv[JT][kBatch], sv[kBatch][4];
 #pragma unroll
         for (int s = 0; s < kBatch; ++s) {
-            if (kb + 4 * s >= k_hi) continue;                 // (small maps end early: 7 of 16 steps at K = 437, 13.1 -> 8.8 us)
+            if (!whole && kb + 4 * s >= k_hi) continue;
             const int k = kb + 4 * s + lk;
             const int kc = k < K ? k : K - 1;                 // clamped row: the loads are unconditional
 #pragma unroll
@@ -135,7 +136,7 @@ __global__ void __launch_bounds__(256) contract_kernel(const float* __restrict__
         }
 #pragma unroll
         for (int s = 0; s < kBatch; ++s) {
-            if (kb + 4 * s >= k_hi) continue;
+            if (!whole && kb + 4 * s >= k_hi) continue;
             const int k = kb + 4 * s + lk;
             const bool occupied = !(FUSED && shift) || n[k < K ? k : K - 1] != 0ull;
 #pragma unroll
@@ -152,7 +153,13 @@ __global__ void __launch_bounds__(256) contract_kernel(const float* __restrict__
                 }
             }
         }
-    }
+    };
+    // (a small map's wavefronts end within the first batch, after 7 of 16 steps at K = 437: leaving the others out is 13.1 -> 8.8 us
+    // there.  Among the whole batches of a large one the same branches keep loads and MFMAs apart: 173 -> 291 us at K = 1024,
+    // D = 2000, so those have none.)
+    int kb = k_lo;
+    for (; kb + 4 * kBatch <= k_hi; kb += 4 * kBatch) batch(kb, std::true_type{});
+    if (kb < k_hi) batch(kb, std::false_type{});
 #pragma unroll
     for (int q = 0; q < JT; ++q) {
         if (q > 0) __syncthreads();
