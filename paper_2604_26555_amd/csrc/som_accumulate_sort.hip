@@ -270,29 +270,38 @@ __global__ void __launch_bounds__(256) sort_sums_kernel(const float* __restrict_
     }
 }
 
-// a workgroup per node, 64 features at a time: sixteen runs of the node's segments, added up in order (a single segment's sums
-// are in S already; with a workgroup per 64 features their mere launch took 60 us at D = 2000)
+// a workgroup per node, 64 features at a time: a run of the node's segments per wavefront, added up in order (a single segment's
+// sums are in S already; with a workgroup per 64 features their mere launch took 60 us at D = 2000).  Sixteen loads under way in
+// a run, and eight runs, four where the workgroups are many and walk on: sixteen runs, four loads at a time, kept the chip in
+// wavefronts without a segment (K = 1024, D = 2000: 58 us, 21 now; D = 200: 16.7, 11; K = 4096, D = 50: 26.5, 21).
 __global__ void __launch_bounds__(1024) sort_finish_kernel(const double* __restrict__ part, const uint32_t* __restrict__ seg, int D,
                                                              int zero_first, double* __restrict__ S)
 {
     __shared__ double run[16][64];
-    const int l = threadIdx.x & 63, r = threadIdx.x >> 6;
+    const int l = threadIdx.x & 63, r = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int k = blockIdx.x;
-    const uint32_t first = seg[k], all = seg[k + 1] - first, per = (all + 15) / 16;
+    const uint32_t first = seg[k], all = seg[k + 1] - first, runs = blockDim.x >> 6, per = (all + runs - 1) / runs;
     if (all == 1 && zero_first) return;
     const uint32_t lo = r * per, hi = lo + per < all ? lo + per : all;
     for (int f0 = 64 * blockIdx.y; f0 < D; f0 += 64 * gridDim.y) {
         const int f = f0 + l;
         double s = 0.0;
-        if (f < D) {
-#pragma unroll 4
-            for (uint32_t q = lo; q < hi; ++q) s += part[(size_t)(first + q) * D + f];
+        const int fc = f < D ? f : D - 1;
+        for (uint32_t q0 = lo; q0 < hi; q0 += 16) {
+            double v[16];
+#pragma unroll
+            for (uint32_t u = 0; u < 16; ++u) {
+                v[u] = 0.0;
+                if (q0 + u < hi) v[u] = part[(size_t)(first + q0 + u) * D + fc];
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < 16; ++u) s += v[u];
         }
         run[r][l] = s;
         __syncthreads();
         if (r == 0 && f < D) {
 #pragma unroll
-            for (int q = 1; q < 16; ++q) s += run[q][l];
+            for (uint32_t q = 1; q < 16; ++q) s += q < runs ? run[q][l] : 0.0;
             const size_t e = (size_t)k * D + f;
             S[e] = (zero_first ? 0.0 : S[e]) + s;
         }
@@ -373,7 +382,7 @@ int accumulate_sort_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, co
     hipLaunchKernelGGL(kern, dim3(groups), dim3(256), 0, ctx->stream, X, D, ldx, start, seg, K, perm, (uint32_t)rows, slabs, part,
                        zero_first ? S : (double*)nullptr);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) sums launch")) return rc;
-    hipLaunchKernelGGL(sort_finish_kernel, dim3(K, D > 256 ? 4 : 1), dim3(1024), 0, ctx->stream, part, seg, D, zero_first ? 1 : 0, S);
+    hipLaunchKernelGGL(sort_finish_kernel, dim3(K, D > 256 ? 4 : 1), dim3(D > 256 ? 256 : 512), 0, ctx->stream, part, seg, D, zero_first ? 1 : 0, S);
     return check_hip(ctx, hipGetLastError(), "accumulate (sort) finish launch");
 }
 
