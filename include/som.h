@@ -161,7 +161,7 @@ int som_neighborhood_update(som_ctx* ctx, const double* S, const uint64_t* n, co
 /*
  * som_neighborhood_update for callers that cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and same results as som_neighborhood_update,
- * but the split-k partial sums (and the exponent shifts of SOM_SAFEGUARD_SHIFT) go to a fixed device array of 8.25 MiB
+ * but the split-k partial sums (and the exponent shifts of SOM_SAFEGUARD_SHIFT) go to a fixed device array of 4.25 MiB
  * that the library holds on each GPU it runs on until the process ends, instead of a workspace grown on demand; the
  * call makes no hipMalloc / hipFree and enqueues no memset (counters are cleared by a small kernel).
  * Limits: D <= 63, K <= 32768 and K * (D + 1) <= 65536 (for instance 1024 nodes x 63 features, 4096 x 15); larger

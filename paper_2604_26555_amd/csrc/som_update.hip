@@ -24,7 +24,24 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // kSplitK workgroups share a block of updated nodes where those alone leave the chip idle (their partials are stored, then
 // summed in order).  With sixteen stored partials whatever the shape, the partials were most of the traffic: 262 MB each way
 // at K = 1024, D = 2000 (207 + 53 us for contraction and finish there, 96 + 11 now; 228 + 28 -> 153 + 14 us at K = 4096, D = 50).
-constexpr int kSplitK = 4;
+constexpr int kSplitK = 8;
+
+// The shape of a contraction.  Two wavefronts for every SIMD, so that one's loads and exponentials run beside the other's MFMAs:
+// 4 per block of nodes and 64 columns, more parts where those are too few.  (One for every SIMD: K = 4096, D = 50 150 us, 100 with
+// two; K = 1024, D = 50 17.5, 12.6; K = 437, D = 37 8.8, 6.)
+struct UpdateShape {
+    int jt, blocks_j, blocks_c, splits;
+};
+static UpdateShape update_shape(int K, int D)
+{
+    UpdateShape u;
+    u.jt = K >= 2048 ? 2 : 1;
+    u.blocks_j = (K + 16 * u.jt - 1) / (16 * u.jt);
+    u.blocks_c = (D + 1 + 63) / 64;
+    const int64_t blocks = (int64_t)u.blocks_j * u.blocks_c;
+    u.splits = blocks >= 512 ? 1 : blocks >= 256 ? 2 : blocks >= 128 ? 4 : kSplitK;
+    return u;
+}
 
 // shift[j] = min over occupied nodes k of G[k][j]^2 (+inf when there is none): 16 columns per workgroup, every 64th row a thread,
 // eight loads under way.  A chain of loads is all there is: with 64 columns and runs of K / 16 rows, whose branches on n[k] kept
@@ -87,7 +104,7 @@ __global__ void __launch_bounds__(256) influence_kernel(const float* __restrict_
 // B[k = l / 16][c = l % 16] = S[k][c0 + c] (column D is n); its register r receives row l / 16 + 4 r, column l % 16.
 // JT = 2: two blocks of sixteen updated nodes per wavefront, for maps with enough of them: S is read half as often.
 template <bool FUSED, int JT>
-__global__ void __launch_bounds__(256) contract_kernel(const float* __restrict__ G, const double* __restrict__ H,
+__global__ void __launch_bounds__(256, 2) contract_kernel(const float* __restrict__ G, const double* __restrict__ H,
                                                        double inv2s2, const double* __restrict__ shift,
                                                        const double* __restrict__ S,
                                                        const unsigned long long* __restrict__ n, int K, int D,
@@ -114,7 +131,7 @@ __global__ void __launch_bounds__(256) contract_kernel(const float* __restrict__
     }
     // kBatch k-steps at a time: first every load of the batch (one wavefront per SIMD has nothing else to cover a
     // round trip to L2 with), then the exponentials, then the MFMAs.
-    constexpr int kBatch = 16 / JT;
+    constexpr int kBatch = FUSED ? 8 : 16 / JT;            // (sixteen with the exponentials take more than 256 registers: one wavefront)
     auto batch = [&](int kb, auto whole) {
         float gv[JT][kBatch];
         double nv[JT][kBatch], sv[kBatch][4];
@@ -179,7 +196,8 @@ __global__ void __launch_bounds__(256) contract_kernel(const float* __restrict__
 }
 
 // plain = true: w <- Num / Den (eta = 1, no momentum);  otherwise delta = eta (Num / Den - w) + mu v, w += delta
-__global__ void __launch_bounds__(256) finish_kernel(const double* __restrict__ part, int splits,
+template <int SPLITS>
+__global__ void __launch_bounds__(256) finish_kernel(const double* __restrict__ part,
                                                      const unsigned long long* __restrict__ n, int K, int D,
                                                      double eps_h, bool plain, double eta, double mu,
                                                      float* __restrict__ V, float* __restrict__ W,
@@ -191,7 +209,8 @@ __global__ void __launch_bounds__(256) finish_kernel(const double* __restrict__ 
         // guarded and empty nodes: one atomic per wavefront and counter (one per node, all on two words, took 20 us of a
         // 4096-node map's update)
         double den = 0.0;
-        for (int z = 0; z < splits; ++z) den += part[z * stride + (size_t)e * (D + 1) + D];
+#pragma unroll
+        for (int z = 0; z < SPLITS; ++z) den += part[z * stride + (size_t)e * (D + 1) + D];
         const unsigned long long guarded = __ballot(!(den >= eps_h)), empty = __ballot(n[e] == 0ull);
         if ((threadIdx.x & 63) == 0) {
             if (guarded) atomicAdd(&small[0], (int)__popcll(guarded));
@@ -202,7 +221,8 @@ __global__ void __launch_bounds__(256) finish_kernel(const double* __restrict__ 
     const int j = e / D, d = e % D;
     const double* row = part + (size_t)j * (D + 1);
     double num = 0.0, den = 0.0;
-    for (int z = 0; z < splits; ++z) {
+#pragma unroll
+    for (int z = 0; z < SPLITS; ++z) {
         num += row[z * stride + d];
         den += row[z * stride + D];
     }
@@ -217,7 +237,7 @@ __global__ void __launch_bounds__(256) finish_kernel(const double* __restrict__ 
     }
 }
 
-// the three launches of one update on the given workspaces: H [K*K] (only when D + 1 > 64), part [kSplitK*K*(D+1)],
+// the three launches of one update on the given workspaces: H [K*K] (only when D + 1 > 64), part [splits*K*(D+1)],
 // shift [K] (only with the shifted-exponent safeguard)
 static int update_launch(som_ctx* ctx, double* H, double* part, double* shift_ws, const double* S,
                          const unsigned long long* n, const float* G, int32_t K, int32_t D, double sigma, double eps_h,
@@ -225,12 +245,9 @@ static int update_launch(som_ctx* ctx, double* H, double* part, double* shift_ws
 {
     const size_t h_elems = (size_t)K * K;
     const double inv2s2 = 1.0 / (2.0 * sigma * sigma);
-    // two wavefronts for every SIMD, so that one's loads and exponentials run beside the other's MFMAs: 4 per block of nodes and
-    // 64 columns, more splits where those are too few (one for every SIMD: 150 us at K = 4096, D = 50, and 100 with two)
-    const int jt = K >= 2048 ? 2 : 1;
-    const int blocks = ((K + 16 * jt - 1) / (16 * jt)) * ((D + 1 + 63) / 64);
-    const int splits = blocks >= 512 ? 1 : blocks >= 256 ? 2 : kSplitK;
-    const dim3 grid((K + 16 * jt - 1) / (16 * jt), (D + 1 + 63) / 64, splits);
+    const UpdateShape u = update_shape(K, D);
+    const int jt = u.jt, splits = u.splits;
+    const dim3 grid(u.blocks_j, u.blocks_c, splits);
     double* shift = nullptr;
     if (ctx->safeguard == SOM_SAFEGUARD_SHIFT) {
         shift = shift_ws;
@@ -250,7 +267,8 @@ static int update_launch(som_ctx* ctx, double* H, double* part, double* shift_ws
     }
     if (int rc = check_hip(ctx, hipGetLastError(), "contraction kernel launch")) return rc;
     const bool plain = ctx->eta == 1.0 && ctx->mu == 0.0;
-    hipLaunchKernelGGL(finish_kernel, dim3((K * D + 255) / 256), dim3(256), 0, ctx->stream, part, splits, n, K, D, eps_h, plain,
+    auto finish = splits == 1 ? finish_kernel<1> : splits == 2 ? finish_kernel<2> : splits == 4 ? finish_kernel<4> : finish_kernel<kSplitK>;
+    hipLaunchKernelGGL(finish, dim3((K * D + 255) / 256), dim3(256), 0, ctx->stream, part, n, K, D, eps_h, plain,
                        ctx->eta, ctx->mu, ctx->velocity, W, small);
     return check_hip(ctx, hipGetLastError(), "update finish launch");
 }
@@ -259,7 +277,8 @@ int update_run(som_ctx* ctx, const double* S, const unsigned long long* n, const
                double sigma, double eps_h, float* W, int32_t* small)
 {
     const size_t h_elems = (size_t)K * K;
-    const size_t need = (h_elems + (size_t)kSplitK * K * (D + 1) + K) * sizeof(double);
+    const size_t parts = (size_t)update_shape(K, D).splits * K * (D + 1);
+    const size_t need = (h_elems + parts + K) * sizeof(double);
     if (need > ctx->upd_bytes) {
         if (ctx->upd_blob) {
             if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync before workspace growth")) return rc;
@@ -275,7 +294,7 @@ int update_run(som_ctx* ctx, const double* S, const unsigned long long* n, const
     }
     double* H = (double*)ctx->upd_blob;
     double* part = H + h_elems;
-    return update_launch(ctx, H, part, part + (size_t)kSplitK * K * (D + 1), S, n, G, K, D, sigma, eps_h, W, small);
+    return update_launch(ctx, H, part, part + parts, S, n, G, K, D, sigma, eps_h, W, small);
 }
 
 // ---------------------------------------------------------------------------------------------------------
