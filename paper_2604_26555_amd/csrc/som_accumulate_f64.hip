@@ -31,9 +31,13 @@ namespace som {
 constexpr int kFThreads = 1024;
 constexpr size_t kFLdsBytes = 150 * 1024;     // slab
 
-// GATHER: rows are taken through the index list (a scalar load per row; kept out of the plain variant because its
-// wait would also wait for the LDS atomics in flight)
-template <bool GATHER>
+// GATHER: rows are taken through the index list.  A pass's row numbers are one vector load, requested with its ballot, and a row's is
+// read off its lane: as a scalar load per row each batch waited for them (10^6 listed rows of 50 features on 1024 nodes 93 -> 80 us).
+// R: rows to a load and an LDS instruction.  An LDS atomic takes its 15.6 cycles whatever its width, so rows of up to 15 features
+// share one by four and of up to 31 by two: 10^7 x 12 on 1024 nodes 221 -> 193 us, 10^7 x 28 308 -> 286; through a list 439 -> 257
+// and 622 -> 412; 10^5 x 5 on 400 17.9 -> 14.5.  (Four rows have eight loads under way: with sixteen their addresses do not fit the
+// scalar registers, 10^6 x 8 33 us instead of 30.)
+template <bool GATHER, int R>
 __global__ void __launch_bounds__(kFThreads) accumulate_f64_kernel(const float* __restrict__ X, int D, int64_t ldx,
                                                                    const uint32_t* __restrict__ idx, int64_t m,
                                                                    const int32_t* __restrict__ bmu, int K, int ks,
@@ -59,7 +63,9 @@ __global__ void __launch_bounds__(kFThreads) accumulate_f64_kernel(const float* 
     for (int c = tid; c < ks * DS; c += kFThreads) P[c] = 0.0;
     __syncthreads();
 
-    constexpr int G = 16;                                                 // rows in flight per wavefront
+    constexpr int G = R == 4 ? 8 : 16;                                           // row loads in flight per wavefront, of R rows each
+    constexpr int L = 64 / R;                                             // lanes of a row
+    const int fl = lane & (L - 1);
     constexpr int U = 4;                                                  // 64-row passes per load of BMU indices
     // A wavefront takes 64 U consecutive samples at a time: lane l holds the BMUs of samples base + U l .. + U - 1
     // (one 16-byte load, requested a whole round of U passes ahead: with one pass per load the wait for the indices
@@ -100,56 +106,93 @@ __global__ void __launch_bounds__(kFThreads) accumulate_f64_kernel(const float* 
             // with, so whole batches (sixteen rows, then eight, then four) run without per-row conditions, three
             // scalar instructions a row; what is left of the pass goes through one batch of four places whose empty
             // ones repeat the last row's load and skip the addition.
-            int left = __popcll(todo);
-            const int f = lane - 1;                                         // lane 0 carries the count
+            int left = __popcll(todo), p_last = 0;
+            const int f = fl - 1;                                           // a row's first lane carries the count
             const int fcl = f < 0 ? 0 : (f < D ? f : D - 1);
+            const uint32_t row_of_lane = (GATHER && in) ? idx[base + U * lane + q] : 0u;
+            // The next R rows of the mask, one to each group of L lanes: the row's first float and its cells.  Behind the last row
+            // it is repeated; the group's `live` tells.
+            auto take = [&](auto all_there, int& cell, bool& live) -> const float* {
+                if constexpr (R == 1) {
+                    int p;
+                    if constexpr (decltype(all_there)::value) {
+                        p = __builtin_ctzll(todo);
+                        asm("s_bitset0_b64 %0, %1" : "+s"(todo) : "s"(p));
+                        live = true;
+                    } else {
+                        live = todo != 0ull;
+                        p = live ? (int)__ffsll((long long)todo) - 1 : p_last;
+                        if (live) {
+                            todo &= todo - 1ull;
+                            p_last = p;
+                        }
+                    }
+                    cell = __builtin_amdgcn_readlane(ncell, p);
+                    // plain variant: 32-bit offset from the pass's first row (63 U rows of ldx floats stay far below 2^31)
+                    return GATHER ? X + (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)row_of_lane, p) * ldx : xpass + (unsigned)(p * ldxu);
+                } else {
+                    int c = 0;
+                    unsigned at = 0u;
+                    live = true;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        int p;
+                        bool on = true;
+                        if constexpr (decltype(all_there)::value) {
+                            p = __builtin_ctzll(todo);
+                            asm("s_bitset0_b64 %0, %1" : "+s"(todo) : "s"(p));
+                        } else {
+                            on = todo != 0ull;
+                            p = on ? (int)__ffsll((long long)todo) - 1 : p_last;
+                            if (on) {
+                                todo &= todo - 1ull;
+                                p_last = p;
+                            }
+                        }
+                        const int cp = __builtin_amdgcn_readlane(ncell, p);
+                        const unsigned ap = GATHER ? (unsigned)__builtin_amdgcn_readlane((int)row_of_lane, p) : (unsigned)(p * ldxu);
+                        const bool mine = lane >= r * L;
+                        c = mine ? cp : c;
+                        at = mine ? ap : at;
+                        live = mine ? on : live;
+                    }
+                    cell = c;
+                    return GATHER ? X + (int64_t)at * ldx : xpass + at;
+                }
+            };
             auto whole_batch = [&](auto width) {
                 constexpr int GB = decltype(width)::value;
                 float v[GB];
                 int cell[GB];
 #pragma unroll
                 for (int t = 0; t < GB; ++t) {
-                    const int p = __builtin_ctzll(todo);                    // todo has at least GB bits set here
-                    asm("s_bitset0_b64 %0, %1" : "+s"(todo) : "s"(p));
-                    // plain variant: 32-bit offset from the pass's first row (63 U rows of ldx floats stay far
-                    // below 2^31)
-                    const float* xrow = GATHER ? X + (int64_t)idx[base + U * p + q] * ldx : xpass + (unsigned)(p * ldxu);
-                    cell[t] = __builtin_amdgcn_readlane(ncell, p);
-                    const float xv = xrow[fcl];
-                    v[t] = (lane == 0) ? 1.0f : xv;
+                    bool live;
+                    const float xv = take(std::true_type{}, cell[t], live)[fcl];        // (todo has at least GB R bits set here)
+                    v[t] = (fl == 0) ? 1.0f : xv;
                 }
-                if (lane < DS) {
+                if (fl < DS) {
 #pragma unroll
-                    for (int t = 0; t < GB; ++t) unsafeAtomicAdd(&P[cell[t] + lane], (double)v[t]);
+                    for (int t = 0; t < GB; ++t) unsafeAtomicAdd(&P[cell[t] + fl], (double)v[t]);
                 }
-                left -= GB;
+                left -= GB * R;
             };
-            while (left >= G) whole_batch(std::integral_constant<int, G>{});
-            if (left >= G / 2) whole_batch(std::integral_constant<int, G / 2>{});
-            if (left >= G / 4) whole_batch(std::integral_constant<int, G / 4>{});
+            while (left >= G * R) whole_batch(std::integral_constant<int, G>{});
+            if (left >= G / 2 * R) whole_batch(std::integral_constant<int, G / 2>{});
+            if (left >= G / 4 * R) whole_batch(std::integral_constant<int, G / 4>{});
             if (left > 0) {
                 constexpr int GB = G / 4;
                 float v[GB];
                 int cell[GB];
                 bool live[GB];
-                int p_last = 0;
 #pragma unroll
                 for (int t = 0; t < GB; ++t) {
-                    live[t] = todo != 0ull;
-                    const int p = live[t] ? (int)__ffsll((long long)todo) - 1 : p_last;
-                    if (live[t]) {
-                        todo &= todo - 1ull;
-                        p_last = p;
-                    }
-                    const float* xrow = GATHER ? X + (int64_t)idx[base + U * p + q] * ldx : xpass + (unsigned)(p * ldxu);
-                    cell[t] = __builtin_amdgcn_readlane(ncell, p);
-                    const float xv = xrow[fcl];
-                    v[t] = (lane == 0) ? 1.0f : xv;
+                    const float xv = take(std::false_type{}, cell[t], live[t])[fcl];
+                    v[t] = (fl == 0) ? 1.0f : xv;
                 }
 #pragma unroll
                 for (int t = 0; t < GB; ++t) {
                     if (live[t]) {
-                        if (lane < DS) unsafeAtomicAdd(&P[cell[t] + lane], (double)v[t]);
+                        if (fl < DS) unsafeAtomicAdd(&P[cell[t] + fl], (double)v[t]);
                     }
                 }
             }
@@ -244,7 +287,10 @@ int accumulate_f64_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, con
     }
     double* part = (double*)ctx->acc_blob;
     const dim3 grid((unsigned)(ranges_padded * nslabs));
-    auto kern = idx ? accumulate_f64_kernel<true> : accumulate_f64_kernel<false>;
+    const int together = window < 16 ? 4 : window < 32 ? 2 : 1;          // rows to a load and an addition: as fit 64 lanes
+    auto kern = together == 4 ? (idx ? accumulate_f64_kernel<true, 4> : accumulate_f64_kernel<false, 4>)
+                : together == 2 ? (idx ? accumulate_f64_kernel<true, 2> : accumulate_f64_kernel<false, 2>)
+                                : (idx ? accumulate_f64_kernel<true, 1> : accumulate_f64_kernel<false, 1>);
     if (int rc = check_hip(ctx,
                            hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFLdsBytes),

@@ -321,6 +321,29 @@ def test_accumulation_by_sort_at_its_limits(som, reproducible, m, K, D):
         som.som_set_reproducible(False)
 
 
+@pytest.mark.parametrize("listed", [False, True])
+@pytest.mark.parametrize("m,K,D", [(20_011, 300, 4), (20_011, 1025, 15), (20_011, 1100, 16), (70_001, 700, 31), (70_001, 700, 32), (999, 2300, 15),
+                                   (1, 5, 7), (66, 1, 9), (257, 3, 30), (5000, 4000, 14)])
+def test_accumulation_of_several_rows_together(som, listed, m, K, D):
+    """Four rows of up to 15 features, two of up to 31: whole and partial batches, one and several slabs, one node for many rows."""
+    gen = torch.Generator(device="cuda").manual_seed(m + K + D)
+    X = torch.randn((3 * m if listed else m, D + 1), device="cuda", generator=gen)[:, :D]
+    idx = torch.randperm(3 * m, device="cuda", generator=gen)[:m].int() if listed else None
+    bmu = (torch.rand(m, device="cuda", generator=gen) ** 3 * K).int().clamp_(max=K - 1)
+    S = torch.full((K, D), 7.0, device="cuda", dtype=torch.float64)
+    n = torch.full((K,), 7, device="cuda", dtype=torch.int64)
+    som.som_accumulate(X, bmu, K, S, n, idx=idx)
+    rows_, b = (X if idx is None else X[idx.long()]).double().cpu().numpy(), bmu.cpu().numpy()
+    want = np.zeros((K, D))
+    np.add.at(want, b, rows_)
+    size = np.zeros((K, D))
+    np.add.at(size, b, np.abs(rows_))
+    count = np.bincount(b, minlength=K)
+    assert np.array_equal(n.cpu().numpy(), count)
+    # n_k roundings of sums below the sum of magnitudes, on both sides
+    assert (np.abs(S.cpu().numpy() - want) <= 2 * count[:, None] * 2.0 ** -53 * size).all()
+
+
 @pytest.mark.parametrize("m,K,D,ldx", [(40, 16, 8, 1 << 22), (33, 300, 70, (1 << 22) + 3), (650_000, 200, 1000, 1000), (700_001, 3, 900, 900)])
 def test_accumulation_by_sort_of_rows_far_apart_and_of_large_matrices(som, m, K, D, ldx):
     """Strides beyond the slab kernel's offsets; matrices beyond 2.5 GB, whose segments are shorter: float64 sums in both."""
