@@ -166,23 +166,6 @@ __device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& 
     lo = __builtin_bit_cast(bf16x8, l);
 }
 
-// the same, and what the first parts leave over is added to left2 (squares)
-__device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo, float& left2)
-{
-    uint4 h, l;
-    uint32_t* hp = &h.x;
-    uint32_t* lp = &l.x;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const SplitPair p(v[2 * i], v[2 * i + 1]);
-        hp[i] = p.hi;
-        lp[i] = p.lo;
-        left2 = fmaf(p.left1, p.left1, fmaf(p.left0, p.left0, left2));
-    }
-    hi = __builtin_bit_cast(bf16x8, h);
-    lo = __builtin_bit_cast(bf16x8, l);
-}
-
 // the same with the squares of the first parts, of the second parts and of what both leave over
 __device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& lo, float& hi2, float& lo2, float& rest2)
 {

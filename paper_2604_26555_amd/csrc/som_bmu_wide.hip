@@ -30,6 +30,28 @@
 
 namespace som {
 
+// Eight values as two bf16 parts each, one by one.  (As pairs, which is what the narrow search's prologue takes, this tile has eleven
+// registers spilled instead of five, and 10^6 x 200 on 1024 nodes takes 1 to 2 % longer.)
+__device__ __forceinline__ void cut8(const float (&v)[8], bf16x8& hi, bf16x8& lo)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        hi[i] = (__bf16)v[i];
+        lo[i] = (__bf16)(v[i] - (float)hi[i]);
+    }
+}
+// the same, and what the first parts leave over is added to left2 (squares)
+__device__ __forceinline__ void cut8(const float (&v)[8], bf16x8& hi, bf16x8& lo, float& left2)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        hi[i] = (__bf16)v[i];
+        const float left = v[i] - (float)hi[i];
+        lo[i] = (__bf16)left;
+        left2 = fmaf(left, left, left2);
+    }
+}
+
 constexpr int kWThreads = 512;
 constexpr int kWTile = 256;                       // samples, and nodes, of a tile
 constexpr int kWChunk = 32;                       // features of a chunk
@@ -101,7 +123,7 @@ __global__ void __launch_bounds__(256) bmu_wide_prep_kernel(const float* __restr
             v[4 * h + 3] = shift <= 3 ? w4.w - c4.w : 0.0f;
         }
         bf16x8 hi, lo;
-        split8(v, hi, lo, lo2);
+        cut8(v, hi, lo, lo2);
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             nrm += (double)v[t] * (double)v[t];
@@ -197,11 +219,11 @@ __device__ __forceinline__ void wide_tile(const BmuArgs& a, const WideArgs& p, i
         }
         bf16x8 hi, lo;
         if (!CAND && norms) {
-            split8(v, hi, lo, left2[it]);
+            cut8(v, hi, lo, left2[it]);
 #pragma unroll
             for (int t = 0; t < 8; ++t) xs[it] = fmaf(v[t], v[t], xs[it]);
         } else {
-            split8(v, hi, lo);
+            cut8(v, hi, lo);
         }
         const int s = (tid >> 2) + 128 * it;
         char* frag = bufB + buf * kWBuf + ((s >> 5) * 4 + (oct >> 1) * 2) * 1024 + ((oct & 1) * 32 + ((s & 31) ^ (2 * oct))) * 16;
