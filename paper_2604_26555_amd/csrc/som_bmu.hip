@@ -1265,7 +1265,8 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // operands of its stage's last block, are issued during the block before that barrier and waited for before
     // it, so once a wavefront is past the barrier of stage s the buffer of stage s is free for stage s + 2, which
     // nobody writes before the middle of stage s + 1; and the barrier of stage s stands between every wavefront's
-    // writes of stage s + 1 and the first reads of it.
+    // writes of stage s + 1 and the first reads of it.  That holds within a tile: a partial last stage (below) is read with no
+    // barrier behind it, so who takes another tile with the same LDS puts one in between.
     constexpr int NB = kNodesPerStage / 32;
     static_assert(NB == 4, "two blocks, the LDS writes, one block, the barrier, one block");
     // A last stage that ends in whole blocks of padding nodes (K = 400: a fifth of all blocks) is left to the code behind the
@@ -1502,6 +1503,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
         asm volatile("" : "+s"(b.centre), "+s"(b.D), "+s"(b.tail_r), "+s"(b.K));
         if (t < full) bmu_split_tile<KB, TAIL, MS, true>(b, 0, t, count, lds4);
         else bmu_split_tile<KB, TAIL, MS / 2, true>(b, (int64_t)full * per_tile, t - full, count, lds4);
+        // The next tile starts by filling buffer 0, and a tile's last stage, where it is a partial one, is read behind the tile's
+        // last barrier: from buffer 0 with an odd number of stages.  (A wavefront there may be far behind the others: it may have
+        // had its queue to serve.)
+        __syncthreads();
     }
 }
 

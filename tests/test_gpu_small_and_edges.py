@@ -368,6 +368,9 @@ def test_accumulation_by_sort_of_rows_far_apart_and_of_large_matrices(som, m, K,
     (20_000, 1024, 512, 50), (20_000, 1000, 333, 25), (20_000, 1024, 256, 37),      # two, three and four nodes exactly as near: the pair list
     (3000, 1024, 256, 50), (20_000, 1024, 60, 64), (20_000, 4096, 500, 20),         # more: the candidate pass (short lists: all nodes)
     (20_000, 1024, 4, 50), (20_000, 640, 3, 64), (20_001, 130, 2, 8),               # so many that its queues overflow
+    # every row on the list, so that its workgroups take two tiles, whose last stage is a partial one in the first tile's buffer
+    # (K mod 256 in 33 ... 96): few candidates, and so many that the queues are served between the stages; half tiles, full ones
+    (20_000, 300, 60, 50), (20_000, 576, 96, 37), (20_001, 340, 68, 20), (20_000, 300, 25, 50), (20_000, 576, 48, 37), (150_000, 289, 29, 12),
 ])
 def test_bmu_exact_ties_over_many_nodes(som, m, K, bases, D):
     """Every node is one of `bases` rows far apart, so each sample has K / bases winners that are exactly as near: the lowest index,
