@@ -1039,15 +1039,15 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             xa += __shfl_xor(xa, 32);
             lo2 += __shfl_xor(lo2, 32);
             rest2 += __shfl_xor(rest2, 32);
-            const float lo_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.norms[1])) * 1.001f;
-            const float rest_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.norms[2])) * 1.001f;
+            const float lo_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.norms[1]) + kSquaresFloor) * 1.001f;
+            const float rest_w = __builtin_amdgcn_sqrtf(__uint_as_float(a.norms[2]) + kSquaresFloor) * 1.001f;
             // |xl| (before its own cut) and |x| are at most what their parts add up to
-            const float nr = __builtin_amdgcn_sqrtf(rest2 + kRestFloor) * 1.0001f;
-            const float nl = __builtin_amdgcn_sqrtf(lo2) * 1.0001f + nr, nh = __builtin_amdgcn_sqrtf(hi2) * 1.0001f;
+            const float nr = __builtin_amdgcn_sqrtf(rest2 + kSquaresFloor) * 1.0001f;
+            const float nl = __builtin_amdgcn_sqrtf(lo2 + kSquaresFloor) * 1.0001f + nr, nh = __builtin_amdgcn_sqrtf(hi2 + kSquaresFloor) * 1.0001f;
             const float nx = nh + nl;
             constexpr float unit = 5.9604645e-08f;
             stash[(3 * mb + 0) * kThreads] = nx;
-            stash[(3 * mb + 1) * kThreads] = nr * 1.0078125f + nl * (32.64f * KB * unit) + __builtin_amdgcn_sqrtf(xa) * (1.0001f * 16.256f * unit) + nx * (6.0f * unit);
+            stash[(3 * mb + 1) * kThreads] = nr * 1.0078125f + nl * (32.64f * KB * unit) + __builtin_amdgcn_sqrtf(xa + kSquaresFloor) * (1.0001f * 16.256f * unit) + nx * (6.0f * unit);
             stash[(3 * mb + 2) * kThreads] = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (32.64f * KB * unit));
         }
     }

@@ -18,7 +18,11 @@ __device__ __forceinline__ double wave_sum(double v)
 
 constexpr int kScalLo = 8;        // scal[8], scal[9]: bits of the largest |w - hi|^2 and |w - hi - lo|^2 (split search)
 
-constexpr float kRestFloor = 1e-37f;          // added to rest2 (split8): covers squares that underflow
+// Added to the sums of squares that enter a bound before their root is taken: v_sqrt_f32 returns zero for a subnormal number, which
+// would take up to 2^-63 from a norm.  The sums themselves keep subnormal squares, those by v_dot2c_f32_bf16 (square2) as
+// well as those by fma (seen for squares and sums of 2^-112 to 2^-142), and what is lost below that, 2^-149 a square, is
+// covered too.
+constexpr float kSquaresFloor = 1e-37f;
 
 constexpr float kSplitPadNorm = -3.0e38f;     // padding nodes of the split search: finite, so that position bits cannot make a NaN
 
@@ -144,7 +148,7 @@ struct SplitPair {
     }
 };
 
-// sum + the squares of a pair of parts (v_dot2c_f32_bf16: for norms that enter bounds with a factor to spare)
+// sum + the squares of a pair of parts (v_dot2c_f32_bf16: for norms that enter bounds with a factor to spare and kSquaresFloor)
 __device__ __forceinline__ float square2(uint32_t p, float sum)
 {
     const bf16x2 v = __builtin_bit_cast(bf16x2, p);

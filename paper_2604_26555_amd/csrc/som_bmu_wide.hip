@@ -532,11 +532,11 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
         constexpr float unit = 5.9604645e-08f;
         auto root = [](float v) { return __builtin_amdgcn_sqrtf(v); };      // within a unit in the last place
         const float wmax2 = __uint_as_float(a.scal[0]), wmax = root(wmax2) * 1.00001f;
-        const float lo_w = root(__uint_as_float(a.scal[kScalLo])) * 1.001f, rest_w = root(__uint_as_float(a.scal[kScalLo + 1])) * 1.001f;
+        const float lo_w = root(__uint_as_float(a.scal[kScalLo]) + kSquaresFloor) * 1.001f, rest_w = root(__uint_as_float(a.scal[kScalLo + 1]) + kSquaresFloor) * 1.001f;
         // (float32 sums over up to 2^13 squares in this order are within 2^-14 of their own size)
-        const float nx = root(n.x) * 1.0002f, nl = root(n.z) * 1.0002f;
+        const float nx = root(n.x + kSquaresFloor) * 1.0002f, nl = root(n.z + kSquaresFloor) * 1.0002f;
         const float add = (float)(p.nch + 1) * 1.016f;
-        const float err_w = nl * (1.0078125f / 256.0f + 65.28f * unit) + root(n.y) * (1.0002f * 16.256f * unit) + nx * ((6.0f + add) * unit);
+        const float err_w = nl * (1.0078125f / 256.0f + 65.28f * unit) + root(n.y + kSquaresFloor) * (1.0002f * 16.256f * unit) + nx * ((6.0f + add) * unit);
         const float err_0 = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (65.28f * unit));
         const float err_n = 0.5f * (6.0f + add) * unit;
         const float wn = -2.0f * p.norms[node];

@@ -386,6 +386,18 @@ def test_bmu_exact_ties_over_many_nodes(som, m, K, bases, D):
     assert np.array_equal(b.cpu().numpy(), first[near])
 
 
+@pytest.mark.parametrize("m,K,D", [(20_000, 512, 17), (20_000, 512, 50), (20_000, 512, 64), (20_000, 512, 100)])
+def test_bmu_where_squares_of_the_parts_underflow(som, m, K, D):
+    """Rows of about 10^-17: what the first bf16 part leaves over has squares around the smallest normal number, below which the
+    hardware's root returns zero; every node has another one close by, so that the bounds formed from those squares decide who is listed."""
+    rng = np.random.default_rng(D)
+    base = rng.uniform(-10, 10, (K // 2, D))
+    W = (np.concatenate([base, base + rng.normal(size=base.shape) * 0.02]) * 2.0 ** -58).astype(np.float32)
+    X = ((base[rng.integers(K // 2, size=m)] + rng.normal(size=(m, D)) * 0.05) * 2.0 ** -58).astype(np.float32)
+    b, _, _ = som.som_bmu(dev(X), dev(W))
+    check_units(b.cpu().numpy(), X, W)
+
+
 @pytest.mark.parametrize("shape,K", [("chain", 2), ("chain", 3), ("chain", 65), ("chain", 1500), ("star", 4), ("star", 70), ("star", 300),
                                      ("comb", 66), ("comb", 513), ("random", 1), ("random", 1025), ("random", 2500)])
 def test_spanning_tree_hops_of_every_shape(som, shape, K):
