@@ -533,17 +533,19 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
         auto root = [](float v) { return __builtin_amdgcn_sqrtf(v); };      // within a unit in the last place
         const float wmax2 = __uint_as_float(a.scal[0]), wmax = root(wmax2) * 1.00001f;
         const float lo_w = root(__uint_as_float(a.scal[kScalLo]) + kSquaresFloor) * 1.001f, rest_w = root(__uint_as_float(a.scal[kScalLo + 1]) + kSquaresFloor) * 1.001f;
-        // (float32 sums over up to 2^13 squares in this order are within 2^-14 of their own size)
-        const float nx = root(n.x + kSquaresFloor) * 1.0002f, nl = root(n.z + kSquaresFloor) * 1.0002f;
+        // (four float32 sums of 8 nch squares each, added up: short of their size by one rounding a square at most, half of that in
+        // the root; 1 + 2^-13 at D = 16384)
+        const float grown = 1.0001f + (float)p.nch * (4.1f * unit);
+        const float nx = root(n.x + kSquaresFloor) * grown, nl = root(n.z + kSquaresFloor) * grown;
         const float add = (float)(p.nch + 1) * 1.016f;
-        const float err_w = nl * (1.0078125f / 256.0f + 65.28f * unit) + root(n.y + kSquaresFloor) * (1.0002f * 16.256f * unit) + nx * ((6.0f + add) * unit);
+        const float err_w = nl * (1.0078125f / 256.0f + 65.28f * unit) + root(n.y + kSquaresFloor) * (grown * 16.256f * unit) + nx * ((6.0f + add) * unit);
         const float err_0 = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (65.28f * unit));
         const float err_n = 0.5f * (6.0f + add) * unit;
         const float wn = -2.0f * p.norms[node];
         const float wb = fminf(root(wn) * 1.00001f, wmax);
         const float err_b = err_w * wb + err_0 + err_n * wb * wb;
         const float bits = fabsf(best) * (1.01f * 1.9073486e-06f);          // two scores' position bits
-        const float far2 = fmaxf(n.x * 1.0002f - 2.0f * best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
+        const float far2 = fmaxf(nx * nx * 1.00001f - 2.0f * best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
         const float wo = fminf((nx + root(far2)) * 1.0001f, wmax);          // norm of any node as near as the winner
         const float bound = err_b + err_w * wo + err_0 + err_n * wo * wo + bits;
         close = a.K > 1 && !((best - second) > bound);

@@ -266,7 +266,7 @@ def test_wide_search_at_the_limits_of_its_records(som, m, K):
 
 
 @pytest.mark.parametrize("m,K,D", [(500, 1700, 70), (257, 1281, 65), (255, 2560, 97), (513, 769, 128), (300, 4353, 66), (1, 700, 80),
-                                   (2049, 257, 96), (100, 255, 127)])
+                                   (2049, 257, 96), (100, 255, 127), (300, 40, 30_000)])
 def test_wide_search_with_ragged_splits(som, m, K, D):
     """Node tiles that do not divide among the workgroups of a sample tile, last tiles of a few nodes, sample tiles of one row."""
     X, W = rows(200 + K, m, D), rows(201 + K, K, D)
