@@ -181,7 +181,8 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
 //     one MFMA.
 //   * Norms: -|w|^2 / 2 behind the stage's rows (and as three bf16 parts in the packed block), the largest norms of the nodes
 //     and of what the bf16 cut leaves over (w - hi, w - hi - lo) in scal.
-// The result words of this call were cleared by the call before; this one clears the next one's (scal_next).
+// Clears the result words that the later kernels of the call count into; the maxima it adds to (tops) were left zero by the
+// re-decision of the call before.
 // ---------------------------------------------------------------------------------------------------------
 // Which node a row of the stages holds.  The search keeps its winners by class of rows (bits 0, 2 and 5 of the row: bmu_split_tile), and
 // a near tie within one class costs a pass of its own, so nodes that come close should fall into different classes: the rows of a
@@ -189,7 +190,11 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
 // two elements, modulo x^3 + x^2 + 1 (bit i adds kClassOf[i % 7]).  Two nodes next to each other on a lattice, whatever its width
 // from 8 to 64, then share a class in 5 % of the cases on average and 11 % at worst (in a diagonal 14 and 24, two columns or rows
 // on 5 and 10); with nodes in their own order 6 and 50 (11 and 75, 38 and 77).  Samples left to the candidate pass, 10^6 x 50 on
-// 64 x 64 nodes: 254,000 then, 79,000 now; on 32 x 32 36,000 and 23,000; on 20 x 20 (500,000 x 64) 1,500 and 6,000.
+// 64 x 64 nodes: 254,000 then, 79,000 now (an epoch 1.62 -> 1.41 ms); on 32 x 32 36,000 and 23,000 (422 -> 416 us).  Lattices whose
+// own order happens to separate their neighbours lose a little: 20 x 20, 500,000 x 64 1,500 and 6,000 (233 us both), 900,000
+// x 25 with distances 300 and 2,500 (154 -> 158 us).  No order that does not know the lattice avoids that: over the widths, a node's
+// neighbours in the next row fall into each of eight classes about equally often, so the mean over widths, 0 along the rows and
+// 1/8 across, cannot be much below the 6.5 % of this one.
 constexpr unsigned class_mask(int bit)                    // the bits of a node's number, from bit 3 on, that flip this bit of its class
 {
     constexpr unsigned kClassOf[7] = {1, 2, 4, 5, 7, 3, 6};
@@ -774,10 +779,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
 // The same search with the contraction on the bf16 matrix pipe (this kernel: 4 <= D <= 64, som_bmu_wide.hip: D > 64; the default for every map of more than one node).
 //
 // A float32 value v is cut into two bf16 parts, hi = bf16(v) and lo = bf16(v - hi) (both rounded to nearest, the
-// difference is exact in float32), so that |v - hi - lo| <= 2^-18 |v|.  A score then takes three bf16 MFMAs per 16
-// features (v_mfma_f32_32x32x16_bf16, products exact, float32 accumulation):
+// difference is exact in float32), so that |v - lo - hi| <= 2^-16 |v| (2^-8 from each part's eight significant bits).  A score then
+// takes three bf16 MFMAs per 16 features (v_mfma_f32_32x32x16_bf16, products exact, float32 accumulation):
 //     x . w  ~  xh . wh + xl . wh + xh . wl,
-// the dropped parts together below 3 * 2^-18 |x| |w|.  The bf16 pipe runs these three in 96 cycles where the
+// the dropped parts together below 3 * 2^-16 |x| |w|.  The bf16 pipe runs these three in 96 cycles where the
 // float32 MFMAs of the same 16 features take 512, and unlike those it leaves three quarters of the vector issue
 // slots to the fold, which runs beside it.  Nothing else changes: the error bound is wider (the split, and the pipe's
 // accumulation error per MFMA, charged as any-order float32 summation), samples inside it go on the same list and are decided by the same direct
@@ -808,7 +813,7 @@ constexpr int kSplitMS = 2;
 // a lane an entry, so that lanes share the work whosever samples' it is, and the nearest candidate of each sample is kept as the
 // least (distance, node) in one 64-bit word.  (With up to seven ids in each lane's registers, every lane walked the longest
 // set of its wavefront, and samples with more went to the all-nodes pass.)  10^6 x 50 on
-// 64 x 64 nodes: pass and all-nodes pass 430 + 284 us then, 352 + 23 with the queue.
+// 64 x 64 nodes, 254,000 entries: pass and all-nodes pass 430 + 284 us then, 352 + 23 with the queue.
 struct CandQueue {
     static constexpr size_t kFixed = 64 * (sizeof(unsigned long long) + sizeof(uint32_t));
     unsigned long long* nearest;     // [64] per sample of the tile
@@ -1459,8 +1464,9 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     int near = 0;
     if (r_valid) {
         if (a.qe) {
-            // The statistic n_recheck counts the near ties: best two scores inside a band of fixed relative width, 3 * 2^-18 for
-            // the cut and all MFMAs at the full magnitude.  Only those that this sample's own bound leaves open are listed.
+            // The statistic n_recheck counts the near ties: best two scores inside a band of fixed relative width, which takes 3 * 2^-18
+            // for the cut (four times less than it can lose: a figure to compare runs by, not a bound) and all MFMAs at the full
+            // magnitude.  Only those that this sample's own bound leaves open are listed.
             constexpr float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(49 * KB + (TAIL ? 17 : 0) + 1) * 5.9604645e-08f + 1.9073486e-06f) +
                                   12.0f * 5.9604645e-08f;
             const float band = 0.5f * rel * ((xl2 * wb + 0.5f * wb * wb) + (xl2 * wmax + 0.5f * wmax2));

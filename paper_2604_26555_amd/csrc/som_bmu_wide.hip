@@ -11,10 +11,13 @@
 // Data path.  The weights are cut once per preparation and stored in the order in which the MFMA's lanes take them, so a
 // chunk of a node tile is 32 KB that go straight from memory to LDS (global_load_lds_dwordx4).  The samples are read in
 // float32, 128 contiguous bytes of a row per four lanes, centred, cut and written to LDS by the workgroup itself, for
-// every node tile again: the vector instructions (64 per thread and chunk) run beside 48 MFMAs, while a conversion pass
-// of its own would move every row twice more through memory (it took 0.3 ms of 3.2 at 10^6 x 200).  Both operands are
+// every node tile again, beside the MFMAs; a conversion pass of its own moves every row twice more through memory (386 us at
+// 10^6 x 200; the tile, with both operands straight from memory, then took 1410 us instead of 1581: dropped).  Both operands are
 // double-buffered; one barrier per chunk.  Chunks run on without a break across node tiles: a tile's scores are folded
 // while the next tile's first chunk is on the matrix pipe.
+// What bounds it is neither pipe alone: at 10^6 x 200 the matrix pipes are busy 42 % of the time and the vector port, with 6.9
+// instructions beside each MFMA (of a wavefront's 331 a chunk, 128 add the chunk's products up), about 58 %; an MFMA takes 36 to 39 ns where the probe sustains 23 with
+// six vector instructions beside each, and the clock stays at 2.2 GHz.
 //
 // Accumulation.  A chunk's products are summed on their own from zero, the small ones (lo hi, hi lo) first, and then
 // added to the tile's accumulators: the roundings inside a chunk are relative to |x_chunk| |w_chunk|, which add up to at
@@ -552,7 +555,7 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
         cut = best - bound;
         a.bmu[i] = node;
         if (a.qe) {
-            // the statistic n_recheck: best two scores inside a band of fixed relative width, 3 * 2^-18 for the cut
+            // the statistic n_recheck: best two scores inside a band of fixed relative width, as in bmu_split_tile
             const float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(196 + (a.D + 63) / 64 + 1) * unit) + 12.0f * unit;
             near = close || (a.K > 1 && !((best - second) > (root(n.x) * wmax + 0.5f * wmax2) * rel));
         }

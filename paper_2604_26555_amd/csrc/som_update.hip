@@ -23,7 +23,7 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // Parts of the k range: the four wavefronts of a workgroup take a quarter each and add their results in LDS, and up to
 // kSplitK workgroups share a block of updated nodes where those alone leave the chip idle (their partials are stored, then
 // summed in order).  With sixteen stored partials whatever the shape, the partials were most of the traffic: 262 MB each way
-// at K = 1024, D = 2000 (207 + 53 us for contraction and finish there, 96 + 11 now; 228 + 28 -> 153 + 14 us at K = 4096, D = 50).
+// at K = 1024, D = 2000 (207 + 53 us for contraction and finish there, 153 to 173 + 7 now; 228 + 28 -> 96 + 5 us at K = 4096, D = 50).
 constexpr int kSplitK = 8;
 
 // The shape of a contraction.  Two wavefronts for every SIMD, so that one's loads and exponentials run beside the other's MFMAs:
