@@ -56,7 +56,8 @@ __global__ void __launch_bounds__(256) node_d2_kernel(const float* __restrict__ 
     }
 }
 
-// adjacency matrix A (K x K bytes) <- minimum spanning tree.  Ties between equal keys go to the lowest node index.
+// adjacency matrix A (K x K bytes) <- minimum spanning tree.  Ties between equal keys go to the lowest node index.  The
+// rounds end early where no distance that is a number joins another node to the tree: those nodes stay apart.
 __global__ void __launch_bounds__(1024) mst_prim_kernel(const double* __restrict__ d2, int K, unsigned char* __restrict__ A)
 {
     extern __shared__ double prim_lds[];
@@ -105,13 +106,16 @@ __global__ void __launch_bounds__(1024) mst_prim_kernel(const double* __restrict
                     mi = red_i[w];
                 }
             chosen = mi;
-            const int f = from[mi];
-            A[(size_t)mi * K + f] = 1;
-            A[(size_t)f * K + mi] = 1;
-            key[mi] = -1.0;
+            if (mi < K) {
+                const int f = from[mi];
+                A[(size_t)mi * K + f] = 1;
+                A[(size_t)f * K + mi] = 1;
+                key[mi] = -1.0;
+            }
         }
         __syncthreads();
         const int u = chosen;
+        if (u >= K) break;
         const double* row = d2 + (size_t)u * K;
         for (int v = tid; v < K; v += 1024) {
             const double k = key[v];

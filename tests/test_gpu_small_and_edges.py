@@ -417,3 +417,23 @@ def test_spanning_tree_hops_of_every_shape(som, shape, K):
     W = W.astype(np.float32)
     T = som.som_topology(dev(W), "mst").cpu().numpy()
     assert np.array_equal(T, oracle.graph_distances("mst", W).astype(np.float32))
+
+
+def test_spanning_tree_where_a_node_holds_no_number(som):
+    """More nodes than Boruvka's rounds take, one of them NaN: no distance of its own is below another, so it stays apart, and
+    the edges that are left are no tree of all nodes: their hop counts are searched breadth first."""
+    from scipy.sparse import csr_matrix
+    from scipy.sparse.csgraph import shortest_path
+    K, bad = 4100, 77
+    W = rows(19, K, 3, 4)
+    keep = np.delete(np.arange(K), bad)
+    e = keep[oracle.mst_edges(W[keep])]
+    W[bad, 1] = np.nan
+    T = som.som_topology(dev(W), "mst").cpu().numpy()
+    adj = np.zeros((K, K), dtype=bool)
+    adj[e[:, 0], e[:, 1]] = adj[e[:, 1], e[:, 0]] = True
+    assert np.array_equal(T == 1, adj)
+    assert np.isinf(T[bad, keep]).all() and np.isinf(T[keep, bad]).all() and (T.diagonal() == 0).all()
+    src = [0, bad, 1234, K - 1]
+    hops = shortest_path(csr_matrix(adj.astype(np.int8)), unweighted=True, indices=src)
+    assert np.array_equal(T[src], hops.astype(np.float32))
