@@ -386,6 +386,23 @@ def test_bmu_exact_ties_over_many_nodes(som, m, K, bases, D):
     assert np.array_equal(b.cpu().numpy(), first[near])
 
 
+@pytest.mark.parametrize("m,K,D,run", [(20_000, 300, 50, 32), (20_000, 320, 64, 32), (20_000, 577, 50, 32), (150_000, 289, 12, 64)])
+def test_bmu_exact_ties_uneven_among_wavefronts(som, m, K, D, run):
+    """One wavefront of four has samples of 40 equally near nodes, the others of five: they are far apart when a workgroup goes on to its
+    next tile (every row is listed; last stages as above)."""
+    rng = np.random.default_rng(m + K + D)
+    heavy = 2
+    base = rng.uniform(-10, 10, (heavy + -(-(K - 40 * heavy) // 5), D)).astype(np.float32)
+    of = np.concatenate([np.repeat(np.arange(heavy), 40), heavy + np.arange(K - 40 * heavy) // 5])
+    W = base[of[rng.permutation(K)]]
+    many = np.arange(m) // run % 4 == 0
+    near = np.where(many, rng.integers(heavy, size=m), rng.integers(heavy, len(base), size=m))
+    X = (base[near] + rng.normal(size=(m, D)) * 0.05).astype(np.float32)
+    first = np.array([np.flatnonzero((W == b).all(1))[0] for b in base])
+    b, _, _ = som.som_bmu(dev(X), dev(W))
+    assert np.array_equal(b.cpu().numpy(), first[near])
+
+
 @pytest.mark.parametrize("m,K,D", [(20_000, 512, 17), (20_000, 512, 50), (20_000, 512, 64), (20_000, 512, 100)])
 def test_bmu_where_squares_of_the_parts_underflow(som, m, K, D):
     """Rows of about 10^-17: what the first bf16 part leaves over has squares around the smallest normal number, below which the
@@ -437,3 +454,12 @@ def test_spanning_tree_where_a_node_holds_no_number(som):
     src = [0, bad, 1234, K - 1]
     hops = shortest_path(csr_matrix(adj.astype(np.int8)), unweighted=True, indices=src)
     assert np.array_equal(T[src], hops.astype(np.float32))
+
+
+@pytest.mark.parametrize("K", [9102, 9103])
+def test_spanning_tree_hops_at_the_limit_of_lds(som, K):
+    """A chain of the most nodes whose records, list and stack fit 160 KB, and of one more, which goes breadth first."""
+    place = torch.randperm(K, generator=torch.Generator().manual_seed(K)).cuda()
+    T = som.som_topology(place.float()[:, None].contiguous(), "mst")
+    for lo in range(0, K, 1024):
+        assert torch.equal(T[lo:lo + 1024], (place[lo:lo + 1024, None] - place[None]).abs().float())
