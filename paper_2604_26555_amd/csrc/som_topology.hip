@@ -366,18 +366,27 @@ __global__ void __launch_bounds__(256) csr_degree_kernel(const unsigned char* __
     if (lane == 0) deg[v] = c;
 }
 
+// off[0 .. K]: where the nodes' lists begin; off[K + 1]: nodes of more than two neighbours (K: most nodes hang on hubs)
 __global__ void __launch_bounds__(1024) csr_scan_kernel(const int* __restrict__ deg, int K, int* __restrict__ off)
 {
     __shared__ int part[1024];
+    __shared__ int branching, ends;                           // nodes of more than two neighbours, and of one
     const int tid = threadIdx.x;
     const int per = (K + 1023) / 1024;
-    int s = 0;
+    int s = 0, more = 0, one = 0;
     for (int t = 0; t < per; ++t) {
         const int v = tid * per + t;
-        if (v < K) s += deg[v];
+        if (v < K) {
+            s += deg[v];
+            more += deg[v] > 2 ? 1 : 0;
+            one += deg[v] == 1 ? 1 : 0;
+        }
     }
+    if (tid == 0) branching = ends = 0;
     part[tid] = s;
     __syncthreads();
+    if (more) atomicAdd(&branching, more);
+    if (one) atomicAdd(&ends, one);
     for (int o = 1; o < 1024; o <<= 1) {
         const int add = (tid >= o) ? part[tid - o] : 0;
         __syncthreads();
@@ -392,7 +401,10 @@ __global__ void __launch_bounds__(1024) csr_scan_kernel(const int* __restrict__ 
             run += deg[v];
         }
     }
-    if (tid == 1023) off[K] = part[1023];
+    if (tid == 1023) {
+        off[K] = part[1023];
+        off[K + 1] = ends > K / 2 ? K : branching;
+    }
 }
 
 __global__ void __launch_bounds__(256) csr_fill_kernel(const unsigned char* __restrict__ A, int K,
@@ -457,9 +469,18 @@ __device__ __forceinline__ void bfs_source(const int* __restrict__ off, const in
     }
 }
 
+// Where the walk over a spanning tree (below) has more sources than wavefronts that LDS lets run at once, it is the faster one only on
+// trees of long branches, and the breadth-first search on the others: both kernels are launched, and `pick` makes one of them end
+// at once.  Whole call, walk / breadth first, by the share of branching nodes at 2049 to 4096 nodes: none (nodes along a line) 0.59 to
+// 0.80; 1 to 2.4 % (maps after epochs of a large radius) 0.74 to 0.99, but 1.15 to 1.40 where they are hubs and most nodes hang on
+// them; 8 to 12 % (of a small radius) 0.99 to 1.17; 20 % and more (nodes that are data rows) 1.09 to 1.33.  2048 nodes, which is one round:
+// 0.54 to 0.99 on all of them.
+__device__ __forceinline__ bool long_branches(const int* off, int K) { return off[K + 1] <= K / 32; }
+
 __global__ void __launch_bounds__(64) bfs_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K,
-                                                 float* __restrict__ G)
+                                                 float* __restrict__ G, bool pick)
 {
+    if (pick && long_branches(off, K)) return;
     extern __shared__ int bfs_lds[];
     bfs_source(off, nbr, K, blockIdx.x, bfs_lds, G);
 }
@@ -481,8 +502,9 @@ __host__ __device__ constexpr size_t tree_list_bytes(int K) { return (size_t)K *
 __host__ __device__ constexpr size_t tree_source_bytes(int K) { return ((size_t)K * 6 + 3) / 4 * 4; }
 
 __global__ void __launch_bounds__(64 * kTreeSources) tree_hops_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K,
-                                                                      float* __restrict__ G)
+                                                                      float* __restrict__ G, bool pick)
 {
+    if (pick && !long_branches(off, K)) return;
     extern __shared__ unsigned int tree_lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int src = blockIdx.x * (int)(blockDim.x >> 6) + wave;
@@ -588,7 +610,7 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
     double* d2 = (double*)ctx->topo_blob;
     double* best_w = d2 + kk;
     int* deg = (int*)(best_w + K);
-    int* off = deg + K;                                  // K + 1 entries
+    int* off = deg + K;                                  // K + 2 entries
     int* comp = off + K + 2;
     int* best_u = comp + K;
     int* state = best_u + K;                             // 4 entries
@@ -626,6 +648,7 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
     hipLaunchKernelGGL(csr_scan_kernel, dim3(1), dim3(1024), 0, ctx->stream, deg, K, off);
     hipLaunchKernelGGL(csr_fill_kernel, dim3((K + 3) / 4), dim3(256), 0, ctx->stream, A, K, off, nbr);
     if (int rc = check_hip(ctx, hipGetLastError(), "adjacency launch")) return rc;
+    bool pick = false;
     if (kind == SOM_TOPOLOGY_MST && tree_list_bytes(K) + tree_source_bytes(K) <= kTreeLds) {
         // as many sources to a workgroup as give a compute unit most wavefronts
         int sources = 1;
@@ -641,14 +664,21 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
         if (lds > 48 * 1024) {
             if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(tree_hops_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTreeLds), "raising the dynamic LDS limit")) return rc;
         }
-        hipLaunchKernelGGL(tree_hops_kernel, dim3((K + sources - 1) / sources), dim3(64 * sources), lds, ctx->stream, off, nbr, K, G);
-        return check_hip(ctx, hipGetLastError(), "hop-count launch");
+        if (ctx->units == 0) {
+            int units = 0;
+            if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || units < 1) units = 256;
+            ctx->units = units;
+        }
+        pick = most * (size_t)ctx->units < (size_t)K;
+        hipLaunchKernelGGL(tree_hops_kernel, dim3((K + sources - 1) / sources), dim3(64 * sources), lds, ctx->stream, off, nbr, K, G, pick);
+        if (int rc = check_hip(ctx, hipGetLastError(), "hop-count launch")) return rc;
+        if (!pick) return SOM_OK;
     }
     // dist[K] int32 + queue[K] uint16 per wavefront (72 KB at the 12000-node limit)
     const size_t bfs_lds_bytes = ((size_t)K * 6 + 3) / 4 * 4;
     if (bfs_lds_bytes > 48 * 1024) {
         if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(bfs_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 12000 * 6), "raising the dynamic LDS limit")) return rc;
     }
-    hipLaunchKernelGGL(bfs_kernel, dim3(K), dim3(64), bfs_lds_bytes, ctx->stream, off, nbr, K, G);
+    hipLaunchKernelGGL(bfs_kernel, dim3(K), dim3(64), bfs_lds_bytes, ctx->stream, off, nbr, K, G, pick);
     return check_hip(ctx, hipGetLastError(), "hop-count launch");
 }

@@ -416,7 +416,9 @@ def test_bmu_where_squares_of_the_parts_underflow(som, m, K, D):
 
 
 @pytest.mark.parametrize("shape,K", [("chain", 2), ("chain", 3), ("chain", 65), ("chain", 1500), ("star", 4), ("star", 70), ("star", 300),
-                                     ("comb", 66), ("comb", 513), ("random", 1), ("random", 1025), ("random", 2500)])
+                                     ("comb", 66), ("comb", 513), ("random", 1), ("random", 1025), ("random", 2500),
+                                     # the largest map that is always walked; above, long branches are walked and others searched
+                                     ("random", 2048), ("chain", 2049), ("random", 2049), ("hubs", 2048), ("hubs", 2049)])
 def test_spanning_tree_hops_of_every_shape(som, shape, K):
     """The walk over a spanning tree: long branches, nodes with very many branches, both mixed, and sizes around a wavefront."""
     rng = np.random.default_rng(K)
@@ -429,6 +431,8 @@ def test_spanning_tree_hops_of_every_shape(som, shape, K):
     elif shape == "comb":                                   # a spine with teeth of four nodes
         i = np.arange(K)
         W = np.stack([(i // 5) * 3.0 + 0.001 * (i // 5) ** 1.1, (i % 5) * (1.0 + 0.0005 * i)], 1)
+    elif shape == "hubs":                                   # eight far apart, every other node around one of them
+        W = 1000.0 * np.eye(8, 64)[np.arange(K) % 8] + rng.normal(size=(K, 64)) * (np.arange(K) >= 8)[:, None]
     else:
         W = rng.normal(size=(K, 6))
     W = W.astype(np.float32)
@@ -436,13 +440,15 @@ def test_spanning_tree_hops_of_every_shape(som, shape, K):
     assert np.array_equal(T, oracle.graph_distances("mst", W).astype(np.float32))
 
 
-def test_spanning_tree_where_a_node_holds_no_number(som):
+@pytest.mark.parametrize("shape", ["random", "chain"])
+def test_spanning_tree_where_a_node_holds_no_number(som, shape):
     """More nodes than Boruvka's rounds take, one of them NaN: no distance of its own is below another, so it stays apart, and
-    the edges that are left are no tree of all nodes: their hop counts are searched breadth first."""
+    the edges that are left are no tree of all nodes.  Their hop counts are searched breadth first, from the start or (a chain)
+    by the walk that finds it out."""
     from scipy.sparse import csr_matrix
     from scipy.sparse.csgraph import shortest_path
     K, bad = 4100, 77
-    W = rows(19, K, 3, 4)
+    W = rows(19, K, 3, 4) if shape == "random" else np.random.default_rng(19).permutation(K).astype(np.float32)[:, None] * np.ones(3, np.float32)
     keep = np.delete(np.arange(K), bad)
     e = keep[oracle.mst_edges(W[keep])]
     W[bad, 1] = np.nan
