@@ -43,16 +43,20 @@ __global__ void __launch_bounds__(kSortThreads) sort_hist_kernel(const int32_t* 
     for (int k = tid; k < K; k += kSortThreads) hist[(size_t)blockIdx.x * K + k] = sort_lds[k];
 }
 
-// hist[block][k] -> number of node k's samples in the blocks before; total[k]; n[k] (+)= total[k].  16 nodes and 64 runs of
-// blocks per workgroup: a thread's loads follow each other, so that short runs count (64 nodes and sixteen runs: 12.6 us for
-// 1023 blocks of 400 nodes, 6.0 now).
+// hist[block][k] -> number of node k's samples in the blocks before; total[k]; n[k] (+)= total[k].  NODES nodes and
+// 1024 / NODES runs of blocks per workgroup.  Small maps wait for latency: a thread's loads follow each other, so that short runs count
+// (64 nodes and sixteen runs: 12.6 us for 1023 blocks of 400 nodes, 6.0 with 16 nodes).  Of large ones the counts are tens of MB, and 16
+// nodes are half a line: the stable sum of 300,000 rows of 10 on 8000 nodes 155 us, 137 with 32 nodes; 500,000 of 20 on 2304
+// nodes 94.8 and 92.4.
+template <int NODES>
 __global__ void __launch_bounds__(1024) sort_columns_kernel(uint32_t* __restrict__ hist, int K, int blocks, uint32_t* __restrict__ total,
                                                             unsigned long long* __restrict__ n, int zero_first)
 {
-    __shared__ uint32_t run[16][16];
-    const int l = threadIdx.x & 15, seg = threadIdx.x >> 4, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int k = blockIdx.x * 16 + l, kc = k < K ? k : K - 1;
-    const int per = (blocks + 63) / 64, lo = seg * per, hi = lo + per < blocks ? lo + per : blocks;
+    __shared__ uint32_t run[16][NODES];
+    constexpr int kRuns = 1024 / NODES;
+    const int l = threadIdx.x & (NODES - 1), seg = threadIdx.x / NODES, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int k = blockIdx.x * NODES + l, kc = k < K ? k : K - 1;
+    const int per = (blocks + kRuns - 1) / kRuns, lo = seg * per, hi = lo + per < blocks ? lo + per : blocks;
     uint32_t s = 0u;
     for (int b0 = lo; b0 < hi; b0 += 8) {
         uint32_t v[8];
@@ -61,13 +65,13 @@ __global__ void __launch_bounds__(1024) sort_columns_kernel(uint32_t* __restrict
 #pragma unroll
         for (int u = 0; u < 8; ++u) s += b0 + u < hi ? v[u] : 0u;
     }
-    uint32_t at = s;                                           // up to and with this run, in the wavefront's four
+    uint32_t at = s;                                           // up to and with this run, among the wavefront's
 #pragma unroll
-    for (int o = 16; o < 64; o <<= 1) {
+    for (int o = NODES; o < 64; o <<= 1) {
         const uint32_t before = __shfl_up(at, o);
         if (lane >= o) at += before;
     }
-    if (lane >= 48) run[wave][l] = at;
+    if (lane >= 64 - NODES) run[wave][l] = at;
     at -= s;
     __syncthreads();
     uint32_t all = 0u;
@@ -369,7 +373,8 @@ int accumulate_sort_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, co
     if (stable) hipLaunchKernelGGL(stable_hist_kernel, grid, wg, lds, ctx->stream, bmu, m, K, per_block, blocks, hist);
     else hipLaunchKernelGGL(sort_hist_kernel, grid, wg, lds, ctx->stream, bmu, m, K, per_block, hist);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) histogram launch")) return rc;
-    hipLaunchKernelGGL(sort_columns_kernel, dim3((K + 15) / 16), dim3(1024), 0, ctx->stream, hist, K, blocks, total, n, zero_first ? 1 : 0);
+    const int columns = K < 2048 ? 16 : 32;                 // (timed at K = 1600, 2025, 2304 and above)
+    hipLaunchKernelGGL(columns == 16 ? sort_columns_kernel<16> : sort_columns_kernel<32>, dim3((K + columns - 1) / columns), dim3(1024), 0, ctx->stream, hist, K, blocks, total, n, zero_first ? 1 : 0);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) offsets launch")) return rc;
     hipLaunchKernelGGL(sort_starts_kernel, dim3(1), dim3(1024), 0, ctx->stream, total, K, (uint32_t)rows, start, seg);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) starts launch")) return rc;
