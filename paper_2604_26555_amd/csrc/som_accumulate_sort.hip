@@ -277,7 +277,9 @@ __global__ void __launch_bounds__(256) sort_sums_kernel(const float* __restrict_
 // a workgroup per node, 64 features at a time: a run of the node's segments per wavefront, added up in order (a single segment's
 // sums are in S already; with a workgroup per 64 features their mere launch took 60 us at D = 2000).  Sixteen loads under way in
 // a run, and eight runs, four where the workgroups are many and walk on: sixteen runs, four loads at a time, kept the chip in
-// wavefronts without a segment (K = 1024, D = 2000: 58 us, 21 now; D = 200: 16.7, 11; K = 4096, D = 50: 26.5, 21).
+// wavefronts without a segment (K = 1024, D = 2000: 58 us, 21 now; D = 200: 16.7, 11; K = 4096, D = 50: 26.5, 21).  What is left is the
+// chain of a node with many segments, so up to eight workgroups share its features (`shares`): the whole call with half of 50,000 rows x
+// 1000 on one of 1024 nodes 88 us with sixteen runs, 103 with four and four workgroups, 86 with eight; evenly spread rows 76, 64, 65.
 __global__ void __launch_bounds__(1024) sort_finish_kernel(const double* __restrict__ part, const uint32_t* __restrict__ seg, int D,
                                                              int zero_first, double* __restrict__ S)
 {
@@ -387,7 +389,9 @@ int accumulate_sort_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, co
     hipLaunchKernelGGL(kern, dim3(groups), dim3(256), 0, ctx->stream, X, D, ldx, start, seg, K, perm, (uint32_t)rows, slabs, part,
                        zero_first ? S : (double*)nullptr);
     if (int rc = check_hip(ctx, hipGetLastError(), "accumulate (sort) sums launch")) return rc;
-    hipLaunchKernelGGL(sort_finish_kernel, dim3(K, D > 256 ? 4 : 1), dim3(D > 256 ? 256 : 512), 0, ctx->stream, part, seg, D, zero_first ? 1 : 0, S);
+    // D > 256: workgroups of a node, which share its features (K = 4096, D = 600: 49.5 us a call with four, 52.4 with eight)
+    const int most_shares = K <= 2048 ? 8 : 4, shares = D <= 256 ? 1 : (D + 63) / 64 < most_shares ? (D + 63) / 64 : most_shares;
+    hipLaunchKernelGGL(sort_finish_kernel, dim3(K, shares), dim3(D > 256 ? 256 : 512), 0, ctx->stream, part, seg, D, zero_first ? 1 : 0, S);
     return check_hip(ctx, hipGetLastError(), "accumulate (sort) finish launch");
 }
 

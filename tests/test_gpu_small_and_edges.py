@@ -285,7 +285,7 @@ def test_wide_search_with_ragged_splits(som, m, K, D):
 @pytest.mark.parametrize("reproducible", [False, True])
 @pytest.mark.parametrize("m,K,D", [(9000, 8192, 70), (9000, 8193, 70), (5000, 16384, 66), (5000, 16385, 66), (257, 1, 200), (4097, 300, 64),
                                    (20_001, 100, 126), (2048, 77, 129), (3000, 16385, 20), (64, 8192, 50), (30_000, 40, 2001),
-                                   (30_000, 2047, 70), (30_000, 2048, 70), (20_000, 2081, 66)])
+                                   (30_000, 2047, 70), (30_000, 2048, 70), (20_000, 2081, 66), (20_000, 2048, 600), (20_000, 2049, 600), (20_000, 33, 321), (9000, 9, 257)])
 def test_accumulation_by_sort_at_its_limits(som, reproducible, m, K, D):
     """Per-node counters at the ends of their LDS, one node, one segment, many segments, sums that a call adds to."""
     X = rows(600 + K + D, m, D)
