@@ -477,10 +477,11 @@ __device__ __forceinline__ void bfs_source(const int* __restrict__ off, const in
 // 0.54 to 0.99 on all of them.
 __device__ __forceinline__ bool long_branches(const int* off, int K) { return off[K + 1] <= K / 32; }
 
+template <bool PICK>                                      // (a graph that is no tree: false)
 __global__ void __launch_bounds__(64) bfs_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K,
-                                                 float* __restrict__ G, bool pick)
+                                                 float* __restrict__ G)
 {
-    if (pick && long_branches(off, K)) return;
+    if (PICK && long_branches(off, K)) return;
     extern __shared__ int bfs_lds[];
     bfs_source(off, nbr, K, blockIdx.x, bfs_lds, G);
 }
@@ -661,24 +662,25 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
             }
         }
         const size_t lds = tree_list_bytes(K) + sources * tree_source_bytes(K);
-        if (lds > 48 * 1024) {
-            if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(tree_hops_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTreeLds), "raising the dynamic LDS limit")) return rc;
-        }
         if (ctx->units == 0) {
             int units = 0;
             if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || units < 1) units = 256;
             ctx->units = units;
         }
         pick = most * (size_t)ctx->units < (size_t)K;
+        if (lds > 48 * 1024) {
+            if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(tree_hops_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTreeLds), "raising the dynamic LDS limit")) return rc;
+        }
         hipLaunchKernelGGL(tree_hops_kernel, dim3((K + sources - 1) / sources), dim3(64 * sources), lds, ctx->stream, off, nbr, K, G, pick);
         if (int rc = check_hip(ctx, hipGetLastError(), "hop-count launch")) return rc;
         if (!pick) return SOM_OK;
     }
     // dist[K] int32 + queue[K] uint16 per wavefront (72 KB at the 12000-node limit)
     const size_t bfs_lds_bytes = ((size_t)K * 6 + 3) / 4 * 4;
+    auto search = pick ? bfs_kernel<true> : bfs_kernel<false>;
     if (bfs_lds_bytes > 48 * 1024) {
-        if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(bfs_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 12000 * 6), "raising the dynamic LDS limit")) return rc;
+        if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(search), hipFuncAttributeMaxDynamicSharedMemorySize, 12000 * 6), "raising the dynamic LDS limit")) return rc;
     }
-    hipLaunchKernelGGL(bfs_kernel, dim3(K), dim3(64), bfs_lds_bytes, ctx->stream, off, nbr, K, G, pick);
+    hipLaunchKernelGGL(search, dim3(K), dim3(64), bfs_lds_bytes, ctx->stream, off, nbr, K, G);
     return check_hip(ctx, hipGetLastError(), "hop-count launch");
 }
