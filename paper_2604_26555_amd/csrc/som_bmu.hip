@@ -2099,8 +2099,8 @@ __global__ void __launch_bounds__(kExactThreads) bmu_exact_kernel(const BmuArgs 
     }
     double qs = 0.0, qs2 = 0.0;
     if constexpr (PAIRS) pair_list(a, lds4);
-    // (PAIRS: from the last workgroup on, so that a short list goes to workgroups without pairs: the
-    // kernel 17.5 -> 13.6 us at 250,000 x 37, together with a grid that is resident at once)
+    // (PAIRS: from the last workgroup on, so that a short list goes to workgroups without pairs: the kernel 17.5 -> 13.6 us at
+    // 250,000 x 37, together with half as many workgroups.  One fits a compute unit, by registers, so the grid is two rounds.)
     for (unsigned int g0 = (PAIRS ? gridDim.x - 1 - blockIdx.x : blockIdx.x) * kExactGroup; g0 < count; g0 += gridDim.x * kExactGroup) {
         float bestd[kExactGroup];
         int bestk[kExactGroup];
@@ -2873,7 +2873,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
                     return rc;
                 attr_set = true;
             }
-            // (rows of D features; two workgroups fit a compute unit up to D = 52)
+            // (rows of D features; one workgroup of 160 registers a thread fits a compute unit, at most 108 KB of LDS)
             const size_t rows = (size_t)(kExactThreads / 64) * pair_lds_f4(a.D) * 16, lds = rows > kExactLds ? rows : kExactLds;
             BmuArgs b = a;                       // the distances come afterwards, for all samples
             b.d2 = nullptr;

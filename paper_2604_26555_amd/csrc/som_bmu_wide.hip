@@ -15,9 +15,10 @@
 // 10^6 x 200; the tile, with both operands straight from memory, then took 1410 us instead of 1581: dropped).  Both operands are
 // double-buffered; one barrier per chunk.  Chunks run on without a break across node tiles: a tile's scores are folded
 // while the next tile's first chunk is on the matrix pipe.
-// What bounds it is neither pipe alone: at 10^6 x 200 the matrix pipes are busy 42 % of the time and the vector port, with 6.9
-// instructions beside each MFMA (of a wavefront's 331 a chunk, 128 add the chunk's products up), about 58 %; an MFMA takes 36 to 39 ns where the probe sustains 23 with
-// six vector instructions beside each, and the clock stays at 2.2 GHz.
+// What bounds it is neither pipe alone: at 10^6 x 200 the matrix pipes are busy 42 % of the time and the vector units, with 6.9
+// instructions for each MFMA (of a wavefront's 331 a chunk, 128 add the chunk's products up), 36 %, but only a quarter of those run
+// beside an MFMA, and for 30 % of the time neither works; an MFMA takes 36 to 39 ns where the probe sustains 23 with six vector
+// instructions beside each, and the clock stays at 2.24 GHz.
 //
 // Accumulation.  A chunk's products are summed on their own from zero, the small ones (lo hi, hi lo) first, and then
 // added to the tile's accumulators: the roundings inside a chunk are relative to |x_chunk| |w_chunk|, which add up to at
