@@ -366,7 +366,8 @@ __global__ void __launch_bounds__(256) csr_degree_kernel(const unsigned char* __
     if (lane == 0) deg[v] = c;
 }
 
-// off[0 .. K]: where the nodes' lists begin; off[K + 1]: nodes of more than two neighbours (K: most nodes hang on hubs)
+// off[0 .. K]: where the nodes' lists begin; COUNT: off[K + 1] nodes of more than two neighbours (K: most nodes hang on hubs)
+template <bool COUNT>
 __global__ void __launch_bounds__(1024) csr_scan_kernel(const int* __restrict__ deg, int K, int* __restrict__ off)
 {
     __shared__ int part[1024];
@@ -378,15 +379,19 @@ __global__ void __launch_bounds__(1024) csr_scan_kernel(const int* __restrict__ 
         const int v = tid * per + t;
         if (v < K) {
             s += deg[v];
-            more += deg[v] > 2 ? 1 : 0;
-            one += deg[v] == 1 ? 1 : 0;
+            if constexpr (COUNT) {
+                more += deg[v] > 2 ? 1 : 0;
+                one += deg[v] == 1 ? 1 : 0;
+            }
         }
     }
-    if (tid == 0) branching = ends = 0;
+    if (COUNT && tid == 0) branching = ends = 0;
     part[tid] = s;
     __syncthreads();
-    if (more) atomicAdd(&branching, more);
-    if (one) atomicAdd(&ends, one);
+    if constexpr (COUNT) {
+        if (more) atomicAdd(&branching, more);
+        if (one) atomicAdd(&ends, one);
+    }
     for (int o = 1; o < 1024; o <<= 1) {
         const int add = (tid >= o) ? part[tid - o] : 0;
         __syncthreads();
@@ -403,7 +408,7 @@ __global__ void __launch_bounds__(1024) csr_scan_kernel(const int* __restrict__ 
     }
     if (tid == 1023) {
         off[K] = part[1023];
-        off[K + 1] = ends > K / 2 ? K : branching;
+        if constexpr (COUNT) off[K + 1] = ends > K / 2 ? K : branching;
     }
 }
 
@@ -645,14 +650,10 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
         hipLaunchKernelGGL(rng_verify_kernel, dim3(K), dim3(256), 0, ctx->stream, d2, K, A);
     }
     if (int rc = check_hip(ctx, hipGetLastError(), "edge kernel launch")) return rc;
-    hipLaunchKernelGGL(csr_degree_kernel, dim3((K + 3) / 4), dim3(256), 0, ctx->stream, A, K, deg);
-    hipLaunchKernelGGL(csr_scan_kernel, dim3(1), dim3(1024), 0, ctx->stream, deg, K, off);
-    hipLaunchKernelGGL(csr_fill_kernel, dim3((K + 3) / 4), dim3(256), 0, ctx->stream, A, K, off, nbr);
-    if (int rc = check_hip(ctx, hipGetLastError(), "adjacency launch")) return rc;
+    int sources = 0;                                     // of a workgroup of the walk over a spanning tree (0: none)
     bool pick = false;
     if (kind == SOM_TOPOLOGY_MST && tree_list_bytes(K) + tree_source_bytes(K) <= kTreeLds) {
         // as many sources to a workgroup as give a compute unit most wavefronts
-        int sources = 1;
         size_t most = 0;
         for (int n = 1; n <= kTreeSources; ++n) {
             const size_t bytes = tree_list_bytes(K) + n * tree_source_bytes(K), waves = bytes <= kTreeLds ? n * (kTreeLds / bytes) : 0;
@@ -661,13 +662,19 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
                 sources = n;
             }
         }
-        const size_t lds = tree_list_bytes(K) + sources * tree_source_bytes(K);
         if (ctx->units == 0) {
             int units = 0;
             if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || units < 1) units = 256;
             ctx->units = units;
         }
         pick = most * (size_t)ctx->units < (size_t)K;
+    }
+    hipLaunchKernelGGL(csr_degree_kernel, dim3((K + 3) / 4), dim3(256), 0, ctx->stream, A, K, deg);
+    hipLaunchKernelGGL(pick ? csr_scan_kernel<true> : csr_scan_kernel<false>, dim3(1), dim3(1024), 0, ctx->stream, deg, K, off);
+    hipLaunchKernelGGL(csr_fill_kernel, dim3((K + 3) / 4), dim3(256), 0, ctx->stream, A, K, off, nbr);
+    if (int rc = check_hip(ctx, hipGetLastError(), "adjacency launch")) return rc;
+    if (sources > 0) {
+        const size_t lds = tree_list_bytes(K) + sources * tree_source_bytes(K);
         if (lds > 48 * 1024) {
             if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(tree_hops_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTreeLds), "raising the dynamic LDS limit")) return rc;
         }
