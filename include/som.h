@@ -102,6 +102,13 @@ int som_profile_read(som_ctx* ctx, float* ms, int32_t capacity, int32_t* count);
 int som_matrix_pipe_probe(som_ctx* ctx, const uint16_t* A, const uint16_t* Bt, const float* C, float* Dout, int64_t n);
 
 /*
+ * The same for the two MFMAs of the search for 65 to 256 features (operands as half-precision bit patterns):
+ *   kind 0  v_mfma_f32_32x32x16_f16:                   A, Bt uint16[n][32][16]
+ *   kind 1  v_mfma_scale_f32_32x32x64_f8f6f4 on fp6:   A, Bt uint16[n][32][64], rounded to fp6 (e2m3) on the way in; both scales 1
+ */
+int som_matrix_pipe_probe_parts(som_ctx* ctx, int kind, const uint16_t* A, const uint16_t* Bt, const float* C, float* Dout, int64_t n);
+
+/*
  * Measurement support (not an operation of the paper): a loop of v_mfma_f32_32x32x16_bf16 on pseudo-random operands,
  * eight per trip on two accumulators, with fold_steps (0..2) fold steps of three vector instructions beside each, on one
  * workgroup of four wavefronts per compute unit and waves_per_simd (1 or 2) of them resident.  It executes

@@ -28,7 +28,7 @@
 //
 // The default search (bmu_split_kernel further down for D <= 64, som_bmu_wide.hip above) is the same scheme with the
 // contraction on the bf16 matrix pipe, samples and weights cut into two bf16 parts each.
-#include "som_bmu_common.hpp"
+#include "som_bmu_wide.hpp"
 
 #include <math.h>
 
@@ -64,14 +64,16 @@ constexpr int stage_floats_for(int stride)
 // centre[f] = mean over nodes of W[k][f], f < D; zero up to the next multiple of 64.  Any vector would do (distances do not change when the same vector is
 // taken off samples and weights); the mean keeps |w_k - centre| as small as the spread of the map.
 __global__ void __launch_bounds__(1024) bmu_centre_kernel(const float* __restrict__ W, int K, int D, float* __restrict__ centre,
-                                                          unsigned int* __restrict__ scal)
+                                                          unsigned int* __restrict__ scal, float* __restrict__ spread)
 {
     __shared__ double part[16][64];
+    __shared__ float ends[16][64][2];
     const int fl = threadIdx.x & 63, grp = threadIdx.x >> 6;
     const int f = blockIdx.x * 64 + fl;
     // this kernel runs first in every preparation: it also clears the result words (maximum norm, list lengths)
     if (blockIdx.x == 0 && threadIdx.x < 16) scal[threadIdx.x] = 0u;
     double s = 0.0;
+    float low = INFINITY, high = -INFINITY;
     if (f < D) {
         // sixteen loads in flight per thread: the kernel is a chain of memory round trips otherwise
         int k = grp;
@@ -80,16 +82,38 @@ __global__ void __launch_bounds__(1024) bmu_centre_kernel(const float* __restric
 #pragma unroll
             for (int u = 0; u < 16; ++u) v[u] = W[(size_t)(k + 16 * u) * D + f];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) s += (double)v[u];
+            for (int u = 0; u < 16; ++u) {
+                s += (double)v[u];
+                low = fminf(low, v[u]);
+                high = fmaxf(high, v[u]);
+            }
         }
-        for (; k < K; k += 16) s += (double)W[(size_t)k * D + f];
+        for (; k < K; k += 16) {
+            const float v = W[(size_t)k * D + f];
+            s += (double)v;
+            low = fminf(low, v);
+            high = fmaxf(high, v);
+        }
     }
     part[grp][fl] = s;
+    ends[grp][fl][0] = low;
+    ends[grp][fl][1] = high;
     __syncthreads();
     if (grp == 0) {                       // the padding up to the next multiple of 64 entries is zeroed
         double t = 0.0;
         for (int q = 0; q < 16; ++q) t += part[q][fl];
-        centre[f] = (f < D) ? (float)(t / K) : 0.0f;
+        const float c = (f < D) ? (float)(t / K) : 0.0f;
+        centre[f] = c;
+        if (spread && blockIdx.x * 64 < (unsigned)D) {        // largest |w - centre| of these features
+            for (int q = 0; q < 16; ++q) {
+                low = fminf(low, ends[q][fl][0]);
+                high = fmaxf(high, ends[q][fl][1]);
+            }
+            float most = f < D ? fmaxf(high - c, c - low) : 0.0f;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) most = fmaxf(most, __shfl_xor(most, o));
+            if (fl == 0) spread[blockIdx.x] = most;
+        }
     }
 }
 
@@ -183,36 +207,6 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
 //     and of what the bf16 cut leaves over (w - hi, w - hi - lo) in scal.
 // Clears the result words that the later kernels of the call count into; the maxima it adds to (tops) were left zero by the
 // re-decision of the call before.
-// ---------------------------------------------------------------------------------------------------------
-// Which node a row of the stages holds.  The search keeps its winners by class of rows (bits 0, 2 and 5 of the row: bmu_split_tile), and
-// a near tie within one class costs a pass of its own, so nodes that come close should fall into different classes: the rows of a
-// whole stage of 128 are ordered such that those three bits are a remainder of the node's number: its bits as a polynomial over
-// two elements, modulo x^3 + x^2 + 1 (bit i adds kClassOf[i % 7]).  Two nodes next to each other on a lattice, whatever its width
-// from 8 to 64, then share a class in 5 % of the cases on average and 11 % at worst (in a diagonal 14 and 24, two columns or rows
-// on 5 and 10); with nodes in their own order 6 and 50 (11 and 75, 38 and 77).  Samples left to the candidate pass, 10^6 x 50 on
-// 64 x 64 nodes: 254,000 then, 79,000 now (an epoch 1.62 -> 1.41 ms); on 32 x 32 36,000 and 23,000 (422 -> 416 us).  Lattices whose
-// own order happens to separate their neighbours lose a little: 20 x 20, 500,000 x 64 1,500 and 6,000 (233 us both), 900,000
-// x 25 with distances 300 and 2,500 (154 -> 158 us).  No order that does not know the lattice avoids that: over the widths, a node's
-// neighbours in the next row fall into each of eight classes about equally often, so the mean over widths, 0 along the rows and
-// 1/8 across, cannot be much below the 6.5 % of this one.
-constexpr unsigned class_mask(int bit)                    // the bits of a node's number, from bit 3 on, that flip this bit of its class
-{
-    constexpr unsigned kClassOf[7] = {1, 2, 4, 5, 7, 3, 6};
-    unsigned m = 0u;
-    for (int i = 3; i < 32; ++i) m |= ((kClassOf[i % 7] >> bit) & 1u) << i;
-    return m;
-}
-__host__ __device__ __forceinline__ int node_of_row(int row, int K)
-{
-    if ((row | (kNodesPerStage - 1)) >= K) return row;                       // (a stage with padding rows keeps its order)
-    static_assert(kNodesPerStage == 128, "seven bits");
-    constexpr unsigned m0 = class_mask(0), m1 = class_mask(1), m2 = class_mask(2);
-    const unsigned s = (unsigned)row;
-    const unsigned high = (s & ~127u) | (s & 64u) | ((s & 24u) << 1) | ((s & 2u) << 2);      // bits 3 and up of the node
-    const unsigned f = (__builtin_popcount(high & m0) & 1) | (__builtin_popcount(high & m1) & 1) << 1 | (__builtin_popcount(high & m2) & 1) << 2;
-    return (int)(high | (((s & 1u) | ((s & 4u) >> 1) | ((s & 32u) >> 3)) ^ f));
-}
-
 constexpr int kCentreNodes = 64;
 constexpr int kPrepNodes = 16;           // nodes (wavefronts) of a workgroup: 64 bytes of a row of the transposed copy
 
@@ -2393,7 +2387,7 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     const int kb = !split || nch > 1 ? 0 : (tail_r ? D / 16 : (D + 15) / 16);
     // (D > 64: rows in the order of som_bmu_wide.hip)
     const size_t stage16_one = (split && nch == 1) ? (size_t)split_stage_f4(kb, tail_r > 0) * 16 : 0;
-    const size_t stage16_bytes = !split ? 0 : nch == 1 ? (size_t)(kpad / kNodesPerStage) * stage16_one : bmu_wide_blob_bytes(K, D);
+    const size_t stage16_bytes = !split ? 0 : nch == 1 ? (size_t)(kpad / kNodesPerStage) * stage16_one : D <= kHeldFeatures ? bmu_held_blob_bytes(kpad, D) : bmu_wide_blob_bytes(K, D);
     const size_t wrow_bytes = (split && nch == 1) ? (size_t)K * D * sizeof(float) : 0;
     const size_t need = stage_bytes + wt_bytes + centre_bytes + stage16_bytes + wrow_bytes + 256;
     if (need > ctx->prep_bytes) {
@@ -2441,10 +2435,12 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
                            out->centre, out->wt, out->scal, out->tops, qe, small, sp);
         return check_hip(ctx, hipGetLastError(), "bmu (split) preparation launch");
     }
+    const bool held = wide_split && D <= kHeldFeatures;
     hipLaunchKernelGGL(bmu_centre_kernel, dim3((unsigned)(centre_bytes / 256)), dim3(1024), 0, ctx->stream, W, K, D,
-                       out->centre, out->scal);
+                       out->centre, out->scal, held ? bmu_held_spread(*out, D) : nullptr);
     if (wide_split) {
         if (int rc = check_hip(ctx, hipGetLastError(), "bmu_centre launch")) return rc;
+        if (held) return bmu_held_prepare(ctx, W, K, D, *out, qe, small);
         return bmu_wide_prepare(ctx, W, K, D, *out, qe, small);
     }
     // one thread per element of the padded stage matrix and of the transposed copy, one wavefront per four nodes

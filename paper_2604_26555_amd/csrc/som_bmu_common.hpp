@@ -16,7 +16,9 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-constexpr int kScalLo = 8;        // scal[8], scal[9]: bits of the largest |w - hi|^2 and |w - hi - lo|^2 (split search)
+constexpr int kScalLo = 8;        // scal[8], scal[9]: bits of the largest |w - hi|^2 and |w - hi - lo|^2 (split search); three figures of
+                                  // som_bmu_held.hip
+constexpr int kScalShift = 11;    // scal[11]: the weights' scale there
 
 // Added to the sums of squares that enter a bound before their root is taken: v_sqrt_f32 returns zero for a subnormal number, which
 // would take up to 2^-63 from a norm.  The sums themselves keep subnormal squares, those by v_dot2c_f32_bf16 (square2) as
@@ -187,6 +189,36 @@ __device__ __forceinline__ void split8(const float (&v)[8], bf16x8& hi, bf16x8& 
     }
     hi = __builtin_bit_cast(bf16x8, h);
     lo = __builtin_bit_cast(bf16x8, l);
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Which node a row of the stages holds.  The search keeps its winners by class of rows (bits 0, 2 and 5 of the row: bmu_split_tile), and
+// a near tie within one class costs a pass of its own, so nodes that come close should fall into different classes: the rows of a
+// whole stage of 128 are ordered such that those three bits are a remainder of the node's number: its bits as a polynomial over
+// two elements, modulo x^3 + x^2 + 1 (bit i adds kClassOf[i % 7]).  Two nodes next to each other on a lattice, whatever its width
+// from 8 to 64, then share a class in 5 % of the cases on average and 11 % at worst (in a diagonal 14 and 24, two columns or rows
+// on 5 and 10); with nodes in their own order 6 and 50 (11 and 75, 38 and 77).  Samples left to the candidate pass, 10^6 x 50 on
+// 64 x 64 nodes: 254,000 then, 79,000 now (an epoch 1.62 -> 1.41 ms); on 32 x 32 36,000 and 23,000 (422 -> 416 us).  Lattices whose
+// own order happens to separate their neighbours lose a little: 20 x 20, 500,000 x 64 1,500 and 6,000 (233 us both), 900,000
+// x 25 with distances 300 and 2,500 (154 -> 158 us).  No order that does not know the lattice avoids that: over the widths, a node's
+// neighbours in the next row fall into each of eight classes about equally often, so the mean over widths, 0 along the rows and
+// 1/8 across, cannot be much below the 6.5 % of this one.
+constexpr unsigned class_mask(int bit)                    // the bits of a node's number, from bit 3 on, that flip this bit of its class
+{
+    constexpr unsigned kClassOf[7] = {1, 2, 4, 5, 7, 3, 6};
+    unsigned m = 0u;
+    for (int i = 3; i < 32; ++i) m |= ((kClassOf[i % 7] >> bit) & 1u) << i;
+    return m;
+}
+__host__ __device__ __forceinline__ int node_of_row(int row, int K)
+{
+    if ((row | (kNodesPerStage - 1)) >= K) return row;                       // (a stage with padding rows keeps its order)
+    static_assert(kNodesPerStage == 128, "seven bits");
+    constexpr unsigned m0 = class_mask(0), m1 = class_mask(1), m2 = class_mask(2);
+    const unsigned s = (unsigned)row;
+    const unsigned high = (s & ~127u) | (s & 64u) | ((s & 24u) << 1) | ((s & 2u) << 2);      // bits 3 and up of the node
+    const unsigned f = (__builtin_popcount(high & m0) & 1) | (__builtin_popcount(high & m1) & 1) << 1 | (__builtin_popcount(high & m2) & 1) << 2;
+    return (int)(high | (((s & 1u) | ((s & 4u) >> 1) | ((s & 32u) >> 3)) ^ f));
 }
 
 } // namespace som

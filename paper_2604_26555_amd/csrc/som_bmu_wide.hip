@@ -28,7 +28,7 @@
 // formed on the way, and decides which samples are open: those whose candidates are all known get their ids written
 // down, the others go through the tile kernel again (CAND), which notes every node that reaches the sample's cut.
 // bmu_wide_exact_kernel decides both by direct float32 differences, and what it cannot serve is left to the all-nodes pass.
-#include "som_bmu_common.hpp"
+#include "som_bmu_wide.hpp"
 
 #include <math.h>
 
@@ -62,28 +62,6 @@ constexpr int kWChunk = 32;                       // features of a chunk
 constexpr int kWBuf = kWTile * kWChunk * 4;       // bytes of an operand's chunk in LDS (hi and lo parts)
 constexpr int kWState = 12;                       // words of running state per lane
 constexpr size_t kWLds = 4 * (size_t)kWBuf + (kWThreads * kWState + kWTile) * sizeof(float);
-constexpr int kWIds = 14;                         // candidate ids of a record: 4 bytes count, fourteen 16-bit ids
-constexpr int kWRecord = 8;                       // 32-bit words of a record
-
-struct WideArgs {
-    const char* blob;        // weights' parts, [node tile][chunk][node block 8][kb 2][hi | lo][64 lanes][8] bf16
-    const float* norms;      // [node tiles * 256] -|w|^2 / 2
-    int nch, tiles;          // chunks of a row, node tiles
-    int splits, per_split;   // workgroups that share a sample tile, node tiles of each
-    int64_t rows;            // m of the pass
-    float4* best;            // [splits][m] best, second best class winner, highest of all others; id of the best (bits)
-    uint32_t* id2;           // [splits][m] id of the second
-    float4* norm;            // [m] |x|^2, weighted |x|^2, |x - hi|^2
-    uint32_t* record;        // [m][kWRecord] candidates of the listed samples
-    uint32_t cand_min;       // lists up to this length go to the all-nodes pass at once
-};
-
-// 64 lanes x 16 bytes, from the lanes' own addresses to 1 KB of LDS at offset lds (below 64 KB); counted by vmcnt
-__device__ __forceinline__ void lds_load16(const void* from, unsigned lds)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(from) : "memory", "m0");
-}
-
 // ---------------------------------------------------------------------------------------------------------
 // Weight preparation: one wavefront per node cuts its row into parts in fragment order and sums its norms; the rest of the
 // grid writes the transposed copy that the all-nodes pass reads.
@@ -505,25 +483,37 @@ __global__ void __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(
 // ---------------------------------------------------------------------------------------------------------
 // Join: the winner over the splits, the sample's error bound, and the lists.
 // ---------------------------------------------------------------------------------------------------------
-constexpr int kJoinThreads = 256;
+// Threads of a workgroup: each takes one atomic on the lists' lengths, about 10 ns after one another (10^6 samples by 256s: 33 to 55 us, by
+// 1024s 18); few samples spread over more units by 256s (5000 with sixteen splits: 5 us and 12).
+constexpr int kJoinThreads = 1024;
+static int join_threads(int64_t m) { return m >= 256 * (int64_t)kJoinThreads ? kJoinThreads : 256; }
 
+template <bool HELD>
 __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuArgs a, const WideArgs p)
 {
     __shared__ unsigned int wave_base[2][kJoinThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t i = (int64_t)blockIdx.x * kJoinThreads + tid;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + tid;
+    const int waves = blockDim.x / 64;
     const bool live = i < a.m;
     bool close = false, open = false, near = false;
     float cut = 0.0f;
     if (live) {
         float best = -INFINITY, second = -INFINITY;
         int node = 0;
-        for (int s = 0; s < p.splits; ++s) {
-            const float4 r = p.best[(size_t)s * p.rows + i];
-            const bool up = r.x > best;
-            second = fmaxf(fmaxf(second, up ? best : r.x), fmaxf(r.y, r.z));
-            node = up ? __float_as_int(r.w) : node;
-            best = up ? r.x : best;
+        for (int s0 = 0; s0 < p.splits; s0 += 4) {               // (four loads under way)
+            float4 r4[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) r4[u] = p.best[(size_t)(s0 + u < p.splits ? s0 + u : s0) * p.rows + i];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (s0 + u >= p.splits) break;
+                const float4 r = r4[u];
+                const bool up = r.x > best;
+                second = fmaxf(fmaxf(second, up ? best : r.x), fmaxf(r.y, r.z));
+                node = up ? __float_as_int(r.w) : node;
+                best = up ? r.x : best;
+            }
         }
         node = (node >= 0 && node < a.K) ? node : a.K - 1;       // (only padding or non-finite scores get here)
         const float4 n = p.norm[i];
@@ -536,15 +526,24 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
         constexpr float unit = 5.9604645e-08f;
         auto root = [](float v) { return __builtin_amdgcn_sqrtf(v); };      // within a unit in the last place
         const float wmax2 = __uint_as_float(a.scal[0]), wmax = root(wmax2) * 1.00001f;
-        const float lo_w = root(__uint_as_float(a.scal[kScalLo]) + kSquaresFloor) * 1.001f, rest_w = root(__uint_as_float(a.scal[kScalLo + 1]) + kSquaresFloor) * 1.001f;
-        // (four float32 sums of 8 nch squares each, added up: short of their size by one rounding a square at most, half of that in
-        // the root; 1 + 2^-13 at D = 16384)
-        const float grown = 1.0001f + (float)p.nch * (4.1f * unit);
-        const float nx = root(n.x + kSquaresFloor) * grown, nl = root(n.z + kSquaresFloor) * grown;
-        const float add = (float)(p.nch + 1) * 1.016f;
-        const float err_w = nl * (1.0078125f / 256.0f + 65.28f * unit) + root(n.y + kSquaresFloor) * (grown * 16.256f * unit) + nx * ((6.0f + add) * unit);
-        const float err_0 = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (65.28f * unit));
-        const float err_n = 0.5f * (6.0f + add) * unit;
+        float nx, err_w, err_0, err_n;
+        if constexpr (HELD) {
+            nx = n.x;
+            err_w = n.y;
+            err_0 = n.z;
+            err_n = 0.5f * 8.0f * unit;
+        } else {
+            const float lo_w = root(__uint_as_float(a.scal[kScalLo]) + kSquaresFloor) * 1.001f, rest_w = root(__uint_as_float(a.scal[kScalLo + 1]) + kSquaresFloor) * 1.001f;
+            // (four float32 sums of 8 nch squares each, added up: short of their size by one rounding a square at most, half of that in
+            // the root; 1 + 2^-13 at D = 16384)
+            const float grown = 1.0001f + (float)p.nch * (4.1f * unit);
+            nx = root(n.x + kSquaresFloor) * grown;
+            const float nl = root(n.z + kSquaresFloor) * grown;
+            const float add = (float)(p.nch + 1) * 1.016f;
+            err_w = nl * (1.0078125f / 256.0f + 65.28f * unit) + root(n.y + kSquaresFloor) * (grown * 16.256f * unit) + nx * ((6.0f + add) * unit);
+            err_0 = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (65.28f * unit));
+            err_n = 0.5f * (6.0f + add) * unit;
+        }
         const float wn = -2.0f * p.norms[node];
         const float wb = fminf(root(wn) * 1.00001f, wmax);
         const float err_b = err_w * wb + err_0 + err_n * wb * wb;
@@ -558,7 +557,7 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
         if (a.qe) {
             // the statistic n_recheck: best two scores inside a band of fixed relative width, as in bmu_split_tile
             const float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(196 + (a.D + 63) / 64 + 1) * unit) + 12.0f * unit;
-            near = close || (a.K > 1 && !((best - second) > (root(n.x) * wmax + 0.5f * wmax2) * rel));
+            near = close || (a.K > 1 && !((best - second) > ((HELD ? nx : root(n.x)) * wmax + 0.5f * wmax2) * rel));
         }
         if (close) {
             uint32_t* rec = p.record + i * kWRecord;
@@ -588,7 +587,7 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
     if (tid == 0) {
         unsigned int n0 = 0, n1 = 0;
         unsigned int at[2][kJoinThreads / 64];
-        for (int w = 0; w < kJoinThreads / 64; ++w) {
+        for (int w = 0; w < waves; ++w) {
             at[0][w] = n0;
             at[1][w] = n1;
             n0 += wave_base[0][w];
@@ -597,7 +596,7 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
         unsigned long long base = 0ull;
         if (n0 | n1)
             base = atomicAdd(reinterpret_cast<unsigned long long*>(&a.scal[a.slot]), (unsigned long long)n0 | ((unsigned long long)n1 << 32));
-        for (int w = 0; w < kJoinThreads / 64; ++w) {
+        for (int w = 0; w < waves; ++w) {
             wave_base[0][w] = (unsigned int)base + at[0][w];
             wave_base[1][w] = (unsigned int)(base >> 32) + at[1][w];
         }
@@ -778,12 +777,19 @@ static WideArgs wide_args(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t 
     p.tiles = (K + kWTile - 1) / kWTile;
     p.nch = (D + kWChunk - 1) / kWChunk;
     p.blob = (const char*)prep.stage16;
-    p.norms = (const float*)(p.blob + (size_t)p.tiles * p.nch * kWBuf);
-    p.splits = wide_splits((m + kWTile - 1) / kWTile, p.tiles, p.nch, ctx->units > 0 ? ctx->units : 256);
+    const int units = ctx->units > 0 ? ctx->units : 256;
+    const bool held = D <= kHeldFeatures;
+    p.norms = held ? bmu_held_norms(prep, D) : (const float*)(p.blob + (size_t)p.tiles * p.nch * kWBuf);
+    p.splits = held ? bmu_held_splits(m, K, D, units) : wide_splits((m + kWTile - 1) / kWTile, p.tiles, p.nch, units);
     p.per_split = (p.tiles + p.splits - 1) / p.splits;
     p.rows = m;
     return p;
 }
+
+// Lists up to this length go to the all-nodes pass at once: a candidate tile takes one pass over its chunks however few entries it has, the
+// all-nodes pass K D differences an entry.  (That pass takes 33 us at K D = 200,000 and 110 at 800,000 for any list of up to 256
+// entries, a candidate pass of held rows 4 to 15: none of its lists is short enough.)
+static uint32_t cand_min_for(const BmuArgs& a) { return a.K > 65536 ? 0xffffffffu : a.D <= kHeldFeatures ? 0u : 256u; }
 
 // bytes of the pass's workspace: per-split winners, norms, candidate records
 size_t bmu_wide_work_bytes(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t D, int64_t m)
@@ -800,8 +806,14 @@ int bmu_wide_run(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work
     p.norm = (float4*)(w + (size_t)a.m * p.splits * 16);
     p.record = (uint32_t*)(w + (size_t)a.m * (p.splits * 16 + 16));
     p.id2 = (uint32_t*)(w + (size_t)a.m * (p.splits * 16 + 16 + kWRecord * 4));
-    // a candidate tile takes one pass over its chunks however few entries it has; the all-nodes pass K D differences an entry
-    p.cand_min = a.K <= 65536 ? 256u : 0xffffffffu;
+    p.cand_min = cand_min_for(a);
+    const int per_join = join_threads(a.m);
+    const dim3 join_grid((unsigned)((a.m + per_join - 1) / per_join)), join_block(per_join);
+    if (a.D <= kHeldFeatures) {
+        if (int rc = bmu_held_launch(ctx, prep, a, p, false)) return rc;
+        hipLaunchKernelGGL(bmu_wide_join_kernel<true>, join_grid, join_block, 0, ctx->stream, a, p);
+        return check_hip(ctx, hipGetLastError(), "bmu (held rows) join launch");
+    }
     static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
     bool& attr_set = attr_set_dev[ctx->device];
     if (!attr_set) {
@@ -815,7 +827,7 @@ int bmu_wide_run(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work
     const int64_t blocks = (tiles_m + 7) / 8 * 8 * p.splits;
     hipLaunchKernelGGL(bmu_wide_split_kernel, dim3((unsigned)blocks), dim3(kWThreads), kWLds, ctx->stream, a, p);
     if (int rc = check_hip(ctx, hipGetLastError(), "bmu (wide, split) kernel launch")) return rc;
-    hipLaunchKernelGGL(bmu_wide_join_kernel, dim3((unsigned)((a.m + kJoinThreads - 1) / kJoinThreads)), dim3(kJoinThreads), 0, ctx->stream, a, p);
+    hipLaunchKernelGGL(bmu_wide_join_kernel<false>, join_grid, join_block, 0, ctx->stream, a, p);
     return check_hip(ctx, hipGetLastError(), "bmu (wide, split) join launch");
 }
 
@@ -825,10 +837,14 @@ int bmu_wide_recheck(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* 
     WideArgs p = wide_args(ctx, prep, a.K, a.D, a.m);
     char* w = (char*)work;
     p.record = (uint32_t*)(w + (size_t)a.m * (p.splits * 16 + 16));
-    p.cand_min = a.K <= 65536 ? 256u : 0xffffffffu;
-    const int64_t most = (a.m + kWTile - 1) / kWTile * p.tiles;
-    hipLaunchKernelGGL(bmu_wide_split_cand_kernel, dim3((unsigned)(most < 256 ? most : 256)), dim3(kWThreads), kWLds, ctx->stream, a, p);
-    if (int rc = check_hip(ctx, hipGetLastError(), "bmu (wide, split) candidate launch")) return rc;
+    p.cand_min = cand_min_for(a);
+    if (a.D <= kHeldFeatures) {
+        if (int rc = bmu_held_launch(ctx, prep, a, p, true)) return rc;
+    } else {
+        const int64_t most = (a.m + kWTile - 1) / kWTile * p.tiles;
+        hipLaunchKernelGGL(bmu_wide_split_cand_kernel, dim3((unsigned)(most < 256 ? most : 256)), dim3(kWThreads), kWLds, ctx->stream, a, p);
+        if (int rc = check_hip(ctx, hipGetLastError(), "bmu (wide, split) candidate launch")) return rc;
+    }
     const int64_t groups = (a.m + 15) / 16;
     hipLaunchKernelGGL(bmu_wide_exact_kernel, dim3((unsigned)(groups < 2048 ? groups : 2048)), dim3(256), 0, ctx->stream, a, p);
     return check_hip(ctx, hipGetLastError(), "bmu (wide, split) candidate-distance launch");

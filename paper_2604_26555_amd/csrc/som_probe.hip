@@ -32,6 +32,45 @@ __global__ void __launch_bounds__(256) mfma_probe_kernel(const uint16_t* __restr
     for (int r = 0; r < 16; ++r) d[(8 * (r >> 2) + 4 * g + (r & 3)) * 32 + j] = acc[r];
 }
 
+// The same for the MFMAs of som_bmu_held.hip.  kind 0: K = 16, half precision, lanes as above; kind 1: K = 64, lane (j, g) feeds
+// k = 32 g .. 32 g + 31, rounded to fp6 as the search rounds its parts.
+__global__ void __launch_bounds__(256) mfma_parts_probe_kernel(int kind, const uint16_t* __restrict__ A, const uint16_t* __restrict__ Bt,
+                                                              const float* __restrict__ C, float* __restrict__ Dout, int64_t n)
+{
+    typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+    typedef _Float16 halfx32 __attribute__((ext_vector_type(32)));
+    typedef unsigned int uintx6 __attribute__((ext_vector_type(6)));
+    typedef int intx8 __attribute__((ext_vector_type(8)));
+    const int lane = threadIdx.x & 63, j = lane & 31, g = lane >> 5;
+    const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (t >= n) return;
+    const float* c = C + (size_t)t * 1024;
+    floatx16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = c[(8 * (r >> 2) + 4 * g + (r & 3)) * 32 + j];
+    if (kind == 0) {
+        halfx8 av, bv;
+        __builtin_memcpy(&av, A + (size_t)t * 512 + j * 16 + 8 * g, 16);
+        __builtin_memcpy(&bv, Bt + (size_t)t * 512 + j * 16 + 8 * g, 16);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv, acc, 0, 0, 0);
+    } else {
+        halfx32 av, bv;
+        __builtin_memcpy(&av, A + (size_t)t * 2048 + j * 64 + 32 * g, 64);
+        __builtin_memcpy(&bv, Bt + (size_t)t * 2048 + j * 64 + 32 * g, 64);
+        const uintx6 a6 = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(av, 1.0f), b6 = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(bv, 1.0f);
+        intx8 a8 = {}, b8 = {};
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            a8[i] = (int)a6[i];
+            b8[i] = (int)b6[i];
+        }
+        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, acc, 2, 2, 0, 127, 0, 127);
+    }
+    float* d = Dout + (size_t)t * 1024;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) d[(8 * (r >> 2) + 4 * g + (r & 3)) * 32 + j] = acc[r];
+}
+
 // Plain streaming read of a buffer (16-byte loads, one contiguous range per workgroup): what the memory system delivers
 // to a kernel that does nothing else, the yardstick for the HBM-bound accumulation pass.
 __global__ void __launch_bounds__(256) read_probe_kernel(const float4* __restrict__ p, size_t n4, float* __restrict__ out)
@@ -142,5 +181,18 @@ extern "C" int som_matrix_pipe_probe(som_ctx* ctx, const uint16_t* A, const uint
     if (((uintptr_t)A | (uintptr_t)Bt) & 15) return fail(ctx, SOM_EINVAL, "A and Bt must be 16-byte aligned");
     if (int rc = check_hip(ctx, hipSetDevice(ctx->device), "hipSetDevice")) return rc;
     hipLaunchKernelGGL(mfma_probe_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, ctx->stream, A, Bt, C, Dout, n);
+    return check_hip(ctx, hipGetLastError(), "launching the matrix-pipe probe");
+}
+
+extern "C" int som_matrix_pipe_probe_parts(som_ctx* ctx, int kind, const uint16_t* A, const uint16_t* Bt, const float* C, float* Dout, int64_t n)
+{
+    if (!ctx) return SOM_EINVAL;
+    if (kind < 0 || kind > 1) return fail(ctx, SOM_EINVAL, "kind must be 0 or 1");
+    if (n < 0 || n > ((int64_t)1 << 24)) return fail(ctx, SOM_EINVAL, "n must be in [0, 2^24]");
+    if (n == 0) return SOM_OK;
+    if (!A || !Bt || !C || !Dout) return fail(ctx, SOM_EINVAL, "null operand");
+    if (((uintptr_t)A | (uintptr_t)Bt) & 15) return fail(ctx, SOM_EINVAL, "A and Bt must be 16-byte aligned");
+    if (int rc = check_hip(ctx, hipSetDevice(ctx->device), "hipSetDevice")) return rc;
+    hipLaunchKernelGGL(mfma_parts_probe_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, ctx->stream, kind, A, Bt, C, Dout, n);
     return check_hip(ctx, hipGetLastError(), "launching the matrix-pipe probe");
 }

@@ -30,7 +30,7 @@ EXPORTS = [
     "som_create", "som_destroy", "som_strerror", "som_last_error", "som_sync", "som_bmu", "som_accumulate",
     "som_neighborhood_update", "som_epoch", "som_epoch_host", "som_profile", "som_profile_read",
     "som_set_update_rule", "som_topology", "som_set_safeguard", "som_set_reproducible", "som_set_search",
-    "som_matrix_pipe_probe", "som_neighborhood_update_static", "som_epoch_file", "som_read_probe", "som_mfma_rate_probe",
+    "som_matrix_pipe_probe", "som_matrix_pipe_probe_parts", "som_neighborhood_update_static", "som_epoch_file", "som_read_probe", "som_mfma_rate_probe",
 ]
 
 
@@ -94,6 +94,8 @@ def load_library(path: str = LIB_PATH) -> C.CDLL:
     lib.som_topology.restype = C.c_int
     lib.som_matrix_pipe_probe.argtypes = [vp, vp, vp, vp, vp, i64]
     lib.som_matrix_pipe_probe.restype = C.c_int
+    lib.som_matrix_pipe_probe_parts.argtypes = [vp, C.c_int, vp, vp, vp, vp, i64]
+    lib.som_matrix_pipe_probe_parts.restype = C.c_int
     lib.som_epoch.argtypes = [vp, vp, i64, i32, i64, vp, i64, vp, i32, vp, f64, C.c_int, f64, C.POINTER(SomStats)]
     lib.som_epoch.restype = C.c_int
     lib.som_epoch_host.argtypes = [vp, vp, i64, i32, i64, C.c_int, vp, i32, vp, f64, C.c_int, f64,
@@ -243,6 +245,20 @@ class Som:
                                             _ptr(Cm, torch.float32, "C", self.device),
                                             _ptr(Dout, torch.float32, "Dout", self.device), n)
         self._check(rc, "som_matrix_pipe_probe")
+        return Dout
+
+    def som_matrix_pipe_probe_parts(self, kind, A, Bt, Cm):
+        """One half-precision (kind 0: A, Bt (n, 32, 16)) or fp6 (kind 1: (n, 32, 64)) MFMA per problem: Cm + A @ Bt^T."""
+        n, k = A.shape[0], 16 if kind == 0 else 64
+        if A.shape != (n, 32, k) or Bt.shape != (n, 32, k) or Cm.shape != (n, 32, 32) or not (
+                A.is_contiguous() and Bt.is_contiguous() and Cm.is_contiguous()):
+            raise ValueError("shapes: A, Bt (n, 32, 16 or 64) float16, C (n, 32, 32) float32, all contiguous")
+        Dout = torch.empty_like(Cm)
+        rc = self.lib.som_matrix_pipe_probe_parts(self._h, kind, _ptr(A, torch.float16, "A", self.device),
+                                                  _ptr(Bt, torch.float16, "Bt", self.device),
+                                                  _ptr(Cm, torch.float32, "C", self.device),
+                                                  _ptr(Dout, torch.float32, "Dout", self.device), n)
+        self._check(rc, "som_matrix_pipe_probe_parts")
         return Dout
 
     # ------------------------------------------------------------------ stage 1
