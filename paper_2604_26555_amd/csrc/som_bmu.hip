@@ -2387,7 +2387,7 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     const int kb = !split || nch > 1 ? 0 : (tail_r ? D / 16 : (D + 15) / 16);
     // (D > 64: rows in the order of som_bmu_wide.hip)
     const size_t stage16_one = (split && nch == 1) ? (size_t)split_stage_f4(kb, tail_r > 0) * 16 : 0;
-    const size_t stage16_bytes = !split ? 0 : nch == 1 ? (size_t)(kpad / kNodesPerStage) * stage16_one : D <= kHeldFeatures ? bmu_held_blob_bytes(kpad, D) : bmu_wide_blob_bytes(K, D);
+    const size_t stage16_bytes = !split ? 0 : nch == 1 ? (size_t)(kpad / kNodesPerStage) * stage16_one : bmu_wide_blob_bytes(K, D, kpad);
     const size_t wrow_bytes = (split && nch == 1) ? (size_t)K * D * sizeof(float) : 0;
     const size_t need = stage_bytes + wt_bytes + centre_bytes + stage16_bytes + wrow_bytes + 256;
     if (need > ctx->prep_bytes) {
@@ -2435,12 +2435,10 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
                            out->centre, out->wt, out->scal, out->tops, qe, small, sp);
         return check_hip(ctx, hipGetLastError(), "bmu (split) preparation launch");
     }
-    const bool held = wide_split && D <= kHeldFeatures;
     hipLaunchKernelGGL(bmu_centre_kernel, dim3((unsigned)(centre_bytes / 256)), dim3(1024), 0, ctx->stream, W, K, D,
-                       out->centre, out->scal, held ? bmu_held_spread(*out, D) : nullptr);
+                       out->centre, out->scal, wide_split ? bmu_wide_spread(*out, K, D) : nullptr);
     if (wide_split) {
         if (int rc = check_hip(ctx, hipGetLastError(), "bmu_centre launch")) return rc;
-        if (held) return bmu_held_prepare(ctx, W, K, D, *out, qe, small);
         return bmu_wide_prepare(ctx, W, K, D, *out, qe, small);
     }
     // one thread per element of the padded stage matrix and of the transposed copy, one wavefront per four nodes
@@ -2697,7 +2695,7 @@ static int launch_bmu_distances(som_ctx* ctx, const BmuArgs& a)
 
 static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a);
 
-// The rows go through in passes of at most 2^27: the re-decision workspace then stays at 2.7 GB (20 bytes a row; the float32
+// The rows go through in passes of at most 2^27 (rows of more than 64 features: bmu_wide_pass_rows, and of fewer where memory runs out): the re-decision workspace then stays at 2.7 GB (20 bytes a row; the float32
 // searches' candidate sets 0.5 GB more) whatever m is,
 // and a pass's list stays within what the candidate pass can hold (2^24 entries, an eighth of a pass) — one call over
 // 10^9 rows listed more than that and fell back to direct differences over all nodes for every listed sample.
@@ -2706,8 +2704,8 @@ int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     int64_t kRowsPerPass = (int64_t)1 << 27;
     const int64_t m = a.m;
     const bool wide_split = prep.stage16 && prep.nch > 1;
-    if (wide_split) kRowsPerPass = (int64_t)1 << 24;      // (the wide search keeps some hundred bytes per sample of a pass)
-    for (int64_t off = 0; off < m; off += kRowsPerPass) {
+    if (wide_split) kRowsPerPass = bmu_wide_pass_rows(a.K, a.D);
+    for (int64_t off = 0; off < m;) {
         BmuArgs b = a;
         b.m = m - off < kRowsPerPass ? m - off : kRowsPerPass;
         if (a.idx)
@@ -2716,7 +2714,17 @@ int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
             b.X = a.X + off * a.ldx;
         b.bmu = a.bmu + off;
         if (a.d2) b.d2 = a.d2 + off;
-        if (int rc = bmu_run_pass(ctx, prep, b)) return rc;
+        const int calls = prep.calls;
+        const size_t events = ctx->prof_used;
+        const int rc = bmu_run_pass(ctx, prep, b);
+        if (rc == SOM_ENOMEM && wide_split && b.m > 256) {         // (nothing of the pass has been launched)
+            prep.calls = calls;
+            ctx->prof_used = events;
+            kRowsPerPass = (b.m / 2 + 127) / 128 * 128;
+            continue;
+        }
+        if (rc) return rc;
+        off += b.m;
     }
     return SOM_OK;
 }

@@ -30,19 +30,9 @@
 
 namespace som {
 
-typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
-typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
-typedef _Float16 halfx32 __attribute__((ext_vector_type(32)));
-typedef unsigned int uintx6 __attribute__((ext_vector_type(6)));
-typedef unsigned int uintx16 __attribute__((ext_vector_type(16)));
-typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
-typedef unsigned int uintx8 __attribute__((ext_vector_type(8)));
-typedef int intx8 __attribute__((ext_vector_type(8)));
-
 constexpr int kHThreads = 256;
 constexpr int kHWaves = kHThreads / 64;
 constexpr int kHAhead = 3;                         // groups of MFMAs between a fragment's read from LDS and its use
-constexpr int kHTop = 11;                          // the largest element is scaled into [2^11, 2^12): what its half leaves over is below 1
 constexpr int kHRange = 30;                        // largest difference of the samples' and the weights' scales
 constexpr float kHPadNorm = -1.2379400e+27f;       // -2^90: padding rows; times 2^-30 .. 2^30 still below any score
 
@@ -56,15 +46,6 @@ constexpr int held_block_bytes(int H) { return (H * 3584 + 1023) / 1024 * 1024; 
 __device__ __forceinline__ void lds_load4(const void* from, unsigned lds)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(from) : "memory", "m0");
-}
-
-__device__ __forceinline__ float power_of_two(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }
-
-// the scale exponent that takes `most`, the largest magnitude, into [2^kHTop, 2^(kHTop + 1))
-__device__ __forceinline__ int scale_for(float most)
-{
-    const int e = kHTop + 127 - (int)(__float_as_uint(most) >> 23 & 255u);
-    return e < -90 ? -90 : e > 90 ? 90 : e;
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -144,7 +125,7 @@ __global__ void __launch_bounds__(256) bmu_held_prep_kernel(const float* __restr
             uint4 e[4];
         } eights = {{from[0], from[2], from[1], from[3]}};
         const halfx32 v = __builtin_bit_cast(halfx32, eights);
-        const float scale = g == 0 ? power_of_two(kHTop - 2) : power_of_two(-3);
+        const float scale = g == 0 ? power_of_two(kTopBit - 2) : power_of_two(-3);
         const uintx6 q = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(v, scale);
         const halfx32 d = __builtin_amdgcn_cvt_scalef32_pk32_f16_fp6(q, scale);
 #pragma unroll
@@ -190,21 +171,7 @@ struct HeldArgs {
     const char* blob;
     const float* hats;       // [kpad] -|w|^2 / 2 at the weights' scale, in the order of the rows
     int blocks;              // blocks of 32 rows that hold a node
-    int per_split;           // even
 };
-
-// thirty-two fp6 values as the MFMA's builtin takes them (of the eight words six are read)
-__device__ __forceinline__ intx8 fp6_operand(const uintx6& v)
-{
-    return __builtin_bit_cast(intx8, (uintx8)__builtin_shufflevector(v, v, 0, 1, 2, 3, 4, 5, -1, -1));
-}
-
-__device__ __forceinline__ void swap_words(unsigned int& a, unsigned int& b)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
-}
 
 // Blocks [b_lo, b_hi) (b_lo even) for the samples of tile `tile`.  CAND: the samples are the entries of the re-decision list, and every
 // node that reaches the entry's cut is appended to its record; the scores are those of the search bit for bit.
@@ -317,7 +284,7 @@ __device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, c
         const float back_x = power_of_two(-sx);
         back[mb] = back_x;
         if constexpr (CAND) cut[mb] = cut[mb] * s * power_of_two(sw);
-        const float q_scale = g == 0 ? power_of_two(-3) : power_of_two(kHTop - 2);
+        const float q_scale = g == 0 ? power_of_two(-3) : power_of_two(kTopBit - 2);
         float v2 = 0.0f, e2 = 0.0f, after2 = 0.0f;
 #pragma unroll
         for (int u = 0; u < H; ++u) {
@@ -325,13 +292,9 @@ __device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, c
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
                 const float x0 = v[mb][u][t >> 2][2 * (t & 3)] * s, x1 = v[mb][u][t >> 2][2 * (t & 3) + 1] * s;
-                const floatx2 x = {x0, x1};
-                const halfx2 h = __builtin_convertvector(x, halfx2);
-                halfx2 l;
-                l[0] = (_Float16)fmaf((float)h[0], -1.0f, x0);
-                l[1] = (_Float16)fmaf((float)h[1], -1.0f, x1);
-                hi[t] = __builtin_bit_cast(unsigned int, h);
-                lo[t] = __builtin_bit_cast(unsigned int, l);
+                const HalfPair h(x0, x1);
+                hi[t] = h.hi;
+                lo[t] = h.lo;
             }
             xf[mb][u][0] = __builtin_bit_cast(halfx8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
             xf[mb][u][1] = __builtin_bit_cast(halfx8, make_uint4(hi[4], hi[5], hi[6], hi[7]));
@@ -365,24 +328,7 @@ __device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, c
         if constexpr (!CAND) {
             // the lower half of the lanes has the second parts' sums, the upper half the first parts'
             const float h2 = __shfl_xor(v2, 32), eh2 = __shfl_xor(e2, 32), ha2 = __shfl_xor(after2, 32);
-            if (split == 0 && g == 0 && real) {
-                // The error of a score.  (1) What the cuts drop: with x = xh + xl and its fp6 parts qh and ql, w likewise,
-                // |xl - ql| |w| + |ql| |wh - qh_w| + |xh - qh| |wl| + |qh| |wl - ql_w| + |xl| |wl|, from norms that were formed (the
-                // weights' are the largest over the nodes).  (2) The pipe's accumulation, as in bmu_split_tile: an MFMA of half-precision
-                // products is charged sixteen units of its accumulator and products, whose norms add up with the number of MFMAs
-                // that follow; those of fp6 products, sixty-four terms each, come first and hold small numbers only.  A subnormal part
-                // costs what 2^-14 would.  (3) Ten units for the centrings and the norm.
-                constexpr float unit = 5.9604645e-08f;
-                auto root = [](float x) { return __builtin_amdgcn_sqrtf(x); };
-                const float nl0 = root(v2), nl = nl0 * 1.001f + 1.0e-4f, nh = root(h2) * 1.0001f;
-                const float ql = root(e2) * 1.0001f + nl * 4.9e-4f + 1.0e-6f, qh = root(eh2) * 1.0001f;
-                const float nx = nh + nl;
-                const float lo_w = __uint_as_float(a.scal[kScalLo]) * 1.001f, qh_w = __uint_as_float(a.scal[kScalLo + 1]) * 1.001f,
-                            ql_w = __uint_as_float(a.scal[kScalLo + 2]) * 1.001f;
-                const float err_w = ql * 1.001f + root(ha2) * (1.001f * 16.3f * unit) + nl * (80.0f * (H + 2) * unit) + nx * (10.0f * unit);
-                const float err_0 = 1.001f * ((nl + ql) * qh_w + qh * lo_w + (nh + qh) * ql_w + nl * lo_w) + nx * (lo_w * (80.0f * (H + 2) * unit) + power_of_two(-sw) * 1.0e-7f);
-                p.norm[i] = make_float4(nx * back_x, err_w * back_x, err_0 * back_x, 0.0f);
-            }
+            if (split == 0 && g == 0 && real) p.norm[i] = part_norms(a, v2, e2, h2, eh2, ha2, (float)(H + 2), 0.0f, back_x, power_of_two(-sw));
         }
     }
 
@@ -464,7 +410,7 @@ __device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, c
         }
     };
     const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const int scale_a = g == 0 ? 127 + kHTop - 2 : 127 - 3, scale_b = g == 0 ? 127 - 3 : 127 + kHTop - 2;
+    const int scale_a = g == 0 ? 127 + kTopBit - 2 : 127 - 3, scale_b = g == 0 ? 127 - 3 : 127 + kTopBit - 2;
     constexpr int PARTS = 3 * 8 * MS, MFMAS = GROUPS * MS;
     auto block = [&](floatx16 (&cur)[MS], const floatx16 (&prev)[MS], auto prev_par, int b) {
         const char* base = lds + (b & 1) * BLK;
@@ -560,27 +506,9 @@ __device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, c
     float m0 = fmaxf(fmaxf(second[0][0], second[0][1 % CLS]), fmaxf(second[0][2 % CLS], second[0][3 % CLS]));
     float m1 = fmaxf(fmaxf(second[MS - 1][0], second[MS - 1][1 % CLS]), fmaxf(second[MS - 1][2 % CLS], second[MS - 1][3 % CLS]));
     swap_f(m0, m1);
-    float others = fmaxf(m0, m1), b1 = -INFINITY, b2 = -INFINITY;
-    int id1 = 0, id2 = 0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const float v = won[q];
-        const int r = 2 * (int)(__float_as_uint(v) & 7u) + (q & 1);
-        const int row = where[q] * 32 + 8 * (r >> 2) + 4 * (q >> 2) + (r & 3);
-        const bool first = v > b1, next = !first && v > b2;
-        others = fmaxf(others, first ? b2 : next ? b2 : v);
-        id2 = first ? id1 : next ? row : id2;
-        b2 = first ? b1 : next ? v : b2;
-        id1 = first ? row : id1;
-        b1 = first ? v : b1;
-    }
     const int64_t i = wave0 + (MS > 1 ? lane : j);
     const float un = g == 0 ? back[0] : back[MS - 1], uw = power_of_two(-sw);      // (this lane's sample is of block g)
-    if (i < total && (MS > 1 || g == 0)) {
-        const int n1 = node_of_row(id1 < a.kpad ? id1 : 0, a.K), n2 = node_of_row(id2 < a.kpad ? id2 : 0, a.K);
-        p.best[(size_t)split * p.rows + i] = make_float4(b1 * un * uw, b2 * un * uw, others * un * uw, __int_as_float(n1));
-        p.id2[(size_t)split * p.rows + i] = (uint32_t)n2;
-    }
+    if (i < total && (MS > 1 || g == 0)) write_winners(a, p, split, i, won, where, fmaxf(m0, m1), un * uw);
 }
 
 template <int H>
@@ -591,7 +519,7 @@ __device__ __forceinline__ void held_search(const BmuArgs& a, const WideArgs& p,
     const int64_t tile = blk * 8 + within % 8;
     const int split = within / 8;
     if (tile * held_tile_rows(H) >= a.m) return;
-    const int b_lo = split * hp.per_split, b_hi = b_lo + hp.per_split < hp.blocks ? b_lo + hp.per_split : hp.blocks;
+    const int b_lo = split * p.per_split, b_hi = b_lo + p.per_split < hp.blocks ? b_lo + p.per_split : hp.blocks;
     held_tile<H, false>(a, p, hp, tile, split, b_lo, b_hi, a.m, lds);
 }
 
@@ -661,14 +589,16 @@ int bmu_held_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, const B
     return check_hip(ctx, hipGetLastError(), "bmu (held rows) preparation launch");
 }
 
-// Workgroups per sample tile, as wide_splits: bringing in a tile's samples takes as long as about ten blocks.
-int bmu_held_splits(int64_t m, int32_t K, int32_t D, int units)
+// Workgroups per sample tile, as for the tile (som_bmu_wide.hip): bringing in a tile's samples takes as long as about ten blocks.  (The last,
+// partial round split further, as in som_bmu_cut.hip, gives nothing here: 10^5 x 80, 120 and 200 on 1024 nodes 361 us for 360, 509 for 501,
+// 798 for 792.)
+void bmu_held_plan(WideArgs& p, const BmuPrep& prep, int64_t m, int32_t K, int32_t D, int units)
 {
-    const int rows = held_tile_rows(held_units(D));
-    const int blocks = (K + 31) / 32;
+    const int H = held_units(D), rows = held_tile_rows(H), blocks = (K + 31) / 32;
     const int64_t tiles = (m + rows - 1) / rows;
-    units *= held_waves(held_units(D));
-    int best = 1;
+    p.norms = (const float*)((const char*)prep.stage16 + held_blob(prep.kpad, D)) + prep.kpad;
+    units *= held_waves(H);
+    int best = 1, steps = (blocks + 1) / 2 * 2;
     double best_cost = 0.0;
     for (int s = 1; s <= 16 && 2 * s <= blocks + 1; ++s) {
         const int per = ((blocks + s - 1) / s + 1) / 2 * 2;
@@ -676,10 +606,11 @@ int bmu_held_splits(int64_t m, int32_t K, int32_t D, int units)
         const double cost = (double)((tiles * s + units - 1) / units) * ((double)per + 10.0);
         if (s == 1 || cost < best_cost * 0.98) {
             best = s;
+            steps = per;
             best_cost = cost;
         }
     }
-    return best;
+    p.set_splits(m, best, steps, (tiles + 7) / 8 * 8 * best);
 }
 
 template <int H>
@@ -689,13 +620,7 @@ static HeldArgs<H> held_args(const BmuPrep& prep, const WideArgs& p, const BmuAr
     h.blob = (const char*)prep.stage16;
     h.hats = (const float*)(h.blob + held_blob(prep.kpad, a.D));
     h.blocks = (a.K + 31) / 32;
-    h.per_split = ((h.blocks + p.splits - 1) / p.splits + 1) / 2 * 2;
     return h;
-}
-
-const float* bmu_held_norms(const BmuPrep& prep, int32_t D)
-{
-    return (const float*)((const char*)prep.stage16 + held_blob(prep.kpad, D)) + prep.kpad;
 }
 
 template <int H>
@@ -704,13 +629,12 @@ static int launch_held(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, cons
     constexpr size_t lds = 2 * (size_t)held_block_bytes(H) + (4 * 64 + 32 * H) * sizeof(float);
     static_assert(lds <= 65536, "offsets of global_load_lds below 64 KB");
     const HeldArgs<H> h = held_args<H>(prep, p, a);
-    const int64_t tiles = (a.m + held_tile_rows(H) - 1) / held_tile_rows(H);
     using Kernel = void (*)(const BmuArgs, const WideArgs, const HeldArgs<H>);
     const Kernel search = bmu_wide_split_kernel, candidates = bmu_wide_split_cand_kernel;
     if (cand)
         hipLaunchKernelGGL(candidates, dim3(256 * held_waves(H)), dim3(kHThreads), lds, ctx->stream, a, p, h);
     else
-        hipLaunchKernelGGL(search, dim3((unsigned)((tiles + 7) / 8 * 8 * p.splits)), dim3(kHThreads), lds, ctx->stream, a, p, h);
+        hipLaunchKernelGGL(search, dim3((unsigned)p.grid), dim3(kHThreads), lds, ctx->stream, a, p, h);
     return check_hip(ctx, hipGetLastError(), "bmu (held rows) launch");
 }
 

@@ -1,4 +1,5 @@
-// Best-matching-unit search for rows wider than 64 features (the default there): the scores of bmu_split_kernel
+// Best-matching-unit search for rows of more than 256 features on small maps, and what it shares with the other two searches of rows wider
+// than 64 (wide_form): the join, the direct differences and the host side.  The scores are those of bmu_split_kernel
 // (som_bmu.hip: samples and weights cut into two bf16 parts, three bf16 MFMA products per float32 product) as a tiled
 // matrix product with the running arg-max behind it; N x K is never stored.
 //
@@ -15,7 +16,7 @@
 // 10^6 x 200; the tile, with both operands straight from memory, then took 1410 us instead of 1581: dropped).  Both operands are
 // double-buffered; one barrier per chunk.  Chunks run on without a break across node tiles: a tile's scores are folded
 // while the next tile's first chunk is on the matrix pipe.
-// What bounds it is neither pipe alone: at 10^6 x 200 the matrix pipes are busy 42 % of the time and the vector units, with 6.9
+// What bounds it is neither pipe alone: at 10^6 x 200 on 1024 nodes the matrix pipes are busy 42 % of the time and the vector units, with 6.9
 // instructions for each MFMA (of a wavefront's 331 a chunk, 128 add the chunk's products up), 36 %, but only a quarter of those run
 // beside an MFMA, and for 30 % of the time neither works; an MFMA takes 36 to 39 ns where the probe sustains 23 with six vector
 // instructions beside each, and the clock stays at 2.24 GHz.
@@ -412,13 +413,12 @@ __device__ __forceinline__ void wide_tile(const BmuArgs& a, const WideArgs& p, i
             if (oct == 0 && i < total) p.norm[i] = make_float4(s, w, l, 0.0f);
         }
     }
-    // ---- a sample's eight class winners of this workgroup: the two best with their ids, and the highest of all others
+    // ---- a sample's eight class winners of this workgroup
     __syncthreads();
     if (tid < kWTile) {
         const int64_t i = tile * kWTile + tid;
         const float* base = reinterpret_cast<const float*>(lds + 4 * kWBuf);
-        float b1 = -INFINITY, b2 = -INFINITY, others = -INFINITY;
-        int id1 = 0, id2 = 0;
+        BestFour best(-INFINITY);
 #pragma unroll
         for (int wn1 = 0; wn1 < 2; ++wn1)
 #pragma unroll
@@ -430,26 +430,10 @@ __device__ __forceinline__ void wide_tile(const BmuArgs& a, const WideArgs& p, i
                     const float v = st[0];
                     const int where = __float_as_int(st[128]);
                     const int r = 2 * (int)(__float_as_uint(v) & 7u) + c;
-                    const int id = (where >> 2) * kWTile + (2 * (where & 3) + wn1) * 32 + 8 * (r >> 2) + 4 * g1 + (r & 3);
-                    others = fmaxf(others, st[64]);
-                    if (v > b1) {
-                        others = fmaxf(others, b2);
-                        b2 = b1;
-                        id2 = id1;
-                        b1 = v;
-                        id1 = id;
-                    } else if (v > b2) {
-                        others = fmaxf(others, b2);
-                        b2 = v;
-                        id2 = id;
-                    } else {
-                        others = fmaxf(others, v);
-                    }
+                    best.others = fmaxf(best.others, st[64]);
+                    best.add(v, (where >> 2) * kWTile + (2 * (where & 3) + wn1) * 32 + 8 * (r >> 2) + 4 * g1 + (r & 3));
                 }
-        if (i < total) {
-            p.best[(size_t)split * p.rows + i] = make_float4(b1, b2, others, __int_as_float(id1));
-            p.id2[(size_t)split * p.rows + i] = (uint32_t)id2;
-        }
+        if (i < total) best.write(p, split, i, 1.0f);
     }
 }
 
@@ -488,7 +472,7 @@ __global__ void __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(
 constexpr int kJoinThreads = 1024;
 static int join_threads(int64_t m) { return m >= 256 * (int64_t)kJoinThreads ? kJoinThreads : 256; }
 
-template <bool HELD>
+template <bool PARTS>
 __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuArgs a, const WideArgs p)
 {
     __shared__ unsigned int wave_base[2][kJoinThreads / 64];
@@ -501,13 +485,14 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
     if (live) {
         float best = -INFINITY, second = -INFINITY;
         int node = 0;
-        for (int s0 = 0; s0 < p.splits; s0 += 4) {               // (four loads under way)
+        const int splits = i < p.tail_row ? p.splits : p.tail_splits;
+        for (int s0 = 0; s0 < splits; s0 += 4) {                 // (four loads under way)
             float4 r4[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) r4[u] = p.best[(size_t)(s0 + u < p.splits ? s0 + u : s0) * p.rows + i];
+            for (int u = 0; u < 4; ++u) r4[u] = p.best[(size_t)(s0 + u < splits ? s0 + u : s0) * p.rows + i];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                if (s0 + u >= p.splits) break;
+                if (s0 + u >= splits) break;
                 const float4 r = r4[u];
                 const bool up = r.x > best;
                 second = fmaxf(fmaxf(second, up ? best : r.x), fmaxf(r.y, r.z));
@@ -525,9 +510,9 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
         // accumulators; six units for the centrings and -|w|^2 / 2.
         constexpr float unit = 5.9604645e-08f;
         auto root = [](float v) { return __builtin_amdgcn_sqrtf(v); };      // within a unit in the last place
-        const float wmax2 = __uint_as_float(a.scal[0]), wmax = root(wmax2) * 1.00001f;
+        const float wmax2 = __uint_as_float(a.scal[0]), wmax = root(wmax2 + kSquaresFloor) * 1.00001f;
         float nx, err_w, err_0, err_n;
-        if constexpr (HELD) {
+        if constexpr (PARTS) {
             nx = n.x;
             err_w = n.y;
             err_0 = n.z;
@@ -545,30 +530,32 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
             err_n = 0.5f * (6.0f + add) * unit;
         }
         const float wn = -2.0f * p.norms[node];
-        const float wb = fminf(root(wn) * 1.00001f, wmax);
+        const float wb = fminf(root(wn + kSquaresFloor) * 1.00001f, wmax);
         const float err_b = err_w * wb + err_0 + err_n * wb * wb;
         const float bits = fabsf(best) * (1.01f * 1.9073486e-06f);          // two scores' position bits
         const float far2 = fmaxf(nx * nx * 1.00001f - 2.0f * best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
         const float wo = fminf((nx + root(far2)) * 1.0001f, wmax);          // norm of any node as near as the winner
-        const float bound = err_b + err_w * wo + err_0 + err_n * wo * wo + bits;
+        const float bound = err_b + err_w * wo + err_0 + err_n * wo * wo + bits + kSquaresFloor;
         close = a.K > 1 && !((best - second) > bound);
         cut = best - bound;
         a.bmu[i] = node;
         if (a.qe) {
             // the statistic n_recheck: best two scores inside a band of fixed relative width, as in bmu_split_tile
             const float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(196 + (a.D + 63) / 64 + 1) * unit) + 12.0f * unit;
-            near = close || (a.K > 1 && !((best - second) > ((HELD ? nx : root(n.x)) * wmax + 0.5f * wmax2) * rel));
+            near = close || (a.K > 1 && !((best - second) > ((PARTS ? nx : root(n.x)) * wmax + 0.5f * wmax2) * rel));
         }
         if (close) {
             uint32_t* rec = p.record + i * kWRecord;
             uint16_t* ids = reinterpret_cast<uint16_t*>(rec + 1);
             int hits = 0;
             open = a.K > 65536 || !(cut == cut);
-            for (int s = 0; s < p.splits && !open; ++s) {
+            for (int s = 0; s < splits && !open; ++s) {
                 const float4 r = p.best[(size_t)s * p.rows + i];
-                const uint32_t id2 = p.id2[(size_t)s * p.rows + i];
+                const uint4 q = p.next[(size_t)s * p.rows + i];
                 if (r.x >= cut && hits < kWIds) ids[hits++] = (uint16_t)__float_as_int(r.w);
-                if (r.y >= cut && hits < kWIds) ids[hits++] = (uint16_t)id2;
+                if (r.y >= cut && hits < kWIds) ids[hits++] = (uint16_t)q.z;
+                if (__uint_as_float(q.x) >= cut && hits < kWIds) ids[hits++] = (uint16_t)(q.z >> 16);
+                if (__uint_as_float(q.y) >= cut && hits < kWIds) ids[hits++] = (uint16_t)q.w;
                 open = open || r.z >= cut || hits >= kWIds;
             }
             rec[0] = open ? 0u : (unsigned)hits;                 // an open sample's record is filled by the candidate pass
@@ -620,7 +607,7 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
 __global__ void __launch_bounds__(256) bmu_wide_exact_kernel(const BmuArgs a, const WideArgs p)
 {
     const unsigned int n_open = a.scal[a.slot], n_known = a.scal[a.slot + 1], count = n_open + n_known;
-    const int sub = threadIdx.x & 15;
+    const int sub = threadIdx.x & 15, whole = a.D / 64 * 64;
     constexpr unsigned int per_group = 256 / 16;
     for (unsigned int p0 = blockIdx.x * per_group; p0 < count; p0 += gridDim.x * per_group) {
         const unsigned int q = p0 + (threadIdx.x >> 4);
@@ -647,28 +634,42 @@ __global__ void __launch_bounds__(256) bmu_wide_exact_kernel(const BmuArgs a, co
                 node[tt] = k < a.K ? k : -1;
                 d[tt] = 0.0f;
             }
-            for (int f0 = 0; f0 < a.D; f0 += 64) {
-                float xv[4], wv[kBatch][4];
-                int fo[4];
+            const float* wr[kBatch];
+#pragma unroll
+            for (int tt = 0; tt < kBatch; ++tt) wr[tt] = a.W + (size_t)(node[tt] >= 0 ? node[tt] : 0) * a.D;
+            auto add4 = [](float& sum, const float4& x, const float4& w) {
+                const float d0 = x.x - w.x, d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
+                sum = fmaf(d0, d0, sum);
+                sum = fmaf(d1, d1, sum);
+                sum = fmaf(d2, d2, sum);
+                sum = fmaf(d3, d3, sum);
+            };
+            int f = 4 * sub;
+            for (; f + 3 * 64 < whole; f += 4 * 64) {            // (twelve loads under way)
+                float4 x[4], w[kBatch][4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int f = f0 + 16 * u + sub;
-                    fo[u] = f < a.D ? f : -1;
-                    xv[u] = xr[fo[u] >= 0 ? f : a.D - 1];
+                    x[u] = load4(xr + f + 64 * u);
+#pragma unroll
+                    for (int tt = 0; tt < kBatch; ++tt) w[tt][u] = load4(wr[tt] + f + 64 * u);
                 }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int tt = 0; tt < kBatch; ++tt) add4(d[tt], x[u], w[tt][u]);
+            }
+            for (; f < whole; f += 64) {
+                const float4 x = load4(xr + f);
+#pragma unroll
+                for (int tt = 0; tt < kBatch; ++tt) add4(d[tt], x, load4(wr[tt] + f));
+            }
+            for (int t = whole + sub; t < a.D; t += 16) {
+                const float x = xr[t];
 #pragma unroll
                 for (int tt = 0; tt < kBatch; ++tt) {
-                    const float* wr = a.W + (size_t)(node[tt] >= 0 ? node[tt] : 0) * a.D;
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) wv[tt][u] = wr[fo[u] >= 0 ? fo[u] : a.D - 1];
+                    const float df = x - wr[tt][t];
+                    d[tt] = fmaf(df, df, d[tt]);
                 }
-#pragma unroll
-                for (int tt = 0; tt < kBatch; ++tt)
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const float df = fo[u] >= 0 ? xv[u] - wv[tt][u] : 0.0f;
-                        d[tt] = fmaf(df, df, d[tt]);
-                    }
             }
 #pragma unroll
             for (int tt = 0; tt < kBatch; ++tt) {
@@ -734,13 +735,13 @@ __global__ void __launch_bounds__(256) bmu_wide_distance_kernel(const BmuArgs a)
 // ---------------------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------------------
-size_t bmu_wide_blob_bytes(int32_t K, int32_t D)
+static size_t tile_blob_bytes(int32_t K, int32_t D)
 {
     const size_t tiles = ((size_t)K + kWTile - 1) / kWTile, nch = ((size_t)D + kWChunk - 1) / kWChunk;
     return tiles * nch * kWBuf + tiles * kWTile * sizeof(float);
 }
 
-int bmu_wide_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, const BmuPrep& prep, double* qe, int32_t* small)
+static int tile_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, const BmuPrep& prep, double* qe, int32_t* small)
 {
     const int tiles = (K + kWTile - 1) / kWTile, nch = (D + kWChunk - 1) / kWChunk;
     char* blob = (char*)prep.stage16;
@@ -754,80 +755,156 @@ int bmu_wide_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, const B
 // Workgroups per sample tile: enough that the compute units are busy to the end.  A unit takes one workgroup at a time
 // (LDS), so the time goes with rounds x node tiles per workgroup, plus about half a node tile's chunks for filling the
 // pipeline and writing the results.
-static int wide_splits(int64_t tiles_m, int tiles, int nch, int units)
+static void tile_plan(WideArgs& p, int64_t m, int32_t K, int32_t D, int units)
 {
+    p.tiles = (K + kWTile - 1) / kWTile;
+    p.nch = (D + kWChunk - 1) / kWChunk;
+    const int64_t tiles_m = (m + kWTile - 1) / kWTile;
     int best = 1;
     double best_cost = 0.0;
-    for (int s = 1; s <= tiles && s <= 16; ++s) {
-        const int per = (tiles + s - 1) / s;
-        if ((tiles + per - 1) / per != s) continue;
+    for (int s = 1; s <= p.tiles && s <= 16; ++s) {
+        const int per = (p.tiles + s - 1) / s;
+        if ((p.tiles + per - 1) / per != s) continue;
         const double rounds = (double)((tiles_m * s + units - 1) / units);
-        const double cost = rounds * ((double)per * nch + 3.0);
+        const double cost = rounds * ((double)per * p.nch + 3.0);
         if (s == 1 || cost < best_cost * 0.98) {
             best = s;
             best_cost = cost;
         }
     }
-    return best;
+    p.norms = (const float*)(p.blob + (size_t)p.tiles * p.nch * kWBuf);
+    p.set_splits(m, best, (p.tiles + best - 1) / best, (tiles_m + 7) / 8 * 8 * best);
+}
+
+static int tile_launch(som_ctx* ctx, const BmuArgs& a, const WideArgs& p, bool cand)
+{
+    if (cand) {
+        const int64_t most = (a.m + kWTile - 1) / kWTile * p.tiles;
+        hipLaunchKernelGGL(bmu_wide_split_cand_kernel, dim3((unsigned)(most < 256 ? most : 256)), dim3(kWThreads), kWLds, ctx->stream, a, p);
+    } else {
+        static bool attr_set_dev[kMaxDevices] = {};
+        const void* kernels[] = {reinterpret_cast<const void*>(static_cast<void (*)(const BmuArgs, const WideArgs)>(bmu_wide_split_kernel)),
+                                 reinterpret_cast<const void*>(static_cast<void (*)(const BmuArgs, const WideArgs)>(bmu_wide_split_cand_kernel))};
+        if (int rc = wide_raise_lds(ctx, attr_set_dev, kernels, kWLds)) return rc;
+        hipLaunchKernelGGL(bmu_wide_split_kernel, dim3((unsigned)p.grid), dim3(kWThreads), kWLds, ctx->stream, a, p);
+    }
+    return check_hip(ctx, hipGetLastError(), "bmu (wide, split) launch");
+}
+
+int wide_raise_lds(som_ctx* ctx, bool* done, const void* const (&kernels)[2], size_t bytes)
+{
+    bool& attr_set = done[ctx->device];               // the attribute belongs to the device, not to the process
+    if (attr_set) return SOM_OK;
+    for (const void* k : kernels)
+        if (int rc = check_hip(ctx, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes), "raising the dynamic LDS limit"))
+            return rc;
+    attr_set = true;
+    return SOM_OK;
+}
+
+size_t bmu_wide_blob_bytes(int32_t K, int32_t D, int32_t kpad)
+{
+    switch (wide_form(K, D)) {
+    case kWideHeld: return bmu_held_blob_bytes(kpad, D);
+    case kWideCut: return bmu_cut_blob_bytes(K, D);
+    default: return tile_blob_bytes(K, D);
+    }
+}
+
+float* bmu_wide_spread(const BmuPrep& prep, int32_t K, int32_t D)
+{
+    switch (wide_form(K, D)) {
+    case kWideHeld: return bmu_held_spread(prep, D);
+    case kWideCut: return bmu_cut_spread(prep, K, D);
+    default: return nullptr;
+    }
+}
+
+int bmu_wide_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, const BmuPrep& prep, double* qe, int32_t* small)
+{
+    switch (wide_form(K, D)) {
+    case kWideHeld: return bmu_held_prepare(ctx, W, K, D, prep, qe, small);
+    case kWideCut: return bmu_cut_prepare(ctx, W, K, D, prep, qe, small);
+    default: return tile_prepare(ctx, W, K, D, prep, qe, small);
+    }
 }
 
 static WideArgs wide_args(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t D, int64_t m)
 {
     WideArgs p{};
-    p.tiles = (K + kWTile - 1) / kWTile;
-    p.nch = (D + kWChunk - 1) / kWChunk;
     p.blob = (const char*)prep.stage16;
-    const int units = ctx->units > 0 ? ctx->units : 256;
-    const bool held = D <= kHeldFeatures;
-    p.norms = held ? bmu_held_norms(prep, D) : (const float*)(p.blob + (size_t)p.tiles * p.nch * kWBuf);
-    p.splits = held ? bmu_held_splits(m, K, D, units) : wide_splits((m + kWTile - 1) / kWTile, p.tiles, p.nch, units);
-    p.per_split = (p.tiles + p.splits - 1) / p.splits;
     p.rows = m;
+    const int units = ctx->units > 0 ? ctx->units : 256;
+    switch (wide_form(K, D)) {
+    case kWideHeld: bmu_held_plan(p, prep, m, K, D, units); break;
+    case kWideCut: bmu_cut_plan(p, prep, m, K, D, units); break;
+    default: tile_plan(p, m, K, D, units); break;
+    }
     return p;
+}
+
+static int wide_launch(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, const WideArgs& p, bool cand)
+{
+    switch (wide_form(a.K, a.D)) {
+    case kWideHeld: return bmu_held_launch(ctx, prep, a, p, cand);
+    case kWideCut: return bmu_cut_launch(ctx, a, p, cand);
+    default: return tile_launch(ctx, a, p, cand);
+    }
 }
 
 // Lists up to this length go to the all-nodes pass at once: a candidate tile takes one pass over its chunks however few entries it has, the
 // all-nodes pass K D differences an entry.  (That pass takes 33 us at K D = 200,000 and 110 at 800,000 for any list of up to 256
-// entries, a candidate pass of held rows 4 to 15: none of its lists is short enough.)
-static uint32_t cand_min_for(const BmuArgs& a) { return a.K > 65536 ? 0xffffffffu : a.D <= kHeldFeatures ? 0u : 256u; }
+// entries, a candidate pass of held rows 4 to 15, and of rows cut beforehand 14 us where it takes 48 (300 x 1024) and 76 where it takes 322
+// (2000 x 1024): none of their lists is short enough.)
+static uint32_t cand_min_for(const BmuArgs& a) { return a.K > 65536 ? 0xffffffffu : wide_form(a.K, a.D) != kWideTile ? 0u : 256u; }
 
-// bytes of the pass's workspace: per-split winners, norms, candidate records
+// A pass's workspace: per-split winners, norms, candidate records, and the parts of rows cut beforehand with their scales.
+static size_t wide_work(WideArgs& p, char* w, int32_t K, int32_t D, int64_t m)
+{
+    size_t at = 0;
+    auto take = [&](size_t bytes) {
+        char* q = w + at;
+        at += (bytes + 255) / 256 * 256;
+        return q;
+    };
+    p.best = (float4*)take((size_t)m * p.most_splits * sizeof(float4));
+    p.norm = (float4*)take((size_t)m * sizeof(float4));
+    p.record = (uint32_t*)take((size_t)m * kWRecord * sizeof(uint32_t));
+    p.next = (uint4*)take((size_t)m * p.most_splits * sizeof(uint4));
+    if (wide_form(K, D) == kWideCut) {
+        p.scales = (float*)take(bmu_cut_scales_bytes(D, m));
+        p.cut = take(bmu_cut_parts_bytes(D, m));
+    }
+    return at;
+}
+
 size_t bmu_wide_work_bytes(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t D, int64_t m)
 {
-    const WideArgs p = wide_args(ctx, prep, K, D, m);
-    return (size_t)m * ((size_t)p.splits * 20 + 16 + kWRecord * 4) + 64;
+    WideArgs p = wide_args(ctx, prep, K, D, m);
+    return wide_work(p, nullptr, K, D, m);
+}
+
+// most rows of a pass: some hundred bytes a sample, and the parts of rows cut beforehand
+int64_t bmu_wide_pass_rows(int32_t K, int32_t D)
+{
+    const int64_t most = (int64_t)1 << 24;
+    if (wide_form(K, D) != kWideCut) return most;
+    const int64_t rows = bmu_cut_pass_rows(D);
+    return rows < most ? rows : most;
 }
 
 int bmu_wide_run(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work)
 {
     WideArgs p = wide_args(ctx, prep, a.K, a.D, a.m);
-    char* w = (char*)work;
-    p.best = (float4*)w;
-    p.norm = (float4*)(w + (size_t)a.m * p.splits * 16);
-    p.record = (uint32_t*)(w + (size_t)a.m * (p.splits * 16 + 16));
-    p.id2 = (uint32_t*)(w + (size_t)a.m * (p.splits * 16 + 16 + kWRecord * 4));
+    wide_work(p, (char*)work, a.K, a.D, a.m);
     p.cand_min = cand_min_for(a);
+    if (int rc = wide_launch(ctx, prep, a, p, false)) return rc;
     const int per_join = join_threads(a.m);
     const dim3 join_grid((unsigned)((a.m + per_join - 1) / per_join)), join_block(per_join);
-    if (a.D <= kHeldFeatures) {
-        if (int rc = bmu_held_launch(ctx, prep, a, p, false)) return rc;
+    if (wide_form(a.K, a.D) == kWideTile)
+        hipLaunchKernelGGL(bmu_wide_join_kernel<false>, join_grid, join_block, 0, ctx->stream, a, p);
+    else
         hipLaunchKernelGGL(bmu_wide_join_kernel<true>, join_grid, join_block, 0, ctx->stream, a, p);
-        return check_hip(ctx, hipGetLastError(), "bmu (held rows) join launch");
-    }
-    static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
-    bool& attr_set = attr_set_dev[ctx->device];
-    if (!attr_set) {
-        for (const void* k : {reinterpret_cast<const void*>(bmu_wide_split_kernel), reinterpret_cast<const void*>(bmu_wide_split_cand_kernel)})
-            if (int rc = check_hip(ctx, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWLds),
-                                   "raising the dynamic LDS limit"))
-                return rc;
-        attr_set = true;
-    }
-    const int64_t tiles_m = (a.m + kWTile - 1) / kWTile;
-    const int64_t blocks = (tiles_m + 7) / 8 * 8 * p.splits;
-    hipLaunchKernelGGL(bmu_wide_split_kernel, dim3((unsigned)blocks), dim3(kWThreads), kWLds, ctx->stream, a, p);
-    if (int rc = check_hip(ctx, hipGetLastError(), "bmu (wide, split) kernel launch")) return rc;
-    hipLaunchKernelGGL(bmu_wide_join_kernel<false>, join_grid, join_block, 0, ctx->stream, a, p);
     return check_hip(ctx, hipGetLastError(), "bmu (wide, split) join launch");
 }
 
@@ -835,16 +912,9 @@ int bmu_wide_run(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work
 int bmu_wide_recheck(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work)
 {
     WideArgs p = wide_args(ctx, prep, a.K, a.D, a.m);
-    char* w = (char*)work;
-    p.record = (uint32_t*)(w + (size_t)a.m * (p.splits * 16 + 16));
+    wide_work(p, (char*)work, a.K, a.D, a.m);
     p.cand_min = cand_min_for(a);
-    if (a.D <= kHeldFeatures) {
-        if (int rc = bmu_held_launch(ctx, prep, a, p, true)) return rc;
-    } else {
-        const int64_t most = (a.m + kWTile - 1) / kWTile * p.tiles;
-        hipLaunchKernelGGL(bmu_wide_split_cand_kernel, dim3((unsigned)(most < 256 ? most : 256)), dim3(kWThreads), kWLds, ctx->stream, a, p);
-        if (int rc = check_hip(ctx, hipGetLastError(), "bmu (wide, split) candidate launch")) return rc;
-    }
+    if (int rc = wide_launch(ctx, prep, a, p, true)) return rc;
     const int64_t groups = (a.m + 15) / 16;
     hipLaunchKernelGGL(bmu_wide_exact_kernel, dim3((unsigned)(groups < 2048 ? groups : 2048)), dim3(256), 0, ctx->stream, a, p);
     return check_hip(ctx, hipGetLastError(), "bmu (wide, split) candidate-distance launch");

@@ -16,7 +16,7 @@ constexpr int kMaxStepsResident = 32; // BMU kernel keeps a sample's features in
 
 struct BmuPrep {
     float* stage = nullptr;        // [Kpad / 128][nch] blobs: 128 padded weight rows of a chunk, then -|w|^2 / 2
-    void* stage16 = nullptr;       // bf16 hi/lo parts of the weights for the split search (D <= 64: stage rows; D > 64: som_bmu_wide.hip), else null
+    void* stage16 = nullptr;       // parts of the weights for the split searches (D <= 64: stage rows of bf16 parts; D > 64: wide_form), else null
     float* wrow = nullptr;         // [K][D] the weights as given in the stages' order (split search for D <= 64)
     int kb = 0;                    // whole 16-feature blocks of a stage16 row
     int tail_r = 0;                // features of the packed tail block behind them (0: none; D <= 64 only)
@@ -24,7 +24,8 @@ struct BmuPrep {
     float* centre = nullptr;       // [D] column means of W; stage rows and sample registers hold values minus this
     // Result words, cleared by every preparation: [0] = bits of max_k |w_k - centre|^2, [3] = total,
     // [4], [5] = length of the second list (samples whose candidate slots overflowed; alternating calls),
-    // [12], [13] = length of the list and of the pair list, [14], [15] the next call's, [8], [9] = bits of max_k |w - hi|^2 and |w - hi - lo|^2 (bf16 parts)
+    // [12], [13] = length of the list and of the pair list, [14], [15] the next call's; bf16 parts: [8], [9] = bits of max_k |w - hi|^2 and
+    // |w - hi - lo|^2; half-precision and fp6 parts: [8..10] = of max_k |second part|, |what fp6 leaves of the first|, |of the second|, [11] = the scale
     unsigned int* scal = nullptr;
     // Split search for D <= 64: the three maxima above are found by atomics in [0..2], which are zero whenever no call is in
     // progress; the first pass moves them to [4..6], where later passes read them.  (What a call leaves behind
@@ -149,9 +150,10 @@ int launch_fill_zero(som_ctx* ctx, void* p, size_t bytes);
 int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out, double* qe, int32_t* small);
 int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs args);
 // split search for D > 64 (som_bmu_wide.hip)
-size_t bmu_wide_blob_bytes(int32_t K, int32_t D);
+size_t bmu_wide_blob_bytes(int32_t K, int32_t D, int32_t kpad);
 int bmu_wide_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, const BmuPrep& prep, double* qe, int32_t* small);
 size_t bmu_wide_work_bytes(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t D, int64_t m);
+int64_t bmu_wide_pass_rows(int32_t K, int32_t D);
 int bmu_wide_run(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work);
 int bmu_wide_recheck(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work);
 int bmu_wide_distances(som_ctx* ctx, const BmuArgs& a);

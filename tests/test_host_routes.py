@@ -192,3 +192,23 @@ def test_dynamic_lds_is_raised_on_every_device(library):
     finally:
         for ctx in contexts:
             ctx.close()
+
+
+def test_wide_rows_on_both_sides_of_their_lines(ctx):
+    """Rows of 65 to 256 features are held in registers; wider ones are cut beforehand on maps of more than 320 nodes."""
+    for K, D, cut in ((321, 256, False), (320, 257, False), (321, 257, True), (1024, 2000, True), (70000, 300, True)):
+        rc, names = ctx.bmu(1000, K, D)
+        assert rc == 0 and names.count("bmu_cut_samples_kernel") == cut and ("bmu_wide_split_kernel" in names) != cut, (K, D, names)
+
+
+def test_rows_cut_beforehand_go_in_passes_that_memory_holds(ctx):
+    """The parts of a pass take at most a gigabyte, and where an allocation fails, half as many rows, down to a tile's."""
+    passes = lambda m, K, D: ctx.bmu(m, K, D)[1].count("bmu_cut_samples_kernel")
+    ctx.limit(10 << 20)                                          # the preparation takes 7.6 MB
+    rc, names = ctx.bmu(3000, 400, 2000)
+    assert rc == 0 and names.count("bmu_cut_samples_kernel") > 1
+    ctx.limit(64 << 20)
+    assert passes(100_000, 400, 2000) in range(12, 27)
+    ctx.limit()
+    per = (1 << 30) // (32 * 228) // 256 * 256                   # 32 chunks of 64 features, a row's 224 bytes and a scale each
+    assert passes(per, 400, 2000) == 1 and passes(per + 1, 400, 2000) == 2
