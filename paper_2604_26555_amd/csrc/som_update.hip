@@ -4,7 +4,7 @@
 //     w_j <- Num_j / Den_j  where Den_j >= eps_h, otherwise w_j stays.
 // The contraction Num = H^T S (with n as one more column of S) is a dense K x K . K x (D + 1) product in float64:
 // it runs on v_mfma_f64_16x16x4_f64.
-//   1. contract_kernel     one wavefront = 16 or 32 updated nodes x up to 64 columns x a quarter of a part of the k range; for
+//   1. contract_kernel     one wavefront = 16, 32 or 64 updated nodes x up to 64 columns x a quarter of a part of the k range; for
 //                          D + 1 <= 64 the influences h = exp(-G^2 / 2 sigma^2) are computed in the wavefront right
 //                          where the MFMA needs them (each one is needed exactly once), otherwise influence_kernel
 //                          writes them out first and the wavefronts of the column slabs read them;
@@ -23,21 +23,28 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // Parts of the k range: the four wavefronts of a workgroup take a quarter each and add their results in LDS, and up to
 // kSplitK workgroups share a block of updated nodes where those alone leave the chip idle (their partials are stored, then
 // summed in order).  With sixteen stored partials whatever the shape, the partials were most of the traffic: 262 MB each way
-// at K = 1024, D = 2000 (207 + 53 us for contraction and finish there, 153 to 173 + 7 now; 228 + 28 -> 96 + 5 us at K = 4096, D = 50).
+// at K = 1024, D = 2000 (207 + 53 us for contraction and finish there, 153 to 173 + 7 without; 228 + 28 -> 96 + 5 us at K = 4096, D = 50).
 constexpr int kSplitK = 8;
 
 // The shape of a contraction.  Two wavefronts for every SIMD, so that one's loads and exponentials run beside the other's MFMAs:
 // 4 per block of nodes and 64 columns, more parts where those are too few.  (One for every SIMD: K = 4096, D = 50 150 us, 100 with
 // two; K = 1024, D = 50 17.5, 12.6; K = 437, D = 37 8.8, 6.)
+// Several column blocks: as many nodes a wavefront as leave that many.  S comes straight from L2, 512 bytes for each float64 MFMA and block of
+// sixteen nodes: with one block L2 is what bounds it, four read it a quarter as often.  Whole update, one block, two, four: K = 1024
+// D = 500 66, 48, 44 us, D = 1000 85, 85, 71, D = 2000 122, 120, 116; K = 400 D = 500 24, 26, 26, D = 1000 30, 29, 35, D = 2000 43, 40, 41;
+// K = 256 D = 1000 18.5, 21, 24.  (With the masks of ragged ends on every operand, as one block had them before, K = 1024 D = 500 60,
+// D = 2000 161; the matrix pipe alone would take 54.)
 struct UpdateShape {
     int jt, blocks_j, blocks_c, splits;
 };
 static UpdateShape update_shape(int K, int D)
 {
     UpdateShape u;
-    u.jt = K >= 2048 ? 2 : 1;
-    u.blocks_j = (K + 16 * u.jt - 1) / (16 * u.jt);
     u.blocks_c = (D + 1 + 63) / 64;
+    auto blocks_of = [&](int jt) { return (int64_t)((K + 16 * jt - 1) / (16 * jt)) * u.blocks_c; };
+    if (u.blocks_c > 1) u.jt = K >= 1024 && blocks_of(4) >= 100 ? 4 : K >= 400 && blocks_of(2) >= 128 ? 2 : 1;
+    else u.jt = K >= 2048 ? 2 : 1;
+    u.blocks_j = (K + 16 * u.jt - 1) / (16 * u.jt);
     const int64_t blocks = (int64_t)u.blocks_j * u.blocks_c;
     u.splits = blocks >= 512 ? 1 : blocks >= 256 ? 2 : blocks >= 128 ? 4 : kSplitK;
     return u;
@@ -102,7 +109,7 @@ __global__ void __launch_bounds__(256) influence_kernel(const float* __restrict_
 // grid (ceil(K / (16 JT)), ceil((D + 1) / 64), splits), 4 wavefronts per workgroup, a quarter of the workgroup's k range each.
 // MFMA operands (16 x 16 x 4, float64): lane l supplies A[i = l % 16][k = l / 16] = h[k][j0 + i] and
 // B[k = l / 16][c = l % 16] = S[k][c0 + c] (column D is n); its register r receives row l / 16 + 4 r, column l % 16.
-// JT = 2: two blocks of sixteen updated nodes per wavefront, for maps with enough of them: S is read half as often.
+// JT: blocks of sixteen updated nodes per wavefront.
 template <bool FUSED, int JT>
 __global__ void __launch_bounds__(256, 2) contract_kernel(const float* __restrict__ G, const double* __restrict__ H,
                                                        double inv2s2, const double* __restrict__ shift,
@@ -132,7 +139,8 @@ __global__ void __launch_bounds__(256, 2) contract_kernel(const float* __restric
     // kBatch k-steps at a time: first every load of the batch (one wavefront per SIMD has nothing else to cover a
     // round trip to L2 with), then the exponentials, then the MFMAs.
     constexpr int kBatch = FUSED ? 8 : 16 / JT;            // (sixteen with the exponentials take more than 256 registers: one wavefront)
-    auto batch = [&](int kb, auto whole) {
+    // (inner: all columns are of S.  Rows and columns behind the last are formed and not stored.)
+    auto batch = [&](int kb, auto whole, auto inner) {
         float gv[JT][kBatch];
         double nv[JT][kBatch], sv[kBatch][4];
 #pragma unroll
@@ -148,7 +156,7 @@ __global__ void __launch_bounds__(256, 2) contract_kernel(const float* __restric
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int c = c0 + 16 * t + li;
-                sv[s][t] = (c == D) ? (double)n[kc] : S[(size_t)kc * D + (c < D ? c : D - 1)];
+                sv[s][t] = (!inner && c == D) ? (double)n[kc] : S[(size_t)kc * D + (inner || c < D ? c : D - 1)];
             }
         }
 #pragma unroll
@@ -158,14 +166,13 @@ __global__ void __launch_bounds__(256, 2) contract_kernel(const float* __restric
             const bool occupied = !(FUSED && shift) || n[k < K ? k : K - 1] != 0ull;
 #pragma unroll
             for (int q = 0; q < JT; ++q) {
-                const bool in = k < k_hi && j0 + 16 * q + li < K;
+                const bool in = whole || k < k_hi;
                 double h;
                 if (FUSED) h = in ? influence_of((double)gv[q][s], inv2s2, shift_j[q], occupied) : 0.0;
                 else h = in ? nv[q][s] : 0.0;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    const int c = c0 + 16 * t + li;
-                    const double b = (k < k_hi && c <= D) ? sv[s][t] : 0.0;
+                    const double b = whole || k < k_hi ? sv[s][t] : 0.0;
                     acc[q][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(h, b, acc[q][t], 0, 0, 0);
                 }
             }
@@ -174,9 +181,13 @@ __global__ void __launch_bounds__(256, 2) contract_kernel(const float* __restric
     // (a small map's wavefronts end within the first batch, after 7 of 16 steps at K = 437: leaving the others out is 13.1 -> 8.8 us
     // there.  Among the whole batches of a large one the same branches keep loads and MFMAs apart: 173 -> 291 us at K = 1024,
     // D = 2000, so those have none.)
-    int kb = k_lo;
-    for (; kb + 4 * kBatch <= k_hi; kb += 4 * kBatch) batch(kb, std::true_type{});
-    if (kb < k_hi) batch(kb, std::false_type{});
+    auto all = [&](auto inner) {
+        int kb = k_lo;
+        for (; kb + 4 * kBatch <= k_hi; kb += 4 * kBatch) batch(kb, std::true_type{}, inner);
+        if (kb < k_hi) batch(kb, std::false_type{}, inner);
+    };
+    if (c0 + 64 <= D) all(std::true_type{});
+    else all(std::false_type{});
 #pragma unroll
     for (int q = 0; q < JT; ++q) {
         if (q > 0) __syncthreads();
@@ -262,7 +273,7 @@ static int update_launch(som_ctx* ctx, double* H, double* part, double* shift_ws
         hipLaunchKernelGGL(influence_kernel, dim3((unsigned)((h_elems + 255) / 256)), dim3(256), 0, ctx->stream, G, K, inv2s2,
                            (const double*)shift, n, H);
         if (int rc = check_hip(ctx, hipGetLastError(), "influence kernel launch")) return rc;
-        auto kern = jt == 2 ? contract_kernel<false, 2> : contract_kernel<false, 1>;
+        auto kern = jt == 4 ? contract_kernel<false, 4> : jt == 2 ? contract_kernel<false, 2> : contract_kernel<false, 1>;
         hipLaunchKernelGGL(kern, grid, dim3(256), 0, ctx->stream, G, (const double*)H, inv2s2, (const double*)nullptr, S, n, K, D, part);
     }
     if (int rc = check_hip(ctx, hipGetLastError(), "contraction kernel launch")) return rc;
