@@ -1882,100 +1882,125 @@ __global__ void __launch_bounds__(256) bmu_cand_exact_kernel(const BmuArgs a)
 
 // ---------------------------------------------------------------------------------------------------------
 // The pair list: samples whose candidates (at most four) the split search already knows (D <= 64).
-// LP lanes (4, 8 or 16: sixteen bytes of a row each) take an entry, a wavefront four entries for each LP lanes a round, on its own (no
-// barrier): the sample's row and two candidates' in one coalesced load each, differences squared and added up in the lane and across the LP
-// lanes; lowest distance, then lowest node index.
+// A wavefront takes a round of entries at a time, on its own (no barrier): LP lanes (4, 8 or 16, sixteen bytes of a row each) fetch one or
+// two entries' rows, the sample's and two candidates', in coalesced loads; the rows meet in the wavefront's part of LDS, the next entries'
+// rows are requested, and one lane per candidate adds its squared differences up, features in order as the other re-decisions do;
+// lowest distance, then lowest node index.
 // The chain sample position -> ids and row number -> rows is three dependent trips to memory: positions are read three rounds ahead, ids and
-// row numbers two, rows one.  10^7 x 50 on 1024 nodes, 3.8 million entries: 410 us, for about 1.2 GB of the rows' lines; one, two, three or
-// four entries a lane's round 438, 412, 415, 487 (the last by registers one workgroup a unit), so it is the lines that bound it.  (With the ids
-// read beside the rows before those that need them, and rows summed out of LDS by a lane a candidate, 501; 900,000 x 25 on 400 nodes 20 us
-// for 14.)
+// row numbers two, rows one, and two workgroups of eight wavefronts fit a unit.  10^7 x 50 on 1024 nodes, 3.8 million entries: 440 us, by the lines
+// of their rows; sums across the LP lanes instead of out of LDS take 410, but they add in another order, and a sample that lies between two nodes
+// must not go to one of them in a look-up and to the other in an epoch.
+// (With the ids read a round ahead, beside the rows before those that need them, and sixteen entries a round, whose registers left one workgroup
+// a unit, 10^7 x 50 on 1024 nodes, 3.8 million entries, took 501 us; 900,000 x 25 on 400 nodes 20 us for 13.)
 // The few entries with a third or fourth candidate wait in LDS until there is a round of them.
 // (Served in the round where they came, nearly every round waited for their rows: 4.0 million entries of 10^7 x 50 took 0.62 ms
 // for 0.48.)
 // ---------------------------------------------------------------------------------------------------------
-constexpr int kPairEach = 2;                  // entries of LP lanes' round
 constexpr int pair_lanes(int D) { return D <= 16 ? 4 : D <= 32 ? 8 : 16; }
-// bytes of LDS that a wavefront's entries take: two rounds that wait
-constexpr size_t pair_lds(int D) { return 2 * (size_t)kPairEach * (64 / pair_lanes(D)) * sizeof(uint4); }
+constexpr int pair_each(int LP) { return LP == 4 ? 1 : 2; }             // entries of LP lanes' round
+constexpr int pair_round(int LP) { return pair_each(LP) * (64 / LP); }
+// float4 of LDS that a wavefront's entries take: three rows (an odd number each, so that the lanes' 16-byte reads fall into distinct
+// banks), their ids, and twice as many entries that wait
+__host__ __device__ constexpr int pair_lds_f4(int D, int LP) { return pair_round(LP) * (3 * (((D + 3) / 4) | 1) + 1 + 2); }
 
 template <int LP>
-__device__ __forceinline__ void pair_list(const BmuArgs& a, char* __restrict__ lds)
+__device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__ lds)
 {
-    constexpr int EACH = kPairEach, ROUND = EACH * (64 / LP);
+    constexpr int EACH = pair_each(LP), GROUPS = 64 / LP, ROUND = pair_round(LP);
+    static_assert(2 * ROUND <= 64, "a lane a candidate");
     const unsigned int count = a.scal[a.slot + 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int sub = lane & (LP - 1), grp = lane / LP;
-    uint4* const later = reinterpret_cast<uint4*>(lds) + wave * 2 * ROUND;      // third and fourth id, sample position, nearest so far (distance, row of the stages)
+    const int D = a.D, whole = D / 4, rest = D - 4 * whole;
+    const int stride = ((D + 3) / 4) | 1;             // float4 of a row
+    float4* const rows = lds + wave * pair_lds_f4(D, LP);
+    uint4* const info = reinterpret_cast<uint4*>(rows + ROUND * 3 * stride);      // [entry] ids, sample position
+    uint4* const later = info + ROUND;                // [2 ROUND] third and fourth id, sample position, nearest so far (distance, row of the stages)
     unsigned int waiting = 0u;
+    const int start = 4 * sub < D - 4 ? 4 * sub : D - 4;           // window inside the row
+    const bool own = 4 * sub < D;
     const unsigned int step = gridDim.x * (kExactThreads / 64) * ROUND;
     const unsigned int first = (blockIdx.x * (kExactThreads / 64) + wave) * ROUND;
     if (first >= count) return;
-    // the window [start, start + 4), inside the row; its elements from `shift` on are this lane's own
-    const int start = 4 * sub < a.D - 4 ? 4 * sub : a.D - 4, shift = 4 * sub - start;
     const unsigned int k_most = (unsigned int)a.K - 1u;
-    auto row_of = [&](unsigned int id) { return load4(a.wrow + (size_t)(id < k_most ? id : k_most) * a.D + start); };
+    auto row_of = [&](unsigned int id) { return load4(a.wrow + (size_t)(id < k_most ? id : k_most) * D + start); };
     float4 x[EACH], w[EACH][2];
-    // entry u's rows (a single candidate's twice)
+    // entry u's rows for this lane's window (a single candidate's twice)
     auto fetch = [&](int u, unsigned int both, uint32_t row) {
         const unsigned int i0 = both & 0xffffu, i1 = both >> 16;
         x[u] = load4(a.X + (int64_t)row * a.ldx + start);
         w[u][0] = row_of(i0);
         w[u][1] = row_of(i1 == 0xffffu ? i0 : i1);
     };
-    auto squares = [&](const float4& p, const float4& q) {
-        const float d0 = shift <= 0 ? p.x - q.x : 0.0f, d1 = shift <= 1 ? p.y - q.y : 0.0f, d2 = shift <= 2 ? p.z - q.z : 0.0f,
-                    d3 = shift <= 3 ? p.w - q.w : 0.0f;
-        return fmaf(d3, d3, fmaf(d2, d2, fmaf(d1, d1, d0 * d0)));
+    auto lay = [&](int u) {
+        float4* r = rows + (GROUPS * u + grp) * 3 * stride + sub;
+        if (own) {
+            r[0] = x[u];
+            r[stride] = w[u][0];
+            r[2 * stride] = w[u][1];
+        }
     };
-    // the sum over the LP lanes, in each of them
-    auto all = [](float v) {
-        auto add = [&](auto ctrl) {
-            v += __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), decltype(ctrl)::value, 0xf, 0xf, true));
-        };
-        add(std::integral_constant<int, 0xb1>{});                              // lanes 1, 0, 3, 2 of four
-        add(std::integral_constant<int, 0x4e>{});                              // 2, 3, 0, 1
-        if constexpr (LP > 4) add(std::integral_constant<int, 0x141>{});       // of eight, from the other end
-        if constexpr (LP > 8) add(std::integral_constant<int, 0x140>{});       // of sixteen
-        return v;
-    };
-    // (which node a row of the stages holds matters only where two are exactly as near)
-    auto nearer = [&](float d, int k, float& bd, int& bk) {
+    // this lane's candidate: entry lane / 2, place lane % 2
+    const int e = (lane >> 1) & (ROUND - 1), c = lane & 1;
+    float bd;
+    int bk;                                           // row of the stages
+    // (which node a row holds matters only where two are exactly as near)
+    auto nearer = [&](float d, int k) {
         bool take = d < bd;
         const bool tie = d == bd && d < INFINITY;
         if (__ballot(tie) != 0ull) take = take || (tie && node_of_row(k, a.K) < node_of_row(bk, a.K));
         bd = take ? d : bd;
         bk = take ? k : bk;
     };
-    auto decide = [&](const float (&d)[2], unsigned int both, float& bd, int& bk) {
-        const unsigned int i0 = both & 0xffffu, i1 = both >> 16;
-        nearer(i0 != 0xffffu ? d[0] : INFINITY, (int)i0, bd, bk);
-        nearer(i1 != 0xffffu ? d[1] : INFINITY, (int)i1, bd, bk);
+    auto sum = [&](unsigned int both) {
+        const unsigned int id = c == 0 ? both & 0xffffu : both >> 16;
+        const float4* rx = rows + e * 3 * stride;
+        const float4* rw = rx + (1 + c) * stride;
+        float d = 0.0f;
+        if (lane < 2 * ROUND) {
+#pragma unroll 4
+            for (int q = 0; q < whole; ++q) {
+                const float4 xv = rx[q], wv = rw[q];
+                const float d0 = xv.x - wv.x, d1 = xv.y - wv.y, d2 = xv.z - wv.z, d3 = xv.w - wv.w;
+                d = fmaf(d0, d0, d);
+                d = fmaf(d1, d1, d);
+                d = fmaf(d2, d2, d);
+                d = fmaf(d3, d3, d);
+            }
+            if (rest > 0) {          // the window [D - 4, D): its leading elements are already counted
+                const float4 xv = rx[whole], wv = rw[whole];
+                const float d1 = xv.y - wv.y, d2 = xv.z - wv.z, d3 = xv.w - wv.w;
+                if (rest > 2) d = fmaf(d1, d1, d);
+                if (rest > 1) d = fmaf(d2, d2, d);
+                d = fmaf(d3, d3, d);
+            }
+        }
+        nearer(id != 0xffffu ? d : INFINITY, (int)id);
+        nearer(__shfl_xor(bd, 1), __shfl_xor(bk, 1));
     };
     // up to a round of the entries that wait, the last ones
     auto serve_later = [&]() {
         const unsigned int n = waiting < (unsigned)ROUND ? waiting : (unsigned)ROUND, base = waiting - n;
         __builtin_amdgcn_wave_barrier();
-        uint4 l[EACH];
 #pragma unroll
         for (int u = 0; u < EACH; ++u) {
-            const unsigned int q = (64 / LP) * u + grp;
-            l[u] = later[base + (q < n ? q : 0u)];
-            fetch(u, l[u].x, a.idx ? a.idx[l[u].y] : l[u].y);
+            const unsigned int q = GROUPS * u + grp;
+            const uint4 l = later[base + (q < n ? q : 0u)];
+            fetch(u, l.x, a.idx ? a.idx[l.y] : l.y);
         }
 #pragma unroll
-        for (int u = 0; u < EACH; ++u) {
-            const float d[2] = {all(squares(x[u], w[u][0])), all(squares(x[u], w[u][1]))};
-            float bd = __uint_as_float(l[u].z);
-            int bk = (int)l[u].w;
-            decide(d, l[u].x, bd, bk);
-            if (sub == 0 && (64 / LP) * u + grp < (int)n && bk < a.K) a.bmu[l[u].y] = node_of_row(bk, a.K);
-        }
+        for (int u = 0; u < EACH; ++u) lay(u);
+        __builtin_amdgcn_wave_barrier();
+        const uint4 l = later[base + ((unsigned)e < n ? (unsigned)e : 0u)];
+        bd = __uint_as_float(l.z);
+        bk = (int)l.w;
+        sum(l.x);
+        if (lane < 2 * (int)n && c == 0 && bk < a.K) a.bmu[l.y] = node_of_row(bk, a.K);
         waiting = base;
         __builtin_amdgcn_wave_barrier();
     };
     auto position = [&](unsigned int p, int u) {
-        const unsigned int q = p + (64 / LP) * u + grp;
+        const unsigned int q = p + GROUPS * u + grp;
         return a.recheck_end[-1 - (int64_t)(q < count ? q : count - 1)];
     };
     auto after = [&](unsigned int p) { return count - p > step ? p + step : p; };     // (the last round's again at the end)
@@ -2010,38 +2035,29 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, char* __restrict__ l
             row2[u] = a.idx ? a.idx[at2[u]] : at2[u];
             at3[u] = position(p3, u);
         }
-        float d[EACH][2];
+        // this round's rows to LDS, the next one's on their way
 #pragma unroll
         for (int u = 0; u < EACH; ++u) {
-            d[u][0] = squares(x[u], w[u][0]);
-            d[u][1] = squares(x[u], w[u][1]);
+            lay(u);
+            if (sub == 0) info[GROUPS * u + grp] = make_uint4(ids[u].x, ids[u].y, at[u], 0u);
         }
+        __builtin_amdgcn_wave_barrier();
         const bool last = count - p0 <= step;
         if (!last)
 #pragma unroll
             for (int u = 0; u < EACH; ++u) fetch(u, ids1[u].x, row1[u]);
-        unsigned int more = 0u;
-        float bd[EACH];
-        int bk[EACH];
-#pragma unroll
-        for (int u = 0; u < EACH; ++u) {
-            const float sums[2] = {all(d[u][0]), all(d[u][1])};
-            bd[u] = INFINITY;
-            bk[u] = 0x7fffffff;
-            decide(sums, ids[u].x, bd[u], bk[u]);
-            const bool mine = sub == 0 && p0 + (64 / LP) * u + grp < count;
-            if (mine && ids[u].y != 0xffffffffu) more |= 1u << u;
-            else if (mine && bk[u] < a.K) a.bmu[at[u]] = node_of_row(bk[u], a.K);
-        }
-        if (__ballot(more != 0u) != 0ull) {
-#pragma unroll
-            for (int u = 0; u < EACH; ++u) {
-                const bool waits = (more >> u & 1u) != 0u;
-                const unsigned long long wait = __ballot(waits);
-                const unsigned int to = waiting + __builtin_amdgcn_mbcnt_hi((unsigned)(wait >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)wait, 0));
-                if (waits) later[to] = make_uint4(ids[u].y, at[u], __float_as_uint(bd[u]), (unsigned)bk[u]);
-                waiting += (unsigned)__popcll(wait);
-            }
+        const uint4 my = info[e];
+        const bool mine = lane < 2 * ROUND && p0 + e < count && c == 0;
+        bd = INFINITY;
+        bk = 0x7fffffff;
+        sum(my.x);
+        const bool more = mine && my.y != 0xffffffffu;
+        if (mine && !more && bk < a.K) a.bmu[my.z] = node_of_row(bk, a.K);
+        const unsigned long long wait = __ballot(more);
+        if (wait != 0ull) {
+            const unsigned int to = waiting + __builtin_amdgcn_mbcnt_hi((unsigned)(wait >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)wait, 0));
+            if (more) later[to] = make_uint4(my.y, my.z, __float_as_uint(bd), (unsigned)bk);
+            waiting += (unsigned)__popcll(wait);
             if (waiting >= (unsigned)ROUND) {
                 // (the next round's rows make room, and come again)
                 serve_later();
@@ -2050,6 +2066,7 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, char* __restrict__ l
                     for (int u = 0; u < EACH; ++u) fetch(u, ids1[u].x, row1[u]);
             }
         }
+        __builtin_amdgcn_wave_barrier();
         if (last) break;
 #pragma unroll
         for (int u = 0; u < EACH; ++u) {
@@ -2067,7 +2084,7 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, char* __restrict__ l
 template <bool PAIRS>
 __global__ void __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(4))) bmu_exact_kernel(const BmuArgs a)
 {
-    // entries of the pair list that wait, then the slab of the listed samples' features
+    // PAIRS: three rows of each entry of the pair list in hand; otherwise only the slab of the listed samples' features
     extern __shared__ float4 lds4[];
     float4 (*xs4)[kExactGroup / 4] = reinterpret_cast<float4 (*)[kExactGroup / 4]>(lds4);   // [feature within a 64-wide slab][sample]
     constexpr int kWaves = kExactThreads / 64;
@@ -2097,9 +2114,9 @@ __global__ void __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per
     double qs = 0.0, qs2 = 0.0;
     if constexpr (PAIRS) {
         switch (pair_lanes(a.D)) {
-        case 4: pair_list<4>(a, reinterpret_cast<char*>(lds4)); break;
-        case 8: pair_list<8>(a, reinterpret_cast<char*>(lds4)); break;
-        default: pair_list<16>(a, reinterpret_cast<char*>(lds4)); break;
+        case 4: pair_list<4>(a, lds4); break;
+        case 8: pair_list<8>(a, lds4); break;
+        default: pair_list<16>(a, lds4); break;
         }
     }
     // (PAIRS: from the last workgroup on, so that a short list goes to workgroups without pairs: the kernel 17.5 -> 13.6 us at
@@ -2875,7 +2892,8 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     }
     if (a.K > 1) {
         if (prep.stage16 && prep.nch == 1) {
-            const size_t wait = (size_t)(kExactThreads / 64) * pair_lds(a.D), lds = wait > kExactLds ? wait : kExactLds;
+            // (at most 55 KB: two workgroups of 128 registers a thread fit a compute unit)
+            const size_t rows = (size_t)(kExactThreads / 64) * pair_lds_f4(a.D, pair_lanes(a.D)) * 16, lds = rows > kExactLds ? rows : kExactLds;
             BmuArgs b = a;                       // the distances come afterwards, for all samples
             b.d2 = nullptr;
             b.qe = nullptr;
