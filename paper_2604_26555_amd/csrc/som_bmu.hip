@@ -203,8 +203,9 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
 //     block that is mostly padding) but one packed block whose sixteen slots hold the three products side by side,
 //         weights  [ hi(r) | hi(r) | lo(r) | norm parts (3) | 0 ... ]   against samples  [ hi(r) | lo(r) | hi(r) | 1 1 1 | 0 ... ],
 //     one MFMA.
-//   * Norms: -|w|^2 / 2 behind the stage's rows (and as three bf16 parts in the packed block), the largest norms of the nodes
-//     and of what the bf16 cut leaves over (w - hi, w - hi - lo) in scal.
+//   * Norms: -|w|^2 / 2 + w . (w - hi - lo) behind the stage's rows (and as three bf16 parts in the packed block; the second term is what the
+//     products of a sample that lies at the node drop), the largest norms of the nodes and of what the bf16 cut leaves over (w - hi,
+//     w - hi - lo) in scal.
 // Clears the result words that the later kernels of the call count into; the maxima it adds to (tops) were left zero by the
 // re-decision of the call before.
 constexpr int kCentreNodes = 64;
@@ -270,11 +271,12 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
     const __bf16 lo = (__bf16)left;
     const float rest = left - (float)lo;
     const double nrm = wave_sum((double)v * (double)v);
-    float lo2 = left * left, rest2 = rest * rest;
+    float lo2 = left * left, rest2 = rest * rest, with_rest = v * rest;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         lo2 += __shfl_xor(lo2, o);
         rest2 += __shfl_xor(rest2, o);
+        with_rest += __shfl_xor(with_rest, o);
     }
     char* const row = reinterpret_cast<char*>(rows16) + wave * sp.row_bytes;
     if (real) {
@@ -294,7 +296,7 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
         }
     }
     if (lane == 0) {
-        const float nh = (float)(-0.5 * nrm);
+        const float nh = (float)(-0.5 * nrm + (double)with_rest);
         const float nf = (k < K && nh > kSplitPadNorm) ? nh : kSplitPadNorm;
         reinterpret_cast<float*>(sp.stage16 + (size_t)(k / kNodesPerStage) * sp.stage16_bytes +
                                  (size_t)kNodesPerStage * sp.row_bytes)[k % kNodesPerStage] = nf;
@@ -894,9 +896,9 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
 
     // ---- this wavefront's samples: centred, cut into bf16 parts, kept in registers
     bf16x8 xh[MS][KBA], xl[MS][KBA], xt[MS];
-    // search: squared norm of the centred sample (both lane halves hold the whole row's), err_w and err_0: a score errs by at
-    // most err_w |w| + err_0 + kErrNorm |w|^2 / 2 (see below).  They wait in LDS, behind the stages, for the end of the tile:
-    // the stage loop has no registers to spare for them.
+    // search: norm of the centred sample (both lane halves hold the whole row's), what a score errs by for each unit of |w| and besides
+    // (err_w, err_0), and the norm of what the cut leaves over (see below).  They wait in LDS, behind the stages, for the end of the
+    // tile: the stage loop has no registers to spare for them.
     float* const stash = reinterpret_cast<float*>(lds4 + 2 * STAGE_F4) + threadIdx.x;
     float cut[MS];          // CAND
     unsigned int found[MS]; // CAND: hits of the block in hand
@@ -1023,8 +1025,13 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         }
         if constexpr (!CAND) {
             // The error of a score, in three parts.  (1) What the bf16 cut drops: with x = xh + xl + xr and w likewise,
-            // |xl| |wl| + |xr| |w| + |x| |wr|, where the largest |w - wh| and |wr| over the nodes come from the weight preparation:
-            // norms that were formed (a part has eight significant bits, so the worst case is 3 * 2^-16 |x| |w|, several times more).
+            // xl . wl + xr . w + (x - xr) . wr, of which the preparation gives w . wr back.  Two scores are compared, so what counts is by how
+            // much their errors differ: |xl| |wl| each, |xr| |w_a - w_b|, and |x - w| |wr| and |xr| |wr| each, where neither of the two
+            // nodes is farther from the sample than the winner is, nor from each other than twice that (nor than both norms).  The largest
+            // |w - wh| and |wr| over the nodes come from the weight preparation: norms that were formed (a part has eight significant
+            // bits, so the worst case is 3 * 2^-16 |x| |w|, several times more).  With |w_a| + |w_b| and |x| in the places of the
+            // distances, as before, a map of 1024 nodes along a chain had 38 % of 10^7 x 50 rows listed and has 28 %, one of 64 x 64 48 % of
+            // 10^6 and 40 %.
             // (2) The pipe's accumulation.  How an MFMA orders and rounds the additions of its sixteen exact products to its
             // accumulator C is not documented, so each MFMA is charged what seventeen float32 terms can lose when added in
             // ANY order with one rounding to nearest per addition: 16 * 2^-24 (|C| + sum |products|).  (The largest error seen on
@@ -1045,9 +1052,12 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             const float nl = __builtin_amdgcn_sqrtf(lo2 + kSquaresFloor) * 1.0001f + nr, nh = __builtin_amdgcn_sqrtf(hi2 + kSquaresFloor) * 1.0001f;
             const float nx = nh + nl;
             constexpr float unit = 5.9604645e-08f;
+            const float err_w = nl * (32.64f * KB * unit) + __builtin_amdgcn_sqrtf(xa + kSquaresFloor) * (1.0001f * 16.256f * unit) + nx * (6.0f * unit);
             stash[(3 * mb + 0) * kThreads] = nx;
-            stash[(3 * mb + 1) * kThreads] = nr * 1.0078125f + nl * (32.64f * KB * unit) + __builtin_amdgcn_sqrtf(xa + kSquaresFloor) * (1.0001f * 16.256f * unit) + nx * (6.0f * unit);
-            stash[(3 * mb + 2) * kThreads] = nl * lo_w * 1.0078125f + nx * (rest_w * 1.0078125f + lo_w * (32.64f * KB * unit));
+            stash[(3 * mb + 1) * kThreads] = nl * lo_w * 1.0078125f + nr * rest_w * 1.0078125f + nx * lo_w * (32.64f * KB * unit);
+            // (two figures of sixteen bits, rounded up: LDS is full)
+            stash[(3 * mb + 2) * kThreads] =
+                __uint_as_float(((__float_as_uint(err_w) + 0xffffu) & 0xffff0000u) | ((__float_as_uint(nr * 1.0078125f) + 0xffffu) >> 16));
         }
     }
 
@@ -1423,19 +1433,23 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     const bool r_valid = i < a.m && (MS > 1 || g == 0);
     // the sample's figures from the start of the tile, and the winner's squared norm from the stage blob
     const int own = MS > 1 ? g : 0;
-    const float xl2 = stash[(3 * own + 0) * kThreads], err_w = stash[(3 * own + 1) * kThreads], err_0 = stash[(3 * own + 2) * kThreads];
+    const float nx = stash[(3 * own + 0) * kThreads], err_0 = stash[(3 * own + 1) * kThreads];
+    const unsigned int two = __float_as_uint(stash[(3 * own + 2) * kThreads]);
+    const float err_w = __uint_as_float(two & 0xffff0000u), nr = __uint_as_float(two << 16);
+    const float rest_w = root(__uint_as_float(a.norms[2]) + kSquaresFloor) * 1.0079f;
     const char* blob = reinterpret_cast<const char*>(a.stage16) + (size_t)(r_row / kNodesPerStage) * STAGE_F4 * 16;
     const float wn = -2.0f * reinterpret_cast<const float*>(blob + (size_t)kNodesPerStage * RS)[r_row % kNodesPerStage];
-    // The winner's score errs by its own norm's bound.  A node that is in truth as near as the winner lies within the
-    // winner's distance of the sample, so its norm is at most |x| + |x - w_b| (and at most the largest); no other node
-    // can spoil the decision.  The position bits change a score by at most 2^-19 of itself, and a rival's score is
-    // within the bound of the best one.
-    const float wb = fminf(root(wn) * 1.00001f, wmax);
-    const float err_b = err_w * wb + err_0 + 0.5f * kErrNorm * wb * wb;
+    // The winner's score errs by its own norm's bound, which bounds its distance (far).  A node that is in truth as near as the winner
+    // lies within that distance of the sample, so its norm is at most |x| + far (and at most the largest), and it lies within 2 far of the
+    // winner; no other node can spoil the decision.  The position bits change a score by at most 2^-19 of itself, and a rival's
+    // score is within the bound of the best one.
+    const float wb = fminf(root(wn) * 1.0001f, wmax);
+    const float err_b = (err_w + nr) * wb + err_0 + (nx + wb) * rest_w + 0.5f * kErrNorm * wb * wb;
     const float bits = fabsf(r_best) * (1.01f * 3.8146973e-06f);
-    const float far2 = fmaxf(xl2 * xl2 * 1.00001f - 2.0f * r_best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
-    const float wo = fminf((xl2 + root(far2)) * 1.0001f, wmax);
-    const float bound = err_b + err_w * wo + err_0 + 0.5f * kErrNorm * wo * wo + bits;
+    const float far2 = fmaxf(nx * nx * 1.00001f - 2.0f * r_best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
+    const float far = root(far2) * 1.0001f;
+    const float wo = fminf((nx + far) * 1.0001f, wmax);
+    const float bound = err_w * (wb + wo) + 2.0f * err_0 + nr * fminf(2.0f * far, wb + wo) + 2.0f * far * rest_w + 0.5f * kErrNorm * (wb * wb + wo * wo) + bits;
     const bool close = r_valid && a.K > 1 && !((r_best - r_second) > bound);
     // Candidates: the class winners that reach the cut, four at most; complete when no class's runner-up reaches it.  Otherwise
     // (or with 16-bit ids not enough) the sample goes on the list of the candidate pass.
@@ -1463,7 +1477,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             // magnitude.  Only those that this sample's own bound leaves open are listed.
             constexpr float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(49 * KB + (TAIL ? 17 : 0) + 1) * 5.9604645e-08f + 1.9073486e-06f) +
                                   12.0f * 5.9604645e-08f;
-            const float band = 0.5f * rel * ((xl2 * wb + 0.5f * wb * wb) + (xl2 * wmax + 0.5f * wmax2));
+            const float band = 0.5f * rel * ((nx * wb + 0.5f * wb * wb) + (nx * wmax + 0.5f * wmax2));
             near = (close || (a.K > 1 && !((r_best - r_second) > band))) ? 1 : 0;
         }
         a.bmu[i] = node_of_row(r_row, a.K);
@@ -1887,8 +1901,8 @@ __global__ void __launch_bounds__(256) bmu_cand_exact_kernel(const BmuArgs a)
 // rows are requested, and one lane per candidate adds its squared differences up, features in order as the other re-decisions do;
 // lowest distance, then lowest node index.
 // The chain sample position -> ids and row number -> rows is three dependent trips to memory: positions are read three rounds ahead, ids and
-// row numbers two, rows one, and two workgroups of eight wavefronts fit a unit.  10^7 x 50 on 1024 nodes, 3.8 million entries: 440 us, by the lines
-// of their rows; sums across the LP lanes instead of out of LDS take 410, but they add in another order, and a sample that lies between two nodes
+// row numbers two, rows one, and two workgroups of eight wavefronts fit a unit.  10^7 x 50 on 1024 nodes, 2.8 million entries: 331 us, by the lines
+// of their rows; sums across the LP lanes instead of out of LDS take 312, but they add in another order, and a sample that lies between two nodes
 // must not go to one of them in a look-up and to the other in an epoch.
 // (With the ids read a round ahead, beside the rows before those that need them, and sixteen entries a round, whose registers left one workgroup
 // a unit, 10^7 x 50 on 1024 nodes, 3.8 million entries, took 501 us; 900,000 x 25 on 400 nodes 20 us for 13.)

@@ -1,0 +1,31 @@
+"""The error band of the search for rows of up to 64 features, whose width goes with the sample's distance from its winner and not with its
+distance from the map's middle: choices against float64 where the two are far apart, and for candidates in pairs and crowds."""
+import pytest
+import torch
+
+from test_gpu_held_rows import check, som  # noqa: F401  (the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [4, 5, 15, 16, 17, 20, 21, 32, 33, 37, 48, 50, 52, 53, 64])
+def test_close_nodes_far_from_the_middle(som, D):  # noqa: F811
+    g = torch.Generator(device="cuda").manual_seed(D)
+    r = lambda *s: torch.randn(s, device="cuda", generator=g)
+    for spread, gap, noise in ((30.0, 1e-1, 0.3), (30.0, 1e-2, 0.03), (300.0, 1e-2, 1e-2), (30.0, 1e-3, 1e-3), (30.0, 1e-4, 0.3), (1.0, 1e-5, 1e-5), (3.0, 1e-2, 30.0)):
+        base = spread * r(60, D)
+        crowd = base[:2].repeat_interleave(40, 0)
+        W = torch.cat([base, base + gap * r(60, D), base[:40] + gap * r(40, D), crowd + gap * r(80, D)]).contiguous()
+        X = W[torch.randint(240, (20_000,), device="cuda", generator=g)] + noise * r(20_000, D)
+        check(som, X, W)
+
+
+@pytest.mark.parametrize("D", [8, 50, 64])
+def test_one_node_far_from_the_others(som, D):  # noqa: F811
+    """The largest norms are those of a node that no sample is near to; samples on it, beside it and half way."""
+    g = torch.Generator(device="cuda").manual_seed(D)
+    W = torch.randn((130, D), device="cuda", generator=g)
+    W[77] *= 1e4
+    X = W[torch.randint(130, (20_000,), device="cuda", generator=g)] + 0.1 * torch.randn((20_000, D), device="cuda", generator=g)
+    X[::5] = 0.5 * W[77] + torch.randn((4000, D), device="cuda", generator=g)
+    check(som, X, W.contiguous())
