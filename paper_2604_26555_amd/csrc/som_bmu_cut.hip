@@ -4,7 +4,8 @@
 // Passes.  bmu_cut_samples_kernel cuts every sample once and leaves its parts in memory, 3.5 bytes a value, in the order of the MFMA's lanes:
 // cutting them in the tile again for each 256 nodes takes as long as the products (a row's fp6 conversions and error norms are some 400
 // vector instructions a chunk and wavefront).  It is bound by memory: 331 us at 10^5 x 2000 for 1.5 GB.  bmu_cut_split_kernel forms the
-// scores of 256 samples x 256 nodes a tile; join, candidate pass and direct differences are those of som_bmu_wide.hip.
+// scores of 256 samples x 256 nodes a tile; join and direct differences are those of som_bmu_wide.hip.  For the candidate pass the listed
+// rows are cut once more, into blocks of their own (bmu_cut_listed_kernel).
 //
 // Scales.  As held rows, but for each chunk of 64 features of a row its own; a chunk's products are summed from zero and added to the tile's
 // accumulators with the factor that takes them back, so the roundings of a chunk are relative to its own size.
@@ -168,19 +169,24 @@ __global__ void __launch_bounds__(256) bmu_cut_prep_kernel(const float* __restri
 // of each half unit of row j, centres them, scales them by the power of two that takes the largest of the row's chunk into [2^kTopBit,
 // 2^(kTopBit + 1)), and cuts them: half-precision parts, and fp6 parts of what they leave over (lower lanes) and of them (upper lanes).
 // ---------------------------------------------------------------------------------------------------------
+// LIST: the rows of the re-decision list's entries, 32 of them to a block, once the search is through with the parts.  (The candidate pass
+// gathered them from the blocks of the samples, where an entry's 224 bytes of a chunk lie in fourteen lines: 10^5 x 2000 uniform values on
+// 1024 nodes, 202 us; cut again 21, and the pass over whole blocks 48.)
 constexpr int kCutThreads = 512;
 
-__global__ void __launch_bounds__(kCutThreads) bmu_cut_samples_kernel(const BmuArgs a, const WideArgs p)
+template <bool LIST>
+__device__ __forceinline__ void cut_block(const BmuArgs& a, const WideArgs& p, int64_t block, int64_t total, float (*sums)[64][3])
 {
     constexpr int WAVES = kCutThreads / 64;
-    __shared__ float sums[WAVES][64][3];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 31, g = lane >> 5;
-    const int64_t i = (int64_t)blockIdx.x * 32 + j, ic = i < a.m ? i : a.m - 1;
+    const int64_t i = block * 32 + j;
+    int64_t ic = i < total ? i : total - 1;
+    if constexpr (LIST) ic = (int64_t)a.recheck[ic];
     const float* const row = a.X + (a.idx ? (int64_t)a.idx[ic] : ic) * a.ldx;
-    char* const to = p.cut + (size_t)blockIdx.x * p.nch * kCutBlock;
-    float* const scales = p.scales + (size_t)blockIdx.x * p.nch * 32;
+    char* const to = p.cut + (size_t)block * p.nch * kCutBlock;
+    float* const scales = p.scales + (size_t)block * p.nch * 32;
     const float q_scale = g == 0 ? power_of_two(-3) : power_of_two(kTopBit - 2);
     float l2 = 0.0f, e2 = 0.0f, w2 = 0.0f;                  // lower lanes: of second parts; upper: of first parts
     for (int ch = wave; ch < p.nch; ch += WAVES) {
@@ -234,6 +240,7 @@ __global__ void __launch_bounds__(kCutThreads) bmu_cut_samples_kernel(const BmuA
             const uintx6 q = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(__builtin_bit_cast(halfx32, w), q_scale);
             *reinterpret_cast<uint4*>(at + u * 3072 + 2048 + lane * 16) = make_uint4(q[0], q[1], q[2], q[3]);
             *reinterpret_cast<uint2*>(at + 6144 + u * 512 + lane * 8) = make_uint2(q[4], q[5]);
+            if constexpr (LIST) continue;                       // (a listed sample has its norms)
             const uintx16 d = __builtin_bit_cast(uintx16, __builtin_amdgcn_cvt_scalef32_pk32_f16_fp6(q, q_scale));
             float s2 = 0.0f, r2 = 0.0f;
 #pragma unroll
@@ -249,6 +256,7 @@ __global__ void __launch_bounds__(kCutThreads) bmu_cut_samples_kernel(const BmuA
             w2 = fmaf(after * after * s2 * fx, fx, w2);
         }
     }
+    if constexpr (LIST) return;
     sums[wave][lane][0] = l2;
     sums[wave][lane][1] = e2;
     sums[wave][lane][2] = w2;
@@ -263,6 +271,19 @@ __global__ void __launch_bounds__(kCutThreads) bmu_cut_samples_kernel(const BmuA
         if (g == 0 && i < a.m)
             p.norm[i] = part_norms(a, l2, e2, h2, eh2, ha2, 4.0f, (float)(p.nch + 2), 1.0f, power_of_two(-(int)a.scal[kScalShift]));
     }
+}
+
+__global__ void __launch_bounds__(kCutThreads) bmu_cut_samples_kernel(const BmuArgs a, const WideArgs p)
+{
+    __shared__ float sums[kCutThreads / 64][64][3];
+    cut_block<false>(a, p, blockIdx.x, a.m, sums);
+}
+
+__global__ void __launch_bounds__(kCutThreads) bmu_cut_listed_kernel(const BmuArgs a, const WideArgs p)
+{
+    const unsigned int count = a.scal[a.slot];
+    if (count <= p.cand_min) return;
+    for (int64_t block = blockIdx.x; block * 32 < (int64_t)count; block += gridDim.x) cut_block<true>(a, p, block, (int64_t)count, nullptr);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -313,13 +334,11 @@ __device__ __forceinline__ void cut_tile(const BmuArgs& a, const WideArgs& p, in
         entry = (int64_t)a.recheck[entry];
     }
     // parts of the chunk in hand and of the next one
-    // (CAND: gathered; otherwise a block of 32 rows, the last one for wavefronts behind it)
-    const int64_t blocks = (p.rows + 31) / 32, block = wave0 / 32 < blocks ? wave0 / 32 : blocks - 1;
-    const char* const parts = CAND ? p.cut : p.cut + (size_t)block * nch * kCutBlock;
-    const float* const scales = CAND ? p.scales : p.scales + (size_t)block * nch * 32;
-    const unsigned from16 = CAND ? (unsigned)(entry >> 5) * (unsigned)nch * kCutBlock + (unsigned)(g * 32 + (int)(entry & 31)) * 16 : lane16;
-    const unsigned from8 = CAND ? (unsigned)(entry >> 5) * (unsigned)nch * kCutBlock + (unsigned)(g * 32 + (int)(entry & 31)) * 8 : (unsigned)lane * 8;
-    const unsigned from4 = CAND ? ((unsigned)(entry >> 5) * (unsigned)nch * 32 + (unsigned)(entry & 31)) * 4 : (unsigned)j * 4;
+    // (a block of 32 rows, the last one for wavefronts behind it)
+    const int64_t blocks = (total + 31) / 32, block = wave0 / 32 < blocks ? wave0 / 32 : blocks - 1;
+    const char* const parts = p.cut + (size_t)block * nch * kCutBlock;
+    const float* const scales = p.scales + (size_t)block * nch * 32;
+    const unsigned from8 = (unsigned)lane * 8, from4 = (unsigned)j * 4;
     struct Parts {
         uintx4 f[2][2];
         uintx6 q[2];
@@ -330,9 +349,9 @@ __device__ __forceinline__ void cut_tile(const BmuArgs& a, const WideArgs& p, in
         const char* at = parts + (size_t)ch * kCutBlock;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            x.f[u][0] = *reinterpret_cast<const uintx4*>(at + u * 3072 + from16);
-            x.f[u][1] = *reinterpret_cast<const uintx4*>(at + u * 3072 + 1024 + from16);
-            const uint4 q = *reinterpret_cast<const uint4*>(at + u * 3072 + 2048 + from16);
+            x.f[u][0] = *reinterpret_cast<const uintx4*>(at + u * 3072 + lane16);
+            x.f[u][1] = *reinterpret_cast<const uintx4*>(at + u * 3072 + 1024 + lane16);
+            const uint4 q = *reinterpret_cast<const uint4*>(at + u * 3072 + 2048 + lane16);
             const uint2 r = *reinterpret_cast<const uint2*>(at + 6144 + u * 512 + from8);
             x.q[u][0] = q.x;
             x.q[u][1] = q.y;
@@ -657,6 +676,9 @@ void bmu_cut_plan(WideArgs& p, const BmuPrep& prep, int64_t m, int32_t K, int32_
 int bmu_cut_launch(som_ctx* ctx, const BmuArgs& a, const WideArgs& p, bool cand)
 {
     if (cand) {
+        const int64_t blocks = (a.m + 31) / 32;
+        hipLaunchKernelGGL(bmu_cut_listed_kernel, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(kCutThreads), 0, ctx->stream, a, p);
+        if (int rc = check_hip(ctx, hipGetLastError(), "bmu (rows cut beforehand) list cut launch")) return rc;
         hipLaunchKernelGGL(bmu_cut_split_cand_kernel, dim3(256), dim3(kTileThreads), kCutLds, ctx->stream, a, p);
         return check_hip(ctx, hipGetLastError(), "bmu (rows cut beforehand) candidate launch");
     }

@@ -43,6 +43,24 @@ def test_lists_of_rows_and_rows_that_start_anywhere(som):  # noqa: F811
     check(som, big[:, 1:302], W, idx)
 
 
+@pytest.mark.parametrize("m", [32768, 40001])
+def test_long_lists(som, m):  # noqa: F811
+    """Six nodes close together everywhere, so that almost every row is listed: as many blocks of the list as workgroups cut them, and more; the
+    first and the last rows."""
+    g = torch.Generator(device="cuda").manual_seed(m)
+    base = torch.randn((60, 260), device="cuda", generator=g)
+    W = (base[:, None, :] + 1e-4 * torch.randn((60, 6, 260), device="cuda", generator=g)).reshape(360, 260)
+    X = torch.randn((m + 7, 260), device="cuda", generator=g)
+    idx = torch.randperm(m + 7, device="cuda", generator=g)[:m].int()
+    b, _, _ = som.som_bmu(X, W, idx=idx)
+    rows = torch.cat([torch.arange(0, 600), torch.arange(m - 1500, m), torch.randint(m, (1000,))]).cuda()
+    x, w = X[idx[rows].long()].double(), W.double()
+    for lo in range(0, len(rows), 100):
+        d2 = ((x[lo:lo + 100, None, :] - w[None, :, :]) ** 2).sum(2)
+        got = d2.gather(1, b[rows[lo:lo + 100]].long()[:, None])[:, 0]
+        assert (got / d2.min(1).values - 1.0).max().item() <= 264 * 2.0 ** -23
+
+
 @pytest.mark.parametrize("D", [300, 512])
 def test_error_band(som, D):  # noqa: F811
     """Pairs and triples of nodes so close that the samples' best two scores lie on both sides of the error band: lists of any length, short ones
