@@ -129,7 +129,8 @@ int som_create(som_ctx** out, int device, void* hip_stream)
         ok = ok && hipEventCreateWithFlags(&c->ev_copied[i], hipEventDisableTiming) == hipSuccess;
         ok = ok && hipEventCreateWithFlags(&c->ev_consumed[i], hipEventDisableTiming) == hipSuccess;
     }
-    for (int i = 0; i < 4 && ok; ++i) ok = ok && hipEventCreate(&c->ev_t[i]) == hipSuccess;
+    int khz = 0;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0) c->clock_khz = khz;
     ok = ok && update_static_init(c) == SOM_OK;
     if (!ok) {
         (void)hipGetLastError();
@@ -155,8 +156,6 @@ void som_destroy(som_ctx* c)
         if (c->pinned[i]) (void)hipHostFree(c->pinned[i]);
         if (c->dchunk[i]) (void)hipFree(c->dchunk[i]);
     }
-    for (int i = 0; i < 4; ++i)
-        if (c->ev_t[i]) (void)hipEventDestroy(c->ev_t[i]);
     if (c->prep_blob) (void)hipFree(c->prep_blob);
     if (c->recheck) (void)hipFree(c->recheck);
     if (c->bmu_ws) (void)hipFree(c->bmu_ws);
@@ -327,18 +326,36 @@ int som_neighborhood_update_static(som_ctx* ctx, const double* S, const uint64_t
 struct HostSmall {
     double qe[2];
     int32_t small[4];
-    unsigned int scal[4];
+    unsigned int n_recheck;
+    unsigned long long at[3];      // start of the epoch, of the update, end of it: ticks of wall_clock64
 };
 
-static __global__ void stats_kernel(const double* __restrict__ qe, const int32_t* __restrict__ small, const unsigned int* __restrict__ scal,
-                             HostSmall* __restrict__ out)
+// the epoch's partial sums (left zero for the next call, as qe_finish_kernel leaves them), counters and times to the host
+static __global__ void __launch_bounds__(kQeSlots) stats_kernel(double* __restrict__ part, const int32_t* __restrict__ small,
+                                                                const unsigned int* __restrict__ scal, HostSmall* __restrict__ out)
 {
+    __shared__ double w[kQeSlots / 64][3];
     const int t = threadIdx.x;
-    if (t < 2) out->qe[t] = qe[t];
-    if (t < 4) {
-        out->small[t] = small[t];
-        out->scal[t] = scal[t];
+    if (t == 0) out->at[2] = wall_clock64();
+    double s[3] = {part[2 * t], part[2 * t + 1], part[2 * kQeSlots + t]};
+    part[2 * t] = 0.0;
+    part[2 * t + 1] = 0.0;
+    part[2 * kQeSlots + t] = 0.0;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s[q] += __shfl_xor(s[q], o);
+        if ((t & 63) == 0) w[t >> 6][q] = s[q];
     }
+    __syncthreads();
+    if (t < 2) out->at[t] = reinterpret_cast<const unsigned long long*>(small + kStampWord)[t];
+    if (t < 3) {
+        double sum = 0.0;
+        for (int q = 0; q < kQeSlots / 64; ++q) sum += w[q][t];
+        if (t < 2) out->qe[t] = sum;
+        else out->n_recheck = scal[3] + (unsigned int)sum;
+    }
+    if (t < 4) out->small[t] = small[t];
 }
 
 static int begin_epoch(som_ctx* ctx, int32_t K, int32_t D, int64_t chunk_rows)
@@ -349,28 +366,37 @@ static int begin_epoch(som_ctx* ctx, int32_t K, int32_t D, int64_t chunk_rows)
     return SOM_OK;   // qe and the small counters are cleared by the weight-preparation kernel
 }
 
-// scal: the preparation's result words
-static int finish_stats(som_ctx* ctx, const unsigned int* scal, int64_t m, som_stats* stats, bool timed, float ms_h2d)
+// after a call that failed between its search and stats_kernel
+static void drop_partial_sums(som_ctx* ctx)
 {
-    HostSmall* h = (HostSmall*)ctx->host_small;
+    char said[sizeof(ctx->err)];
+    memcpy(said, ctx->err, sizeof(said));
+    (void)launch_fill_zero(ctx, ctx->qe_part, kQeSlots * 3 * sizeof(double));
+    memcpy(ctx->err, said, sizeof(said));
+}
+
+// scal: the preparation's result words
+static int launch_stats(som_ctx* ctx, const unsigned int* scal)
+{
     // (one small kernel writes all of them to the pinned mirror: three copies of a few words each took 4 us of the stream
     // apiece and as much of the host's time)
-    hipLaunchKernelGGL(stats_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->qe, ctx->small, scal, h);
-    if (int rc = check_hip(ctx, hipGetLastError(), "reading statistics")) return rc;
-    if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "waiting for the epoch")) return rc;
+    hipLaunchKernelGGL(stats_kernel, dim3(1), dim3(kQeSlots), 0, ctx->stream, ctx->qe_part, ctx->small, scal, (HostSmall*)ctx->host_small);
+    return check_hip(ctx, hipGetLastError(), "reading statistics");
+}
+
+// once the stream has been waited for
+static void read_stats(som_ctx* ctx, int64_t m, som_stats* stats, float ms_h2d)
+{
+    const HostSmall* h = (const HostSmall*)ctx->host_small;
     stats->sum_dist = h->qe[0];
     stats->sum_dist2 = h->qe[1];
     stats->m = m;
-    stats->n_recheck = h->scal[3];
+    stats->n_recheck = h->n_recheck;
     stats->n_guarded = h->small[0];
     stats->n_empty = h->small[1];
-    stats->ms_bmu_acc = stats->ms_update = 0.f;
+    stats->ms_bmu_acc = (float)((double)(h->at[1] - h->at[0]) / ctx->clock_khz);
+    stats->ms_update = (float)((double)(h->at[2] - h->at[1]) / ctx->clock_khz);
     stats->ms_h2d = ms_h2d;
-    if (timed) {
-        (void)hipEventElapsedTime(&stats->ms_bmu_acc, ctx->ev_t[0], ctx->ev_t[1]);
-        (void)hipEventElapsedTime(&stats->ms_update, ctx->ev_t[1], ctx->ev_t[2]);
-    }
-    return SOM_OK;
 }
 
 int som_epoch(som_ctx* ctx, const float* X, int64_t N, int32_t D, int64_t ldx, const uint32_t* idx, int64_t m, float* W,
@@ -394,7 +420,6 @@ int som_epoch(som_ctx* ctx, const float* X, int64_t N, int32_t D, int64_t ldx, c
         if (const int rc = small_epoch_run(ctx, X, D, ldx, idx, m, W, K, G, sigma, eps_h); rc != 1) return rc;
     if (int rc = begin_epoch(ctx, K, D, m)) return rc;
     BmuPrep prep;
-    if (stats) (void)hipEventRecord(ctx->ev_t[0], ctx->stream);
     if (int rc = bmu_prepare(ctx, W, K, D, &prep, ctx->qe, ctx->small)) return rc;
     BmuArgs a{};
     a.X = X;
@@ -405,14 +430,19 @@ int som_epoch(som_ctx* ctx, const float* X, int64_t N, int32_t D, int64_t ldx, c
     a.K = K;
     a.W = W;
     a.qe = stats ? ctx->qe : nullptr;       // no statistics asked for: the search forms no distances
+    a.qe_later = true;
     a.bmu = ctx->bmu_ws;
-    if (int rc = bmu_run(ctx, prep, a)) return rc;
-    if (int rc = accumulate_run(ctx, X, D, ldx, idx, m, ctx->bmu_ws, K, ctx->S, ctx->n, true)) return rc;
-    if (stats) (void)hipEventRecord(ctx->ev_t[1], ctx->stream);
-    if (int rc = update_run(ctx, ctx->S, ctx->n, G, K, D, sigma, eps_h, W, ctx->small)) return rc;
+    int rc = bmu_run(ctx, prep, a);
+    if (!rc) rc = accumulate_run(ctx, X, D, ldx, idx, m, ctx->bmu_ws, K, ctx->S, ctx->n, true);
+    if (!rc) rc = update_run(ctx, ctx->S, ctx->n, G, K, D, sigma, eps_h, W, ctx->small);
+    if (!rc && stats) rc = launch_stats(ctx, prep.scal);
+    if (rc) {
+        if (stats) drop_partial_sums(ctx);
+        return rc;
+    }
     if (stats) {
-        (void)hipEventRecord(ctx->ev_t[2], ctx->stream);
-        if (int rc = finish_stats(ctx, prep.scal, m, stats, true, 0.f)) return rc;
+        if ((rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "waiting for the epoch"))) return rc;
+        read_stats(ctx, m, stats, 0.f);
     }
     return SOM_OK;
 }
@@ -521,13 +551,13 @@ static int stream_epoch(som_ctx* ctx, const ChunkSource& src, int64_t N, int32_t
         ctx->h2d_events.push_back(e);
     }
     BmuPrep prep;
-    (void)hipEventRecord(ctx->ev_t[0], ctx->stream);
     if (int rc = bmu_prepare(ctx, W, K, D, &prep, ctx->qe, ctx->small)) return rc;
 
     // After a failure inside the loop both streams are drained before the call returns: nothing of this epoch is
     // still in flight into the chunk buffers when the caller uses the context again.
     auto bail = [&](int rc) {
         (void)hipStreamSynchronize(ctx->copy_stream);
+        if (stats) drop_partial_sums(ctx);
         (void)hipStreamSynchronize(ctx->stream);
         (void)hipGetLastError();
         return rc;
@@ -568,14 +598,15 @@ static int stream_epoch(som_ctx* ctx, const ChunkSource& src, int64_t N, int32_t
         a.K = K;
         a.W = W;
         a.qe = stats ? ctx->qe : nullptr;
+        a.qe_later = true;
         a.bmu = ctx->bmu_ws;
         if (int rc = bmu_run(ctx, prep, a)) return bail(rc);
         if (int rc = accumulate_run(ctx, ctx->dchunk[b], D, D, nullptr, rows, ctx->bmu_ws, K, ctx->S, ctx->n, c == 0)) return bail(rc);
         (void)hipEventRecord(ctx->ev_consumed[b], ctx->stream);
     }
-    (void)hipEventRecord(ctx->ev_t[1], ctx->stream);
     if (int rc = update_run(ctx, ctx->S, ctx->n, G, K, D, sigma, eps_h, W, ctx->small)) return bail(rc);
-    (void)hipEventRecord(ctx->ev_t[2], ctx->stream);
+    if (stats)
+        if (int rc = launch_stats(ctx, prep.scal)) return bail(rc);
     int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "waiting for the epoch");
     if (!rc) rc = check_hip(ctx, hipStreamSynchronize(ctx->copy_stream), "waiting for the copy stream");
     if (rc) return bail(rc);
@@ -584,7 +615,7 @@ static int stream_epoch(som_ctx* ctx, const ChunkSource& src, int64_t N, int32_t
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, ctx->h2d_events[2 * c], ctx->h2d_events[2 * c + 1]) == hipSuccess) ms_h2d += ms;
     }
-    if (stats) return finish_stats(ctx, prep.scal, N, stats, true, ms_h2d);
+    if (stats) read_stats(ctx, N, stats, ms_h2d);
     return SOM_OK;
 }
 

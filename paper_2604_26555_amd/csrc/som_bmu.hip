@@ -64,8 +64,9 @@ constexpr int stage_floats_for(int stride)
 // centre[f] = mean over nodes of W[k][f], f < D; zero up to the next multiple of 64.  Any vector would do (distances do not change when the same vector is
 // taken off samples and weights); the mean keeps |w_k - centre| as small as the spread of the map.
 __global__ void __launch_bounds__(1024) bmu_centre_kernel(const float* __restrict__ W, int K, int D, float* __restrict__ centre,
-                                                          unsigned int* __restrict__ scal, float* __restrict__ spread)
+                                                          unsigned int* __restrict__ scal, float* __restrict__ spread, int32_t* __restrict__ small)
 {
+    stamp(small, kStampStart);
     __shared__ double part[16][64];
     __shared__ float ends[16][64][2];
     const int fl = threadIdx.x & 63, grp = threadIdx.x >> 6;
@@ -239,6 +240,7 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
     __shared__ float most[kPrepNodes][3];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int k0 = blockIdx.x * kPrepNodes, k = k0 + wave;           // rows of the stages (and of the transposed copy)
+    stamp(small, kStampStart);
     if (blockIdx.x == 0) {
         if (tid < 16) scal[tid] = 0u;
         if (tid < 2 && qe) qe[tid] = 0.0;
@@ -2476,7 +2478,7 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
         return check_hip(ctx, hipGetLastError(), "bmu (split) preparation launch");
     }
     hipLaunchKernelGGL(bmu_centre_kernel, dim3((unsigned)(centre_bytes / 256)), dim3(1024), 0, ctx->stream, W, K, D,
-                       out->centre, out->scal, wide_split ? bmu_wide_spread(*out, K, D) : nullptr);
+                       out->centre, out->scal, wide_split ? bmu_wide_spread(*out, K, D) : nullptr, small);
     if (wide_split) {
         if (int rc = check_hip(ctx, hipGetLastError(), "bmu_centre launch")) return rc;
         return bmu_wide_prepare(ctx, W, K, D, *out, qe, small);
@@ -2874,7 +2876,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
         }
         if (a.d2 || a.qe)
             if (int rc = bmu_wide_distances(ctx, a)) return rc;
-        if (a.qe) {
+        if (a.qe && !a.qe_later) {
             hipLaunchKernelGGL(qe_finish_kernel, dim3(1), dim3(kQeSlots), 0, ctx->stream, a.qe_part, a.qe, a.scal);
             return check_hip(ctx, hipGetLastError(), "quantisation-error reduction launch");
         }
@@ -2920,7 +2922,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     }
     if (prep.stage16 && (a.d2 || a.qe))
         if ((rc = launch_bmu_distances(ctx, a))) return rc;
-    if (a.qe) {
+    if (a.qe && !a.qe_later) {
         hipLaunchKernelGGL(qe_finish_kernel, dim3(1), dim3(kQeSlots), 0, ctx->stream, a.qe_part, a.qe, a.scal);
         rc = check_hip(ctx, hipGetLastError(), "quantisation-error reduction launch");
     }

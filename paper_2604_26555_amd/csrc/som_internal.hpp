@@ -72,10 +72,20 @@ struct BmuArgs {
     float* d2;               // may be null
     double* qe;              // [2], accumulated (caller zeroes); may be null
     double* qe_part;         // [kQeSlots][2] partial sums, then [kQeSlots] near ties (zero on entry, zeroed again by qe_finish_kernel)
+    bool qe_later;           // the caller adds them up and zeroes them: qe is not written
     int32_t counts_near;     // the search counts the near ties itself (n_recheck); otherwise the list's length is counted
 };
 
 constexpr int kQeSlots = 256;
+// Times of an epoch's stages for its statistics, noted by the first workgroup of the kernel that a stage begins with (two 64-bit
+// ticks of wall_clock64 in som_ctx::small).  An event between two kernels holds the stream up by 4 us: an epoch of
+// 250,000 x 37 on 437 nodes took 149 us with three of them and takes 136.
+constexpr int kStampWord = 8, kStampStart = 0, kStampUpdate = 1;
+__device__ __forceinline__ void stamp(int32_t* small, int which)
+{
+    if (small && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+        reinterpret_cast<unsigned long long*>(small + kStampWord)[which] = wall_clock64();
+}
 constexpr int kMaxDevices = 64;                 // devices the per-device tables hold
 constexpr int kUpdateStaticCells = 65536;       // som_neighborhood_update_static: K * (D + 1) at most
 constexpr int kUpdateStaticNodes = 32768;       // and K at most
@@ -123,7 +133,8 @@ struct som_ctx {
     unsigned long long* n = nullptr;
     size_t n_elems = 0;
     double* qe = nullptr;          // double[2]
-    int32_t* small = nullptr;      // int32[4]: n_guarded, n_empty, spare
+    int32_t* small = nullptr;      // int32[4]: n_guarded, n_empty, spare; from kStampWord on the times of an epoch
+    double clock_khz = 1e5;        // rate of the device's wall clock
     void* host_small = nullptr;    // pinned mirror for reading results back
     // streaming
     float* pinned[2] = {nullptr, nullptr};
@@ -131,7 +142,6 @@ struct som_ctx {
     size_t chunk_elems = 0;
     hipEvent_t ev_copied[2] = {nullptr, nullptr};
     hipEvent_t ev_consumed[2] = {nullptr, nullptr};
-    hipEvent_t ev_t[4] = {nullptr, nullptr, nullptr, nullptr};
     std::vector<hipEvent_t> h2d_events;   // (start, stop) per chunk of a streamed epoch; grown on demand, reused
     // measurement support: event pairs around every launch of the main BMU kernel while profiling is on
     bool profiling = false;

@@ -54,8 +54,9 @@ static UpdateShape update_shape(int K, int D)
 // eight loads under way.  A chain of loads is all there is: with 64 columns and runs of K / 16 rows, whose branches on n[k] kept
 // the loads apart, 12.8 us at K = 400, 4.6 now.
 __global__ void __launch_bounds__(1024) shift_kernel(const float* __restrict__ G, const unsigned long long* __restrict__ n,
-                                                     int K, double* __restrict__ shift)
+                                                     int K, double* __restrict__ shift, int32_t* __restrict__ stamps)
 {
+    stamp(stamps, kStampUpdate);
     __shared__ double low[16][16];
     const int l = threadIdx.x & 15, seg = threadIdx.x >> 4, wave = threadIdx.x >> 6;
     const int j = blockIdx.x * 16 + l, jc = j < K ? j : K - 1;
@@ -98,8 +99,9 @@ __device__ __forceinline__ double influence_of(double gd, double inv2s2, double 
 
 __global__ void __launch_bounds__(256) influence_kernel(const float* __restrict__ G, int K, double inv2s2,
                                                         const double* __restrict__ shift,
-                                                        const unsigned long long* __restrict__ n, double* __restrict__ H)
+                                                        const unsigned long long* __restrict__ n, double* __restrict__ H, int32_t* __restrict__ stamps)
 {
+    stamp(stamps, kStampUpdate);
     const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= (size_t)K * K) return;
     const int k = (int)(e / K), j = (int)(e % K);
@@ -115,8 +117,9 @@ __global__ void __launch_bounds__(256, 2) contract_kernel(const float* __restric
                                                        double inv2s2, const double* __restrict__ shift,
                                                        const double* __restrict__ S,
                                                        const unsigned long long* __restrict__ n, int K, int D,
-                                                       double* __restrict__ part)
+                                                       double* __restrict__ part, int32_t* __restrict__ stamps)
 {
+    stamp(stamps, kStampUpdate);
     __shared__ double sums[4][4][4][64];               // [wavefront][column block][register][lane]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j0 = blockIdx.x * 16 * JT, c0 = blockIdx.y * 64;
@@ -260,21 +263,23 @@ static int update_launch(som_ctx* ctx, double* H, double* part, double* shift_ws
     const int jt = u.jt, splits = u.splits;
     const dim3 grid(u.blocks_j, u.blocks_c, splits);
     double* shift = nullptr;
+    int32_t* stamps = small;                                  // the first launch notes the time
     if (ctx->safeguard == SOM_SAFEGUARD_SHIFT) {
         shift = shift_ws;
-        hipLaunchKernelGGL(shift_kernel, dim3((K + 15) / 16), dim3(1024), 0, ctx->stream, G, n, K, shift);
+        hipLaunchKernelGGL(shift_kernel, dim3((K + 15) / 16), dim3(1024), 0, ctx->stream, G, n, K, shift, stamps);
+        stamps = nullptr;
         if (int rc = check_hip(ctx, hipGetLastError(), "exponent shift launch")) return rc;
     }
     if (grid.y == 1) {
         auto kern = jt == 2 ? contract_kernel<true, 2> : contract_kernel<true, 1>;
         hipLaunchKernelGGL(kern, grid, dim3(256), 0, ctx->stream, G, (const double*)nullptr, inv2s2, (const double*)shift, S, n, K, D,
-                           part);
+                           part, stamps);
     } else {
         hipLaunchKernelGGL(influence_kernel, dim3((unsigned)((h_elems + 255) / 256)), dim3(256), 0, ctx->stream, G, K, inv2s2,
-                           (const double*)shift, n, H);
+                           (const double*)shift, n, H, stamps);
         if (int rc = check_hip(ctx, hipGetLastError(), "influence kernel launch")) return rc;
         auto kern = jt == 4 ? contract_kernel<false, 4> : jt == 2 ? contract_kernel<false, 2> : contract_kernel<false, 1>;
-        hipLaunchKernelGGL(kern, grid, dim3(256), 0, ctx->stream, G, (const double*)H, inv2s2, (const double*)nullptr, S, n, K, D, part);
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, ctx->stream, G, (const double*)H, inv2s2, (const double*)nullptr, S, n, K, D, part, (int32_t*)nullptr);
     }
     if (int rc = check_hip(ctx, hipGetLastError(), "contraction kernel launch")) return rc;
     const bool plain = ctx->eta == 1.0 && ctx->mu == 0.0;
