@@ -46,6 +46,10 @@ constexpr uint32_t kCandMinFloat = 8192;        // the same of the float32 searc
 constexpr uint32_t kCandHalfTiles = 65536;      // up to this length its tiles are halved (one per compute unit and more)
 constexpr size_t kCandCapMax = (size_t)1 << 24; // longest one (bounds the candidate buffer at 512 MB + 64 MB)
 constexpr int kCandGrid = 2048;
+// Maps of fewer nodes send samples of more than four candidates to the candidate pass, whose time goes with the nodes; others keep up to eight.
+// Candidate pass and pair list, 10^6 x 50 on 64 x 64 nodes close together: 197 + 56 us with four kept, 106 + 78 with eight; search on 1024 nodes 334 us
+// and 326, 100,000 x 30 on 4096 141 and 134; but on 400 nodes (500,000 x 64) 23 + 18 and 23 + 20.
+constexpr int kPairMany = 1024;
 constexpr int kPairNodes = 65535;               // largest map whose node ids fit the pair list's 16-bit places (0xffff: none)
 
 // floats of one 128-node stage (padded rows + half squared norms), rounded up to one float4 per thread
@@ -1453,23 +1457,23 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     const float wo = fminf((nx + far) * 1.0001f, wmax);
     const float bound = err_w * (wb + wo) + 2.0f * err_0 + nr * fminf(2.0f * far, wb + wo) + 2.0f * far * rest_w + 0.5f * kErrNorm * (wb * wb + wo * wo) + bits;
     const bool close = r_valid && a.K > 1 && !((r_best - r_second) > bound);
-    // Candidates: the class winners that reach the cut, four at most; complete when no class's runner-up reaches it.  Otherwise
-    // (or with 16-bit ids not enough) the sample goes on the list of the candidate pass.
+    // Candidates: the class winners that reach the cut, four at most on small maps; complete when no class's runner-up reaches it.
+    // Otherwise (or with 16-bit ids not enough) the sample goes on the list of the candidate pass.
     const float cut_at = r_best - bound;
     bool open = !(most < cut_at) || a.K > kPairNodes;
     if (__ballot(close) != 0ull) {
-        unsigned int p0 = 0xffffffffu, p1 = 0xffffffffu;         // four places, the used ones in front
-        int hits = 0;
+        unsigned int p0 = 0xffffffffu, p1 = 0xffffffffu, p2 = 0xffffffffu, p3 = 0xffffffffu;      // eight places, the used ones in front
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const bool hit = won[q] >= cut_at;
             const unsigned id = (unsigned)row_of(won[q], from[q], q);
+            p3 = hit ? (p3 << 16) | (p2 >> 16) : p3;
+            p2 = hit ? (p2 << 16) | (p1 >> 16) : p2;
             p1 = hit ? (p1 << 16) | (p0 >> 16) : p1;
             p0 = hit ? (p0 << 16) | id : p0;
-            hits += hit ? 1 : 0;
         }
-        open = open || hits > 4;
-        if (close && !open) *reinterpret_cast<uint2*>(a.pairs + 2 * i) = make_uint2(p0, p1);
+        open = open || (p2 != 0xffffffffu && a.K < kPairMany);
+        if (close && !open) *reinterpret_cast<uint4*>(a.pairs + 4 * i) = make_uint4(p0, p1, p2, p3);
     }
     int near = 0;
     if (r_valid) {
@@ -1897,7 +1901,7 @@ __global__ void __launch_bounds__(256) bmu_cand_exact_kernel(const BmuArgs a)
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// The pair list: samples whose candidates (at most four) the split search already knows (D <= 64).
+// The pair list: samples whose candidates (at most eight) the split search already knows (D <= 64).
 // A wavefront takes a round of entries at a time, on its own (no barrier): LP lanes (4, 8 or 16, sixteen bytes of a row each) fetch one or
 // two entries' rows, the sample's and two candidates', in coalesced loads; the rows meet in the wavefront's part of LDS, the next entries'
 // rows are requested, and one lane per candidate adds its squared differences up, features in order as the other re-decisions do;
@@ -1908,7 +1912,7 @@ __global__ void __launch_bounds__(256) bmu_cand_exact_kernel(const BmuArgs a)
 // must not go to one of them in a look-up and to the other in an epoch.
 // (With the ids read a round ahead, beside the rows before those that need them, and sixteen entries a round, whose registers left one workgroup
 // a unit, 10^7 x 50 on 1024 nodes, 3.8 million entries, took 501 us; 900,000 x 25 on 400 nodes 20 us for 13.)
-// The few entries with a third or fourth candidate wait in LDS until there is a round of them.
+// The few entries with a third to an eighth candidate wait in LDS until there is a round of them, two candidates at a time.
 // (Served in the round where they came, nearly every round waited for their rows: 4.0 million entries of 10^7 x 50 took 0.62 ms
 // for 0.48.)
 // ---------------------------------------------------------------------------------------------------------
@@ -1931,7 +1935,9 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
     const int stride = ((D + 3) / 4) | 1;             // float4 of a row
     float4* const rows = lds + wave * pair_lds_f4(D, LP);
     uint4* const info = reinterpret_cast<uint4*>(rows + ROUND * 3 * stride);      // [entry] ids, sample position
-    uint4* const later = info + ROUND;                // [2 ROUND] third and fourth id, sample position, nearest so far (distance, row of the stages)
+    // [2 ROUND] next two ids, sample position, nearest so far (distance; row of the stages, and which word of its ids the two are)
+    uint4* const later = info + ROUND;
+    constexpr unsigned int kNoRow = 0xffffffu;
     unsigned int waiting = 0u;
     const int start = 4 * sub < D - 4 ? 4 * sub : D - 4;           // window inside the row
     const bool own = 4 * sub < D;
@@ -2008,11 +2014,22 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
         for (int u = 0; u < EACH; ++u) lay(u);
         __builtin_amdgcn_wave_barrier();
         const uint4 l = later[base + ((unsigned)e < n ? (unsigned)e : 0u)];
+        const unsigned int word = l.w >> 24;           // of its ids
         bd = __uint_as_float(l.z);
-        bk = (int)l.w;
+        bk = (int)(l.w & kNoRow);
         sum(l.x);
-        if (lane < 2 * (int)n && c == 0 && bk < a.K) a.bmu[l.y] = node_of_row(bk, a.K);
+        const bool mine = lane < 2 * (int)n && c == 0;
+        unsigned int rest_of = 0xffffffffu;
+        if (mine && word < 3u && l.x >> 16 != 0xffffu) rest_of = a.pairs[4 * (int64_t)l.y + word + 1u];
+        const bool more = rest_of != 0xffffffffu;
+        if (mine && !more && bk < a.K) a.bmu[l.y] = node_of_row(bk, a.K);
         waiting = base;
+        const unsigned long long wait = __ballot(more);
+        if (wait != 0ull) {
+            const unsigned int to = base + __builtin_amdgcn_mbcnt_hi((unsigned)(wait >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)wait, 0));
+            if (more) later[to] = make_uint4(rest_of, l.y, __float_as_uint(bd), ((unsigned)bk & kNoRow) | (word + 1u) << 24);
+            waiting += (unsigned)__popcll(wait);
+        }
         __builtin_amdgcn_wave_barrier();
     };
     auto position = [&](unsigned int p, int u) {
@@ -2033,9 +2050,9 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
         }
 #pragma unroll
         for (int u = 0; u < EACH; ++u) {
-            ids[u] = *reinterpret_cast<const uint2*>(a.pairs + 2 * (int64_t)at[u]);
+            ids[u] = *reinterpret_cast<const uint2*>(a.pairs + 4 * (int64_t)at[u]);
             row[u] = a.idx ? a.idx[at[u]] : at[u];
-            ids1[u] = *reinterpret_cast<const uint2*>(a.pairs + 2 * (int64_t)at1[u]);
+            ids1[u] = *reinterpret_cast<const uint2*>(a.pairs + 4 * (int64_t)at1[u]);
             row1[u] = a.idx ? a.idx[at1[u]] : at1[u];
         }
 #pragma unroll
@@ -2047,7 +2064,7 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
         const unsigned int p3 = after(after(after(p0)));
 #pragma unroll
         for (int u = 0; u < EACH; ++u) {
-            ids2[u] = *reinterpret_cast<const uint2*>(a.pairs + 2 * (int64_t)at2[u]);
+            ids2[u] = *reinterpret_cast<const uint2*>(a.pairs + 4 * (int64_t)at2[u]);
             row2[u] = a.idx ? a.idx[at2[u]] : at2[u];
             at3[u] = position(p3, u);
         }
@@ -2072,11 +2089,11 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
         const unsigned long long wait = __ballot(more);
         if (wait != 0ull) {
             const unsigned int to = waiting + __builtin_amdgcn_mbcnt_hi((unsigned)(wait >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)wait, 0));
-            if (more) later[to] = make_uint4(my.y, my.z, __float_as_uint(bd), (unsigned)bk);
+            if (more) later[to] = make_uint4(my.y, my.z, __float_as_uint(bd), ((unsigned)bk & kNoRow) | 1u << 24);
             waiting += (unsigned)__popcll(wait);
             if (waiting >= (unsigned)ROUND) {
                 // (the next round's rows make room, and come again)
-                serve_later();
+                while (waiting >= (unsigned)ROUND) serve_later();
                 if (!last)
 #pragma unroll
                     for (int u = 0; u < EACH; ++u) fetch(u, ids1[u].x, row1[u]);
@@ -2094,7 +2111,7 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
             row1[u] = row2[u];
         }
     }
-    if (waiting != 0u) serve_later();
+    while (waiting != 0u) serve_later();              // (each entry comes three times at most)
 }
 
 template <bool PAIRS>
@@ -2737,7 +2754,7 @@ static int launch_bmu_distances(som_ctx* ctx, const BmuArgs& a)
 
 static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a);
 
-// The rows go through in passes of at most 2^27 (rows of more than 64 features: bmu_wide_pass_rows, and of fewer where memory runs out): the re-decision workspace then stays at 2.7 GB (20 bytes a row; the float32
+// The rows go through in passes of at most 2^27 (rows of more than 64 features: bmu_wide_pass_rows, and of fewer where memory runs out): the re-decision workspace then stays at 3.8 GB (28 bytes a row; the float32
 // searches' candidate sets 0.5 GB more) whatever m is,
 // and a pass's list stays within what the candidate pass can hold (2^24 entries, an eighth of a pass) — one call over
 // 10^9 rows listed more than that and fell back to direct differences over all nodes for every listed sample.
@@ -2786,10 +2803,10 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
             ctx->recheck_cap = 0;
             ctx->recheck_sets = false;
         }
-        // sample positions [cap], cuts [cap], per-sample cuts [cap], pair-list ids [cap][2], candidate sets [cand_cap][2]; the capacity is a
+        // sample positions [cap], cuts [cap], per-sample cuts [cap], pair-list ids [cap][4], candidate sets [cand_cap][2]; the capacity is a
         // multiple of four entries so that the 16-byte candidate sets stay aligned
         const size_t cap = ((size_t)a.m + 3) / 4 * 4, ccap = cand_cap_for(cap);
-        const size_t bytes = cap * 20 + (sets ? ccap * 2 * sizeof(ulonglong2) : 0);
+        const size_t bytes = cap * 28 + (sets ? ccap * 2 * sizeof(ulonglong2) : 0);
         if (hipMalloc((void**)&ctx->recheck, bytes) != hipSuccess) {
             (void)hipGetLastError();
             return fail(ctx, SOM_ENOMEM, "cannot allocate the %lld-entry recheck list", (long long)a.m);
@@ -2815,7 +2832,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     a.pairs = ctx->recheck + 3 * ctx->recheck_cap;
     // (the per-sample cuts are dead once the lists are made: the second list takes their place)
     a.recheck2 = ctx->recheck + 2 * ctx->recheck_cap;
-    a.cand = (ulonglong2*)(ctx->recheck + 5 * ctx->recheck_cap);
+    a.cand = (ulonglong2*)(ctx->recheck + 7 * ctx->recheck_cap);
     a.cand_cap = (uint32_t)cand_cap_for(ctx->recheck_cap);
     // The candidate pass repeats the search for the listed samples at matrix speed (under a nanosecond per sample
     // at K D = 51200, against 3.8 ns for direct differences over all nodes) but has the latency of a whole tile, so

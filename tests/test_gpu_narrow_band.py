@@ -29,3 +29,20 @@ def test_one_node_far_from_the_others(som, D):  # noqa: F811
     X = W[torch.randint(130, (20_000,), device="cuda", generator=g)] + 0.1 * torch.randn((20_000, D), device="cuda", generator=g)
     X[::5] = 0.5 * W[77] + torch.randn((4000, D), device="cuda", generator=g)
     check(som, X, W.contiguous())
+
+
+@pytest.mark.parametrize("K", [1023, 1024, 1100, 2900])
+@pytest.mark.parametrize("D", [5, 16, 17, 32, 50, 64])
+def test_two_to_nine_close_nodes(som, D, K):  # noqa: F811
+    """Groups of two to nine nodes close together, so that samples have any number of candidates among their class winners: on both sides of
+    the size from which eight of them are kept, in a short list and in one of several rounds, rows in order and by a list."""
+    g = torch.Generator(device="cuda").manual_seed(D + K)
+    r = lambda *s: torch.randn(s, device="cuda", generator=g)
+    size = 2 + torch.arange(K, device="cuda") % 8
+    group = torch.repeat_interleave(torch.arange(K, device="cuda"), size)[:K]
+    W = (5.0 * r(K, D))[group] + 1e-5 * r(K, D)
+    W = W[torch.randperm(K, device="cuda", generator=g)].contiguous()
+    for m in (70, 9000):
+        X = W[torch.randint(K, (m,), device="cuda", generator=g)] + 0.1 * r(m, D)
+        check(som, X, W)
+        check(som, X, W, torch.randint(m, (m,), device="cuda", generator=g).int())
