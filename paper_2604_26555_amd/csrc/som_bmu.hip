@@ -2410,7 +2410,7 @@ int launch_fill_zero(som_ctx* ctx, void* p, size_t bytes)
     return check_hip(ctx, hipGetLastError(), "fill_zero launch");
 }
 
-int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out, double* qe, int32_t* small)
+int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, int64_t rows, BmuPrep* out, double* qe, int32_t* small)
 {
     int steps, nch;
     if (D <= 2 * kMaxStepsResident) {
@@ -2432,6 +2432,7 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     const int stride = 2 * steps + 1;
     const int kpad = ((K + kNodesPerStage - 1) / kNodesPerStage) * kNodesPerStage;
     const bool wide_split = D > 2 * kMaxStepsResident && K > kSplitMinNodes && ctx->search != SOM_SEARCH_FLOAT32;
+    out->form = wide_split ? bmu_wide_form(ctx, K, D, rows) : 0;
     const bool no_stage = wide_split || (D >= 4 && K > kSplitMinNodes && ctx->search != SOM_SEARCH_FLOAT32);
     const size_t stage_bytes = no_stage ? 0 : (size_t)(kpad / kNodesPerStage) * nch * stage_floats_for(stride) * sizeof(float);
     const size_t wt_bytes = (size_t)D * kpad * sizeof(float) + 255 & ~(size_t)255;
@@ -2446,7 +2447,7 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out
     const int kb = !split || nch > 1 ? 0 : (tail_r ? D / 16 : (D + 15) / 16);
     // (D > 64: rows in the order of som_bmu_wide.hip)
     const size_t stage16_one = (split && nch == 1) ? (size_t)split_stage_f4(kb, tail_r > 0) * 16 : 0;
-    const size_t stage16_bytes = !split ? 0 : nch == 1 ? (size_t)(kpad / kNodesPerStage) * stage16_one : bmu_wide_blob_bytes(K, D, kpad);
+    const size_t stage16_bytes = !split ? 0 : nch == 1 ? (size_t)(kpad / kNodesPerStage) * stage16_one : bmu_wide_blob_bytes(out->form, K, D, kpad);
     const size_t wrow_bytes = (split && nch == 1) ? (size_t)K * D * sizeof(float) : 0;
     const size_t need = stage_bytes + wt_bytes + centre_bytes + stage16_bytes + wrow_bytes + 256;
     if (need > ctx->prep_bytes) {
@@ -2763,7 +2764,7 @@ int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     int64_t kRowsPerPass = (int64_t)1 << 27;
     const int64_t m = a.m;
     const bool wide_split = prep.stage16 && prep.nch > 1;
-    if (wide_split) kRowsPerPass = bmu_wide_pass_rows(a.K, a.D);
+    if (wide_split) kRowsPerPass = bmu_wide_pass_rows(prep, a.D);
     for (int64_t off = 0; off < m;) {
         BmuArgs b = a;
         b.m = m - off < kRowsPerPass ? m - off : kRowsPerPass;

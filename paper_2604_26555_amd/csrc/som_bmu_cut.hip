@@ -1,4 +1,4 @@
-// Best-matching-unit search for rows of more than 256 features (wide_form): the arithmetic of som_bmu_held.hip, half-precision first
+// Best-matching-unit search for rows of more than 256 features (bmu_wide_form): the arithmetic of som_bmu_held.hip, half-precision first
 // parts and fp6 cross products, three MFMAs for 32 features where two bf16 parts take six, for rows that no wavefront can hold.
 //
 // Passes.  bmu_cut_samples_kernel cuts every sample once and leaves its parts in memory, 3.5 bytes a value, in the order of the MFMA's lanes:

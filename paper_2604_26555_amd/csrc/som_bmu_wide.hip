@@ -1,5 +1,5 @@
 // Best-matching-unit search for rows of more than 256 features on small maps, and what it shares with the other two searches of rows wider
-// than 64 (wide_form): the join, the direct differences and the host side.  The scores are those of bmu_split_kernel
+// than 64 (bmu_wide_form): the join, the direct differences and the host side.  The scores are those of bmu_split_kernel
 // (som_bmu.hip: samples and weights cut into two bf16 parts, three bf16 MFMA products per float32 product) as a tiled
 // matrix product with the running arg-max behind it; N x K is never stored.
 //
@@ -802,9 +802,22 @@ int wide_raise_lds(som_ctx* ctx, bool* done, const void* const (&kernels)[2], si
     return SOM_OK;
 }
 
-size_t bmu_wide_blob_bytes(int32_t K, int32_t D, int32_t kpad)
+// Which form the rows take.  On 321 to 448 nodes, two tiles of nodes, a round of the tile (128 rows a unit) takes 0.72 of what cutting and
+// searching its rows does, but a round that is not full counts as one, and its candidate pass or its short list take 1.5 more.
+// Cut beforehand against the tile, whole search on 330 and 448 nodes: 500,000 x 300 663 us and 610, 690 and 658; 250,000 x 600 643 and 589, 682
+// and 642; but 140,000 x 600 407 and 428, 430 and 434, 30,000 x 1110 190 and 256, 200,000 x 900 778 and 786, 813 and 792.
+int bmu_wide_form(const som_ctx* ctx, int32_t K, int32_t D, int64_t rows)
 {
-    switch (wide_form(K, D)) {
+    if (D <= kHeldFeatures) return kWideHeld;
+    if (K <= kCutNodes) return kWideTile;
+    if (K > kCutNodesMany) return kWideCut;
+    const int64_t units = ctx->units > 0 ? ctx->units : 256, groups = (rows + kWTile - 1) / kWTile * 2, rounds = (groups + units - 1) / units;
+    return (double)rounds + 1.5 < 1.38 * (double)rows / (0.5 * kWTile * (double)units) ? kWideTile : kWideCut;
+}
+
+size_t bmu_wide_blob_bytes(int form, int32_t K, int32_t D, int32_t kpad)
+{
+    switch (form) {
     case kWideHeld: return bmu_held_blob_bytes(kpad, D);
     case kWideCut: return bmu_cut_blob_bytes(K, D);
     default: return tile_blob_bytes(K, D);
@@ -813,7 +826,7 @@ size_t bmu_wide_blob_bytes(int32_t K, int32_t D, int32_t kpad)
 
 float* bmu_wide_spread(const BmuPrep& prep, int32_t K, int32_t D)
 {
-    switch (wide_form(K, D)) {
+    switch (prep.form) {
     case kWideHeld: return bmu_held_spread(prep, D);
     case kWideCut: return bmu_cut_spread(prep, K, D);
     default: return nullptr;
@@ -822,7 +835,7 @@ float* bmu_wide_spread(const BmuPrep& prep, int32_t K, int32_t D)
 
 int bmu_wide_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, const BmuPrep& prep, double* qe, int32_t* small)
 {
-    switch (wide_form(K, D)) {
+    switch (prep.form) {
     case kWideHeld: return bmu_held_prepare(ctx, W, K, D, prep, qe, small);
     case kWideCut: return bmu_cut_prepare(ctx, W, K, D, prep, qe, small);
     default: return tile_prepare(ctx, W, K, D, prep, qe, small);
@@ -835,7 +848,7 @@ static WideArgs wide_args(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t 
     p.blob = (const char*)prep.stage16;
     p.rows = m;
     const int units = ctx->units > 0 ? ctx->units : 256;
-    switch (wide_form(K, D)) {
+    switch (prep.form) {
     case kWideHeld: bmu_held_plan(p, prep, m, K, D, units); break;
     case kWideCut: bmu_cut_plan(p, prep, m, K, D, units); break;
     default: tile_plan(p, m, K, D, units); break;
@@ -845,7 +858,7 @@ static WideArgs wide_args(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t 
 
 static int wide_launch(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, const WideArgs& p, bool cand)
 {
-    switch (wide_form(a.K, a.D)) {
+    switch (prep.form) {
     case kWideHeld: return bmu_held_launch(ctx, prep, a, p, cand);
     case kWideCut: return bmu_cut_launch(ctx, a, p, cand);
     default: return tile_launch(ctx, a, p, cand);
@@ -856,10 +869,10 @@ static int wide_launch(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, cons
 // all-nodes pass K D differences an entry.  (That pass takes 33 us at K D = 200,000 and 110 at 800,000 for any list of up to 256
 // entries, a candidate pass of held rows 4 to 15, and of rows cut beforehand 14 us where it takes 48 (300 x 1024) and 76 where it takes 322
 // (2000 x 1024): none of their lists is short enough.)
-static uint32_t cand_min_for(const BmuArgs& a) { return a.K > 65536 ? 0xffffffffu : wide_form(a.K, a.D) != kWideTile ? 0u : 256u; }
+static uint32_t cand_min_for(const BmuPrep& prep, const BmuArgs& a) { return a.K > 65536 ? 0xffffffffu : prep.form != kWideTile ? 0u : 256u; }
 
 // A pass's workspace: per-split winners, norms, candidate records, and the parts of rows cut beforehand with their scales.
-static size_t wide_work(WideArgs& p, char* w, int32_t K, int32_t D, int64_t m)
+static size_t wide_work(WideArgs& p, char* w, const BmuPrep& prep, int32_t D, int64_t m)
 {
     size_t at = 0;
     auto take = [&](size_t bytes) {
@@ -871,7 +884,7 @@ static size_t wide_work(WideArgs& p, char* w, int32_t K, int32_t D, int64_t m)
     p.norm = (float4*)take((size_t)m * sizeof(float4));
     p.record = (uint32_t*)take((size_t)m * kWRecord * sizeof(uint32_t));
     p.next = (uint4*)take((size_t)m * p.most_splits * sizeof(uint4));
-    if (wide_form(K, D) == kWideCut) {
+    if (prep.form == kWideCut) {
         p.scales = (float*)take(bmu_cut_scales_bytes(D, m));
         p.cut = take(bmu_cut_parts_bytes(D, m));
     }
@@ -881,14 +894,14 @@ static size_t wide_work(WideArgs& p, char* w, int32_t K, int32_t D, int64_t m)
 size_t bmu_wide_work_bytes(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t D, int64_t m)
 {
     WideArgs p = wide_args(ctx, prep, K, D, m);
-    return wide_work(p, nullptr, K, D, m);
+    return wide_work(p, nullptr, prep, D, m);
 }
 
 // most rows of a pass: some hundred bytes a sample, and the parts of rows cut beforehand
-int64_t bmu_wide_pass_rows(int32_t K, int32_t D)
+int64_t bmu_wide_pass_rows(const BmuPrep& prep, int32_t D)
 {
     const int64_t most = (int64_t)1 << 24;
-    if (wide_form(K, D) != kWideCut) return most;
+    if (prep.form != kWideCut) return most;
     const int64_t rows = bmu_cut_pass_rows(D);
     return rows < most ? rows : most;
 }
@@ -896,12 +909,12 @@ int64_t bmu_wide_pass_rows(int32_t K, int32_t D)
 int bmu_wide_run(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work)
 {
     WideArgs p = wide_args(ctx, prep, a.K, a.D, a.m);
-    wide_work(p, (char*)work, a.K, a.D, a.m);
-    p.cand_min = cand_min_for(a);
+    wide_work(p, (char*)work, prep, a.D, a.m);
+    p.cand_min = cand_min_for(prep, a);
     if (int rc = wide_launch(ctx, prep, a, p, false)) return rc;
     const int per_join = join_threads(a.m);
     const dim3 join_grid((unsigned)((a.m + per_join - 1) / per_join)), join_block(per_join);
-    if (wide_form(a.K, a.D) == kWideTile)
+    if (prep.form == kWideTile)
         hipLaunchKernelGGL(bmu_wide_join_kernel<false>, join_grid, join_block, 0, ctx->stream, a, p);
     else
         hipLaunchKernelGGL(bmu_wide_join_kernel<true>, join_grid, join_block, 0, ctx->stream, a, p);
@@ -912,8 +925,8 @@ int bmu_wide_run(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work
 int bmu_wide_recheck(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work)
 {
     WideArgs p = wide_args(ctx, prep, a.K, a.D, a.m);
-    wide_work(p, (char*)work, a.K, a.D, a.m);
-    p.cand_min = cand_min_for(a);
+    wide_work(p, (char*)work, prep, a.D, a.m);
+    p.cand_min = cand_min_for(prep, a);
     if (int rc = wide_launch(ctx, prep, a, p, true)) return rc;
     const int64_t groups = (a.m + 15) / 16;
     hipLaunchKernelGGL(bmu_wide_exact_kernel, dim3((unsigned)(groups < 2048 ? groups : 2048)), dim3(256), 0, ctx->stream, a, p);

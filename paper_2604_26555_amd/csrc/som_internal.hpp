@@ -16,7 +16,7 @@ constexpr int kMaxStepsResident = 32; // BMU kernel keeps a sample's features in
 
 struct BmuPrep {
     float* stage = nullptr;        // [Kpad / 128][nch] blobs: 128 padded weight rows of a chunk, then -|w|^2 / 2
-    void* stage16 = nullptr;       // parts of the weights for the split searches (D <= 64: stage rows of bf16 parts; D > 64: wide_form), else null
+    void* stage16 = nullptr;       // parts of the weights for the split searches (D <= 64: stage rows of bf16 parts; D > 64: bmu_wide_form), else null
     float* wrow = nullptr;         // [K][D] the weights as given in the stages' order (split search for D <= 64)
     int kb = 0;                    // whole 16-feature blocks of a stage16 row
     int tail_r = 0;                // features of the packed tail block behind them (0: none; D <= 64 only)
@@ -33,6 +33,7 @@ struct BmuPrep {
     unsigned int* tops = nullptr;
     int kpad = 0, steps = 0, stride = 0;
     int nch = 1;                   // feature chunks of 2 * steps features (1 unless D > 64)
+    int form = 0;                  // D > 64: WideForm
     int calls = 0;                 // bmu_run calls served by this preparation (selects the list counter)
 };
 
@@ -157,13 +158,15 @@ int check_hip(som_ctx* ctx, hipError_t e, const char* what);
 // kernels' host launchers (each returns SOM_OK or an error code after recording detail in ctx)
 int launch_fill_zero(som_ctx* ctx, void* p, size_t bytes);
 // qe (double[2]) and small (int32[4]) are zeroed by the preparation kernel when given
-int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, BmuPrep* out, double* qe, int32_t* small);
+// rows: how many a bmu_run will bring, as far as the caller knows
+int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, int64_t rows, BmuPrep* out, double* qe, int32_t* small);
 int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs args);
 // split search for D > 64 (som_bmu_wide.hip)
-size_t bmu_wide_blob_bytes(int32_t K, int32_t D, int32_t kpad);
+int bmu_wide_form(const som_ctx* ctx, int32_t K, int32_t D, int64_t rows);
+size_t bmu_wide_blob_bytes(int form, int32_t K, int32_t D, int32_t kpad);
 int bmu_wide_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, const BmuPrep& prep, double* qe, int32_t* small);
 size_t bmu_wide_work_bytes(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t D, int64_t m);
-int64_t bmu_wide_pass_rows(int32_t K, int32_t D);
+int64_t bmu_wide_pass_rows(const BmuPrep& prep, int32_t D);
 int bmu_wide_run(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work);
 int bmu_wide_recheck(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, void* work);
 int bmu_wide_distances(som_ctx* ctx, const BmuArgs& a);

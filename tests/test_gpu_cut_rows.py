@@ -43,6 +43,20 @@ def test_lists_of_rows_and_rows_that_start_anywhere(som):  # noqa: F811
     check(som, big[:, 1:302], W, idx)
 
 
+@pytest.mark.parametrize("K", [320, 321, 448, 449])
+@pytest.mark.parametrize("m", [129_000, 131_072, 140_000])
+def test_both_sides_of_the_line_by_rows(som, m, K):  # noqa: F811
+    """Rows that fill the tile's rounds, and rows that just do not; the first and the last ones."""
+    X, W = draw(m, K, 260, m + K)
+    rows = torch.cat([torch.arange(0, 512), torch.arange(m - 1024, m), torch.randint(m, (1024,))]).cuda()
+    b, _, _ = som.som_bmu(X, W)
+    x, w = X[rows].double(), W.double()
+    for lo in range(0, len(rows), 64):
+        d2 = ((x[lo:lo + 64, None, :] - w[None, :, :]) ** 2).sum(2)
+        got = d2.gather(1, b[rows[lo:lo + 64]].long()[:, None])[:, 0]
+        assert (got / d2.min(1).values - 1.0).max().item() <= 264 * 2.0 ** -23
+
+
 @pytest.mark.parametrize("m", [32768, 40001])
 def test_long_lists(som, m):  # noqa: F811
     """Six nodes close together everywhere, so that almost every row is listed: as many blocks of the list as workgroups cut them, and more; the
