@@ -88,6 +88,13 @@ def test_replayed_searches(cap, search, m, distinct, copies, D):
     assert np.array_equal(bmu.cpu().numpy(), want[0])
 
 
+# rows cut beforehand (every sample listed; none), rows held in registers on a map of several stages, five and eight candidates a sample
+@pytest.mark.parametrize("m,distinct,copies,D", [(6_000, 180, 2, 300), (4_000, 400, 1, 513), (6_000, 300, 2, 200),
+                                                 (20_000, 256, 5, 50), (20_000, 160, 8, 50)])
+def test_replayed_searches_of_wide_rows_and_many_candidates(cap, m, distinct, copies, D):
+    test_replayed_searches(cap, "auto", m, distinct, copies, D)
+
+
 # the last two are small epochs (two kernels each)
 @pytest.mark.parametrize("m,rows,D,epochs", [(20_000, 20, 50, 1), (20_000, 20, 50, 2), (3_000, 12, 80, 1),
                                              (5_000, 10, 8, 1), (5_000, 10, 8, 2)])
