@@ -33,6 +33,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace som {
 
 // Eight values as two bf16 parts each, one by one.  (As pairs, which is what the narrow search's prologue takes, this tile has eleven
@@ -600,14 +602,14 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Direct differences over the recorded candidates of both lists: sixteen lanes per sample, each a sixteenth of the features;
+// Direct differences over the recorded candidates of both lists: sixteen lanes per sample, each every sixteenth feature;
 // lowest distance, then lowest node index.  Samples without a usable record (more than fourteen candidates, none, or a
 // list that the candidate pass did not serve) go to the second list, which the all-nodes pass takes.
 // ---------------------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) bmu_wide_exact_kernel(const BmuArgs a, const WideArgs p)
 {
     const unsigned int n_open = a.scal[a.slot], n_known = a.scal[a.slot + 1], count = n_open + n_known;
-    const int sub = threadIdx.x & 15, whole = a.D / 64 * 64;
+    const int sub = threadIdx.x & 15;
     constexpr unsigned int per_group = 256 / 16;
     for (unsigned int p0 = blockIdx.x * per_group; p0 < count; p0 += gridDim.x * per_group) {
         const unsigned int q = p0 + (threadIdx.x >> 4);
@@ -637,40 +639,29 @@ __global__ void __launch_bounds__(256) bmu_wide_exact_kernel(const BmuArgs a, co
             const float* wr[kBatch];
 #pragma unroll
             for (int tt = 0; tt < kBatch; ++tt) wr[tt] = a.W + (size_t)(node[tt] >= 0 ? node[tt] : 0) * a.D;
-            auto add4 = [](float& sum, const float4& x, const float4& w) {
-                const float d0 = x.x - w.x, d1 = x.y - w.y, d2 = x.z - w.z, d3 = x.w - w.w;
-                sum = fmaf(d0, d0, sum);
-                sum = fmaf(d1, d1, sum);
-                sum = fmaf(d2, d2, sum);
-                sum = fmaf(d3, d3, sum);
+            // Lane `sub` adds up features sub, sub + 16, ...: the order is part of the result, since it decides which of two nodes gets a sample
+            // that lies between them to the last bit.  (By four neighbouring features a lane, sixteen bytes a load, such samples went elsewhere.)
+            auto add = [&](int f, auto many) {
+                constexpr int U = decltype(many)::value;
+                float x[U], w[kBatch][U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    x[u] = xr[f + 16 * u];
+#pragma unroll
+                    for (int tt = 0; tt < kBatch; ++tt) w[tt][u] = wr[tt][f + 16 * u];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int tt = 0; tt < kBatch; ++tt) {
+                        const float df = x[u] - w[tt][u];
+                        d[tt] = fmaf(df, df, d[tt]);
+                    }
             };
-            int f = 4 * sub;
-            for (; f + 3 * 64 < whole; f += 4 * 64) {            // (twelve loads under way)
-                float4 x[4], w[kBatch][4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    x[u] = load4(xr + f + 64 * u);
-#pragma unroll
-                    for (int tt = 0; tt < kBatch; ++tt) w[tt][u] = load4(wr[tt] + f + 64 * u);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int tt = 0; tt < kBatch; ++tt) add4(d[tt], x[u], w[tt][u]);
-            }
-            for (; f < whole; f += 64) {
-                const float4 x = load4(xr + f);
-#pragma unroll
-                for (int tt = 0; tt < kBatch; ++tt) add4(d[tt], x, load4(wr[tt] + f));
-            }
-            for (int t = whole + sub; t < a.D; t += 16) {
-                const float x = xr[t];
-#pragma unroll
-                for (int tt = 0; tt < kBatch; ++tt) {
-                    const float df = x - wr[tt][t];
-                    d[tt] = fmaf(df, df, d[tt]);
-                }
-            }
+            int f = sub;
+            for (; f - sub + 256 <= a.D; f += 256) add(f, std::integral_constant<int, 16>{});      // (48 loads under way)
+            for (; f - sub + 64 <= a.D; f += 64) add(f, std::integral_constant<int, 4>{});
+            for (; f < a.D; f += 16) add(f, std::integral_constant<int, 1>{});
 #pragma unroll
             for (int tt = 0; tt < kBatch; ++tt) {
                 float v = d[tt];
