@@ -641,7 +641,10 @@ int64_t bmu_cut_pass_rows(int32_t D)
 // What workgroups take: pieces of the map's stages, a unit one piece at a time.  The time goes with the rounds, times the stages of a piece and
 // about seven more (10^5 x 2000: 93 us a round of one stage, 126 of four).  Whole rounds of sample tiles in pieces of whole node tiles, by
 // preference of one: four and more pieces of a sample tile share its parts in an XCD's L2, and eight sample tiles the weights' (10^5 x 2000 on
-// 1024 nodes in pieces of four node tiles: 823 us instead of 727).  What is left over goes into smaller pieces, down to a stage.
+// 1024 nodes in pieces of four node tiles: 823 us instead of 727).  What is left over goes into smaller pieces, down to a stage, where an XCD's
+// eighth of the units then holds its eighth of the sample tiles: 10^5 x 2000 on 1024 nodes 1092 -> 1059 us, 22,526 x 951 on 1024 137 -> 125, 11,414 x
+// 914 on 530 72 -> 59; with two rounds of them 10,618 x 916 on 729 72 -> 88.  Behind whole rounds only where sample tiles have no short last piece or
+// four pieces and more: units that are through with short pieces take up the rest as it is (43,989 x 444 on 576 nodes 90 us, 93 in smaller pieces).
 void bmu_cut_plan(WideArgs& p, const BmuPrep& prep, int64_t m, int32_t K, int32_t D, int units)
 {
     p.nch = (D + kCutChunk - 1) / kCutChunk;
@@ -657,7 +660,7 @@ void bmu_cut_plan(WideArgs& p, const BmuPrep& prep, int64_t m, int32_t K, int32_
         int64_t first = tiles * pieces / units * units / pieces / 8 * 8;          // (the numbering goes by eight tiles)
         if (tiles * pieces % units == 0) first = tiles;
         int tail = per;
-        for (int t = per - whole; t >= 1 && first < tiles; t = t > whole ? t - whole : t / 2)
+        for (int t = per - whole; t >= 1 && first < tiles; t = t > whole ? t - whole : t / 2)        // (none where a piece is a node tile)
             if ((steps + t - 1) / t <= 16 && cost_of(tiles - first, t) < cost_of(tiles - first, tail) * 0.98) tail = t;
         const double cost = (first > 0 ? cost_of(first, per) : 0.0) + (first < tiles ? cost_of(tiles - first, tail) : 0.0);
         if (best > 0.0 && !(cost < best * 0.98)) continue;
@@ -665,12 +668,18 @@ void bmu_cut_plan(WideArgs& p, const BmuPrep& prep, int64_t m, int32_t K, int32_
         p.per_split = per;
         p.splits = pieces;
         p.tail_tile = first;
-        p.tail_row = first * kCutRows;
         p.tail_per = tail;
-        p.tail_splits = (steps + tail - 1) / tail;
-        p.most_splits = pieces > p.tail_splits ? pieces : p.tail_splits;
-        p.grid = (first + 7) / 8 * 8 * pieces + (tiles - first + 7) / 8 * 8 * p.tail_splits;
     }
+    const int64_t first = p.tail_tile, last = tiles - first;
+    if (p.per_split == whole && last > 0 && (first == 0 || p.splits >= 4 || steps % whole == 0)) {
+        const int64_t eighth = units < 8 ? 1 : units / 8;                         // (every eighth workgroup runs on the same XCD)
+        auto cost_on_one = [&](int per) { return (double)(((last + 7) / 8 * ((steps + per - 1) / per) + eighth - 1) / eighth) * ((double)per + 7.0); };
+        for (int t = whole / 2; t >= 1; t /= 2)
+            if ((steps + t - 1) / t <= 16 && cost_on_one(t) < cost_on_one(p.tail_per) * 0.98) p.tail_per = t;
+    }
+    p.tail_row = first * kCutRows < m ? first * kCutRows : m;
+    p.tail_splits = (steps + p.tail_per - 1) / p.tail_per;
+    p.grid = (first + 7) / 8 * 8 * p.splits + (last + 7) / 8 * 8 * p.tail_splits;
 }
 
 int bmu_cut_launch(som_ctx* ctx, const BmuArgs& a, const WideArgs& p, bool cand)

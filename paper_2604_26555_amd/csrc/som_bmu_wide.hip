@@ -491,7 +491,7 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
         for (int s0 = 0; s0 < splits; s0 += 4) {                 // (four loads under way)
             float4 r4[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) r4[u] = p.best[(size_t)(s0 + u < splits ? s0 + u : s0) * p.rows + i];
+            for (int u = 0; u < 4; ++u) r4[u] = p.best[p.result(s0 + u < splits ? s0 + u : s0, i)];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 if (s0 + u >= splits) break;
@@ -552,8 +552,8 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
             int hits = 0;
             open = a.K > 65536 || !(cut == cut);
             for (int s = 0; s < splits && !open; ++s) {
-                const float4 r = p.best[(size_t)s * p.rows + i];
-                const uint4 q = p.next[(size_t)s * p.rows + i];
+                const float4 r = p.best[p.result(s, i)];
+                const uint4 q = p.next[p.result(s, i)];
                 if (r.x >= cut && hits < kWIds) ids[hits++] = (uint16_t)__float_as_int(r.w);
                 if (r.y >= cut && hits < kWIds) ids[hits++] = (uint16_t)q.z;
                 if (__uint_as_float(q.x) >= cut && hits < kWIds) ids[hits++] = (uint16_t)(q.z >> 16);
@@ -871,10 +871,10 @@ static size_t wide_work(WideArgs& p, char* w, const BmuPrep& prep, int32_t D, in
         at += (bytes + 255) / 256 * 256;
         return q;
     };
-    p.best = (float4*)take((size_t)m * p.most_splits * sizeof(float4));
+    p.best = (float4*)take(p.results() * sizeof(float4));
     p.norm = (float4*)take((size_t)m * sizeof(float4));
     p.record = (uint32_t*)take((size_t)m * kWRecord * sizeof(uint32_t));
-    p.next = (uint4*)take((size_t)m * p.most_splits * sizeof(uint4));
+    p.next = (uint4*)take(p.results() * sizeof(uint4));
     if (prep.form == kWideCut) {
         p.scales = (float*)take(bmu_cut_scales_bytes(D, m));
         p.cut = take(bmu_cut_parts_bytes(D, m));

@@ -15,11 +15,11 @@ struct WideArgs {
     const float* norms;      // [K] -|w|^2 / 2
     int nch, tiles;          // chunks of a row; node tiles (som_bmu_wide.hip)
     int splits, per_split;   // workgroups that share a sample tile, steps (node tiles, stages of 64 nodes or blocks of 32) of each
-    int tail_splits, tail_per, most_splits;      // the same of the sample tiles from tail_tile, and the rows from tail_row, on
+    int tail_splits, tail_per;                   // the same of the sample tiles from tail_tile, and the rows from tail_row, on
     int64_t tail_tile, tail_row, grid;
     int64_t rows;            // m of the pass
-    float4* best;            // [splits][m] best, second best class winner, highest of all but the best four; id of the best (bits)
-    uint4* next;             // [splits][m] third and fourth (bits); 16-bit ids of the second and third, of the fourth
+    float4* best;            // [result] best, second best class winner, highest of all but the best four; id of the best (bits)
+    uint4* next;             // [result] third and fourth (bits); 16-bit ids of the second and third, of the fourth
     float4* norm;            // [m] |x|, and what a score errs by at most: y |w| + z + rounding of |w|^2 / 2 (bf16 parts: |x|^2, weighted |x|^2, |x - hi|^2)
     uint32_t* record;        // [m][kWRecord] candidates of the listed samples
     char* cut;               // the samples' parts, [block of 32][chunk], as a block of the weights; and the scales that take them back, [32] each
@@ -29,11 +29,18 @@ struct WideArgs {
     // all sample tiles alike
     void set_splits(int64_t m, int n, int per, int64_t groups)
     {
-        splits = tail_splits = most_splits = n;
+        splits = tail_splits = n;
         per_split = tail_per = per;
         tail_tile = tail_row = m;
         grid = groups;
     }
+    // Where the workgroup with number `split` of a sample leaves its winners: [splits][tail_row], then [tail_splits][rows - tail_row].  (The tail has up
+    // to sixteen splits and few rows: 32 bytes for every row and each of them would be most of a pass's memory.)
+    __host__ __device__ size_t result(int split, int64_t i) const
+    {
+        return i < tail_row ? (size_t)split * tail_row + i : (size_t)splits * tail_row + (size_t)split * (rows - tail_row) + (i - tail_row);
+    }
+    size_t results() const { return (size_t)splits * tail_row + (size_t)tail_splits * (rows - tail_row); }
 };
 
 typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
@@ -131,7 +138,7 @@ struct BestFour {
     }
     __device__ __forceinline__ void write(const WideArgs& p, int split, int64_t i, float back)
     {
-        const size_t at = (size_t)split * p.rows + i;
+        const size_t at = p.result(split, i);
         p.best[at] = make_float4(v[0] * back, v[1] * back, others * back, __int_as_float(id[0]));
         p.next[at] = make_uint4(__float_as_uint(v[2] * back), __float_as_uint(v[3] * back), (unsigned)id[1] & 0xffffu | (unsigned)id[2] << 16, (unsigned)id[3] & 0xffffu);
     }

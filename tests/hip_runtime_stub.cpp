@@ -30,7 +30,7 @@ std::map<void*, size_t> device_memory;
 std::map<std::pair<int, const void*>, size_t> lds_limit;     // per device: what a kernel's dynamic LDS was raised to
 int device = 0;
 std::string launched;                       // one line per launch: name grid.x grid.y grid.z block lds
-size_t limit = ~(size_t)0, allocated = 0, freed = 0;
+size_t limit = ~(size_t)0, allocated = 0, freed = 0, peak = 0;      // peak: largest allocation since it was reset
 bool capturing = false;
 std::string failing;                        // launches of kernels with this name fail
 hipError_t last_error = hipSuccess;
@@ -54,6 +54,8 @@ void stub_limit(size_t bytes) { limit = bytes; }
 void stub_capturing(int on) { capturing = on != 0; }
 size_t stub_allocated() { return allocated; }
 size_t stub_freed() { return freed; }
+size_t stub_peak() { return peak; }
+void stub_peak_reset() { peak = 0; }
 
 void** __hipRegisterFatBinary(const void*)
 {
@@ -109,6 +111,7 @@ hipError_t hipMalloc(void** p, size_t bytes)
     *p = malloc(bytes ? bytes : 1);
     device_memory[*p] = bytes;
     allocated += bytes;
+    if (bytes > peak) peak = bytes;
     return hipSuccess;
 }
 hipError_t hipFree(void* p)

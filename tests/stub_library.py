@@ -28,7 +28,7 @@ class StubContext:
 
     def __init__(self, path: str, stream=None, device=0):
         self.lib = C.CDLL(path)
-        for name in ("stub_allocated", "stub_freed"):
+        for name in ("stub_allocated", "stub_freed", "stub_peak"):
             getattr(self.lib, name).restype = C.c_size_t
         self.lib.stub_launches.restype = C.c_char_p
         self.lib.stub_limit.argtypes = [C.c_size_t]

@@ -24,9 +24,24 @@ def test_both_sides_of_the_line_to_the_tile(som, K):  # noqa: F811
 
 @pytest.mark.parametrize("m,K", [(33000, 330), (66000, 400), (70000, 1024), (1000, 4100)])
 def test_pieces(som, m, K):  # noqa: F811
-    """Whole rounds of tiles and a last, partial one in smaller pieces; few rows in pieces of one stage; the first and the last rows of each."""
+    """Whole rounds of tiles and a last, partial one in smaller pieces; few rows in pieces of eight stages; the first and the last rows of each."""
     X, W = draw(m, K, 260, m)
     rows = torch.cat([torch.arange(0, min(m, 512)), torch.arange(max(0, m - 1024), m), torch.randint(m, (1024,))]).cuda()
+    b, _, _ = som.som_bmu(X, W)
+    x, w = X[rows].double(), W.double()
+    for lo in range(0, len(rows), 64):
+        d2 = ((x[lo:lo + 64, None, :] - w[None, :, :]) ** 2).sum(2)
+        got = d2.gather(1, b[rows[lo:lo + 64]].long()[:, None])[:, 0]
+        assert (got / d2.min(1).values - 1.0).max().item() <= 264 * 2.0 ** -23
+
+
+@pytest.mark.parametrize("m,K,line", [(50_000, 600, 43_008), (22_526, 1024, 16_384), (100_000, 1024, 98_304), (50_497, 800, 49_152), (100_000, 1600, 98_304)])
+def test_whole_rounds_and_smaller_pieces_behind_them(som, m, K, line):  # noqa: F811
+    """Whole rounds of workgroups end at row `line`; the rows behind it are searched in pieces of four stages (as the others), two, one, one, and
+    two where the others take eight.  Nodes in close pairs, so that winners of every place decide; rows on both sides of the line and at either end."""
+    X, W = draw(m, K, 260, m + K)
+    W[K // 2:] = W[:K - K // 2] + 1e-4 * torch.randn((K - K // 2, 260), device="cuda", generator=torch.Generator(device="cuda").manual_seed(K))
+    rows = torch.cat([torch.arange(0, 512), torch.arange(line - 512, line + 512), torch.arange(m - 512, m), torch.randint(line, m, (1024,))]).cuda()
     b, _, _ = som.som_bmu(X, W)
     x, w = X[rows].double(), W.double()
     for lo in range(0, len(rows), 64):

@@ -204,6 +204,26 @@ def test_wide_rows_on_both_sides_of_their_lines(ctx):
         assert rc == 0 and names.count("bmu_cut_samples_kernel") == cut and ("bmu_wide_split_kernel" in names) != cut, (K, D, names)
 
 
+# workgroups: whole rounds of sample tiles (counted by eights) times their pieces, and the tiles left over times theirs
+@pytest.mark.parametrize("m,K,groups", [
+    (100_000, 1024, 384 * 4 + 8 * 16), (50_497, 800, 192 * 4 + 8 * 13), (100_000, 1600, 384 * 4 + 8 * 13), (10_000, 600, 40 * 5),
+    (140_000, 600, 512 * 3 + 40 * 3),                             # (a short last piece behind whole rounds of three)
+    (65_536, 1024, 256 * 4), (10_000, 1024, 40 * 4), (10_618, 729, 48 * 3), (1000, 4100, 8 * 9)])
+def test_the_last_round_of_rows_cut_beforehand_goes_in_smaller_pieces(ctx, m, K, groups):
+    rc, names = ctx.bmu(m, K, 600)
+    assert rc == 0 and [w[1] for w in ctx.launches if w[0] == "bmu_cut_split_kernel"] == [groups]
+
+
+def test_smaller_pieces_take_memory_for_their_own_rows_only(ctx):
+    """Sixteen pieces of the last tiles don't make every row's results sixteen: 300,000 rows on 1024 nodes and the whole rounds among them."""
+    whole, more = 65_536 * 4, 65_536 * 4 + 256 * 4
+    assert ctx.bmu(whole, 1024, 300)[0] == 0 and [w[1] for w in ctx.launches if w[0] == "bmu_cut_split_kernel"] == [whole // 256 * 4]
+    ctx.lib.stub_peak_reset()
+    assert ctx.bmu(more, 1024, 300)[0] == 0 and [w[1] for w in ctx.launches if w[0] == "bmu_cut_split_kernel"] == [whole // 256 * 4 + 8 * 16]
+    per_row = 5 * 228 + 16 + 32                                   # parts, scales, norm, record; and 32 bytes a result
+    assert ctx.lib.stub_peak() <= more * (per_row + 4 * 32) + 1024 * 12 * 32 + 4096
+
+
 def test_rows_cut_beforehand_go_in_passes_that_memory_holds(ctx):
     """The parts of a pass take at most a gigabyte, and where an allocation fails, half as many rows, down to a tile's."""
     passes = lambda m, K, D: ctx.bmu(m, K, D)[1].count("bmu_cut_samples_kernel")
