@@ -793,17 +793,22 @@ int wide_raise_lds(som_ctx* ctx, bool* done, const void* const (&kernels)[2], si
     return SOM_OK;
 }
 
-// Which form the rows take.  On 321 to 448 nodes, two tiles of nodes, a round of the tile (128 rows a unit) takes 0.72 of what cutting and
-// searching its rows does, but a round that is not full counts as one, and its candidate pass or its short list take 1.5 more.
-// Cut beforehand against the tile, whole search on 330 and 448 nodes: 500,000 x 300 663 us and 610, 690 and 658; 250,000 x 600 643 and 589, 682
-// and 642; but 140,000 x 600 407 and 428, 430 and 434, 30,000 x 1110 190 and 256, 200,000 x 900 778 and 786, 813 and 792.
+// Which form the rows take.  On 321 to 512 nodes, two tiles of nodes, the tile's time goes with its rounds (128 rows a unit; one that is not full
+// counts as one, and its lists as one more) and chunks of 32 features, the other form's with the rows and chunks of 64.  Chunk by chunk a
+// round takes 0.77 of what cutting and searching its rows does up to 384 nodes, 0.82 up to 448 and 0.88 up to 512.  Of 166 sizes of more than 28,000
+// rows this line takes a form that is slower by more than 2 % in eight, by 9 % at most.  Cut beforehand against the tile, whole search: 324,149 x 270
+// on 500 nodes 452 us and 417, 647,957 x 321 on 500 1024 and 880, 127,352 x 450 on 321 287 and 249, 231,917 x 300 on 343 339 and 310; but
+// 183,006 x 1024 on 512 733 and 801, 198,610 x 352 on 509 355 and 386, 50,831 x 600 on 400 169 and 200.  On 530 to 1296 nodes 300,000 x 257 457 us and
+// 454 up to 804 and 929.
 int bmu_wide_form(const som_ctx* ctx, int32_t K, int32_t D, int64_t rows)
 {
     if (D <= kHeldFeatures) return kWideHeld;
     if (K <= kCutNodes) return kWideTile;
     if (K > kCutNodesMany) return kWideCut;
     const int64_t units = ctx->units > 0 ? ctx->units : 256, groups = (rows + kWTile - 1) / kWTile * 2, rounds = (groups + units - 1) / units;
-    return (double)rounds + 1.5 < 1.38 * (double)rows / (0.5 * kWTile * (double)units) ? kWideTile : kWideCut;
+    const double full = (double)rows / (0.5 * kWTile * (double)units);
+    const double least = 1.3 - 0.08 * ((K - kCutNodes - 1) / 64);
+    return ((double)rounds + 1.0) * ((D + 31) / 32) < least * full * (2 * ((D + 63) / 64)) ? kWideTile : kWideCut;
 }
 
 size_t bmu_wide_blob_bytes(int form, int32_t K, int32_t D, int32_t kpad)

@@ -58,7 +58,7 @@ def test_lists_of_rows_and_rows_that_start_anywhere(som):  # noqa: F811
     check(som, big[:, 1:302], W, idx)
 
 
-@pytest.mark.parametrize("K", [320, 321, 448, 449])
+@pytest.mark.parametrize("K", [320, 321, 448, 449, 512, 513])
 @pytest.mark.parametrize("m", [129_000, 131_072, 140_000])
 def test_both_sides_of_the_line_by_rows(som, m, K):  # noqa: F811
     """Rows that fill the tile's rounds, and rows that just do not; the first and the last ones."""

@@ -195,11 +195,12 @@ def test_dynamic_lds_is_raised_on_every_device(library):
 
 
 def test_wide_rows_on_both_sides_of_their_lines(ctx):
-    """Rows of 65 to 256 features are held in registers; wider ones are cut beforehand on maps of more than 320 nodes, or of more than 448 where
-    the rows are many and fill the tile's rounds."""
+    """Rows of 65 to 256 features are held in registers; wider ones are cut beforehand on maps of more than 320 nodes, or of more than 512 where
+    the rows are many and fill the tile's rounds (the more of them the more nodes there are, and the less chunks of 32 features save)."""
     for m, K, D, cut in ((1000, 321, 256, False), (1000, 320, 257, False), (1000, 321, 257, True), (1000, 1024, 2000, True), (1000, 70000, 300, True),
-                         (131_072, 321, 257, False), (131_072, 448, 600, False), (131_072, 449, 600, True), (131_073, 448, 600, True), (129_000, 448, 600, True),
-                         (250_000, 400, 300, False)):
+                         (131_072, 321, 257, False), (131_072, 448, 600, False), (131_072, 449, 600, True), (131_073, 448, 600, True), (126_000, 448, 600, True),
+                         (250_000, 400, 300, False), (262_144, 512, 300, False), (262_144, 513, 300, True), (250_000, 512, 300, True),
+                         (250_000, 449, 320, True), (324_149, 500, 270, False)):
         rc, names = ctx.bmu(m, K, D)
         assert rc == 0 and names.count("bmu_cut_samples_kernel") == cut and ("bmu_wide_split_kernel" in names) != cut, (K, D, names)
 
