@@ -158,6 +158,7 @@ void som_destroy(som_ctx* c)
     }
     if (c->prep_blob) (void)hipFree(c->prep_blob);
     if (c->recheck) (void)hipFree(c->recheck);
+    if (c->pairs) (void)hipFree(c->pairs);
     if (c->bmu_ws) (void)hipFree(c->bmu_ws);
     if (c->acc_blob) (void)hipFree(c->acc_blob);
     if (c->parts_blob) (void)hipFree(c->parts_blob);

@@ -1506,7 +1506,10 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             p0 = hit ? (p0 << 16) | id : p0;
         }
         open = open || (p2 != 0xffffffffu && a.K < kPairMany);
-        if (close && !open) *reinterpret_cast<uint4*>(a.pairs + 4 * i) = make_uint4(p0, p1, p2, p3);
+        if (close && !open) {
+            if (a.K >= kPairMany) *reinterpret_cast<uint4*>(a.pairs + 4 * i) = make_uint4(p0, p1, p2, p3);
+            else *reinterpret_cast<uint2*>(a.pairs + 2 * i) = make_uint2(p0, p1);
+        }
     }
     int near = 0;
     if (r_valid) {
@@ -1971,6 +1974,7 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
     // [2 ROUND] next two ids, sample position, nearest so far (distance; row of the stages, and which word of its ids the two are)
     uint4* const later = info + ROUND;
     constexpr unsigned int kNoRow = 0xffffffu;
+    const int pair_shift = a.K >= kPairMany ? 2 : 1;                // words of an entry's ids
     unsigned int waiting = 0u;
     const int start = 4 * sub < D - 4 ? 4 * sub : D - 4;           // window inside the row
     const bool own = 4 * sub < D;
@@ -2053,7 +2057,7 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
         sum(l.x);
         const bool mine = lane < 2 * (int)n && c == 0;
         unsigned int rest_of = 0xffffffffu;
-        if (mine && word < 3u && l.x >> 16 != 0xffffu) rest_of = a.pairs[4 * (int64_t)l.y + word + 1u];
+        if (mine && word + 1u < 1u << pair_shift && l.x >> 16 != 0xffffu) rest_of = a.pairs[((int64_t)l.y << pair_shift) + word + 1u];
         const bool more = rest_of != 0xffffffffu;
         if (mine && !more && bk < a.K) a.bmu[l.y] = node_of_row(bk, a.K);
         waiting = base;
@@ -2083,9 +2087,9 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
         }
 #pragma unroll
         for (int u = 0; u < EACH; ++u) {
-            ids[u] = *reinterpret_cast<const uint2*>(a.pairs + 4 * (int64_t)at[u]);
+            ids[u] = *reinterpret_cast<const uint2*>(a.pairs + ((int64_t)at[u] << pair_shift));
             row[u] = a.idx ? a.idx[at[u]] : at[u];
-            ids1[u] = *reinterpret_cast<const uint2*>(a.pairs + 4 * (int64_t)at1[u]);
+            ids1[u] = *reinterpret_cast<const uint2*>(a.pairs + ((int64_t)at1[u] << pair_shift));
             row1[u] = a.idx ? a.idx[at1[u]] : at1[u];
         }
 #pragma unroll
@@ -2097,7 +2101,7 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
         const unsigned int p3 = after(after(after(p0)));
 #pragma unroll
         for (int u = 0; u < EACH; ++u) {
-            ids2[u] = *reinterpret_cast<const uint2*>(a.pairs + 4 * (int64_t)at2[u]);
+            ids2[u] = *reinterpret_cast<const uint2*>(a.pairs + ((int64_t)at2[u] << pair_shift));
             row2[u] = a.idx ? a.idx[at2[u]] : at2[u];
             at3[u] = position(p3, u);
         }
@@ -2788,10 +2792,10 @@ static int launch_bmu_distances(som_ctx* ctx, const BmuArgs& a)
 
 static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a);
 
-// The rows go through in passes of at most 2^27 (rows of more than 64 features: bmu_wide_pass_rows, and of fewer where memory runs out): the re-decision workspace then stays at 3.8 GB (28 bytes a row; the float32
-// searches' candidate sets 0.5 GB more) whatever m is,
-// and a pass's list stays within what the candidate pass can hold (2^24 entries, an eighth of a pass) — one call over
-// 10^9 rows listed more than that and fell back to direct differences over all nodes for every listed sample.
+// The rows go through in passes of at most 2^27 (rows of more than 64 features: bmu_wide_pass_rows), and of fewer where memory runs out.  The
+// re-decision workspace then stays at 3.8 GB whatever m is (28 bytes a row on maps of kPairMany nodes and more, 20 on others, 12 and the candidate
+// sets, 0.5 GB, in the float32 searches), and a pass's list stays within what the candidate pass can hold (2^24 entries, an eighth of a
+// pass) — one call over 10^9 rows listed more than that and fell back to direct differences over all nodes for every listed sample.
 int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
 {
     int64_t kRowsPerPass = (int64_t)1 << 27;
@@ -2810,7 +2814,7 @@ int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
         const int calls = prep.calls;
         const size_t events = ctx->prof_used;
         const int rc = bmu_run_pass(ctx, prep, b);
-        if (rc == SOM_ENOMEM && wide_split && b.m > 256) {         // (nothing of the pass has been launched)
+        if (rc == SOM_ENOMEM && b.m > 256) {         // (nothing of the pass has been launched)
             prep.calls = calls;
             ctx->prof_used = events;
             kRowsPerPass = (b.m / 2 + 127) / 128 * 128;
@@ -2837,16 +2841,30 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
             ctx->recheck_cap = 0;
             ctx->recheck_sets = false;
         }
-        // sample positions [cap], cuts [cap], per-sample cuts [cap], pair-list ids [cap][4], candidate sets [cand_cap][2]; the capacity is a
-        // multiple of four entries so that the 16-byte candidate sets stay aligned
+        // sample positions [cap], cuts [cap], per-sample cuts [cap], candidate sets [cand_cap][2]; the capacity is a multiple of four
+        // entries so that the 16-byte candidate sets stay aligned
         const size_t cap = ((size_t)a.m + 3) / 4 * 4, ccap = cand_cap_for(cap);
-        const size_t bytes = cap * 28 + (sets ? ccap * 2 * sizeof(ulonglong2) : 0);
+        const size_t bytes = cap * 12 + (sets ? ccap * 2 * sizeof(ulonglong2) : 0);
         if (hipMalloc((void**)&ctx->recheck, bytes) != hipSuccess) {
             (void)hipGetLastError();
             return fail(ctx, SOM_ENOMEM, "cannot allocate the %lld-entry recheck list", (long long)a.m);
         }
         ctx->recheck_cap = cap;
         ctx->recheck_sets = sets;
+    }
+    const size_t pair_words = prep.stage16 && prep.nch == 1 ? (a.K >= kPairMany ? 4 : 2) : 0;
+    if (const size_t need = (size_t)a.m * pair_words * sizeof(uint32_t); need > ctx->pairs_bytes) {
+        if (ctx->pairs) {
+            if (int rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync before workspace growth")) return rc;
+            (void)hipFree(ctx->pairs);
+            ctx->pairs = nullptr;
+            ctx->pairs_bytes = 0;
+        }
+        if (hipMalloc((void**)&ctx->pairs, need) != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(ctx, SOM_ENOMEM, "cannot allocate the %lld-entry pair list", (long long)a.m);
+        }
+        ctx->pairs_bytes = need;
     }
     a.kpad = prep.kpad;
     a.stage = prep.stage;
@@ -2863,10 +2881,10 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     a.cutv = (float*)(ctx->recheck + ctx->recheck_cap);
     a.cut_all = (float*)(ctx->recheck + 2 * ctx->recheck_cap);
     a.recheck_end = ctx->recheck + ctx->recheck_cap;
-    a.pairs = ctx->recheck + 3 * ctx->recheck_cap;
+    a.pairs = ctx->pairs;
     // (the per-sample cuts are dead once the lists are made: the second list takes their place)
     a.recheck2 = ctx->recheck + 2 * ctx->recheck_cap;
-    a.cand = (ulonglong2*)(ctx->recheck + 7 * ctx->recheck_cap);
+    a.cand = (ulonglong2*)(ctx->recheck + 3 * ctx->recheck_cap);
     a.cand_cap = (uint32_t)cand_cap_for(ctx->recheck_cap);
     // The candidate pass repeats the search for the listed samples at matrix speed (under a nanosecond per sample
     // at K D = 51200, against 3.8 ns for direct differences over all nodes) but has the latency of a whole tile, so

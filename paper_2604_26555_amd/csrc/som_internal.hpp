@@ -60,7 +60,8 @@ struct BmuArgs {
     float* cut_all;          // [m] per presented sample: its cut when it is to be re-decided, a NaN otherwise
     uint32_t* recheck;       // [m] sample positions to re-decide (compacted from cut_all by bmu_list_kernel)
     uint32_t* recheck_end;   // end of the recheck array, from which the pair list grows down
-    uint32_t* pairs;         // [m][4] per sample on the pair list: up to eight 16-bit rows of the stages, the used ones in front (0xffff: none)
+    uint32_t* pairs;         // [m][2], on large maps [m][4], per sample on the pair list: up to four (eight) 16-bit rows of the stages, the used ones
+                             // in front (0xffff: none)
     // Candidate pass (long lists only): the search is repeated for the listed samples, and every node whose score
     // reaches the sample's cut is noted; direct differences are then taken over those few nodes only.
     float* cutv;             // [m] per list entry: best score minus the rounding bound
@@ -107,9 +108,11 @@ struct som_ctx {
     void* prep_blob = nullptr;
     size_t prep_bytes = 0;
     bool prep_clean = false;       // its maxima (BmuPrep::tops) are zero
-    uint32_t* recheck = nullptr;   // one allocation: lists [cap], cuts [cap], per-sample marks or second list [cap], pair ids [cap][4], candidate sets
+    uint32_t* recheck = nullptr;   // one allocation: lists [cap], cuts [cap], per-sample marks or second list [cap], candidate sets
     size_t recheck_cap = 0;
     bool recheck_sets = false;     // the allocation holds the candidate sets
+    uint32_t* pairs = nullptr;     // pair ids, by the row: the searches for up to 64 features only, and on small maps half as many
+    size_t pairs_bytes = 0;
     int32_t* bmu_ws = nullptr;     // BMU indices of the epoch drivers (one chunk's worth)
     size_t bmu_elems = 0;
     void* acc_blob = nullptr;      // per-workgroup float64 slices + counts of the accumulation pass

@@ -56,6 +56,10 @@ class StubContext:
         """Allocations above nbytes fail from here on (None: none does)."""
         self.lib.stub_limit(C.c_size_t(nbytes if nbytes is not None else 2 ** 64 - 1))
 
+    def in_use(self) -> int:
+        """Bytes that are allocated now, by every context."""
+        return self.lib.stub_allocated() - self.lib.stub_freed()
+
     def error(self) -> str:
         return self.lib.som_last_error(self.ctx).decode()
 

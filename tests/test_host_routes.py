@@ -236,3 +236,37 @@ def test_rows_cut_beforehand_go_in_passes_that_memory_holds(ctx):
     ctx.limit()
     per = (1 << 30) // (32 * 228) // 256 * 256                   # 32 chunks of 64 features, a row's 224 bytes and a scale each
     assert passes(per, 400, 2000) == 1 and passes(per + 1, 400, 2000) == 2
+
+
+# bytes a row: list, cut and mark; two words of pair ids on small maps and four on large ones, for rows of up to 64 features only
+@pytest.mark.parametrize("K,D,search,per_row", [(400, 50, 0, 20), (1023, 50, 0, 20), (1024, 50, 0, 28), (3000, 20, 0, 28), (400, 50, 1, 12 + 32), (1024, 3, 0, 12 + 32)])
+def test_bytes_of_the_lists(library, K, D, search, per_row):
+    ctx = stub_library.StubContext(library)
+    try:
+        ctx.switch("som_set_search", search)
+        assert ctx.bmu(1000, K, D)[0] == 0
+        m, before = 4_000_000, ctx.in_use()
+        assert ctx.bmu(m, K, D)[0] == 0
+        assert per_row * (m - 100_000) <= ctx.in_use() - before <= per_row * m + 4 * K * (4 * D + 1000)
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("K,D,search,kernel,per_row", [(400, 50, 0, "bmu_split_kernel", 12), (1024, 50, 0, "bmu_split_kernel", 16),
+                                                       (300, 50, 1, "bmu_kernel", 44)])
+@pytest.mark.parametrize("passes", [1, 2, 4])
+def test_searches_without_memory_for_their_lists_go_in_passes(library, K, D, search, kernel, per_row, passes):
+    """Half as many rows where the largest allocation of a pass fails, and again; an error where nothing is left."""
+    ctx = stub_library.StubContext(library)
+    try:
+        ctx.switch("som_set_search", search)
+        m = 1_000_000
+        ctx.limit(m // passes * per_row + (1 << 16))
+        rc, names = ctx.bmu(m, K, D)
+        assert rc == 0 and sum(n.split("<")[0] == kernel for n in names) == passes, names
+        ctx.limit(1 << 10)
+        assert ctx.bmu(4 * m, 9 * K, D)[0] == -2
+        ctx.limit()
+        assert ctx.bmu(4 * m, K, D)[0] == 0
+    finally:
+        ctx.close()
