@@ -2792,16 +2792,36 @@ static int launch_bmu_distances(som_ctx* ctx, const BmuArgs& a)
 
 static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a);
 
+// what a pass's workspaces can have
+static size_t memory_left(som_ctx* ctx)
+{
+    size_t left = 0, total = 0;
+    if (hipMemGetInfo(&left, &total) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    const size_t sets = ctx->recheck_sets ? (ctx->recheck_cap < kCandCapMax ? ctx->recheck_cap : kCandCapMax) * 2 * sizeof(ulonglong2) : 0;
+    return left + ctx->recheck_cap * 12 + sets + ctx->pairs_bytes + ctx->parts_bytes;
+}
+
 // The rows go through in passes of at most 2^27 (rows of more than 64 features: bmu_wide_pass_rows), and of fewer where memory runs out.  The
 // re-decision workspace then stays at 3.8 GB whatever m is (28 bytes a row on maps of kPairMany nodes and more, 20 on others, 12 and the candidate
 // sets, 0.5 GB, in the float32 searches), and a pass's list stays within what the candidate pass can hold (2^24 entries, an eighth of a
 // pass) — one call over 10^9 rows listed more than that and fell back to direct differences over all nodes for every listed sample.
+// A search that memory kept from its passes starts with the rows that it held when it comes again, unless more memory is left than then: a
+// failing allocation costs a wait for the stream and the workspace that served the last call.
 int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
 {
     int64_t kRowsPerPass = (int64_t)1 << 27;
     const int64_t m = a.m;
     const bool wide_split = prep.stage16 && prep.nch > 1;
     if (wide_split) kRowsPerPass = bmu_wide_pass_rows(prep, a.D);
+    const int64_t asked = m < kRowsPerPass ? m : kRowsPerPass;
+    auto& scarce = ctx->scarce;
+    if (asked == scarce.asked && a.K == scarce.K && a.D == scarce.D) {
+        if (memory_left(ctx) <= scarce.left) kRowsPerPass = scarce.held;
+        else scarce.asked = 0;
+    }
     for (int64_t off = 0; off < m;) {
         BmuArgs b = a;
         b.m = m - off < kRowsPerPass ? m - off : kRowsPerPass;
@@ -2818,6 +2838,11 @@ int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
             prep.calls = calls;
             ctx->prof_used = events;
             kRowsPerPass = (b.m / 2 + 127) / 128 * 128;
+            scarce.left = memory_left(ctx);
+            scarce.asked = asked;
+            scarce.held = kRowsPerPass;
+            scarce.K = a.K;
+            scarce.D = a.D;
             continue;
         }
         if (rc) return rc;

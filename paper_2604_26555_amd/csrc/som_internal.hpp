@@ -118,6 +118,13 @@ struct som_ctx {
     void* acc_blob = nullptr;      // per-workgroup float64 slices + counts of the accumulation pass
     void* parts_blob = nullptr;    // workspace of a pass of the wide split search (D > 64)
     size_t parts_bytes = 0;
+    // The last search that memory kept from passes of `asked` rows: how many it held, and what was left of memory then, the workspaces of a
+    // pass counted in.
+    struct {
+        int64_t asked = 0, held = 0;
+        int32_t K = 0, D = 0;
+        size_t left = 0;
+    } scarce;
     size_t acc_bytes = 0;
     void* upd_blob = nullptr;      // influence matrix + split-k partials of the update
     size_t upd_bytes = 0;

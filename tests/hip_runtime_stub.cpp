@@ -31,6 +31,7 @@ std::map<std::pair<int, const void*>, size_t> lds_limit;     // per device: what
 int device = 0;
 std::string launched;                       // one line per launch: name grid.x grid.y grid.z block lds
 size_t limit = ~(size_t)0, allocated = 0, freed = 0, peak = 0;      // peak: largest allocation since it was reset
+size_t taken = 0;                           // device memory that others hold
 bool capturing = false;
 std::string failing;                        // launches of kernels with this name fail
 hipError_t last_error = hipSuccess;
@@ -50,6 +51,7 @@ void stub_reset()
 }
 void stub_fail(const char* kernel) { failing = kernel; }
 const char* stub_launches() { return launched.c_str(); }
+void stub_taken(size_t bytes) { taken = bytes; }
 void stub_limit(size_t bytes) { limit = bytes; }
 void stub_capturing(int on) { capturing = on != 0; }
 size_t stub_allocated() { return allocated; }
@@ -121,6 +123,12 @@ hipError_t hipFree(void* p)
     freed += it->second;
     device_memory.erase(it);
     free(p);
+    return hipSuccess;
+}
+hipError_t hipMemGetInfo(size_t* left, size_t* total)
+{
+    *total = (size_t)288 << 30;
+    *left = *total - taken - (allocated - freed);
     return hipSuccess;
 }
 hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) { return hipMalloc(p, bytes); }

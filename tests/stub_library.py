@@ -31,7 +31,7 @@ class StubContext:
         for name in ("stub_allocated", "stub_freed", "stub_peak"):
             getattr(self.lib, name).restype = C.c_size_t
         self.lib.stub_launches.restype = C.c_char_p
-        self.lib.stub_limit.argtypes = [C.c_size_t]
+        self.lib.stub_limit.argtypes = self.lib.stub_taken.argtypes = [C.c_size_t]
         self.lib.som_last_error.restype = C.c_char_p
         self.lib.som_last_error.argtypes = [C.c_void_p]
         self._buf = C.create_string_buffer(4096)          # stands for every array: no kernel runs, nothing is read

@@ -270,3 +270,36 @@ def test_searches_without_memory_for_their_lists_go_in_passes(library, K, D, sea
         assert ctx.bmu(4 * m, K, D)[0] == 0
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("m,K,D,kernel,limit", [(100_000, 400, 2000, "bmu_cut_samples_kernel", 64 << 20), (1_000_000, 1024, 50, "bmu_split_kernel", 5 << 20)])
+def test_passes_that_memory_held_are_kept(library, m, K, D, kernel, limit):
+    """The same call again starts with the rows that memory held: nothing is allocated and nothing given back.  With more memory it tries
+    again, and what fails then is kept in turn; another call is not touched."""
+    ctx = stub_library.StubContext(library)
+    passes = lambda *call: [n.split("<")[0] for n in ctx.bmu(*call)[1]].count(kernel)
+    moved = lambda: (ctx.lib.stub_allocated(), ctx.lib.stub_freed())
+    try:
+        ctx.lib.stub_taken(1 << 30)                               # (somebody else's)
+        ctx.limit(limit)
+        few = passes(m, K, D)
+        assert few > 1
+        before = moved()
+        for _ in range(3):
+            assert passes(m, K, D) == few and moved() == before
+        assert passes(m // 50, K, D) == 1 and passes(m, K, D) == few and moved() == before
+        ctx.lib.stub_taken(1 << 20)                               # more is left, but allocations fail as before
+        assert passes(m, K, D) == few and moved()[1] > before[1]
+        before = moved()
+        assert passes(m, K, D) == few and moved() == before
+        ctx.limit()
+        assert passes(m, K, D) == few and moved() == before
+        ctx.lib.stub_taken(0)
+        assert passes(m, K, D) == 1
+        before = moved()
+        ctx.limit(limit)
+        assert passes(m, K, D) == 1 and moved() == before
+    finally:
+        ctx.lib.stub_taken(0)
+        ctx.limit()
+        ctx.close()
