@@ -129,8 +129,9 @@ int som_create(som_ctx** out, int device, void* hip_stream)
         ok = ok && hipEventCreateWithFlags(&c->ev_copied[i], hipEventDisableTiming) == hipSuccess;
         ok = ok && hipEventCreateWithFlags(&c->ev_consumed[i], hipEventDisableTiming) == hipSuccess;
     }
-    int khz = 0;
+    int khz = 0, units = 0;
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0) c->clock_khz = khz;
+    if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && units > 0) c->units = units;
     ok = ok && update_static_init(c) == SOM_OK;
     if (!ok) {
         (void)hipGetLastError();

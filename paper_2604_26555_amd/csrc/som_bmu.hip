@@ -2652,12 +2652,6 @@ static int launch_bmu(som_ctx* ctx, const BmuArgs& a)
     // last, partial round goes with the number of sample blocks it gets.  When halving the tiles of that round
     // lowers the largest share (measured at 10^6 samples on 256 units: 7.63 rounds cost as much as 8), they are
     // halved.
-    if (ctx->units == 0) {
-        int units = 0;
-        if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || units < 1)
-            units = 256;
-        ctx->units = units;
-    }
     const int64_t per_group = (int64_t)kWavesPerGroup * MS * 32;
     const int64_t tiles = (a.m + per_group - 1) / per_group;
     const int64_t units = ctx->units, rem = tiles % (2 * units);
@@ -2688,12 +2682,6 @@ static int launch_bmu_split(som_ctx* ctx, const BmuArgs& a)
                                "raising the dynamic LDS limit"))
             return rc;
         attr_set = true;
-    }
-    if (ctx->units == 0) {
-        int units = 0;
-        if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || units < 1)
-            units = 256;
-        ctx->units = units;
     }
     // full tiles, and half tiles for the last partial round where that lowers the largest share (as launch_bmu)
     const int64_t per_group = (int64_t)kWavesPerGroup * MS * 32;
@@ -2936,12 +2924,6 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
         ++ctx->prof_used;
     }
     const bool wide_split = prep.stage16 && prep.nch > 1;
-    if (ctx->units == 0) {
-        int units = 0;
-        if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || units < 1)
-            units = 256;
-        ctx->units = units;
-    }
     if (wide_split) {
         const size_t need = bmu_wide_work_bytes(ctx, prep, a.K, a.D, a.m);
         if (need > ctx->parts_bytes) {

@@ -805,7 +805,7 @@ int bmu_wide_form(const som_ctx* ctx, int32_t K, int32_t D, int64_t rows)
     if (D <= kHeldFeatures) return kWideHeld;
     if (K <= kCutNodes) return kWideTile;
     if (K > kCutNodesMany) return kWideCut;
-    const int64_t units = ctx->units > 0 ? ctx->units : 256, groups = (rows + kWTile - 1) / kWTile * 2, rounds = (groups + units - 1) / units;
+    const int64_t units = ctx->units, groups = (rows + kWTile - 1) / kWTile * 2, rounds = (groups + units - 1) / units;
     const double full = (double)rows / (0.5 * kWTile * (double)units);
     const double least = 1.3 - 0.08 * ((K - kCutNodes - 1) / 64);
     return ((double)rounds + 1.0) * ((D + 31) / 32) < least * full * (2 * ((D + 63) / 64)) ? kWideTile : kWideCut;
@@ -843,7 +843,7 @@ static WideArgs wide_args(som_ctx* ctx, const BmuPrep& prep, int32_t K, int32_t 
     WideArgs p{};
     p.blob = (const char*)prep.stage16;
     p.rows = m;
-    const int units = ctx->units > 0 ? ctx->units : 256;
+    const int units = ctx->units;
     switch (prep.form) {
     case kWideHeld: bmu_held_plan(p, prep, m, K, D, units); break;
     case kWideCut: bmu_cut_plan(p, prep, m, K, D, units); break;

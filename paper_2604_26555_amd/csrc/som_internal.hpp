@@ -97,7 +97,7 @@ constexpr int kCandSlots = 8;         // 16-bit places per (list entry, half-wav
 
 struct som_ctx {
     int device = 0;
-    int units = 0;                 // compute units of the device (queried on first use)
+    int units = 256;               // compute units of the device
     hipStream_t stream = nullptr;
     hipStream_t copy_stream = nullptr;
     char err[512] = {0};

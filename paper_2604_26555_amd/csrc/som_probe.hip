@@ -149,11 +149,6 @@ extern "C" int som_mfma_rate_probe(som_ctx* ctx, int fold_steps, int waves_per_s
     if (fold_steps < 0 || fold_steps > 2 || waves_per_simd < 1 || waves_per_simd > 2 || iters < 1 || iters > (1 << 24))
         return fail(ctx, SOM_EINVAL, "fold_steps in 0..2, waves_per_simd in 1..2, iters in 1..2^24");
     if (int rc = check_hip(ctx, hipSetDevice(ctx->device), "hipSetDevice")) return rc;
-    if (ctx->units == 0) {
-        int units = 0;
-        if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || units < 1) units = 256;
-        ctx->units = units;
-    }
     const dim3 grid((unsigned)(ctx->units * waves_per_simd));
     auto kern = fold_steps == 0 ? mfma_rate_kernel<0> : fold_steps == 1 ? mfma_rate_kernel<1> : mfma_rate_kernel<2>;
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, ctx->stream, iters, 12345u, (float*)ctx->small);

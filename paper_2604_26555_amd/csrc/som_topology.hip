@@ -662,11 +662,6 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
                 sources = n;
             }
         }
-        if (ctx->units == 0) {
-            int units = 0;
-            if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || units < 1) units = 256;
-            ctx->units = units;
-        }
         pick = most * (size_t)ctx->units < (size_t)K;
     }
     hipLaunchKernelGGL(csr_degree_kernel, dim3((K + 3) / 4), dim3(256), 0, ctx->stream, A, K, deg);

@@ -31,6 +31,7 @@ std::map<std::pair<int, const void*>, size_t> lds_limit;     // per device: what
 int device = 0;
 std::string launched;                       // one line per launch: name grid.x grid.y grid.z block lds
 size_t limit = ~(size_t)0, allocated = 0, freed = 0, peak = 0;      // peak: largest allocation since it was reset
+int units = 256;
 size_t taken = 0;                           // device memory that others hold
 bool capturing = false;
 std::string failing;                        // launches of kernels with this name fail
@@ -51,6 +52,7 @@ void stub_reset()
 }
 void stub_fail(const char* kernel) { failing = kernel; }
 const char* stub_launches() { return launched.c_str(); }
+void stub_units(int n) { units = n; }
 void stub_taken(size_t bytes) { taken = bytes; }
 void stub_limit(size_t bytes) { limit = bytes; }
 void stub_capturing(int on) { capturing = on != 0; }
@@ -177,9 +179,9 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* prop, int)
     strcpy(prop->gcnArchName, "gfx950:sramecc+:xnack-");
     return hipSuccess;
 }
-hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int)
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t which, int)
 {
-    *v = 256;
+    *v = which == hipDeviceAttributeMultiprocessorCount ? units : 256;
     return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }

@@ -303,3 +303,20 @@ def test_passes_that_memory_held_are_kept(library, m, K, D, kernel, limit):
         ctx.lib.stub_taken(0)
         ctx.limit()
         ctx.close()
+
+
+def test_the_first_call_knows_the_units_of_its_device(library):
+    """131,072 rows fill the tile's rounds on 128 units and not on 256: the first call of a context takes the form that later ones take, and
+    sizes their workspaces."""
+    for units, cut in ((128, 0), (256, 1)):
+        library_units = stub_library.C.CDLL(library).stub_units
+        library_units(units)
+        ctx = stub_library.StubContext(library)
+        try:
+            first = ctx.bmu(131_072, 400, 300)
+            held = ctx.lib.stub_allocated()
+            assert first[0] == 0 and first[1].count("bmu_cut_samples_kernel") == cut
+            assert ctx.bmu(131_072, 400, 300) == first and ctx.lib.stub_allocated() == held
+        finally:
+            library_units(256)
+            ctx.close()
