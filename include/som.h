@@ -137,6 +137,10 @@ int som_read_probe(som_ctx* ctx, const void* p, int64_t bytes);
  * The N x K distance matrix is never formed in memory.  m == 0 is allowed (qe becomes {0, 0}).
  * With d2 and qe both NULL no distance is formed for samples that are not re-decided: the default search for D >= 4 then
  * reads every row once instead of twice.
+ * Memory that the library allocates for a search and keeps until som_destroy: 20 bytes a row (28 on maps of 1024 nodes and more),
+ * for at most 2^27 rows; rows of more than 64 features 12, and 80 to 560 for at most 2^24 rows; of more than 256 features, on maps of
+ * more than 320 nodes, also 3.6 bytes a value in parts, at most a gigabyte.  Where an allocation fails, the rows go in passes of half as
+ * many, and SOM_ENOMEM is returned when 256 find no memory.
  */
 int som_bmu(som_ctx* ctx, const float* X, int64_t N, int32_t D, int64_t ldx,
             const uint32_t* idx, int64_t m, const float* W, int32_t K,

@@ -2482,7 +2482,7 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, int64_t rows
     // instead of three for a block that would be mostly padding); larger remainders get a block of their own
     const int tail_r = (split && nch == 1 && D % 16 >= 1 && D % 16 <= 4) ? D % 16 : 0;
     const int kb = !split || nch > 1 ? 0 : (tail_r ? D / 16 : (D + 15) / 16);
-    // (D > 64: rows in the order of som_bmu_wide.hip)
+    // (D > 64: rows in the order of the form that the call takes)
     const size_t stage16_one = (split && nch == 1) ? (size_t)split_stage_f4(kb, tail_r > 0) * 16 : 0;
     const size_t stage16_bytes = !split ? 0 : nch == 1 ? (size_t)(kpad / kNodesPerStage) * stage16_one : bmu_wide_blob_bytes(out->form, K, D, kpad);
     const size_t wrow_bytes = (split && nch == 1) ? (size_t)K * D * sizeof(float) : 0;
@@ -2984,8 +2984,11 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     }
     if (a.K > 1) {
         if (prep.stage16 && prep.nch == 1) {
-            // (at most 55 KB: two workgroups of 128 registers a thread fit a compute unit)
-            const size_t rows = (size_t)(kExactThreads / 64) * pair_lds_f4(a.D, pair_lanes(a.D)) * 16, lds = rows > kExactLds ? rows : kExactLds;
+            // (at most 60 KB, at 29 to 32 features: two workgroups of 128 registers a thread fit a compute unit, and no limit has to be raised)
+            constexpr size_t kOwn = 2 * 4 * (kExactThreads / 64) * kExactGroup + 16 * 2 * 8 + 16 * 4;      // red_d, red_k and group_qe_add's
+            auto rows_of = [](int D) constexpr { return (size_t)(kExactThreads / 64) * pair_lds_f4(D, pair_lanes(D)) * 16; };
+            static_assert(rows_of(16) + kOwn <= 65536 && rows_of(32) + kOwn <= 65536 && rows_of(64) + kOwn <= 65536, "LDS of a launch");
+            const size_t rows = rows_of(a.D), lds = rows > kExactLds ? rows : kExactLds;
             BmuArgs b = a;                       // the distances come afterwards, for all samples
             b.d2 = nullptr;
             b.qe = nullptr;

@@ -1,4 +1,4 @@
-// Device helpers shared by the best-matching-unit kernels (som_bmu.hip, som_bmu_wide.hip).
+// Device helpers shared by the best-matching-unit kernels (som_bmu.hip and the three wide forms).
 #pragma once
 
 #include "som_internal.hpp"

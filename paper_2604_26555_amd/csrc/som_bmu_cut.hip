@@ -537,7 +537,7 @@ __device__ __forceinline__ void cut_tile(const BmuArgs& a, const WideArgs& p, in
     }
     if constexpr (CAND) return;
 
-    // ---- the sample's eight class winners of this workgroup: the two best with their ids, and the highest of all others
+    // ---- the sample's eight class winners of this workgroup: the four best with their ids, and the highest of all others
     float won[8];
     int where[8];
 #pragma unroll

@@ -201,7 +201,7 @@ __device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, c
             const int q = wave + kHWaves * i;
             if (q < BLK / 1024) lds_load16(from + q * 1024, to + q * 1024);
         }
-        // (lanes behind the thirty-second read the next block's norms, which nobody looks at)
+        // (lanes behind the thirty-second read the block's norms a second time, which nobody looks at)
         if (wave == kHWaves - 1) lds_load4(hp.hats + b * 32 + j, lds0 + 2 * BLK + (unsigned)(b & 3) * 256);
     };
     load_block(b_lo);

@@ -1,4 +1,4 @@
-// What the searches for more than 64 features share (som_bmu_wide.hip, som_bmu_held.hip): a pass's workspace and its join.
+// What the searches for more than 64 features share (som_bmu_wide.hip, som_bmu_held.hip, som_bmu_cut.hip): a pass's workspace and its join.
 #pragma once
 
 #include "som_bmu_common.hpp"

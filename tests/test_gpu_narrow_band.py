@@ -35,7 +35,7 @@ def test_one_node_far_from_the_others(som, D):  # noqa: F811
 @pytest.mark.parametrize("D", [5, 16, 17, 32, 50, 64])
 def test_two_to_nine_close_nodes(som, D, K):  # noqa: F811
     """Groups of two to nine nodes close together, so that samples have any number of candidates among their class winners: on both sides of
-    the size from which eight of them are kept, in a short list and in one of several rounds, rows in order and by a list."""
+    the size from which eight of them are kept, in short lists, rows in order and by a list."""
     g = torch.Generator(device="cuda").manual_seed(D + K)
     r = lambda *s: torch.randn(s, device="cuda", generator=g)
     size = 2 + torch.arange(K, device="cuda") % 8
@@ -46,3 +46,26 @@ def test_two_to_nine_close_nodes(som, D, K):  # noqa: F811
         X = W[torch.randint(K, (m,), device="cuda", generator=g)] + 0.1 * r(m, D)
         check(som, X, W)
         check(som, X, W, torch.randint(m, (m,), device="cuda", generator=g).int())
+
+
+@pytest.mark.parametrize("candidates", [2, 3, 4, 5, 8])
+@pytest.mark.parametrize("K,D", [(1024, 16), (1024, 32), (1152, 50), (512, 50)])
+def test_pair_lists_of_several_rounds(som, K, D, candidates):  # noqa: F811
+    """Every row is on the pair list, three rounds of it and more (512 workgroups of eight wavefronts take 65,536 entries a round up to 32
+    features, 32,768 above): the first `candidates` of every eight nodes in a row, which fall into eight classes, are close together.  Entries
+    of more than two wait among those of the rounds after theirs.  (On 512 nodes those of more than four go to the candidate pass.)"""
+    m = 140_000
+    g = torch.Generator(device="cuda").manual_seed(K + D + candidates)
+    r = lambda *s: torch.randn(s, device="cuda", generator=g)
+    base = 5.0 * r(K, D).view(K // 8, 8, D)
+    base[:, :candidates] = base[:, :1] + 1e-5 * r(K // 8, candidates, D)
+    W = base.view(K, D).contiguous()
+    eight = torch.randint(K // 8, (m,), device="cuda", generator=g)
+    X = base[eight, 0] + 0.1 * r(m, D)
+    for idx in (None, torch.randperm(m, device="cuda", generator=g)[:m - 5].int()):
+        b = som.som_bmu(X, W, idx=idx)[0].long()
+        rows = slice(None) if idx is None else idx.long()
+        x, near = X[rows].double(), base[eight[rows], :candidates].double()
+        nearest = ((x[:, None, :] - near) ** 2).sum(2).min(1).values
+        got = ((x - W[b].double()) ** 2).sum(1)
+        assert (got / nearest - 1.0).max().item() <= (D + 4) * 2.0 ** -23
