@@ -75,3 +75,27 @@ def test_units_do_not_go_with_the_number_of_rows(som, K, D):  # noqa: F811
     x, w = X[some[at].long()].double(), W.double()
     a, b = ((x - w[many[at]]) ** 2).sum(1), ((x - w[few[at]]) ** 2).sum(1)
     assert len(at) == 0 or ((a - b).abs() / torch.minimum(a, b)).max().item() <= (D + 4) * 2.0 ** -23
+
+
+def test_units_against_float64(som):  # noqa: F811
+    """Searches of all three forms, uniform and Gaussian rows, maps as given and collapsed to a fiftieth: how many units are not float64's nearest
+    node, and that those are nodes which float32 direct differences do not tell apart."""
+    differ = rows = 0
+    for K, D in ((1024, 100), (1024, 200), (600, 300), (300, 500), (1024, 1000), (1024, 2000)):
+        for uniform in (True, False):
+            m = 60_000 if D <= 500 else 30_000
+            g = torch.Generator(device="cuda").manual_seed(K + D + uniform)
+            X = torch.rand((m, D), device="cuda", generator=g) if uniform else torch.randn((m, D), device="cuda", generator=g)
+            W = X[torch.randperm(m, device="cuda", generator=g)[:K]]
+            for shrink in (1.0, 0.02):
+                w = (W.mean(0) + shrink * (W - W.mean(0))).contiguous()
+                b = som.som_bmu(X, w)[0].long()
+                for lo in range(0, m, 10_000):
+                    x, v = X[lo:lo + 10_000].double(), w.double()
+                    want = ((v * v).sum(1) - 2.0 * (x @ v.t())).argmin(1)
+                    at = (want != b[lo:lo + 10_000]).nonzero()[:, 0]
+                    best, got = ((x[at] - v[want[at]]) ** 2).sum(1), ((x[at] - v[b[lo + at]]) ** 2).sum(1)
+                    assert len(at) == 0 or (got / best - 1.0).max().item() <= (D + 4) * 2.0 ** -23, (K, D, uniform, shrink)
+                    differ += len(at)
+                rows += m
+    print(f"{differ} of {rows} units are not float64's nearest node", flush=True)
