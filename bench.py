@@ -271,21 +271,28 @@ def main() -> int:
                 "note": "over the whole epoch; the peak is that of the float32 vector unit as well"}
     elif split:
         # MFMAs of 32 nodes x 32 samples x 16 slots the kernel issues per 32 x 32 block: three per whole 16-feature block
-        # (hi.hi, lo.hi, hi.lo), one packed block for a remainder of 1..4 features (D <= 64); six per chunk of 32 features
-        # above.  Blocks of 32 nodes that hold none are left out.
+        # (hi.hi, lo.hi, hi.lo), one packed block for a remainder of 1..4 features (D <= 64).  Above, per 32 features two of half
+        # precision and one of fp6 (32 x 32 x 64); rows of more than 256 features on maps of up to 512 nodes may go by six of
+        # bf16 instead.  Blocks of 32 nodes that hold none are left out.
+        issued = None
         if wl.d <= 64:
             tail = 1 <= wl.d % 16 <= 4
             n_mfma = 3 * (wl.d // 16) + 1 if tail else 3 * ((wl.d + 15) // 16)
+            kpad = (wl.k + 31) // 32 * 32
+            issued = 2.0 * m * kpad * 16 * n_mfma
+            kernel = "bmu_split_kernel + bmu_list_kernel (scores from bf16 parts on the bf16 matrix pipe + arg-max; the samples to re-decide compacted into lists)"
         else:
-            n_mfma = 6 * ((wl.d + 31) // 32)
-        kpad = (wl.k + 31) // 32 * 32
-        issued = 2.0 * m * kpad * 16 * n_mfma
-        roof = {"bound": "mfma", "kernel": ("bmu_split_kernel + bmu_list_kernel" if wl.d <= 64 else "bmu_wide_split_kernel + bmu_wide_join_kernel") +
-                          " (scores from bf16 parts on the bf16 matrix pipe + arg-max; the samples to re-decide compacted into lists)",
+            units = (wl.d + 31) // 32 if wl.d <= 256 else 2 * ((wl.d + 63) // 64)
+            n_mfma = {"f16": 2 * units, "fp6": units}
+            kernel = ("bmu_wide_split_kernel" if wl.d <= 256 else "bmu_cut_samples_kernel + bmu_cut_split_kernel") + \
+                     " + bmu_wide_join_kernel (scores from half-precision parts and fp6 cross products + arg-max; the samples to re-decide compacted into lists)"
+            if wl.d > 256 and wl.k <= 512:
+                n_mfma, kernel = None, "one of the two forms for more than 256 features + bmu_wide_join_kernel"
+        roof = {"bound": "mfma", "kernel": kernel,
                 "achieved": achieved, "peak": PEAK_BF16_MFMA_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / PEAK_BF16_MFMA_TFLOPS if kernel_ms else None,
-                "issued": issued / (avg_kernel_ms * 1e-3) / 1e12 if kernel_ms else None,
-                "issued_frac": issued / (avg_kernel_ms * 1e-3) / 1e12 / PEAK_BF16_MFMA_TFLOPS if kernel_ms else None,
+                "issued": issued / (avg_kernel_ms * 1e-3) / 1e12 if kernel_ms and issued else None,
+                "issued_frac": issued / (avg_kernel_ms * 1e-3) / 1e12 / PEAK_BF16_MFMA_TFLOPS if kernel_ms and issued else None,
                 "mfma_per_block": n_mfma,
                 "note": "achieved = algorithmic 2 m K D float32 flops per launch; issued = the bf16 MFMA flops the kernel "
                         "executes for them (mfma_per_block instructions of 32 x 32 x 16 per 32 nodes x 32 samples, K padded to 32); "
@@ -312,7 +319,7 @@ def main() -> int:
             return float(np.median(last[-5:])) * 1e6 / (8.0 * iters * 2)
         simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
         ns_alone, ns_valu = sustained(0), sustained(2)
-        ns_kernel = avg_kernel_ms * 1e6 / (issued / (2.0 * 32 * 32 * 16) / simds)
+        ns_kernel = avg_kernel_ms * 1e6 / (issued / (2.0 * 32 * 32 * 16) / simds) if issued else None
         roof["power_limit"] = {"mfma_alone_ns": ns_alone, "mfma_with_6_vector_instructions_ns": ns_valu, "peak_ns": 13.333,
                                "mfma_alone_frac_of_peak": 13.333 / ns_alone, "with_6_vector_instructions_frac_of_peak": 13.333 / ns_valu,
                                "search_kernel_ns_per_mfma": ns_kernel,
@@ -407,7 +414,7 @@ def main() -> int:
         "metric": METRIC, "value": value, "unit": "samples/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None,
-        "dtype": ("bf16x2-split MFMA scores (float32 accumulate), f32 re-decision and distances, f64 sums and update" if split
+        "dtype": (("bf16x2-split" if wl.d <= 64 else "f16+fp6-split") + " MFMA scores (float32 accumulate), f32 re-decision and distances, f64 sums and update" if split
                   else "f32 MFMA scores, f32 re-decision and distances, f64 sums and update"),
         "data": "synthetic",
         "config": {"workload": f"{wl.name}: {wl.k}-node {wl.topology} map, {wl.n} x {wl.d} float32 samples resident in HBM"
@@ -415,7 +422,8 @@ def main() -> int:
                                f"sigma {wl.sigma[0]}->{wl.sigma[1]} over {args.steps} epochs",
                    "samples": wl.n, "presented_per_epoch": m_sel, "features": wl.d, "nodes": wl.k, "topology": wl.topology,
                    "final_qe": final_qe, "topology_rebuilt_on_device_each_epoch": lattice_G is None,
-                   "search": "bf16 parts on the bf16 matrix pipe, re-decision in float32" if split else "float32 MFMA"},
+                   "search": "float32 MFMA" if not split else "bf16 parts on the bf16 matrix pipe, re-decision in float32" if wl.d <= 64 else
+                             "half-precision parts and fp6 cross products on the matrix pipe, re-decision in float32"},
         "roofline": roof,
         "stages": stages,
     }
