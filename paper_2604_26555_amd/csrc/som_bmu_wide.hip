@@ -551,14 +551,26 @@ __global__ void __launch_bounds__(kJoinThreads) bmu_wide_join_kernel(const BmuAr
             uint16_t* ids = reinterpret_cast<uint16_t*>(rec + 1);
             int hits = 0;
             open = a.K > 65536 || !(cut == cut);
-            for (int s = 0; s < splits && !open; ++s) {
-                const float4 r = p.best[p.result(s, i)];
-                const uint4 q = p.next[p.result(s, i)];
-                if (r.x >= cut && hits < kWIds) ids[hits++] = (uint16_t)__float_as_int(r.w);
-                if (r.y >= cut && hits < kWIds) ids[hits++] = (uint16_t)q.z;
-                if (__uint_as_float(q.x) >= cut && hits < kWIds) ids[hits++] = (uint16_t)(q.z >> 16);
-                if (__uint_as_float(q.y) >= cut && hits < kWIds) ids[hits++] = (uint16_t)q.w;
-                open = open || r.z >= cut || hits >= kWIds;
+            for (int s0 = 0; s0 < splits && !open; s0 += 4) {    // (one after the other: 10^5 x 2000, whose last rows have sixteen pieces, 20.1 us for 16.5)
+                float4 r4[4];
+                uint4 q4[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const size_t at = p.result(s0 + u < splits ? s0 + u : s0, i);
+                    r4[u] = p.best[at];
+                    q4[u] = p.next[at];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (s0 + u >= splits || open) break;
+                    const float4 r = r4[u];
+                    const uint4 q = q4[u];
+                    if (r.x >= cut && hits < kWIds) ids[hits++] = (uint16_t)__float_as_int(r.w);
+                    if (r.y >= cut && hits < kWIds) ids[hits++] = (uint16_t)q.z;
+                    if (__uint_as_float(q.x) >= cut && hits < kWIds) ids[hits++] = (uint16_t)(q.z >> 16);
+                    if (__uint_as_float(q.y) >= cut && hits < kWIds) ids[hits++] = (uint16_t)q.w;
+                    open = open || r.z >= cut || hits >= kWIds;
+                }
             }
             rec[0] = open ? 0u : (unsigned)hits;                 // an open sample's record is filled by the candidate pass
         }
