@@ -2806,6 +2806,7 @@ int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     if (wide_split) kRowsPerPass = bmu_wide_pass_rows(prep, a.D);
     const int64_t asked = m < kRowsPerPass ? m : kRowsPerPass;
     auto& scarce = ctx->scarce;
+    bool fewer = false;
     if (asked == scarce.asked && a.K == scarce.K && a.D == scarce.D) {
         if (memory_left(ctx) <= scarce.left) kRowsPerPass = scarce.held;
         else scarce.asked = 0;
@@ -2826,15 +2827,18 @@ int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
             prep.calls = calls;
             ctx->prof_used = events;
             kRowsPerPass = (b.m / 2 + 127) / 128 * 128;
-            scarce.left = memory_left(ctx);
-            scarce.asked = asked;
-            scarce.held = kRowsPerPass;
-            scarce.K = a.K;
-            scarce.D = a.D;
+            fewer = true;
             continue;
         }
         if (rc) return rc;
         off += b.m;
+    }
+    if (fewer) {                                   // (a call that failed altogether, under capture for instance, says nothing about memory)
+        scarce.left = memory_left(ctx);
+        scarce.asked = asked;
+        scarce.held = kRowsPerPass;
+        scarce.K = a.K;
+        scarce.D = a.D;
     }
     return SOM_OK;
 }

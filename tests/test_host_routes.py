@@ -299,6 +299,10 @@ def test_passes_that_memory_held_are_kept(library, m, K, D, kernel, limit):
         before = moved()
         ctx.limit(limit)
         assert passes(m, K, D) == 1 and moved() == before
+        ctx.limit(1 << 10)                                        # a call that fails altogether is not kept: the next one asks for all rows
+        assert ctx.bmu(m * 13 // 10, K, D)[0] == -2
+        ctx.limit()
+        assert passes(m * 13 // 10, K, D) == 1
     finally:
         ctx.lib.stub_taken(0)
         ctx.limit()
