@@ -15,8 +15,8 @@
 // ahead (global_load_lds) with one barrier a stage.  What bounds it is the caches: 28 KB a stage and unit, 8 TB/s from L2 at 10^5 x 2000
 // on 1024 nodes, where the products by themselves would take 400 us of 730 at the power limit.
 //
-// Measured, whole search, 10^5 rows on 1024 nodes, against the tile of som_bmu_wide.hip: 300 features 321 -> 233 us, 1000 896 -> 666,
-// 2000 1716 -> 1235; on 1296 nodes 409 -> 289, 1263 -> 785, 2524 -> 1468 (of which the short lists, which no longer go through all nodes,
+// Measured, whole search, 10^5 rows on 1024 nodes, against the tile of som_bmu_wide.hip: 300 features 317 -> 229 us, 1000 893 -> 641,
+// 2000 1707 -> 1172; on 1296 nodes 403 -> 290, 1233 -> 770, 2450 -> 1421 (of which the short lists, which no longer go through all nodes,
 // 35, 130 and 280).
 #include "som_bmu_wide.hpp"
 

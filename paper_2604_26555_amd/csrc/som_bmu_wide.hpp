@@ -168,8 +168,8 @@ __device__ __forceinline__ void lds_load16(const void* from, unsigned lds)
 // Which search rows of more than 64 features take: held in the wavefronts' registers (som_bmu_held.hip) where they fit; wider ones are cut once
 // beforehand (som_bmu_cut.hip), except on small maps, where that pass over memory costs more than the shorter products give back
 // (som_bmu_wide.hip).  Up to 512 nodes, two tiles of nodes, the tile also stays ahead where the rows are many and fill its rounds (bmu_wide_form).
-// Whole search, 10^5 rows, cut beforehand against the tile: 600 features 311 us and 299 on 320 nodes, 310 and 316 on 361,
-// 439 and 546 on 1024; 2000 features 915 and 955, 902 and 997, 1235 and 1716; on 256 nodes 787 and 685.
+// Whole search, 10^5 rows, cut beforehand against the tile: 600 features 311 us and 299 on 320 nodes, 309 and 289 on 361,
+// 423 and 531 on 1024; 2000 features 915 and 955, 902 and 997, 1172 and 1707; on 256 nodes 787 and 685.
 enum WideForm { kWideTile, kWideHeld, kWideCut };
 constexpr int kCutNodes = 320;                    // most nodes that the tile always takes,
 constexpr int kCutNodesMany = 512;                // and most that it takes for many rows

@@ -24,7 +24,8 @@ def test_both_sides_of_the_line_to_the_tile(som, K):  # noqa: F811
 
 @pytest.mark.parametrize("m,K", [(33000, 330), (66000, 400), (70000, 1024), (1000, 4100)])
 def test_pieces(som, m, K):  # noqa: F811
-    """Whole rounds of tiles and a last, partial one in smaller pieces; few rows in pieces of eight stages; the first and the last rows of each."""
+    """Whole rounds of tiles and a last, partial one, in pieces as large and in smaller ones; few rows in pieces of eight stages; the first and the last
+    rows of each."""
     X, W = draw(m, K, 260, m)
     rows = torch.cat([torch.arange(0, min(m, 512)), torch.arange(max(0, m - 1024), m), torch.randint(m, (1024,))]).cuda()
     b, _, _ = som.som_bmu(X, W)
