@@ -263,6 +263,7 @@ def main() -> int:
     flops = 2.0 * m * wl.k * wl.d                          # algorithmic: 2 K D per presented sample
     achieved = flops / (avg_kernel_ms * 1e-3) / 1e12 if kernel_ms else None
     # which matrix pipe the dominant kernel runs on decides the peak it is priced against
+    half_parts = False
     split = args.search == "auto" and wl.d >= 4 and wl.k > 1       # (what SOM_SEARCH_AUTO means in the library)
     if small:
         roof = {"bound": "latency", "kernel": "small_kernel + small_update_kernel (direct differences, sums in LDS, update: two launches an epoch)",
@@ -270,17 +271,26 @@ def main() -> int:
                 "unit": "TFLOP/s", "frac": flops / (gpu_s / max(args.steps, 1)) / 1e12 / PEAK_FP32_MFMA_TFLOPS if gpu_s > 0 else None,
                 "note": "over the whole epoch; the peak is that of the float32 vector unit as well"}
     elif split:
-        # MFMAs of 32 nodes x 32 samples x 16 slots the kernel issues per 32 x 32 block: three per whole 16-feature block
-        # (hi.hi, lo.hi, hi.lo), one packed block for a remainder of 1..4 features (D <= 64).  Above, per 32 features two of half
-        # precision and one of fp6 (32 x 32 x 64); rows of more than 256 features on maps of up to 512 nodes may go by six of
+        # MFMAs of 32 nodes x 32 samples x 16 slots the kernel issues per 32 x 32 block (D <= 64): three per whole 16-feature block
+        # (hi.hi, lo.hi, hi.lo), one packed block for a remainder of 1..4 features; large calls of more than 20 features one of half
+        # precision per 16 places (the norms take four) and one of fp6 (32 x 32 x 64, the same cycles) per 32 features.  Above, per 32
+        # features two of half precision and one of fp6; rows of more than 256 features on maps of up to 512 nodes may go by six of
         # bf16 instead.  Blocks of 32 nodes that hold none are left out.
         issued = None
+        half_parts = wl.d > 64
         if wl.d <= 64:
             tail = 1 <= wl.d % 16 <= 4
             n_mfma = 3 * (wl.d // 16) + 1 if tail else 3 * ((wl.d + 15) // 16)
             kpad = (wl.k + 31) // 32 * 32
             issued = 2.0 * m * kpad * 16 * n_mfma
             kernel = "bmu_split_kernel + bmu_list_kernel (scores from bf16 parts on the bf16 matrix pipe + arg-max; the samples to re-decide compacted into lists)"
+            first, cross = (wl.d + 3) // 4 // 4 + 1, (wl.d + 31) // 32
+            fewer = kpad // 32 * (n_mfma - first - cross)
+            if wl.d > 20 and fewer >= 40 and m * fewer >= 40000000:          # (half_parts_pay in the library)
+                n_mfma = {"f16": first, "fp6": cross}
+                issued = 2.0 * m * kpad * 16 * (first + cross)
+                half_parts = True
+                kernel = "bmu_split_kernel + bmu_list_kernel (scores from half-precision parts and fp6 cross products + arg-max; the samples to re-decide compacted into lists)"
         else:
             units = (wl.d + 31) // 32 if wl.d <= 256 else 2 * ((wl.d + 63) // 64)
             n_mfma = {"f16": 2 * units, "fp6": units}
@@ -294,8 +304,9 @@ def main() -> int:
                 "issued": issued / (avg_kernel_ms * 1e-3) / 1e12 if kernel_ms and issued else None,
                 "issued_frac": issued / (avg_kernel_ms * 1e-3) / 1e12 / PEAK_BF16_MFMA_TFLOPS if kernel_ms and issued else None,
                 "mfma_per_block": n_mfma,
-                "note": "achieved = algorithmic 2 m K D float32 flops per launch; issued = the bf16 MFMA flops the kernel "
-                        "executes for them (mfma_per_block instructions of 32 x 32 x 16 per 32 nodes x 32 samples, K padded to 32); "
+                "note": "achieved = algorithmic 2 m K D float32 flops per launch; issued = the MFMA flops the kernel "
+                        "executes for them (mfma_per_block instructions per 32 nodes x 32 samples, K padded to 32, each counted as one of "
+                        "32 x 32 x 16, whose cycles it takes); "
                         "under the search for up to 64 features the chip holds its power limit at a shader clock of about 1.9 GHz, the peak assumes 2.4"}
     else:
         roof = {"bound": "mfma", "kernel": "bmu_kernel (fused float32 score contraction + arg-max)",
@@ -414,7 +425,7 @@ def main() -> int:
         "metric": METRIC, "value": value, "unit": "samples/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None,
-        "dtype": (("bf16x2-split" if wl.d <= 64 else "f16+fp6-split") + " MFMA scores (float32 accumulate), f32 re-decision and distances, f64 sums and update" if split
+        "dtype": (("f16+fp6-split" if half_parts else "bf16x2-split") + " MFMA scores (float32 accumulate), f32 re-decision and distances, f64 sums and update" if split
                   else "f32 MFMA scores, f32 re-decision and distances, f64 sums and update"),
         "data": "synthetic",
         "config": {"workload": f"{wl.name}: {wl.k}-node {wl.topology} map, {wl.n} x {wl.d} float32 samples resident in HBM"
@@ -422,8 +433,8 @@ def main() -> int:
                                f"sigma {wl.sigma[0]}->{wl.sigma[1]} over {args.steps} epochs",
                    "samples": wl.n, "presented_per_epoch": m_sel, "features": wl.d, "nodes": wl.k, "topology": wl.topology,
                    "final_qe": final_qe, "topology_rebuilt_on_device_each_epoch": lattice_G is None,
-                   "search": "float32 MFMA" if not split else "bf16 parts on the bf16 matrix pipe, re-decision in float32" if wl.d <= 64 else
-                             "half-precision parts and fp6 cross products on the matrix pipe, re-decision in float32"},
+                   "search": "float32 MFMA" if not split else "half-precision parts and fp6 cross products on the matrix pipe, re-decision in float32" if half_parts else
+                             "bf16 parts on the bf16 matrix pipe, re-decision in float32"},
         "roofline": roof,
         "stages": stages,
     }

@@ -37,6 +37,27 @@
 namespace som {
 
 constexpr int kWavesPerGroup = 4;
+// Form of the split search's rows (D <= 64): whole 16-feature blocks of two bf16 parts; the packed block of four features alone;
+// half-precision and fp6 parts of up to 32 features, and of up to 64.
+enum SplitForm { kFormWhole, kFormTail, kFormHalf1, kFormHalf2 };
+constexpr int form_units(int form) { return form < kFormHalf1 ? 0 : form - kFormHalf1 + 1; }
+constexpr int kHalfBit = 9;            // scales of the half-precision parts: the largest element comes to lie in [2^9, 2^10)
+constexpr int kHalfRange = 28;         // most that the scales of samples lie below the weights'
+constexpr int kHalfNorm = 14;          // the norms lie 2^14 below them,
+constexpr float kHalfMost = 65504.0f;  // and fit half precision
+constexpr int half_norm_group(int D) { return (D + 3) / 4; }       // their place in the row, in fours: behind the features
+__device__ __forceinline__ int half_scale(float most)
+{
+    const int e = kHalfBit + 127 - (int)(__float_as_uint(most) >> 23 & 255u);
+    return e < -90 ? -90 : e > 90 ? 90 : e;
+}
+// the exponent of the fp6 scale that takes `most` into [3.75, 7.5]
+__device__ __forceinline__ int fp6_scale(float most)
+{
+    const unsigned b = __float_as_uint(most);
+    const int e = (int)(b >> 23 & 255u) - 129 + ((b & 0x7fffffu) > 0x700000u ? 1 : 0);
+    return e < -40 ? -40 : e > 40 ? 40 : e;
+}
 constexpr int kThreads = kWavesPerGroup * 64;
 
 constexpr uint32_t kCandMin = 4096;             // shortest list the candidate pass serves: its tiles take 15 to 30 us however few they are, the all-nodes
@@ -208,6 +229,8 @@ __global__ void __launch_bounds__(256) bmu_prep_kernel(const float* __restrict__
 //     block that is mostly padding) but one packed block whose sixteen slots hold the three products side by side,
 //         weights  [ hi(r) | hi(r) | lo(r) | norm parts (3) | 0 ... ]   against samples  [ hi(r) | lo(r) | hi(r) | 1 1 1 | 0 ... ],
 //     one MFMA.
+//   * HALF: half-precision and fp6 parts instead (layout at bmu_split_tile; a wavefront's lanes trade them through its own part of LDS), the
+//     norms' three parts in the places behind the features.  8.5 us at 1024 x 50, 6.2 with two bf16 parts.
 //   * Norms: -|w|^2 / 2 + w . (w - hi - lo) behind the stage's rows (and as three bf16 parts in the packed block; the second term is what the
 //     products of a sample that lies at the node drop), the largest norms of the nodes and of what the bf16 cut leaves over (w - hi,
 //     w - hi - lo) in scal.
@@ -252,14 +275,37 @@ template <typename T> __device__ __forceinline__ T lanes_sum(T x)
     return both<true>(both<false>(x));
 }
 
+template <bool HALVES> __device__ __forceinline__ float larger(float x)
+{
+    const auto r = traded<HALVES>(__float_as_uint(x));
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float lanes_max(float x)
+{
+    x = fmaxf(x, rotated<0x128>(x));
+    x = fmaxf(x, rotated<0x124>(x));
+    x = fmaxf(x, rotated<0x122>(x));
+    x = fmaxf(x, rotated<0x121>(x));
+    return larger<true>(larger<false>(x));
+}
+
 constexpr int kCentreNodes = 64;
 constexpr int kPrepNodes = 16;           // nodes (wavefronts) of a workgroup: 64 bytes of a row of the transposed copy
+
+// a wavefront's writes to LDS before, its reads behind
+__device__ __forceinline__ void wave_lds()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
 
 struct SplitPrep {
     char* stage16;
     float* wrow;
-    int kb_count, tail_r, row_bytes, stage16_bytes;
+    int kb_count, tail_r, units, row_bytes, stage16_bytes;
 };
+struct HalfPrep : SplitPrep {};          // (half-precision and fp6 parts)
 
 // the t-th of `count` nodes whose mean is the centre (count = K: all of them)
 __device__ __forceinline__ int centre_node(int t, int count, int K)
@@ -272,15 +318,16 @@ __device__ __forceinline__ int centre_node(int t, int count, int K)
     return (int)((int64_t)t * K / count) + (int)__umulhi(h, (uint32_t)(K / count));
 }
 
-__global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const float* __restrict__ W, int K, int D, int kpad,
-                                                                         float* __restrict__ centre, float* __restrict__ wt,
-                                                                         unsigned int* __restrict__ scal, unsigned int* __restrict__ tops,
-                                                                         double* __restrict__ qe, int32_t* __restrict__ small, const SplitPrep sp)
+template <bool HALF>
+__device__ __forceinline__ void split_prep(const float* __restrict__ W, int K, int D, int kpad, float* __restrict__ centre, float* __restrict__ wt,
+                                           unsigned int* __restrict__ scal, unsigned int* __restrict__ tops, double* __restrict__ qe,
+                                           int32_t* __restrict__ small, const SplitPrep& sp)
 {
     __shared__ float part[kPrepNodes][64];
     __shared__ float given[kPrepNodes][65];
     __shared__ uint4 rows16[kPrepNodes * 272 / 16];           // [node][row_bytes]
-    __shared__ float most[kPrepNodes][3];
+    __shared__ float most[kPrepNodes][4];
+    __shared__ __align__(16) _Float16 parts[HALF ? kPrepNodes : 1][2][64];          // HALF: first and second parts, by the places of a row
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int k0 = blockIdx.x * kPrepNodes, k = k0 + wave;           // rows of the stages (and of the transposed copy)
     stamp(small, kStampStart);
@@ -289,6 +336,7 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
         if (tid < 2 && qe) qe[tid] = 0.0;
         if (tid < 4 && small) small[tid] = 0;
     }
+    __shared__ float spread[kPrepNodes];
     const bool real = k < K && lane < D;
     const float w = real ? W[(size_t)node_of_row(k, K) * D + lane] : 0.0f;
     const int count = K < kCentreNodes ? K : kCentreNodes;
@@ -302,6 +350,18 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
 #pragma unroll
     for (int u = 0; u < kCentreNodes / kPrepNodes; ++u) s += v4[u];
     part[wave][lane] = s;
+    if constexpr (HALF) {
+        // how far the nodes of the centre lie from the first of them: the centre's own distances to within a factor of two
+        const float v0 = lane < D ? W[(size_t)centre_node(0, count, K) * D + lane] : 0.0f;
+        float top = 0.0f;
+#pragma unroll
+        for (int u = 0; u < kCentreNodes / kPrepNodes; ++u)
+            top = fmaxf(top, wave * (kCentreNodes / kPrepNodes) + u < count ? fabsf(v4[u] - v0) : 0.0f);
+        top = lanes_max(top);
+        if (lane == 0) spread[wave] = top;
+        parts[wave][0][lane] = (_Float16)0.0f;
+        parts[wave][1][lane] = (_Float16)0.0f;
+    }
     given[wave][lane] = w;
     for (int e = tid; e < kPrepNodes * sp.row_bytes / 16; e += 64 * kPrepNodes) rows16[e] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
@@ -311,49 +371,131 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
     c /= (float)count;                                        // zero behind the row
     if (blockIdx.x == 0 && wave == 0) centre[lane] = c;
     const float v = real ? w - c : 0.0f;
-    const __bf16 hi = (__bf16)v;
-    const float left = v - (float)hi;
-    const __bf16 lo = (__bf16)left;
-    const float rest = left - (float)lo;
-    const double nrm = lanes_sum((double)v * (double)v);
-    const float lo2 = lanes_sum(left * left), rest2 = lanes_sum(rest * rest), with_rest = lanes_sum(v * rest);
     char* const row = reinterpret_cast<char*>(rows16) + wave * sp.row_bytes;
-    if (real) {
-        const int tail0 = D - sp.tail_r;
-        if (lane < tail0) {
-            // slot group q = four features, its window [min(4 q, D - 4), + 4): own elements only, zeros in front of them
-            const int q = lane >> 2, start = 4 * q < D - 4 ? 4 * q : D - 4;
-            const int kb = q >> 2, g = (q >> 1) & 1, t = (q & 1) * 4 + lane - start;
-            __bf16* cell = reinterpret_cast<__bf16*>(row + kb * 64 + g * 32) + t;
-            cell[0] = hi;
-            cell[8] = lo;
-        } else {
-            __bf16* cell = reinterpret_cast<__bf16*>(row + sp.kb_count * 64) + (lane - tail0);
-            cell[0] = hi;
-            cell[sp.tail_r] = hi;
-            cell[2 * sp.tail_r] = lo;
+    if constexpr (HALF) {
+        // the scale: from the nodes that the centre is the mean of; others may lie twenty times as far out and more (kHalfBit)
+        float top = spread[lane & (kPrepNodes - 1)];
+        top = fmaxf(top, rotated<0x128>(top));
+        top = fmaxf(top, rotated<0x124>(top));
+        top = fmaxf(top, rotated<0x122>(top));
+        top = fmaxf(top, rotated<0x121>(top));
+        static_assert(kPrepNodes == 16, "a row of lanes");
+        const int sw = half_scale(top);
+        const float up = power_of_two(sw), back = power_of_two(-sw);
+        if (blockIdx.x == 0 && tid == kScalShift) scal[kScalShift] = (unsigned)sw;
+        const float h = v * up;
+        const _Float16 hi = (_Float16)h;
+        const float left = h - (float)hi;
+        // place of this lane's feature: features in fours, the last ones' window shifted back into the row (own features only, zeros in front)
+        const int q = lane >> 2, start = 4 * q < D - 4 ? 4 * q : D - 4, slot = 4 * q + lane - start;
+        if (real) {
+            parts[wave][0][slot] = hi;
+            parts[wave][1][slot] = (_Float16)left;
+            reinterpret_cast<_Float16*>(row)[slot] = hi;
         }
-    }
-    if (lane == 0) {
-        const float nh = (float)(-0.5 * nrm + (double)with_rest);
-        const float nf = (k < K && nh > kSplitPadNorm) ? nh : kSplitPadNorm;
-        reinterpret_cast<float*>(sp.stage16 + (size_t)(k / kNodesPerStage) * sp.stage16_bytes +
-                                 (size_t)kNodesPerStage * sp.row_bytes)[k % kNodesPerStage] = nf;
-        if (sp.tail_r) {
-            // cut into three bf16 parts (exactly: 3 x 8 bits), which meet ones on the samples' side
-            const __bf16 p0 = (__bf16)nf;
-            const __bf16 p1 = (__bf16)(nf - (float)p0);
-            const __bf16 p2 = (__bf16)((nf - (float)p0) - (float)p1);
-            __bf16* cell = reinterpret_cast<__bf16*>(row + sp.kb_count * 64) + 3 * sp.tail_r;
-            cell[0] = p0;
-            cell[1] = p1;
-            cell[2] = p2;
+        const double nrm = lanes_sum((double)v * (double)v);
+        const float lo2 = lanes_sum(left * left);
+        wave_lds();
+        if (lane < 2 * sp.units) {
+            const int u = lane >> 1, g = lane & 1;               // the first lane half feeds first parts, the other one second parts
+            // (the order in which the tile's lanes come by a unit's values: its eights 0, 2, 1 and 3)
+            uint4* from = reinterpret_cast<uint4*>(&parts[wave][g][32 * u]);
+            struct {
+                uint4 e[4];
+            } eights = {{from[0], from[2], from[1], from[3]}};
+            const halfx32 x = __builtin_bit_cast(halfx32, eights);
+            const uintx16 pairs = __builtin_bit_cast(uintx16, eights);
+            halfx2 big[4] = {};
+#pragma unroll
+            for (int i = 0; i < 16; ++i) big[i & 3] = __builtin_elementwise_max(big[i & 3], __builtin_bit_cast(halfx2, (unsigned int)pairs[i] & 0x7fff7fffu));
+            big[0] = __builtin_elementwise_max(__builtin_elementwise_max(big[0], big[1]), __builtin_elementwise_max(big[2], big[3]));
+            const int e = fp6_scale(fmaxf((float)big[0][0], (float)big[0][1]));
+            const uintx6 p = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(x, power_of_two(e));
+            const halfx32 d = __builtin_amdgcn_cvt_scalef32_pk32_f16_fp6(p, power_of_two(e));
+            eights = __builtin_bit_cast(decltype(eights), d);
+            from[0] = eights.e[0];
+            from[2] = eights.e[1];
+            from[1] = eights.e[2];
+            from[3] = eights.e[3];
+            char* const to = row + 32 * sp.kb_count;
+            *reinterpret_cast<uint4*>(to + u * 32 + g * 16) = make_uint4(p[0], p[1], p[2], p[3]);
+            *reinterpret_cast<uint2*>(to + sp.units * 32 + u * 16 + g * 8) = make_uint2(p[4], p[5]);
+            reinterpret_cast<uint8_t*>(sp.stage16 + (size_t)(k / kNodesPerStage) * sp.stage16_bytes + (size_t)kNodesPerStage * (sp.row_bytes + 4))
+                [4 * (k % kNodesPerStage) + 2 * g + u] = (uint8_t)(127 + e);
         }
-        float up = (float)nrm;
-        if ((double)up < nrm) up = nextafterf(up, INFINITY);
-        most[wave][0] = k < K ? up : 0.0f;
-        most[wave][1] = lo2;
-        most[wave][2] = rest2;
+        wave_lds();
+        const float off_hi = real ? (float)hi - (float)parts[wave][0][slot] : 0.0f, off_lo = real ? left - (float)parts[wave][1][slot] : 0.0f;
+        const float off_hi2 = lanes_sum(off_hi * off_hi), off_lo2 = lanes_sum(off_lo * off_lo),
+                    with_rest = lanes_sum(v * (off_lo * back));
+        if (lane == 0) {
+            const double full = -0.5 * nrm + (double)with_rest;
+            const float nh = (float)full;
+            reinterpret_cast<float*>(sp.stage16 + (size_t)(k / kNodesPerStage) * sp.stage16_bytes +
+                                     (size_t)kNodesPerStage * sp.row_bytes)[k % kNodesPerStage] = (k < K && nh > kSplitPadNorm) ? nh : kSplitPadNorm;
+            // three parts (11 bits each) of the norm at 2^-kHalfNorm of its scale, which meet that factor on the samples' side, and what
+            // keeps padding rows below all others
+            const float at = (float)(full * (double)up * (double)up * (1.0 / (1 << kHalfNorm)));
+            const bool fits = !(fabsf(at) >= kHalfMost);             // (no number: its scores are none either)
+            _Float16* cell = reinterpret_cast<_Float16*>(row) + 4 * half_norm_group(D);
+            const _Float16 p0 = (_Float16)at, p1 = (_Float16)(at - (float)p0), p2 = (_Float16)((at - (float)p0) - (float)p1);
+            const _Float16 least = (_Float16)-kHalfMost;
+            cell[0] = k < K ? p0 : least;
+            cell[1] = k < K ? p1 : least;
+            cell[2] = k < K ? p2 : least;
+            cell[3] = k < K ? (_Float16)0.0f : least;
+            float most2 = (float)nrm;
+            if ((double)most2 < nrm) most2 = nextafterf(most2, INFINITY);
+            most[wave][0] = k < K ? most2 : 0.0f;
+            // (a node whose norm does not fit: every sample is decided by direct differences)
+            most[wave][1] = k < K && !fits ? INFINITY : sqrtf(lo2) * back;
+            most[wave][2] = sqrtf(off_hi2) * back;
+            most[wave][3] = sqrtf(off_lo2) * back;
+        }
+    } else {
+        const __bf16 hi = (__bf16)v;
+        const float left = v - (float)hi;
+        const __bf16 lo = (__bf16)left;
+        const float rest = left - (float)lo;
+        const double nrm = lanes_sum((double)v * (double)v);
+        const float lo2 = lanes_sum(left * left), rest2 = lanes_sum(rest * rest), with_rest = lanes_sum(v * rest);
+        if (real) {
+            const int tail0 = D - sp.tail_r;
+            if (lane < tail0) {
+                // slot group q = four features, its window [min(4 q, D - 4), + 4): own elements only, zeros in front of them
+                const int q = lane >> 2, start = 4 * q < D - 4 ? 4 * q : D - 4;
+                const int kb = q >> 2, g = (q >> 1) & 1, t = (q & 1) * 4 + lane - start;
+                __bf16* cell = reinterpret_cast<__bf16*>(row + kb * 64 + g * 32) + t;
+                cell[0] = hi;
+                cell[8] = lo;
+            } else {
+                __bf16* cell = reinterpret_cast<__bf16*>(row + sp.kb_count * 64) + (lane - tail0);
+                cell[0] = hi;
+                cell[sp.tail_r] = hi;
+                cell[2 * sp.tail_r] = lo;
+            }
+        }
+        if (lane == 0) {
+            const float nh = (float)(-0.5 * nrm + (double)with_rest);
+            const float nf = (k < K && nh > kSplitPadNorm) ? nh : kSplitPadNorm;
+            reinterpret_cast<float*>(sp.stage16 + (size_t)(k / kNodesPerStage) * sp.stage16_bytes +
+                                     (size_t)kNodesPerStage * sp.row_bytes)[k % kNodesPerStage] = nf;
+            if (sp.tail_r) {
+                // cut into three bf16 parts (exactly: 3 x 8 bits), which meet ones on the samples' side
+                const __bf16 p0 = (__bf16)nf;
+                const __bf16 p1 = (__bf16)(nf - (float)p0);
+                const __bf16 p2 = (__bf16)((nf - (float)p0) - (float)p1);
+                __bf16* cell = reinterpret_cast<__bf16*>(row + sp.kb_count * 64) + 3 * sp.tail_r;
+                cell[0] = p0;
+                cell[1] = p1;
+                cell[2] = p2;
+            }
+            float up = (float)nrm;
+            if ((double)up < nrm) up = nextafterf(up, INFINITY);
+            most[wave][0] = k < K ? up : 0.0f;
+            most[wave][1] = lo2;
+            most[wave][2] = rest2;
+            most[wave][3] = 0.0f;
+        }
     }
     __syncthreads();
     // sixteen rows of a stage are contiguous (kNodesPerStage is a multiple of sixteen)
@@ -362,11 +504,26 @@ __global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const f
     const int f = tid >> 4, q = tid & 15;
     if (f < D) wt[(size_t)f * kpad + k0 + q] = given[q][f];
     if (real) sp.wrow[(size_t)k * D + lane] = w;
-    if (tid < 3) {
+    if (tid < 4) {
         float m = most[0][tid];
         for (int u = 1; u < kPrepNodes; ++u) m = fmaxf(m, most[u][tid]);
         if (m > 0.0f) atomicMax(&tops[tid], __float_as_uint(m));
     }
+}
+
+__global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const float* __restrict__ W, int K, int D, int kpad,
+                                                                         float* __restrict__ centre, float* __restrict__ wt,
+                                                                         unsigned int* __restrict__ scal, unsigned int* __restrict__ tops,
+                                                                         double* __restrict__ qe, int32_t* __restrict__ small, const SplitPrep sp)
+{
+    split_prep<false>(W, K, D, kpad, centre, wt, scal, tops, qe, small, sp);
+}
+__global__ void __launch_bounds__(64 * kPrepNodes) bmu_split_prep_kernel(const float* __restrict__ W, int K, int D, int kpad,
+                                                                         float* __restrict__ centre, float* __restrict__ wt,
+                                                                         unsigned int* __restrict__ scal, unsigned int* __restrict__ tops,
+                                                                         double* __restrict__ qe, int32_t* __restrict__ small, const HalfPrep sp)
+{
+    split_prep<true>(W, K, D, kpad, centre, wt, scal, tops, qe, small, sp);
 }
 
 __global__ void fill_zero_kernel(uint32_t* p, size_t words)
@@ -829,15 +986,35 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
 // features, and no feature is counted twice.  A stage row is [kb][g][hi x 8 | lo x 8] bf16 plus 16 bytes of padding
 // (row stride 64 * blocks + 16 bytes: the 16-byte reads of sixteen consecutive rows fall into distinct banks), followed
 // by the stage's 128 half squared norms in float32.
+// Half-precision and fp6 parts (HALF; large calls of 21 to 64 features: half_parts_pay).  A value is cut into its half-precision part and what
+// that leaves over; a score takes the product of the first parts on v_mfma_f32_32x32x16_f16 and both cross products from fp6 copies of the parts
+// in one v_mfma_scale_f32_32x32x64_f8f6f4 for 32 features ([second | first] against [first | second], as in som_bmu_held.hip): 4 + 2
+// MFMAs a block at 50 features where two bf16 parts take 10.  The norms travel as three half-precision parts in the four places behind the
+// features, against a factor on the samples' side; the fourth keeps padding rows below all others.  A sample is scaled by the power of
+// two of its largest element, the weights by one that 64 of them give (kHalfBit leaves room for others), and each node's 32 features have
+// an fp6 scale of their own in LDS behind the norms.  The bound is about 2.2 times that of two bf16 parts (fp6 has four significant bits:
+// |first - fp6| |second| and its mirror image for each of the two scores compared), so about twice as many samples are listed.
+// 10^6 x 50: search on 1024 nodes 292 -> 242 us, on 4096 1070 -> 814; with the longer lists the epochs take 411 -> 378 and 1367 -> 1225 us.
+// What bounds it: the port that issues vector instructions and MFMAs (41 and 6 a block of 32 x 32, the matrix pipe busy 0.45 to 0.55 of the
+// time at 1.8 to 2.0 GHz).  Third and fourth fp6 products (what fp6 leaves of the first parts) would bring the bound back to that of bf16 for 7 or
+// 8 MFMAs a block: an estimated 7 % of the search for what the lists would give back; not built.
+// The fold takes a class's scores four at a time: two medians meet the runner-up in one v_max3 (10 vector instructions for four scores
+// until then, 9 now; 838 -> 814 us of search on 4096 nodes).
 // The fold keeps the position inside a block in the low four bits of the score (one and-or instead of a compare
 // and a select; 16 units of the last place are part of the bound), so padding nodes carry a large finite negative
 // norm here instead of -inf.
 // ---------------------------------------------------------------------------------------------------------
-// bytes of a stage row: kb whole 16-feature blocks of 64 bytes, 32 bytes for a packed tail block, 16 bytes of padding
-constexpr int split_row_bytes(int kb, bool tail = false) { return kb * 64 + (tail ? 32 : 0) + 16; }
-constexpr int split_stage_f4(int kb, bool tail = false)
+// bytes of a stage row.  bf16 parts: kb whole 16-feature blocks of 64 bytes, 32 bytes for a packed tail block, 16 bytes of padding.
+// Half-precision and fp6 parts: 32 bytes a 16-feature block, 48 bytes 32 features, an odd number of sixteens.
+constexpr int split_row_bytes(int kb, int form)
 {
-    return ((kNodesPerStage * split_row_bytes(kb, tail) + kNodesPerStage * 4) / 16 + kThreads - 1) / kThreads * kThreads;
+    return form_units(form) ? (kb * 32 + form_units(form) * 48) / 16 * 16 + ((kb * 2 + form_units(form) * 3) % 2 ? 0 : 16)
+                            : kb * 64 + (form == kFormTail ? 32 : 0) + 16;
+}
+// (behind the rows 128 norms, and with fp6 parts their scales: a byte for each half and unit)
+constexpr int split_stage_f4(int kb, int form)
+{
+    return ((kNodesPerStage * split_row_bytes(kb, form) + kNodesPerStage * (form_units(form) ? 8 : 4)) / 16 + kThreads - 1) / kThreads * kThreads;
 }
 constexpr int kSplitMinNodes = 1;              // SOM_SEARCH_AUTO: every map of more than this many nodes (measured faster than the
                                                // float32 search from 2 x 2 nodes and from D = 4 on)
@@ -855,14 +1032,14 @@ struct CandQueue {
     uint32_t* row;                   // [64] its row of X
     uint2* entry;                    // [kQueue]
 };
-constexpr int cand_queue(int kb, bool tail)            // entries; two workgroups fit a compute unit
+constexpr int cand_queue(int kb, int form)            // entries; two workgroups fit a compute unit
 {
-    const size_t left = (80 * 1024 - 2 * (size_t)split_stage_f4(kb, tail) * 16) / kWavesPerGroup - CandQueue::kFixed;
+    const size_t left = (80 * 1024 - 2 * (size_t)split_stage_f4(kb, form) * 16) / kWavesPerGroup - CandQueue::kFixed;
     return left / sizeof(uint2) < 512 ? (int)(left / sizeof(uint2)) / 16 * 16 : 512;
 }
-constexpr size_t cand_lds(int kb, bool tail)
+constexpr size_t cand_lds(int kb, int form)
 {
-    return 2 * (size_t)split_stage_f4(kb, tail) * 16 + kWavesPerGroup * (CandQueue::kFixed + (size_t)cand_queue(kb, tail) * sizeof(uint2));
+    return 2 * (size_t)split_stage_f4(kb, form) * 16 + kWavesPerGroup * (CandQueue::kFixed + (size_t)cand_queue(kb, form) * sizeof(uint2));
 }
 
 // first feature of slot group q (four consecutive features)
@@ -873,15 +1050,17 @@ __device__ __forceinline__ int split_window(int q, int D) { return 4 * q < D - 4
 // KB whole 16-feature blocks (three MFMAs each) and, with TAIL, one packed block for the last a.tail_r <= 4 features
 // (one MFMA; layout at bmu_split_prep_kernel).
 // first feature of lane half g's h-th window of k-block kb: only the last block of a row without a packed tail can be shifted
-template <int KB, bool TAIL>
+template <int KB, int FORM>
 __device__ __forceinline__ int split_start(int kb, int g, int h, int D)
 {
-    return TAIL || kb < KB - 1 ? 16 * kb + 8 * g + 4 * h : split_window(4 * kb + 2 * g + h, D);
+    return kb < KB - (form_units(FORM) ? 2 : 1) ? 16 * kb + 8 * g + 4 * h : split_window(4 * kb + 2 * g + h, D);
 }
 
 // A lane's part of the rows of MS sample blocks, as given.
-template <int KB, bool TAIL, int MS, bool CAND>
+template <int KB, int FORM, int MS, bool CAND>
 struct SplitRows {
+    static constexpr bool TAIL = FORM == kFormTail;
+    static constexpr int LOADED = form_units(FORM) && KB > 2 * form_units(FORM) ? KB - 1 : KB;      // (a last block that holds the norms only)
     float4 x[MS][KB > 0 ? KB : 1][2], t[MS];
 
     __device__ __forceinline__ void load(const BmuArgs& a, int64_t wave0, int64_t total, int j, int g)
@@ -893,10 +1072,62 @@ struct SplitRows {
             if constexpr (CAND) ii = (int64_t)a.recheck[ii];
             const float* xr = a.X + (a.idx ? (int64_t)a.idx[ii] : ii) * a.ldx;
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
+            for (int kb = 0; kb < LOADED; ++kb)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) x[mb][kb][h] = load4(xr + split_start<KB, TAIL>(kb, g, h, a.D));
+                for (int h = 0; h < 2; ++h) x[mb][kb][h] = load4(xr + split_start<KB, FORM>(kb, g, h, a.D));
             if constexpr (TAIL) t[mb] = load4(xr + a.D - 4);         // (inside the row: D >= 4)
+        }
+    }
+};
+
+// A lane's operands of a node block: whole blocks' first and second bf16 parts, the packed block and the norms; or half-precision parts, fp6 parts and
+// the scales of those.
+template <int KB, int FORM>
+struct SplitFragments {
+    static constexpr bool TAIL = FORM == kFormTail;
+    static constexpr int H = form_units(FORM), KBA = KB > 0 ? KB : 1;
+    bf16x8 wh[KBA], wl[KBA], wtl;
+    floatx16 c;
+    halfx8 half[KBA];
+    uintx6 q[H > 0 ? H : 1];
+    int scales;
+
+    __device__ __forceinline__ void read_half(int kb, const char* row) { half[kb] = *reinterpret_cast<const halfx8*>(row + 32 * kb); }
+    __device__ __forceinline__ void read_fp6(int u, const char* row, int g)
+    {
+        const uint4 t = *reinterpret_cast<const uint4*>(row + 32 * KB + 32 * u);
+        const uint2 r = *reinterpret_cast<const uint2*>(row + 32 * KB + 32 * H + 16 * u - 8 * g);         // (row carries g * 16)
+        q[u][0] = t.x;
+        q[u][1] = t.y;
+        q[u][2] = t.z;
+        q[u][3] = t.w;
+        q[u][4] = r.x;
+        q[u][5] = r.y;
+    }
+    __device__ __forceinline__ void first(const char* row, const char* tail, int g)
+    {
+        if constexpr (H > 0) {
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) read_half(kb, row);
+#pragma unroll
+            for (int u = 0; u < H; ++u) read_fp6(u, row, g);
+            scales = *reinterpret_cast<const uint16_t*>(tail);
+        } else {
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+                wh[kb] = *reinterpret_cast<const bf16x8*>(row + kb * 64);
+                wl[kb] = *reinterpret_cast<const bf16x8*>(row + kb * 64 + 16);
+            }
+            if constexpr (TAIL) wtl = *reinterpret_cast<const bf16x8*>(row + KB * 64 - g * 16);
+            const float4* nh = reinterpret_cast<const float4*>(tail);
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+                const float4 t = TAIL ? float4{0.f, 0.f, 0.f, 0.f} : nh[2 * n];
+                c[4 * n + 0] = t.x;
+                c[4 * n + 1] = t.y;
+                c[4 * n + 2] = t.z;
+                c[4 * n + 3] = t.w;
+            }
         }
     }
 };
@@ -915,12 +1146,15 @@ __device__ __forceinline__ void swap_halves(int& a, int& b)
     b = (int)r[1];
 }
 
-template <int KB, bool TAIL, int MS, bool CAND>
+template <int KB, int FORM, int MS, bool CAND>
 __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, int64_t tile_index, unsigned int count,
                                                float4* lds4)
 {
-    constexpr int RS = split_row_bytes(KB, TAIL);
-    constexpr int STAGE_F4 = split_stage_f4(KB, TAIL);
+    constexpr bool TAIL = FORM == kFormTail;
+    constexpr int H = form_units(FORM), HA = H > 0 ? H : 1;
+    constexpr bool HALF = H > 0;
+    constexpr int RS = split_row_bytes(KB, FORM);
+    constexpr int STAGE_F4 = split_stage_f4(KB, FORM);
     constexpr int KBA = KB > 0 ? KB : 1;               // array lengths (no zero-length arrays when D <= 4)
     constexpr int PRE = STAGE_F4 / kThreads;
     const char* ldsb = reinterpret_cast<const char*>(lds4);
@@ -942,11 +1176,11 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     float cut[MS];          // CAND
     unsigned int found[MS]; // CAND: hits of the block in hand
     const int64_t total = CAND ? (int64_t)count : a.m;
-    SplitRows<KB, TAIL, MS, CAND> raw;
+    SplitRows<KB, FORM, MS, CAND> raw;
     raw.load(a, wave0, total, j, g);
     // CAND: the wavefront's queue, its length (which may pass the end: those entries are lost, and lost remembers whose), and each
     // sample's row
-    constexpr int QUEUE = cand_queue(KB, TAIL);
+    constexpr int QUEUE = cand_queue(KB, FORM);
     CandQueue cq{};
     unsigned int queued = 0u, lost = 0u;
     if constexpr (CAND) {
@@ -964,6 +1198,136 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             if (g == 0) {
                 cq.row[mb * 32 + j] = a.idx ? a.idx[is] : is;
                 cq.nearest[mb * 32 + j] = ~0ull;
+            }
+        }
+    }
+    // HALF: the half-precision parts' fragments, the fp6 parts', and their scales (a byte for each unit)
+    halfx8 xf[MS][KBA];
+    uintx6 xq[MS][HA];
+    int xs[MS];
+    const int sw = HALF ? (int)a.scal[kScalShift] : 0;
+    if constexpr (HALF) {
+#pragma unroll
+        for (int mb = 0; mb < MS; ++mb) {
+            constexpr int LOADED = SplitRows<KB, FORM, MS, CAND>::LOADED;
+            float v[LOADED][8], most = 0.0f;
+#pragma unroll
+            for (int kb = 0; kb < LOADED; ++kb)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int at = 16 * kb + 8 * g + 4 * h, start = split_start<KB, FORM>(kb, g, h, a.D);
+                    const float4 cen = load4(a.centre + start), x4 = raw.x[mb][kb][h];
+                    float* to = &v[kb][4 * h];
+                    to[0] = x4.x - cen.x;
+                    to[1] = x4.y - cen.y;
+                    to[2] = x4.z - cen.z;
+                    to[3] = x4.w - cen.w;
+                    if (kb >= KB - 2) {            // (windows shifted back: own elements only)
+                        const int shift = at - start;
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) to[t] = shift <= t ? to[t] : 0.0f;
+                    }
+                    most = fmaxf(most, fmaxf(fmaxf(fabsf(to[0]), fabsf(to[1])), fmaxf(fabsf(to[2]), fabsf(to[3]))));
+                }
+            float other = most;
+            swap_halves(most, other);
+            most = fmaxf(most, other);
+            // The sample's scale: its largest element into [2^9, 2^10), unless that leaves what the norms' factor can hold (elements past what half
+            // precision holds make the bound infinite: such a sample goes to the all-nodes pass).
+            int sx = half_scale(most);
+            sx = sx < sw - kHalfRange ? sw - kHalfRange : sx > sw + 1 ? sw + 1 : sx;
+            const float s = power_of_two(sx), back = power_of_two(-sx);
+            // scales of the fp6 parts: second parts are at most a half unit of the largest element's first part (lanes 0 to 31 pack them)
+            const int eh = (int)(__float_as_uint(most * s) >> 23) - 129, eq = g == 0 ? eh - 12 : eh;
+            const int e = eq < -40 ? -40 : eq > 40 ? 40 : eq;
+            const float q_scale = power_of_two(e);
+            xs[mb] = (127 + e) * 0x101;
+            float v2 = 0.0f, e2 = 0.0f, after2 = 0.0f;
+#pragma unroll
+            for (int u = 0; u < H; ++u) {
+                unsigned int hi[8], lo[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const int kb = 2 * u + (t >> 2);
+                    hi[t] = lo[t] = 0u;
+                    if (kb < LOADED) {
+                        const HalfPair h(v[kb < LOADED ? kb : 0][2 * (t & 3)] * s, v[kb < LOADED ? kb : 0][2 * (t & 3) + 1] * s);
+                        hi[t] = h.hi;
+                        lo[t] = h.lo;
+                    }
+                }
+                xf[mb][2 * u] = __builtin_bit_cast(halfx8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+                if (2 * u + 1 < KB) xf[mb][2 * u + 1 < KB ? 2 * u + 1 : 0] = __builtin_bit_cast(halfx8, make_uint4(hi[4], hi[5], hi[6], hi[7]));
+                // the first lane half packs the second parts of all thirty-two features, the other half the first parts
+                uintx16 w;
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    unsigned int m = lo[t], n = hi[t];
+                    swap_words(m, n);
+                    w[t] = m;
+                    w[8 + t] = n;
+                }
+                const uintx6 q = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(__builtin_bit_cast(halfx32, w), q_scale);
+                xq[mb][u] = q;
+                if constexpr (!CAND) {
+                    const uintx16 d = __builtin_bit_cast(uintx16, __builtin_amdgcn_cvt_scalef32_pk32_f16_fp6(q, q_scale));
+                    float s2[2] = {0.0f, 0.0f};
+#pragma unroll
+                    for (int t = 0; t < 16; ++t) {
+                        const halfx2 o = __builtin_bit_cast(halfx2, (unsigned int)w[t]);
+                        const halfx2 r = o - __builtin_bit_cast(halfx2, (unsigned int)d[t]);
+                        s2[(t >> 2) & 1] = __builtin_amdgcn_fdot2(o, o, s2[(t >> 2) & 1], false);
+                        e2 = __builtin_amdgcn_fdot2(r, r, e2, false);
+                    }
+                    v2 += s2[0] + s2[1];
+                    const float after = (float)(KB - 2 * u);          // MFMAs of first parts from its own on
+                    after2 = fmaf(after * after, s2[0], fmaf((after - 1.0f) * (after - 1.0f), s2[1], after2));
+                }
+            }
+            if constexpr (KB > 2 * H) xf[mb][KB - 1] = __builtin_bit_cast(halfx8, make_uint4(0u, 0u, 0u, 0u));
+            {
+                // the norms' factor, 2^(kHalfNorm + sx - sw) three times, and 2^15 (padding rows)
+                const unsigned int f = (unsigned)(15 + kHalfNorm + sx - sw) << 10;
+                const int group = half_norm_group(a.D);
+                const uint4 w = __builtin_bit_cast(uint4, xf[mb][KB - 1]);
+                const bool here = ((group >> 1) & 1) == g, second = (group & 1) != 0;
+                const unsigned int f0 = here ? f | f << 16 : 0u, f1 = here ? f | 0x7800u << 16 : 0u;
+                xf[mb][KB - 1] = __builtin_bit_cast(halfx8, make_uint4(w.x | (second ? 0u : f0), w.y | (second ? 0u : f1), w.z | (second ? f0 : 0u),
+                                                                       w.w | (second ? f1 : 0u)));
+            }
+            if constexpr (CAND) {
+                cut[mb] = ldexpf(cut[mb], sx + sw);
+            } else {
+                // The error of a score.  (1) What the cuts drop: with x = xh + xl, ql and qh the fp6 copies of the parts, and w likewise, a score misses
+                // (xl - ql) . wh + ql . (wh - qh_w) + xh . (wl - ql_w) + (xh - qh) . ql_w + xl . wl.  Two scores are compared, so the first
+                // counts by wh_a - wh_b; of the third the preparation gives w . (wl - ql_w) back, which leaves (x - w) . (wl - ql_w) and
+                // xl . (wl - ql_w).  All norms are formed; the weights' are the largest over the nodes.  (A second part is rounded to half
+                // precision before it goes to fp6.)
+                // (2) The pipe's accumulation: an MFMA of first parts is charged sixteen units of its accumulator and products
+                // (any order of its additions), those of fp6 products sixty-four terms each; they go first and hold small numbers
+                // only.  Block kb of the first parts is in the accumulator of KB - kb MFMAs, the norm in that of the last.
+                // (3) Six units for the roundings of the two centrings and of -|w|^2 / 2, and what its third part can lose.
+                float h2 = v2, eh2 = e2, ha2 = after2;               // lower lanes: second parts; upper lanes: first parts
+                swap_halves(v2, h2);
+                swap_halves(e2, eh2);
+                swap_halves(after2, ha2);
+                auto root = [&](float x) { return __builtin_amdgcn_sqrtf(x + kSquaresFloor) * (1.001f * back); };
+                constexpr float unit = 5.9604645e-08f, small = 80.0f * (H + 2) * unit;
+                const float lo_w = __uint_as_float(a.norms[1]) * 1.001f, qh_w = __uint_as_float(a.norms[2]) * 1.001f, ql_w = __uint_as_float(a.norms[3]) * 1.001f;
+                const float nh = root(h2);
+                const float nl = root(v2) * 1.001f + nh * 1.0e-9f, nx = nh + nl;
+                const float nr = root(e2) + nl * 4.9e-4f + nx * 1.0e-9f, qh = root(eh2);
+                const float err_w = root(ha2) * (16.3f * unit) + nl * small + nx * (6.0f * unit);
+                const float back_w = power_of_two(-sw);
+                const float err_0 = 1.001f * (nr * lo_w + (nl + nr) * qh_w + nl * ql_w + qh * (lo_w + ql_w) + nl * lo_w) + nx * lo_w * small +
+                                    back_w * back_w * 1.0e-3f;
+                if (MS == 1 || mb == g) {
+                    stash[0] = nx;
+                    stash[kThreads] = err_w;
+                    stash[2 * kThreads] = nr * 1.001f;
+                    stash[3 * kThreads] = err_0;
+                    stash[4 * kThreads] = __int_as_float(-(sx + sw));
+                }
             }
         }
     }
@@ -1000,7 +1364,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         else choose(std::integral_constant<int, 4>{});
     }
 #pragma unroll
-    for (int mb = 0; mb < MS; ++mb) {
+    for (int mb = 0; mb < (HALF ? 0 : MS); ++mb) {
         // squares: of the first parts, the same weighted by how many of the large MFMAs follow (xa), of the second parts (lo2) and
         // of what both leave over (rest2)
         float hi2 = 0.0f, xa = 0.0f, lo2 = 0.0f, rest2 = 0.0f;
@@ -1038,7 +1402,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             float v[8];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const int q = 4 * kb + 2 * g + h, start = split_start<KB, TAIL>(kb, g, h, a.D);
+                const int q = 4 * kb + 2 * g + h, start = split_start<KB, FORM>(kb, g, h, a.D);
                 const float4 cen = load4(a.centre + start), x4 = raw.x[mb][kb][h];
                 v[4 * h + 0] = x4.x - cen.x;
                 v[4 * h + 1] = x4.y - cen.y;
@@ -1092,11 +1456,14 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             const float nx = nh + nl;
             constexpr float unit = 5.9604645e-08f;
             const float err_w = nl * (32.64f * KB * unit) + __builtin_amdgcn_sqrtf(xa + kSquaresFloor) * (1.0001f * 16.256f * unit) + nx * (6.0f * unit);
-            stash[(3 * mb + 0) * kThreads] = nx;
-            stash[(3 * mb + 1) * kThreads] = nl * lo_w * 1.0078125f + nr * rest_w * 1.0078125f + nx * lo_w * (32.64f * KB * unit);
-            // (two figures of sixteen bits, rounded up: LDS is full)
-            stash[(3 * mb + 2) * kThreads] =
-                __uint_as_float(((__float_as_uint(err_w) + 0xffffu) & 0xffff0000u) | ((__float_as_uint(nr * 1.0078125f) + 0xffffu) >> 16));
+            // (lane (j, g) finishes sample j of block g)
+            if (MS == 1 || mb == g) {
+                stash[0] = nx;
+                stash[kThreads] = nl * lo_w * 1.0078125f + nr * rest_w * 1.0078125f + nx * lo_w * (32.64f * KB * unit);
+                // (two figures of sixteen bits, rounded up: LDS is full)
+                stash[2 * kThreads] =
+                    __uint_as_float(((__float_as_uint(err_w) + 0xffffu) & 0xffff0000u) | ((__float_as_uint(nr * 1.0078125f) + 0xffffu) >> 16));
+            }
         }
     }
 
@@ -1120,12 +1487,14 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     }
     // one fold step: scores r, r + 2 of sample block mb of node block nb of stage st.  With v1, v2 the two scores (position
     // r / 2 + 8 (nb / 2) of the class in the stage in their low four bits), the largest of {best, second, v1, v2} is
-    // max3(best, v1, v2) and, because second <= best, the second largest is max(second, med3(best, v1, v2)): five vector
-    // instructions per two scores, plus two per stage and class for the stage number.  (The vector port is as busy as the
+    // max3(best, v1, v2) and, because second <= best, the second largest is max(second, med3(best, v1, v2)), the maximum with two steps'
+    // medians at once: nine vector instructions per four scores, plus two per stage and class for the stage number.  (The vector port is as busy as the
     // matrix pipe here: with the class's block number updated per block, two instructions more per block and class, the
     // kernel took 7 % longer.)
+    float mid0 = 0.0f;
     auto fold_step = [&](const floatx16 (&acc)[MS], int step, int st, int nb) {
-        const int mb = step >> 3, p = step & 1, r0 = 4 * ((step & 7) >> 1) + p, r1 = r0 + 2;
+        // (a class's two steps of four scores behind one another)
+        const int mb = step >> 3, p = (step >> 1) & 1, r0 = 4 * (2 * ((step & 7) >> 2) + (step & 1)) + p, r1 = r0 + 2;
         if constexpr (CAND) {
             // A bit per score that reaches the cut, two instructions each and no branch; what a block found is noted behind
             // its last step.  (A compare and a branch per score kept the fold from running beside the MFMAs: 2.2 ns an entry at
@@ -1153,7 +1522,8 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             const float v2 = __uint_as_float((__float_as_uint(acc[mb][r1]) & 0xfffffff0u) | (unsigned)(pos + (r1 >> 1)));
             const float mid = __builtin_amdgcn_fmed3f(best[mb][c], v1, v2);
             best[mb][c] = vmax3(best[mb][c], v1, v2);
-            second[mb][c] = vmax(second[mb][c], mid);
+            if ((step & 1) == 0) mid0 = mid;
+            else second[mb][c] = vmax3(second[mb][c], mid0, mid);
             if (nb >= 2 && r1 >= 14) tsel[mb][c] = (best[mb][c] > before[mb][c]) ? st : tsel[mb][c];
         }
     };
@@ -1176,11 +1546,45 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
 #pragma unroll
         for (int r = 0; r < 16; ++r) accB[mb][r] = kSplitPadNorm;
 
-    constexpr int GROUPS = 3 * KB + (TAIL ? 1 : 0);   // groups of MS MFMAs per node block
+    constexpr int GROUPS = HALF ? H + KB : 3 * KB + (TAIL ? 1 : 0);   // groups of MS MFMAs per node block
     const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     constexpr int STEPS_ALL = 8 * MS;          // fold steps (two scores each) per node block
-    auto block = [&](floatx16 (&cur)[MS], const floatx16 (&prev)[MS], bf16x8 (&wh)[KBA], bf16x8 (&wl)[KBA], bf16x8& wtl,
-                     floatx16& c, const char* wnext, const float4* nhnext, bool more, int prev_st, int prev_nb) {
+    auto block = [&](floatx16 (&cur)[MS], const floatx16 (&prev)[MS], SplitFragments<KB, FORM>& f, const char* wnext, const char* tnext, bool more,
+                     int prev_st, int prev_nb) {
+        if constexpr (HALF) {
+            // the small products first, into accumulators that hold nothing else
+#pragma unroll
+            for (int grp = 0; grp < GROUPS; ++grp) {
+#pragma unroll
+                for (int mb = 0; mb < MS; ++mb) {
+                    if (grp == 0)
+                        cur[mb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp6_operand(f.q[0]), fp6_operand(xq[mb][0]), zero16, 2, 2, 0, f.scales, 0, xs[mb]);
+                    else if (grp < H)
+                        cur[mb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp6_operand(f.q[HA - 1]), fp6_operand(xq[mb][HA - 1]), cur[mb], 2, 2, 1,
+                                                                                  f.scales, 1, xs[mb]);
+                    else
+                        cur[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.half[grp - H < 0 ? 0 : grp - H], xf[mb][grp - H < 0 ? 0 : grp - H], cur[mb], 0, 0, 0);
+                    const int m = grp * MS + mb;
+                    const int s0 = m * STEPS_ALL / (GROUPS * MS), s1 = (m + 1) * STEPS_ALL / (GROUPS * MS);
+#pragma unroll
+                    for (int sidx = s0; sidx < s1; ++sidx) fold_step(prev, sidx, prev_st, prev_nb);
+                    if (mb + 1 < MS) __builtin_amdgcn_sched_barrier(0);
+                }
+                // LDS reads of the next block, into the registers this group has just finished with
+                if (more) {
+                    if (grp < H) f.read_fp6(grp, wnext, g);
+                    else f.read_half(grp - H, wnext);
+                    if (grp == H - 1) f.scales = *reinterpret_cast<const uint16_t*>(tnext);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            return;
+        }
+        bf16x8(&wh)[KBA] = f.wh;
+        bf16x8(&wl)[KBA] = f.wl;
+        bf16x8& wtl = f.wtl;
+        floatx16& c = f.c;
+        const float4* nhnext = reinterpret_cast<const float4*>(tnext);
         // the norms of the next block replace c once the block's first group has read it
         auto next_norms = [&]() {
             if constexpr (TAIL) return;      // the norms travel inside the packed block
@@ -1253,7 +1657,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                 if (bits != 0u) {
                     const int bit = 31 - __builtin_clz(bits);          // 15 - place in the order of the steps
                     bits ^= 1u << bit;
-                    const int place = 15 - bit, r = 4 * (place >> 2) + ((place >> 1) & 1) + 2 * (place & 1);
+                    const int place = 15 - bit, r = 8 * (place >> 3) + 4 * ((place >> 1) & 1) + ((place >> 2) & 1) + 2 * (place & 1);
                     const unsigned int id = (unsigned)node_of_row((int)(base + 8 * (r >> 2) + (r & 3)), a.K);
                     if (id < (unsigned)a.K) {
                         const float* wr = a.W + (size_t)id * D;
@@ -1285,26 +1689,13 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     };
 
     // The first node block's operands; every later block's are read while the block before it is on the matrix pipe.
-    bf16x8 wh[KBA], wl[KBA], wtl;
-    floatx16 c;
-    {
-        const char* wrow = ldsb + j * RS + g * 32;
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-            wh[kb] = *reinterpret_cast<const bf16x8*>(wrow + kb * 64);
-            wl[kb] = *reinterpret_cast<const bf16x8*>(wrow + kb * 64 + 16);
-        }
-        if constexpr (TAIL) wtl = *reinterpret_cast<const bf16x8*>(wrow + KB * 64 - g * 16);
-        const float4* nh = reinterpret_cast<const float4*>(ldsb + kNodesPerStage * RS) + g;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 t = TAIL ? float4{0.f, 0.f, 0.f, 0.f} : nh[2 * q];
-            c[4 * q + 0] = t.x;
-            c[4 * q + 1] = t.y;
-            c[4 * q + 2] = t.z;
-            c[4 * q + 3] = t.w;
-        }
-    }
+    // a lane's row of a node block, and its part of what stands behind the rows: norms, or scales
+    auto rows_of = [&](const char* base, int nb) { return base + (nb * 32 + j) * RS + g * (HALF ? 16 : 32); };
+    auto tail_of = [&](const char* base, int nb) {
+        return HALF ? base + kNodesPerStage * (RS + 4) + (nb * 32 + j) * 4 + g * 2 : base + kNodesPerStage * RS + nb * 32 * 4 + g * 16;
+    };
+    SplitFragments<KB, FORM> f;
+    f.first(rows_of(ldsb, 0), tail_of(ldsb, 0), g);
     // One stage: the next stage travels global -> registers at the start and registers -> the idle LDS buffer after
     // the second block; the stage's only barrier stands in front of its last block, whose spare LDS slots then read
     // the first block of the next stage.  (With the barrier at the end of the stage a wavefront stood still for an
@@ -1339,17 +1730,13 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         __builtin_amdgcn_sched_barrier(0);
         const char* wbuf = ldsb + (size_t)buf * STAGE_F4 * 16;
         const char* obuf = ldsb + (size_t)(buf ^ 1) * STAGE_F4 * 16;
-        auto rows_of = [&](const char* base, int nb) { return base + (nb * 32 + j) * RS + g * 32; };
-        auto norms_of = [&](const char* base, int nb) {
-            return reinterpret_cast<const float4*>(base + kNodesPerStage * RS + nb * 32 * 4) + g;
-        };
-        block(accA, accB, wh, wl, wtl, c, rows_of(wbuf, 1), norms_of(wbuf, 1), true, st - 1, 3);
+        block(accA, accB, f, rows_of(wbuf, 1), tail_of(wbuf, 1), true, st - 1, 3);
         if constexpr (FIRST < PRE) {
             SOM_PRE_ALL(SOM_PRE_STORE)
             SOM_PRE_ALL(SOM_PRE_LOAD2)
             __builtin_amdgcn_sched_barrier(0);
         }
-        block(accB, accA, wh, wl, wtl, c, rows_of(wbuf, 2), norms_of(wbuf, 2), true, st, 0);
+        block(accB, accA, f, rows_of(wbuf, 2), tail_of(wbuf, 2), true, st, 0);
         if constexpr (FIRST < PRE) {
             SOM_PRE_ALL(SOM_PRE_STORE2)
         } else {
@@ -1361,9 +1748,9 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
 #undef SOM_PRE_STORE2
 #undef SOM_PRE_ALL
         __builtin_amdgcn_sched_barrier(0);
-        block(accA, accB, wh, wl, wtl, c, rows_of(wbuf, 3), norms_of(wbuf, 3), true, st, 1);
+        block(accA, accB, f, rows_of(wbuf, 3), tail_of(wbuf, 3), true, st, 1);
         __syncthreads();
-        block(accB, accA, wh, wl, wtl, c, rows_of(obuf, 0), norms_of(obuf, 0), true, st, 2);
+        block(accB, accA, f, rows_of(obuf, 0), tail_of(obuf, 0), true, st, 2);
         if constexpr (CAND) {
             if (queued > (unsigned)QUEUE / 2) serve();
         }
@@ -1387,17 +1774,15 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     } else {
         const int st = nstages - 1;
         const char* wbuf = ldsb + (size_t)(st & 1) * STAGE_F4 * 16;
-        auto rows_of = [&](int nb) { return wbuf + (nb * 32 + j) * RS + g * 32; };
-        auto norms_of = [&](int nb) { return reinterpret_cast<const float4*>(wbuf + kNodesPerStage * RS + nb * 32 * 4) + g; };
-        block(accA, accB, wh, wl, wtl, c, rows_of(1), norms_of(1), true, st - 1, 3);
+        block(accA, accB, f, rows_of(wbuf, 1), tail_of(wbuf, 1), true, st - 1, 3);
         if (live_last == 1) {
             fold_last(accA, std::integral_constant<int, 0>{});
         } else {
-            block(accB, accA, wh, wl, wtl, c, rows_of(2), norms_of(2), true, st, 0);
+            block(accB, accA, f, rows_of(wbuf, 2), tail_of(wbuf, 2), true, st, 0);
             if (live_last == 2) {
                 fold_last(accB, std::integral_constant<int, 1>{});
             } else {
-                block(accA, accB, wh, wl, wtl, c, nullptr, nullptr, false, st, 1);
+                block(accA, accB, f, nullptr, nullptr, false, st, 1);
                 fold_last(accA, std::integral_constant<int, 2>{});
             }
         }
@@ -1422,7 +1807,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     const float wmax2 = __uint_as_float(a.norms[0]);
     const float wmax = sqrtf(wmax2) * 1.000001f;
     // |w|^2 / 2 in the accumulators: see (2) at the start of the tile; and six units as for the products
-    constexpr float kErrNorm = ((TAIL ? 16.256f : 48.768f * KB) + 6.0f) * 5.9604645e-08f;
+    constexpr float kErrNorm = ((TAIL || HALF ? 16.256f : 48.768f * KB) + 6.0f) * 5.9604645e-08f;
     // (square roots here are the hardware's, good to a unit in the last place; the factors behind them cover it)
     auto root = [](float v) { return __builtin_amdgcn_sqrtf(v); };
     // Lane (j, g) finishes sample j of block g (MS = 1: half 0 does): the halves trade what they hold of each other's block, and
@@ -1444,6 +1829,12 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         float m1 = fmaxf(fmaxf(second[MS - 1][0], second[MS - 1][1]), fmaxf(second[MS - 1][2], second[MS - 1][3]));
         swap_halves(m0, m1);
         most = fmaxf(m0, m1);
+    }
+    if constexpr (HALF) {                          // (a power of two: the position bits stay as they are)
+        const int down = __float_as_int(stash[4 * kThreads]);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) won[q] = ldexpf(won[q], down);
+        most = ldexpf(most, down);
     }
     // winner and runner-up (equal scores are a near tie, decided elsewhere: any of them)
     float r_best = won[0], r_second = -INFINITY;
@@ -1470,25 +1861,33 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     r_row = (r_row >= 0 && r_row < a.K) ? r_row : a.K - 1;               // (only padding or non-finite scores get here)
     const int64_t i = wave0 + (MS > 1 ? lane : j);
     const bool r_valid = i < a.m && (MS > 1 || g == 0);
-    // the sample's figures from the start of the tile, and the winner's squared norm from the stage blob
-    const int own = MS > 1 ? g : 0;
-    const float nx = stash[(3 * own + 0) * kThreads], err_0 = stash[(3 * own + 1) * kThreads];
-    const unsigned int two = __float_as_uint(stash[(3 * own + 2) * kThreads]);
-    const float err_w = __uint_as_float(two & 0xffff0000u), nr = __uint_as_float(two << 16);
-    const float rest_w = root(__uint_as_float(a.norms[2]) + kSquaresFloor) * 1.0079f;
+    // the winner's squared norm from the stage blob, and the sample's figures from the start of the tile
     const char* blob = reinterpret_cast<const char*>(a.stage16) + (size_t)(r_row / kNodesPerStage) * STAGE_F4 * 16;
     const float wn = -2.0f * reinterpret_cast<const float*>(blob + (size_t)kNodesPerStage * RS)[r_row % kNodesPerStage];
     // The winner's score errs by its own norm's bound, which bounds its distance (far).  A node that is in truth as near as the winner
     // lies within that distance of the sample, so its norm is at most |x| + far (and at most the largest), and it lies within 2 far of the
     // winner; no other node can spoil the decision.  The position bits change a score by at most 2^-19 of itself, and a rival's
     // score is within the bound of the best one.
-    const float wb = fminf(root(wn) * 1.0001f, wmax);
-    const float err_b = (err_w + nr) * wb + err_0 + (nx + wb) * rest_w + 0.5f * kErrNorm * wb * wb;
+    const float nx = stash[0], wb = fminf(root(wn) * 1.0001f, wmax);
     const float bits = fabsf(r_best) * (1.01f * 3.8146973e-06f);
-    const float far2 = fmaxf(nx * nx * 1.00001f - 2.0f * r_best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
-    const float far = root(far2) * 1.0001f;
-    const float wo = fminf((nx + far) * 1.0001f, wmax);
-    const float bound = err_w * (wb + wo) + 2.0f * err_0 + nr * fminf(2.0f * far, wb + wo) + 2.0f * far * rest_w + 0.5f * kErrNorm * (wb * wb + wo * wo) + bits;
+    float bound;
+    if constexpr (HALF) {
+        const float err_w = stash[kThreads], nr = stash[2 * kThreads], err_0 = stash[3 * kThreads], rest_w = __uint_as_float(a.norms[3]) * 1.001f;
+        const float err_b = (err_w + nr) * wb + err_0 + (nx + wb) * rest_w + 0.5f * kErrNorm * wb * wb;
+        const float far = root(fmaxf(nx * nx * 1.00001f - 2.0f * r_best, 0.0f) * 1.00001f + 2.0f * (err_b + bits)) * 1.0001f;
+        const float wo = fminf((nx + far) * 1.0001f, wmax);
+        bound = err_w * (wb + wo) + 2.0f * (err_0 + far * rest_w) + nr * fminf(2.0f * far, wb + wo) + 0.5f * kErrNorm * (wb * wb + wo * wo) + bits;
+    } else {
+        const float err_0 = stash[kThreads];
+        const unsigned int two = __float_as_uint(stash[2 * kThreads]);
+        const float err_w = __uint_as_float(two & 0xffff0000u), nr = __uint_as_float(two << 16);
+        const float rest_w = root(__uint_as_float(a.norms[2]) + kSquaresFloor) * 1.0079f;
+        const float err_b = (err_w + nr) * wb + err_0 + (nx + wb) * rest_w + 0.5f * kErrNorm * wb * wb;
+        const float far2 = fmaxf(nx * nx * 1.00001f - 2.0f * r_best, 0.0f) * 1.00001f + 2.0f * (err_b + bits);
+        const float far = root(far2) * 1.0001f;
+        const float wo = fminf((nx + far) * 1.0001f, wmax);
+        bound = err_w * (wb + wo) + 2.0f * err_0 + nr * fminf(2.0f * far, wb + wo) + 2.0f * far * rest_w + 0.5f * kErrNorm * (wb * wb + wo * wo) + bits;
+    }
     const bool close = r_valid && a.K > 1 && !((r_best - r_second) > bound);
     // Candidates: the class winners that reach the cut, four at most on small maps; complete when no class's runner-up reaches it.
     // Otherwise (or with 16-bit ids not enough) the sample goes on the list of the candidate pass.
@@ -1517,8 +1916,9 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             // The statistic n_recheck counts the near ties: best two scores inside a band of fixed relative width, which takes 3 * 2^-18
             // for the cut (four times less than it can lose: a figure to compare runs by, not a bound) and all MFMAs at the full
             // magnitude.  Only those that this sample's own bound leaves open are listed.
-            constexpr float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(49 * KB + (TAIL ? 17 : 0) + 1) * 5.9604645e-08f + 1.9073486e-06f) +
-                                  12.0f * 5.9604645e-08f;
+            // (the MFMAs of two bf16 parts: three a 16-feature block, one for a remainder of up to four features)
+            const int left = a.D % 16, mfmas = left >= 1 && left <= 4 ? 49 * (a.D / 16) + 17 : 49 * ((a.D + 15) / 16);
+            const float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(mfmas + 1) * 5.9604645e-08f + 1.9073486e-06f) + 12.0f * 5.9604645e-08f;
             const float band = 0.5f * rel * ((nx * wb + 0.5f * wb * wb) + (nx * wmax + 0.5f * wmax2));
             near = (close || (a.K > 1 && !((r_best - r_second) > band))) ? 1 : 0;
         }
@@ -1529,21 +1929,21 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
 }
 
 // full tiles for the workgroups below a.full_tiles, half tiles for the last partial round (as bmu_kernel)
-template <int KB, bool TAIL, int MS>
+template <int KB, int FORM, int MS>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) bmu_split_kernel(const BmuArgs a)
 {
     extern __shared__ float4 lds4[];
     if ((int64_t)blockIdx.x < a.full_tiles) {
-        bmu_split_tile<KB, TAIL, MS, false>(a, 0, blockIdx.x, 0u, lds4);
+        bmu_split_tile<KB, FORM, MS, false>(a, 0, blockIdx.x, 0u, lds4);
     } else if constexpr (MS > 1) {
         constexpr int64_t per_full = (int64_t)kWavesPerGroup * MS * 32;
-        bmu_split_tile<KB, TAIL, MS / 2, false>(a, a.full_tiles * per_full, (int64_t)blockIdx.x - a.full_tiles, 0u, lds4);
+        bmu_split_tile<KB, FORM, MS / 2, false>(a, a.full_tiles * per_full, (int64_t)blockIdx.x - a.full_tiles, 0u, lds4);
     }
 }
 
 // candidate pass of the split search: a fixed grid walks the tiles of the list.  Whole rounds of two tiles per compute unit,
 // and what is left (a short list: everything) in tiles of half the size: a list of 1032 tiles took three rounds for two.
-template <int KB, bool TAIL, int MS>
+template <int KB, int FORM, int MS>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) bmu_split_cand_kernel(const BmuArgs a)
 {
     extern __shared__ float4 lds4[];
@@ -1557,8 +1957,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
     for (unsigned int t = blockIdx.x; t < full + halves; t += gridDim.x) {
         BmuArgs b = a;                     // (nothing derived from these is carried from tile to tile: registers)
         asm volatile("" : "+s"(b.centre), "+s"(b.D), "+s"(b.tail_r), "+s"(b.K));
-        if (t < full) bmu_split_tile<KB, TAIL, MS, true>(b, 0, t, count, lds4);
-        else bmu_split_tile<KB, TAIL, MS / 2, true>(b, (int64_t)full * per_tile, t - full, count, lds4);
+        if (t < full) bmu_split_tile<KB, FORM, MS, true>(b, 0, t, count, lds4);
+        else bmu_split_tile<KB, FORM, MS / 2, true>(b, (int64_t)full * per_tile, t - full, count, lds4);
         // The next tile starts by filling buffer 0, and a tile's last stage, where it is a partial one, is read behind the tile's
         // last barrier: from buffer 0 with an odd number of stages.  (A wavefront there may be far behind the others: it may have
         // had its queue to serve.)
@@ -2177,7 +2577,7 @@ __global__ void __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per
         a.scal[27 - a.slot] = 0u;
         a.scal[9 - a.slot2] = 0u;
     }
-    if (PAIRS && a.tops && blockIdx.x == 0 && tid < 3) {   // the search has read its maxima: kept for later passes, zero again for the next preparation
+    if (PAIRS && a.tops && blockIdx.x == 0 && tid < 4) {   // the search has read its maxima: kept for later passes, zero again for the next preparation
         a.tops[4 + tid] = a.tops[tid];
         a.tops[tid] = 0u;
     }
@@ -2447,6 +2847,20 @@ int launch_fill_zero(som_ctx* ctx, void* p, size_t bytes)
     return check_hip(ctx, hipGetLastError(), "fill_zero launch");
 }
 
+// Whether a search for up to 64 features takes half-precision and fp6 parts, or two bf16 parts.  The former need `fewer` MFMAs less for a block
+// of 32 nodes, but their samples cost more to cut (10 to 13 us for 10^6 rows), their preparation 2 us more, and their wider bound lists about
+// twice as many samples, up to 10 us even where those are few.  Whole searches, two bf16 parts and these: on 400 nodes, 10^6 x 25 120 us
+// and 121, 10^6 x 50 166 and 161; on 256 nodes 10^6 x 25 89 and 96, 10^6 x 56 144 and 135; on 1024 nodes 120,000 x 50 66 and 68, 250,000 x 56
+// 117 and 103, 10^6 x 25 233 and 200, 10^6 x 50 343 and 317, 10^6 x 64 398 and 331; 500,000 x 50 on 2500 395 and 361.  Up to 20 features
+// they save one MFMA or none and lose on every map (10^6 x 16 on 1024 nodes 168 and 180, 10^6 x 20 on 400 108 and 122).
+static bool half_parts_pay(int32_t K, int32_t D, int64_t rows)
+{
+    if (D <= 20) return false;
+    const int left = D % 16, two_parts = left >= 1 && left <= 4 ? 3 * (D / 16) + 1 : 3 * ((D + 15) / 16);
+    const int64_t fewer = (int64_t)((K + 31) / 32) * (two_parts - (D + 31) / 32 - (half_norm_group(D) / 4 + 1));
+    return fewer >= 40 && rows * fewer >= 40000000;
+}
+
 int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, int64_t rows, BmuPrep* out, double* qe, int32_t* small)
 {
     int steps, nch;
@@ -2478,12 +2892,14 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, int64_t rows
     const size_t centre_bytes = ((centre_floats > (size_t)D ? centre_floats : (size_t)D) * sizeof(float) + 255) / 256 * 256;
     // rows for the bf16 matrix pipe where the split search applies
     const bool split = D >= 4 && K > kSplitMinNodes && ctx->search != SOM_SEARCH_FLOAT32;
-    // D <= 64: whole 16-feature blocks, and a remainder of one to four features goes into one packed block (one MFMA
-    // instead of three for a block that would be mostly padding); larger remainders get a block of their own
-    const int tail_r = (split && nch == 1 && D % 16 >= 1 && D % 16 <= 4) ? D % 16 : 0;
-    const int kb = !split || nch > 1 ? 0 : (tail_r ? D / 16 : (D + 15) / 16);
+    // D <= 64: half-precision and fp6 parts, the norms in four places behind the features; narrow rows two bf16 parts
+    const bool half = split && nch == 1 && half_parts_pay(K, D, rows);
+    const int units = half ? (D + 31) / 32 : 0, tail_r = split && nch == 1 && !half && D % 16 >= 1 && D % 16 <= 4 ? D % 16 : 0;
+    const int kb = !split || nch > 1 ? 0 : half ? half_norm_group(D) / 4 + 1 : tail_r ? D / 16 : (D + 15) / 16;
+    const int form = units ? kFormHalf1 + units - 1 : tail_r ? kFormTail : kFormWhole;
+    if (!wide_split) out->form = form;
     // (D > 64: rows in the order of the form that the call takes)
-    const size_t stage16_one = (split && nch == 1) ? (size_t)split_stage_f4(kb, tail_r > 0) * 16 : 0;
+    const size_t stage16_one = (split && nch == 1) ? (size_t)split_stage_f4(kb, form) * 16 : 0;
     const size_t stage16_bytes = !split ? 0 : nch == 1 ? (size_t)(kpad / kNodesPerStage) * stage16_one : bmu_wide_blob_bytes(out->form, K, D, kpad);
     const size_t wrow_bytes = (split && nch == 1) ? (size_t)K * D * sizeof(float) : 0;
     const size_t need = stage_bytes + wt_bytes + centre_bytes + stage16_bytes + wrow_bytes + 256;
@@ -2521,15 +2937,22 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, int64_t rows
         if (!ctx->prep_clean)
             if (int rc = launch_fill_zero(ctx, out->tops, 64)) return rc;
         ctx->prep_clean = false;
-        SplitPrep sp{};
+        HalfPrep sp{};
         sp.stage16 = (char*)out->stage16;
         sp.wrow = out->wrow;
         sp.kb_count = kb;
         sp.tail_r = tail_r;
-        sp.row_bytes = split_row_bytes(kb, tail_r > 0);
+        sp.units = units;
+        sp.row_bytes = split_row_bytes(kb, form);
         sp.stage16_bytes = (int)stage16_one;
-        hipLaunchKernelGGL(bmu_split_prep_kernel, dim3((unsigned)(kpad / kPrepNodes)), dim3(64 * kPrepNodes), 0, ctx->stream, W, K, D, kpad,
-                           out->centre, out->wt, out->scal, out->tops, qe, small, sp);
+        const dim3 grid((unsigned)(kpad / kPrepNodes)), block(64 * kPrepNodes);
+        if (half) {
+            void (*kernel)(const float*, int, int, int, float*, float*, unsigned int*, unsigned int*, double*, int32_t*, const HalfPrep) = bmu_split_prep_kernel;
+            hipLaunchKernelGGL(kernel, grid, block, 0, ctx->stream, W, K, D, kpad, out->centre, out->wt, out->scal, out->tops, qe, small, sp);
+        } else {
+            void (*kernel)(const float*, int, int, int, float*, float*, unsigned int*, unsigned int*, double*, int32_t*, const SplitPrep) = bmu_split_prep_kernel;
+            hipLaunchKernelGGL(kernel, grid, block, 0, ctx->stream, W, K, D, kpad, out->centre, out->wt, out->scal, out->tops, qe, small, (const SplitPrep&)sp);
+        }
         return check_hip(ctx, hipGetLastError(), "bmu (split) preparation launch");
     }
     hipLaunchKernelGGL(bmu_centre_kernel, dim3((unsigned)(centre_bytes / 256)), dim3(1024), 0, ctx->stream, W, K, D,
@@ -2667,14 +3090,14 @@ static int launch_bmu(som_ctx* ctx, const BmuArgs& a)
     return check_hip(ctx, hipGetLastError(), "bmu kernel launch");
 }
 
-template <int KB, bool TAIL, int MS>
+template <int KB, int FORM, int MS>
 static int launch_bmu_split(som_ctx* ctx, const BmuArgs& a)
 {
-    constexpr size_t lds_bytes = 2 * (size_t)split_stage_f4(KB, TAIL) * 16 + 3 * MS * kThreads * sizeof(float);
+    constexpr size_t lds_bytes = 2 * (size_t)split_stage_f4(KB, FORM) * 16 + 5 * kThreads * sizeof(float);
     static_assert(lds_bytes + 512 <= 80 * 1024, "two workgroups per compute unit");
     static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
     bool& attr_set = attr_set_dev[ctx->device];
-    auto kern = bmu_split_kernel<KB, TAIL, MS>;
+    auto kern = bmu_split_kernel<KB, FORM, MS>;
     if (!attr_set) {
         if (int rc = check_hip(ctx,
                                hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -2699,14 +3122,14 @@ static int launch_bmu_split(som_ctx* ctx, const BmuArgs& a)
     return check_hip(ctx, hipGetLastError(), "bmu split kernel launch");
 }
 
-template <int KB, bool TAIL, int MS>
+template <int KB, int FORM, int MS>
 static int launch_bmu_split_cand(som_ctx* ctx, const BmuArgs& a)
 {
-    constexpr size_t lds_bytes = cand_lds(KB, TAIL);
+    constexpr size_t lds_bytes = cand_lds(KB, FORM);
     static_assert(lds_bytes <= 80 * 1024, "two workgroups per compute unit");
     static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
     bool& attr_set = attr_set_dev[ctx->device];
-    auto kern = bmu_split_cand_kernel<KB, TAIL, MS>;
+    auto kern = bmu_split_cand_kernel<KB, FORM, MS>;
     if (!attr_set) {
         if (int rc = check_hip(ctx,
                                hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -2720,34 +3143,37 @@ static int launch_bmu_split_cand(som_ctx* ctx, const BmuArgs& a)
     return check_hip(ctx, hipGetLastError(), "bmu split candidate kernel launch");
 }
 
-static int dispatch_bmu_split_cand(som_ctx* ctx, int kb, bool tail, const BmuArgs& a)
+// calls launch with the (blocks, form) of a row as types
+template <typename F>
+static int dispatch_split(som_ctx* ctx, int kb, int form, F&& launch)
 {
-    switch (kb * 2 + (tail ? 1 : 0)) {
-    case 1: return launch_bmu_split_cand<0, true, kSplitMS>(ctx, a);
-    case 2: return launch_bmu_split_cand<1, false, kSplitMS>(ctx, a);
-    case 3: return launch_bmu_split_cand<1, true, kSplitMS>(ctx, a);
-    case 4: return launch_bmu_split_cand<2, false, kSplitMS>(ctx, a);
-    case 5: return launch_bmu_split_cand<2, true, kSplitMS>(ctx, a);
-    case 6: return launch_bmu_split_cand<3, false, kSplitMS>(ctx, a);
-    case 7: return launch_bmu_split_cand<3, true, kSplitMS>(ctx, a);
-    case 8: return launch_bmu_split_cand<4, false, kSplitMS>(ctx, a);
-    }
-    return fail(ctx, SOM_EINVAL, "no split candidate kernel for %d blocks%s", kb, tail ? " and a tail" : "");
+#define SOM_SPLIT_CASE(KB, FORM) \
+    if (kb == KB && form == FORM) return launch(std::integral_constant<int, KB>{}, std::integral_constant<int, FORM>{});
+    SOM_SPLIT_CASE(0, kFormTail)
+    SOM_SPLIT_CASE(1, kFormWhole)
+    SOM_SPLIT_CASE(1, kFormTail)
+    SOM_SPLIT_CASE(2, kFormWhole)
+    SOM_SPLIT_CASE(2, kFormTail)
+    SOM_SPLIT_CASE(3, kFormWhole)
+    SOM_SPLIT_CASE(3, kFormTail)
+    SOM_SPLIT_CASE(4, kFormWhole)
+    SOM_SPLIT_CASE(2, kFormHalf1)
+    SOM_SPLIT_CASE(3, kFormHalf1)
+    SOM_SPLIT_CASE(3, kFormHalf2)
+    SOM_SPLIT_CASE(4, kFormHalf2)
+    SOM_SPLIT_CASE(5, kFormHalf2)
+#undef SOM_SPLIT_CASE
+    return fail(ctx, SOM_EINVAL, "no split BMU kernel for %d blocks of form %d", kb, form);
 }
 
-static int dispatch_bmu_split(som_ctx* ctx, int kb, bool tail, const BmuArgs& a)
+static int dispatch_bmu_split(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a)
 {
-    switch (kb * 2 + (tail ? 1 : 0)) {
-    case 1: return launch_bmu_split<0, true, kSplitMS>(ctx, a);
-    case 2: return launch_bmu_split<1, false, kSplitMS>(ctx, a);
-    case 3: return launch_bmu_split<1, true, kSplitMS>(ctx, a);
-    case 4: return launch_bmu_split<2, false, kSplitMS>(ctx, a);
-    case 5: return launch_bmu_split<2, true, kSplitMS>(ctx, a);
-    case 6: return launch_bmu_split<3, false, kSplitMS>(ctx, a);
-    case 7: return launch_bmu_split<3, true, kSplitMS>(ctx, a);
-    case 8: return launch_bmu_split<4, false, kSplitMS>(ctx, a);
-    }
-    return fail(ctx, SOM_EINVAL, "no split BMU kernel for %d blocks%s", kb, tail ? " and a tail" : "");
+    return dispatch_split(ctx, prep.kb, prep.form, [&](auto kb, auto form) { return launch_bmu_split<kb, form, kSplitMS>(ctx, a); });
+}
+
+static int dispatch_bmu_split_cand(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a)
+{
+    return dispatch_split(ctx, prep.kb, prep.form, [&](auto kb, auto form) { return launch_bmu_split_cand<kb, form, kSplitMS>(ctx, a); });
 }
 
 static int dispatch_bmu(som_ctx* ctx, int steps, const BmuArgs& a)
@@ -2965,7 +3391,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     int rc = prep.nch > 1 ? (prep.steps == 25   ? launch_bmu_wide<25>(ctx, a)
                              : prep.steps == 28 ? launch_bmu_wide<28>(ctx, a)
                                                 : launch_bmu_wide<32>(ctx, a))
-                          : (prep.stage16 ? dispatch_bmu_split(ctx, prep.kb, prep.tail_r > 0, a) : dispatch_bmu(ctx, prep.steps, a));
+                          : (prep.stage16 ? dispatch_bmu_split(ctx, prep, a) : dispatch_bmu(ctx, prep.steps, a));
     if (rc) return rc;
     if (a.K > 1) {
         const int64_t chunks = (a.m + kListThreads * kListPerThread - 1) / (kListThreads * kListPerThread);
@@ -2977,7 +3403,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
         rc = prep.nch > 1 ? (prep.steps == 25   ? launch_bmu_wide_cand<25>(ctx, a)
                              : prep.steps == 28 ? launch_bmu_wide_cand<28>(ctx, a)
                                                 : launch_bmu_wide_cand<32>(ctx, a))
-                          : (prep.stage16 ? dispatch_bmu_split_cand(ctx, prep.kb, prep.tail_r > 0, a) : dispatch_bmu_cand(ctx, prep.steps, a));
+                          : (prep.stage16 ? dispatch_bmu_split_cand(ctx, prep, a) : dispatch_bmu_cand(ctx, prep.steps, a));
         if (rc) return rc;
         // (the split search for D <= 64 takes the direct differences over its candidates at the end of the candidate
         // tile itself; the others hand their candidate sets to a kernel of their own)

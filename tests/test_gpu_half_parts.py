@@ -1,0 +1,119 @@
+"""The search of 21 to 64 features by half-precision and fp6 parts, which large calls take, against float64 and against the same rows
+presented in pieces small enough for the two bf16 parts.
+
+Either way a sample whose best two scores lie inside the rounding bound is decided by direct float32 differences, features in order, so the
+units are the same, bit for bit; a bound that is too small shows as a difference.  (Samples a hundred times as far out as the nodes lie from one
+another are told apart by the scores better than by those differences: there the wider of two bounds may show.)  Against float64, a float32 sum of
+D squared differences is off by at most (D + 2) * 2^-24 of itself, so a unit may only miss the nearest node where the two distances are closer
+than twice that.
+"""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def som():
+    from paper_2604_26555_amd import Som
+    s = Som(0)
+    yield s
+    s.close()
+
+
+def rows_for(K, D):
+    """Rows that take the call to these parts, and a piece that does not (the rule of half_parts_pay: rows times MFMAs saved a row)."""
+    left = D % 16
+    two = 3 * (D // 16) + 1 if 1 <= left <= 4 else 3 * ((D + 15) // 16)
+    fewer = (K + 31) // 32 * (two - (D + 31) // 32 - ((D + 3) // 4 // 4 + 1))
+    assert fewer >= 40, "no such map"
+    return 40_000_000 // fewer + 7, 40_000_000 // fewer // 3
+
+
+def check(som, X, W, idx=None, same=True):
+    K, D = W.shape
+    m = X.shape[0] if idx is None else idx.numel()
+    whole, _, _ = som.som_bmu(X, W, idx=idx)
+    whole = whole.clone()
+    _, piece = rows_for(K, D)
+    parts = []
+    for lo in range(0, m, piece):
+        hi = min(m, lo + piece)
+        b, _, _ = som.som_bmu(X[lo:hi] if idx is None else X, W, idx=None if idx is None else idx[lo:hi])
+        parts.append(b.clone())
+    differ = whole != torch.cat(parts)
+    if not same:
+        differ &= (torch.linalg.norm(X - W.mean(0), dim=1) < 100 * torch.linalg.norm(W - W.mean(0), dim=1).max())
+    assert not differ.any(), int(differ.sum())
+    return whole
+
+
+def against_float64(X, W, units):
+    w, D = W.double(), W.shape[1]
+    c = w.mean(0)
+    worst = 0.0
+    for lo in range(0, X.shape[0], 16384):
+        x = X[lo:lo + 16384].double()
+        d = ((x - c) ** 2).sum(1)[:, None] - 2 * (x - c) @ (w - c).t() + ((w - c) ** 2).sum(1)
+        own = ((x - w[units[lo:lo + 16384].long()]) ** 2).sum(1)
+        least = d.min(1).values
+        worst = max(worst, float(((own - least) / own.clamp_min(1e-300)).max()))
+    assert worst <= 2 * (D + 2) * 2.0 ** -24, worst
+
+
+@pytest.mark.parametrize("D,K", [(21, 1024), (24, 1025), (25, 449), (28, 1151), (29, 2500), (32, 700), (33, 1300), (36, 1024), (37, 437), (44, 1100),
+                                 (45, 1030), (48, 1089), (49, 640), (50, 4096), (52, 321), (53, 1024), (60, 300), (61, 1024), (64, 999)])
+def test_units_of_every_form(som, D, K):
+    m, _ = rows_for(K, D)
+    g = torch.Generator(device=DEV).manual_seed(D * 7919 + K)
+    W = torch.randn((K, D), device=DEV, generator=g) * 3 + 11
+    X = W[torch.randint(K, (m,), device=DEV, generator=g)] * 0.7 + 3 + torch.randn((m, D), device=DEV, generator=g)
+    against_float64(X, W, check(som, X, W))
+
+
+@pytest.mark.parametrize("regime", ["collapsed", "pairs", "far samples", "far node", "tiny", "huge", "near the middle", "no numbers"])
+def test_units_of_uneven_values(som, regime):
+    K, D = 1100, 50
+    m, _ = rows_for(K, D)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    randn = lambda *s: torch.randn(s, device=DEV, generator=g)
+    W, X = randn(K, D), 2 * randn(m, D)
+    numbers = True
+    if regime == "collapsed":                              # samples a thousand times as far out as the nodes lie from one another
+        W = 5 + 1e-3 * W
+    elif regime == "pairs":                                # every node has a neighbour a few units of the last place of a score away
+        W[K // 2:] = W[:K // 2] + 1e-5 * randn(K // 2, D)
+    elif regime == "far samples":
+        X[::97] *= 1e5
+    elif regime == "far node":                             # past what half precision holds at the other nodes' scale
+        W[17] *= 1e4
+        X[::1009] = W[17] + randn(X[::1009].shape[0], D)
+    elif regime == "tiny":
+        W, X = W * 1e-17, X * 1e-17
+    elif regime == "huge":
+        W, X = W * 1e15, X * 1e15
+    elif regime == "near the middle":
+        X *= 1e-4
+    else:
+        X[::101, 3] = float("nan")
+        X[::103, 49] = float("inf")
+        X[::107] = 3e38
+        numbers = False
+    units = check(som, X, W, same=regime not in ("collapsed", "far samples"))
+    assert int(units.min()) >= 0 and int(units.max()) < K
+    if numbers and regime != "tiny":                       # (squares of 10^-17 are all but subnormal)
+        against_float64(X, W, units)
+
+
+def test_listed_rows_of_a_wider_matrix(som):
+    K, D = 1024, 37
+    m, _ = rows_for(K, D)
+    g = torch.Generator(device=DEV).manual_seed(9)
+    wide = torch.randn((m + 1000, D + 6), device=DEV, generator=g)
+    X = wide[:, 3:3 + D]
+    W = torch.randn((K, D), device=DEV, generator=g)
+    idx = torch.randperm(m + 1000, device=DEV, generator=g)[:m].int().contiguous()
+    units = check(som, X, W, idx=idx)
+    against_float64(X[idx.long()], W, units)
