@@ -994,7 +994,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
 // two of its largest element, the weights by one that 64 of them give (kHalfBit leaves room for others), and each node's 32 features have
 // an fp6 scale of their own in LDS behind the norms.  The bound is about 2.2 times that of two bf16 parts (fp6 has four significant bits:
 // |first - fp6| |second| and its mirror image for each of the two scores compared), so about twice as many samples are listed.
-// 10^6 x 50: search on 1024 nodes 292 -> 242 us, on 4096 1070 -> 814; with the longer lists the epochs take 411 -> 378 and 1367 -> 1225 us.
+// 10^6 x 50: search on 1024 nodes 292 -> 242 us, on 4096 1070 -> 814; with the longer lists the epochs took 414 -> 372 and 1340 -> 1211 us.
 // What bounds it: the port that issues vector instructions and MFMAs (41 and 6 a block of 32 x 32, the matrix pipe busy 0.45 to 0.55 of the
 // time at 1.8 to 2.0 GHz).  Third and fourth fp6 products (what fp6 leaves of the first parts) would bring the bound back to that of bf16 for 7 or
 // 8 MFMAs a block: an estimated 7 % of the search for what the lists would give back; not built.
@@ -1016,6 +1016,16 @@ constexpr int split_stage_f4(int kb, int form)
 {
     return ((kNodesPerStage * split_row_bytes(kb, form) + kNodesPerStage * (form_units(form) ? 8 : 4)) / 16 + kThreads - 1) / kThreads * kThreads;
 }
+// Stages go from memory to LDS directly (DIRECT: no registers, no vector instructions for it) where two of them lie below 64 KB, in whole
+// kilobytes; others, of 61 to 64 features, by way of registers.
+// Search of 10^6 x 50 on 4096 nodes 814 us by registers and 754, on 1024 242 and 225; of 10^7 x 50 on 1024 2212 and 2123.
+constexpr int split_pitch_direct(int kb, int form)
+{
+    return (kNodesPerStage * split_row_bytes(kb, form) + kNodesPerStage * (form_units(form) ? 8 : 4) + 1023) / 1024 * 1024;
+}
+constexpr bool split_direct(int kb, int form) { return 2 * split_pitch_direct(kb, form) <= 64512; }        // (a kilobyte for what lies in front)
+// bytes from one stage to the next in LDS
+constexpr int split_pitch(int kb, int form) { return split_direct(kb, form) ? split_pitch_direct(kb, form) : split_stage_f4(kb, form) * 16; }
 constexpr int kSplitMinNodes = 1;              // SOM_SEARCH_AUTO: every map of more than this many nodes (measured faster than the
                                                // float32 search from 2 x 2 nodes and from D = 4 on)
 constexpr int kSplitMS = 2;
@@ -1034,12 +1044,12 @@ struct CandQueue {
 };
 constexpr int cand_queue(int kb, int form)            // entries; two workgroups fit a compute unit
 {
-    const size_t left = (80 * 1024 - 2 * (size_t)split_stage_f4(kb, form) * 16) / kWavesPerGroup - CandQueue::kFixed;
+    const size_t left = (80 * 1024 - 2 * (size_t)split_pitch(kb, form)) / kWavesPerGroup - CandQueue::kFixed;
     return left / sizeof(uint2) < 512 ? (int)(left / sizeof(uint2)) / 16 * 16 : 512;
 }
 constexpr size_t cand_lds(int kb, int form)
 {
-    return 2 * (size_t)split_stage_f4(kb, form) * 16 + kWavesPerGroup * (CandQueue::kFixed + (size_t)cand_queue(kb, form) * sizeof(uint2));
+    return 2 * (size_t)split_pitch(kb, form) + kWavesPerGroup * (CandQueue::kFixed + (size_t)cand_queue(kb, form) * sizeof(uint2));
 }
 
 // first feature of slot group q (four consecutive features)
@@ -1157,6 +1167,8 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     constexpr int STAGE_F4 = split_stage_f4(KB, FORM);
     constexpr int KBA = KB > 0 ? KB : 1;               // array lengths (no zero-length arrays when D <= 4)
     constexpr int PRE = STAGE_F4 / kThreads;
+    constexpr bool DIRECT = split_direct(KB, FORM);
+    constexpr int PITCH = split_pitch(KB, FORM);
     const char* ldsb = reinterpret_cast<const char*>(lds4);
 
     const int tid = threadIdx.x;
@@ -1172,7 +1184,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // search: norm of the centred sample (both lane halves hold the whole row's), what a score errs by for each unit of |w| and besides
     // (err_w, err_0), and the norm of what the cut leaves over (see below).  They wait in LDS, behind the stages, for the end of the
     // tile: the stage loop has no registers to spare for them.
-    float* const stash = reinterpret_cast<float*>(lds4 + 2 * STAGE_F4) + threadIdx.x;
+    float* const stash = reinterpret_cast<float*>(lds4 + 2 * PITCH / 16) + threadIdx.x;
     float cut[MS];          // CAND
     unsigned int found[MS]; // CAND: hits of the block in hand
     const int64_t total = CAND ? (int64_t)count : a.m;
@@ -1184,7 +1196,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     CandQueue cq{};
     unsigned int queued = 0u, lost = 0u;
     if constexpr (CAND) {
-        char* at = reinterpret_cast<char*>(lds4 + 2 * STAGE_F4) + wave * (CandQueue::kFixed + QUEUE * sizeof(uint2));
+        char* at = reinterpret_cast<char*>(lds4 + 2 * PITCH / 16) + wave * (CandQueue::kFixed + QUEUE * sizeof(uint2));
         cq.nearest = reinterpret_cast<unsigned long long*>(at);
         cq.entry = reinterpret_cast<uint2*>(at + 64 * sizeof(unsigned long long));
         cq.row = reinterpret_cast<uint32_t*>(at + 64 * sizeof(unsigned long long) + QUEUE * sizeof(uint2));
@@ -1530,11 +1542,29 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // ---- stream the nodes through LDS
     const int nstages = a.kpad / kNodesPerStage;
     const float4* src4 = reinterpret_cast<const float4*>(a.stage16);
-    {
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) char*)lds4);
+    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+    // DIRECT: a stage's kilobytes from memory to LDS, a stretch of them for each wavefront
+    auto load_stage = [&](int st, int buf) {
+        constexpr int KBYTES = PITCH / 1024, PER = (KBYTES + kWavesPerGroup - 1) / kWavesPerGroup;
+        const char* from = reinterpret_cast<const char*>(src4) + (size_t)st * STAGE_F4 * 16 + wave_s * (PER * 1024);
+        const unsigned to = lds0 + (unsigned)(buf * PITCH + wave_s * (PER * 1024));
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (wave_s * PER + q < KBYTES) lds_load16(from + q * 1024, (unsigned)lane * 16u, to + q * 1024);
+    };
+    // what this wavefront brings in and reads is there, for all to see
+    auto stage_barrier = [] {
+        if constexpr (DIRECT) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        else __syncthreads();
+    };
+    if constexpr (DIRECT) {
+        load_stage(0, 0);
+    } else {
 #pragma unroll
         for (int p = 0; p < PRE; ++p) lds4[tid + p * kThreads] = src4[tid + p * kThreads];
     }
-    __syncthreads();
+    stage_barrier();
 
     // The scores of a node block are folded while the matrix pipe works on the next block: two sets of accumulators
     // take turns, and the fold's instructions are written between the MFMAs (the pipe is busy 32 cycles per MFMA,
@@ -1696,14 +1726,15 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     };
     SplitFragments<KB, FORM> f;
     f.first(rows_of(ldsb, 0), tail_of(ldsb, 0), g);
-    // One stage: the next stage travels global -> registers at the start and registers -> the idle LDS buffer after
-    // the second block; the stage's only barrier stands in front of its last block, whose spare LDS slots then read
+    // One stage: the next stage travels to the idle LDS buffer from the start on (DIRECT), or global -> registers at the start and
+    // registers -> the idle LDS buffer after the second block; the stage's only barrier stands in front of its last block, whose spare LDS slots then read
     // the first block of the next stage.  (With the barrier at the end of the stage a wavefront stood still for an
     // LDS write, the barrier and an LDS read once per stage; alone on its SIMD, while the unit's other workgroup
     // loads or stores its samples, that cost a fifth of its time.)  Why this is safe: a buffer's last reads, the
     // operands of its stage's last block, are issued during the block before that barrier and waited for before
     // it, so once a wavefront is past the barrier of stage s the buffer of stage s is free for stage s + 2, which
-    // nobody writes before the middle of stage s + 1; and the barrier of stage s stands between every wavefront's
+    // nobody writes before the start of stage s + 1 (DIRECT: what a wavefront has on its way it waits for in front of the same
+    // barrier); and the barrier of stage s stands between every wavefront's
     // writes of stage s + 1 and the first reads of it.  That holds within a tile: a partial last stage (below) is read with no
     // barrier behind it, so who takes another tile with the same LDS puts one in between.
     constexpr int NB = kNodesPerStage / 32;
@@ -1718,26 +1749,30 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         // Nine float4 per thread (D > 50) would not leave the registers for the rest: they travel in two batches.
         float4 pre0, pre1, pre2, pre3, pre4, pre5, pre6, pre7, pre8;
         static_assert(PRE <= 9, "stage copy holds at most nine float4 per thread");
-        constexpr int FIRST = PRE > 8 ? 5 : PRE;
+        constexpr int FIRST = DIRECT ? 0 : PRE > 8 ? 5 : PRE;
         const float4* s4 = src4 + (size_t)((st + 1 < nstages) ? st + 1 : st) * STAGE_F4 + tid;
-        float4* d4 = lds4 + (buf ^ 1) * STAGE_F4 + tid;
+        float4* d4 = lds4 + (buf ^ 1) * (PITCH / 16) + tid;
 #define SOM_PRE_LOAD(i) if constexpr (PRE > i && i < FIRST) pre##i = s4[i * kThreads];
 #define SOM_PRE_STORE(i) if constexpr (PRE > i && i < FIRST) d4[i * kThreads] = pre##i;
 #define SOM_PRE_LOAD2(i) if constexpr (PRE > i && i >= FIRST) pre##i = s4[i * kThreads];
 #define SOM_PRE_STORE2(i) if constexpr (PRE > i && i >= FIRST) d4[i * kThreads] = pre##i;
 #define SOM_PRE_ALL(op) op(0) op(1) op(2) op(3) op(4) op(5) op(6) op(7) op(8)
+        if constexpr (DIRECT) {
+            if (st + 1 < nstages) load_stage(st + 1, buf ^ 1);
+        }
         SOM_PRE_ALL(SOM_PRE_LOAD)
         __builtin_amdgcn_sched_barrier(0);
-        const char* wbuf = ldsb + (size_t)buf * STAGE_F4 * 16;
-        const char* obuf = ldsb + (size_t)(buf ^ 1) * STAGE_F4 * 16;
+        const char* wbuf = ldsb + (size_t)buf * PITCH;
+        const char* obuf = ldsb + (size_t)(buf ^ 1) * PITCH;
         block(accA, accB, f, rows_of(wbuf, 1), tail_of(wbuf, 1), true, st - 1, 3);
-        if constexpr (FIRST < PRE) {
+        if constexpr (!DIRECT && FIRST < PRE) {
             SOM_PRE_ALL(SOM_PRE_STORE)
             SOM_PRE_ALL(SOM_PRE_LOAD2)
             __builtin_amdgcn_sched_barrier(0);
         }
         block(accB, accA, f, rows_of(wbuf, 2), tail_of(wbuf, 2), true, st, 0);
-        if constexpr (FIRST < PRE) {
+        if constexpr (DIRECT) {
+        } else if constexpr (FIRST < PRE) {
             SOM_PRE_ALL(SOM_PRE_STORE2)
         } else {
             SOM_PRE_ALL(SOM_PRE_STORE)
@@ -1749,7 +1784,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
 #undef SOM_PRE_ALL
         __builtin_amdgcn_sched_barrier(0);
         block(accA, accB, f, rows_of(wbuf, 3), tail_of(wbuf, 3), true, st, 1);
-        __syncthreads();
+        stage_barrier();
         block(accB, accA, f, rows_of(obuf, 0), tail_of(obuf, 0), true, st, 2);
         if constexpr (CAND) {
             if (queued > (unsigned)QUEUE / 2) serve();
@@ -1773,7 +1808,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         fold_last(accB, std::integral_constant<int, 3>{});
     } else {
         const int st = nstages - 1;
-        const char* wbuf = ldsb + (size_t)(st & 1) * STAGE_F4 * 16;
+        const char* wbuf = ldsb + (size_t)(st & 1) * PITCH;
         block(accA, accB, f, rows_of(wbuf, 1), tail_of(wbuf, 1), true, st - 1, 3);
         if (live_last == 1) {
             fold_last(accA, std::integral_constant<int, 0>{});
@@ -3093,7 +3128,7 @@ static int launch_bmu(som_ctx* ctx, const BmuArgs& a)
 template <int KB, int FORM, int MS>
 static int launch_bmu_split(som_ctx* ctx, const BmuArgs& a)
 {
-    constexpr size_t lds_bytes = 2 * (size_t)split_stage_f4(KB, FORM) * 16 + 5 * kThreads * sizeof(float);
+    constexpr size_t lds_bytes = 2 * (size_t)split_pitch(KB, FORM) + 5 * kThreads * sizeof(float);
     static_assert(lds_bytes + 512 <= 80 * 1024, "two workgroups per compute unit");
     static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
     bool& attr_set = attr_set_dev[ctx->device];

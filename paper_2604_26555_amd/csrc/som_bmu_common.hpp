@@ -101,6 +101,12 @@ __device__ __forceinline__ float4 load4(const float* p)
     return v;
 }
 
+// 64 lanes x 16 bytes, from `base` (the same for all lanes) + the lane's offset to 1 KB of LDS at offset lds (below 64 KB); counted by vmcnt
+__device__ __forceinline__ void lds_load16(const char* base, unsigned offset, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
+}
+
 // plain v_max_f32: the scores are never signalling NaNs worth quieting, and every VALU instruction here is paid
 // for in matrix time (float32 MFMA and the vector ALU share the same lanes)
 __device__ __forceinline__ float vmax(float a, float b)
