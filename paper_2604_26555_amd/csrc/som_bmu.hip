@@ -2373,41 +2373,44 @@ __global__ void __launch_bounds__(256) bmu_cand_exact_kernel(const BmuArgs a)
 
 // ---------------------------------------------------------------------------------------------------------
 // The pair list: samples whose candidates (at most eight) the split search already knows (D <= 64).
-// A wavefront takes a round of entries at a time, on its own (no barrier): LP lanes (4, 8 or 16, sixteen bytes of a row each) fetch one or
-// two entries' rows, the sample's and two candidates', in coalesced loads; the rows meet in the wavefront's part of LDS, the next entries'
-// rows are requested, and one lane per candidate adds its squared differences up, features in order as the other re-decisions do;
+// A wavefront takes a round of sixteen entries at a time, on its own (no barrier): LP lanes (4, 8 or 16, sixteen bytes of a row each) fetch
+// an entry's rows, the sample's and two candidates', in coalesced loads; the differences meet in the wavefront's part of LDS, the next entries'
+// rows are requested, and one lane per candidate adds the squares up, features in order as the other re-decisions do;
 // lowest distance, then lowest node index.
 // The chain sample position -> ids and row number -> rows is three dependent trips to memory: positions are read three rounds ahead, ids and
-// row numbers two, rows one, and two workgroups of eight wavefronts fit a unit.  10^7 x 50 on 1024 nodes, 2.8 million entries: 331 us, by the lines
-// of their rows; sums across the LP lanes instead of out of LDS take 312, but they add in another order, and a sample that lies between two nodes
+// row numbers two, rows one, each by one lane an entry, and two workgroups of eight wavefronts fit a unit.
+// What bounds it beside the rows' lines is instructions: a lane of the sum is a whole wavefront's instruction for 32 candidates at most, so
+// the differences are formed where all lanes have a share of them, and sixteen entries share the sum.  (Eight entries a round, three rows of
+// each in LDS: 10^7 x 50 on a tree's 1024 nodes, half of the rows listed, 636 us, 529 this way; 10^6 x 50 on 4096 nodes 76 and 58.)
+// Sums across the LP lanes would take fewer still, but they add in another order, and a sample that lies between two nodes
 // must not go to one of them in a look-up and to the other in an epoch.
-// (With the ids read a round ahead, beside the rows before those that need them, and sixteen entries a round, whose registers left one workgroup
-// a unit, 10^7 x 50 on 1024 nodes, 3.8 million entries, took 501 us; 900,000 x 25 on 400 nodes 20 us for 13.)
-// The few entries with a third to an eighth candidate wait in LDS until there is a round of them, two candidates at a time.
-// (Served in the round where they came, nearly every round waited for their rows: 4.0 million entries of 10^7 x 50 took 0.62 ms
-// for 0.48.)
+// The few entries with a third to an eighth candidate wait in LDS until there is a round of them, two candidates at a time, which then takes
+// its turn among the others: its rows, too, are on their way during the round before.  (Served between two rounds, with the next one's rows
+// fetched again behind them: 529 us, 483 this way; 10^6 x 50 on 4096 nodes 58 and 52.)
 // ---------------------------------------------------------------------------------------------------------
 constexpr int pair_lanes(int D) { return D <= 16 ? 4 : D <= 32 ? 8 : 16; }
-constexpr int pair_each(int LP) { return LP == 4 ? 1 : 2; }             // entries of LP lanes' round
-constexpr int pair_round(int LP) { return pair_each(LP) * (64 / LP); }
-// float4 of LDS that a wavefront's entries take: three rows (an odd number each, so that the lanes' 16-byte reads fall into distinct
-// banks), their ids, and twice as many entries that wait
-__host__ __device__ constexpr int pair_lds_f4(int D, int LP) { return pair_round(LP) * (3 * (((D + 3) / 4) | 1) + 1 + 2); }
+constexpr int kPairRound = 16;                                          // entries of a round
+// float4 of LDS that a wavefront's entries take: two differences (an odd number each, so that the lanes' 16-byte reads fall into distinct
+// banks), what two rounds and twice as many waiting entries note, and their row numbers
+__host__ __device__ constexpr int pair_lds_f4(int D) { return kPairRound * (2 * (((D + 3) / 4) | 1) + 2 + 2 + 1); }
 
 template <int LP>
 __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__ lds)
 {
-    constexpr int EACH = pair_each(LP), GROUPS = 64 / LP, ROUND = pair_round(LP);
+    constexpr int ROUND = kPairRound, GROUPS = 64 / LP, EACH = ROUND / GROUPS;
     static_assert(2 * ROUND <= 64, "a lane a candidate");
     const unsigned int count = a.scal[a.slot + 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int sub = lane & (LP - 1), grp = lane / LP;
     const int D = a.D, whole = D / 4, rest = D - 4 * whole;
-    const int stride = ((D + 3) / 4) | 1;             // float4 of a row
-    float4* const rows = lds + wave * pair_lds_f4(D, LP);
-    uint4* const info = reinterpret_cast<uint4*>(rows + ROUND * 3 * stride);      // [entry] ids, sample position
-    // [2 ROUND] next two ids, sample position, nearest so far (distance; row of the stages, and which word of its ids the two are)
-    uint4* const later = info + ROUND;
+    const int stride = ((D + 3) / 4) | 1;             // float4 of a difference
+    float4* const rows = lds + wave * pair_lds_f4(D);
+    // What a round's entries note, [round's parity][entry]: of new ones two words of ids and the sample's position; of entries that waited
+    // the next two ids, the position, the nearest so far (distance; row of the stages, and which word of its ids the two are).
+    uint4* const info = reinterpret_cast<uint4*>(rows + ROUND * 2 * stride);
+    uint4* const later = info + 2 * ROUND;                          // [2 ROUND]
+    uint32_t* const info_row = reinterpret_cast<uint32_t*>(later + 2 * ROUND);    // [2][ROUND], the samples' rows
+    uint32_t* const later_row = info_row + 2 * ROUND;               // [2 ROUND]
     constexpr unsigned int kNoRow = 0xffffffu;
     const int pair_shift = a.K >= kPairMany ? 2 : 1;                // words of an entry's ids
     unsigned int waiting = 0u;
@@ -2417,7 +2420,11 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
     const unsigned int first = (blockIdx.x * (kExactThreads / 64) + wave) * ROUND;
     if (first >= count) return;
     const unsigned int k_most = (unsigned int)a.K - 1u;
-    auto row_of = [&](unsigned int id) { return load4(a.wrow + (size_t)(id < k_most ? id : k_most) * D + start); };
+    const char* const wrow = reinterpret_cast<const char*>(a.wrow);
+    // (a map of 65535 nodes x 64 features has 16 MB)
+    auto row_of = [&](unsigned int id) {
+        return load4(reinterpret_cast<const float*>(wrow + (((id < k_most ? id : k_most) * (unsigned)D + (unsigned)start) * 4u)));
+    };
     float4 x[EACH], w[EACH][2];
     // entry u's rows for this lane's window (a single candidate's twice)
     auto fetch = [&](int u, unsigned int both, uint32_t row) {
@@ -2427,11 +2434,11 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
         w[u][1] = row_of(i1 == 0xffffu ? i0 : i1);
     };
     auto lay = [&](int u) {
-        float4* r = rows + (GROUPS * u + grp) * 3 * stride + sub;
+        float4* r = rows + (GROUPS * u + grp) * 2 * stride + sub;
         if (own) {
-            r[0] = x[u];
-            r[stride] = w[u][0];
-            r[2 * stride] = w[u][1];
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                r[c * stride] = make_float4(x[u].x - w[u][c].x, x[u].y - w[u][c].y, x[u].z - w[u][c].z, x[u].w - w[u][c].w);
         }
     };
     // this lane's candidate: entry lane / 2, place lane % 2
@@ -2448,142 +2455,112 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
     };
     auto sum = [&](unsigned int both) {
         const unsigned int id = c == 0 ? both & 0xffffu : both >> 16;
-        const float4* rx = rows + e * 3 * stride;
-        const float4* rw = rx + (1 + c) * stride;
+        const float4* r = rows + (2 * e + c) * stride;
         float d = 0.0f;
         if (lane < 2 * ROUND) {
 #pragma unroll 4
             for (int q = 0; q < whole; ++q) {
-                const float4 xv = rx[q], wv = rw[q];
-                const float d0 = xv.x - wv.x, d1 = xv.y - wv.y, d2 = xv.z - wv.z, d3 = xv.w - wv.w;
-                d = fmaf(d0, d0, d);
-                d = fmaf(d1, d1, d);
-                d = fmaf(d2, d2, d);
-                d = fmaf(d3, d3, d);
+                const float4 v = r[q];
+                d = fmaf(v.x, v.x, d);
+                d = fmaf(v.y, v.y, d);
+                d = fmaf(v.z, v.z, d);
+                d = fmaf(v.w, v.w, d);
             }
             if (rest > 0) {          // the window [D - 4, D): its leading elements are already counted
-                const float4 xv = rx[whole], wv = rw[whole];
-                const float d1 = xv.y - wv.y, d2 = xv.z - wv.z, d3 = xv.w - wv.w;
-                if (rest > 2) d = fmaf(d1, d1, d);
-                if (rest > 1) d = fmaf(d2, d2, d);
-                d = fmaf(d3, d3, d);
+                const float4 v = r[whole];
+                if (rest > 2) d = fmaf(v.y, v.y, d);
+                if (rest > 1) d = fmaf(v.z, v.z, d);
+                d = fmaf(v.w, v.w, d);
             }
         }
         nearer(id != 0xffffu ? d : INFINITY, (int)id);
         nearer(__shfl_xor(bd, 1), __shfl_xor(bk, 1));
     };
-    // up to a round of the entries that wait, the last ones
-    auto serve_later = [&]() {
-        const unsigned int n = waiting < (unsigned)ROUND ? waiting : (unsigned)ROUND, base = waiting - n;
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int u = 0; u < EACH; ++u) {
-            const unsigned int q = GROUPS * u + grp;
-            const uint4 l = later[base + (q < n ? q : 0u)];
-            fetch(u, l.x, a.idx ? a.idx[l.y] : l.y);
-        }
-#pragma unroll
-        for (int u = 0; u < EACH; ++u) lay(u);
-        __builtin_amdgcn_wave_barrier();
-        const uint4 l = later[base + ((unsigned)e < n ? (unsigned)e : 0u)];
-        const unsigned int word = l.w >> 24;           // of its ids
-        bd = __uint_as_float(l.z);
-        bk = (int)(l.w & kNoRow);
-        sum(l.x);
-        const bool mine = lane < 2 * (int)n && c == 0;
-        unsigned int rest_of = 0xffffffffu;
-        if (mine && word + 1u < 1u << pair_shift && l.x >> 16 != 0xffffu) rest_of = a.pairs[((int64_t)l.y << pair_shift) + word + 1u];
-        const bool more = rest_of != 0xffffffffu;
-        if (mine && !more && bk < a.K) a.bmu[l.y] = node_of_row(bk, a.K);
-        waiting = base;
-        const unsigned long long wait = __ballot(more);
-        if (wait != 0ull) {
-            const unsigned int to = base + __builtin_amdgcn_mbcnt_hi((unsigned)(wait >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)wait, 0));
-            if (more) later[to] = make_uint4(rest_of, l.y, __float_as_uint(bd), ((unsigned)bk & kNoRow) | (word + 1u) << 24);
-            waiting += (unsigned)__popcll(wait);
-        }
-        __builtin_amdgcn_wave_barrier();
-    };
-    auto position = [&](unsigned int p, int u) {
-        const unsigned int q = p + GROUPS * u + grp;
+    // entry `lane % ROUND` of the round at p (behind the list's end its last one)
+    auto position = [&](unsigned int p) {
+        const unsigned int q = p + (lane & (ROUND - 1));
         return a.recheck_end[-1 - (int64_t)(q < count ? q : count - 1)];
     };
-    auto after = [&](unsigned int p) { return count - p > step ? p + step : p; };     // (the last round's again at the end)
-    uint32_t at[EACH], at1[EACH], at2[EACH], row1[EACH];
-    uint2 ids[EACH], ids1[EACH];
-    {
-        uint32_t row[EACH];
-        const unsigned int p1 = after(first), p2 = after(p1);
-#pragma unroll
-        for (int u = 0; u < EACH; ++u) {
-            at[u] = position(first, u);
-            at1[u] = position(p1, u);
-            at2[u] = position(p2, u);
-        }
-#pragma unroll
-        for (int u = 0; u < EACH; ++u) {
-            ids[u] = *reinterpret_cast<const uint2*>(a.pairs + ((int64_t)at[u] << pair_shift));
-            row[u] = a.idx ? a.idx[at[u]] : at[u];
-            ids1[u] = *reinterpret_cast<const uint2*>(a.pairs + ((int64_t)at1[u] << pair_shift));
-            row1[u] = a.idx ? a.idx[at1[u]] : at1[u];
-        }
-#pragma unroll
-        for (int u = 0; u < EACH; ++u) fetch(u, ids[u].x, row[u]);
-    }
-    for (unsigned int p0 = first;; p0 += step) {
-        uint2 ids2[EACH];
-        uint32_t at3[EACH], row2[EACH];
-        const unsigned int p3 = after(after(after(p0)));
-#pragma unroll
-        for (int u = 0; u < EACH; ++u) {
-            ids2[u] = *reinterpret_cast<const uint2*>(a.pairs + ((int64_t)at2[u] << pair_shift));
-            row2[u] = a.idx ? a.idx[at2[u]] : at2[u];
-            at3[u] = position(p3, u);
-        }
-        // this round's rows to LDS, the next one's on their way
-#pragma unroll
-        for (int u = 0; u < EACH; ++u) {
-            lay(u);
-            if (sub == 0) info[GROUPS * u + grp] = make_uint4(ids[u].x, ids[u].y, at[u], 0u);
+    auto ids_of = [&](uint32_t at) { return *reinterpret_cast<const uint2*>(a.pairs + ((int64_t)at << pair_shift)); };
+    auto row_at = [&](uint32_t at) { return a.idx ? a.idx[at] : at; };
+    // new entries: the next round's ids and row numbers, the positions of the one behind it
+    unsigned int p = first, left = (count - first + step - 1) / step;          // their first one, how many rounds of them are left
+    uint32_t at1 = position(p), at2 = position(left > 1u ? p + step : p), row1 = row_at(at1);
+    uint2 ids1 = ids_of(at1);
+    int parity = 0;
+    // The next round: entries that wait where they fill one, the last ones first, or (end) where none is in hand whose entries could join them;
+    // otherwise new ones.  Its rows are on their way afterwards.  Returns how many entries it has.
+    auto next_round = [&](bool& waited, bool end) -> unsigned int {
+        waited = waiting >= (unsigned)ROUND || left == 0u;
+        unsigned int n;
+        if (waited) {
+            n = waiting < (unsigned)ROUND ? waiting : (unsigned)ROUND;
+            if (n == 0u || (n < (unsigned)ROUND && !end)) return 0u;
+            waiting -= n;
+            if (lane < ROUND) {
+                const unsigned int q = waiting + ((unsigned)lane < n ? (unsigned)lane : 0u);
+                info[parity * ROUND + lane] = later[q];
+                info_row[parity * ROUND + lane] = later_row[q];
+            }
+        } else {
+            n = count - p < (unsigned)ROUND ? count - p : (unsigned)ROUND;
+            const uint2 ids2 = ids_of(at2);
+            const uint32_t row2 = row_at(at2), at3 = position(left > 2u ? p + 2u * step : p);
+            if (lane < ROUND) {
+                info[parity * ROUND + lane] = make_uint4(ids1.x, ids1.y, at1, 0u);
+                info_row[parity * ROUND + lane] = row1;
+            }
+            ids1 = ids2;
+            row1 = row2;
+            at1 = at2;
+            at2 = at3;
+            p += step;
+            --left;
         }
         __builtin_amdgcn_wave_barrier();
-        const bool last = count - p0 <= step;
-        if (!last)
 #pragma unroll
-            for (int u = 0; u < EACH; ++u) fetch(u, ids1[u].x, row1[u]);
-        const uint4 my = info[e];
-        const bool mine = lane < 2 * ROUND && p0 + e < count && c == 0;
-        bd = INFINITY;
-        bk = 0x7fffffff;
+        for (int u = 0; u < EACH; ++u) {
+            const int q = parity * ROUND + GROUPS * u + grp;
+            fetch(u, info[q].x, info_row[q]);
+        }
+        return n;
+    };
+    bool waited;
+    unsigned int n = next_round(waited, false);
+    while (n != 0u) {
+        // this round's differences to LDS, the next one's rows on their way
+#pragma unroll
+        for (int u = 0; u < EACH; ++u) lay(u);
+        const uint4* const mine = info + parity * ROUND;
+        const bool old = waited;
+        const unsigned int m = n;
+        parity ^= 1;
+        n = next_round(waited, false);
+        __builtin_amdgcn_wave_barrier();
+        const uint4 my = mine[e];
+        const unsigned int word = old ? my.w >> 24 : 0u;               // of its ids
+        const uint32_t at = old ? my.y : my.z;
+        bd = old ? __uint_as_float(my.z) : INFINITY;
+        bk = old ? (int)(my.w & kNoRow) : 0x7fffffff;
         sum(my.x);
-        const bool more = mine && my.y != 0xffffffffu;
-        if (mine && !more && bk < a.K) a.bmu[my.z] = node_of_row(bk, a.K);
+        const bool here = lane < 2 * (int)m && c == 0;
+        unsigned int rest_of = 0xffffffffu;
+        if (!old) rest_of = here ? my.y : 0xffffffffu;
+        else if (here && word + 1u < 1u << pair_shift && my.x >> 16 != 0xffffu) rest_of = a.pairs[((int64_t)at << pair_shift) + word + 1u];
+        const bool more = rest_of != 0xffffffffu;
+        if (here && !more && bk < a.K) a.bmu[at] = node_of_row(bk, a.K);
         const unsigned long long wait = __ballot(more);
         if (wait != 0ull) {
             const unsigned int to = waiting + __builtin_amdgcn_mbcnt_hi((unsigned)(wait >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)wait, 0));
-            if (more) later[to] = make_uint4(my.y, my.z, __float_as_uint(bd), ((unsigned)bk & kNoRow) | 1u << 24);
-            waiting += (unsigned)__popcll(wait);
-            if (waiting >= (unsigned)ROUND) {
-                // (the next round's rows make room, and come again)
-                while (waiting >= (unsigned)ROUND) serve_later();
-                if (!last)
-#pragma unroll
-                    for (int u = 0; u < EACH; ++u) fetch(u, ids1[u].x, row1[u]);
+            if (more) {
+                later[to] = make_uint4(rest_of, at, __float_as_uint(bd), ((unsigned)bk & kNoRow) | (word + 1u) << 24);
+                later_row[to] = info_row[(parity ^ 1) * ROUND + e];
             }
+            waiting += (unsigned)__popcll(wait);
         }
         __builtin_amdgcn_wave_barrier();
-        if (last) break;
-#pragma unroll
-        for (int u = 0; u < EACH; ++u) {
-            at[u] = at1[u];
-            at1[u] = at2[u];
-            at2[u] = at3[u];
-            ids[u] = ids1[u];
-            ids1[u] = ids2[u];
-            row1[u] = row2[u];
-        }
+        if (n == 0u) n = next_round(waited, true);          // (the last rounds' entries that wait; each entry comes four times at most)
     }
-    while (waiting != 0u) serve_later();              // (each entry comes three times at most)
 }
 
 template <bool PAIRS>
@@ -3449,11 +3426,20 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     }
     if (a.K > 1) {
         if (prep.stage16 && prep.nch == 1) {
-            // (at most 60 KB, at 29 to 32 features: two workgroups of 128 registers a thread fit a compute unit, and no limit has to be raised)
+            // (two workgroups of 128 registers a thread fit a compute unit; above 53 features a workgroup's rows take more than 64 KB)
             constexpr size_t kOwn = 2 * 4 * (kExactThreads / 64) * kExactGroup + 16 * 2 * 8 + 16 * 4;      // red_d, red_k and group_qe_add's
-            auto rows_of = [](int D) constexpr { return (size_t)(kExactThreads / 64) * pair_lds_f4(D, pair_lanes(D)) * 16; };
-            static_assert(rows_of(16) + kOwn <= 65536 && rows_of(32) + kOwn <= 65536 && rows_of(64) + kOwn <= 65536, "LDS of a launch");
+            auto rows_of = [](int D) constexpr { return (size_t)(kExactThreads / 64) * pair_lds_f4(D) * 16; };
+            static_assert(2 * (rows_of(64) + kOwn) <= 160 * 1024, "LDS of two workgroups");
             const size_t rows = rows_of(a.D), lds = rows > kExactLds ? rows : kExactLds;
+            static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
+            bool& attr_set = attr_set_dev[ctx->device];
+            if (!attr_set) {
+                if ((rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(bmu_exact_kernel<true>),
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)rows_of(64)),
+                                    "raising the dynamic LDS limit")))
+                    return rc;
+                attr_set = true;
+            }
             BmuArgs b = a;                       // the distances come afterwards, for all samples
             b.d2 = nullptr;
             b.qe = nullptr;

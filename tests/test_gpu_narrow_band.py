@@ -51,8 +51,7 @@ def test_two_to_nine_close_nodes(som, D, K):  # noqa: F811
 @pytest.mark.parametrize("candidates", [2, 3, 4, 5, 8])
 @pytest.mark.parametrize("K,D", [(1024, 16), (1024, 32), (1152, 50), (512, 50)])
 def test_pair_lists_of_several_rounds(som, K, D, candidates):  # noqa: F811
-    """Every row is on the pair list, three rounds of it and more (512 workgroups of eight wavefronts take 65,536 entries a round up to 32
-    features, 32,768 above): the first `candidates` of every eight nodes in a row, which fall into eight classes, are close together.  Entries
+    """Every row is on the pair list, three rounds of it (512 workgroups of eight wavefronts take 65,536 entries a round): the first `candidates` of every eight nodes in a row, which fall into eight classes, are close together.  Entries
     of more than two wait among those of the rounds after theirs.  (On 512 nodes those of more than four go to the candidate pass.)"""
     m = 140_000
     g = torch.Generator(device="cuda").manual_seed(K + D + candidates)
