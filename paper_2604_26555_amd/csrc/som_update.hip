@@ -28,7 +28,7 @@ constexpr int kSplitK = 8;
 
 // The shape of a contraction.  Two wavefronts for every SIMD, so that one's loads and exponentials run beside the other's MFMAs:
 // 4 per block of nodes and 64 columns, more parts where those are too few.  (One for every SIMD: K = 4096, D = 50 150 us, 100 with
-// two; K = 1024, D = 50 17.5, 12.6; K = 437, D = 37 8.8, 6.)
+// two; K = 1024, D = 50 17.5, 12.6; K = 437, D = 37 8.8, 6: all with the library's exponential.)
 // Several column blocks: as many nodes a wavefront as leave that many.  S comes straight from L2, 512 bytes for each float64 MFMA and block of
 // sixteen nodes: with one block L2 is what bounds it, four read it a quarter as often.  Whole update, one block, two, four: K = 1024
 // D = 500 66, 48, 44 us, D = 1000 85, 85, 71, D = 2000 122, 120, 116; K = 400 D = 500 24, 26, 26, D = 1000 30, 29, 35, D = 2000 43, 40, 41;
@@ -90,11 +90,40 @@ __global__ void __launch_bounds__(1024) shift_kernel(const float* __restrict__ G
     }
 }
 
+// exp(x) for x <= 0 (any other x gives some value, NaN gives NaN), to 0.82 units in the last place: x = n ln 2 + r, |r| <= ln 2 / 2, and
+// 1 + r + r^2 q(r), q interpolated at ten Chebyshev nodes (error 3e-18).  Without a branch and with its constants in scalar registers: the
+// library's took some sixty instructions and three branches for 24, and branches keep a batch's loads and MFMAs apart.
+// Contraction of K = 4096, D = 50, sixteen million of them: 92 us with the library's, 70 with these.
+__device__ __forceinline__ double exp_below(double x)
+{
+    double c9 = 0x1.af38a9b0ec855p-26, c8 = 0x1.289185613a3d6p-22, c7 = 0x1.71de0dae63bb3p-19, c6 = 0x1.a019b90d2ae7ap-16,
+           c5 = 0x1.a01a01a7c41d5p-13, c4 = 0x1.6c16c1788bd90p-10, c3 = 0x1.11111111109b3p-7, c2 = 0x1.5555555553d63p-5,
+           c1 = 0x1.5555555555556p-3, c0 = 0x1.0000000000001p-1, log2e = 0x1.71547652b82fep+0, ln2_hi = 0x1.62e42fefa0000p-1,
+           ln2_lo = 0x1.cf79abc9e3b3ap-40;
+    asm("" : "+s"(c8), "+s"(c7), "+s"(c6), "+s"(c5), "+s"(c4), "+s"(c3), "+s"(c2), "+s"(c1), "+s"(c0));
+    asm("" : "+s"(log2e), "+s"(ln2_hi), "+s"(ln2_lo), "+s"(c9));
+    x = x < -1100.0 ? -1100.0 : x;                            // (zero from -746 on)
+    const double n = __builtin_rint(x * log2e);
+    const double r = fma(-n, ln2_lo, fma(-n, ln2_hi, x));
+    double q = fma(c9, r, c8);
+    q = fma(q, r, c7);
+    q = fma(q, r, c6);
+    q = fma(q, r, c5);
+    q = fma(q, r, c4);
+    q = fma(q, r, c3);
+    q = fma(q, r, c2);
+    q = fma(q, r, c1);
+    q = fma(q, r, c0);
+    q = fma(fma(q, r, 1.0), r, 1.0);
+    return __builtin_amdgcn_ldexp(q, (int)n);
+}
+
 // h = exp(-(g^2 - shift_j) / 2 sigma^2); with a shift only occupied nodes k contribute (their exponent is <= 0)
 __device__ __forceinline__ double influence_of(double gd, double inv2s2, double shift_j, bool occupied)
 {
-    const double e = -(gd * gd - shift_j) * inv2s2;
-    return (isinf(gd) || isinf(shift_j) || !occupied) ? 0.0 : exp(e);
+    double h = exp_below(-(gd * gd - shift_j) * inv2s2);
+    asm("" : "+v"(h));                                        // (formed for every lane: the compiler would branch around it otherwise)
+    return (isinf(gd) || isinf(shift_j) || !occupied) ? 0.0 : h;
 }
 
 __global__ void __launch_bounds__(256) influence_kernel(const float* __restrict__ G, int K, double inv2s2,
@@ -139,55 +168,78 @@ __global__ void __launch_bounds__(256, 2) contract_kernel(const float* __restric
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[q][t] = doublex4{0.0, 0.0, 0.0, 0.0};
     }
-    // kBatch k-steps at a time: first every load of the batch (one wavefront per SIMD has nothing else to cover a
-    // round trip to L2 with), then the exponentials, then the MFMAs.
-    constexpr int kBatch = FUSED ? 8 : 16 / JT;            // (sixteen with the exponentials take more than 256 registers: one wavefront)
+    // kBatch k-steps at a time, the next batch's loads under way during the exponentials and MFMAs of the one in hand.  (Twice as many steps
+    // with their loads in front of them: K = 1024, D = 2000 93 us, 79 this way; K = 437, D = 37 5.4 and 4.7; K = 1024, D = 50 9.6 and 10.3.)
+    constexpr int kBatch = FUSED ? 4 : JT == 4 ? 2 : 4;
+    struct Batch {
+        float g[FUSED ? JT : 1][kBatch];
+        double h[FUSED ? 1 : JT][kBatch];
+        double s[kBatch][4];
+        unsigned long long count[kBatch];
+    };
     // (inner: all columns are of S.  Rows and columns behind the last are formed and not stored.)
-    auto batch = [&](int kb, auto whole, auto inner) {
-        float gv[JT][kBatch];
-        double nv[JT][kBatch], sv[kBatch][4];
+    auto load = [&](int kb, Batch& b, auto inner) {
 #pragma unroll
         for (int s = 0; s < kBatch; ++s) {
-            if (!whole && kb + 4 * s >= k_hi) continue;
             const int k = kb + 4 * s + lk;
             const int kc = k < K ? k : K - 1;                 // clamped row: the loads are unconditional
 #pragma unroll
             for (int q = 0; q < JT; ++q) {
-                if (FUSED) gv[q][s] = G[(size_t)kc * K + jc[q]];
-                else nv[q][s] = H[(size_t)kc * K + jc[q]];
+                if constexpr (FUSED) b.g[q][s] = G[(size_t)kc * K + jc[q]];
+                else b.h[q][s] = H[(size_t)kc * K + jc[q]];
             }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int c = c0 + 16 * t + li;
-                sv[s][t] = (!inner && c == D) ? (double)n[kc] : S[(size_t)kc * D + (inner || c < D ? c : D - 1)];
+                b.s[s][t] = S[(size_t)kc * D + (inner || c < D ? c : D - 1)];
             }
+            // (every lane loads the count and one of sixteen takes it: loads of those lanes alone were a branch each between the others)
+            if (!inner) b.count[s] = n[kc];
         }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto use = [&](int kb, Batch& b, auto whole, auto inner) {
 #pragma unroll
         for (int s = 0; s < kBatch; ++s) {
             if (!whole && kb + 4 * s >= k_hi) continue;
             const int k = kb + 4 * s + lk;
-            const bool occupied = !(FUSED && shift) || n[k < K ? k : K - 1] != 0ull;
+            const bool occupied = !(FUSED && shift) || b.count[s] != 0ull;       // (FUSED: one block of columns, the last one)
+            if (!inner) {
+                const double cd = (double)b.count[s];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) b.s[s][t] = c0 + 16 * t + li == D ? cd : b.s[s][t];
+            }
 #pragma unroll
             for (int q = 0; q < JT; ++q) {
                 const bool in = whole || k < k_hi;
                 double h;
-                if (FUSED) h = in ? influence_of((double)gv[q][s], inv2s2, shift_j[q], occupied) : 0.0;
-                else h = in ? nv[q][s] : 0.0;
+                if constexpr (FUSED) h = in ? influence_of((double)b.g[q][s], inv2s2, shift_j[q], occupied) : 0.0;
+                else h = in ? b.h[q][s] : 0.0;
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const double b = whole || k < k_hi ? sv[s][t] : 0.0;
-                    acc[q][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(h, b, acc[q][t], 0, 0, 0);
-                }
+                for (int t = 0; t < 4; ++t) acc[q][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(h, in ? b.s[s][t] : 0.0, acc[q][t], 0, 0, 0);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
-    // (a small map's wavefronts end within the first batch, after 7 of 16 steps at K = 437: leaving the others out is 13.1 -> 8.8 us
-    // there.  Among the whole batches of a large one the same branches keep loads and MFMAs apart: 173 -> 291 us at K = 1024,
-    // D = 2000, so those have none.)
+    // (the steps that a small map's last batch has not are left out; among whole batches the same branches would keep loads and MFMAs apart)
     auto all = [&](auto inner) {
+        constexpr int STEP = 4 * kBatch;
+        Batch one, two;
         int kb = k_lo;
-        for (; kb + 4 * kBatch <= k_hi; kb += 4 * kBatch) batch(kb, std::true_type{}, inner);
-        if (kb < k_hi) batch(kb, std::false_type{}, inner);
+        if (kb < k_hi) load(kb, one, inner);
+        for (; kb + 2 * STEP <= k_hi; kb += 2 * STEP) {
+            load(kb + STEP, two, inner);
+            use(kb, one, std::true_type{}, inner);
+            load(kb + 2 * STEP, one, inner);
+            use(kb + STEP, two, std::true_type{}, inner);
+        }
+        if (kb + STEP <= k_hi) {
+            load(kb + STEP, two, inner);
+            use(kb, one, std::true_type{}, inner);
+            if (kb + STEP < k_hi) use(kb + STEP, two, std::false_type{}, inner);
+        } else if (kb < k_hi) {
+            use(kb, one, std::false_type{}, inner);
+        }
     };
     if (c0 + 64 <= D) all(std::true_type{});
     else all(std::false_type{});
