@@ -18,6 +18,9 @@
 // At the end the slab moves to the range's slice of a global workspace and a second kernel adds the slices in a
 // fixed order.  Counts are exact; the sums are float64 throughout (the order of the atomic additions varies from
 // run to run, which moves a sum by a few units in the 16th digit).
+// A slab holds every nslabs-th node: nodes that lie together hold similar shares of the samples, and stretches of the nodes' order gave the
+// fullest of three slabs 1.2 to 1.6 thirds of them, for which the others' workgroups then waited (10^7 x 50 on a chain of 1024 nodes 586 us and
+// 453, 4 * 10^6 listed rows 273 and 253, 10^6 on a lattice, whose few crowded nodes decide, 55 to 60 and 54 to 60 with the reduction).
 // The slabs of one sample range get workgroup numbers 8 apart so that they run on the same XCD: rows are not
 // aligned to cache lines, and the lines two neighbouring rows share are then fetched into that XCD's L2 once.
 #include "som_internal.hpp"
@@ -53,8 +56,7 @@ __global__ void __launch_bounds__(kFThreads) accumulate_f64_kernel(const float* 
     const int blk = blockIdx.x / (8 * nslabs), within = blockIdx.x % (8 * nslabs);
     const int slab = within / 8;
     const int64_t range = (int64_t)blk * 8 + (within % 8);
-    const int k0 = slab * ks;
-    const int kn = (k0 + ks <= K) ? ks : K - k0;                           // nodes of this slab (may be <= 0)
+    const int kn = (K - slab + nslabs - 1) / nslabs;                       // nodes of this slab: slab, slab + nslabs, ...
     const int64_t lo = range * rows_per_range;
     if (lo >= m) return;                                   // padding of the last block of 8 ranges (whole workgroup)
     int64_t hi = lo + rows_per_range;
@@ -88,6 +90,7 @@ __global__ void __launch_bounds__(kFThreads) accumulate_f64_kernel(const float* 
     int bq_next[U];
     load_bmus(lo + (int64_t)wave * 64 * U, bq_next);
     const int ldxu = (int)ldx * U;                                         // distance between a pass's rows
+    const unsigned recip = 0xffffffffu / (unsigned)nslabs + 1u;            // (exact for node numbers below 2^28: at most sixteen slabs)
     for (int64_t base = lo + (int64_t)wave * 64 * U; base < hi; base += (int64_t)kFThreads * U) {
         int bq[U];
 #pragma unroll
@@ -96,10 +99,11 @@ __global__ void __launch_bounds__(kFThreads) accumulate_f64_kernel(const float* 
 #pragma unroll
         for (int q = 0; q < U; ++q) {
             const int b = bq[q];
-            const bool in = b >= k0 && b < k0 + kn;
+            const unsigned ub = (unsigned)b, at = nslabs == 1 ? ub : __umulhi(ub, recip);      // b / nslabs
+            const bool in = ub < (unsigned)K && ub - at * (unsigned)nslabs == (unsigned)slab;
             unsigned long long todo = __ballot(in);                        // wave-uniform: lanes whose row is ours
             const float* xpass = X + (base + q) * ldx;
-            const int ncell = (b - k0) * DS;                                // this lane's row of P, if its sample is ours
+            const int ncell = (int)at * DS;                                 // this lane's row of P, if its sample is ours
             // Rows are taken off the mask with scalar instructions only (find-first-set, read-lane): no list in
             // LDS, no wait between a row's decoding and its load, so up to G row loads are in flight per wavefront.
             // The scalar unit is shared by the compute unit's wavefronts and this bookkeeping is what it is busy
@@ -200,9 +204,13 @@ __global__ void __launch_bounds__(kFThreads) accumulate_f64_kernel(const float* 
     }
     __syncthreads();
     // slab -> the range's slice [K][DS]
-    if (kn > 0) {
-        double* out = part + ((size_t)range * K + k0) * DS;
-        for (int c = tid; c < kn * DS; c += kFThreads) out[c] = P[c];
+    // (a row of at most 64 cells a wavefront at a time)
+    double* out = part + (size_t)range * K * DS;
+    if (nslabs == 1) {
+        for (int c = tid; c < K * DS; c += kFThreads) out[c] = P[c];
+    } else if (lane < DS) {
+#pragma unroll 4
+        for (int at = wave; at < kn; at += kFThreads / 64) out[(size_t)(at * nslabs + slab) * DS + lane] = P[at * DS + lane];
     }
 }
 
