@@ -12,7 +12,7 @@
 //                      d2[p][q]: every pair against 64 nodes near p first, the few pairs left against all nodes
 //   csr_*              degree count, exclusive scan, ascending neighbour lists
 //   bfs_kernel         one wavefront per source, frontier queue and distance row in LDS
-//   tree_hops_kernel   the same for spanning trees: lanes walk along the branches
+//   tree_tour_kernel, tree_hops_kernel   the same for spanning trees: the nodes in depth-first order with their depths, and minima of those
 #include "som_internal.hpp"
 
 #include <math.h>
@@ -149,7 +149,8 @@ __global__ void __launch_bounds__(256) boruvka_init_kernel(int K, int* __restric
     if (e == 0) state[0] = K;
 }
 
-// one wavefront per node v: cheapest edge to a node of another component
+// one wavefront per node v: cheapest edge to a node of another component, eight loads under way (each behind its component's test, a first
+// round at K = 1024 took 13.5 us instead of 7.8)
 __global__ void __launch_bounds__(256) boruvka_scan_kernel(const double* __restrict__ d2, int K, const int* __restrict__ comp,
                                                            const int* __restrict__ state, double* __restrict__ best_w,
                                                            int* __restrict__ best_u)
@@ -160,15 +161,24 @@ __global__ void __launch_bounds__(256) boruvka_scan_kernel(const double* __restr
     const int cv = comp[v];
     double bw = INFINITY;
     int bu = -1, blo = 0x7fffffff, bhi = 0x7fffffff;
-    for (int u = lane; u < K; u += 64) {
-        if (comp[u] == cv) continue;
-        const double w = d2[(size_t)v * K + u];
-        const int lo = v < u ? v : u, hi = v < u ? u : v;
-        if (bu < 0 || edge_before(w, lo, hi, bw, blo, bhi)) {
-            bw = w;
-            bu = u;
-            blo = lo;
-            bhi = hi;
+    for (int u0 = lane; u0 < K; u0 += 8 * 64) {
+        double w[8];
+        int c[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int u = u0 + 64 * t < K ? u0 + 64 * t : u0;
+            c[t] = comp[u];
+            w[t] = d2[(size_t)v * K + u];
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int u = u0 + 64 * t, lo = v < u ? v : u, hi = v < u ? u : v;
+            if (u < K && c[t] != cv && (bu < 0 || edge_before(w[t], lo, hi, bw, blo, bhi))) {
+                bw = w[t];
+                bu = u;
+                blo = lo;
+                bhi = hi;
+            }
         }
     }
 #pragma unroll
@@ -366,32 +376,19 @@ __global__ void __launch_bounds__(256) csr_degree_kernel(const unsigned char* __
     if (lane == 0) deg[v] = c;
 }
 
-// off[0 .. K]: where the nodes' lists begin; COUNT: off[K + 1] nodes of more than two neighbours (K: most nodes hang on hubs)
-template <bool COUNT>
+// off[0 .. K]: where the nodes' lists begin
 __global__ void __launch_bounds__(1024) csr_scan_kernel(const int* __restrict__ deg, int K, int* __restrict__ off)
 {
     __shared__ int part[1024];
-    __shared__ int branching, ends;                           // nodes of more than two neighbours, and of one
     const int tid = threadIdx.x;
     const int per = (K + 1023) / 1024;
-    int s = 0, more = 0, one = 0;
+    int s = 0;
     for (int t = 0; t < per; ++t) {
         const int v = tid * per + t;
-        if (v < K) {
-            s += deg[v];
-            if constexpr (COUNT) {
-                more += deg[v] > 2 ? 1 : 0;
-                one += deg[v] == 1 ? 1 : 0;
-            }
-        }
+        if (v < K) s += deg[v];
     }
-    if (COUNT && tid == 0) branching = ends = 0;
     part[tid] = s;
     __syncthreads();
-    if constexpr (COUNT) {
-        if (more) atomicAdd(&branching, more);
-        if (one) atomicAdd(&ends, one);
-    }
     for (int o = 1; o < 1024; o <<= 1) {
         const int add = (tid >= o) ? part[tid - o] : 0;
         __syncthreads();
@@ -406,10 +403,7 @@ __global__ void __launch_bounds__(1024) csr_scan_kernel(const int* __restrict__ 
             run += deg[v];
         }
     }
-    if (tid == 1023) {
-        off[K] = part[1023];
-        if constexpr (COUNT) off[K + 1] = ends > K / 2 ? K : branching;
-    }
+    if (tid == 1023) off[K] = part[1023];
 }
 
 __global__ void __launch_bounds__(256) csr_fill_kernel(const unsigned char* __restrict__ A, int K,
@@ -474,115 +468,174 @@ __device__ __forceinline__ void bfs_source(const int* __restrict__ off, const in
     }
 }
 
-// Where the walk over a spanning tree (below) has more sources than wavefronts that LDS lets run at once, it is the faster one only on
-// trees of long branches, and the breadth-first search on the others: both kernels are launched, and `pick` makes one of them end
-// at once.  Whole call, walk / breadth first, by the share of branching nodes at 2049 to 4096 nodes: none (nodes along a line) 0.59 to
-// 0.80; 1 to 2.4 % (maps after epochs of a large radius) 0.74 to 0.99, but 1.15 to 1.40 where they are hubs and most nodes hang on
-// them; 8 to 12 % (of a small radius) 0.99 to 1.17; 20 % and more (nodes that are data rows) 1.09 to 1.33.  2048 nodes, which is one round:
-// 0.54 to 0.99 on all of them.
-__device__ __forceinline__ bool long_branches(const int* off, int K) { return off[K + 1] <= K / 32; }
-
-template <bool PICK>                                      // (a graph that is no tree: false)
-__global__ void __launch_bounds__(64) bfs_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K,
-                                                 float* __restrict__ G)
+__global__ void __launch_bounds__(64) bfs_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K, float* __restrict__ G)
 {
-    if (PICK && long_branches(off, K)) return;
     extern __shared__ int bfs_lds[];
     bfs_source(off, nbr, K, blockIdx.x, bfs_lds, G);
 }
 
-// The same for a spanning tree: between two nodes there is one way, so nothing has to be claimed.  A lane walks on from its node to a
-// neighbour that is not where it came from, notes the distance and puts what else branches off on a stack in LDS, from which idle
-// lanes take; the sources of a workgroup share the lists, as 16-bit numbers in LDS.  A step is one LDS read: a node's
-// record holds its first two neighbours, and only a node with more (or a source with two) looks at the list.
-// Bound by latency: a tree of K nodes is up to K levels deep, and at each the breadth-first search goes queue -> list -> neighbour ->
-// claim, once per neighbour: 0.36 ms at K = 1024 (a map along a path, 10^7 x 50), with its lists in LDS as well; this
-// walk takes 0.18 ms.
-// (Weights that are no numbers can give edges that are no tree: more visits than nodes, or fewer, and the source is searched
-// breadth first instead.)
-constexpr int kTreeSources = 4;
+// Hop counts of a spanning tree.  With the nodes in depth-first order, the last common ancestor of the nodes at places p < q lies one above the
+// shallowest node of the places (p, q], or is the node at p itself; so a source's distances to all nodes are a running minimum of
+// depths along the order, to either side of it.  (Walks along the branches, a lane each, took a step of LDS latency a level:
+// 186 us for the trained map of 10^7 x 50 on 1024 nodes, 13 + 13 now; whole call for nodes along a line 347 and 136 us at K = 1024,
+// 3982 and 646 at 4096, for data rows as nodes 169 and 117, 991 and 472.)
+//
+// The order: every edge once in each direction, one behind the other around the tree (the Euler tour: behind (u, v) comes v's edge after the
+// one to u, in a circle), cut at node 0.  Places along the tour by pointer jumping (list ranking, Wyllie's), then depths by a sum over it.
+// One workgroup, bound by the latency of log2(2 K) rounds.  An edge's word holds where it points (END: nowhere) and how many edges on that
+// is; both change together and are true at any time, so a round needs no second copy.
+// tour[place]: node, depth from bit 16.  state[1]: whether the graph is one tree of all nodes (weights that are no numbers can give another).
 constexpr size_t kTreeLds = 160 * 1024;
+constexpr int kTourThreads = 1024;
+constexpr size_t kTourOwn = 1024;                          // what the kernel and its votes hold besides
+// bytes of LDS: per directed edge (2 (K - 1)) its word, its end and its way back; per node where its edges begin
+__host__ __device__ constexpr size_t tour_bytes(int K) { return (size_t)K * 18 + 4; }
 
-// bytes of LDS: records ([K] offset, degree, two neighbours) and list ([2 (K - 1)] neighbours), and per source stack and distances
-__host__ __device__ constexpr size_t tree_list_bytes(int K) { return (size_t)K * 12; }
-__host__ __device__ constexpr size_t tree_source_bytes(int K) { return ((size_t)K * 6 + 3) / 4 * 4; }
+__global__ void __launch_bounds__(kTourThreads) tree_tour_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K,
+                                                                unsigned short* __restrict__ seq, unsigned int* __restrict__ tour,
+                                                                int* __restrict__ state)
+{
+    extern __shared__ unsigned int tour_lds[];
+    const int E = 2 * (K - 1), tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    unsigned int* const word = tour_lds;                                               // [E] next edge, edges up to there from bit 16
+    unsigned short* const end = reinterpret_cast<unsigned short*>(word + E);           // [E]
+    unsigned short* const back = end + E;                                              // [E]
+    unsigned short* const begin = back + E;                                            // [K + 1]
+    __shared__ int2 sums[kTourThreads / 64];
+    constexpr unsigned kEnd = 0xffffu;                     // (E <= 18202)
+    bool tree = off[K] == E;
+    if (tree) {                                            // (the same for all)
+        for (int v = tid; v <= K; v += kTourThreads) begin[v] = (unsigned short)off[v];
+        for (int e = tid; e < E; e += kTourThreads) end[e] = (unsigned short)nbr[e];
+    }
+    __syncthreads();
+    if (tree) {
+        for (int v = tid; v < K; v += kTourThreads) tree = tree && (K == 1 || begin[v + 1] > begin[v]);
+        for (int e = tid; e < E; e += kTourThreads) {
+            int u = 0, top = K;                            // whose edge it is: the last node that begins at or before it
+            while (top - u > 1) {
+                const int mid = (u + top) >> 1;
+                if ((int)begin[mid] <= e) u = mid;
+                else top = mid;
+            }
+            const int v = end[e], first = begin[v], last = begin[v + 1];
+            int t = first, above = last;                   // v's edge to u (lists are in ascending order)
+            while (above - t > 1) {
+                const int mid = (t + above) >> 1;
+                if ((int)end[mid] <= u) t = mid;
+                else above = mid;
+            }
+            back[e] = (unsigned short)t;
+            const int next = t + 1 < last ? t + 1 : first;
+            word[e] = (next == 0 ? kEnd : (unsigned)next) | 1u << 16;      // (node 0's first edge is edge 0)
+        }
+    }
+    tree = __syncthreads_and(tree);
+    for (int reach = 1; tree && reach < E; reach <<= 1) {
+        for (int e = tid; e < E; e += kTourThreads) {
+            const unsigned w = word[e], n = w & 0xffffu;
+            if (n != kEnd) {
+                const unsigned x = word[n];
+                word[e] = (x & 0xffffu) | ((w >> 16) + (x >> 16)) << 16;
+            }
+        }
+        __syncthreads();
+    }
+    if (tree)
+        for (int e = tid; e < E; e += kTourThreads) tree = tree && (word[e] & 0xffffu) == kEnd;
+    tree = __syncthreads_and(tree);
+    if (tid == 0) state[1] = tree ? 1 : 0;
+    if (!tree) return;
+    // ends along the tour, and whether an edge leads away from node 0 (its way back comes later)
+    for (int e = tid; e < E; e += kTourThreads) {
+        const unsigned left = word[e] >> 16;
+        seq[E - (int)left] = (unsigned short)(end[e] | (left > word[back[e]] >> 16 ? 0x8000u : 0u));
+    }
+    __syncthreads();
+    // every thread takes a run of the tour: steps away less steps back, and steps away
+    const int per = (E + kTourThreads - 1) / kTourThreads, lo = tid * per < E ? tid * per : E, hi = lo + per < E ? lo + per : E;
+    int2 mine = make_int2(0, 0);
+    for (int i = lo; i < hi; ++i) {
+        const bool away = (seq[i] & 0x8000u) != 0u;
+        mine.x += away ? 1 : -1;
+        mine.y += away ? 1 : 0;
+    }
+    int2 at = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(at.x, o), y = __shfl_up(at.y, o);
+        at.x += lane >= o ? x : 0;
+        at.y += lane >= o ? y : 0;
+    }
+    if (lane == 63) sums[wave] = at;
+    __syncthreads();
+    int depth = at.x - mine.x, place = at.y - mine.y;
+    for (int w = 0; w < wave; ++w) {
+        depth += sums[w].x;
+        place += sums[w].y;
+    }
+    if (tid == 0) tour[0] = 0u;
+    for (int i = lo; i < hi; ++i) {
+        const unsigned v = seq[i];
+        depth += (v & 0x8000u) ? 1 : -1;
+        if (v & 0x8000u) tour[++place] = (v & 0x7fffu) | (unsigned)depth << 16;
+    }
+}
+
+// A wavefront a source, sixty-four places at a time; the row goes through LDS so that its lines are written whole.
+constexpr int kTreeSources = 4;
+__host__ __device__ constexpr size_t tree_source_bytes(int K) { return ((size_t)K * 6 + 3) / 4 * 4; }      // (of a search; a row takes four a node)
 
 __global__ void __launch_bounds__(64 * kTreeSources) tree_hops_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K,
-                                                                      float* __restrict__ G, bool pick)
+                                                                      const unsigned int* __restrict__ tour, const int* __restrict__ state,
+                                                                      float* __restrict__ G)
 {
-    if (pick && !long_branches(off, K)) return;
     extern __shared__ unsigned int tree_lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int src = blockIdx.x * (int)(blockDim.x >> 6) + wave;
-    uint2* node = reinterpret_cast<uint2*>(tree_lds);                                  // [K] offset and degree; first and second neighbour
-    unsigned short* list = reinterpret_cast<unsigned short*>(tree_lds + 2 * K);        // [2 K]
-    unsigned int* stack = tree_lds + 3 * K + wave * (tree_source_bytes(K) / 4);        // [K] node, where from above bit 16
-    unsigned short* dist = reinterpret_cast<unsigned short*>(stack + K);               // [K]
-    constexpr unsigned kNowhere = 0xffffu;                 // (K <= 12000)
-    const int nnz = off[K];                                                            // 2 (K - 1)
-    for (int v = threadIdx.x; v < K; v += blockDim.x) {
-        const int o = off[v], deg = off[v + 1] - o;
-        const unsigned n0 = deg > 0 ? (unsigned)nbr[o] : kNowhere, n1 = deg > 1 ? (unsigned)nbr[o + 1] : kNowhere;
-        node[v] = make_uint2((unsigned)o | (unsigned)deg << 16, n0 | n1 << 16);
-    }
-    for (int e = threadIdx.x; e < nnz && e < 2 * K; e += blockDim.x) list[e] = (unsigned short)nbr[e];
-    __syncthreads();
-    if (src >= K) return;
-    unsigned v = lane == 0 ? (unsigned)src : kNowhere, from = kNowhere, d = 0;
-    unsigned pending = 0;
-    int visits = 0;
-    while (nnz == 2 * (K - 1) && visits <= K) {
-        const bool active = v != kNowhere;
-        const uint2 r = node[active ? v : 0u];
-        visits += (int)__popcll(__ballot(active));
-        if (active) dist[v] = (unsigned short)d;
-        const unsigned n0 = r.y & 0xffffu, n1 = r.y >> 16, deg = r.x >> 16;
-        const unsigned next = !active ? kNowhere : n0 != from ? n0 : n1;
-        unsigned left = active && (deg > 2 || (n0 != from && n1 != from && deg == 2)) ? deg : 0u;
-        if (__any(left > 0)) {
-            unsigned e = r.x & 0xffffu;
-            do {
-                bool put = false;
-                unsigned u = 0;
-                if (left > 0) {
-                    u = list[e];
-                    ++e;
-                    --left;
-                    put = u != from && u != next;
-                }
-                const unsigned long long mask = __ballot(put);
-                if (put) {
-                    const unsigned at = pending + __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
-                    if (at < (unsigned)K) stack[at] = u | v << 16;
-                }
-                pending = pending + (unsigned)__popcll(mask) < (unsigned)K ? pending + (unsigned)__popcll(mask) : (unsigned)K;
-            } while (__any(left > 0));
-        }
-        from = v;
-        v = next;
-        ++d;
-        const unsigned long long idle = __ballot(v == kNowhere);
-        if (pending > 0) {
-            __builtin_amdgcn_wave_barrier();
-            const unsigned place = __builtin_amdgcn_mbcnt_hi((unsigned)(idle >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)idle, 0));
-            if (v == kNowhere && place < pending) {
-                const unsigned s = stack[pending - 1 - place];
-                v = s & 0xffffu;
-                from = s >> 16;
-                d = (unsigned)dist[from] + 1;
-            }
-            const unsigned taken = (unsigned)__popcll(idle);
-            pending = pending > taken ? pending - taken : 0;
-        } else if (idle == ~0ull) {
-            break;
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    if (visits != K) {
-        bfs_source(off, nbr, K, src, reinterpret_cast<int*>(stack), G);
+    if (src >= K) return;                                     // (no barrier below)
+    unsigned int* const own = tree_lds + wave * (tree_source_bytes(K) / 4);
+    if (state[1] == 0) {
+        bfs_source(off, nbr, K, src, reinterpret_cast<int*>(own), G);
         return;
     }
-    for (int u = lane; u < K; u += 64) G[(size_t)src * K + u] = (float)dist[u];
+    float* const row = reinterpret_cast<float*>(own);
+    const unsigned here = tour[src];
+    const int u = (int)(here & 0xffffu), du = (int)(here >> 16);
+    if (lane == 0) row[u] = 0.0f;
+    auto lowest = [&](int x) {                                // of this lane and those before it
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(x, o);
+            x = lane >= o && y < x ? y : x;
+        }
+        return x;
+    };
+    constexpr int kFar = 0x7fff;
+    int low = du;                                             // depth of the common ancestor so far
+    for (int q0 = src + 1; q0 < K; q0 += 64) {
+        const int q = q0 + lane;
+        const unsigned t = tour[q < K ? q : K - 1];
+        const int d = (int)(t >> 16);
+        int x = lowest(q < K ? d - 1 : kFar);
+        x = x < low ? x : low;
+        if (q < K) row[t & 0xffffu] = (float)(du + d - 2 * x);
+        low = __shfl(x, 63);
+    }
+    low = du - 1;                                             // one above the shallowest of the places passed
+    for (int q0 = src - 1; q0 >= 0; q0 -= 64) {
+        const int q = q0 - lane;
+        const unsigned t = tour[q >= 0 ? q : 0];
+        const int d = (int)(t >> 16), x = lowest(q >= 0 ? d - 1 : kFar);
+        int before = __shfl_up(x, 1);
+        before = lane > 0 && before < low ? before : low;
+        const int c = d < before ? d : before;
+        if (q >= 0) row[t & 0xffffu] = (float)(du + d - 2 * c);
+        const int all = __shfl(x, 63);
+        low = all < low ? all : low;
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (int v = lane; v < K; v += 64) G[(size_t)u * K + v] = row[v];
 }
 
 } // namespace som
@@ -616,8 +669,8 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
     double* d2 = (double*)ctx->topo_blob;
     double* best_w = d2 + kk;
     int* deg = (int*)(best_w + K);
-    int* off = deg + K;                                  // K + 2 entries
-    int* comp = off + K + 2;
+    int* off = deg + K;                                  // K + 1 entries
+    int* comp = off + K + 1;
     int* best_u = comp + K;
     int* state = best_u + K;                             // 4 entries
     int* nbr = state + 4;                                // at most K * K entries
@@ -650,39 +703,32 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
         hipLaunchKernelGGL(rng_verify_kernel, dim3(K), dim3(256), 0, ctx->stream, d2, K, A);
     }
     if (int rc = check_hip(ctx, hipGetLastError(), "edge kernel launch")) return rc;
-    int sources = 0;                                     // of a workgroup of the walk over a spanning tree (0: none)
-    bool pick = false;
-    if (kind == SOM_TOPOLOGY_MST && tree_list_bytes(K) + tree_source_bytes(K) <= kTreeLds) {
-        // as many sources to a workgroup as give a compute unit most wavefronts
-        size_t most = 0;
-        for (int n = 1; n <= kTreeSources; ++n) {
-            const size_t bytes = tree_list_bytes(K) + n * tree_source_bytes(K), waves = bytes <= kTreeLds ? n * (kTreeLds / bytes) : 0;
-            if (waves >= most && waves > 0) {
-                most = waves;
-                sources = n;
-            }
-        }
-        pick = most * (size_t)ctx->units < (size_t)K;
-    }
     hipLaunchKernelGGL(csr_degree_kernel, dim3((K + 3) / 4), dim3(256), 0, ctx->stream, A, K, deg);
-    hipLaunchKernelGGL(pick ? csr_scan_kernel<true> : csr_scan_kernel<false>, dim3(1), dim3(1024), 0, ctx->stream, deg, K, off);
+    hipLaunchKernelGGL(csr_scan_kernel, dim3(1), dim3(1024), 0, ctx->stream, deg, K, off);
     hipLaunchKernelGGL(csr_fill_kernel, dim3((K + 3) / 4), dim3(256), 0, ctx->stream, A, K, off, nbr);
     if (int rc = check_hip(ctx, hipGetLastError(), "adjacency launch")) return rc;
-    if (sources > 0) {
-        const size_t lds = tree_list_bytes(K) + sources * tree_source_bytes(K);
+    if (kind == SOM_TOPOLOGY_MST && tour_bytes(K) + kTourOwn <= kTreeLds) {
+        const size_t tour_lds = tour_bytes(K);
+        int sources = kTreeSources;                      // of a workgroup
+        while (sources * tree_source_bytes(K) > kTreeLds) --sources;
+        const size_t lds = sources * tree_source_bytes(K);
+        if (tour_lds > 48 * 1024) {
+            if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(tree_tour_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kTreeLds - kTourOwn)), "raising the dynamic LDS limit")) return rc;
+        }
         if (lds > 48 * 1024) {
             if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(tree_hops_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTreeLds), "raising the dynamic LDS limit")) return rc;
         }
-        hipLaunchKernelGGL(tree_hops_kernel, dim3((K + sources - 1) / sources), dim3(64 * sources), lds, ctx->stream, off, nbr, K, G, pick);
-        if (int rc = check_hip(ctx, hipGetLastError(), "hop-count launch")) return rc;
-        if (!pick) return SOM_OK;
+        // (best_u and comp have no more use: the order, and in front of it what the tour passes, 2 (K - 1) 16-bit words)
+        hipLaunchKernelGGL(tree_tour_kernel, dim3(1), dim3(kTourThreads), tour_lds, ctx->stream, off, nbr, K, (unsigned short*)comp, (unsigned int*)best_u, state);
+        if (int rc = check_hip(ctx, hipGetLastError(), "tree order launch")) return rc;
+        hipLaunchKernelGGL(tree_hops_kernel, dim3((K + sources - 1) / sources), dim3(64 * sources), lds, ctx->stream, off, nbr, K, (const unsigned int*)best_u, state, G);
+        return check_hip(ctx, hipGetLastError(), "hop-count launch");
     }
     // dist[K] int32 + queue[K] uint16 per wavefront (72 KB at the 12000-node limit)
     const size_t bfs_lds_bytes = ((size_t)K * 6 + 3) / 4 * 4;
-    auto search = pick ? bfs_kernel<true> : bfs_kernel<false>;
     if (bfs_lds_bytes > 48 * 1024) {
-        if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(search), hipFuncAttributeMaxDynamicSharedMemorySize, 12000 * 6), "raising the dynamic LDS limit")) return rc;
+        if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(bfs_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 12000 * 6), "raising the dynamic LDS limit")) return rc;
     }
-    hipLaunchKernelGGL(search, dim3(K), dim3(64), bfs_lds_bytes, ctx->stream, off, nbr, K, G);
+    hipLaunchKernelGGL(bfs_kernel, dim3(K), dim3(64), bfs_lds_bytes, ctx->stream, off, nbr, K, G);
     return check_hip(ctx, hipGetLastError(), "hop-count launch");
 }

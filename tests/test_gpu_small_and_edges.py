@@ -418,10 +418,11 @@ def test_bmu_where_squares_of_the_parts_underflow(som, m, K, D):
 
 @pytest.mark.parametrize("shape,K", [("chain", 2), ("chain", 3), ("chain", 65), ("chain", 1500), ("star", 4), ("star", 70), ("star", 300),
                                      ("comb", 66), ("comb", 513), ("random", 1), ("random", 1025), ("random", 2500),
-                                     # the largest map that is always walked; above, long branches are walked and others searched
+                                     # a wavefront's and a workgroup's share of the tour, and one edge more
+                                     ("random", 33), ("random", 34), ("star", 513), ("random", 513), ("chain", 514), ("hubs", 1026),
                                      ("random", 2048), ("chain", 2049), ("random", 2049), ("hubs", 2048), ("hubs", 2049)])
 def test_spanning_tree_hops_of_every_shape(som, shape, K):
-    """The walk over a spanning tree: long branches, nodes with very many branches, both mixed, and sizes around a wavefront."""
+    """The order of a spanning tree's nodes: long branches, nodes with very many branches, both mixed, and sizes around a wavefront."""
     rng = np.random.default_rng(K)
     if shape == "chain":                                    # along a line, in a mixed order
         W = (np.sort(rng.uniform(0, 10 * K, K))[rng.permutation(K)])[:, None]
@@ -444,8 +445,7 @@ def test_spanning_tree_hops_of_every_shape(som, shape, K):
 @pytest.mark.parametrize("shape", ["random", "chain"])
 def test_spanning_tree_where_a_node_holds_no_number(som, shape):
     """More nodes than Boruvka's rounds take, one of them NaN: no distance of its own is below another, so it stays apart, and
-    the edges that are left are no tree of all nodes.  Their hop counts are searched breadth first, from the start or (a chain)
-    by the walk that finds it out."""
+    the edges that are left are no tree of all nodes.  Their hop counts are searched breadth first."""
     from scipy.sparse import csr_matrix
     from scipy.sparse.csgraph import shortest_path
     K, bad = 4100, 77
@@ -463,9 +463,9 @@ def test_spanning_tree_where_a_node_holds_no_number(som, shape):
     assert np.array_equal(T[src], hops.astype(np.float32))
 
 
-@pytest.mark.parametrize("K", [9102, 9103])
+@pytest.mark.parametrize("K", [9045, 9046, 9102, 9103])
 def test_spanning_tree_hops_at_the_limit_of_lds(som, K):
-    """A chain of the most nodes whose records, list and stack fit 160 KB, and of one more, which goes breadth first."""
+    """A chain of the most nodes whose tour fits 160 KB, and of more, which go breadth first."""
     place = torch.randperm(K, generator=torch.Generator().manual_seed(K)).cuda()
     T = som.som_topology(place.float()[:, None].contiguous(), "mst")
     for lo in range(0, K, 1024):
