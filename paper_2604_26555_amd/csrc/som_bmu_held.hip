@@ -164,7 +164,9 @@ __global__ void __launch_bounds__(256) bmu_held_prep_kernel(const float* __restr
     }
 }
 
-template <int H>
+// H: units of 32 features; SHORT: the last one has sixteen at most, so that its other sixteen need no MFMA of first parts (10^6 x 200 on 1024
+// nodes, one of 21: 853 -> 842 us; zeros draw little power, which is what bounds the rest)
+template <int H, bool SHORT>
 struct HeldArgs {
     // [block of 32 rows][unit][first parts of 16 features | of the other 16 | fp6, 16 of a lane's 24 bytes], then [unit][fp6, the other 8]: in the
     // order of the lanes, rounded up to whole kilobytes
@@ -175,8 +177,8 @@ struct HeldArgs {
 
 // Blocks [b_lo, b_hi) (b_lo even) for the samples of tile `tile`.  CAND: the samples are the entries of the re-decision list, and every
 // node that reaches the entry's cut is appended to its record; the scores are those of the search bit for bit.
-template <int H, bool CAND>
-__device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, const HeldArgs<H>& hp, int64_t tile, int split, int b_lo, int b_hi,
+template <int H, bool SHORT, bool CAND>
+__device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, const HeldArgs<H, SHORT>& hp, int64_t tile, int split, int b_lo, int b_hi,
                                           int64_t total, char* lds)
 {
     constexpr int MS = held_ms(H);
@@ -232,7 +234,7 @@ __device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, c
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const float4 t = load4(row[mb] + start_of(u, kb, h));
+                    const float4 t = SHORT && u == H - 1 && kb == 1 ? make_float4(0.f, 0.f, 0.f, 0.f) : load4(row[mb] + start_of(u, kb, h));
                     v[mb][u][kb][4 * h + 0] = t.x;
                     v[mb][u][kb][4 * h + 1] = t.y;
                     v[mb][u][kb][4 * h + 2] = t.z;
@@ -262,6 +264,7 @@ __device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, c
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
+                    if (SHORT && u == H - 1 && kb == 1) continue;
                     const int start = start_of(u, kb, h);
                     const float4 c = load4(centre + start);
                     const float cc[4] = {c.x, c.y, c.z, c.w};
@@ -411,7 +414,8 @@ __device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, c
     };
     const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     const int scale_a = g == 0 ? 127 + kTopBit - 2 : 127 - 3, scale_b = g == 0 ? 127 - 3 : 127 + kTopBit - 2;
-    constexpr int PARTS = 3 * 8 * MS, MFMAS = GROUPS * MS;
+    constexpr int USED = SHORT ? GROUPS - 1 : GROUPS;          // (the last group's place in the schedule stays)
+    constexpr int PARTS = 3 * 8 * MS, MFMAS = USED * MS;
     auto block = [&](floatx16 (&cur)[MS], const floatx16 (&prev)[MS], auto prev_par, int b) {
         const char* base = lds + (b & 1) * BLK;
         const char* next = lds + ((b + 1) & 1) * BLK;
@@ -424,6 +428,7 @@ __device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, c
             const int u = small_products ? i : (i - H) >> 1, kb = (i - H) & 1;
 #pragma unroll
             for (int mb = 0; mb < MS; ++mb) {
+                if (i >= USED) continue;
                 if (small_products) {
                     cur[mb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp6_operand(fa[i % AHEAD]), fp6_operand(xq[mb][u]), i == 0 ? zero16 : cur[mb], 2,
                                                                               2, 0, scale_a, 0, scale_b);
@@ -437,7 +442,7 @@ __device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, c
                 if (mb + 1 < MS) __builtin_amdgcn_sched_barrier(0);
             }
             if (i + AHEAD < GROUPS) {
-                read(base, i + AHEAD);
+                if (i + AHEAD < USED) read(base, i + AHEAD);
             } else if (i + AHEAD == GROUPS) {
                 // Everything of this block has been read: its place goes to the block after next, and the next one, on its way
                 // since a block ago, has to be there.
@@ -511,8 +516,8 @@ __device__ __forceinline__ void held_tile(const BmuArgs& a, const WideArgs& p, c
     if (i < total && (MS > 1 || g == 0)) write_winners(a, p, split, i, won, where, fmaxf(m0, m1), un * uw);
 }
 
-template <int H>
-__device__ __forceinline__ void held_search(const BmuArgs& a, const WideArgs& p, const HeldArgs<H>& hp, char* lds)
+template <int H, bool SHORT>
+__device__ __forceinline__ void held_search(const BmuArgs& a, const WideArgs& p, const HeldArgs<H, SHORT>& hp, char* lds)
 {
     const int64_t blk = blockIdx.x / (8 * p.splits);
     const int within = (int)(blockIdx.x % (8 * p.splits));
@@ -520,12 +525,12 @@ __device__ __forceinline__ void held_search(const BmuArgs& a, const WideArgs& p,
     const int split = within / 8;
     if (tile * held_tile_rows(H) >= a.m) return;
     const int b_lo = split * p.per_split, b_hi = b_lo + p.per_split < hp.blocks ? b_lo + p.per_split : hp.blocks;
-    held_tile<H, false>(a, p, hp, tile, split, b_lo, b_hi, a.m, lds);
+    held_tile<H, SHORT, false>(a, p, hp, tile, split, b_lo, b_hi, a.m, lds);
 }
 
 // A fixed grid walks the (tile of the list, range of blocks) units: as many ranges as keep it busy.
-template <int H>
-__device__ __forceinline__ void held_candidates(const BmuArgs& a, const WideArgs& p, const HeldArgs<H>& hp, char* lds)
+template <int H, bool SHORT>
+__device__ __forceinline__ void held_candidates(const BmuArgs& a, const WideArgs& p, const HeldArgs<H, SHORT>& hp, char* lds)
 {
     const unsigned int count = a.scal[a.slot];
     if (count <= p.cand_min) return;
@@ -537,31 +542,33 @@ __device__ __forceinline__ void held_candidates(const BmuArgs& a, const WideArgs
     ranges = (hp.blocks + per - 1) / per;
     for (int64_t u = blockIdx.x; u < (int64_t)tiles * ranges; u += gridDim.x) {
         const int b_lo = (int)(u % ranges) * per, b_hi = b_lo + per < hp.blocks ? b_lo + per : hp.blocks;
-        held_tile<H, true>(a, p, hp, u / ranges, 0, b_lo, b_hi, (int64_t)count, lds);
+        held_tile<H, SHORT, true>(a, p, hp, u / ranges, 0, b_lo, b_hi, (int64_t)count, lds);
         __syncthreads();
     }
 }
 
-// (overloads of the wide search's two kernels, one for each number of units)
-#define SOM_HELD_KERNELS(H)                                                                                                                        \
+// (overloads of the wide search's two kernels, one for each number of units and kind of the last)
+#define SOM_HELD_KERNELS(H, SHORT)                                                                                                                 \
     __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(held_waves(H), held_waves(H))))                                \
-    bmu_wide_split_kernel(const BmuArgs a, const WideArgs p, const HeldArgs<H> hp)                                                                 \
+    bmu_wide_split_kernel(const BmuArgs a, const WideArgs p, const HeldArgs<H, SHORT> hp)                                                          \
     {                                                                                                                                              \
         extern __shared__ float4 held_lds[];                                                                                                       \
-        held_search<H>(a, p, hp, reinterpret_cast<char*>(held_lds));                                                                               \
+        held_search(a, p, hp, reinterpret_cast<char*>(held_lds));                                                                                  \
     }                                                                                                                                              \
     __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(held_waves(H), held_waves(H))))                                \
-    bmu_wide_split_cand_kernel(const BmuArgs a, const WideArgs p, const HeldArgs<H> hp)                                                            \
+    bmu_wide_split_cand_kernel(const BmuArgs a, const WideArgs p, const HeldArgs<H, SHORT> hp)                                                     \
     {                                                                                                                                              \
         extern __shared__ float4 held_lds[];                                                                                                       \
-        held_candidates<H>(a, p, hp, reinterpret_cast<char*>(held_lds));                                                                           \
+        held_candidates(a, p, hp, reinterpret_cast<char*>(held_lds));                                                                              \
     }
-SOM_HELD_KERNELS(3)
-SOM_HELD_KERNELS(4)
-SOM_HELD_KERNELS(5)
-SOM_HELD_KERNELS(6)
-SOM_HELD_KERNELS(7)
-SOM_HELD_KERNELS(8)
+#define SOM_HELD_BOTH(H) SOM_HELD_KERNELS(H, false) SOM_HELD_KERNELS(H, true)
+SOM_HELD_BOTH(3)
+SOM_HELD_BOTH(4)
+SOM_HELD_BOTH(5)
+SOM_HELD_BOTH(6)
+SOM_HELD_BOTH(7)
+SOM_HELD_BOTH(8)
+#undef SOM_HELD_BOTH
 #undef SOM_HELD_KERNELS
 
 // ---------------------------------------------------------------------------------------------------------
@@ -613,23 +620,23 @@ void bmu_held_plan(WideArgs& p, const BmuPrep& prep, int64_t m, int32_t K, int32
     p.set_splits(m, best, steps, (tiles + 7) / 8 * 8 * best);
 }
 
-template <int H>
-static HeldArgs<H> held_args(const BmuPrep& prep, const WideArgs& p, const BmuArgs& a)
+template <int H, bool SHORT>
+static HeldArgs<H, SHORT> held_args(const BmuPrep& prep, const BmuArgs& a)
 {
-    HeldArgs<H> h{};
+    HeldArgs<H, SHORT> h{};
     h.blob = (const char*)prep.stage16;
     h.hats = (const float*)(h.blob + held_blob(prep.kpad, a.D));
     h.blocks = (a.K + 31) / 32;
     return h;
 }
 
-template <int H>
+template <int H, bool SHORT>
 static int launch_held(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, const WideArgs& p, bool cand)
 {
     constexpr size_t lds = 2 * (size_t)held_block_bytes(H) + (4 * 64 + 32 * H) * sizeof(float);
     static_assert(lds <= 65536, "offsets of global_load_lds below 64 KB");
-    const HeldArgs<H> h = held_args<H>(prep, p, a);
-    using Kernel = void (*)(const BmuArgs, const WideArgs, const HeldArgs<H>);
+    const HeldArgs<H, SHORT> h = held_args<H, SHORT>(prep, a);
+    using Kernel = void (*)(const BmuArgs, const WideArgs, const HeldArgs<H, SHORT>);
     const Kernel search = bmu_wide_split_kernel, candidates = bmu_wide_split_cand_kernel;
     if (cand)
         hipLaunchKernelGGL(candidates, dim3(256 * held_waves(H)), dim3(kHThreads), lds, ctx->stream, a, p, h);
@@ -640,13 +647,20 @@ static int launch_held(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, cons
 
 int bmu_held_launch(som_ctx* ctx, const BmuPrep& prep, const BmuArgs& a, const WideArgs& p, bool cand)
 {
-    switch (held_units(a.D)) {
-    case 3: return launch_held<3>(ctx, prep, a, p, cand);
-    case 4: return launch_held<4>(ctx, prep, a, p, cand);
-    case 5: return launch_held<5>(ctx, prep, a, p, cand);
-    case 6: return launch_held<6>(ctx, prep, a, p, cand);
-    case 7: return launch_held<7>(ctx, prep, a, p, cand);
-    case 8: return launch_held<8>(ctx, prep, a, p, cand);
+    const int last = (a.D - 1) % 32 + 1;                       // features of the last unit
+    switch (2 * held_units(a.D) + (last <= 16 ? 1 : 0)) {
+    case 6: return launch_held<3, false>(ctx, prep, a, p, cand);
+    case 7: return launch_held<3, true>(ctx, prep, a, p, cand);
+    case 8: return launch_held<4, false>(ctx, prep, a, p, cand);
+    case 9: return launch_held<4, true>(ctx, prep, a, p, cand);
+    case 10: return launch_held<5, false>(ctx, prep, a, p, cand);
+    case 11: return launch_held<5, true>(ctx, prep, a, p, cand);
+    case 12: return launch_held<6, false>(ctx, prep, a, p, cand);
+    case 13: return launch_held<6, true>(ctx, prep, a, p, cand);
+    case 14: return launch_held<7, false>(ctx, prep, a, p, cand);
+    case 15: return launch_held<7, true>(ctx, prep, a, p, cand);
+    case 16: return launch_held<8, false>(ctx, prep, a, p, cand);
+    case 17: return launch_held<8, true>(ctx, prep, a, p, cand);
     }
     return fail(ctx, SOM_EINVAL, "no kernel for held rows of %d features", a.D);
 }

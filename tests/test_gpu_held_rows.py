@@ -90,7 +90,7 @@ def draw(m, K, D, seed, noise=0.3):
     return X, W.contiguous()
 
 
-@pytest.mark.parametrize("D", [65, 68, 96, 97, 99, 128, 129, 160, 161, 192, 193, 200, 224, 225, 255, 256])
+@pytest.mark.parametrize("D", [65, 68, 80, 81, 96, 97, 99, 128, 129, 160, 161, 192, 193, 200, 224, 225, 240, 241, 255, 256])
 def test_units_and_tiles(som, D):
     """Rows that end anywhere in a unit of 32 features, maps that end anywhere in a block of 32 or a stage of 128 nodes, tiles that
     are not full, one block, two and an odd number of them; the sizes where several workgroups share a tile's nodes, and where not."""
