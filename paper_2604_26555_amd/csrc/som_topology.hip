@@ -294,8 +294,10 @@ __global__ void __launch_bounds__(256) rng_near_kernel(const double* __restrict_
     near[(size_t)p * kNear + lane] = br;
 }
 
-// one workgroup per lower end p; thread -> upper ends q = tid, tid + 256, ...
-__global__ void __launch_bounds__(256) rng_prefilter_kernel(const double* __restrict__ d2, int K,
+// one workgroup per lower end p; thread -> upper ends q = tid, tid + 512, ...; eight of the near nodes' distances at a time, a trip to L2 each.
+// K = 1024, the map of 4 * 10^7 x 50, 24 us (44 with one at a time and half as many threads), data rows as nodes 35 (66); K = 4096 197 (386)
+constexpr int kPrefilterThreads = 512;
+__global__ void __launch_bounds__(kPrefilterThreads) rng_prefilter_kernel(const double* __restrict__ d2, int K,
                                                             const int* __restrict__ near, unsigned char* __restrict__ A)
 {
     __shared__ int nr_in[kNear], nr[kNear];
@@ -317,14 +319,18 @@ __global__ void __launch_bounds__(256) rng_prefilter_kernel(const double* __rest
         dpr[rank] = mine;
     }
     __syncthreads();
-    for (int q = tid; q < K; q += 256) {
+    for (int q = tid; q < K; q += kPrefilterThreads) {
         if (q == p) A[(size_t)p * K + p] = 0;
         if (q <= p) continue;
         const double lim = rp[q];
         bool blocked = false;
-        for (int o = 0; o < kNear && !blocked; ++o) {
+        for (int o = 0; o < kNear && !blocked; o += 8) {
             if (!(dpr[o] < lim)) break;                       // sorted: no later node is closer to p than the pair is long
-            blocked = d2[(size_t)nr[o] * K + q] < lim;
+            double v[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) v[t] = d2[(size_t)(nr[o + t] < 0 ? 0 : nr[o + t]) * K + q];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) blocked = blocked || (dpr[o + t] < lim && v[t] < lim);
         }
         const unsigned char keep = blocked ? 0 : 1;
         A[(size_t)p * K + q] = keep;
@@ -333,12 +339,14 @@ __global__ void __launch_bounds__(256) rng_prefilter_kernel(const double* __rest
 }
 
 // one workgroup per lower end p; a wavefront takes the surviving pairs of 64 upper ends at a time, all its lanes
-// scan the third nodes of one pair together
-__global__ void __launch_bounds__(256) rng_verify_kernel(const double* __restrict__ d2, int K, unsigned char* __restrict__ A)
+// scan the third nodes of one pair together, 512 of them with their loads under way (256, and four wavefronts instead of
+// eight: K = 1024 45 us, 12 this way; K = 4096 673 and 221)
+constexpr int kVerifyThreads = 512;
+__global__ void __launch_bounds__(kVerifyThreads) rng_verify_kernel(const double* __restrict__ d2, int K, unsigned char* __restrict__ A)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, p = blockIdx.x;
     const double* rp = d2 + (size_t)p * K;
-    for (int qb = wave * 64; qb < K; qb += 256) {
+    for (int qb = wave * 64; qb < K; qb += kVerifyThreads) {
         const int q = qb + lane;
         const bool alive = q > p && q < K && A[(size_t)p * K + q] != 0;
         unsigned long long mask = __ballot(alive);
@@ -349,12 +357,16 @@ __global__ void __launch_bounds__(256) rng_verify_kernel(const double* __restric
             const double* rq = d2 + (size_t)qq * K;
             bool found = false;
             // r = p and r = q give max = d2[p][q] itself, never strictly smaller: no masking needed
-            for (int r0 = 0; r0 < K; r0 += 4 * 64) {
+            for (int r0 = 0; r0 < K; r0 += 8 * 64) {
+                double a[8], c[8];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int r = r0 + 64 * u + lane;
-                    if (r < K) found = found || (fmax(rp[r], rq[r]) < lim);
+                for (int u = 0; u < 8; ++u) {
+                    const int r = r0 + 64 * u + lane < K ? r0 + 64 * u + lane : K - 1;
+                    a[u] = rp[r];
+                    c[u] = rq[r];
                 }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) found = found || (fmax(a[u], c[u]) < lim);
                 if (__any(found)) break;
             }
             if (__any(found) && lane == 0) {
@@ -422,56 +434,86 @@ __global__ void __launch_bounds__(256) csr_fill_kernel(const unsigned char* __re
     }
 }
 
-// Hop counts from source = blockIdx.x to every node: one wavefront per source, no barriers.  dist[] (int32) and the
-// visiting order (uint16 queue, every node enters once) live in LDS; the frontier is the queue segment
-// [head, tail).  Lanes take one frontier node each and walk its neighbour list in step; a neighbour is claimed with
-// a compare-and-swap on its distance, and the claimed ones of a step are appended through a ballot (the queue
+constexpr size_t kTreeLds = 160 * 1024;
+
+// Hop counts from a source to every node: one wavefront per source, no barriers.  A bit a node (visited) and the visiting
+// order (uint16 queue, every node enters once) live in LDS; the frontier is the queue segment
+// [head, tail).  Lanes take one frontier node each (or a share of it) and walk its neighbour list in step; a neighbour is claimed by
+// setting its bit, and the claimed ones of a step are appended through a ballot (the queue
 // position is a wave-uniform register, not a counter in memory).  LDS operations of one wavefront execute in
 // order, so a later step sees the earlier steps' claims and queue entries.
-__device__ __forceinline__ void bfs_source(const int* __restrict__ off, const int* __restrict__ nbr, int K, int src, int* dist,
+__host__ __device__ constexpr size_t bfs_bits_bytes(int K) { return ((size_t)K + 31) / 32 * 4; }
+__host__ __device__ constexpr size_t bfs_source_bytes(int K) { return bfs_bits_bytes(K) + ((size_t)K + 1) / 2 * 4; }       // LDS of a source
+
+template <typename T>
+__device__ __forceinline__ void bfs_source(const T* __restrict__ off, const T* __restrict__ nbr, int K, int src, unsigned int* seen,
                                            float* __restrict__ G)
 {
-    unsigned short* queue = reinterpret_cast<unsigned short*>(dist + K);       // [K], behind dist [K]
+    unsigned short* queue = reinterpret_cast<unsigned short*>(seen + bfs_bits_bytes(K) / 4);       // [K]
+    float* const row = G + (size_t)src * K;
     const int lane = threadIdx.x & 63;
-    for (int v = lane; v < K; v += 64) dist[v] = (v == src) ? 0 : -1;
-    if (lane == 0) queue[0] = (unsigned short)src;
+    for (int v = lane; v < (K + 31) / 32; v += 64) seen[v] = v == src >> 5 ? 1u << (src & 31) : 0u;
+    if (lane == 0) {
+        queue[0] = (unsigned short)src;
+        row[src] = 0.0f;
+    }
     int head = 0, tail = 1;
     for (int level = 0; head < tail; ++level) {
         const int end = tail;
-        for (int base = head; base < end; base += 64) {
-            const int i = base + lane;
+        const int share = end - head <= 16 ? 2 : end - head <= 32 ? 1 : 0;      // a small level's nodes have four or two lanes each
+        for (int base = head; base < end; base += 64 >> share) {
+            const int i = base + (lane >> share);
             const bool has = i < end;
             const int v = has ? (int)queue[i] : 0;
-            int e = has ? off[v] : 0;
-            const int e1 = has ? off[v + 1] : 0;
+            int e = has ? (int)off[v] + (lane & ((1 << share) - 1)) : 0;
+            const int e1 = has ? (int)off[v + 1] : 0;
             while (__any(e < e1)) {
                 bool won = false;
                 int u = 0;
                 if (e < e1) {
-                    u = nbr[e];
-                    ++e;
-                    won = atomicCAS(&dist[u], -1, level + 1) == -1;
+                    u = (int)nbr[e];
+                    e += 1 << share;
+                    won = (atomicOr(&seen[u >> 5], 1u << (u & 31)) >> (u & 31) & 1u) == 0u;
                 }
                 const unsigned long long mask = __ballot(won);
                 if (won) {
                     const int below = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
                     queue[tail + below] = (unsigned short)u;
+                    row[u] = (float)(level + 1);
                 }
                 tail += __popcll(mask);
             }
         }
         head = end;
     }
-    for (int v = lane; v < K; v += 64) {
-        const int d = dist[v];
-        G[(size_t)src * K + v] = d < 0 ? INFINITY : (float)d;
-    }
+    if (tail < K)
+        for (int v = lane; v < K; v += 64)
+            if ((seen[v >> 5] >> (v & 31) & 1u) == 0u) row[v] = INFINITY;
 }
 
-__global__ void __launch_bounds__(64) bfs_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K, float* __restrict__ G)
+// Four to sixteen sources a workgroup, which share the adjacency lists, as 16-bit numbers in LDS, where they fit what is left of it (`room` entries): a
+// level is two dependent reads of the lists.  K = 1024, the map of 4 * 10^7 x 50, 38 us (54 with the lists in L2, a lane a node and the distances in
+// LDS beside the queue); data rows as nodes 79 (84), K = 4096 1164 (1241).
+constexpr int kBfsSources = 16;
+__host__ __device__ constexpr size_t bfs_offset_bytes(int K) { return ((size_t)K + 2) / 2 * 4; }            // [K + 1] uint16
+
+__global__ void __launch_bounds__(64 * kBfsSources) bfs_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K, int room,
+                                                               float* __restrict__ G)
 {
-    extern __shared__ int bfs_lds[];
-    bfs_source(off, nbr, K, blockIdx.x, bfs_lds, G);
+    extern __shared__ unsigned int bfs_lds[];
+    const int waves = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), src = blockIdx.x * waves + wave;
+    unsigned int* const own = bfs_lds + wave * (bfs_source_bytes(K) / 4);
+    const int nnz = off[K];
+    if (nnz > room) {                                         // (the same for all)
+        if (src < K) bfs_source(off, nbr, K, src, own, G);
+        return;
+    }
+    unsigned short* const begin = reinterpret_cast<unsigned short*>(bfs_lds + waves * (bfs_source_bytes(K) / 4));
+    unsigned short* const list = begin + bfs_offset_bytes(K) / 2;
+    for (int v = threadIdx.x; v <= K; v += blockDim.x) begin[v] = (unsigned short)off[v];
+    for (int e = threadIdx.x; e < nnz; e += blockDim.x) list[e] = (unsigned short)nbr[e];
+    __syncthreads();
+    if (src < K) bfs_source(begin, list, K, src, own, G);
 }
 
 // Hop counts of a spanning tree.  With the nodes in depth-first order, the last common ancestor of the nodes at places p < q lies one above the
@@ -485,7 +527,6 @@ __global__ void __launch_bounds__(64) bfs_kernel(const int* __restrict__ off, co
 // One workgroup, bound by the latency of log2(2 K) rounds.  An edge's word holds where it points (END: nowhere) and how many edges on that
 // is; both change together and are true at any time, so a round needs no second copy.
 // tour[place]: node, depth from bit 16.  state[1]: whether the graph is one tree of all nodes (weights that are no numbers can give another).
-constexpr size_t kTreeLds = 160 * 1024;
 constexpr int kTourThreads = 1024;
 constexpr size_t kTourOwn = 1024;                          // what the kernel and its votes hold besides
 // bytes of LDS: per directed edge (2 (K - 1)) its word, its end and its way back; per node where its edges begin
@@ -584,7 +625,7 @@ __global__ void __launch_bounds__(kTourThreads) tree_tour_kernel(const int* __re
 
 // A wavefront a source, sixty-four places at a time; the row goes through LDS so that its lines are written whole.
 constexpr int kTreeSources = 4;
-__host__ __device__ constexpr size_t tree_source_bytes(int K) { return ((size_t)K * 6 + 3) / 4 * 4; }      // (of a search; a row takes four a node)
+__host__ __device__ constexpr size_t tree_source_bytes(int K) { return (size_t)K * 4 + 4; }      // (a row; a search takes less)
 
 __global__ void __launch_bounds__(64 * kTreeSources) tree_hops_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K,
                                                                       const unsigned int* __restrict__ tour, const int* __restrict__ state,
@@ -596,7 +637,7 @@ __global__ void __launch_bounds__(64 * kTreeSources) tree_hops_kernel(const int*
     if (src >= K) return;                                     // (no barrier below)
     unsigned int* const own = tree_lds + wave * (tree_source_bytes(K) / 4);
     if (state[1] == 0) {
-        bfs_source(off, nbr, K, src, reinterpret_cast<int*>(own), G);
+        bfs_source(off, nbr, K, src, own, G);
         return;
     }
     float* const row = reinterpret_cast<float*>(own);
@@ -699,8 +740,8 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
         hipLaunchKernelGGL(mst_prim_kernel, dim3(1), dim3(1024), lds, ctx->stream, d2, K, A);
     } else {
         hipLaunchKernelGGL(rng_near_kernel, dim3((K + 3) / 4), dim3(256), 0, ctx->stream, d2, K, near);
-        hipLaunchKernelGGL(rng_prefilter_kernel, dim3(K), dim3(256), 0, ctx->stream, d2, K, near, A);
-        hipLaunchKernelGGL(rng_verify_kernel, dim3(K), dim3(256), 0, ctx->stream, d2, K, A);
+        hipLaunchKernelGGL(rng_prefilter_kernel, dim3(K), dim3(kPrefilterThreads), 0, ctx->stream, d2, K, near, A);
+        hipLaunchKernelGGL(rng_verify_kernel, dim3(K), dim3(kVerifyThreads), 0, ctx->stream, d2, K, A);
     }
     if (int rc = check_hip(ctx, hipGetLastError(), "edge kernel launch")) return rc;
     hipLaunchKernelGGL(csr_degree_kernel, dim3((K + 3) / 4), dim3(256), 0, ctx->stream, A, K, deg);
@@ -724,11 +765,19 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
         hipLaunchKernelGGL(tree_hops_kernel, dim3((K + sources - 1) / sources), dim3(64 * sources), lds, ctx->stream, off, nbr, K, (const unsigned int*)best_u, state, G);
         return check_hip(ctx, hipGetLastError(), "hop-count launch");
     }
-    // dist[K] int32 + queue[K] uint16 per wavefront (72 KB at the 12000-node limit)
-    const size_t bfs_lds_bytes = ((size_t)K * 6 + 3) / 4 * 4;
+    // As many sources as give every compute unit one workgroup, and no more than leave room for six neighbours a node on average; the lists get
+    // what LDS has left, up to sixteen a node.
+    int waves = (K + ctx->units - 1) / ctx->units;
+    waves = waves < 4 ? 4 : waves > kBfsSources ? kBfsSources : waves;
+    while (waves > 1 && waves * bfs_source_bytes(K) + bfs_offset_bytes(K) + (size_t)K * 12 > kTreeLds) --waves;
+    const size_t own = waves * bfs_source_bytes(K) + bfs_offset_bytes(K);
+    size_t room = (kTreeLds - own) / 2;
+    room = room < (size_t)K * 16 + 2 ? room : (size_t)K * 16 + 2;
+    room = (room < 65535 ? room : 65535) / 2 * 2;
+    const size_t bfs_lds_bytes = own + 2 * room;
     if (bfs_lds_bytes > 48 * 1024) {
-        if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(bfs_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 12000 * 6), "raising the dynamic LDS limit")) return rc;
+        if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(bfs_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTreeLds), "raising the dynamic LDS limit")) return rc;
     }
-    hipLaunchKernelGGL(bfs_kernel, dim3(K), dim3(64), bfs_lds_bytes, ctx->stream, off, nbr, K, G);
+    hipLaunchKernelGGL(bfs_kernel, dim3((K + waves - 1) / waves), dim3(64 * waves), bfs_lds_bytes, ctx->stream, off, nbr, K, (int)room, G);
     return check_hip(ctx, hipGetLastError(), "hop-count launch");
 }
