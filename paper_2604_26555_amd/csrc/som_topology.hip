@@ -160,7 +160,10 @@ __global__ void __launch_bounds__(256) boruvka_scan_kernel(const double* __restr
     if (v >= K) return;
     const int cv = comp[v];
     double bw = INFINITY;
-    int bu = -1, blo = 0x7fffffff, bhi = 0x7fffffff;
+    int bu = -1;
+    auto before = [&](double w, int u) {                       // (v, u) before the best so far
+        return bu < 0 || edge_before(w, v < u ? v : u, v < u ? u : v, bw, v < bu ? v : bu, v < bu ? bu : v);
+    };
     for (int u0 = lane; u0 < K; u0 += 8 * 64) {
         double w[8];
         int c[8];
@@ -172,24 +175,20 @@ __global__ void __launch_bounds__(256) boruvka_scan_kernel(const double* __restr
         }
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            const int u = u0 + 64 * t, lo = v < u ? v : u, hi = v < u ? u : v;
-            if (u < K && c[t] != cv && (bu < 0 || edge_before(w[t], lo, hi, bw, blo, bhi))) {
+            const int u = u0 + 64 * t;
+            if (u < K && c[t] != cv && before(w[t], u)) {
                 bw = w[t];
                 bu = u;
-                blo = lo;
-                bhi = hi;
             }
         }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const double ow = __shfl_xor(bw, o);
-        const int ou = __shfl_xor(bu, o), olo = __shfl_xor(blo, o), ohi = __shfl_xor(bhi, o);
-        if (ou >= 0 && (bu < 0 || edge_before(ow, olo, ohi, bw, blo, bhi))) {
+        const int ou = __shfl_xor(bu, o);
+        if (ou >= 0 && before(ow, ou)) {
             bw = ow;
             bu = ou;
-            blo = olo;
-            bhi = ohi;
         }
     }
     if (lane == 0) {
@@ -198,7 +197,11 @@ __global__ void __launch_bounds__(256) boruvka_scan_kernel(const double* __restr
     }
 }
 
-// single workgroup: per-component minimum of the node picks, edges into A, merge of the joined components
+// single workgroup: per-component minimum of the node picks, edges into A, merge of the joined components.  A chain of latencies: what a
+// thread needs of its nodes comes in at once and stays in registers, the labels in LDS, and pointers jump in place until none moves
+// (three trips to memory, one more for the labels of an edge's ends, and log2 K jumps each time: whole call for data rows as nodes K = 4096
+// 472 us, 407 this way, K = 1024 117 and 112).
+constexpr int kMergeEach = kBoruvkaMaxNodes / 1024;
 __global__ void __launch_bounds__(1024) boruvka_merge_kernel(int K, int* __restrict__ comp, int* __restrict__ state,
                                                              const double* __restrict__ best_w, const int* __restrict__ best_u,
                                                              unsigned char* __restrict__ A)
@@ -208,60 +211,94 @@ __global__ void __launch_bounds__(1024) boruvka_merge_kernel(int K, int* __restr
     unsigned long long* cw = bor_lds;                                 // [K] bit pattern of the cheapest length
     unsigned long long* ce = cw + K;                                  // [K] its ends, lower << 32 | higher
     int* parent = reinterpret_cast<int*>(ce + K);                     // [K]
-    int* parent2 = parent + K;                                        // [K]
+    int* label = parent + K;                                          // [K] comp
     __shared__ int count;
     const int tid = threadIdx.x;
-    for (int c = tid; c < K; c += 1024) {
-        cw[c] = ~0ull;
-        ce[c] = ~0ull;
+    int mine[kMergeEach], other[kMergeEach];
+    unsigned long long length[kMergeEach];
+#pragma unroll
+    for (int t = 0; t < kMergeEach; ++t) {
+        const int v = tid + 1024 * t;
+        mine[t] = v < K ? comp[v] : 0;
+        other[t] = v < K ? best_u[v] : -1;
+        length[t] = v < K ? (unsigned long long)__double_as_longlong(best_w[v]) : 0ull;
+    }
+#pragma unroll
+    for (int t = 0; t < kMergeEach; ++t) {
+        const int v = tid + 1024 * t;
+        if (v < K) {
+            cw[v] = ~0ull;
+            ce[v] = ~0ull;
+            label[v] = mine[t];
+        }
     }
     if (tid == 0) count = 0;
     __syncthreads();
     // lengths are non-negative doubles (or +inf): their bit patterns order like the values
-    for (int v = tid; v < K; v += 1024)
-        if (best_u[v] >= 0) atomicMin(&cw[comp[v]], (unsigned long long)__double_as_longlong(best_w[v]));
+#pragma unroll
+    for (int t = 0; t < kMergeEach; ++t)
+        if (other[t] >= 0) atomicMin(&cw[mine[t]], length[t]);
     __syncthreads();
-    for (int v = tid; v < K; v += 1024) {
-        const int u = best_u[v];
-        if (u >= 0 && (unsigned long long)__double_as_longlong(best_w[v]) == cw[comp[v]]) {
+#pragma unroll
+    for (int t = 0; t < kMergeEach; ++t) {
+        const int v = tid + 1024 * t, u = other[t];
+        if (u >= 0 && length[t] == cw[mine[t]]) {
             const unsigned long long lo = v < u ? v : u, hi = v < u ? u : v;
-            atomicMin(&ce[comp[v]], (lo << 32) | hi);
+            atomicMin(&ce[mine[t]], (lo << 32) | hi);
         }
     }
     __syncthreads();
-    for (int c = tid; c < K; c += 1024) {
-        int par = c;
-        if (comp[c] == c && ce[c] != ~0ull) {
+    int par[kMergeEach];
+#pragma unroll
+    for (int t = 0; t < kMergeEach; ++t) {
+        const int c = tid + 1024 * t;
+        par[t] = c;
+        if (c < K && mine[t] == c && ce[c] != ~0ull) {
             const int lo = (int)(ce[c] >> 32), hi = (int)(ce[c] & 0xffffffffull);
             A[(size_t)lo * K + hi] = 1;
             A[(size_t)hi * K + lo] = 1;
-            par = (comp[lo] == c) ? comp[hi] : comp[lo];
+            par[t] = label[lo] == c ? label[hi] : label[lo];
         }
-        parent[c] = par;
+        if (c < K) parent[c] = par[t];
     }
     __syncthreads();
     // two components that picked each other (necessarily the same edge): the lower label becomes the root
-    for (int c = tid; c < K; c += 1024) {
-        const int par = parent[c];
-        parent2[c] = (parent[par] == c && c < par) ? c : par;
+#pragma unroll
+    for (int t = 0; t < kMergeEach; ++t) {
+        const int c = tid + 1024 * t;
+        if (c < K && parent[par[t]] == c && c < par[t]) par[t] = c;
     }
     __syncthreads();
-    int* from = parent2;
-    int* to = parent;
+#pragma unroll
+    for (int t = 0; t < kMergeEach; ++t)
+        if (tid + 1024 * t < K) parent[tid + 1024 * t] = par[t];
+    __syncthreads();
+    // (a pointer is one word and always leads to a node further on: no second copy; the rounds are bounded for weights that are no numbers)
     for (int span = 1; span < K; span <<= 1) {
-        for (int c = tid; c < K; c += 1024) to[c] = from[from[c]];
-        __syncthreads();
-        int* t = from;
-        from = to;
-        to = t;
+        bool moved = false;
+#pragma unroll
+        for (int t = 0; t < kMergeEach; ++t) {
+            const int c = tid + 1024 * t;
+            if (c < K) {
+                const int next = parent[par[t]];
+                moved = moved || next != par[t];
+                par[t] = next;
+                parent[c] = next;
+            }
+        }
+        if (!__syncthreads_or(moved)) break;
     }
-    int mine = 0;
-    for (int v = tid; v < K; v += 1024) {
-        const int root = from[comp[v]];      // from[] is not written any more; comp[v] is this thread's own entry
-        comp[v] = root;
-        if (root == v) ++mine;
+    int roots = 0;
+#pragma unroll
+    for (int t = 0; t < kMergeEach; ++t) {
+        const int v = tid + 1024 * t;
+        if (v < K) {
+            const int root = parent[mine[t]];
+            comp[v] = root;
+            if (root == v) ++roots;
+        }
     }
-    if (mine) atomicAdd(&count, mine);
+    if (roots > 0) atomicAdd(&count, roots);
     __syncthreads();
     if (tid == 0) state[0] = count;
 }
