@@ -1307,9 +1307,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                 xf[mb][KB - 1] = __builtin_bit_cast(halfx8, make_uint4(w.x | (second ? 0u : f0), w.y | (second ? 0u : f1), w.z | (second ? f0 : 0u),
                                                                        w.w | (second ? f1 : 0u)));
             }
-            if constexpr (CAND) {
-                cut[mb] = ldexpf(cut[mb], sx + sw);
-            } else {
+            if constexpr (!CAND) {
                 // The error of a score.  (1) What the cuts drop: with x = xh + xl, ql and qh the fp6 copies of the parts, and w likewise, a score misses
                 // (xl - ql) . wh + ql . (wh - qh_w) + xh . (wl - ql_w) + (xh - qh) . ql_w + xl . wl.  Two scores are compared, so the first
                 // counts by wh_a - wh_b; of the third the preparation gives w . (wl - ql_w) back, which leaves (x - w) . (wl - ql_w) and
@@ -1338,7 +1336,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                     stash[kThreads] = err_w;
                     stash[2 * kThreads] = nr * 1.001f;
                     stash[3 * kThreads] = err_0;
-                    stash[4 * kThreads] = __int_as_float(-(sx + sw));
+                    stash[4 * kThreads] = __int_as_float(sx + sw);
                 }
             }
         }
@@ -1865,12 +1863,9 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         swap_halves(m0, m1);
         most = fmaxf(m0, m1);
     }
-    if constexpr (HALF) {                          // (a power of two: the position bits stay as they are)
-        const int down = __float_as_int(stash[4 * kThreads]);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) won[q] = ldexpf(won[q], down);
-        most = ldexpf(most, down);
-    }
+    // HALF: the scores stay at the scale they were formed at, and bounds and cuts go there: taken to the values' own, a score of zero
+    // or one that is subnormal there would lose its position.
+    const int up = HALF ? __float_as_int(stash[4 * kThreads]) : 0;
     // winner and runner-up (equal scores are a near tie, decided elsewhere: any of them)
     float r_best = won[0], r_second = -INFINITY;
 #pragma unroll
@@ -1904,14 +1899,15 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // winner; no other node can spoil the decision.  The position bits change a score by at most 2^-19 of itself, and a rival's
     // score is within the bound of the best one.
     const float nx = stash[0], wb = fminf(root(wn) * 1.0001f, wmax);
-    const float bits = fabsf(r_best) * (1.01f * 3.8146973e-06f);
+    const float top = HALF ? ldexpf(r_best, -up) : r_best;
+    const float bits = fabsf(top) * (1.01f * 3.8146973e-06f);
     float bound;
     if constexpr (HALF) {
         const float err_w = stash[kThreads], nr = stash[2 * kThreads], err_0 = stash[3 * kThreads], rest_w = __uint_as_float(a.norms[3]) * 1.001f;
         const float err_b = (err_w + nr) * wb + err_0 + (nx + wb) * rest_w + 0.5f * kErrNorm * wb * wb;
-        const float far = root(fmaxf(nx * nx * 1.00001f - 2.0f * r_best, 0.0f) * 1.00001f + 2.0f * (err_b + bits)) * 1.0001f;
+        const float far = root(fmaxf(nx * nx * 1.00001f - 2.0f * top, 0.0f) * 1.00001f + 2.0f * (err_b + bits)) * 1.0001f;
         const float wo = fminf((nx + far) * 1.0001f, wmax);
-        bound = err_w * (wb + wo) + 2.0f * (err_0 + far * rest_w) + nr * fminf(2.0f * far, wb + wo) + 0.5f * kErrNorm * (wb * wb + wo * wo) + bits;
+        bound = ldexpf(err_w * (wb + wo) + 2.0f * (err_0 + far * rest_w) + nr * fminf(2.0f * far, wb + wo) + 0.5f * kErrNorm * (wb * wb + wo * wo) + bits, up);
     } else {
         const float err_0 = stash[kThreads];
         const unsigned int two = __float_as_uint(stash[2 * kThreads]);
@@ -1955,7 +1951,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             const int left = a.D % 16, mfmas = left >= 1 && left <= 4 ? 49 * (a.D / 16) + 17 : 49 * ((a.D + 15) / 16);
             const float rel = 2.0f * (3.0f * 3.8146973e-06f * 1.0078125f + (float)(mfmas + 1) * 5.9604645e-08f + 1.9073486e-06f) + 12.0f * 5.9604645e-08f;
             const float band = 0.5f * rel * ((nx * wb + 0.5f * wb * wb) + (nx * wmax + 0.5f * wmax2));
-            near = (close || (a.K > 1 && !((r_best - r_second) > band))) ? 1 : 0;
+            near = (close || (a.K > 1 && !((r_best - r_second) > (HALF ? ldexpf(band, up) : band)))) ? 1 : 0;
         }
         a.bmu[i] = node_of_row(r_row, a.K);
         a.cut_all[i] = !close ? kNotListed : open ? list_cut(cut_at) : kPairs;

@@ -64,7 +64,7 @@ struct BmuArgs {
                              // in front (0xffff: none)
     // Candidate pass (long lists only): the search is repeated for the listed samples, and every node whose score
     // reaches the sample's cut is noted; direct differences are then taken over those few nodes only.
-    float* cutv;             // [m] per list entry: best score minus the rounding bound
+    float* cutv;             // [m] per list entry: best score minus the rounding bound (half-precision parts of up to 64 features: at the sample's scale)
     ulonglong2* cand;        // [cand_cap][2]: per list entry and half-wavefront, seven 16-bit node ids and their count
     uint32_t* recheck2;      // [cand_cap] samples left to the all-nodes pass (slots overflowed, or no candidate)
     int32_t slot2;           // which of scal[4], scal[5] counts recheck2

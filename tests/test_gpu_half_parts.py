@@ -117,3 +117,30 @@ def test_listed_rows_of_a_wider_matrix(som):
     idx = torch.randperm(m + 1000, device=DEV, generator=g)[:m].int().contiguous()
     units = check(som, X, W, idx=idx)
     against_float64(X[idx.long()], W, units)
+
+
+def centre_nodes(K):
+    """The sixty-four nodes whose mean the search of up to 64 features takes off samples and weights."""
+    nodes = []
+    for t in range(64):
+        h = t * 0x9E3779B1 & 0xFFFFFFFF
+        h ^= h >> 15
+        h = h * 0x85EBCA77 & 0xFFFFFFFF
+        h ^= h >> 13
+        nodes.append(t * K // 64 + (h * (K // 64) >> 32))
+    return nodes
+
+
+@pytest.mark.parametrize("K,D", [(1100, 50), (1024, 25), (4096, 33)])
+def test_scores_of_zero(som, K, D):
+    """A sample halfway between the centre and its node scores x . w - |w|^2 / 2 = 0 there, and all are small whole numbers of 1/128, so
+    exactly zero: a number whose low bits, which carry the node's place, do not survive any scaling."""
+    m, _ = rows_for(K, D)
+    g = torch.Generator(device=DEV).manual_seed(K + D)
+    W = torch.randint(-1, 2, (K, D), device=DEV, generator=g).float()
+    c = W[torch.tensor(centre_nodes(K), device=DEV)].mean(0)
+    want = torch.arange(m, device=DEV) % K
+    X = (c + W[want]) / 2
+    units, _, _ = som.som_bmu(X, W)
+    differ = units.long() != want
+    assert not differ.any(), int(differ.sum())
