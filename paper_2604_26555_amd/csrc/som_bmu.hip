@@ -1898,16 +1898,20 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // lies within that distance of the sample, so its norm is at most |x| + far (and at most the largest), and it lies within 2 far of the
     // winner; no other node can spoil the decision.  The position bits change a score by at most 2^-19 of itself, and a rival's
     // score is within the bound of the best one.
-    const float nx = stash[0], wb = fminf(root(wn) * 1.0001f, wmax);
+    const float nx = stash[0], wb = fminf(root(wn + (HALF ? kSquaresFloor : 0.0f)) * 1.0001f, wmax);
     const float top = HALF ? ldexpf(r_best, -up) : r_best;
     const float bits = fabsf(top) * (1.01f * 3.8146973e-06f);
     float bound;
     if constexpr (HALF) {
         const float err_w = stash[kThreads], nr = stash[2 * kThreads], err_0 = stash[3 * kThreads], rest_w = __uint_as_float(a.norms[3]) * 1.001f;
+        // (kSquaresFloor: norms and errors were formed at the scaled size, and small ones, or their products, vanish here.  Scores that
+        // small are all listed.)
         const float err_b = (err_w + nr) * wb + err_0 + (nx + wb) * rest_w + 0.5f * kErrNorm * wb * wb;
-        const float far = root(fmaxf(nx * nx * 1.00001f - 2.0f * top, 0.0f) * 1.00001f + 2.0f * (err_b + bits)) * 1.0001f;
+        const float far = root(fmaxf(nx * nx * 1.00001f - 2.0f * top, 0.0f) * 1.00001f + 2.0f * (err_b + bits) + kSquaresFloor) * 1.0001f;
         const float wo = fminf((nx + far) * 1.0001f, wmax);
-        bound = ldexpf(err_w * (wb + wo) + 2.0f * (err_0 + far * rest_w) + nr * fminf(2.0f * far, wb + wo) + 0.5f * kErrNorm * (wb * wb + wo * wo) + bits, up);
+        bound = ldexpf(err_w * (wb + wo) + 2.0f * (err_0 + far * rest_w) + nr * fminf(2.0f * far, wb + wo) + 0.5f * kErrNorm * (wb * wb + wo * wo) + bits +
+                           kSquaresFloor,
+                       up);
     } else {
         const float err_0 = stash[kThreads];
         const unsigned int two = __float_as_uint(stash[2 * kThreads]);

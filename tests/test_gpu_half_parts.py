@@ -131,6 +131,26 @@ def centre_nodes(K):
     return nodes
 
 
+@pytest.mark.parametrize("size", [1e-17, 1e-18, 1e-19, 3e-20, 1e-20, 1e-21, 1e-22])
+def test_units_of_tiny_values(som, size):
+    """Rows whose squares are subnormal or nearly so: a unit's squared distance lies above the least one by what a float32 sum of D squares
+    of that size can lose: (D + 2) * 2^-24 of itself and half of 2^-149 for each of D squares and D additions, for either of the two."""
+    K, D = 1100, 50
+    m, _ = rows_for(K, D)
+    g = torch.Generator(device=DEV).manual_seed(6)
+    W, X = torch.randn((K, D), device=DEV, generator=g) * size, torch.randn((m, D), device=DEV, generator=g) * (2 * size)
+    units, _, _ = som.som_bmu(X, W)
+    w = W.double()
+    over = 0.0
+    for lo in range(0, m, 65536):
+        x = X[lo:lo + 65536].double()
+        d = ((x / size) ** 2).sum(1)[:, None] - 2 * (x / size) @ (w / size).t() + ((w / size) ** 2).sum(1)
+        least = ((x - w[d.argmin(1)]) ** 2).sum(1)
+        own = ((x - w[units[lo:lo + 65536].long()]) ** 2).sum(1)
+        over = max(over, float(((own - least) / (2 * ((D + 2) * 2.0 ** -24 * own + D * 2.0 ** -149))).max()))
+    assert over <= 1.0, over
+
+
 @pytest.mark.parametrize("K,D", [(1100, 50), (1024, 25), (4096, 33)])
 def test_scores_of_zero(som, K, D):
     """A sample halfway between the centre and its node scores x . w - |w|^2 / 2 = 0 there, and all are small whole numbers of 1/128, so
