@@ -41,14 +41,18 @@ constexpr int kWavesPerGroup = 4;
 // half-precision and fp6 parts of up to 32 features, and of up to 64.
 enum SplitForm { kFormWhole, kFormTail, kFormHalf1, kFormHalf2 };
 constexpr int form_units(int form) { return form < kFormHalf1 ? 0 : form - kFormHalf1 + 1; }
-constexpr int kHalfBit = 9;            // scales of the half-precision parts: the largest element comes to lie in [2^9, 2^10)
+// Scales of the half-precision parts: a sample's largest element comes to lie in [2^9, 2^10) (but the scale is at most twice the weights'), that
+// of the nodes that the weights' scale is taken from in [2^2, 2^3), which leaves room for nodes 5800 times as far out.
+constexpr int kHalfBit = 9, kHalfBitWeights = 2;
 constexpr int kHalfRange = 28;         // most that the scales of samples lie below the weights'
 constexpr int kHalfNorm = 14;          // the norms lie 2^14 below them,
-constexpr float kHalfMost = 65504.0f;  // and fit half precision
+constexpr float kHalfMost = 65504.0f;  // and fit half precision;
+constexpr int kHalfThird = 10;         // the last of their three parts 2^10 less far
+constexpr float kHalfNearest = 0.0625f;        // at the weights' scale: added to a node's norm where errors are charged for each unit of it
 constexpr int half_norm_group(int D) { return (D + 3) / 4; }       // their place in the row, in fours: behind the features
-__device__ __forceinline__ int half_scale(float most)
+__device__ __forceinline__ int half_scale(float most, int bit)
 {
-    const int e = kHalfBit + 127 - (int)(__float_as_uint(most) >> 23 & 255u);
+    const int e = bit + 127 - (int)(__float_as_uint(most) >> 23 & 255u);
     return e < -90 ? -90 : e > 90 ? 90 : e;
 }
 // the exponent of the fp6 scale that takes `most` into [3.75, 7.5]
@@ -326,7 +330,7 @@ __device__ __forceinline__ void split_prep(const float* __restrict__ W, int K, i
     __shared__ float part[kPrepNodes][64];
     __shared__ float given[kPrepNodes][65];
     __shared__ uint4 rows16[kPrepNodes * 272 / 16];           // [node][row_bytes]
-    __shared__ float most[kPrepNodes][4];
+    __shared__ float most[kPrepNodes][kTops];
     __shared__ __align__(16) _Float16 parts[HALF ? kPrepNodes : 1][2][64];          // HALF: first and second parts, by the places of a row
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int k0 = blockIdx.x * kPrepNodes, k = k0 + wave;           // rows of the stages (and of the transposed copy)
@@ -373,17 +377,21 @@ __device__ __forceinline__ void split_prep(const float* __restrict__ W, int K, i
     const float v = real ? w - c : 0.0f;
     char* const row = reinterpret_cast<char*>(rows16) + wave * sp.row_bytes;
     if constexpr (HALF) {
-        // the scale: from the nodes that the centre is the mean of; others may lie twenty times as far out and more (kHalfBit)
+        // the scale: from the nodes that the centre is the mean of
         float top = spread[lane & (kPrepNodes - 1)];
         top = fmaxf(top, rotated<0x128>(top));
         top = fmaxf(top, rotated<0x124>(top));
         top = fmaxf(top, rotated<0x122>(top));
         top = fmaxf(top, rotated<0x121>(top));
         static_assert(kPrepNodes == 16, "a row of lanes");
-        const int sw = half_scale(top);
+        const int sw = half_scale(top, kHalfBitWeights);
         const float up = power_of_two(sw), back = power_of_two(-sw);
         if (blockIdx.x == 0 && tid == kScalShift) scal[kScalShift] = (unsigned)sw;
-        const float h = v * up;
+        // A node too far out for this scale has a row below all others, and the samples that may be near it are decided by direct
+        // differences over all nodes.  (A weight that is no number stays: its scores are none either.)
+        const double nrm = lanes_sum((double)v * (double)v);
+        const bool out = 0.5 * nrm * (double)up * (double)up >= (double)(0.99f * kHalfMost) * (1 << kHalfNorm);
+        const float h = out ? 0.0f : v * up;
         const _Float16 hi = (_Float16)h;
         const float left = h - (float)hi;
         // place of this lane's feature: features in fours, the last ones' window shifted back into the row (own features only, zeros in front)
@@ -393,7 +401,6 @@ __device__ __forceinline__ void split_prep(const float* __restrict__ W, int K, i
             parts[wave][1][slot] = (_Float16)left;
             reinterpret_cast<_Float16*>(row)[slot] = hi;
         }
-        const double nrm = lanes_sum((double)v * (double)v);
         const float lo2 = lanes_sum(left * left);
         wave_lds();
         if (lane < 2 * sp.units) {
@@ -432,24 +439,31 @@ __device__ __forceinline__ void split_prep(const float* __restrict__ W, int K, i
             const float nh = (float)full;
             reinterpret_cast<float*>(sp.stage16 + (size_t)(k / kNodesPerStage) * sp.stage16_bytes +
                                      (size_t)kNodesPerStage * sp.row_bytes)[k % kNodesPerStage] = (k < K && nh > kSplitPadNorm) ? nh : kSplitPadNorm;
-            // three parts (11 bits each) of the norm at 2^-kHalfNorm of its scale, which meet that factor on the samples' side, and what
-            // keeps padding rows below all others
+            // three parts (11 bits each) of the norm at 2^-kHalfNorm of its scale, which meet that factor on the samples' side (the last
+            // one, which may be as small as half precision goes, at 2^kHalfThird of theirs), and what keeps padding rows below all others
             const float at = (float)(full * (double)up * (double)up * (1.0 / (1 << kHalfNorm)));
-            const bool fits = !(fabsf(at) >= kHalfMost);             // (no number: its scores are none either)
             _Float16* cell = reinterpret_cast<_Float16*>(row) + 4 * half_norm_group(D);
-            const _Float16 p0 = (_Float16)at, p1 = (_Float16)(at - (float)p0), p2 = (_Float16)((at - (float)p0) - (float)p1);
+            const _Float16 p0 = (_Float16)at, p1 = (_Float16)(at - (float)p0), p2 = (_Float16)(((at - (float)p0) - (float)p1) * (float)(1 << kHalfThird));
             const _Float16 least = (_Float16)-kHalfMost;
-            cell[0] = k < K ? p0 : least;
-            cell[1] = k < K ? p1 : least;
-            cell[2] = k < K ? p2 : least;
-            cell[3] = k < K ? (_Float16)0.0f : least;
+            const bool own = k < K && !out;
+            cell[0] = own ? p0 : least;
+            cell[1] = own ? p1 : least;
+            cell[2] = own ? p2 : least;
+            cell[3] = own ? (_Float16)0.0f : least;
             float most2 = (float)nrm;
             if ((double)most2 < nrm) most2 = nextafterf(most2, INFINITY);
             most[wave][0] = k < K ? most2 : 0.0f;
-            // (a node whose norm does not fit: every sample is decided by direct differences)
-            most[wave][1] = k < K && !fits ? INFINITY : sqrtf(lo2) * back;
-            most[wave][2] = sqrtf(off_hi2) * back;
-            most[wave][3] = sqrtf(off_lo2) * back;
+            // Norms of what the parts leave over, as they are and for each unit of the node's own (and kHalfNearest): a bound charges two nodes
+            // theirs, not twice the farthest one's.
+            const float norm = sqrtf(most2), per = own ? 1.0f / (norm + kHalfNearest * back) : 0.0f;
+            const float over[3] = {sqrtf(lo2) * back, sqrtf(off_hi2) * back, sqrtf(off_lo2) * back};
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                most[wave][1 + t] = over[t] * per;
+                most[wave][4 + t] = own ? over[t] : 0.0f;
+            }
+            // the nearest of the nodes that are too far out: how far its bits lie below those of infinity
+            most[wave][7] = k < K && out ? __uint_as_float(0x7f800000u - __float_as_uint(norm * 0.999999f)) : 0.0f;
         }
     } else {
         const __bf16 hi = (__bf16)v;
@@ -494,7 +508,7 @@ __device__ __forceinline__ void split_prep(const float* __restrict__ W, int K, i
             most[wave][0] = k < K ? up : 0.0f;
             most[wave][1] = lo2;
             most[wave][2] = rest2;
-            most[wave][3] = 0.0f;
+            for (int t = 3; t < kTops; ++t) most[wave][t] = 0.0f;
         }
     }
     __syncthreads();
@@ -504,7 +518,7 @@ __device__ __forceinline__ void split_prep(const float* __restrict__ W, int K, i
     const int f = tid >> 4, q = tid & 15;
     if (f < D) wt[(size_t)f * kpad + k0 + q] = given[q][f];
     if (real) sp.wrow[(size_t)k * D + lane] = w;
-    if (tid < 4) {
+    if (tid < kTops) {
         float m = most[0][tid];
         for (int u = 1; u < kPrepNodes; ++u) m = fmaxf(m, most[u][tid]);
         if (m > 0.0f) atomicMax(&tops[tid], __float_as_uint(m));
@@ -991,8 +1005,11 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
 // in one v_mfma_scale_f32_32x32x64_f8f6f4 for 32 features ([second | first] against [first | second], as in som_bmu_held.hip): 4 + 2
 // MFMAs a block at 50 features where two bf16 parts take 10.  The norms travel as three half-precision parts in the four places behind the
 // features, against a factor on the samples' side; the fourth keeps padding rows below all others.  A sample is scaled by the power of
-// two of its largest element, the weights by one that 64 of them give (kHalfBit leaves room for others), and each node's 32 features have
-// an fp6 scale of their own in LDS behind the norms.  The bound is about 2.2 times that of two bf16 parts (fp6 has four significant bits:
+// two of its largest element, the weights by one that 64 of them give, and each node's 32 features have
+// an fp6 scale of their own in LDS behind the norms.  Nodes up to some 5800 times as far out as those 64 fit (kHalfBitWeights); of one farther
+// still no score is formed, and only samples at least half as far out are decided over all nodes.  10^6 x 50 on 1024 nodes, one of them 100, 1000
+// or 10,000 times as far out: search 240 us, as without it (two bf16 parts 309, 344 and 966).  Errors are charged by the norms of the nodes
+// that come into question: with the largest over all nodes such a node would widen every sample's bound.  The bound is about 2.2 times that of two bf16 parts (fp6 has four significant bits:
 // |first - fp6| |second| and its mirror image for each of the two scores compared), so about twice as many samples are listed.
 // 10^6 x 50: search on 1024 nodes 292 -> 242 us, on 4096 1070 -> 814; with the longer lists the epochs took 414 -> 372 and 1340 -> 1211 us.
 // What bounds it: the port that issues vector instructions and MFMAs (41 and 6 a block of 32 x 32, the matrix pipe busy 0.45 to 0.55 of the
@@ -1182,7 +1199,8 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // ---- this wavefront's samples: centred, cut into bf16 parts, kept in registers
     bf16x8 xh[MS][KBA], xl[MS][KBA], xt[MS];
     // search: norm of the centred sample (both lane halves hold the whole row's), what a score errs by for each unit of |w| and besides
-    // (err_w, err_0), and the norm of what the cut leaves over (see below).  They wait in LDS, behind the stages, for the end of the
+    // (err_w, err_0), and the norm of what the cut leaves over (see below); HALF: err_w, the norms of that, of the second part and of what
+    // fp6 leaves of the first, and the scale of the scores.  They wait in LDS, behind the stages, for the end of the
     // tile: the stage loop has no registers to spare for them.
     float* const stash = reinterpret_cast<float*>(lds4 + 2 * PITCH / 16) + threadIdx.x;
     float cut[MS];          // CAND
@@ -1246,7 +1264,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             most = fmaxf(most, other);
             // The sample's scale: its largest element into [2^9, 2^10), unless that leaves what the norms' factor can hold (elements past what half
             // precision holds make the bound infinite: such a sample goes to the all-nodes pass).
-            int sx = half_scale(most);
+            int sx = half_scale(most, kHalfBit);
             sx = sx < sw - kHalfRange ? sw - kHalfRange : sx > sw + 1 ? sw + 1 : sx;
             const float s = power_of_two(sx), back = power_of_two(-sx);
             // scales of the fp6 parts: second parts are at most a half unit of the largest element's first part (lanes 0 to 31 pack them)
@@ -1298,12 +1316,15 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             }
             if constexpr (KB > 2 * H) xf[mb][KB - 1] = __builtin_bit_cast(halfx8, make_uint4(0u, 0u, 0u, 0u));
             {
-                // the norms' factor, 2^(kHalfNorm + sx - sw) three times, and 2^15 (padding rows)
+                // the norms' factor, 2^(kHalfNorm + sx - sw), twice, 2^-kHalfThird of it (which may be subnormal), and 2^15 (padding rows)
                 const unsigned int f = (unsigned)(15 + kHalfNorm + sx - sw) << 10;
+                const int third = 15 + kHalfNorm - kHalfThird + sx - sw;
+                static_assert(15 + kHalfNorm - kHalfThird - kHalfRange >= -9, "2^-24 at least");
+                const unsigned int f2 = third >= 1 ? (unsigned)third << 10 : 1u << (9 + third);
                 const int group = half_norm_group(a.D);
                 const uint4 w = __builtin_bit_cast(uint4, xf[mb][KB - 1]);
                 const bool here = ((group >> 1) & 1) == g, second = (group & 1) != 0;
-                const unsigned int f0 = here ? f | f << 16 : 0u, f1 = here ? f | 0x7800u << 16 : 0u;
+                const unsigned int f0 = here ? f | f << 16 : 0u, f1 = here ? f2 | 0x7800u << 16 : 0u;
                 xf[mb][KB - 1] = __builtin_bit_cast(halfx8, make_uint4(w.x | (second ? 0u : f0), w.y | (second ? 0u : f1), w.z | (second ? f0 : 0u),
                                                                        w.w | (second ? f1 : 0u)));
             }
@@ -1311,32 +1332,31 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                 // The error of a score.  (1) What the cuts drop: with x = xh + xl, ql and qh the fp6 copies of the parts, and w likewise, a score misses
                 // (xl - ql) . wh + ql . (wh - qh_w) + xh . (wl - ql_w) + (xh - qh) . ql_w + xl . wl.  Two scores are compared, so the first
                 // counts by wh_a - wh_b; of the third the preparation gives w . (wl - ql_w) back, which leaves (x - w) . (wl - ql_w) and
-                // xl . (wl - ql_w).  All norms are formed; the weights' are the largest over the nodes.  (A second part is rounded to half
-                // precision before it goes to fp6.)
+                // xl . (wl - ql_w).  All norms are formed; the weights' are the largest over the nodes for each unit of |w| (and
+                // kHalfNearest).  (A second part is rounded to half precision before it goes to fp6, and a subnormal part costs what 2^-14
+                // would: 2^-25 at the sample's scale, a feature.)
                 // (2) The pipe's accumulation: an MFMA of first parts is charged sixteen units of its accumulator and products
                 // (any order of its additions), those of fp6 products sixty-four terms each; they go first and hold small numbers
                 // only.  Block kb of the first parts is in the accumulator of KB - kb MFMAs, the norm in that of the last.
-                // (3) Six units for the roundings of the two centrings and of -|w|^2 / 2, and what its third part can lose.
+                // (3) Six units for the roundings of the two centrings and of -|w|^2 / 2, and what its third part can lose: 2^-25 of the
+                // weights' scale, 2^(kHalfNorm - kHalfThird) times.
                 float h2 = v2, eh2 = e2, ha2 = after2;               // lower lanes: second parts; upper lanes: first parts
                 swap_halves(v2, h2);
                 swap_halves(e2, eh2);
                 swap_halves(after2, ha2);
                 auto root = [&](float x) { return __builtin_amdgcn_sqrtf(x + kSquaresFloor) * (1.001f * back); };
                 constexpr float unit = 5.9604645e-08f, small = 80.0f * (H + 2) * unit;
-                const float lo_w = __uint_as_float(a.norms[1]) * 1.001f, qh_w = __uint_as_float(a.norms[2]) * 1.001f, ql_w = __uint_as_float(a.norms[3]) * 1.001f;
-                const float nh = root(h2);
-                const float nl = root(v2) * 1.001f + nh * 1.0e-9f, nx = nh + nl;
-                const float nr = root(e2) + nl * 4.9e-4f + nx * 1.0e-9f, qh = root(eh2);
+                const float nh = root(h2), least = 2.5e-7f * back;            // 2^-25 in each of 64 features
+                const float nl = root(v2) * 1.001f + least, nx = nh + nl;
+                const float nr = root(e2) + nl * 4.9e-4f + least, qh = root(eh2);
                 const float err_w = root(ha2) * (16.3f * unit) + nl * small + nx * (6.0f * unit);
-                const float back_w = power_of_two(-sw);
-                const float err_0 = 1.001f * (nr * lo_w + (nl + nr) * qh_w + nl * ql_w + qh * (lo_w + ql_w) + nl * lo_w) + nx * lo_w * small +
-                                    back_w * back_w * 1.0e-3f;
                 if (MS == 1 || mb == g) {
                     stash[0] = nx;
                     stash[kThreads] = err_w;
                     stash[2 * kThreads] = nr * 1.001f;
-                    stash[3 * kThreads] = err_0;
-                    stash[4 * kThreads] = __int_as_float(sx + sw);
+                    stash[3 * kThreads] = nl * 1.001f;
+                    stash[4 * kThreads] = qh * 1.001f;
+                    stash[5 * kThreads] = __int_as_float(sx + sw);
                 }
             }
         }
@@ -1865,7 +1885,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     }
     // HALF: the scores stay at the scale they were formed at, and bounds and cuts go there: taken to the values' own, a score of zero
     // or one that is subnormal there would lose its position.
-    const int up = HALF ? __float_as_int(stash[4 * kThreads]) : 0;
+    const int up = HALF ? __float_as_int(stash[5 * kThreads]) : 0;
     // winner and runner-up (equal scores are a near tie, decided elsewhere: any of them)
     float r_best = won[0], r_second = -INFINITY;
 #pragma unroll
@@ -1903,15 +1923,24 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     const float bits = fabsf(top) * (1.01f * 3.8146973e-06f);
     float bound;
     if constexpr (HALF) {
-        const float err_w = stash[kThreads], nr = stash[2 * kThreads], err_0 = stash[3 * kThreads], rest_w = __uint_as_float(a.norms[3]) * 1.001f;
-        // (kSquaresFloor: norms and errors were formed at the scaled size, and small ones, or their products, vanish here.  Scores that
-        // small are all listed.)
-        const float err_b = (err_w + nr) * wb + err_0 + (nx + wb) * rest_w + 0.5f * kErrNorm * wb * wb;
-        const float far = root(fmaxf(nx * nx * 1.00001f - 2.0f * top, 0.0f) * 1.00001f + 2.0f * (err_b + bits) + kSquaresFloor) * 1.0001f;
-        const float wo = fminf((nx + far) * 1.0001f, wmax);
-        bound = ldexpf(err_w * (wb + wo) + 2.0f * (err_0 + far * rest_w) + nr * fminf(2.0f * far, wb + wo) + 0.5f * kErrNorm * (wb * wb + wo * wo) + bits +
-                           kSquaresFloor,
+        const float err_w = stash[kThreads], nr = stash[2 * kThreads], nl = stash[3 * kThreads], qh = stash[4 * kThreads];
+        static_assert(25 - kHalfNorm + kHalfThird == 21, "5.0e-7: 2^-21");
+        const float back_w = power_of_two(-sw), err_n = back_w * back_w * 5.0e-7f + kSquaresFloor;
+        // what a score errs by for each unit of its node's second part, of what fp6 leaves of its first, and of its second part
+        constexpr float small = 80.0f * (H + 2) * 5.9604645e-08f;
+        const float by_lo = nr + qh + nl + nx * small, by_qh = nl + nr, by_ql = nl + qh;
+        // those of a node of this norm, in the order of norms[1..3] and norms[4..6]
+        auto over = [&](int part, float norm) {
+            return fminf(__uint_as_float(a.norms[1 + part]) * (norm + kHalfNearest * back_w), __uint_as_float(a.norms[4 + part])) * 1.001f;
+        };
+        const float lo_b = over(0, wb), qh_b = over(1, wb), ql_b = over(2, wb);
+        const float err_b = (err_w + nr) * wb + by_lo * lo_b + by_qh * qh_b + (by_ql + nx + wb) * ql_b + err_n + 0.5f * kErrNorm * wb * wb;
+        const float far = root(fmaxf(nx * nx * 1.00001f - 2.0f * top, 0.0f) * 1.00001f + 2.0f * (err_b + bits)) * 1.0001f;
+        const float reach = (nx + far) * 1.0001f, wo = fminf(reach, wmax), two = wb + wo;
+        bound = ldexpf(err_w * two + by_lo * (lo_b + over(0, wo)) + by_qh * (qh_b + over(1, wo)) + (by_ql + far) * (ql_b + over(2, wo)) +
+                           nr * fminf(2.0f * far, two) + 2.0f * err_n + 0.5f * kErrNorm * (wb * wb + wo * wo) + bits,
                        up);
+        if (!(reach < __uint_as_float(0x7f800000u - a.norms[7]))) bound = INFINITY;          // (a node without a row may be as near)
     } else {
         const float err_0 = stash[kThreads];
         const unsigned int two = __float_as_uint(stash[2 * kThreads]);
@@ -2589,8 +2618,8 @@ __global__ void __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per
         a.scal[27 - a.slot] = 0u;
         a.scal[9 - a.slot2] = 0u;
     }
-    if (PAIRS && a.tops && blockIdx.x == 0 && tid < 4) {   // the search has read its maxima: kept for later passes, zero again for the next preparation
-        a.tops[4 + tid] = a.tops[tid];
+    if (PAIRS && a.tops && blockIdx.x == 0 && tid < kTops) {   // the search has read its maxima: kept for later passes, zero again for the next preparation
+        a.tops[kTopsKept + tid] = a.tops[tid];
         a.tops[tid] = 0u;
     }
     double qs = 0.0, qs2 = 0.0;
@@ -3105,7 +3134,7 @@ static int launch_bmu(som_ctx* ctx, const BmuArgs& a)
 template <int KB, int FORM, int MS>
 static int launch_bmu_split(som_ctx* ctx, const BmuArgs& a)
 {
-    constexpr size_t lds_bytes = 2 * (size_t)split_pitch(KB, FORM) + 5 * kThreads * sizeof(float);
+    constexpr size_t lds_bytes = 2 * (size_t)split_pitch(KB, FORM) + 6 * kThreads * sizeof(float);
     static_assert(lds_bytes + 512 <= 80 * 1024, "two workgroups per compute unit");
     static bool attr_set_dev[kMaxDevices] = {};       // the attribute belongs to the device, not to the process
     bool& attr_set = attr_set_dev[ctx->device];
@@ -3330,7 +3359,7 @@ static int bmu_run_pass(som_ctx* ctx, BmuPrep& prep, BmuArgs a)
     a.wrow = prep.wrow;
     a.centre = prep.centre;
     a.scal = prep.scal;
-    a.norms = prep.calls == 0 ? prep.tops : prep.tops + 4;
+    a.norms = prep.calls == 0 ? prep.tops : prep.tops + kTopsKept;
     a.tops = prep.stage16 && prep.nch == 1 && prep.calls == 0 ? prep.tops : nullptr;
     a.recheck = ctx->recheck;
     a.cutv = (float*)(ctx->recheck + ctx->recheck_cap);

@@ -12,6 +12,7 @@
 namespace som {
 
 constexpr int kNodesPerStage = 128;   // nodes of W staged through LDS at a time by the BMU kernel
+constexpr int kTops = 8, kTopsKept = 8;         // BmuPrep::tops
 constexpr int kMaxStepsResident = 32; // BMU kernel keeps a sample's features in registers up to D = 64
 
 struct BmuPrep {
@@ -24,16 +25,19 @@ struct BmuPrep {
     float* centre = nullptr;       // [D] column means of W; stage rows and sample registers hold values minus this
     // Result words, cleared by every preparation: [0] = bits of max_k |w_k - centre|^2, [3] = total,
     // [4], [5] = length of the second list (samples whose candidate slots overflowed; alternating calls),
-    // [12], [13] = length of the list and of the pair list, [14], [15] the next call's; bf16 parts: [8], [9] = bits of max_k |w - hi|^2 and
-    // |w - hi - lo|^2; half-precision and fp6 parts: [8..10] = of max_k |second part|, |what fp6 leaves of the first|, |of the second|, [11] = the scale
+    // [12], [13] = length of the list and of the pair list, [14], [15] the next call's; D > 64, bf16 parts: [8], [9] = bits of max_k |w - hi|^2 and
+    // |w - hi - lo|^2, half-precision and fp6 parts: [8..10] = of max_k |second part|, |what fp6 leaves of the first|, |of the second|;
+    // half-precision and fp6 parts, any D: [11] = the scale
     unsigned int* scal = nullptr;
-    // Split search for D <= 64: the three maxima above are found by atomics in [0..2], which are zero whenever no call is in
-    // progress; the first pass moves them to [4..6], where later passes read them.  (What a call leaves behind
-    // does not depend on which call it is, so a captured call can be replayed.)
+    // Split search for D <= 64: kTops maxima, found by atomics in [0..], which are zero whenever no call is in
+    // progress; the first pass moves them to [kTopsKept..], where later passes read them.  (What a call leaves behind
+    // does not depend on which call it is, so a captured call can be replayed.)  Bits of max_k |w_k - centre|^2; with bf16 parts of |w - hi|^2 and
+    // |w - hi - lo|^2; with half-precision and fp6 parts, of |second part|, |what fp6 leaves of the first|, |of the second|, for each unit of
+    // |w_k| and as they are, and how far the bits of the least |w_k| without a row of its own lie below those of infinity (0: all have one).
     unsigned int* tops = nullptr;
     int kpad = 0, steps = 0, stride = 0;
     int nch = 1;                   // feature chunks of 2 * steps features (1 unless D > 64)
-    int form = 0;                  // D > 64: WideForm
+    int form = 0;                  // split searches: SplitForm (D <= 64) or WideForm
     int calls = 0;                 // bmu_run calls served by this preparation (selects the list counter)
 };
 
@@ -53,7 +57,7 @@ struct BmuArgs {
     const float* wrow;       // BmuPrep::wrow
     const float* centre;     // BmuPrep::centre
     unsigned int* scal;      // BmuPrep::scal
-    const unsigned int* norms;   // split search, D <= 64: the three maxima (BmuPrep::tops, or + 4 after the first pass)
+    const unsigned int* norms;   // split search, D <= 64: the maxima (BmuPrep::tops, or + kTopsKept after the first pass)
     unsigned int* tops;      // first pass of the same: BmuPrep::tops, to be moved; else null
     int32_t slot;            // scal[slot], scal[slot + 1] count this call's list and pair list (12 or 14)
     int64_t full_tiles;      // bmu_kernel: workgroups below this number take full tiles, the others half tiles

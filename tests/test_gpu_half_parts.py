@@ -107,6 +107,62 @@ def test_units_of_uneven_values(som, regime):
         against_float64(X, W, units)
 
 
+@pytest.mark.parametrize("out", [30.0, 300.0, 2000.0, 2e4, 1e6, 1e12, float("inf")])
+def test_units_with_outlying_nodes(som, out):
+    """Nodes inside and outside of what half precision holds at the scale of the others (some 5800 times as far out), samples near them and
+    halfway to them among the rest."""
+    K, D = 1100, 50
+    m, _ = rows_for(K, D)
+    g = torch.Generator(device=DEV).manual_seed(8)
+    randn = lambda *s: torch.randn(s, device=DEV, generator=g)
+    W, X = randn(K, D), 2 * randn(m, D)
+    W[17] *= out
+    W[900] *= 3 * out
+    far = W.clone()
+    if out == float("inf"):                                # a node that no sample is near, its distances infinite
+        W[17] = W[900] = out
+        far[17] = far[900] = 1e18
+    else:
+        for step, node in ((1009, 17), (1013, 900)):
+            X[::step] = W[node] + randn(X[::step].shape[0], D)
+            X[1::step] = W[node] * torch.rand((X[1::step].shape[0], 1), device=DEV, generator=g)
+    units, w = check(som, X, W).long(), far.double()
+    for lo in range(0, m, 16384):                          # (the four nearest by products, by differences among those: products of far rows round)
+        x = X[lo:lo + 16384].double()
+        four = ((w ** 2).sum(1) - 2 * x @ w.t()).topk(4, largest=False).indices
+        least = ((x[:, None] - w[four]) ** 2).sum(2).min(1).values
+        own = ((x - w[units[lo:lo + 16384]]) ** 2).sum(1)
+        assert ((own - least) / own.clamp_min(1e-300)).max() <= 2 * (D + 2) * 2.0 ** -24
+
+
+def test_an_outlying_node_costs_no_call(som):
+    """One node far out leaves the others' samples to the matrix pipe (they took seventeen times as long when its norm decided for all)."""
+    K, D, m = 1024, 50, 500_000
+    g = torch.Generator(device=DEV).manual_seed(10)
+    base, X = torch.randn((K, D), device=DEV, generator=g), torch.randn((m, D), device=DEV, generator=g)
+    b = torch.empty(m, dtype=torch.int32, device=DEV)
+
+    def best_of(W):
+        times = []
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(4):
+                som.som_bmu(X, W, bmu=b)
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end))
+        return min(times)
+
+    plain = best_of(base)
+    for out in (50.0, 1000.0, 1e5):
+        W = base.clone()
+        W[17] *= out
+        t = best_of(W)
+        print(f"node times {out:g}: {t / 4 * 1e3:.0f} us, {plain / 4 * 1e3:.0f} without", flush=True)
+        assert t < 3 * plain, (out, t, plain)
+
+
 def test_listed_rows_of_a_wider_matrix(som):
     K, D = 1024, 37
     m, _ = rows_for(K, D)
