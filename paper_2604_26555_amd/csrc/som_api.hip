@@ -253,7 +253,7 @@ int som_bmu(som_ctx* ctx, const float* X, int64_t N, int32_t D, int64_t ldx, con
     if (m == 0) return qe ? launch_fill_zero(ctx, qe, 2 * sizeof(double)) : SOM_OK;
     if (const int rc = small_bmu_run(ctx, X, D, ldx, idx, m, W, K, bmu, d2, qe); rc != 1) return rc;
     BmuPrep prep;
-    if (int rc = bmu_prepare(ctx, W, K, D, m, &prep, qe, nullptr)) return rc;
+    if (int rc = bmu_prepare(ctx, W, K, D, m, m, &prep, qe, nullptr)) return rc;
     BmuArgs a{};
     a.X = X;
     a.ldx = ldx;
@@ -422,7 +422,7 @@ int som_epoch(som_ctx* ctx, const float* X, int64_t N, int32_t D, int64_t ldx, c
         if (const int rc = small_epoch_run(ctx, X, D, ldx, idx, m, W, K, G, sigma, eps_h); rc != 1) return rc;
     if (int rc = begin_epoch(ctx, K, D, m)) return rc;
     BmuPrep prep;
-    if (int rc = bmu_prepare(ctx, W, K, D, m, &prep, ctx->qe, ctx->small)) return rc;
+    if (int rc = bmu_prepare(ctx, W, K, D, m, m, &prep, ctx->qe, ctx->small)) return rc;
     BmuArgs a{};
     a.X = X;
     a.ldx = ldx;
@@ -553,7 +553,7 @@ static int stream_epoch(som_ctx* ctx, const ChunkSource& src, int64_t N, int32_t
         ctx->h2d_events.push_back(e);
     }
     BmuPrep prep;
-    if (int rc = bmu_prepare(ctx, W, K, D, chunk_rows, &prep, ctx->qe, ctx->small)) return rc;
+    if (int rc = bmu_prepare(ctx, W, K, D, chunk_rows, N, &prep, ctx->qe, ctx->small)) return rc;
 
     // After a failure inside the loop both streams are drained before the call returns: nothing of this epoch is
     // still in flight into the chunk buffers when the caller uses the context again.

@@ -2894,6 +2894,8 @@ int launch_fill_zero(som_ctx* ctx, void* p, size_t bytes)
 // and 121, 10^6 x 50 166 and 161; on 256 nodes 10^6 x 25 89 and 96, 10^6 x 56 144 and 135; on 1024 nodes 120,000 x 50 66 and 68, 250,000 x 56
 // 117 and 103, 10^6 x 25 233 and 200, 10^6 x 50 343 and 317, 10^6 x 64 398 and 331; 500,000 x 50 on 2500 395 and 361.  Up to 20 features
 // they save one MFMA or none and lose on every map (10^6 x 16 on 1024 nodes 168 and 180, 10^6 x 20 on 400 108 and 122).
+// (rows: of the whole epoch, also where they come in chunks.  The forms list different samples, and of nodes that float32 differences cannot tell
+// apart a listed one may get another than a score would give it: an epoch's units must not depend on the length of its chunks.)
 static bool half_parts_pay(int32_t K, int32_t D, int64_t rows)
 {
     if (D <= 20) return false;
@@ -2902,7 +2904,7 @@ static bool half_parts_pay(int32_t K, int32_t D, int64_t rows)
     return fewer >= 40 && rows * fewer >= 40000000;
 }
 
-int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, int64_t rows, BmuPrep* out, double* qe, int32_t* small)
+int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, int64_t rows, int64_t all, BmuPrep* out, double* qe, int32_t* small)
 {
     int steps, nch;
     if (D <= 2 * kMaxStepsResident) {
@@ -2934,7 +2936,7 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, int64_t rows
     // rows for the bf16 matrix pipe where the split search applies
     const bool split = D >= 4 && K > kSplitMinNodes && ctx->search != SOM_SEARCH_FLOAT32;
     // D <= 64: half-precision and fp6 parts, the norms in four places behind the features; narrow rows two bf16 parts
-    const bool half = split && nch == 1 && half_parts_pay(K, D, rows);
+    const bool half = split && nch == 1 && half_parts_pay(K, D, all);
     const int units = half ? (D + 31) / 32 : 0, tail_r = split && nch == 1 && !half && D % 16 >= 1 && D % 16 <= 4 ? D % 16 : 0;
     const int kb = !split || nch > 1 ? 0 : half ? half_norm_group(D) / 4 + 1 : tail_r ? D / 16 : (D + 15) / 16;
     const int form = units ? kFormHalf1 + units - 1 : tail_r ? kFormTail : kFormWhole;

@@ -172,8 +172,8 @@ int check_hip(som_ctx* ctx, hipError_t e, const char* what);
 // kernels' host launchers (each returns SOM_OK or an error code after recording detail in ctx)
 int launch_fill_zero(som_ctx* ctx, void* p, size_t bytes);
 // qe (double[2]) and small (int32[4]) are zeroed by the preparation kernel when given
-// rows: how many a bmu_run will bring, as far as the caller knows
-int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, int64_t rows, BmuPrep* out, double* qe, int32_t* small);
+// rows: how many a bmu_run will bring, as far as the caller knows; all: how many its runs bring together
+int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, int64_t rows, int64_t all, BmuPrep* out, double* qe, int32_t* small);
 int bmu_run(som_ctx* ctx, BmuPrep& prep, BmuArgs args);
 // split search for D > 64 (som_bmu_wide.hip)
 int bmu_wide_form(const som_ctx* ctx, int32_t K, int32_t D, int64_t rows);

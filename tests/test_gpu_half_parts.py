@@ -163,6 +163,22 @@ def test_an_outlying_node_costs_no_call(som):
         assert t < 3 * plain, (out, t, plain)
 
 
+def test_streamed_epochs_take_the_parts_of_resident_ones(som):
+    """Samples a thousand times as far out as the nodes lie from one another, where the two forms' units differ: one node of some 250 samples
+    that gets one more or less moves by far more than the last places of its weights."""
+    K, D = 1089, 50
+    m, piece = rows_for(K, D)
+    g = torch.Generator(device=DEV).manual_seed(12)
+    W, X = 5 + 1e-3 * torch.randn((K, D), device=DEV, generator=g), 2 * torch.randn((m, D), device=DEV, generator=g)
+    at = torch.arange(K, device=DEV, dtype=torch.float32)
+    G = (at[:, None] - at[None, :]).abs()
+    Wr, Ws = W.clone(), W.clone()
+    som.som_epoch(X, Wr, G, 0.3)
+    som.som_epoch_host(X.cpu().numpy(), Ws, G, 0.3, chunk_rows=piece)
+    torch.cuda.synchronize()
+    assert (Wr - Ws).abs().max() <= 2.0 ** -22 * Wr.abs().max()
+
+
 def test_listed_rows_of_a_wider_matrix(som):
     K, D = 1024, 37
     m, _ = rows_for(K, D)
