@@ -1034,8 +1034,11 @@ constexpr int split_stage_f4(int kb, int form)
     return ((kNodesPerStage * split_row_bytes(kb, form) + kNodesPerStage * (form_units(form) ? 8 : 4)) / 16 + kThreads - 1) / kThreads * kThreads;
 }
 // Stages go from memory to LDS directly (DIRECT: no registers, no vector instructions for it) where two of them lie below 64 KB, in whole
-// kilobytes; others, of 61 to 64 features, by way of registers.
-// Search of 10^6 x 50 on 4096 nodes 814 us by registers and 754, on 1024 242 and 225; of 10^7 x 50 on 1024 2212 and 2123.
+// kilobytes; others by way of registers: four whole blocks of two bf16 parts (53 to 64 features) and half-precision parts of 61 to 64.
+// Search of 10^6 x 50 on 4096 nodes 814 us by registers and 754, on 1024 242 and 225; of 10^7 x 50 on 1024 2212 and 2123.  The first stage is
+// asked for before the samples are: behind their cutting it was waited for in full, which on small maps is much of a tile (10^6 rows on 100
+// nodes, 50 features 71.6 us by registers, 72.9 with the first stage asked for late, 64.6 early; 20 features 45.2, 44.6, 43.7; 900,000 x 25 on 400
+// nodes 84.5, 80.7, 80.5; 1024 and 4096 nodes the same).
 constexpr int split_pitch_direct(int kb, int form)
 {
     return (kNodesPerStage * split_row_bytes(kb, form) + kNodesPerStage * (form_units(form) ? 8 : 4) + 1023) / 1024 * 1024;
@@ -1206,6 +1209,21 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     float cut[MS];          // CAND
     unsigned int found[MS]; // CAND: hits of the block in hand
     const int64_t total = CAND ? (int64_t)count : a.m;
+    // DIRECT: a stage's kilobytes from memory to LDS, a stretch of them for each wavefront
+    const float4* src4 = reinterpret_cast<const float4*>(a.stage16);
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) char*)lds4);
+    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+    auto load_stage = [&](int st, int buf) {
+        constexpr int KBYTES = PITCH / 1024, PER = (KBYTES + kWavesPerGroup - 1) / kWavesPerGroup;
+        const char* from = reinterpret_cast<const char*>(src4) + (size_t)st * STAGE_F4 * 16 + wave_s * (PER * 1024);
+        const unsigned to = lds0 + (unsigned)(buf * PITCH + wave_s * (PER * 1024));
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (wave_s * PER + q < KBYTES) lds_load16(from + q * 1024, (unsigned)lane * 16u, to + q * 1024);
+    };
+    // (the first stage is on its way while the samples come in and are cut: nobody has read or written this buffer yet, or not since the
+    // barrier between two tiles)
+    if constexpr (DIRECT) load_stage(0, 0);
     SplitRows<KB, FORM, MS, CAND> raw;
     raw.load(a, wave0, total, j, g);
     // CAND: the wavefront's queue, its length (which may pass the end: those entries are lost, and lost remembers whose), and each
@@ -1559,26 +1577,12 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     };
     // ---- stream the nodes through LDS
     const int nstages = a.kpad / kNodesPerStage;
-    const float4* src4 = reinterpret_cast<const float4*>(a.stage16);
-    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) char*)lds4);
-    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-    // DIRECT: a stage's kilobytes from memory to LDS, a stretch of them for each wavefront
-    auto load_stage = [&](int st, int buf) {
-        constexpr int KBYTES = PITCH / 1024, PER = (KBYTES + kWavesPerGroup - 1) / kWavesPerGroup;
-        const char* from = reinterpret_cast<const char*>(src4) + (size_t)st * STAGE_F4 * 16 + wave_s * (PER * 1024);
-        const unsigned to = lds0 + (unsigned)(buf * PITCH + wave_s * (PER * 1024));
-#pragma unroll
-        for (int q = 0; q < PER; ++q)
-            if (wave_s * PER + q < KBYTES) lds_load16(from + q * 1024, (unsigned)lane * 16u, to + q * 1024);
-    };
     // what this wavefront brings in and reads is there, for all to see
     auto stage_barrier = [] {
         if constexpr (DIRECT) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         else __syncthreads();
     };
-    if constexpr (DIRECT) {
-        load_stage(0, 0);
-    } else {
+    if constexpr (!DIRECT) {
 #pragma unroll
         for (int p = 0; p < PRE; ++p) lds4[tid + p * kThreads] = src4[tid + p * kThreads];
     }
