@@ -565,9 +565,13 @@ __global__ void __launch_bounds__(64 * kBfsSources) bfs_kernel(const int* __rest
 // is; both change together and are true at any time, so a round needs no second copy.
 // tour[place]: node, depth from bit 16.  state[1]: whether the graph is one tree of all nodes (weights that are no numbers can give another).
 constexpr int kTourThreads = 1024;
-constexpr size_t kTourOwn = 1024;                          // what the kernel and its votes hold besides
-// bytes of LDS: per directed edge (2 (K - 1)) its word, its end and its way back; per node where its edges begin
-__host__ __device__ constexpr size_t tour_bytes(int K) { return (size_t)K * 18 + 4; }
+// bytes of LDS: per directed edge (2 (K - 1)) its word, its end and its way back; per node where its edges begin; a word for votes
+// (the sums of the wavefronts take the place of the edges' words in the end)
+__host__ __device__ constexpr size_t tour_vote(int K) { return K < 16 ? 256 : ((size_t)K * 18 - 14 + 3) / 4 * 4; }
+__host__ __device__ constexpr size_t tour_bytes(int K) { return tour_vote(K) + 4; }
+constexpr int kTourNodes = (int)((kTreeLds - 4 + 14) / 18);       // most that fit (9102)
+static_assert(tour_bytes(kTourNodes) <= kTreeLds && tour_bytes(kTourNodes + 1) > kTreeLds, "kTourNodes");
+static_assert(2 * (kTourNodes - 1) < 0xffff && kTourNodes < 0x8000, "numbers of edges in sixteen bits, of nodes in fifteen");
 
 __global__ void __launch_bounds__(kTourThreads) tree_tour_kernel(const int* __restrict__ off, const int* __restrict__ nbr, int K,
                                                                 unsigned short* __restrict__ seq, unsigned int* __restrict__ tour,
@@ -579,8 +583,18 @@ __global__ void __launch_bounds__(kTourThreads) tree_tour_kernel(const int* __re
     unsigned short* const end = reinterpret_cast<unsigned short*>(word + E);           // [E]
     unsigned short* const back = end + E;                                              // [E]
     unsigned short* const begin = back + E;                                            // [K + 1]
-    __shared__ int2 sums[kTourThreads / 64];
-    constexpr unsigned kEnd = 0xffffu;                     // (E <= 18202)
+    int2* const sums = reinterpret_cast<int2*>(tour_lds);                              // [wavefront]
+    volatile int* const vote = reinterpret_cast<int*>(tour_lds + tour_vote(K) / 4);
+    auto all = [&](bool yes) {
+        if (tid == 0) *vote = 1;
+        __syncthreads();
+        if (!yes) *vote = 0;
+        __syncthreads();
+        const bool agreed = *vote != 0;
+        __syncthreads();
+        return agreed;
+    };
+    constexpr unsigned kEnd = 0xffffu;
     bool tree = off[K] == E;
     if (tree) {                                            // (the same for all)
         for (int v = tid; v <= K; v += kTourThreads) begin[v] = (unsigned short)off[v];
@@ -608,7 +622,7 @@ __global__ void __launch_bounds__(kTourThreads) tree_tour_kernel(const int* __re
             word[e] = (next == 0 ? kEnd : (unsigned)next) | 1u << 16;      // (node 0's first edge is edge 0)
         }
     }
-    tree = __syncthreads_and(tree);
+    tree = all(tree);
     for (int reach = 1; tree && reach < E; reach <<= 1) {
         for (int e = tid; e < E; e += kTourThreads) {
             const unsigned w = word[e], n = w & 0xffffu;
@@ -621,7 +635,7 @@ __global__ void __launch_bounds__(kTourThreads) tree_tour_kernel(const int* __re
     }
     if (tree)
         for (int e = tid; e < E; e += kTourThreads) tree = tree && (word[e] & 0xffffu) == kEnd;
-    tree = __syncthreads_and(tree);
+    tree = all(tree);
     if (tid == 0) state[1] = tree ? 1 : 0;
     if (!tree) return;
     // ends along the tour, and whether an edge leads away from node 0 (its way back comes later)
@@ -785,13 +799,13 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
     hipLaunchKernelGGL(csr_scan_kernel, dim3(1), dim3(1024), 0, ctx->stream, deg, K, off);
     hipLaunchKernelGGL(csr_fill_kernel, dim3((K + 3) / 4), dim3(256), 0, ctx->stream, A, K, off, nbr);
     if (int rc = check_hip(ctx, hipGetLastError(), "adjacency launch")) return rc;
-    if (kind == SOM_TOPOLOGY_MST && tour_bytes(K) + kTourOwn <= kTreeLds) {
+    if (kind == SOM_TOPOLOGY_MST && K <= kTourNodes) {
         const size_t tour_lds = tour_bytes(K);
         int sources = kTreeSources;                      // of a workgroup
         while (sources * tree_source_bytes(K) > kTreeLds) --sources;
         const size_t lds = sources * tree_source_bytes(K);
         if (tour_lds > 48 * 1024) {
-            if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(tree_tour_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kTreeLds - kTourOwn)), "raising the dynamic LDS limit")) return rc;
+            if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(tree_tour_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTreeLds), "raising the dynamic LDS limit")) return rc;
         }
         if (lds > 48 * 1024) {
             if (int rc = check_hip(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(tree_hops_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTreeLds), "raising the dynamic LDS limit")) return rc;
