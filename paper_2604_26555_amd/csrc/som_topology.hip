@@ -528,7 +528,7 @@ __device__ __forceinline__ void bfs_source(const T* __restrict__ off, const T* _
             if ((seen[v >> 5] >> (v & 31) & 1u) == 0u) row[v] = INFINITY;
 }
 
-// Four to sixteen sources a workgroup, which share the adjacency lists, as 16-bit numbers in LDS, where they fit what is left of it (`room` entries): a
+// Up to sixteen sources a workgroup, which share the adjacency lists, as 16-bit numbers in LDS, where they fit what is left of it (`room` entries): a
 // level is two dependent reads of the lists.  K = 1024, the map of 4 * 10^7 x 50, 38 us (54 with the lists in L2, a lane a node and the distances in
 // LDS beside the queue); data rows as nodes 79 (84), K = 4096 1164 (1241).
 constexpr int kBfsSources = 16;
@@ -541,7 +541,7 @@ __global__ void __launch_bounds__(64 * kBfsSources) bfs_kernel(const int* __rest
     const int waves = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), src = blockIdx.x * waves + wave;
     unsigned int* const own = bfs_lds + wave * (bfs_source_bytes(K) / 4);
     const int nnz = off[K];
-    if (nnz > room) {                                         // (the same for all)
+    if (room == 0 || nnz > room) {                            // (the same for all)
         if (src < K) bfs_source(off, nbr, K, src, own, G);
         return;
     }
@@ -817,12 +817,21 @@ extern "C" int som_topology(som_ctx* ctx, const float* W, int32_t K, int32_t D, 
         return check_hip(ctx, hipGetLastError(), "hop-count launch");
     }
     // As many sources as give every compute unit one workgroup, and no more than leave room for six neighbours a node on average; the lists get
-    // what LDS has left, up to sixteen a node.
-    int waves = (K + ctx->units - 1) / ctx->units;
-    waves = waves < 4 ? 4 : waves > kBfsSources ? kBfsSources : waves;
-    while (waves > 1 && waves * bfs_source_bytes(K) + bfs_offset_bytes(K) + (size_t)K * 12 > kTreeLds) --waves;
-    const size_t own = waves * bfs_source_bytes(K) + bfs_offset_bytes(K);
-    size_t room = (kTreeLds - own) / 2;
+    // what LDS has left, up to sixteen a node.  Where they leave room for less than half of the sources that fit without them they stay in L2:
+    // on 6000 nodes (8 features, six neighbours) 868 us with six sources and lists, 922 with twelve and none; on 7000 (four, eleven) 1682 and 1493,
+    // 9000 (one, eight) 13,150 and 2830, 12,000 (one, six) 29,600 and 5730.  (A source a workgroup, its distances beside the queue: 1403, 2666, 6160,
+    // 11,020.)
+    const int even = (K + ctx->units - 1) / ctx->units, asked = even < 4 ? 4 : even > kBfsSources ? kBfsSources : even;
+    auto sources_beside = [&](size_t lists) {
+        int n = asked;
+        while (n > 1 && n * bfs_source_bytes(K) + lists > kTreeLds) --n;
+        return n;
+    };
+    const int beside = sources_beside(bfs_offset_bytes(K) + (size_t)K * 12), alone = sources_beside(0);
+    const bool lists = 2 * beside + 1 >= alone;
+    const int waves = lists ? beside : alone;
+    const size_t own = waves * bfs_source_bytes(K) + (lists ? bfs_offset_bytes(K) : 0);
+    size_t room = lists ? (kTreeLds - own) / 2 : 0;
     room = room < (size_t)K * 16 + 2 ? room : (size_t)K * 16 + 2;
     room = (room < 65535 ? room : 65535) / 2 * 2;
     const size_t bfs_lds_bytes = own + 2 * room;

@@ -470,3 +470,32 @@ def test_spanning_tree_hops_at_the_limit_of_lds(som, K):
     T = som.som_topology(place.float()[:, None].contiguous(), "mst")
     for lo in range(0, K, 1024):
         assert torch.equal(T[lo:lo + 1024], (place[lo:lo + 1024, None] - place[None]).abs().float())
+
+
+@pytest.mark.parametrize("K", [6124, 6125, 6500, 6653, 9103, 12000])
+def test_neighbourhood_graph_hops_on_both_sides_of_the_lists_limit(som, K):
+    """Nodes along a line: breadth first with the adjacency lists in LDS, and in memory where they would crowd out the sources."""
+    place = torch.randperm(K, generator=torch.Generator().manual_seed(K)).cuda()
+    T = som.som_topology(place.float()[:, None].contiguous(), "rng")
+    for lo in range(0, K, 1024):
+        assert torch.equal(T[lo:lo + 1024], (place[lo:lo + 1024, None] - place[None]).abs().float())
+
+
+def test_neighbourhood_graphs_of_many_nodes_cost_no_more_per_pair(som):
+    """Graphs of 9000 nodes against 6000 (2.25 times the pairs): nine times as long a call when the lists left room for one source to a compute
+    unit, three times without them."""
+    times = []
+    for K in (6000, 9000):
+        W = torch.randn((K, 8), device="cuda", generator=torch.Generator(device="cuda").manual_seed(K))
+        G = torch.empty((K, K), device="cuda")
+        best = float("inf")
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            som.som_topology(W, "rng", G=G)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        times.append(best)
+    print(f"6000 nodes {times[0]:.2f} ms, 9000 {times[1]:.2f}", flush=True)
+    assert times[1] < 5 * times[0], times
