@@ -1183,6 +1183,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     constexpr bool TAIL = FORM == kFormTail;
     constexpr int H = form_units(FORM), HA = H > 0 ? H : 1;
     constexpr bool HALF = H > 0;
+    constexpr bool FOUR = HALF || KB < 4;              // scores are folded four at a time, otherwise two (below)
     constexpr int RS = split_row_bytes(KB, FORM);
     constexpr int STAGE_F4 = split_stage_f4(KB, FORM);
     constexpr int KBA = KB > 0 ? KB : 1;               // array lengths (no zero-length arrays when D <= 4)
@@ -1222,8 +1223,13 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             if (wave_s * PER + q < KBYTES) lds_load16(from + q * 1024, (unsigned)lane * 16u, to + q * 1024);
     };
     // (the first stage is on its way while the samples come in and are cut: nobody has read or written this buffer yet, or not since the
-    // barrier between two tiles)
-    if constexpr (DIRECT) load_stage(0, 0);
+    // barrier between two tiles; by registers too: 10^6 x 64 on 100 nodes 89 us behind the cut and 85)
+    if constexpr (DIRECT) {
+        load_stage(0, 0);
+    } else {
+#pragma unroll
+        for (int p = 0; p < PRE; ++p) lds4[tid + p * kThreads] = src4[tid + p * kThreads];
+    }
     SplitRows<KB, FORM, MS, CAND> raw;
     raw.load(a, wave0, total, j, g);
     // CAND: the wavefront's queue, its length (which may pass the end: those entries are lost, and lost remembers whose), and each
@@ -1538,11 +1544,13 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // max3(best, v1, v2) and, because second <= best, the second largest is max(second, med3(best, v1, v2)), the maximum with two steps'
     // medians at once: nine vector instructions per four scores, plus two per stage and class for the stage number.  (The vector port is as busy as the
     // matrix pipe here: with the class's block number updated per block, two instructions more per block and class, the
-    // kernel took 7 % longer.)
+    // kernel took 7 % longer.)  Four whole blocks of two bf16 parts take each two scores' median by itself, ten instructions: they have no register
+    // for one that waits (search four at a time and two: 10^6 x 61 on 200 nodes 128 us and 120, 10^6 x 56 on 50 77 and 71, 300,000 x 64 on 324
+    // 54 and 51, 500,000 x 64 on 400 81.5 and 82.9; 10^6 x 50 on 200 84 and 88, 10^6 x 12 on 600 89 and 95).
     float mid0 = 0.0f;
     auto fold_step = [&](const floatx16 (&acc)[MS], int step, int st, int nb) {
         // (a class's two steps of four scores behind one another)
-        const int mb = step >> 3, p = (step >> 1) & 1, r0 = 4 * (2 * ((step & 7) >> 2) + (step & 1)) + p, r1 = r0 + 2;
+        const int mb = step >> 3, p = FOUR ? (step >> 1) & 1 : step & 1, r0 = FOUR ? 4 * (2 * ((step & 7) >> 2) + (step & 1)) + p : 4 * ((step & 7) >> 1) + p, r1 = r0 + 2;
         if constexpr (CAND) {
             // A bit per score that reaches the cut, two instructions each and no branch; what a block found is noted behind
             // its last step.  (A compare and a branch per score kept the fold from running beside the MFMAs: 2.2 ns an entry at
@@ -1570,7 +1578,8 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
             const float v2 = __uint_as_float((__float_as_uint(acc[mb][r1]) & 0xfffffff0u) | (unsigned)(pos + (r1 >> 1)));
             const float mid = __builtin_amdgcn_fmed3f(best[mb][c], v1, v2);
             best[mb][c] = vmax3(best[mb][c], v1, v2);
-            if ((step & 1) == 0) mid0 = mid;
+            if constexpr (!FOUR) second[mb][c] = vmax(second[mb][c], mid);
+            else if ((step & 1) == 0) mid0 = mid;
             else second[mb][c] = vmax3(second[mb][c], mid0, mid);
             if (nb >= 2 && r1 >= 14) tsel[mb][c] = (best[mb][c] > before[mb][c]) ? st : tsel[mb][c];
         }
@@ -1582,10 +1591,6 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
         if constexpr (DIRECT) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         else __syncthreads();
     };
-    if constexpr (!DIRECT) {
-#pragma unroll
-        for (int p = 0; p < PRE; ++p) lds4[tid + p * kThreads] = src4[tid + p * kThreads];
-    }
     stage_barrier();
 
     // The scores of a node block are folded while the matrix pipe works on the next block: two sets of accumulators
@@ -1709,7 +1714,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
                 if (bits != 0u) {
                     const int bit = 31 - __builtin_clz(bits);          // 15 - place in the order of the steps
                     bits ^= 1u << bit;
-                    const int place = 15 - bit, r = 8 * (place >> 3) + 4 * ((place >> 1) & 1) + ((place >> 2) & 1) + 2 * (place & 1);
+                    const int place = 15 - bit, r = FOUR ? 8 * (place >> 3) + 4 * ((place >> 1) & 1) + ((place >> 2) & 1) + 2 * (place & 1) : 4 * (place >> 2) + ((place >> 1) & 1) + 2 * (place & 1);
                     const unsigned int id = (unsigned)node_of_row((int)(base + 8 * (r >> 2) + (r & 3)), a.K);
                     if (id < (unsigned)a.K) {
                         const float* wr = a.W + (size_t)id * D;
