@@ -40,15 +40,16 @@ constexpr size_t kFLdsBytes = 150 * 1024;     // slab
 // share one by four and of up to 31 by two: 10^7 x 12 on 1024 nodes 221 -> 193 us, 10^7 x 28 308 -> 286; through a list 439 -> 257
 // and 622 -> 412; 10^5 x 5 on 400 17.9 -> 14.5.  (Four rows have eight loads under way: with sixteen their addresses do not fit the
 // scalar registers, 10^6 x 8 33 us instead of 30.)
-template <bool GATHER, int R>
+// ONE: one slab, which holds all nodes (dividing node numbers all the same took 3 to 8 % of the kernel: 400,000 x 2 on 4096 nodes 22.2 -> 23.8 us)
+template <bool GATHER, int R, bool ONE>
 __global__ void __launch_bounds__(kFThreads) accumulate_f64_kernel(const float* __restrict__ X, int D, int64_t ldx,
                                                                    const uint32_t* __restrict__ idx, int64_t m,
                                                                    const int32_t* __restrict__ bmu, int K, int ks,
-                                                                   int nslabs, int64_t rows_per_range,
+                                                                   int slabs, int64_t rows_per_range,
                                                                    double* __restrict__ part)
 {
     extern __shared__ double f64_lds[];
-    const int DS = D + 1;
+    const int DS = D + 1, nslabs = ONE ? 1 : slabs;
     double* P = f64_lds;                                                   // [ks][DS]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -56,7 +57,7 @@ __global__ void __launch_bounds__(kFThreads) accumulate_f64_kernel(const float* 
     const int blk = blockIdx.x / (8 * nslabs), within = blockIdx.x % (8 * nslabs);
     const int slab = within / 8;
     const int64_t range = (int64_t)blk * 8 + (within % 8);
-    const int kn = (K - slab + nslabs - 1) / nslabs;                       // nodes of this slab: slab, slab + nslabs, ...
+    const int kn = ONE ? K : (K - slab + nslabs - 1) / nslabs;                       // nodes of this slab: slab, slab + nslabs, ...
     const int64_t lo = range * rows_per_range;
     if (lo >= m) return;                                   // padding of the last block of 8 ranges (whole workgroup)
     int64_t hi = lo + rows_per_range;
@@ -99,8 +100,8 @@ __global__ void __launch_bounds__(kFThreads) accumulate_f64_kernel(const float* 
 #pragma unroll
         for (int q = 0; q < U; ++q) {
             const int b = bq[q];
-            const unsigned ub = (unsigned)b, at = nslabs == 1 ? ub : __umulhi(ub, recip);      // b / nslabs
-            const bool in = ub < (unsigned)K && ub - at * (unsigned)nslabs == (unsigned)slab;
+            const unsigned ub = (unsigned)b, at = ONE ? ub : __umulhi(ub, recip);              // b / nslabs
+            const bool in = ub < (unsigned)K && (ONE || ub - at * (unsigned)nslabs == (unsigned)slab);
             unsigned long long todo = __ballot(in);                        // wave-uniform: lanes whose row is ours
             const float* xpass = X + (base + q) * ldx;
             const int ncell = (int)at * DS;                                 // this lane's row of P, if its sample is ours
@@ -203,14 +204,15 @@ __global__ void __launch_bounds__(kFThreads) accumulate_f64_kernel(const float* 
         }
     }
     __syncthreads();
-    // slab -> the range's slice [K][DS]
-    // (a row of at most 64 cells a wavefront at a time)
-    double* out = part + (size_t)range * K * DS;
-    if (nslabs == 1) {
+    // slab -> the range's slice [K][DS], a lane a cell: the slab's rows lie nslabs apart there.  (A row a wavefront left most lanes without a
+    // cell on narrow rows: 20,000 x 4 on 4096 nodes 25.8 us, 12.8 this way.)
+    double* out = part + (size_t)range * K * DS + (size_t)slab * DS;
+    const unsigned recip_row = 0xffffffffu / (unsigned)DS + 1u;            // (exact below 2^26: at most 64 cells a row)
+    const int apart = (nslabs - 1) * DS;
+    if constexpr (ONE) {
         for (int c = tid; c < K * DS; c += kFThreads) out[c] = P[c];
-    } else if (lane < DS) {
-#pragma unroll 4
-        for (int at = wave; at < kn; at += kFThreads / 64) out[(size_t)(at * nslabs + slab) * DS + lane] = P[at * DS + lane];
+    } else {
+        for (int c = tid; c < kn * DS; c += kFThreads) out[c + (int)__umulhi((unsigned)c, recip_row) * apart] = P[c];
     }
 }
 
@@ -296,9 +298,14 @@ int accumulate_f64_run(som_ctx* ctx, const float* X, int32_t D, int64_t ldx, con
     double* part = (double*)ctx->acc_blob;
     const dim3 grid((unsigned)(ranges_padded * nslabs));
     const int together = window < 16 ? 4 : window < 32 ? 2 : 1;          // rows to a load and an addition: as fit 64 lanes
-    auto kern = together == 4 ? (idx ? accumulate_f64_kernel<true, 4> : accumulate_f64_kernel<false, 4>)
-                : together == 2 ? (idx ? accumulate_f64_kernel<true, 2> : accumulate_f64_kernel<false, 2>)
-                                : (idx ? accumulate_f64_kernel<true, 1> : accumulate_f64_kernel<false, 1>);
+    using Kernel = decltype(&accumulate_f64_kernel<false, 1, false>);
+    static constexpr Kernel kernels[2][3][2] = {
+#define SOM_F64_KERNELS(R) {accumulate_f64_kernel<false, R, false>, accumulate_f64_kernel<true, R, false>}
+#define SOM_F64_KERNELS_ONE(R) {accumulate_f64_kernel<false, R, true>, accumulate_f64_kernel<true, R, true>}
+        {SOM_F64_KERNELS(1), SOM_F64_KERNELS(2), SOM_F64_KERNELS(4)}, {SOM_F64_KERNELS_ONE(1), SOM_F64_KERNELS_ONE(2), SOM_F64_KERNELS_ONE(4)}};
+#undef SOM_F64_KERNELS
+#undef SOM_F64_KERNELS_ONE
+    const Kernel kern = kernels[nslabs == 1][together / 2][idx ? 1 : 0];
     if (int rc = check_hip(ctx,
                            hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFLdsBytes),

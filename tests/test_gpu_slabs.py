@@ -31,3 +31,25 @@ def test_nodes_of_every_slab(D, slabs):
             want = torch.zeros((K, D), dtype=torch.float64).index_add_(0, use[on].cpu(), x[on].cpu().double())
             assert torch.equal(S.cpu(), want)
             assert torch.equal(n.cpu(), torch.bincount(use[on].cpu(), minlength=K))
+
+
+def test_two_slabs_of_narrow_rows_cost_little_more_than_one():
+    """4096 nodes of three features fit one slab, of four two: 1.6 times as long a call when a slab left LDS a row a wavefront, 0.8 a lane a cell."""
+    som = pkg.Som(0)
+    m, K, times = 20_000, 4096, []
+    for D in (3, 4):
+        X = torch.ones((m, D), device="cuda")
+        b = (torch.arange(m, device="cuda") % K).int()
+        S, n = torch.empty((K, D), device="cuda", dtype=torch.float64), torch.empty(K, device="cuda", dtype=torch.int64)
+        best = float("inf")
+        for _ in range(8):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(50):
+                som.som_accumulate(X, b, K, S, n)
+            end.record()
+            end.synchronize()
+            best = min(best, start.elapsed_time(end) / 50)
+        times.append(best * 1e3)
+    print(f"three features {times[0]:.1f} us, four {times[1]:.1f}", flush=True)
+    assert times[1] < 1.25 * times[0], times
