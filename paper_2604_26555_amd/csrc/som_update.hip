@@ -90,7 +90,8 @@ __global__ void __launch_bounds__(1024) shift_kernel(const float* __restrict__ G
     }
 }
 
-// exp(x) for x <= 0 (any other x gives some value, NaN gives NaN), to 0.82 units in the last place: x = n ln 2 + r, |r| <= ln 2 / 2, and
+// exp(x) for x <= 0 (any other x gives some value, NaN gives NaN), to less than one unit in the last place (0.949 the largest error of
+// 1.5 * 10^8 arguments against quadruple precision): x = n ln 2 + r, |r| <= ln 2 / 2, and
 // 1 + r + r^2 q(r), q interpolated at ten Chebyshev nodes (error 3e-18).  Without a branch and with its constants in scalar registers: the
 // library's took some sixty instructions and three branches for 24, and branches keep a batch's loads and MFMAs apart.
 // Contraction of K = 4096, D = 50, sixteen million of them: 92 us with the library's, 70 with these.
@@ -169,7 +170,8 @@ __global__ void __launch_bounds__(256, 2) contract_kernel(const float* __restric
         for (int t = 0; t < 4; ++t) acc[q][t] = doublex4{0.0, 0.0, 0.0, 0.0};
     }
     // kBatch k-steps at a time, the next batch's loads under way during the exponentials and MFMAs of the one in hand.  (Twice as many steps
-    // with their loads in front of them: K = 1024, D = 2000 93 us, 79 this way; K = 437, D = 37 5.4 and 4.7; K = 1024, D = 50 9.6 and 10.3.)
+    // with their loads in front of them: K = 1024, D = 2000 93 us, 79 this way; K = 437, D = 37 5.4 and 4.7; K = 1024, D = 50 9.6 and 10.3, the
+    // one size of these that loses, and by less than the others gain: one form for all.)
     constexpr int kBatch = FUSED ? 4 : JT == 4 ? 2 : 4;
     struct Batch {
         float g[FUSED ? JT : 1][kBatch];
