@@ -38,8 +38,10 @@ namespace som {
 
 constexpr int kWavesPerGroup = 4;
 // Form of the split search's rows (D <= 64): whole 16-feature blocks of two bf16 parts; the packed block of four features alone;
-// half-precision and fp6 parts of up to 32 features, and of up to 64.
-enum SplitForm { kFormWhole, kFormTail, kFormHalf1, kFormHalf2 };
+// half-precision and fp6 parts of up to 32 features, and of up to 64.  kFormFew: rows as kFormWhole, four blocks of a map of up to
+// kFewNodes nodes (scores are folded two at a time: bmu_split_tile).
+enum SplitForm { kFormFew = -1, kFormWhole, kFormTail, kFormHalf1, kFormHalf2 };
+constexpr int kFewNodes = 3 * kNodesPerStage;
 constexpr int form_units(int form) { return form < kFormHalf1 ? 0 : form - kFormHalf1 + 1; }
 // Scales of the half-precision parts: a sample's largest element comes to lie in [2^9, 2^10) (but the scale is at most twice the weights'), that
 // of the nodes that the weights' scale is taken from in [2^2, 2^3), which leaves room for nodes 5800 times as far out.
@@ -1183,7 +1185,7 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     constexpr bool TAIL = FORM == kFormTail;
     constexpr int H = form_units(FORM), HA = H > 0 ? H : 1;
     constexpr bool HALF = H > 0;
-    constexpr bool FOUR = HALF || KB < 4;              // scores are folded four at a time, otherwise two (below)
+    constexpr bool FOUR = FORM != kFormFew;            // scores are folded four at a time, otherwise two (below)
     constexpr int RS = split_row_bytes(KB, FORM);
     constexpr int STAGE_F4 = split_stage_f4(KB, FORM);
     constexpr int KBA = KB > 0 ? KB : 1;               // array lengths (no zero-length arrays when D <= 4)
@@ -1544,9 +1546,10 @@ __device__ __forceinline__ void bmu_split_tile(const BmuArgs& a, int64_t first, 
     // max3(best, v1, v2) and, because second <= best, the second largest is max(second, med3(best, v1, v2)), the maximum with two steps'
     // medians at once: nine vector instructions per four scores, plus two per stage and class for the stage number.  (The vector port is as busy as the
     // matrix pipe here: with the class's block number updated per block, two instructions more per block and class, the
-    // kernel took 7 % longer.)  Four whole blocks of two bf16 parts take each two scores' median by itself, ten instructions: they have no register
-    // for one that waits (search four at a time and two: 10^6 x 61 on 200 nodes 128 us and 120, 10^6 x 56 on 50 77 and 71, 300,000 x 64 on 324
-    // 54 and 51, 500,000 x 64 on 400 81.5 and 82.9; 10^6 x 50 on 200 84 and 88, 10^6 x 12 on 600 89 and 95).
+    // kernel took 7 % longer.)  Four whole blocks of two bf16 parts have no register for a median that waits, and what that spills counts where a
+    // tile is short: up to three stages they take each two scores' median by itself, ten instructions (search four at a time and two: 10^6 x 61 on
+    // 200 nodes 128 us and 120, 10^6 x 56 on 50 77 and 71, 300,000 x 64 on 324 54 and 51, 500,000 x 64 on 400 81.5 and 82.9; fewer blocks:
+    // 10^6 x 50 on 200 84 and 88, 10^6 x 12 on 600 89 and 95).
     float mid0 = 0.0f;
     auto fold_step = [&](const floatx16 (&acc)[MS], int step, int st, int nb) {
         // (a class's two steps of four scores behind one another)
@@ -2948,7 +2951,7 @@ int bmu_prepare(som_ctx* ctx, const float* W, int32_t K, int32_t D, int64_t rows
     const bool half = split && nch == 1 && half_parts_pay(K, D, all);
     const int units = half ? (D + 31) / 32 : 0, tail_r = split && nch == 1 && !half && D % 16 >= 1 && D % 16 <= 4 ? D % 16 : 0;
     const int kb = !split || nch > 1 ? 0 : half ? half_norm_group(D) / 4 + 1 : tail_r ? D / 16 : (D + 15) / 16;
-    const int form = units ? kFormHalf1 + units - 1 : tail_r ? kFormTail : kFormWhole;
+    const int form = units ? kFormHalf1 + units - 1 : tail_r ? kFormTail : kb == 4 && K <= kFewNodes ? kFormFew : kFormWhole;
     if (!wide_split) out->form = form;
     // (D > 64: rows in the order of the form that the call takes)
     const size_t stage16_one = (split && nch == 1) ? (size_t)split_stage_f4(kb, form) * 16 : 0;
@@ -3209,6 +3212,7 @@ static int dispatch_split(som_ctx* ctx, int kb, int form, F&& launch)
     SOM_SPLIT_CASE(3, kFormWhole)
     SOM_SPLIT_CASE(3, kFormTail)
     SOM_SPLIT_CASE(4, kFormWhole)
+    SOM_SPLIT_CASE(4, kFormFew)
     SOM_SPLIT_CASE(2, kFormHalf1)
     SOM_SPLIT_CASE(3, kFormHalf1)
     SOM_SPLIT_CASE(3, kFormHalf2)

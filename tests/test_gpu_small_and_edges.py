@@ -499,3 +499,15 @@ def test_neighbourhood_graphs_of_many_nodes_cost_no_more_per_pair(som):
         times.append(best)
     print(f"6000 nodes {times[0]:.2f} ms, 9000 {times[1]:.2f}", flush=True)
     assert times[1] < 5 * times[0], times
+
+
+@pytest.mark.parametrize("K", [33, 128, 129, 300, 384, 385, 513])
+@pytest.mark.parametrize("D", [53, 60, 64])
+def test_four_blocks_of_features_on_both_sides_of_the_short_maps_limit(som, D, K):
+    """Scores folded two at a time (up to 384 nodes) and four at a time, through the search, its pair list and its candidate pass (nodes in
+    pairs a ten-thousandth apart, so that samples are listed)."""
+    m = 500_000_000 // (K * D)
+    X = rows(900 + K + D, m, D)
+    W = rows(901 + K + D, K, D)
+    W[K // 2:2 * (K // 2)] = W[:K // 2] + 1e-4 * np.random.default_rng(K).normal(size=(K // 2, D)).astype(np.float32)
+    check_units(som.som_bmu(dev(X), dev(W))[0].cpu().numpy(), X, W)
