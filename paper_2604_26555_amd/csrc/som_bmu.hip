@@ -510,7 +510,6 @@ __device__ __forceinline__ void split_prep(const float* __restrict__ W, int K, i
             most[wave][0] = k < K ? up : 0.0f;
             most[wave][1] = lo2;
             most[wave][2] = rest2;
-            for (int t = 3; t < kTops; ++t) most[wave][t] = 0.0f;
         }
     }
     __syncthreads();
@@ -520,7 +519,7 @@ __device__ __forceinline__ void split_prep(const float* __restrict__ W, int K, i
     const int f = tid >> 4, q = tid & 15;
     if (f < D) wt[(size_t)f * kpad + k0 + q] = given[q][f];
     if (real) sp.wrow[(size_t)k * D + lane] = w;
-    if (tid < kTops) {
+    if (tid < (HALF ? kTops : 3)) {
         float m = most[0][tid];
         for (int u = 1; u < kPrepNodes; ++u) m = fmaxf(m, most[u][tid]);
         if (m > 0.0f) atomicMax(&tops[tid], __float_as_uint(m));
@@ -2607,7 +2606,7 @@ __device__ __forceinline__ void pair_list(const BmuArgs& a, float4* __restrict__
 template <bool PAIRS>
 __global__ void __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(4))) bmu_exact_kernel(const BmuArgs a)
 {
-    // PAIRS: three rows of each entry of the pair list in hand; otherwise only the slab of the listed samples' features
+    // PAIRS: two differences of each entry of the pair list in hand; otherwise only the slab of the listed samples' features
     extern __shared__ float4 lds4[];
     float4 (*xs4)[kExactGroup / 4] = reinterpret_cast<float4 (*)[kExactGroup / 4]>(lds4);   // [feature within a 64-wide slab][sample]
     constexpr int kWaves = kExactThreads / 64;
