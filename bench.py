@@ -307,7 +307,7 @@ def main() -> int:
                 "note": "achieved = algorithmic 2 m K D float32 flops per launch; issued = the MFMA flops the kernel "
                         "executes for them (mfma_per_block instructions per 32 nodes x 32 samples, K padded to 32, each counted as one of "
                         "32 x 32 x 16, whose cycles it takes); "
-                        "under the search for up to 64 features the chip holds its power limit at a shader clock of about 1.9 GHz, the peak assumes 2.4"}
+                        "under the search for up to 64 features the chip holds its power limit at a shader clock of about 2.0 GHz, the peak assumes 2.4"}
     else:
         roof = {"bound": "mfma", "kernel": "bmu_kernel (fused float32 score contraction + arg-max)",
                 "achieved": achieved, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",

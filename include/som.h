@@ -240,11 +240,15 @@ int som_set_reproducible(som_ctx* ctx, int on);
 /*
  * Which matrix pipe forms the scores of the best-matching-unit search (Section 3.3.1: b(x); not an operation of
  * the paper).  The results are the same either way: every sample whose best two scores lie inside the worst-case
- * rounding bound of the arithmetic in use is re-decided by direct float32 differences.
+ * rounding bound of the arithmetic in use is re-decided by direct float32 differences.  One exception: where those differences
+ * cannot tell nodes apart (samples some 300 times as far out as the nodes lie from one another), a sample that is re-decided may get
+ * another of them than its scores would give it, and which samples are re-decided goes by the arithmetic, which in the default search goes by
+ * the rows of the call; all rows of an epoch, resident or in chunks of any length, take the same.
  *   SOM_SEARCH_AUTO (default)  for D >= 4 and K > 1 the samples and weights are cut into two bf16 parts each
  *                              and a score is the sum of three bf16 MFMA products (worst-case error of a
- *                              difference of two scores: below 2^-14 of |x||w| + |w|^2/2), or, in large calls of more
- *                              than 20 features, into a half-precision part and the rest, with fp6 cross products; for D > 64 the call keeps 68 to
+ *                              difference of two scores: below 2^-14 of |x||w| + |w|^2/2), or, for D > 64 and in large calls of more
+ *                              than 20 features, into a half-precision part and the rest, with fp6 cross products (below
+ *                              2^-11); for D > 64 the call keeps 68 to
  *                              368 bytes per sample of a pass of 2^24 rows; other shapes use the float32 MFMA search.
  *                              Small calls form no scores: a look-up (som_bmu with D <= 64, up to about m K D = 4e8) takes
  *                              direct differences over all nodes in one kernel, and a small epoch (no statistics,

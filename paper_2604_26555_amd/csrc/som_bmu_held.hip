@@ -21,8 +21,8 @@
 // run.  With 64 samples a wavefront and one workgroup a unit LDS is read half as often, but nothing runs beside that: 10^6 x 200 on
 // 1024 nodes 852 us, 766 this way (1015 with the compiler's copies between the halves of the register file, 1600 by the 256 x 256
 // tiles of som_bmu_wide.hip, which cut every sample once for each 256 nodes).
-// What bounds it is the power limit: at 4096 nodes the clock is at 1.55 to 1.7 GHz with the matrix pipes busy 0.55 to 0.59 of the time;
-// without the fold the loop takes 9 % less, without its LDS reads 2 %.
+// What bounds it: the power limit (at 4096 nodes the clock is at 1.55 to 1.7 GHz with the matrix pipes busy 0.55 to 0.59 of the time; at 1024 1.6 GHz
+// and 0.48), and waits: at 1024 nodes neither pipe works in a third of the cycles.  Without the fold the loop takes 9 % less, without its LDS reads 2 %.
 #include "som_bmu_common.hpp"
 #include "som_bmu_wide.hpp"
 
@@ -165,7 +165,7 @@ __global__ void __launch_bounds__(256) bmu_held_prep_kernel(const float* __restr
 }
 
 // H: units of 32 features; SHORT: the last one has sixteen at most, so that its other sixteen need no MFMA of first parts (10^6 x 200 on 1024
-// nodes, one of 21: 853 -> 842 us; zeros draw little power, which is what bounds the rest)
+// nodes, one of 21: 853 -> 842 us; zeros draw little power, and the clock is at the power limit)
 template <int H, bool SHORT>
 struct HeldArgs {
     // [block of 32 rows][unit][first parts of 16 features | of the other 16 | fp6, 16 of a lane's 24 bytes], then [unit][fp6, the other 8]: in the

@@ -2,8 +2,9 @@
 presented in pieces small enough for the two bf16 parts.
 
 Either way a sample whose best two scores lie inside the rounding bound is decided by direct float32 differences, features in order, so the
-units are the same, bit for bit; a bound that is too small shows as a difference.  (Samples a hundred times as far out as the nodes lie from one
-another are told apart by the scores better than by those differences: there the wider of two bounds may show.)  Against float64, a float32 sum of
+units are the same, bit for bit; a bound that is too small shows as a difference.  (Samples some hundred times as far out as the nodes lie from one
+another are told apart by the scores better than by those differences: there the wider of two bounds may show, the one exception that
+include/som.h names.)  Against float64, a float32 sum of
 D squared differences is off by at most (D + 2) * 2^-24 of itself, so a unit may only miss the nearest node where the two distances are closer
 than twice that.
 """
